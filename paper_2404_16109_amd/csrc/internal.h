@@ -78,6 +78,18 @@ int eq_table_run(uint32_t* dst, size_t stride, const host::F* u, int nvars, hipS
 // ---- multilinear evaluation ---------------------------------------------------
 // a~(point) into out_words[0, 8) (Montgomery); a is not modified.
 size_t mle_scratch_bytes(int nvars);
+// Up to kMleMaxJobs evaluations at up to two points in the same launches; job q's
+// value goes to its out_words (eight Montgomery words in device-visible memory).
+static const int kMleMaxJobs = 5;
+struct MleJob {
+    const uint32_t* a;
+    size_t stride;
+    int nvars;
+    const host::F* point;  // jobs with the same pointer and length share their constants
+    uint32_t* out_words;
+};
+size_t mle_scratch_bytes_many(const int* nvars, int njobs);
+int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint32_t seq, hipStream_t stream);
 int mle_eval_run(const uint32_t* a, size_t stride, int nvars, const host::F* point, Carver& cv, Mailbox* mb,
                  uint32_t seq, hipStream_t stream);
 
@@ -86,10 +98,6 @@ void launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t stream);
 
 // Copies the leading `n` elements of a limb-major vector.
 void launch_copy(uint32_t* dst, size_t ds, const uint32_t* src, size_t ss, size_t n, hipStream_t stream);
-
-// One folding pass: dst_p = src_p + r (src_{p+half} - src_p), p < half.
-void launch_fold(uint32_t* dst, size_t ds, const uint32_t* src, size_t ss, size_t half, const host::F& r,
-                 hipStream_t stream);
 
 // ---- product sumcheck rounds (shared by sumcheck_prove_product and matmul) ----
 // Runs d rounds over a, b (2^d elements each, folded in place), writing 3 values

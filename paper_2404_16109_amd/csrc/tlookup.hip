@@ -1522,10 +1522,13 @@ static size_t verify_ws_bytes(size_t D, size_t N) {
     Carver cv(nullptr, 0);
     cv.limbs(N);                                   // m as field elements
     cv.take(div_up(N, kLeafCounts) * 32);          // leaf digests
-    cv.take(vec_digest_leaves(D) * 32);            // hash tree over a witness vector
+    cv.take((vec_digest_leaves(D) + vec_digest_leaves(N)) * 32);  // hash trees over the witness vectors A and B
     cv.take(vec_digest_row_digests(D) * 32);
-    cv.take(256);                                  // its ticket
-    cv.take(mle_scratch_bytes(log2_floor(D)));
+    cv.take(vec_digest_row_digests(N) * 32);
+    cv.take(256);                                  // their ticket
+    const int n = log2_floor(D), l = log2_floor(N);
+    const int nvars[kMleMaxJobs] = {l, n, n, l, l};
+    cv.take(mle_scratch_bytes_many(nvars, kMleMaxJobs));
     return cv.used();
 }
 
@@ -1663,32 +1666,10 @@ static int verify_core(const VerifyCall& c) {
     Carver cv(c.ws, c.ws_bytes);
     uint32_t* Mfr = cv.limbs(N_max);
     uint32_t* leaves = (uint32_t*)cv.take(div_up(N_max, kLeafCounts) * 32);
-    uint32_t* dig_leaves = (uint32_t*)cv.take(vec_digest_leaves(D_max) * 32);
+    uint32_t* dig_leaves = (uint32_t*)cv.take((vec_digest_leaves(D_max) + vec_digest_leaves(N_max)) * 32);
     uint32_t* dig_rows = (uint32_t*)cv.take(vec_digest_row_digests(D_max) * 32);
+    uint32_t* dig_rows_b = (uint32_t*)cv.take(vec_digest_row_digests(N_max) * 32);
     uint32_t* dig_ticket = (uint32_t*)cv.take(256);
-    // a witness vector must be the one whose digest the proof carries
-    auto check_digest = [&](const fr_vec& vec, size_t count, const uint8_t* want, int* ok) -> int {
-        const uint32_t seq = mb->next_seq();
-        const VecDigestJob job{vec.limbs, vec.stride, count, dig_rows, mb->words + kMailboxDigest};
-        launch_fill_u32(dig_ticket, 1, 0u, stream);
-        vec_digest_launch(job, nullptr, dig_leaves, mb->words, seq, dig_ticket, stream);
-        ZK_HIP_TRY(hipGetLastError());
-        ZK_TRY(mailbox_wait(mb, seq, stream));
-        ZK_HIP_TRY(hipStreamSynchronize(stream));
-        uint8_t got[32];
-        digest_bytes(got, mb->words + kMailboxDigest);
-        *ok = memcmp(got, want, 32) == 0 ? 1 : 0;
-        return ZK_OK;
-    };
-    auto check = [&](const uint32_t* a, size_t stride, int nv, const F* pt, const F& want, int* ok) -> int {
-        Carver scratch = cv;
-        uint32_t seq = mb->next_seq();
-        ZK_TRY(mle_eval_run(a, stride, nv, pt, scratch, mb, seq, stream));
-        ZK_TRY(mailbox_wait(mb, seq, stream));
-        ZK_HIP_TRY(hipStreamSynchronize(stream));
-        *ok = equal(from_dev(mb->words), want) ? 1 : 0;
-        return ZK_OK;
-    };
     for (size_t i = 0; i < K; ++i) {
         const F* f = fin + 5 * i;
         const size_t D = Ds[i], N = Ns[i];
@@ -1696,38 +1677,62 @@ static int verify_core(const VerifyCall& c) {
         const F* vd = v + skips[i];          // the instance's point
         const F* vt = vd + hs[i];            // its table's
         const uint32_t nleaves = (uint32_t)div_up(N, kLeafCounts);
-        int ok = 0;
-        ZK_TRY(check(c.T[i].limbs, c.T[i].stride, l, vt, f[4], &ok));
-        if (!ok) return ZK_E_REJECT;
-        if (!c.wit) continue;
-        const tlookup_witness* wit = c.wit + i;
-        if (wit->S.limbs) {
-            if (!vec_ok(wit->S, D)) return ZK_E_BADARG;
-            ZK_TRY(check(wit->S.limbs, wit->S.stride, ni, vd, f[1], &ok));
-            if (!ok) return ZK_E_REJECT;
+        const tlookup_witness* wit = c.wit ? c.wit + i : nullptr;
+        const bool have_s = wit && wit->S.limbs && vec_ok(wit->S, D), have_a = wit && wit->A.limbs && vec_ok(wit->A, D),
+                   have_b = wit && wit->B.limbs && vec_ok(wit->B, N), have_m = wit && wit->m;
+        // Everything of the instance is enqueued before anything is waited for: the hash trees of A and B in the same
+        // launches, the values of all tensors in the same launches.
+        launch_fill_u32(dig_ticket, 1, 0u, stream);
+        if (have_a || have_b) {
+            const VecDigestJob ja{wit->A.limbs, wit->A.stride, D, dig_rows, mb->words + kMailboxDigest},
+                jb{wit->B.limbs, wit->B.stride, N, dig_rows_b, mb->words + kMailboxDigest + 8};
+            if (have_a) vec_digest_launch(ja, have_b ? &jb : nullptr, dig_leaves, mb->words, 0, dig_ticket, stream);
+            else vec_digest_launch(jb, nullptr, dig_leaves, mb->words, 0, dig_ticket, stream);
         }
-        if (wit->A.limbs) {
-            if (!vec_ok(wit->A, D)) return ZK_E_BADARG;
-            ZK_TRY(check(wit->A.limbs, wit->A.stride, ni, vd, f[0], &ok));
-            if (!ok) return ZK_E_REJECT;
-            ZK_TRY(check_digest(wit->A, D, ab_digests + 64 * i, &ok));
-            if (!ok) return ZK_E_REJECT;
-        }
-        if (wit->B.limbs) {
-            if (!vec_ok(wit->B, N)) return ZK_E_BADARG;
-            ZK_TRY(check(wit->B.limbs, wit->B.stride, l, vt, f[2], &ok));
-            if (!ok) return ZK_E_REJECT;
-            ZK_TRY(check_digest(wit->B, N, ab_digests + 64 * i + 32, &ok));
-            if (!ok) return ZK_E_REJECT;
-        }
-        if (wit->m) {
+        MleJob jobs[kMleMaxJobs];
+        int njobs = 0;
+        auto add_job = [&](const uint32_t* a, size_t stride, int nv, const F* pt) {
+            jobs[njobs] = MleJob{a, stride, nv, pt, mb->words + 8 * njobs};
+            return njobs++;
+        };
+        const int job_t = add_job(c.T[i].limbs, c.T[i].stride, l, vt);
+        const int job_s = have_s ? add_job(wit->S.limbs, wit->S.stride, ni, vd) : -1;
+        const int job_a = have_a ? add_job(wit->A.limbs, wit->A.stride, ni, vd) : -1;
+        const int job_b = have_b ? add_job(wit->B.limbs, wit->B.stride, l, vt) : -1;
+        int job_m = -1;
+        if (have_m) {
             hipLaunchKernelGGL(k_counts_to_fr, dim3(grid_for(N)), dim3(kBlock), 0, stream, Mfr, N, wit->m, N);
             hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(nleaves, 64)), dim3(64), 0, stream, leaves, wit->m,
                                (uint32_t)N, nleaves);
             ZK_TRY(mailbox_bulk(mb, (size_t)nleaves * 32));
             ZK_HIP_TRY(hipMemcpyAsync(mb->bulk, leaves, (size_t)nleaves * 32, hipMemcpyDeviceToHost, stream));
-            ZK_TRY(check(Mfr, N, l, vt, f[3], &ok));
-            if (!ok) return ZK_E_REJECT;
+            job_m = add_job(Mfr, N, l, vt);
+        }
+        {
+            Carver scratch = cv;
+            const uint32_t seq = mb->next_seq();
+            ZK_TRY(mle_eval_launch(jobs, njobs, scratch, mb, seq, stream));
+            ZK_TRY(mailbox_wait(mb, seq, stream));
+            ZK_HIP_TRY(hipStreamSynchronize(stream));
+        }
+        auto value_is = [&](int job, const F& want) { return equal(from_dev(mb->words + 8 * job), want); };
+        auto digest_is = [&](const uint32_t* words, const uint8_t* want) {
+            uint8_t got[32];
+            digest_bytes(got, words);
+            return memcmp(got, want, 32) == 0;
+        };
+        if (!value_is(job_t, f[4])) return ZK_E_REJECT;
+        if (!wit) continue;
+        if (wit->S.limbs && !have_s) return ZK_E_BADARG;
+        if (have_s && !value_is(job_s, f[1])) return ZK_E_REJECT;
+        if (wit->A.limbs && !have_a) return ZK_E_BADARG;
+        // a witness vector must also be the one whose digest the proof carries
+        if (have_a && (!value_is(job_a, f[0]) || !digest_is(mb->words + kMailboxDigest, ab_digests + 64 * i))) return ZK_E_REJECT;
+        if (wit->B.limbs && !have_b) return ZK_E_BADARG;
+        if (have_b && (!value_is(job_b, f[2]) || !digest_is(mb->words + kMailboxDigest + 8, ab_digests + 64 * i + 32)))
+            return ZK_E_REJECT;
+        if (have_m) {
+            if (!value_is(job_m, f[3])) return ZK_E_REJECT;
             uint8_t md[32];
             digest_of_leaves(md, mb->bulk, nleaves);
             if (memcmp(md, digests + 32 * i, 32) != 0) return ZK_E_REJECT;
