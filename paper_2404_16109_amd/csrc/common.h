@@ -139,10 +139,14 @@ static const size_t kMailboxMaxInstances = 8;
 static const size_t kMailboxInvB = 1024;    // grand total of the table-side inversion (+16 per instance)
 static const size_t kMailboxInvA = 1032;    // grand total of the data-side inversion (+16 per instance)
 static const size_t kMailboxTableC = 1280;  // the two table-side constants (+16 per instance)
-static const size_t kMailboxDigest = 1536;  // digests of A and B, eight hash-state words each (+16 per instance)
+
+// The staging buffer (Mailbox::bulk) starts with the rows of digests the host
+// finishes hash trees from (sixteen vectors, 256 digests each); what other copies
+// need follows.
+static const size_t kBulkDigests = 16 * 256 * 32;
 
 int mailbox_get(Mailbox** out);
-int mailbox_bulk(Mailbox* mb, size_t bytes);
+int mailbox_bulk(Mailbox* mb, size_t bytes);  // room for `bytes` at bulk + kBulkDigests
 // Waits until the flag shows `seq` (spinning, then falling back to
 // synchronising the stream).
 int mailbox_wait(Mailbox* mb, uint32_t seq, hipStream_t stream);

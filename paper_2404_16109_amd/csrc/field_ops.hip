@@ -66,6 +66,7 @@ int mailbox_wait(Mailbox* mb, uint32_t seq, hipStream_t stream) {
 }
 
 int mailbox_bulk(Mailbox* mb, size_t bytes) {
+    bytes += kBulkDigests;
     if (mb->bulk_bytes >= bytes) return ZK_OK;
     if (mb->bulk) (void)hipHostFree(mb->bulk);
     mb->bulk = nullptr;

@@ -348,18 +348,14 @@ static uint32_t mle_table_entries(int nvars) {
     return total;
 }
 
+// Room for jobs of at most these lengths at (at most) two points, whose lengths are
+// at most those of jobs 0 and njobs - 1.  Monotonic in the lengths: a stage is counted
+// with all its 64 constants.
 size_t mle_scratch_bytes_many(const int* nvars, int njobs) {
     Carver cv(nullptr, 0);
-    int distinct[kMleMaxJobs], nd = 0;
-    for (int q = 0; q < njobs; ++q) {
-        bool seen = false;
-        for (int d = 0; d < nd; ++d) seen = seen || distinct[d] == nvars[q];
-        if (!seen) distinct[nd++] = nvars[q];
-        cv.limbs(mle_outputs(nvars[q]));
-    }
-    uint32_t entries = 0;
-    for (int d = 0; d < nd; ++d) entries += mle_table_entries(distinct[d]);
-    cv.take((size_t)entries * kToepBytes);
+    for (int q = 0; q < njobs; ++q) cv.limbs(mle_outputs(nvars[q]));
+    const int stages = mle_stage_count(nvars[0]) + (njobs > 1 ? mle_stage_count(nvars[njobs - 1]) : 0);
+    cv.take((size_t)stages * (kToepBytes << kMleStageVars));
     cv.take(256);
     return cv.used();
 }

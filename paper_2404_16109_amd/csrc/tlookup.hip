@@ -173,7 +173,6 @@ struct ProveWs {
     SmallFold4* fold4;  // constants of the first fold when S comes as small integers (tlookup_prove_small)
     uint32_t* leaves;   // nleaves * 8 words
     uint32_t nleaves;
-    uint32_t* dig_leaves;  // leaf digests of the hash trees over A and B
     uint32_t* dig_rows;    // the shorter rows of A's tree above kTreeChunk leaves
     uint32_t* dig_rows_b;  // the same for B
     size_t part_blocks; // capacity of the two partial-sum buffers, in workgroups
@@ -200,75 +199,104 @@ static size_t vec_digest_row_digests(size_t n) {
     return first ? 2 * first : 1;
 }
 
-// Enqueues the hash trees over one or two vectors (n elements each, powers of two;
-// v2 may be null); a digest's eight state words go to its out_words (device
-// memory or the mailbox `words`, in which case seq != 0 publishes completion of
-// the whole call; `ticket`: one zeroed word of device memory, left zero).
-// leaves: room for vec_digest_leaves(n1) + vec_digest_leaves(n2) digests;
-// rows1, rows2: vec_digest_row_digests(n) digests each.
+// Enqueues the hash trees over up to kDigestMaxJobs vectors (n elements each, powers
+// of two): their last rows (at most kTreeHostRow digests) go to pinned host memory,
+// and the last launch publishes `seq` if it is not zero (`ticket`: one zeroed word of
+// device memory, left zero).  The host then finishes each tree (vec_digest_finish).
+// leaves: room for the sum of vec_digest_leaves(n); rows: vec_digest_row_digests(n)
+// digests each.
 struct VecDigestJob {
     const uint32_t* v;
     size_t stride, n;
     uint32_t* rows;
-    uint32_t* out_words;
+    const uint32_t* host_row;  // set by the launch: the row handed to the host
+    uint32_t host_count;
 };
 
-static void vec_digest_launch(const VecDigestJob& one, const VecDigestJob* two, uint32_t* leaves, uint32_t* words,
-                              uint32_t seq, uint32_t* ticket, hipStream_t stream) {
-    const VecDigestJob* jobs[2] = {&one, two};
-    const int njobs = two ? 2 : 1;
-    // the shorter vector's leaves first: its few long chains start at once
-    const int order[2] = {njobs == 2 && two->n < one.n ? 1 : 0, njobs == 2 && two->n < one.n ? 0 : 1};
-    VecLeavesJob lv[2];
-    const uint32_t* in[2];
-    size_t cnt[2];
-    uint32_t* rows[2];
+static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Mailbox* mb, uint32_t seq, uint32_t* ticket,
+                             hipStream_t stream) {
+    if (njobs < 1 || njobs > kDigestMaxJobs) return ZK_E_BADARG;
+    ZK_TRY(mailbox_bulk(mb, 0));
+    VecLeavesArgs lv;
+    memset(&lv, 0, sizeof lv);
+    lv.njobs = njobs;
+    lv.words = mb->words;
+    lv.ticket = ticket;
+    const uint32_t* in[kDigestMaxJobs];
+    size_t cnt[kDigestMaxJobs];
+    uint32_t* rows[kDigestMaxJobs];
     size_t total = 0;
-    for (int q = 0; q < 2; ++q) {
-        lv[q] = VecLeavesJob{nullptr, 0, 0, 0, nullptr};
-        if (q >= njobs) continue;
-        const VecDigestJob& j = *jobs[order[q]];
-        lv[q] = VecLeavesJob{j.v, j.stride, j.n, vec_digest_leaves(j.n), leaves + total * 8};
-        in[q] = lv[q].out;
-        cnt[q] = lv[q].L;
+    uint32_t blocks = 0;
+    bool more = false;
+    for (int q = 0; q < njobs; ++q) {
+        VecDigestJob& j = jobs[q];
+        cnt[q] = vec_digest_leaves(j.n);
         rows[q] = j.rows;
-        total += lv[q].L;
+        uint32_t* host_row = (uint32_t*)mb->bulk + (size_t)q * kTreeHostRow * 8;
+        j.host_row = host_row;
+        uint32_t* out = cnt[q] <= kTreeHostRow ? host_row : leaves + total * 8;
+        if (cnt[q] > kTreeHostRow) {
+            total += cnt[q];
+            more = true;
+        }
+        lv.job[q] = VecLeavesJob{j.v, j.stride, j.n, cnt[q], out, blocks};
+        in[q] = out;
+        blocks += (uint32_t)div_up(cnt[q], 64);
     }
-    hipLaunchKernelGGL(k_vec_leaves, dim3(grid_for(total)), dim3(kBlock), 0, stream, lv[0], lv[1]);
-    // up the trees, both rows in one launch, a factor of up to kTreeChunk per launch
-    bool done[2] = {false, njobs < 2};
-    while (!done[0] || !done[1]) {
-        DigestTreeJob tj[2];
-        bool finishing = true;
-        for (int q = 0; q < 2; ++q) {
-            tj[q] = DigestTreeJob{nullptr, nullptr, 0, 0};
-            if (done[q]) continue;
-            const size_t chunk = cnt[q] > kTreeChunk ? kTreeChunk : cnt[q];
-            const size_t blocks = cnt[q] / chunk;
-            uint32_t* out = blocks == 1 ? jobs[order[q]]->out_words : rows[q];
-            tj[q] = DigestTreeJob{in[q], out, (uint32_t)chunk, (uint32_t)blocks};
+    lv.seq = more ? 0 : seq;
+    lv.groups = blocks;
+    // the pair of wavefronts per 64 leaves pays while the wavefronts do not outnumber the SIMDs (see the kernel)
+    if (blocks <= kPipedLeafGroups) hipLaunchKernelGGL(k_vec_leaves_piped, dim3((blocks + 1) / 2), dim3(256), 0, stream, lv);
+    else hipLaunchKernelGGL(k_vec_leaves, dim3(blocks), dim3(64), 0, stream, lv);
+    // up the trees, all rows in one launch, a factor of up to kTreeChunk per launch
+    while (more) {
+        DigestTreeArgs tr;
+        memset(&tr, 0, sizeof tr);
+        tr.words = mb->words;
+        tr.ticket = ticket;
+        blocks = 0;
+        more = false;
+        for (int q = 0; q < njobs; ++q) {
+            if (cnt[q] <= kTreeHostRow) continue;
+            uint32_t chunk = 4;
+            while (chunk < kTreeChunk && cnt[q] / chunk > kTreeHostRow) chunk *= 4;
+            cnt[q] /= chunk;
+            uint32_t* out = cnt[q] <= kTreeHostRow ? const_cast<uint32_t*>(jobs[q].host_row) : rows[q];
+            tr.job[tr.njobs++] = DigestTreeJob{in[q], out, chunk, blocks};
             in[q] = out;
-            cnt[q] = blocks;
-            if (blocks == 1) done[q] = true;
-            else {
-                rows[q] += blocks * 8;
-                finishing = false;
+            blocks += (uint32_t)cnt[q];
+            if (cnt[q] > kTreeHostRow) {
+                rows[q] += cnt[q] * 8;
+                more = true;
             }
         }
-        hipLaunchKernelGGL(k_digest_tree, dim3(tj[0].blocks + tj[1].blocks), dim3(kBlock), 0, stream, tj[0], tj[1], words,
-                           finishing ? seq : 0u, ticket);
+        tr.seq = more ? 0 : seq;
+        hipLaunchKernelGGL(k_digest_tree, dim3(blocks), dim3(kBlock), 0, stream, tr);
     }
+    for (int q = 0; q < njobs; ++q) jobs[q].host_count = (uint32_t)cnt[q];
+    ZK_HIP_TRY(hipGetLastError());
+    return ZK_OK;
 }
 
-// Hash-state words -> the digest's bytes.
-static void digest_bytes(uint8_t out[32], const uint32_t* state_words) {
-    for (int k = 0; k < 8; ++k) {
-        const uint32_t v = state_words[k];
-        out[4 * k] = (uint8_t)(v >> 24);
-        out[4 * k + 1] = (uint8_t)(v >> 16);
-        out[4 * k + 2] = (uint8_t)(v >> 8);
-        out[4 * k + 3] = (uint8_t)v;
+// The rest of a tree, from the row the device has handed over: consecutive fours
+// (a last pair in twos) down to one digest.
+static void vec_digest_finish(uint8_t out[32], const VecDigestJob& job) {
+    uint8_t row[kTreeHostRow * 32];
+    uint32_t cnt = job.host_count;
+    for (uint32_t i = 0; i < cnt * 8; ++i) {
+        const uint32_t v = __builtin_bswap32(job.host_row[i]);  // hash-state words: big-endian words of the digest's bytes
+        memcpy(row + 4 * i, &v, 4);
     }
+    while (cnt >= 4) {
+        cnt /= 4;
+        host::Sha256::hash_fours(row, row, cnt);
+    }
+    if (cnt == 2) {
+        host::Sha256 h;
+        h.update(row, 64);
+        h.finish(row);
+    }
+    memcpy(out, row, 32);
 }
 
 static uint32_t hash_capacity(size_t N) {
@@ -298,13 +326,19 @@ static int carve_prove(ProveWs& w, Carver& cv, size_t D, size_t N) {
     w.fold4 = (SmallFold4*)cv.take(sizeof(SmallFold4));
     w.nleaves = (uint32_t)div_up(N, kLeafCounts);
     w.leaves = (uint32_t*)cv.take((size_t)w.nleaves * 32);
-    w.dig_leaves = (uint32_t*)cv.take((vec_digest_leaves(D) + vec_digest_leaves(N)) * 32);
     w.dig_rows = (uint32_t*)cv.take(vec_digest_row_digests(D) * 32);
     w.dig_rows_b = (uint32_t*)cv.take(vec_digest_row_digests(N) * 32);
     w.part_blocks = round_blocks_max(D);
     w.partD = cv.limbs(w.part_blocks * 5);
     w.partT = cv.limbs(w.part_blocks * 6);
     return ZK_OK;
+}
+
+// Leaf digests of the hash trees over the K instances' A and B.
+static size_t dig_leaves_bytes(const size_t* D, const size_t* N, size_t K) {
+    size_t total = 0;
+    for (size_t i = 0; i < K; ++i) total += vec_digest_leaves(D[i]) + vec_digest_leaves(N[i]);
+    return total * 32;
 }
 
 // K instances: their buffers, one pool of weight tables per distinct length of
@@ -316,6 +350,7 @@ static size_t prove_ws_bytes_shapes(const size_t* D, const size_t* N, size_t K) 
         ProveWs w;
         carve_prove(w, cv, D[i], N[i]);
     }
+    cv.take(dig_leaves_bytes(D, N, K));
     for (size_t i = 0; i < K; ++i) {
         bool seen = false;
         for (size_t j = 0; j < i; ++j) seen = seen || D[j] == D[i];
@@ -393,11 +428,12 @@ static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_
     if (counts_as_fr) hipLaunchKernelGGL(k_counts_to_fr, dim3(grid_for(N)), dim3(kBlock), 0, stream, w.M, N, w.m, N);
     ZK_HIP_TRY(hipGetLastError());
     ZK_TRY(mailbox_bulk(mb, (size_t)w.nleaves * 32 + 16));
-    ZK_HIP_TRY(hipMemcpyAsync(mb->bulk, w.flags, 16, hipMemcpyDeviceToHost, stream));
-    ZK_HIP_TRY(hipMemcpyAsync(mb->bulk + 16, w.leaves, (size_t)w.nleaves * 32, hipMemcpyDeviceToHost, stream));
+    uint8_t* staged = mb->bulk + kBulkDigests;
+    ZK_HIP_TRY(hipMemcpyAsync(staged, w.flags, 16, hipMemcpyDeviceToHost, stream));
+    ZK_HIP_TRY(hipMemcpyAsync(staged + 16, w.leaves, (size_t)w.nleaves * 32, hipMemcpyDeviceToHost, stream));
     ZK_HIP_TRY(hipStreamSynchronize(stream));
     uint64_t bad;
-    memcpy(&bad, mb->bulk + 8, 8);
+    memcpy(&bad, staged + 8, 8);
     if (bad != UINT64_MAX) {
         if (bad_index) *bad_index = bad;
         return ZK_E_NOT_IN_TABLE;
@@ -462,7 +498,6 @@ struct Instance {
     uint32_t* words = nullptr;  // this instance's round sums in the mailbox
     uint32_t* inv_words = nullptr;    // totals of its two inversions (B, then A)
     uint32_t* const_words = nullptr;  // its two table-side constants
-    uint32_t* dig_words = nullptr;    // hash-state words of digest(A), then of digest(B)
     host::F c1, c2, cB, sum_A, lam;
     host::F claim;       // the running claim of this instance's own sumcheck: f_i's round polynomial at 0 plus at 1
     host::F fX[4];       // its last round polynomial at X = 0..3
@@ -738,13 +773,13 @@ static int prove_core(const ProveCall& c) {
         I.words = mb->words + kMailboxSlot * i;
         I.inv_words = mb->words + kMailboxInvB + 16 * i;
         I.const_words = mb->words + kMailboxTableC + 16 * i;
-        I.dig_words = mb->words + kMailboxDigest + 16 * i;
         I.c1 = I.c2 = I.cB = I.sum_A = zero();
         I.cD = I.cT = I.half_pow = one();
         I.inv_den = zero();
         I.scale = one();
         for (int t = 0; t < I.h; ++t) I.scale = mul(I.scale, inv2);
     }
+    uint32_t* dig_leaves = (uint32_t*)cv.take(dig_leaves_bytes(Ds, Ns, K));
     if (cv.overflow()) return ZK_E_BUFSZ;
 
     ProfileScope prof_total(kProfTotal, stream);
@@ -772,7 +807,7 @@ static int prove_core(const ProveCall& c) {
             }
         }
         ZK_TRY(rc);
-        digest_of_leaves(inst[i].md, mb->bulk + 16, inst[i].w.nleaves);
+        digest_of_leaves(inst[i].md, mb->bulk + kBulkDigests + 16, inst[i].w.nleaves);
     }
 
     uint64_t dims[1 + 2 * kMailboxMaxInstances];
@@ -865,16 +900,17 @@ static int prove_core(const ProveCall& c) {
     {
         ProfileScope prof(kProfDigest, stream);
         const uint32_t seq = mb->next_seq();
+        VecDigestJob jobs[2 * kMailboxMaxInstances];
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
-            const VecDigestJob ja{I.w.A, I.D, I.D, I.w.dig_rows, I.dig_words}, jb{I.w.B, I.N, I.N, I.w.dig_rows_b, I.dig_words + 8};
-            vec_digest_launch(ja, &jb, I.w.dig_leaves, mb->words, i + 1 == K ? seq : 0, I.w.flags + 1, stream);
+            jobs[2 * i] = VecDigestJob{I.w.A, I.D, I.D, I.w.dig_rows, nullptr, 0};
+            jobs[2 * i + 1] = VecDigestJob{I.w.B, I.N, I.N, I.w.dig_rows_b, nullptr, 0};
         }
-        ZK_HIP_TRY(hipGetLastError());
+        ZK_TRY(vec_digest_launch(jobs, 2 * (int)K, dig_leaves, mb, seq, inst[0].w.flags + 1, stream));
         ZK_TRY(mailbox_wait(mb, seq, stream));
         for (size_t i = 0; i < K; ++i) {
-            digest_bytes(inst[i].dA, inst[i].dig_words);
-            digest_bytes(inst[i].dB, inst[i].dig_words + 8);
+            vec_digest_finish(inst[i].dA, jobs[2 * i]);
+            vec_digest_finish(inst[i].dB, jobs[2 * i + 1]);
             tr.absorb("A", inst[i].dA, 32);
             tr.absorb("B", inst[i].dB, 32);
         }
@@ -1527,7 +1563,7 @@ static size_t verify_ws_bytes(size_t D, size_t N) {
     cv.take(vec_digest_row_digests(N) * 32);
     cv.take(256);                                  // their ticket
     const int n = log2_floor(D), l = log2_floor(N);
-    const int nvars[kMleMaxJobs] = {l, n, n, l, l};
+    const int nvars[kMleMaxJobs] = {n, n, l, l, l};
     cv.take(mle_scratch_bytes_many(nvars, kMleMaxJobs));
     return cv.used();
 }
@@ -1683,12 +1719,12 @@ static int verify_core(const VerifyCall& c) {
         // Everything of the instance is enqueued before anything is waited for: the hash trees of A and B in the same
         // launches, the values of all tensors in the same launches.
         launch_fill_u32(dig_ticket, 1, 0u, stream);
-        if (have_a || have_b) {
-            const VecDigestJob ja{wit->A.limbs, wit->A.stride, D, dig_rows, mb->words + kMailboxDigest},
-                jb{wit->B.limbs, wit->B.stride, N, dig_rows_b, mb->words + kMailboxDigest + 8};
-            if (have_a) vec_digest_launch(ja, have_b ? &jb : nullptr, dig_leaves, mb->words, 0, dig_ticket, stream);
-            else vec_digest_launch(jb, nullptr, dig_leaves, mb->words, 0, dig_ticket, stream);
-        }
+        ZK_TRY(mailbox_bulk(mb, (size_t)nleaves * 32));  // before anything is on its way there
+        VecDigestJob trees[2];
+        int ntrees = 0;
+        if (have_a) trees[ntrees++] = VecDigestJob{wit->A.limbs, wit->A.stride, D, dig_rows, nullptr, 0};
+        if (have_b) trees[ntrees++] = VecDigestJob{wit->B.limbs, wit->B.stride, N, dig_rows_b, nullptr, 0};
+        if (ntrees) ZK_TRY(vec_digest_launch(trees, ntrees, dig_leaves, mb, 0, dig_ticket, stream));
         MleJob jobs[kMleMaxJobs];
         int njobs = 0;
         auto add_job = [&](const uint32_t* a, size_t stride, int nv, const F* pt) {
@@ -1704,8 +1740,7 @@ static int verify_core(const VerifyCall& c) {
             hipLaunchKernelGGL(k_counts_to_fr, dim3(grid_for(N)), dim3(kBlock), 0, stream, Mfr, N, wit->m, N);
             hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(nleaves, 64)), dim3(64), 0, stream, leaves, wit->m,
                                (uint32_t)N, nleaves);
-            ZK_TRY(mailbox_bulk(mb, (size_t)nleaves * 32));
-            ZK_HIP_TRY(hipMemcpyAsync(mb->bulk, leaves, (size_t)nleaves * 32, hipMemcpyDeviceToHost, stream));
+            ZK_HIP_TRY(hipMemcpyAsync(mb->bulk + kBulkDigests, leaves, (size_t)nleaves * 32, hipMemcpyDeviceToHost, stream));
             job_m = add_job(Mfr, N, l, vt);
         }
         {
@@ -1716,9 +1751,9 @@ static int verify_core(const VerifyCall& c) {
             ZK_HIP_TRY(hipStreamSynchronize(stream));
         }
         auto value_is = [&](int job, const F& want) { return equal(from_dev(mb->words + 8 * job), want); };
-        auto digest_is = [&](const uint32_t* words, const uint8_t* want) {
+        auto digest_is = [&](int tree, const uint8_t* want) {
             uint8_t got[32];
-            digest_bytes(got, words);
+            vec_digest_finish(got, trees[tree]);
             return memcmp(got, want, 32) == 0;
         };
         if (!value_is(job_t, f[4])) return ZK_E_REJECT;
@@ -1727,14 +1762,14 @@ static int verify_core(const VerifyCall& c) {
         if (have_s && !value_is(job_s, f[1])) return ZK_E_REJECT;
         if (wit->A.limbs && !have_a) return ZK_E_BADARG;
         // a witness vector must also be the one whose digest the proof carries
-        if (have_a && (!value_is(job_a, f[0]) || !digest_is(mb->words + kMailboxDigest, ab_digests + 64 * i))) return ZK_E_REJECT;
+        if (have_a && (!value_is(job_a, f[0]) || !digest_is(0, ab_digests + 64 * i))) return ZK_E_REJECT;
         if (wit->B.limbs && !have_b) return ZK_E_BADARG;
-        if (have_b && (!value_is(job_b, f[2]) || !digest_is(mb->words + kMailboxDigest + 8, ab_digests + 64 * i + 32)))
+        if (have_b && (!value_is(job_b, f[2]) || !digest_is(ntrees - 1, ab_digests + 64 * i + 32)))
             return ZK_E_REJECT;
         if (have_m) {
             if (!value_is(job_m, f[3])) return ZK_E_REJECT;
             uint8_t md[32];
-            digest_of_leaves(md, mb->bulk, nleaves);
+            digest_of_leaves(md, mb->bulk + kBulkDigests, nleaves);
             if (memcmp(md, digests + 32 * i, 32) != 0) return ZK_E_REJECT;
         }
     }

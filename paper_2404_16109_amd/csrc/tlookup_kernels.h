@@ -447,107 +447,224 @@ static __global__ void __launch_bounds__(64) k_leaf_digests(uint32_t* __restrict
 // digest's bytes).
 static const uint32_t kVecLeaf = 128;
 
-// Up to two vectors are hashed by one launch (the table-side vector's few leaves
-// are chains of 65 dependent blocks: next to the tensor-side vector's they cost
-// nothing, on their own a quarter of a millisecond).
+// All vectors of a call are hashed by one launch (a leaf is a chain of 65 dependent
+// blocks whatever the vector's length: one after the other, short vectors would
+// cost as much as long ones).
 struct VecLeavesJob {
     const uint32_t* v;
-    size_t stride, n, L;  // L = 0: no such vector
-    uint32_t* out;        // L digests
+    size_t stride, n, L;
+    uint32_t* out;         // L digests; device memory, or pinned host memory if the host finishes the tree from here
+    uint32_t first_group;  // of 64 leaves each
+};
+static const int kDigestMaxJobs = 16;  // A and B of eight instances
+struct VecLeavesArgs {
+    VecLeavesJob job[kDigestMaxJobs];
+    int njobs;
+    uint32_t groups;
+    uint32_t* words;   // the mailbox, if this launch is the last to write results (seq != 0)
+    uint32_t* ticket;
+    uint32_t seq;
 };
 
-static __global__ void __launch_bounds__(kBlock) k_vec_leaves(VecLeavesJob first, VecLeavesJob second) {
-    size_t leaf = blockIdx.x * (size_t)kBlock + threadIdx.x;
-    const bool in_first = leaf < first.L;
-    const VecLeavesJob& job = in_first ? first : second;
-    if (!in_first) leaf -= first.L;
-    if (leaf >= job.L) return;
-    const uint32_t* v = job.v;
-    const size_t stride = job.stride, L = job.L;
-    const size_t cnt = job.n / L;  // elements per leaf: kVecLeaf, or all n (a power of two) when n < kVecLeaf
-    uint32_t h[8];
-    sha256_init(h);
-    // the next two elements are asked for before the current two are hashed: one block is some 1400 instructions
-    // during which their loads can be on the way
-    Fr next_a = fr_zero(), next_b = fr_zero();
-    if (cnt >= 2) {
-        next_a = fr_load(v, stride, leaf);
-        next_b = fr_load(v, stride, leaf + L);
+// The sixteen words of block b of one leaf, as the hash takes them.  Elements are
+// asked for one block ahead: a block is some thousand instructions during which
+// their loads can be on the way.
+struct LeafBlocks {
+    const uint32_t* at;  // element 0 of the leaf
+    size_t stride, step;
+    uint32_t cnt;
+    Fr a, b;
+
+    __device__ __forceinline__ void begin(const VecLeavesJob& job, size_t leaf) {
+        at = job.v + leaf;
+        stride = job.stride;
+        step = job.L;
+        cnt = (uint32_t)(job.n / job.L);  // kVecLeaf, or all n (a power of two) when n < kVecLeaf
+        a = fr_load(at, stride, 0);
+        b = cnt >= 2 ? fr_load(at, stride, step) : fr_zero();
     }
-    for (size_t t = 0; t + 1 < cnt; t += 2) {
-        const Fr raw_a = next_a, raw_b = next_b;
-        if (t + 3 < cnt) {
-            next_a = fr_load(v, stride, leaf + (t + 2) * L);
-            next_b = fr_load(v, stride, leaf + (t + 3) * L);
+    __device__ __forceinline__ uint32_t blocks() const { return cnt / 2 + 1; }  // the last holds the padding
+    __device__ __forceinline__ void block(uint32_t (&w)[16], uint32_t index) {
+        const bool data = index < cnt / 2;
+        if (data || cnt == 1) {
+            const Fr x = fr_from_mont(a);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = __builtin_bswap32(x.l[k]);
         }
-        const Fr a = fr_from_mont(raw_a);
-        const Fr b = fr_from_mont(raw_b);
-        uint32_t w[16];
+        if (data) {
+            const Fr y = fr_from_mont(b);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            w[k] = __builtin_bswap32(a.l[k]);
-            w[8 + k] = __builtin_bswap32(b.l[k]);
+            for (int k = 0; k < 8; ++k) w[8 + k] = __builtin_bswap32(y.l[k]);
+            if (2 * index + 3 < cnt) {
+                a = fr_load(at, stride, (2 * index + 2) * step);
+                b = fr_load(at, stride, (2 * index + 3) * step);
+            }
+        } else {
+            const int pad = cnt == 1 ? 8 : 0;  // a vector of one element shares its block with the padding
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                if (k >= pad) w[k] = k == pad ? 0x80000000u : k == 15 ? cnt * 256u : 0u;
         }
-        sha256_compress(h, w);
     }
-    if (cnt == 1) {  // a vector of one element: 32 bytes and the padding in one block
-        const Fr a = fr_from_mont(fr_load(v, stride, leaf));
-        uint32_t w[16];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) w[k] = __builtin_bswap32(a.l[k]);
-        w[8] = 0x80000000u;
-#pragma unroll
-        for (int k = 9; k < 15; ++k) w[k] = 0;
-        w[15] = 256;
-        sha256_compress(h, w);
-    } else {
-        sha256_finish_aligned(h, (uint64_t)cnt * 32);
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) job.out[leaf * 8 + k] = h[k];
+};
+
+__device__ __forceinline__ const VecLeavesJob& leaves_job(const VecLeavesArgs& args, uint32_t group) {
+    int q = 0;
+    while (q + 1 < args.njobs && group >= args.job[q + 1].first_group) ++q;
+    return args.job[q];
 }
 
-// One step up the tree, again for up to two rows at once: workgroup b of a job
-// reduces digests [b*chunk, (b+1)*chunk) of `in` to one (chunk a power of two, at
-// most kTreeChunk, and a power of four unless it is the whole row) and writes it
-// to out[8b..8b+8).  The launch's last workgroup publishes `seq` if it is not zero
-// (then the launch is the last one writing results into the mailbox `words`).
+__device__ __forceinline__ void leaves_done(const VecLeavesArgs& args) {
+    if (args.seq == 0) return;
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(args.ticket, 1u) == gridDim.x - 1) {
+        *args.ticket = 0;
+        mailbox_publish(args.words, args.seq);
+    }
+}
+
+// Many leaves: one lane does all of a leaf.  Bound by instruction issue.
+static __global__ void __launch_bounds__(64) k_vec_leaves(VecLeavesArgs args) {
+    const VecLeavesJob& job = leaves_job(args, blockIdx.x);
+    const size_t leaf = (size_t)(blockIdx.x - job.first_group) * 64 + threadIdx.x;
+    if (leaf < job.L) {
+        LeafBlocks src;
+        src.begin(job, leaf);
+        uint32_t h[8];
+        sha256_init(h);
+        for (uint32_t b = 0; b < src.blocks(); ++b) {
+            uint32_t w[16];
+            src.block(w, b);
+            sha256_compress(h, w);
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) job.out[leaf * 8 + k] = h[k];
+        if (args.seq) mailbox_written();
+    }
+    leaves_done(args);
+}
+
+// Few leaves (no more wavefronts than SIMDs): what counts is the length of one
+// leaf's chain, some 1750 instructions per block with conversion and message
+// schedule.  Two wavefronts share it: the second makes the schedule of the next
+// block (loads, conversion, expansion, round constants added) in LDS while the
+// first does the rounds of the current one, so that a block costs the rounds' 900
+// instructions.  A workgroup is two such pairs, one wavefront per SIMD: two
+// workgroups of one pair each were seen to share two SIMDs and leave two idle.
+// Measured at 2^20 elements (8192 leaves): 220 -> 140 us; above kPipedLeafGroups
+// the wavefronts would have to share SIMDs, and one lane per leaf is as fast.
+static const uint32_t kPipedLeafGroups = 512;
+
+static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs args) {
+    __shared__ uint4 kw[2][2][16][64];  // [pair][buffer][four rounds][lane]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pair = wave >> 1;
+    const bool rounds = (wave & 1) == 0;
+    // both pairs take the same number of barriers: as many as the longer leaf of the two needs
+    const uint32_t group = 2 * blockIdx.x + pair, other = 2 * blockIdx.x + (pair ^ 1);
+    const bool live = group < args.groups;
+    const VecLeavesJob& job = leaves_job(args, live ? group : args.groups - 1);
+    const VecLeavesJob& job2 = leaves_job(args, other < args.groups ? other : args.groups - 1);
+    const uint32_t blocks = live ? (uint32_t)(job.n / job.L) / 2 + 1 : 0;
+    const uint32_t blocks2 = other < args.groups ? (uint32_t)(job2.n / job2.L) / 2 + 1 : 0;
+    const uint32_t steps = blocks > blocks2 ? blocks : blocks2;
+    const size_t leaf = (size_t)(group - job.first_group) * 64 + lane;
+    if (rounds) {
+        uint32_t h[8];
+        sha256_init(h);
+        __syncthreads();
+        for (uint32_t b = 0; b < steps; ++b) {
+            if (b < blocks) {
+                uint32_t s[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) s[i] = h[i];
+#pragma unroll
+                for (int g = 0; g < 16; ++g) {
+                    const uint4 q = kw[pair][b & 1][g][lane];
+                    sha256_round(s, q.x);
+                    sha256_round(s, q.y);
+                    sha256_round(s, q.z);
+                    sha256_round(s, q.w);
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) h[i] += s[i];
+            }
+            __syncthreads();
+        }
+        if (live && leaf < job.L) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) job.out[leaf * 8 + k] = h[k];
+            if (args.seq) mailbox_written();
+        }
+    } else {
+        LeafBlocks src;
+        if (live) src.begin(job, leaf < job.L ? leaf : job.L - 1);
+        for (uint32_t b = 0; b <= steps; ++b) {  // one barrier more than blocks, as the wavefront of the rounds takes
+            if (b < blocks) {
+                uint32_t w[16];
+                src.block(w, b);
+#pragma unroll
+                for (int g = 0; g < 16; ++g) {
+                    if (g >= 4) sha256_schedule4(w, 4 * g);
+                    const int i = (4 * g) & 15;
+                    kw[pair][b & 1][g][lane] = make_uint4(w[i] + kShaK[4 * g], w[i + 1] + kShaK[4 * g + 1],
+                                                          w[i + 2] + kShaK[4 * g + 2], w[i + 3] + kShaK[4 * g + 3]);
+                }
+            }
+            __syncthreads();
+        }
+    }
+    leaves_done(args);
+}
+
+// One step up the trees: workgroup b of a job reduces digests [b*chunk,
+// (b+1)*chunk) of `in` to one (chunk a power of four, at most kTreeChunk) and writes
+// it to out[8b..8b+8).  The last rows of a tree are the host's: a level costs some 8
+// us here whatever its length (three dependent blocks), 64 digests cost the host 3.
 static const uint32_t kTreeChunk = 1024;
+static const uint32_t kTreeHostRow = 256;  // rows of at most this many digests go to the host
 
 struct DigestTreeJob {
     const uint32_t* in;
     uint32_t* out;
     uint32_t chunk;
-    uint32_t blocks;  // 0: no such row
+    uint32_t first_block;
+};
+struct DigestTreeArgs {
+    DigestTreeJob job[kDigestMaxJobs];
+    int njobs;
+    uint32_t* words;
+    uint32_t* ticket;
+    uint32_t seq;
 };
 
-static __global__ void __launch_bounds__(kBlock) k_digest_tree(DigestTreeJob first, DigestTreeJob second, uint32_t* words,
-                                                        uint32_t seq, uint32_t* ticket) {
+static __global__ void __launch_bounds__(kBlock) k_digest_tree(DigestTreeArgs args) {
     __shared__ uint32_t rows[2][kTreeChunk / 4 * 8];  // the row being read and the one being written (at most chunk/4 digests)
-    const bool in_first = blockIdx.x < first.blocks;
-    const DigestTreeJob& job = in_first ? first : second;
-    const uint32_t b = in_first ? blockIdx.x : blockIdx.x - first.blocks;
+    int q = 0;
+    while (q + 1 < args.njobs && blockIdx.x >= args.job[q + 1].first_block) ++q;
+    const DigestTreeJob& job = args.job[q];
+    const uint32_t b = blockIdx.x - job.first_block;
     // the first row comes from memory; every later one from LDS
     const uint32_t* base = job.in + (size_t)b * job.chunk * 8;
     uint32_t cnt = job.chunk;
     int cur = 0;
     bool from_lds = false;
     while (cnt > 1) {
-        const uint32_t group = cnt >= 4 ? 4 : 2;
-        const uint32_t nodes = cnt / group;
+        const uint32_t nodes = cnt / 4;
         for (uint32_t node = threadIdx.x; node < nodes; node += kBlock) {
             uint32_t h[8];
             sha256_init(h);
-            for (uint32_t part = 0; part < group; part += 2) {
+#pragma unroll 1
+            for (uint32_t part = 0; part < 4; part += 2) {
                 uint32_t w[16];
 #pragma unroll
                 for (int k = 0; k < 16; ++k) {
-                    const uint32_t at = (node * group + part) * 8 + k;
+                    const uint32_t at = (node * 4 + part) * 8 + k;
                     w[k] = from_lds ? rows[cur][at] : base[at];
                 }
                 sha256_compress(h, w);
             }
-            sha256_finish_aligned(h, (uint64_t)group * 32);
+            sha256_compress_padding(h, kShaPad128.kw);
 #pragma unroll
             for (int k = 0; k < 8; ++k) rows[cur ^ 1][node * 8 + k] = h[k];
         }
@@ -557,17 +674,14 @@ static __global__ void __launch_bounds__(kBlock) k_digest_tree(DigestTreeJob fir
         cnt = nodes;
     }
     if (threadIdx.x < 8) {
-        const uint32_t v = from_lds ? rows[cur][threadIdx.x] : base[threadIdx.x];
-        job.out[(size_t)b * 8 + threadIdx.x] = v;
-        mailbox_written();
+        job.out[(size_t)b * 8 + threadIdx.x] = from_lds ? rows[cur][threadIdx.x] : base[threadIdx.x];
+        if (args.seq) mailbox_written();
     }
+    if (args.seq == 0) return;
     __syncthreads();
-    if (seq != 0 && threadIdx.x == 0) {
-        const unsigned done = atomicAdd(ticket, 1u);
-        if (done == gridDim.x - 1) {
-            *ticket = 0;
-            mailbox_publish(words, seq);
-        }
+    if (threadIdx.x == 0 && atomicAdd(args.ticket, 1u) == gridDim.x - 1) {
+        *args.ticket = 0;
+        mailbox_publish(args.words, args.seq);
     }
 }
 

@@ -35,6 +35,12 @@ public:
         const uint8_t* p = (const uint8_t*)data;
         total_ += len;
         while (len) {
+            if (fill_ == 0 && len >= 64) {
+                block(p);
+                p += 64;
+                len -= 64;
+                continue;
+            }
             size_t take = 64 - fill_;
             if (take > len) take = len;
             memcpy(buf_ + fill_, p, take);
@@ -60,11 +66,33 @@ public:
         for (int i = 0; i < 8; ++i) buf_[56 + i] = (uint8_t)(bits >> (56 - 8 * i));
         block(buf_);
         fill_ = 0;
-        for (int i = 0; i < 8; ++i) {
-            out[4 * i] = (uint8_t)(h_[i] >> 24);
-            out[4 * i + 1] = (uint8_t)(h_[i] >> 16);
-            out[4 * i + 2] = (uint8_t)(h_[i] >> 8);
-            out[4 * i + 3] = (uint8_t)h_[i];
+        put_state(out);
+    }
+
+    // One row of a hash tree: out[i] = SHA-256 of in[4 i .. 4 i + 3], digests of 32 bytes.  out may be in.
+    static void hash_fours(uint8_t* out, const uint8_t* in, uint32_t nodes) {
+        uint32_t i = 0;
+#if defined(__x86_64__)
+        if (use_sha_instructions()) {
+            uint8_t pad[64] = {0x80};
+            pad[62] = 0x04;  // 1024 bits
+            for (; i + 2 <= nodes; i += 2) {
+                Sha256 x, y;
+                uint32_t (*const h[2])[8] = {&x.h_, &y.h_};
+                const uint8_t* p = in + (size_t)i * 128;
+                for (int part = 0; part < 3; ++part) {
+                    const uint8_t* const b[2] = {part < 2 ? p + 64 * part : pad, part < 2 ? p + 128 + 64 * part : pad};
+                    blocks_shani<2>(h, b);
+                }
+                x.put_state(out + (size_t)i * 32);
+                y.put_state(out + (size_t)i * 32 + 32);
+            }
+        }
+#endif
+        for (; i < nodes; ++i) {
+            Sha256 h;
+            h.update(in + (size_t)i * 128, 128);
+            h.finish(out + (size_t)i * 32);
         }
     }
 
@@ -79,6 +107,12 @@ public:
     }
 
 private:
+    void put_state(uint8_t out[32]) const {
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t v = __builtin_bswap32(h_[i]);
+            memcpy(out + 4 * i, &v, 4);
+        }
+    }
     static uint32_t ror(uint32_t x, int n) { return (x >> n) | (x << (32 - n)); }
 
     static const uint32_t* round_constants() {
@@ -95,45 +129,60 @@ private:
     }
 
 #if defined(__x86_64__)
-    // One block with the x86 SHA extensions.  sha256rnds2 does two rounds on the
-    // state split as (A,B,E,F) and (C,D,G,H), taking W+K of those rounds from the
-    // low half of its third operand; sha256msg1/msg2 produce four schedule words
-    // from the sixteen before them.
-    __attribute__((target("sha,sse4.1,ssse3"))) void block_shani(const uint8_t* b) {
+    // One block of each of N messages with the x86 SHA extensions.  sha256rnds2 does two
+    // rounds on the state split as (A,B,E,F) and (C,D,G,H), taking W+K of those rounds from
+    // the low half of its third operand; sha256msg1/msg2 produce four schedule words from
+    // the sixteen before them.  One message is a chain of dependent instructions; two of
+    // them fill each other's latencies.
+    template <int N>
+    __attribute__((target("sha,sse4.1,ssse3"))) static void blocks_shani(uint32_t (*const (&h)[N])[8], const uint8_t* const (&b)[N]) {
         const __m128i* kk = (const __m128i*)round_constants();
         const __m128i bswap = _mm_set_epi64x(0x0c0d0e0f08090a0bULL, 0x0405060700010203ULL);
-        __m128i abcd = _mm_loadu_si128((const __m128i*)&h_[0]);  // lanes: a b c d (a lowest)
-        __m128i efgh = _mm_loadu_si128((const __m128i*)&h_[4]);
-        // -> (F,E,B,A) and (H,G,D,C), highest lane first, as the instruction expects
-        __m128i t = _mm_shuffle_epi32(abcd, 0xB1);        // b a d c
-        __m128i u = _mm_shuffle_epi32(efgh, 0x1B);        // h g f e
-        __m128i abef = _mm_alignr_epi8(t, u, 8);          // f e b a   (lane0 = f)
-        __m128i cdgh = _mm_blend_epi16(u, t, 0xF0);       // h g d c   (lane0 = h)
-        const __m128i abef0 = abef, cdgh0 = cdgh;
-        __m128i w[4];
-        for (int i = 0; i < 4; ++i) w[i] = _mm_shuffle_epi8(_mm_loadu_si128((const __m128i*)(b + 16 * i)), bswap);
-        for (int g = 0; g < 16; ++g) {  // four rounds per step
-            __m128i cur;
-            if (g < 4) {
-                cur = w[g];
-            } else {
-                // W[4g..4g+3] from the four vectors before it
-                __m128i x = _mm_sha256msg1_epu32(w[g & 3], w[(g + 1) & 3]);
-                x = _mm_add_epi32(x, _mm_alignr_epi8(w[(g + 3) & 3], w[(g + 2) & 3], 4));
-                cur = _mm_sha256msg2_epu32(x, w[(g + 3) & 3]);
-                w[g & 3] = cur;
-            }
-            __m128i wk = _mm_add_epi32(cur, _mm_loadu_si128(kk + g));
-            cdgh = _mm_sha256rnds2_epu32(cdgh, abef, wk);
-            abef = _mm_sha256rnds2_epu32(abef, cdgh, _mm_shuffle_epi32(wk, 0x0E));
+        __m128i abef[N], cdgh[N], abef0[N], cdgh0[N], w[N][4];
+        for (int n = 0; n < N; ++n) {
+            __m128i abcd = _mm_loadu_si128((const __m128i*)&(*h[n])[0]);  // lanes: a b c d (a lowest)
+            __m128i efgh = _mm_loadu_si128((const __m128i*)&(*h[n])[4]);
+            // -> (F,E,B,A) and (H,G,D,C), highest lane first, as the instruction expects
+            __m128i t = _mm_shuffle_epi32(abcd, 0xB1);        // b a d c
+            __m128i u = _mm_shuffle_epi32(efgh, 0x1B);        // h g f e
+            abef0[n] = abef[n] = _mm_alignr_epi8(t, u, 8);          // f e b a   (lane0 = f)
+            cdgh0[n] = cdgh[n] = _mm_blend_epi16(u, t, 0xF0);       // h g d c   (lane0 = h)
+            for (int i = 0; i < 4; ++i) w[n][i] = _mm_shuffle_epi8(_mm_loadu_si128((const __m128i*)(b[n] + 16 * i)), bswap);
         }
-        abef = _mm_add_epi32(abef, abef0);
-        cdgh = _mm_add_epi32(cdgh, cdgh0);
-        // back to a b c d / e f g h
-        t = _mm_shuffle_epi32(abef, 0x1B);                // a b e f  (lane0 = a)
-        u = _mm_shuffle_epi32(cdgh, 0xB1);                // g h c d  (lane0 = g)
-        _mm_storeu_si128((__m128i*)&h_[0], _mm_blend_epi16(t, u, 0xF0));       // a b c d
-        _mm_storeu_si128((__m128i*)&h_[4], _mm_alignr_epi8(u, t, 8));          // e f g h
+#pragma clang loop unroll(full)
+        for (int g = 0; g < 16; ++g) {  // four rounds per step
+#pragma clang loop unroll(full)
+            for (int n = 0; n < N; ++n) {
+                __m128i cur;
+                if (g < 4) {
+                    cur = w[n][g];
+                } else {
+                    // W[4g..4g+3] from the four vectors before it
+                    __m128i x = _mm_sha256msg1_epu32(w[n][g & 3], w[n][(g + 1) & 3]);
+                    x = _mm_add_epi32(x, _mm_alignr_epi8(w[n][(g + 3) & 3], w[n][(g + 2) & 3], 4));
+                    cur = _mm_sha256msg2_epu32(x, w[n][(g + 3) & 3]);
+                    w[n][g & 3] = cur;
+                }
+                __m128i wk = _mm_add_epi32(cur, _mm_loadu_si128(kk + g));
+                cdgh[n] = _mm_sha256rnds2_epu32(cdgh[n], abef[n], wk);
+                abef[n] = _mm_sha256rnds2_epu32(abef[n], cdgh[n], _mm_shuffle_epi32(wk, 0x0E));
+            }
+        }
+        for (int n = 0; n < N; ++n) {
+            abef[n] = _mm_add_epi32(abef[n], abef0[n]);
+            cdgh[n] = _mm_add_epi32(cdgh[n], cdgh0[n]);
+            // back to a b c d / e f g h
+            __m128i t = _mm_shuffle_epi32(abef[n], 0x1B);                // a b e f  (lane0 = a)
+            __m128i u = _mm_shuffle_epi32(cdgh[n], 0xB1);                // g h c d  (lane0 = g)
+            _mm_storeu_si128((__m128i*)&(*h[n])[0], _mm_blend_epi16(t, u, 0xF0));       // a b c d
+            _mm_storeu_si128((__m128i*)&(*h[n])[4], _mm_alignr_epi8(u, t, 8));          // e f g h
+        }
+    }
+
+    void block_shani(const uint8_t* b) {
+        uint32_t (*const h[1])[8] = {&h_};
+        const uint8_t* const in[1] = {b};
+        blocks_shani<1>(h, in);
     }
 #endif
 
