@@ -171,18 +171,17 @@ def raw():
     return _lib
 
 
+_MASK256 = (1 << 256) - 1
+
+
 # ---- marshalling helpers ------------------------------------------------------------
 
 def _fr(x):
-    out = fr_t()
-    x = int(x)
-    for k in range(8):
-        out.l[k] = (x >> (32 * k)) & 0xFFFFFFFF
-    return out
+    return fr_t.from_buffer_copy((int(x) & _MASK256).to_bytes(32, "little"))
 
 
 def _fr_int(f):
-    return sum(int(f.l[k]) << (32 * k) for k in range(8))
+    return int.from_bytes(f, "little")
 
 
 def _stream():
