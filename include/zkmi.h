@@ -215,25 +215,20 @@ int tlookup_multiplicities(uint32_t* m, fr_vec S, const uint32_t* idx, fr_vec T,
  *
  * S not in T is ZK_E_NOT_IN_TABLE with aux->bad_index the smallest such i, as in
  * tlookup_multiplicities.  With idx given (and D > 256, N <= 2^16) the prover does
- * not compare every S_i with T[idx_i] up front: it counts from idx alone and then
- * applies the identity the protocol itself rests on, sum_i 1/(beta+S_i) =
- * sum_j m_j/(beta+T_j) (Section 4), to the sums it has after the first round;
- * only if they differ are all S_i compared with their rows to find bad_index.  A
- * tensor with S_i != T[idx_i] slips through with probability at most (D+N)/|F|
- * over beta (the identity cleared of its denominators is a polynomial identity of
- * degree below D+N; this is the step the soundness proof of Appendix C takes),
- * and the proof it then yields is one the verifier accepts for the same reason. */
+ * not compare every S_i with T[idx_i] while counting: it counts from idx alone and
+ * compares while it hashes A, of which it knows by then that A_i = 1/(beta+S_i) is
+ * the table-side inverse B[idx_i] if S_i is that row (for N <= 2^16 only the N table
+ * entries are inverted, with or without hints).  The check is exact either way. */
 size_t tlookup_proof_bytes(size_t D);
 int tlookup_prove(const uint8_t seed[32], fr_vec S, const uint32_t* idx, fr_vec T, uint8_t* proof, size_t cap,
                   size_t* len, tlookup_aux* aux, void* ws, size_t ws_bytes, void* stream);
 
 /* tlookup_prove with every S_i compared with its hinted row T[idx_i] before
  * anything else is done (while counting), as tlookup_multiplicities does, instead
- * of through the identity after the first round: the same proof, byte for byte,
- * for callers who want the membership check to be exact rather than sound up to
- * (D+N)/|F|.  Costs one more pass over S (36 instead of 4 bytes per element while
- * counting); timed beside the headline by the benchmark.  Without idx it is
- * tlookup_prove. */
+ * of while A is hashed: the same proof, byte for byte, for callers who want a wrong
+ * hint reported before any challenge is drawn.  Costs one more pass over S (36
+ * instead of 4 bytes per element while counting); timed beside the headline by the
+ * benchmark.  Without idx it is tlookup_prove. */
 int tlookup_prove_checked(const uint8_t seed[32], fr_vec S, const uint32_t* idx, fr_vec T, uint8_t* proof, size_t cap,
                           size_t* len, tlookup_aux* aux, void* ws, size_t ws_bytes, void* stream);
 
@@ -243,9 +238,9 @@ int tlookup_prove_checked(const uint8_t seed[32], fr_vec S, const uint32_t* idx,
  * set by combining its two columns with a random rho; T is then T_X + rho T_Y as
  * field elements, as for tlookup_prove), or S_i = X_i with Y and rho both NULL (a
  * range check).  rho: host, canonical.  The proof is tlookup_prove's for that S,
- * byte for byte; S is never written out: the inversion and the first round read
- * eight bytes per entry instead of thirty-two and build beta + S_i from them (two
- * 32x256-bit products and a two-step reduction), the first fold takes the four
+ * byte for byte; S is never written out: the comparison with the hinted rows and the
+ * first round read eight bytes per entry instead of thirty-two and build S_i from them
+ * (two 32x256-bit products and a two-step reduction), the first fold takes the four
  * integers of an entry pair straight to a reduced field element.  Row hints idx
  * are required (for a range check idx_i = X_i - min T).  Shapes with N > 2^16,
  * D < 4 N or D <= 1024 have no such path: S is written out first, into D * 32
@@ -257,11 +252,9 @@ int tlookup_prove_small(const uint8_t seed[32], const int32_t* X, const int32_t*
                         size_t ws_bytes, void* stream);
 
 /* The same proof, byte for byte, for callers that know the table row of every
- * element (idx is required): once S_i = T[idx_i] has been checked, A_i = 1/(beta + S_i)
- * is the table-side inverse B[idx_i], so only the N table entries are inverted and
- * A is gathered from them instead of inverting D elements.  Not what the
- * benchmark's headline times (that is tlookup_prove, with the D-element
- * inversion); reported beside it. */
+ * element (idx is required), whatever the length of the table: only the N table
+ * entries are inverted and A is read off them by row, which tlookup_prove does by
+ * itself for N <= 2^16 only. */
 int tlookup_prove_by_rows(const uint8_t seed[32], fr_vec S, const uint32_t* idx, fr_vec T, uint8_t* proof, size_t cap,
                           size_t* len, tlookup_aux* aux, void* ws, size_t ws_bytes, void* stream);
 

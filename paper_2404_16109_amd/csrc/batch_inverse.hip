@@ -8,17 +8,17 @@
 //   up pass    : each thread receives the inverse of its own total and walks
 //                back over its elements: out_j = inv * prefix_{j-1}, inv *= x_j.
 //
-// A level after the first that is short enough (<= 2^20 elements) is reduced by
-// whole workgroups instead: the threads' totals are multiplied up within the
+// A level that is short enough (<= 2^20 elements, a first level <= 2^17) is reduced
+// by whole workgroups instead: the threads' totals are multiplied up within the
 // workgroup (a scan in LDS), so the next level is 256*K times smaller and fits
 // the top.  That saves dependent launches, which is all the small levels cost:
-// eight for 2^25 elements instead of twelve.  (Longer levels stay with the
-// threads: there the scans cost more than the launches they save.)
+// eight for 2^25 elements instead of twelve, four for a table of 2^16.  (Longer
+// levels stay with the threads: there the scans cost more than the launches they
+// save.)
 //
 // Cost: about 3 multiplications per element plus a geometric tail.  A zero
 // anywhere makes the grand total zero, which is how it is detected.
 #include "internal.h"
-#include "small_dev.h"
 
 namespace zkmi {
 
@@ -42,23 +42,13 @@ __device__ __forceinline__ Fr bi_load(const uint32_t* __restrict__ src, size_t s
     return shifted ? fr_add(x, shift) : x;
 }
 
-// The first vector of the first level given as small integers (SmallSource, see
-// small_dev.h) instead of field elements.
-__device__ __forceinline__ Fr bi_load_small(const SmallSource& small, size_t i, bool shifted, const Fr& shift) {
-    Fr x;
-    small_source_load(x.l, small, i);
-    return shifted ? fr_add(x, shift) : x;
-}
-
 // prefix_i = product of this thread's elements up to and including i; the
 // thread's total goes to next[tid].
 __global__ void __launch_bounds__(kBlock) k_bi_down(const uint32_t* __restrict__ src, size_t ss, size_t n, int shifted,
                                                     Fr shift, uint32_t* __restrict__ prefix, size_t ps,
-                                                    uint32_t* __restrict__ next, size_t ns, BiSecond second,
-                                                    SmallSource small) {
+                                                    uint32_t* __restrict__ next, size_t ns, BiSecond second) {
     size_t tid = blockIdx.x * (size_t)kBlock + threadIdx.x;
     size_t base = blockIdx.x * (size_t)kBlock * kBiK + threadIdx.x;
-    bool from_small = small.x != nullptr;
     if (blockIdx.x * (size_t)kBlock * kBiK >= second.n1) {  // the whole workgroup is in the second vector
         src = second.src;
         ss = second.ss;
@@ -66,7 +56,6 @@ __global__ void __launch_bounds__(kBlock) k_bi_down(const uint32_t* __restrict__
         ps = second.ps;
         base -= second.n1;
         n -= second.n1;
-        from_small = false;
     } else if (n > second.n1) {
         n = second.n1;
     }
@@ -75,7 +64,7 @@ __global__ void __launch_bounds__(kBlock) k_bi_down(const uint32_t* __restrict__
     for (int j = 0; j < kBiK; ++j) {
         size_t i = base + (size_t)j * kBlock;
         if (i < n) {
-            Fr x = from_small ? bi_load_small(small, i, shifted, shift) : bi_load(src, ss, i, shifted, shift);
+            Fr x = bi_load(src, ss, i, shifted, shift);
             acc = first ? x : fr_mul(acc, x);
             first = false;
             fr_store(prefix, ps, i, acc);
@@ -88,10 +77,9 @@ __global__ void __launch_bounds__(kBlock) k_bi_down(const uint32_t* __restrict__
 __global__ void __launch_bounds__(kBlock) k_bi_up(const uint32_t* __restrict__ src, size_t ss, size_t n, int shifted,
                                                   Fr shift, const uint32_t* prefix, size_t ps,
                                                   const uint32_t* __restrict__ inv_next, size_t is, uint32_t* out,
-                                                  size_t os, BiSecond second, SmallSource small) {
+                                                  size_t os, BiSecond second) {
     size_t tid = blockIdx.x * (size_t)kBlock + threadIdx.x;
     size_t base = blockIdx.x * (size_t)kBlock * kBiK + threadIdx.x;
-    bool from_small = small.x != nullptr;
     if (blockIdx.x * (size_t)kBlock * kBiK >= second.n1) {  // prefix and out are the same buffer (see batch_inverse_end)
         src = second.src;
         ss = second.ss;
@@ -101,7 +89,6 @@ __global__ void __launch_bounds__(kBlock) k_bi_up(const uint32_t* __restrict__ s
         os = second.ps;
         base -= second.n1;
         n -= second.n1;
-        from_small = false;
     } else if (n > second.n1) {
         n = second.n1;
     }
@@ -111,7 +98,7 @@ __global__ void __launch_bounds__(kBlock) k_bi_up(const uint32_t* __restrict__ s
         if (i < n) {
             if (j > 0) {
                 Fr before = fr_load(prefix, ps, i - kBlock);
-                Fr x = from_small ? bi_load_small(small, i, shifted, shift) : bi_load(src, ss, i, shifted, shift);
+                Fr x = bi_load(src, ss, i, shifted, shift);
                 fr_store(out, os, i, fr_mul(inv, before));
                 inv = fr_mul(inv, x);
             } else {
@@ -161,8 +148,8 @@ __device__ __forceinline__ Fr block_neighbour(const Fr& scanned, uint32_t* lds, 
 // A level reduced by whole workgroups, down: as k_bi_down, then the product of the
 // workgroup's thread totals goes to next[blockIdx.x].
 template <int kPer>
-__global__ void __launch_bounds__(kBlock) k_bi_down_wg(const uint32_t* __restrict__ src, size_t ss, size_t n,
-                                                       uint32_t* __restrict__ prefix, size_t ps,
+__global__ void __launch_bounds__(kBlock) k_bi_down_wg(const uint32_t* __restrict__ src, size_t ss, size_t n, int shifted,
+                                                       Fr shift, uint32_t* __restrict__ prefix, size_t ps,
                                                        uint32_t* __restrict__ next, size_t ns) {
     __shared__ uint32_t lds[8 * kBlock];
     const size_t base = blockIdx.x * (size_t)kBlock * kPer + threadIdx.x;
@@ -170,7 +157,7 @@ __global__ void __launch_bounds__(kBlock) k_bi_down_wg(const uint32_t* __restric
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
         const size_t i = base + (size_t)j * kBlock;
-        x[j] = i < n ? fr_load(src, ss, i) : fr_one();
+        x[j] = i < n ? bi_load(src, ss, i, shifted, shift) : fr_one();
     }
     Fr acc = x[0];
     if (base < n) fr_store(prefix, ps, base, acc);
@@ -189,8 +176,8 @@ __global__ void __launch_bounds__(kBlock) k_bi_down_wg(const uint32_t* __restric
 // Up: inv_next[blockIdx.x] is the inverse of the workgroup's product; a thread's
 // own inverse is that times the totals of all other threads of the workgroup.
 template <int kPer>
-__global__ void __launch_bounds__(kBlock) k_bi_up_wg(const uint32_t* __restrict__ src, size_t ss, size_t n,
-                                                     const uint32_t* prefix, size_t ps,
+__global__ void __launch_bounds__(kBlock) k_bi_up_wg(const uint32_t* __restrict__ src, size_t ss, size_t n, int shifted,
+                                                     Fr shift, const uint32_t* prefix, size_t ps,
                                                      const uint32_t* __restrict__ inv_next, size_t is, uint32_t* out,
                                                      size_t os) {
     __shared__ uint32_t lds[8 * kBlock];
@@ -215,7 +202,7 @@ __global__ void __launch_bounds__(kBlock) k_bi_up_wg(const uint32_t* __restrict_
         for (int q = 0; q < kStep; ++q) {
             const int j = part * kStep + q;
             const size_t i = base + (size_t)j * kBlock;
-            x[q] = j > 0 && j < count ? fr_load(src, ss, i) : fr_one();
+            x[q] = j > 0 && j < count ? bi_load(src, ss, i, shifted, shift) : fr_one();
             before[q] = j > 0 && j < count ? fr_load(prefix, ps, i - kBlock) : fr_one();
         }
 #pragma unroll
@@ -270,7 +257,7 @@ static const size_t kBiTopMax = kBlock;  // values the top kernels take
 // Whether level `depth` of length n is reduced by whole workgroups, how many
 // elements a thread then takes (as few as still leave the top at most kBiTopMax
 // values: the chain of products is what such a level costs), and the next level's length.
-static bool bi_by_workgroups(int depth, size_t n) { return depth >= 1 && n <= kBiTopMax * kBlock * kBiK; }
+static bool bi_by_workgroups(int depth, size_t n) { return n <= kBiTopMax * kBlock * (depth >= 1 ? kBiK : 2); }
 static int bi_wg_per_thread(size_t n) {
     int per = 2;
     while (per < kBiK && div_up(n, (size_t)kBlock * per) > kBiTopMax) per *= 2;
@@ -282,19 +269,23 @@ static size_t bi_next_size(int depth, size_t n) {
 }
 
 template <int kPer>
-static void bi_launch_wg(bool down, unsigned blocks, hipStream_t stream, const uint32_t* x, size_t xs, size_t n, uint32_t* p,
-                         size_t ps, uint32_t* next_or_inv, size_t ns) {
-    if (down) hipLaunchKernelGGL(k_bi_down_wg<kPer>, dim3(blocks), dim3(kBlock), 0, stream, x, xs, n, p, ps, next_or_inv, ns);
-    else hipLaunchKernelGGL(k_bi_up_wg<kPer>, dim3(blocks), dim3(kBlock), 0, stream, x, xs, n, p, ps, next_or_inv, ns, p, ps);
+static void bi_launch_wg(bool down, unsigned blocks, hipStream_t stream, const BatchInverseJob::Level& lv, const Fr& shift,
+                         uint32_t* next_or_inv, size_t ns) {
+    if (down)
+        hipLaunchKernelGGL(k_bi_down_wg<kPer>, dim3(blocks), dim3(kBlock), 0, stream, lv.x, lv.xs, lv.n, lv.shifted, shift,
+                           lv.p, lv.ps, next_or_inv, ns);
+    else
+        hipLaunchKernelGGL(k_bi_up_wg<kPer>, dim3(blocks), dim3(kBlock), 0, stream, lv.x, lv.xs, lv.n, lv.shifted, shift, lv.p,
+                           lv.ps, next_or_inv, ns, lv.p, lv.ps);
 }
-static void bi_launch_wg_level(bool down, hipStream_t stream, const uint32_t* x, size_t xs, size_t n, uint32_t* p, size_t ps,
+static void bi_launch_wg_level(bool down, hipStream_t stream, const BatchInverseJob::Level& lv, const Fr& shift,
                                uint32_t* next_or_inv, size_t ns) {
-    const int per = bi_wg_per_thread(n);
-    const unsigned blocks = (unsigned)div_up(n, (size_t)kBlock * per);
-    if (per == 2) bi_launch_wg<2>(down, blocks, stream, x, xs, n, p, ps, next_or_inv, ns);
-    else if (per == 4) bi_launch_wg<4>(down, blocks, stream, x, xs, n, p, ps, next_or_inv, ns);
-    else if (per == 8) bi_launch_wg<8>(down, blocks, stream, x, xs, n, p, ps, next_or_inv, ns);
-    else bi_launch_wg<16>(down, blocks, stream, x, xs, n, p, ps, next_or_inv, ns);
+    const int per = bi_wg_per_thread(lv.n);
+    const unsigned blocks = (unsigned)div_up(lv.n, (size_t)kBlock * per);
+    if (per == 2) bi_launch_wg<2>(down, blocks, stream, lv, shift, next_or_inv, ns);
+    else if (per == 4) bi_launch_wg<4>(down, blocks, stream, lv, shift, next_or_inv, ns);
+    else if (per == 8) bi_launch_wg<8>(down, blocks, stream, lv, shift, next_or_inv, ns);
+    else bi_launch_wg<16>(down, blocks, stream, lv, shift, next_or_inv, ns);
 }
 
 size_t batch_inverse_scratch_bytes(size_t n) {
@@ -313,23 +304,16 @@ static BiSecond bi_second_of(const BatchInverseJob& job, int depth) {
     return BiSecond{nullptr, 0, nullptr, 0, SIZE_MAX};
 }
 
-static SmallSource bi_small_of(const BatchInverseJob& job, int depth) {
-    SmallSource none;
-    memset(&none, 0, sizeof none);
-    return depth == 0 && job.small.x ? job.small : none;
+bool batch_inverse_can_join(size_t n1, size_t n2) {
+    return n1 % ((size_t)kBlock * kBiK) == 0 && !bi_by_workgroups(0, n1 + n2);
 }
-
-bool batch_inverse_can_join(size_t n1) { return n1 % ((size_t)kBlock * kBiK) == 0; }
 
 int batch_inverse_begin(BatchInverseJob& job, uint32_t* dst, size_t dst_stride, const uint32_t* src, size_t src_stride,
                         size_t n, const host::F& shift, Carver& cv, uint32_t* total_words, uint32_t* flag_words,
                         uint32_t seq, hipStream_t stream, uint32_t* dst2, size_t dst2_stride, const uint32_t* src2,
-                        size_t src2_stride, size_t n2, const SmallSource* small) {
+                        size_t src2_stride, size_t n2) {
     typedef BatchInverseJob::Level Level;
-    if (n2 && !batch_inverse_can_join(n)) return ZK_E_BADARG;
-    if (small && n <= kBiTopMax) return ZK_E_BADARG;  // the top kernels read field elements
-    memset(&job.small, 0, sizeof job.small);
-    if (small) job.small = *small;
+    if (n2 && !batch_inverse_can_join(n, n2)) return ZK_E_BADARG;
     job.depth = 0;
     job.shift = to_dev(shift);
     job.n2 = n2;
@@ -339,7 +323,6 @@ int batch_inverse_begin(BatchInverseJob& job, uint32_t* dst, size_t dst_stride, 
     job.dst2_stride = dst2_stride;
     int shifted0 = host::is_zero(shift) ? 0 : 1;
     job.lv[0] = Level{src, src_stride, dst, dst_stride, n + n2, shifted0};
-    if (n2 && n + n2 <= kBiTopMax) return ZK_E_BADARG;  // a joined vector is longer than the top kernels take
     while (job.lv[job.depth].n > kBiTopMax) {
         const Level& cur = job.lv[job.depth];
         const size_t m = bi_next_size(job.depth, cur.n);
@@ -348,10 +331,10 @@ int batch_inverse_begin(BatchInverseJob& job, uint32_t* dst, size_t dst_stride, 
         uint32_t* p = cv.limbs(m);
         if (!x || !p) return ZK_E_BUFSZ;
         if (bi_by_workgroups(job.depth, cur.n))
-            bi_launch_wg_level(true, stream, cur.x, cur.xs, cur.n, cur.p, cur.ps, x, m);
+            bi_launch_wg_level(true, stream, cur, job.shift, x, m);
         else
             hipLaunchKernelGGL(k_bi_down, dim3(blocks), dim3(kBlock), 0, stream, cur.x, cur.xs, cur.n, cur.shifted,
-                               job.shift, cur.p, cur.ps, x, m, bi_second_of(job, job.depth), bi_small_of(job, job.depth));
+                               job.shift, cur.p, cur.ps, x, m, bi_second_of(job, job.depth));
         ++job.depth;
         job.lv[job.depth] = Level{x, m, p, m, m, 0};
     }
@@ -372,10 +355,10 @@ int batch_inverse_end(const BatchInverseJob& job, const host::F& inv_total, hipS
         const Level& up = job.lv[d + 1];
         const unsigned blocks = (unsigned)div_up(cur.n, (size_t)kBlock * kBiK);
         if (bi_by_workgroups(d, cur.n))
-            bi_launch_wg_level(false, stream, cur.x, cur.xs, cur.n, cur.p, cur.ps, up.p, up.ps);
+            bi_launch_wg_level(false, stream, cur, job.shift, up.p, up.ps);
         else
             hipLaunchKernelGGL(k_bi_up, dim3(blocks), dim3(kBlock), 0, stream, cur.x, cur.xs, cur.n, cur.shifted, job.shift,
-                               cur.p, cur.ps, up.p, up.ps, cur.p, cur.ps, bi_second_of(job, d), bi_small_of(job, d));
+                               cur.p, cur.ps, up.p, up.ps, cur.p, cur.ps, bi_second_of(job, d));
     }
     ZK_HIP_TRY(hipGetLastError());
     return ZK_OK;
@@ -387,7 +370,7 @@ int batch_inverse_run(uint32_t* dst, size_t dst_stride, const uint32_t* src, siz
     BatchInverseJob job;
     uint32_t seq = mb->next_seq();
     ZK_TRY(batch_inverse_begin(job, dst, dst_stride, src, src_stride, n, shift, cv, mb->words + kMailboxInvA, mb->words,
-                               seq, stream, nullptr, 0, nullptr, 0, 0, nullptr));
+                               seq, stream, nullptr, 0, nullptr, 0, 0));
     ZK_TRY(mailbox_wait(mb, seq, stream));
     host::F total = from_dev(mb->words + kMailboxInvA);
     if (host::is_zero(total)) return ZK_E_ZERO_DENOM;

@@ -139,6 +139,7 @@ static const size_t kMailboxMaxInstances = 8;
 static const size_t kMailboxInvB = 1024;    // grand total of the table-side inversion (+16 per instance)
 static const size_t kMailboxInvA = 1032;    // grand total of the data-side inversion (+16 per instance)
 static const size_t kMailboxTableC = 1280;  // the two table-side constants (+16 per instance)
+static const size_t kMailboxBad = 1408;     // smallest index whose element is not its hinted row, all ones if none (+2 per instance)
 
 // The staging buffer (Mailbox::bulk) starts with the rows of digests the host
 // finishes hash trees from (sixteen vectors, 256 digests each); what other copies

@@ -167,6 +167,8 @@ struct ProveWs {
     uint32_t cap_mask;
     uint32_t* canon;    // N
     uint4* rows;        // N rows of T, eight words each
+    uint4* rows_b;      // N rows of B, sixteen words each (k_rows_of)
+    uint32_t* found;    // D: the row of every S_i, found while counting (calls without hints), else null
     uint32_t* hist;     // per-workgroup histograms (tables of up to 2^16 rows), else null
     uint32_t hist_parts;
     uint32_t* flags;    // [0] duplicate flag, [1] ticket of the final sums, [2..3] smallest bad index (64-bit)
@@ -206,19 +208,29 @@ static size_t vec_digest_row_digests(size_t n) {
 // leaves: room for the sum of vec_digest_leaves(n); rows: vec_digest_row_digests(n)
 // digests each.
 struct VecDigestJob {
-    const uint32_t* v;
+    uint32_t* v;  // only read, unless `from` says that it is made here
     size_t stride, n;
     uint32_t* rows;
-    const uint32_t* host_row;  // set by the launch: the row handed to the host
-    uint32_t host_count;
+    LeafGather from;
+    const uint32_t* host_row = nullptr;  // set by the launch: the row handed to the host
+    uint32_t host_count = 0;
 };
 
+template <int MODE>
+static void launch_leaves(const VecLeavesArgs& lv, hipStream_t stream) {
+    if (leaves_in_pairs<MODE>(lv.groups))
+        hipLaunchKernelGGL(k_vec_leaves_piped<MODE>, dim3((lv.groups + 1) / 2), dim3(256), 0, stream, lv);
+    else hipLaunchKernelGGL(k_vec_leaves<MODE>, dim3(lv.groups), dim3(64), 0, stream, lv);
+}
+
+// The jobs that have rows (LeafGather) all compare them with S, or all with the
+// integers, or none: by `ints` and whether they have an S.
 static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Mailbox* mb, uint32_t seq, uint32_t* ticket,
-                             hipStream_t stream) {
+                             hipStream_t stream, const SmallSource* ints = nullptr) {
     if (njobs < 1 || njobs > kDigestMaxJobs) return ZK_E_BADARG;
     ZK_TRY(mailbox_bulk(mb, 0));
-    VecLeavesArgs lv;
-    memset(&lv, 0, sizeof lv);
+    VecLeavesArgs lv{};
+    if (ints) lv.ints = *ints;
     lv.njobs = njobs;
     lv.words = mb->words;
     lv.ticket = ticket;
@@ -239,15 +251,19 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
             total += cnt[q];
             more = true;
         }
-        lv.job[q] = VecLeavesJob{j.v, j.stride, j.n, cnt[q], out, blocks};
+        lv.job[q] = VecLeavesJob{j.v, j.stride, j.n, cnt[q], out, blocks, j.from};
         in[q] = out;
         blocks += (uint32_t)div_up(cnt[q], 64);
     }
     lv.seq = more ? 0 : seq;
     lv.groups = blocks;
-    // the pair of wavefronts per 64 leaves pays while the wavefronts do not outnumber the SIMDs (see the kernel)
-    if (blocks <= kPipedLeafGroups) hipLaunchKernelGGL(k_vec_leaves_piped, dim3((blocks + 1) / 2), dim3(256), 0, stream, lv);
-    else hipLaunchKernelGGL(k_vec_leaves, dim3(blocks), dim3(64), 0, stream, lv);
+    int mode = kLeafPlain;
+    for (int q = 0; q < njobs; ++q)
+        if (jobs[q].from.rows) mode = jobs[q].from.S ? kLeafRowsCheck : ints ? kLeafRowsInts : kLeafRows;
+    if (mode == kLeafRowsCheck) launch_leaves<kLeafRowsCheck>(lv, stream);
+    else if (mode == kLeafRowsInts) launch_leaves<kLeafRowsInts>(lv, stream);
+    else if (mode == kLeafRows) launch_leaves<kLeafRows>(lv, stream);
+    else launch_leaves<kLeafPlain>(lv, stream);
     // up the trees, all rows in one launch, a factor of up to kTreeChunk per launch
     while (more) {
         DigestTreeArgs tr;
@@ -305,6 +321,9 @@ static uint32_t hash_capacity(size_t N) {
     return (uint32_t)cap;
 }
 
+// Whether A is read off B by row (LeafGather) without being asked to: always with the tables whose rows stay in the L2.
+static bool gather_by_default(size_t N) { return N <= kLdsHistMaxRows; }
+
 static int carve_prove(ProveWs& w, Carver& cv, size_t D, size_t N) {
     w.A = cv.limbs(D);
     w.Sf = cv.limbs(D / 2 ? D / 2 : 1);
@@ -320,6 +339,8 @@ static int carve_prove(ProveWs& w, Carver& cv, size_t D, size_t N) {
     w.slots = (uint32_t*)cv.take((size_t)cap * 4);
     w.canon = (uint32_t*)cv.take(N * 4);
     w.rows = (uint4*)cv.take(N * 32);
+    w.rows_b = (uint4*)cv.take(N * 64);
+    w.found = gather_by_default(N) ? (uint32_t*)cv.take(D * 4) : nullptr;
     w.hist_parts = N <= kLdsHistMaxRows ? kHistParts : 0;
     w.hist = w.hist_parts ? (uint32_t*)cv.take((size_t)w.hist_parts * N * 4) : nullptr;
     w.flags = (uint32_t*)cv.take(64);
@@ -359,6 +380,10 @@ static size_t prove_ws_bytes_shapes(const size_t* D, const size_t* N, size_t K) 
         cv.take(EqPool::entries29(log2_floor(D[i])) * 36);
     }
     for (size_t i = 0; i < K; ++i) {
+        if (gather_by_default(N[i])) {
+            cv.take(batch_inverse_scratch_bytes(N[i]));
+            continue;
+        }
         size_t apart = batch_inverse_scratch_bytes(D[i]) + batch_inverse_scratch_bytes(N[i]),
                joined = batch_inverse_scratch_bytes(D[i] + N[i]);
         cv.take(apart > joined ? apart : joined);
@@ -377,13 +402,15 @@ static size_t prove_ws_bytes(size_t D, size_t N, size_t K = 1) {
 }
 
 // Multiplicities into w.m (and the digest leaves into w.leaves).  Returns
-// ZK_E_NOT_IN_TABLE with *bad_index set if some S_i is not in T.
-// With defer_check (hints given, workgroup histograms in use) the hints are
-// only range-checked here; S_i = T[idx_i] is then checked by the caller.
+// ZK_E_NOT_IN_TABLE with *bad_index set if some S_i is not in T.  Without hints
+// the rows are left in `found`, if the caller wants them.
+// With defer_check (hints given, workgroup histograms in use) the hints are taken
+// as they are; S_i = T[idx_i] is then checked by the caller.
 static bool can_defer_check(const ProveWs& w, const uint32_t* idx, size_t D) { return w.hist && idx && D > (size_t)kBlock; }
 
 static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_t D, size_t N, uint64_t* bad_index,
-                      Mailbox* mb, hipStream_t stream, bool defer_check = false, bool counts_as_fr = false) {
+                      Mailbox* mb, hipStream_t stream, bool defer_check = false, bool counts_as_fr = false,
+                      uint32_t* found = nullptr) {
     if (defer_check && !can_defer_check(w, idx, D)) return ZK_E_BADARG;
     uint32_t cap = w.cap_mask + 1;
     hipLaunchKernelGGL(k_count_init, dim3(grid_for((size_t)cap + N + 4)), dim3(kBlock), 0, stream, w.slots, (size_t)cap, w.m,
@@ -409,18 +436,18 @@ static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_
         if (defer_check)
             hipLaunchKernelGGL(k_count_lds<false>, dim3(w.hist_parts), dim3(kHistThreads), lds_bytes, stream, w.m, w.hist,
                                S.limbs, S.stride, D, per_block, idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots,
-                               w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2));
+                               w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2), found);
         else
             hipLaunchKernelGGL(k_count_lds<true>, dim3(w.hist_parts), dim3(kHistThreads), lds_bytes, stream, w.m, w.hist,
                                S.limbs, S.stride, D, per_block, idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots,
-                               w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2));
+                               w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2), found);
         const uint32_t group = 16;
         hipLaunchKernelGGL(k_hist_reduce, dim3((unsigned)div_up(N, kBlock), (unsigned)div_up(w.hist_parts, group)),
                            dim3(kBlock), 0, stream, w.m, w.hist, w.hist_parts, group, (uint32_t)N);
     } else {
         hipLaunchKernelGGL(k_count, dim3(grid_for(D, kBlock, 8192)), dim3(kBlock), 0, stream, w.m, S.limbs, S.stride, D,
                            idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots, w.cap_mask, w.canon, w.flags,
-                           (unsigned long long*)(w.flags + 2));
+                           (unsigned long long*)(w.flags + 2), found);
     }
     hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(w.nleaves, 64)), dim3(64), 0, stream, w.leaves, w.m,
                        (uint32_t)N, w.nleaves);
@@ -438,19 +465,6 @@ static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_
         if (bad_index) *bad_index = bad;
         return ZK_E_NOT_IN_TABLE;
     }
-    return ZK_OK;
-}
-
-// Smallest i with S_i != row idx_i of the table (w.rows), or all ones.
-static int find_bad_row(ProveWs& w, fr_vec S, const SmallSource& ints, const uint32_t* idx, size_t D, size_t N,
-                        uint64_t* bad, hipStream_t stream) {
-    if (!S.limbs && !ints.x) return ZK_E_BADARG;
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(kBlock), 0, stream, w.flags + 2, (size_t)2, 0xffffffffu);
-    hipLaunchKernelGGL(k_check_rows, dim3(grid_for(D, kBlock, 16384)), dim3(kBlock), 0, stream, S.limbs, S.stride, D, idx,
-                       w.rows, (uint32_t)N, (unsigned long long*)(w.flags + 2), ints);
-    ZK_HIP_TRY(hipGetLastError());
-    ZK_HIP_TRY(hipMemcpyAsync(bad, w.flags + 2, 8, hipMemcpyDeviceToHost, stream));
-    ZK_HIP_TRY(hipStreamSynchronize(stream));
     return ZK_OK;
 }
 
@@ -504,7 +518,8 @@ struct Instance {
     host::F sA_prev[2];  // its last round's sums of A at X = 0, 1
     uint8_t md[32], dA[32], dB[32];
     BatchInverseJob job_a, job_b;
-    bool deferred = false;  // S_i = T[idx_i] is checked through sum A = sum m B after the first round, not while counting
+    bool gather = false;    // A is B by row, made while it is hashed
+    bool deferred = false;  // S_i = T[idx_i] is checked there too, not while counting
 };
 
 struct ProveCall {
@@ -516,7 +531,7 @@ struct ProveCall {
     bool batch = false;                    // batched transcript and proof layout
     bool multi = false;                    // batched, and the instances' shapes may differ (S[i].n, T[i].n)
     const fr_t* forced_beta = nullptr;
-    bool by_rows = false;                  // A as B[idx_i] instead of inverting beta + S_i
+    bool by_rows = false;                  // A as B[idx_i] whatever the table's length
     bool check_upfront = false;            // compare every S_i with its hinted row while counting (no deferred check)
     // S_0 given as small integers x + rho y (K = 1, hints required, S ignored): see tlookup_prove_small
     const int32_t* ints_x = nullptr;
@@ -785,7 +800,7 @@ static int prove_core(const ProveCall& c) {
     ProfileScope prof_total(kProfTotal, stream);
 
     // -- Prep: multiplicities and their digests -------------------------------------------------
-    bool defer_all = !c.by_rows && !c.check_upfront;
+    bool defer_all = !c.check_upfront;
     for (size_t i = 0; i < K; ++i) defer_all = defer_all && can_defer_check(inst[i].w, inst[i].idx, inst[i].D);
     if (from_ints && !defer_all) return ZK_E_BADARG;  // counting would read S as a vector
     for (size_t i = 0; i < K; ++i) {
@@ -793,11 +808,12 @@ static int prove_core(const ProveCall& c) {
         int rc;
         {
             ProfileScope prof(kProfCount, stream);
-            // with hints, the inverse vectors themselves tell whether S_i = T[idx_i] everywhere (see the first round);
-            // all instances or none, so that the first instance at fault is the one reported
-            inst[i].deferred = defer_all;
+            // with hints, S_i = T[idx_i] is checked while A is made and hashed; all instances or none, so that the first
+            // instance at fault is the one reported
+            inst[i].gather = c.by_rows || gather_by_default(inst[i].N);
+            inst[i].deferred = defer_all && inst[i].gather;
             rc = count_rows(inst[i].w, inst[i].S, inst[i].idx, inst[i].T, inst[i].D, inst[i].N, &bad, mb, stream,
-                            inst[i].deferred, true);
+                            inst[i].deferred, true, inst[i].idx ? nullptr : inst[i].w.found);
         }
         if (rc == ZK_E_NOT_IN_TABLE) {
             if (c.aux) c.aux->bad_index = bad;
@@ -831,11 +847,12 @@ static int prove_core(const ProveCall& c) {
     // -- Prove: beta, inverse vectors ---------------------------------------------------------------
     F beta = tr.challenge("beta");
     if (c.forced_beta) beta = from_canonical(*c.forced_beta);
-    if (!c.by_rows) {
+    {
         // all inversions share one wait: the down passes, one round trip, one host
-        // inversion (of the product of all grand totals), the up passes.  The table
-        // is inverted together with the tensor, as one vector, whenever the tensor's
-        // length allows (its small passes then cost nothing of their own).
+        // inversion (of the product of all grand totals), the up passes.  Usually the
+        // table's are the only ones (see LeafGather); a table too long for that is
+        // inverted together with its tensor, as one vector, if the tensor's length
+        // allows (its small passes then cost nothing of their own).
         ProfileScope prof(kProfInverse, stream);
         Carver inv_cv = cv;
         const uint32_t seq = mb->next_seq();
@@ -846,22 +863,20 @@ static int prove_core(const ProveCall& c) {
             Instance& I = inst[i];
             const size_t D = I.D, N = I.N;
             const uint32_t last = i + 1 == K ? seq : 0;
-            const bool joined = batch_inverse_can_join(D) && D > (size_t)kBlock;
-            if (joined) {
-                ZK_TRY(batch_inverse_begin(I.job_a, I.w.A, D, I.S.limbs, I.S.stride, D, beta, inv_cv, I.inv_words + 8,
-                                           mb->words, last, stream, I.w.B, N, I.T.limbs, I.T.stride, N,
-                                           from_ints ? &ints_src : nullptr));
-            } else {
+            const bool joined = !I.gather && batch_inverse_can_join(D, N);
+            if (!joined) {
                 ZK_TRY(batch_inverse_begin(I.job_b, I.w.B, N, I.T.limbs, I.T.stride, N, beta, inv_cv, I.inv_words, mb->words,
-                                           0, stream, nullptr, 0, nullptr, 0, 0));
+                                           I.gather ? last : 0, stream, nullptr, 0, nullptr, 0, 0));
                 jobs[njobs] = &I.job_b;
                 totals[njobs++] = I.inv_words;
-                ZK_TRY(batch_inverse_begin(I.job_a, I.w.A, D, I.S.limbs, I.S.stride, D, beta, inv_cv, I.inv_words + 8,
-                                           mb->words, last, stream, nullptr, 0, nullptr, 0, 0,
-                                           from_ints ? &ints_src : nullptr));
             }
-            jobs[njobs] = &I.job_a;
-            totals[njobs++] = I.inv_words + 8;
+            if (!I.gather) {
+                ZK_TRY(batch_inverse_begin(I.job_a, I.w.A, D, I.S.limbs, I.S.stride, D, beta, inv_cv, I.inv_words + 8,
+                                           mb->words, last, stream, joined ? I.w.B : nullptr, N, I.T.limbs, I.T.stride,
+                                           joined ? N : 0));
+                jobs[njobs] = &I.job_a;
+                totals[njobs++] = I.inv_words + 8;
+            }
         }
         ZK_TRY(mailbox_wait(mb, seq, stream));
         // inverse of each total from one inversion of their product
@@ -878,20 +893,11 @@ static int prove_core(const ProveCall& c) {
             suffix_inv = mul(suffix_inv, tot[q]);
             ZK_TRY(batch_inverse_end(*jobs[q], inv_q, stream));
         }
-    } else {
-        // every S_i has been checked to equal T[idx_i]: invert the table side only
-        // and read A off it (a zero beta + S_i is a zero beta + T[idx_i])
-        ProfileScope prof(kProfInverse, stream);
-        for (size_t i = 0; i < K; ++i) {
-            Instance& I = inst[i];
-            const size_t D = I.D, N = I.N;
-            Carver inv_cv = cv;
-            ZK_TRY(batch_inverse_run(I.w.B, N, I.T.limbs, I.T.stride, N, beta, inv_cv, mb, stream));
-            hipLaunchKernelGGL(k_rows_of, dim3(grid_for(N)), dim3(kBlock), 0, stream, I.w.rows, I.w.B, N, (uint32_t)N);
-            hipLaunchKernelGGL(k_gather_rows, dim3(grid_for(D, kBlock, 16384)), dim3(kBlock), 0, stream, I.w.A, D, D, I.idx,
-                               I.w.rows);
-            ZK_HIP_TRY(hipGetLastError());
-        }
+        for (size_t i = 0; i < K; ++i)
+            if (inst[i].gather)
+                hipLaunchKernelGGL(k_rows_of, dim3(grid_for(inst[i].N)), dim3(kBlock), 0, stream, inst[i].w.rows_b, inst[i].w.B,
+                                   inst[i].N, (uint32_t)inst[i].N);
+        ZK_HIP_TRY(hipGetLastError());
     }
 
     // The prover sends A and B before the sumcheck (Protocol 1, tlookup-Prove): their
@@ -903,10 +909,23 @@ static int prove_core(const ProveCall& c) {
         VecDigestJob jobs[2 * kMailboxMaxInstances];
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
-            jobs[2 * i] = VecDigestJob{I.w.A, I.D, I.D, I.w.dig_rows, nullptr, 0};
-            jobs[2 * i + 1] = VecDigestJob{I.w.B, I.N, I.N, I.w.dig_rows_b, nullptr, 0};
+            LeafGather from;
+            if (I.gather) {
+                from.rows = I.idx ? I.idx : I.w.found;
+                from.T = I.w.rows;
+                from.B = I.w.rows_b;
+                from.N = (uint32_t)I.N;
+                from.bad = (unsigned long long*)(I.w.flags + 2);
+                if (I.deferred) {
+                    from.S = I.S.limbs;  // null with integers
+                    from.ss = I.S.stride;
+                }
+            }
+            jobs[2 * i] = VecDigestJob{I.w.A, I.D, I.D, I.w.dig_rows, from};
+            jobs[2 * i + 1] = VecDigestJob{I.w.B, I.N, I.N, I.w.dig_rows_b, LeafGather()};
         }
-        ZK_TRY(vec_digest_launch(jobs, 2 * (int)K, dig_leaves, mb, seq, inst[0].w.flags + 1, stream));
+        ZK_TRY(vec_digest_launch(jobs, 2 * (int)K, dig_leaves, mb, seq, inst[0].w.flags + 1, stream,
+                                 from_ints ? &ints_src : nullptr));
         ZK_TRY(mailbox_wait(mb, seq, stream));
         for (size_t i = 0; i < K; ++i) {
             vec_digest_finish(inst[i].dA, jobs[2 * i]);
@@ -965,6 +984,8 @@ static int prove_core(const ProveCall& c) {
         }
         a.partials = I.w.partT;
         a.pstride = I.w.part_blocks * 6;
+        a.bad = I.w.flags + 2;
+        a.bad_words = mb->words + kMailboxBad + 2 * i;
         unsigned blocks = grid_for(N, kBlock * 4, kMaxPartialBlocks);
         hipLaunchKernelGGL(k_table_const, dim3(blocks), dim3(kBlock), 0, stream, a);
         // read back together with the first round's sums (or the final values)
@@ -972,14 +993,25 @@ static int prove_core(const ProveCall& c) {
         ZK_HIP_TRY(hipGetLastError());
     }
     bool table_consts_read = false;
-    auto read_table_consts = [&]() {
-        if (table_consts_read) return;
+    auto read_table_consts = [&]() -> int {
+        if (table_consts_read) return ZK_OK;
         for (size_t i = 0; i < K; ++i) {
+            uint64_t bad;
+            memcpy(&bad, mb->words + kMailboxBad + 2 * i, 8);
+            if (bad != UINT64_MAX) {  // found while A was made (LeafGather)
+                if (c.aux) c.aux->bad_index = bad;
+                if (c.baux) {
+                    c.baux->bad_instance = i;
+                    c.baux->bad_index = bad;
+                }
+                return ZK_E_NOT_IN_TABLE;
+            }
             inst[i].c1 = from_dev(inst[i].const_words);
             inst[i].c2 = from_dev(inst[i].const_words + 8);
             inst[i].cB = sub(mul(alpha2, inst[i].c1), inst[i].c2);
         }
         table_consts_read = true;
+        return ZK_OK;
     };
 
     // -- header -----------------------------------------------------------------------------------------
@@ -1374,7 +1406,7 @@ static int prove_core(const ProveCall& c) {
             if (!shared) I.inv_den = inv(mul(wD, e_side[side1 ? 0 : 1]));
         }
         if (any_launch && !host_round) ZK_TRY(mailbox_wait(mb, seq, stream));
-        if (k > 0 || any_launch) read_table_consts();
+        if (k > 0 || any_launch) ZK_TRY(read_table_consts());
 
         F e[4], g[4];
         line_values(e, e_side[0], e_side[1]);
@@ -1448,21 +1480,6 @@ static int prove_core(const ProveCall& c) {
             I.sA_prev[0] = sA0;
             I.sA_prev[1] = sA1;
             if (kk == 0) I.sum_A = add(sA0, sA1);
-            if (kk == 0 && I.deferred && !equal(I.sum_A, I.c2)) {
-                // The counts were taken from the hints without looking at S.  Had every
-                // S_i been the hinted row, sum_i 1/(beta+S_i) = sum_j m_j/(beta+T_j) would hold
-                // (Section 4, first form of the identity); it does not, so some S_i differs
-                // from its row: find the smallest such i by comparing them all.
-                uint64_t bad = UINT64_MAX;
-                ZK_TRY(find_bad_row(I.w, I.S, ints_src, I.idx, I.D, I.N, &bad, stream));
-                if (bad == UINT64_MAX) return ZK_E_HIP;  // the sums disagree although every row matches
-                if (c.aux) c.aux->bad_index = bad;
-                if (c.baux) {
-                    c.baux->bad_instance = i;
-                    c.baux->bad_index = bad;
-                }
-                return ZK_E_NOT_IN_TABLE;
-            }
             F q[4], sa[4], tq[4], tm[4];
             quad_values(q, q0, q1, qi);
             line_values(sa, sA0, sA1);
@@ -1520,7 +1537,7 @@ static int prove_core(const ProveCall& c) {
             ZK_TRY(mailbox_wait(mb, seq, stream));
         }
         ZK_HIP_TRY(hipStreamSynchronize(stream));  // everything of this call has left the device
-        read_table_consts();
+        ZK_TRY(read_table_consts());
         uint8_t* first = out;
         for (size_t i = 0; i < K; ++i) {
             for (int q = 0; q < 5; ++q) {
@@ -1722,8 +1739,8 @@ static int verify_core(const VerifyCall& c) {
         ZK_TRY(mailbox_bulk(mb, (size_t)nleaves * 32));  // before anything is on its way there
         VecDigestJob trees[2];
         int ntrees = 0;
-        if (have_a) trees[ntrees++] = VecDigestJob{wit->A.limbs, wit->A.stride, D, dig_rows, nullptr, 0};
-        if (have_b) trees[ntrees++] = VecDigestJob{wit->B.limbs, wit->B.stride, N, dig_rows_b, nullptr, 0};
+        if (have_a) trees[ntrees++] = VecDigestJob{wit->A.limbs, wit->A.stride, D, dig_rows, LeafGather()};
+        if (have_b) trees[ntrees++] = VecDigestJob{wit->B.limbs, wit->B.stride, N, dig_rows_b, LeafGather()};
         if (ntrees) ZK_TRY(vec_digest_launch(trees, ntrees, dig_leaves, mb, 0, dig_ticket, stream));
         MleJob jobs[kMleMaxJobs];
         int njobs = 0;

@@ -138,13 +138,15 @@ __device__ __forceinline__ void count_merged(uint32_t* m, uint32_t row, bool val
 }
 
 // m[row(S_i)] += 1.  With idx the row is given and only checked; without, it is
-// found through the hash.  The smallest offending i ends up in *bad.
+// found through the hash (and left in `found`, if the caller wants it).  The
+// smallest offending i ends up in *bad.
 static __global__ void __launch_bounds__(kBlock) k_count(uint32_t* m, const uint32_t* __restrict__ S, size_t ss, size_t D,
                                                   const uint32_t* __restrict__ idx, const uint32_t* __restrict__ T,
                                                   size_t ts, const uint4* __restrict__ rows, uint32_t N,
                                                   const uint32_t* __restrict__ slots,
                                                   uint32_t cap_mask, const uint32_t* __restrict__ canon,
-                                                  const uint32_t* __restrict__ dup_flag, unsigned long long* bad) {
+                                                  const uint32_t* __restrict__ dup_flag, unsigned long long* bad,
+                                                  uint32_t* __restrict__ found) {
     const bool dups = *dup_flag != 0;
     // every lane of a wavefront runs the same number of iterations, so the
     // cross-lane steps in count_merged see whole wavefronts
@@ -170,6 +172,7 @@ static __global__ void __launch_bounds__(kBlock) k_count(uint32_t* m, const uint
                 }
             } else {
                 row = hash_find_rows(slots, cap_mask, rows, v);
+                if (found) found[i] = row;
             }
             if (row == kEmptySlot) atomicMin(bad, (unsigned long long)i);
         }
@@ -194,14 +197,15 @@ static const int kHistThreads = 1024;
 static const uint32_t kHistPass = 60 * 1024;  // elements per pass, < 2^16
 
 // CHECK_S = false: rows are taken from the hints unchecked (an out-of-range hint
-// still counts as a failure); the comparison of every S_i with its row is then
-// the caller's business (it rides on the inversion's first pass over S).
+// is not counted); the comparison of every S_i with its row is then the caller's
+// business (it rides on the hash of A, which reads the rows: see LeafGather).
 template <bool CHECK_S>
 static __global__ void __launch_bounds__(kHistThreads)
 k_count_lds(uint32_t* m, uint32_t* __restrict__ part, const uint32_t* __restrict__ S, size_t ss, size_t D,
             size_t chunk, const uint32_t* __restrict__ idx, const uint32_t* __restrict__ T, size_t ts,
             const uint4* __restrict__ rows, uint32_t N, const uint32_t* __restrict__ slots, uint32_t cap_mask,
-            const uint32_t* __restrict__ canon, const uint32_t* __restrict__ dup_flag, unsigned long long* bad) {
+            const uint32_t* __restrict__ canon, const uint32_t* __restrict__ dup_flag, unsigned long long* bad,
+            uint32_t* __restrict__ found) {
     extern __shared__ uint32_t hist[];  // (N+1)/2 words, two 16-bit counters each
     const uint32_t words = (N + 1) / 2;
     const bool dups = *dup_flag != 0;
@@ -252,7 +256,10 @@ k_count_lds(uint32_t* m, uint32_t* __restrict__ part, const uint32_t* __restrict
                     }
                     row[e] = r;
                 } else {
-                    if constexpr (CHECK_S) row[e] = hash_find_rows(slots, cap_mask, rows, v[e]);
+                    if constexpr (CHECK_S) {
+                        row[e] = hash_find_rows(slots, cap_mask, rows, v[e]);
+                        if (found) found[i[e]] = row[e];
+                    }
                 }
                 // without the comparison a hint out of range is left for the caller's check to report
                 if (CHECK_S && row[e] == kEmptySlot) atomicMin(bad, (unsigned long long)i[e]);
@@ -338,47 +345,21 @@ static __global__ void __launch_bounds__(kBlock) k_hist_reduce(uint32_t* __restr
     if (acc) atomicAdd(&m[j], acc);
 }
 
-// Smallest index i whose S_i is not row idx_i of the table (or whose hint is out
-// of range) into *bad.  Only runs after the prover's sums have shown that there
-// is such an index.
-static __global__ void __launch_bounds__(kBlock) k_check_rows(const uint32_t* __restrict__ S, size_t ss, size_t D,
-                                                       const uint32_t* __restrict__ idx, const uint4* __restrict__ rows,
-                                                       uint32_t N, unsigned long long* bad, SmallSource ints) {
-    for (size_t i = blockIdx.x * (size_t)kBlock + threadIdx.x; i < D; i += (size_t)gridDim.x * kBlock) {
-        const uint32_t r = idx[i];
-        bool ok = r < N;
-        if (ok) {
-            Fr x;
-            if (ints.x) small_source_load(x.l, ints, i);
-            else x = fr_load(S, ss, i);
-            const uint4 lo = rows[2 * (size_t)r], hi = rows[2 * (size_t)r + 1];
-            ok = ((lo.x ^ x.l[0]) | (lo.y ^ x.l[1]) | (lo.z ^ x.l[2]) | (lo.w ^ x.l[3]) | (hi.x ^ x.l[4]) | (hi.y ^ x.l[5]) |
-                  (hi.z ^ x.l[6]) | (hi.w ^ x.l[7])) == 0;
-        }
-        if (!ok) atomicMin(bad, (unsigned long long)i);
-    }
-}
-
-// A_i = B[row_i]: with the row of every S_i known and checked, 1/(beta + S_i) is
-// the table-side inverse of that row.  B is read row-major (one 32-byte access per
-// element) from a copy written by k_rows_of.
+// Row j of B as sixteen consecutive words, so that reading it by number is one
+// 64-byte access: the element, then its canonical value as the hash takes it
+// (big-endian bytes of little-endian words).
 static __global__ void __launch_bounds__(kBlock) k_rows_of(uint4* __restrict__ rows, const uint32_t* __restrict__ B,
                                                     size_t bs, uint32_t N) {
     for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < N; j += gridDim.x * kBlock) {
-        Fr v = fr_load(B, bs, j);
-        rows[2 * j] = make_uint4(v.l[0], v.l[1], v.l[2], v.l[3]);
-        rows[2 * j + 1] = make_uint4(v.l[4], v.l[5], v.l[6], v.l[7]);
-    }
-}
-
-static __global__ void __launch_bounds__(kBlock) k_gather_rows(uint32_t* __restrict__ A, size_t as, size_t D,
-                                                        const uint32_t* __restrict__ idx,
-                                                        const uint4* __restrict__ rows) {
-    for (size_t i = blockIdx.x * (size_t)kBlock + threadIdx.x; i < D; i += (size_t)gridDim.x * kBlock) {
-        size_t r = idx[i];
-        uint4 lo = rows[2 * r], hi = rows[2 * r + 1];
-        Fr v = Fr{{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}};
-        fr_store(A, as, i, v);
+        const Fr v = fr_load(B, bs, j);
+        Fr c = fr_from_mont(v);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c.l[k] = __builtin_bswap32(c.l[k]);
+        uint4* at = rows + 4 * (size_t)j;
+        at[0] = make_uint4(v.l[0], v.l[1], v.l[2], v.l[3]);
+        at[1] = make_uint4(v.l[4], v.l[5], v.l[6], v.l[7]);
+        at[2] = make_uint4(c.l[0], c.l[1], c.l[2], c.l[3]);
+        at[3] = make_uint4(c.l[4], c.l[5], c.l[6], c.l[7]);
     }
 }
 
@@ -450,11 +431,36 @@ static const uint32_t kVecLeaf = 128;
 // All vectors of a call are hashed by one launch (a leaf is a chain of 65 dependent
 // blocks whatever the vector's length: one after the other, short vectors would
 // cost as much as long ones).
+//
+// A lookup's A need not be there yet.  S_i is the table's row rho_i, so A_i =
+// 1/(beta + S_i) is B[rho_i]: with a LeafGather the same pass reads B by row, writes
+// A, hashes it and, where the rows are the caller's hints, compares every S_i with
+// T[rho_i].  The hash is bound by instruction issue, so the 68 bytes per element this
+// moves ride under it, and the inversion of D elements (three multiplications and 160
+// bytes per element) becomes one of N.  For tables of up to 2^16 rows, whose row-major
+// copies (96 bytes per row) the caches hold.  Measured at 2^25 elements and 2^16 rows,
+// inversion and leaves: 2.32 ms (1.21 and 1.11) -> 1.14 ms (0.06 and 1.08).
+enum LeafMode {
+    kLeafPlain = 0,      // the vector is there
+    kLeafRows = 1,       // made by row, the rows known to be right
+    kLeafRowsCheck = 2,  // made by row, S compared with T's rows
+    kLeafRowsInts = 3    // the same with S_i from VecLeavesArgs::ints
+};
+struct LeafGather {
+    const uint32_t* rows = nullptr;    // row numbers; null: the vector itself is hashed
+    const uint32_t* S = nullptr;       // what kLeafRowsCheck compares
+    size_t ss = 0;
+    const uint4* T = nullptr;          // N rows, two uint4 each (k_canon_rows)
+    const uint4* B = nullptr;          // N rows, four uint4 each (k_rows_of)
+    uint32_t N = 0;
+    unsigned long long* bad = nullptr; // smallest i with S_i != T[row_i] or row_i >= N
+};
 struct VecLeavesJob {
-    const uint32_t* v;
+    uint32_t* v;           // read, or written with a LeafGather
     size_t stride, n, L;
     uint32_t* out;         // L digests; device memory, or pinned host memory if the host finishes the tree from here
     uint32_t first_group;  // of 64 leaves each
+    LeafGather from;
 };
 static const int kDigestMaxJobs = 16;  // A and B of eight instances
 struct VecLeavesArgs {
@@ -464,47 +470,158 @@ struct VecLeavesArgs {
     uint32_t* words;   // the mailbox, if this launch is the last to write results (seq != 0)
     uint32_t* ticket;
     uint32_t seq;
+    SmallSource ints;  // of the job that asks for it
 };
 
-// The sixteen words of block b of one leaf, as the hash takes them.  Elements are
-// asked for one block ahead: a block is some thousand instructions during which
-// their loads can be on the way.
-struct LeafBlocks {
-    const uint32_t* at;  // element 0 of the leaf
-    size_t stride, step;
-    uint32_t cnt;
-    Fr a, b;
+// The pointers of a job come out of an array, so the compiler does not know that
+// they are global memory; flat accesses would share a counter with the loads of the
+// round constants and be waited for long before they are needed.  An element's words
+// are addressed by a wave-uniform part (scalar registers) and the lane's byte offset:
+// as sixteen 64-bit addresses per lane they took the registers that the elements on
+// their way in need.
+typedef __attribute__((address_space(1))) uint32_t GlobalWord;
+typedef __attribute__((address_space(1))) char GlobalByte;
+typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) Vec4 GlobalVec4;
 
-    __device__ __forceinline__ void begin(const VecLeavesJob& job, size_t leaf) {
-        at = job.v + leaf;
-        stride = job.stride;
-        step = job.L;
-        cnt = (uint32_t)(job.n / job.L);  // kVecLeaf, or all n (a power of two) when n < kVecLeaf
-        a = fr_load(at, stride, 0);
-        b = cnt >= 2 ? fr_load(at, stride, step) : fr_zero();
+__device__ __forceinline__ GlobalWord* at_lane(const void* p, size_t uniform, uint32_t lane_bytes) {
+    return (GlobalWord*)((GlobalByte*)((GlobalWord*)p + uniform) + lane_bytes);
+}
+__device__ __forceinline__ Fr fr_load_lane(const uint32_t* p, size_t stride, size_t uniform, uint32_t lane_bytes) {
+    Fr a;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a.l[k] = *at_lane(p, uniform + k * stride, lane_bytes);
+    return a;
+}
+template <int STEP, int AT>
+__device__ __forceinline__ Fr fr_load_row(const uint4* table, uint32_t r) {
+    const GlobalVec4* rows = (const GlobalVec4*)table;
+    const Vec4 lo = rows[(size_t)STEP * r + AT], hi = rows[(size_t)STEP * r + AT + 1];
+    return Fr{{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}};
+}
+
+// The sixteen words of block b of one leaf, as the hash takes them.  Elements are
+// asked for one block ahead, row numbers two: a block is some thousand instructions
+// during which the loads can be on the way.
+template <int MODE>
+struct LeafBlocks {
+    VecLeavesJob job;
+    uint32_t lane_bytes;  // four times the leaf's number: there are at most 2^24 leaves
+    uint32_t cnt;
+    bool live;            // lanes past the last leaf read what the last one reads and write nothing
+    uint32_t row0, row1;    // row numbers of the two elements held,
+    uint32_t next0, next1;  // and of the two after them
+    uint32_t first_bad;     // the leaf's first element that is not its row
+    Fr x0, x1;              // with rows: in the words of the hash (y: the elements themselves)
+    Fr y0, y1;
+    struct Check {          // of an element's S with its row
+        Fr s, t;            // with integers, s holds the two of them
+    };
+
+    __device__ __forceinline__ uint32_t row_number(uint32_t i) const {
+        return MODE == kLeafPlain ? 0u : *at_lane(job.from.rows, i * job.L, lane_bytes);
+    }
+    __device__ __forceinline__ uint32_t in_table(uint32_t row) const { return row < job.from.N ? row : 0u; }
+    __device__ __forceinline__ void fetch(Fr& x, Fr& y, uint32_t i, uint32_t row) {
+        if constexpr (MODE == kLeafPlain) {
+            x = fr_load_lane(job.v, job.stride, i * job.L, lane_bytes);
+        } else {
+            y = fr_load_row<4, 0>(job.from.B, in_table(row));
+            x = fr_load_row<4, 2>(job.from.B, in_table(row));
+        }
+    }
+    // A's element on its way to memory
+    __device__ __forceinline__ void write(const Fr& x, uint32_t i) {
+        if (MODE == kLeafPlain || !live) return;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) *at_lane(job.v, i * job.L + k * job.stride, lane_bytes) = x.l[k];
+    }
+    __device__ __forceinline__ void check_ask(const SmallSource& ints, Check& c, uint32_t i, uint32_t row) {
+        if constexpr (MODE >= kLeafRowsCheck) c.t = fr_load_row<2, 0>(job.from.T, in_table(row));
+        if constexpr (MODE == kLeafRowsCheck) c.s = fr_load_lane(job.from.S, job.from.ss, i * job.L, lane_bytes);
+        if constexpr (MODE == kLeafRowsInts) {
+            c.s.l[0] = *at_lane(ints.x, i * job.L, lane_bytes);
+            c.s.l[1] = ints.y ? *at_lane(ints.y, i * job.L, lane_bytes) : 0u;
+        }
+    }
+    __device__ __forceinline__ void check(const SmallSource& ints, const Check& c, uint32_t i, uint32_t row) {
+        if constexpr (MODE >= kLeafRowsCheck) {
+            Fr s = c.s;
+            if constexpr (MODE == kLeafRowsInts) small_combine32(s.l, (int32_t)c.s.l[0], (int32_t)c.s.l[1], ints);
+            uint32_t diff = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) diff |= s.l[k] ^ c.t.l[k];
+            if ((diff || row >= job.from.N) && i < first_bad) first_bad = i;
+        }
+    }
+    __device__ __forceinline__ void report() {
+        if (MODE >= kLeafRowsCheck && live && first_bad < cnt)
+            atomicMin(job.from.bad, (unsigned long long)(first_bad * job.L + lane_bytes / 4));
+    }
+    __device__ __forceinline__ void words(uint32_t* w, const Fr& el) {
+        const Fr x = MODE == kLeafPlain ? fr_from_mont(el) : el;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[k] = MODE == kLeafPlain ? __builtin_bswap32(x.l[k]) : x.l[k];
+    }
+
+    __device__ __forceinline__ void begin(const VecLeavesJob& j, size_t which) {
+        job = j;
+        live = which < j.L;
+        lane_bytes = (uint32_t)(live ? which : j.L - 1) * 4;
+        cnt = (uint32_t)(j.n / j.L);  // kVecLeaf, or all n (a power of two) when n < kVecLeaf
+        const uint32_t last = cnt - 1;  // short vectors: places past the end read the last element again
+        row0 = row_number(0);
+        row1 = row_number(last < 1 ? last : 1);
+        next0 = row_number(last < 2 ? last : 2);
+        next1 = row_number(last < 3 ? last : 3);
+        first_bad = 0xffffffffu;
+        fetch(x0, y0, 0, row0);
+        fetch(x1, y1, last < 1 ? last : 1, row1);
     }
     __device__ __forceinline__ uint32_t blocks() const { return cnt / 2 + 1; }  // the last holds the padding
-    __device__ __forceinline__ void block(uint32_t (&w)[16], uint32_t index) {
-        const bool data = index < cnt / 2;
-        if (data || cnt == 1) {
-            const Fr x = fr_from_mont(a);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) w[k] = __builtin_bswap32(x.l[k]);
+    // The words of elements 2b and 2b+1; what follows is asked for before work() runs
+    // (the block's rounds, or the making of its schedule; in two halves), and the
+    // elements' checks ride on its halves: all at once their words took more registers
+    // than four wavefronts per SIMD leave (and spilled: 1.9 ms instead of 1.1 at 2^25 elements).
+    template <class First, class Second>
+    __device__ __forceinline__ void data_block(const SmallSource& ints, uint32_t (&w)[16], uint32_t b, First&& first, Second&& second) {
+        write(y0, 2 * b);
+        write(y1, 2 * b + 1);
+        words(w, x0);
+        words(w + 8, x1);
+        // past the end: the last two again
+        const uint32_t end = cnt - 2, i = 2 * b + 2 < end ? 2 * b + 2 : end, ii = i + 2 < end ? i + 2 : end;
+        fetch(x0, y0, i, next0);
+        fetch(x1, y1, i + 1, next1);
+        const uint32_t after0 = row_number(ii), after1 = row_number(ii + 1);
+        Check c;
+        check_ask(ints, c, 2 * b, row0);
+        __builtin_amdgcn_sched_barrier(0);  // asked for here, not where they are used
+        first();
+        __builtin_amdgcn_sched_barrier(0);
+        check(ints, c, 2 * b, row0);
+        check_ask(ints, c, 2 * b + 1, row1);
+        __builtin_amdgcn_sched_barrier(0);
+        second();
+        __builtin_amdgcn_sched_barrier(0);
+        check(ints, c, 2 * b + 1, row1);
+        row0 = next0;
+        row1 = next1;
+        next0 = after0;
+        next1 = after1;
+    }
+    __device__ __forceinline__ void last_block(const SmallSource& ints, uint32_t (&w)[16]) {
+        if (cnt == 1) {  // a vector of one element shares its block with the padding
+            Check c;
+            check_ask(ints, c, 0, row0);
+            write(y0, 0);
+            check(ints, c, 0, row0);
+            words(w, x0);
         }
-        if (data) {
-            const Fr y = fr_from_mont(b);
+        const int pad = cnt == 1 ? 8 : 0;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) w[8 + k] = __builtin_bswap32(y.l[k]);
-            if (2 * index + 3 < cnt) {
-                a = fr_load(at, stride, (2 * index + 2) * step);
-                b = fr_load(at, stride, (2 * index + 3) * step);
-            }
-        } else {
-            const int pad = cnt == 1 ? 8 : 0;  // a vector of one element shares its block with the padding
-#pragma unroll
-            for (int k = 0; k < 16; ++k)
-                if (k >= pad) w[k] = k == pad ? 0x80000000u : k == 15 ? cnt * 256u : 0u;
-        }
+        for (int k = 0; k < 16; ++k)
+            if (k >= pad) w[k] = k == pad ? 0x80000000u : k == 15 ? cnt * 256u : 0u;
     }
 };
 
@@ -524,37 +641,99 @@ __device__ __forceinline__ void leaves_done(const VecLeavesArgs& args) {
 }
 
 // Many leaves: one lane does all of a leaf.  Bound by instruction issue.
-static __global__ void __launch_bounds__(64) k_vec_leaves(VecLeavesArgs args) {
+template <int MODE>
+__device__ __forceinline__ void leaf_by_lane(const VecLeavesArgs& args, const VecLeavesJob& job, size_t leaf) {
+    LeafBlocks<MODE> src;
+    src.begin(job, leaf);
+    uint32_t h[8];
+    sha256_init(h);
+    uint32_t w[16];
+#pragma unroll 1
+    for (uint32_t b = 0; b + 1 < src.blocks(); ++b) {
+        uint32_t s[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s[i] = h[i];
+        src.data_block(args.ints, w, b, [&] { sha256_rounds<0, 32>(s, w); sha256_pin(s, w); }, [&] { sha256_rounds<32, 64>(s, w); });
+#pragma unroll
+        for (int i = 0; i < 8; ++i) h[i] += s[i];
+    }
+    src.last_block(args.ints, w);
+    src.report();
+    sha256_compress(h, w);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) job.out[leaf * 8 + k] = h[k];
+    if (args.seq) mailbox_written();
+}
+
+// MODE: of the jobs that have rows.
+template <int MODE>
+static __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) k_vec_leaves(VecLeavesArgs args) {
     const VecLeavesJob& job = leaves_job(args, blockIdx.x);
     const size_t leaf = (size_t)(blockIdx.x - job.first_group) * 64 + threadIdx.x;
     if (leaf < job.L) {
-        LeafBlocks src;
-        src.begin(job, leaf);
-        uint32_t h[8];
-        sha256_init(h);
-        for (uint32_t b = 0; b < src.blocks(); ++b) {
-            uint32_t w[16];
-            src.block(w, b);
-            sha256_compress(h, w);
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) job.out[leaf * 8 + k] = h[k];
-        if (args.seq) mailbox_written();
+        if (MODE != kLeafPlain && job.from.rows) leaf_by_lane<MODE>(args, job, leaf);
+        else leaf_by_lane<kLeafPlain>(args, job, leaf);
     }
     leaves_done(args);
 }
 
-// Few leaves (no more wavefronts than SIMDs): what counts is the length of one
-// leaf's chain, some 1750 instructions per block with conversion and message
-// schedule.  Two wavefronts share it: the second makes the schedule of the next
-// block (loads, conversion, expansion, round constants added) in LDS while the
-// first does the rounds of the current one, so that a block costs the rounds' 900
-// instructions.  A workgroup is two such pairs, one wavefront per SIMD: two
-// workgroups of one pair each were seen to share two SIMDs and leave two idle.
-// Measured at 2^20 elements (8192 leaves): 220 -> 140 us; above kPipedLeafGroups
-// the wavefronts would have to share SIMDs, and one lane per leaf is as fast.
-static const uint32_t kPipedLeafGroups = 512;
+// Few leaves: what counts is the length of one leaf's chain, some 1750 instructions
+// per block with conversion and message schedule.  Two wavefronts share it: the
+// second makes the schedule of the next block (loads, conversion, expansion, round
+// constants added) in LDS while the first does the rounds of the current one, so that
+// a block costs the rounds' 900 instructions.  A workgroup is two such pairs, one
+// wavefront per SIMD: two workgroups of one pair each were seen to share two SIMDs and
+// leave two idle.  Measured at 2^20 elements (8192 leaves): 220 -> 140 us.  Above
+// kPipedLeafGroups the wavefronts share SIMDs.  Where the words come ready from B's
+// rows one lane per leaf is then as fast (a tensor of 2^22 with its table, 520 groups:
+// 205 us, in pairs 239); where every element is converted or built from integers first, whose long
+// chains one wavefront per SIMD waits out, the pairs are still ahead at twice as many
+// (the same without rows: 408 us, in pairs 235; 2^23 entries from integers, 1032
+// groups: 608 us, in pairs 425).  At 2^25 elements, 1079 us against 1145 in pairs.
+static const uint32_t kPipedLeafGroups = 512, kPipedLeafGroupsConverting = 1040;
+template <int MODE>
+static bool leaves_in_pairs(uint32_t groups) {
+    return groups <= (MODE == kLeafPlain || MODE == kLeafRowsInts ? kPipedLeafGroupsConverting : kPipedLeafGroups);
+}
 
+// The second wavefront's part: the schedules of all blocks of its lanes' leaves.
+template <int MODE>
+__device__ __forceinline__ void leaf_schedules(const VecLeavesArgs& args, const VecLeavesJob& job, bool live, size_t leaf,
+                                               uint32_t blocks, uint32_t steps, uint4 (*kw)[16][64]) {
+    const int lane = threadIdx.x & 63;
+    LeafBlocks<MODE> src;
+    if (live) src.begin(job, leaf);
+    for (uint32_t b = 0; b <= steps; ++b) {  // one barrier more than blocks, as the wavefront of the rounds takes
+        if (b < blocks) {
+            uint32_t w[16];
+            const auto four_words = [&](int g) {
+                if (g >= 4) sha256_schedule4(w, 4 * g);
+                const int i = (4 * g) & 15;
+                kw[b & 1][g][lane] = make_uint4(w[i] + kShaK[4 * g], w[i + 1] + kShaK[4 * g + 1], w[i + 2] + kShaK[4 * g + 2],
+                                                w[i + 3] + kShaK[4 * g + 3]);
+            };
+            const auto first_half = [&] {
+#pragma unroll
+                for (int g = 0; g < 8; ++g) four_words(g);
+            };  // (stores to LDS: they stay where they are)
+            const auto second_half = [&] {
+#pragma unroll
+                for (int g = 8; g < 16; ++g) four_words(g);
+            };
+            if (b + 1 < blocks) {
+                src.data_block(args.ints, w, b, first_half, second_half);
+            } else {
+                src.last_block(args.ints, w);
+                src.report();
+                first_half();
+                second_half();
+            }
+        }
+        __syncthreads();
+    }
+}
+
+template <int MODE>
 static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs args) {
     __shared__ uint4 kw[2][2][16][64];  // [pair][buffer][four rounds][lane]
     const int lane = threadIdx.x & 63;
@@ -597,22 +776,8 @@ static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs a
             if (args.seq) mailbox_written();
         }
     } else {
-        LeafBlocks src;
-        if (live) src.begin(job, leaf < job.L ? leaf : job.L - 1);
-        for (uint32_t b = 0; b <= steps; ++b) {  // one barrier more than blocks, as the wavefront of the rounds takes
-            if (b < blocks) {
-                uint32_t w[16];
-                src.block(w, b);
-#pragma unroll
-                for (int g = 0; g < 16; ++g) {
-                    if (g >= 4) sha256_schedule4(w, 4 * g);
-                    const int i = (4 * g) & 15;
-                    kw[pair][b & 1][g][lane] = make_uint4(w[i] + kShaK[4 * g], w[i + 1] + kShaK[4 * g + 1],
-                                                          w[i + 2] + kShaK[4 * g + 2], w[i + 3] + kShaK[4 * g + 3]);
-                }
-            }
-            __syncthreads();
-        }
+        if (MODE != kLeafPlain && job.from.rows) leaf_schedules<MODE>(args, job, live, leaf, blocks, steps, kw[pair]);
+        else leaf_schedules<kLeafPlain>(args, job, live, leaf, blocks, steps, kw[pair]);
     }
     leaves_done(args);
 }
@@ -1239,10 +1404,16 @@ struct TableConstArgs {
     EqSplit eq;
     uint32_t* partials;  // 2 values per workgroup
     size_t pstride;
+    const uint32_t* bad;   // two words on their way to the host: the smallest index the hash of A has found at fault
+    uint32_t* bad_words;
 };
 
 static __global__ void __launch_bounds__(kBlock) k_table_const(TableConstArgs g) {
     __shared__ uint32_t lds[4 * 2 * 8];
+    if (blockIdx.x == 0 && threadIdx.x < 2) {
+        g.bad_words[threadIdx.x] = g.bad[threadIdx.x];
+        mailbox_written();
+    }
     Fr tot[2] = {fr_zero(), fr_zero()};
     const size_t lo_mask = ((size_t)1 << g.eq.lbits) - 1;
     for (size_t j = blockIdx.x * (size_t)kBlock + threadIdx.x; j < g.N; j += (size_t)gridDim.x * kBlock) {

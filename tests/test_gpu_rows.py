@@ -1,0 +1,76 @@
+"""A read off B by row while it is hashed (LeafGather in csrc/tlookup_kernels.h), at the lengths where its leaves change
+shape: a single element, leaves shorter than 128, one block of lanes that is not full, more than one; with and without
+row numbers, from strided tensors, and with a wrong element first, last and in a lane of its own.  The table-side
+inversion at the lengths where its levels change.  Exact arithmetic: equality with the oracle."""
+import random
+
+import numpy as np
+import pytest
+import torch
+
+from tests.pyref import R
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def zk():
+    import paper_2404_16109_amd as zk
+    assert torch.cuda.is_available()
+    return zk
+
+
+def _instance(orc, zk, D, N, seed):
+    rng = random.Random(seed)
+    Tb = orc.to_bytes([rng.randrange(R) for _ in range(N)])
+    rows = np.random.default_rng(seed).integers(0, N, size=D)
+    Sb = Tb[rows]
+    Sv = zk.Vec(D, D + 3)
+    Sv.data[:, :D].copy_(zk.vec_from_bytes(Sb).data[:, :D])
+    return Sb, Tb, Sv, zk.vec_from_bytes(Tb), torch.from_numpy(rows.astype(np.int32)).cuda()
+
+
+@pytest.mark.parametrize("D,N", [(1, 1), (2, 1), (2, 2), (4, 2), (64, 64), (128, 16), (256, 256), (512, 4), (1 << 13, 512),
+                                 (1 << 14, 2)])
+def test_every_entry_point(zk, orc, D, N):
+    seed = bytes([D % 251, N % 251]) * 16
+    Sb, Tb, Sv, Tv, idx = _instance(orc, zk, D, N, D + N)
+    rc, want, _ = orc.tlookup_prove(seed, Sb, Tb)
+    assert rc == 0
+    for name, call in (("hints", lambda: zk.tlookup_prove(seed, Sv, idx, Tv)),
+                       ("found", lambda: zk.tlookup_prove(seed, Sv, None, Tv)),
+                       ("checked", lambda: zk.tlookup_prove_checked(seed, Sv, idx, Tv)),
+                       ("rows", lambda: zk.tlookup_prove_by_rows(seed, Sv, idx, Tv))):
+        rc, proof, _ = call()
+        assert rc == 0 and proof == want, name
+
+
+@pytest.mark.parametrize("D", [512, 1 << 13])
+def test_wrong_elements(zk, orc, D):
+    Sb, Tb, Sv, Tv, idx = _instance(orc, zk, D, 64, D)
+    outsider = zk.vec_from_bytes(orc.to_bytes([12345]))
+    for places in ((D - 1,), (0,), (D - 1, D // 2 + 1), (D // 2 + 3, D // 2 + 1, D - 2)):
+        bad = zk.Vec(D)
+        bad.data.copy_(Sv.data[:, :D])
+        for p in places:
+            bad.data[:, p].copy_(outsider.data[:, 0])
+        for call in (zk.tlookup_prove, zk.tlookup_prove_by_rows):
+            rc, _, info = call(b"\x05" * 32, bad, idx, Tv)
+            assert rc == zk.ZK_E_NOT_IN_TABLE and info["bad_index"] == min(places)
+        wrong = idx.clone()
+        for p in places:
+            wrong[p] = 1 << 30
+        rc, _, info = zk.tlookup_prove(b"\x05" * 32, Sv, wrong, Tv)
+        assert rc == zk.ZK_E_NOT_IN_TABLE and info["bad_index"] == min(places)
+
+
+@pytest.mark.parametrize("n", [256, 257, 512, 513, (1 << 16) - 1, 1 << 16, (1 << 17) - 1, 1 << 17, (1 << 17) + 1])
+def test_inversion_levels(zk, orc, n):
+    rows = np.random.default_rng(n).integers(0, 256, size=(n, 32), dtype=np.uint8)
+    rows[:, 31] &= 0x3F
+    v, w, p = zk.vec_from_bytes(rows), zk.Vec(n), zk.Vec(n)
+    assert zk.fr_batch_inverse(w, v) == 0
+    assert zk.fr_mul(p, v, w) == 0
+    want = np.zeros((n, 32), dtype=np.uint8)
+    want[:, 0] = 1
+    assert np.array_equal(zk.vec_to_bytes(p), want)
