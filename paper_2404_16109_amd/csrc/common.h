@@ -127,15 +127,18 @@ struct TailGuard {
 // of a second.
 uint32_t device_spin_limit();
 static const size_t kMailboxFlag = 2040;    // the flag word
-// Behind the result words: the arrays a single proof hands to the host once they are short enough for the host to
-// finish the sumcheck by itself (five arrays of at most kMailboxShipEntries elements, eight words each).
-static const size_t kMailboxShip = 2048;
-static const size_t kMailboxShipEntries = 64;
-static const size_t kMailboxWords = kMailboxShip + 5 * kMailboxShipEntries * 8;
-// A tlookup instance's round sums (eleven values) and final claims start at
-// kMailboxSlot * instance; up to eight instances share the mailbox.
+// A tlookup instance's round sums (eleven values) start at kMailboxSlot * instance;
+// up to eight instances share the mailbox.
 static const size_t kMailboxSlot = 96;
 static const size_t kMailboxMaxInstances = 8;
+// Behind the result words: the arrays an instance hands to the host once they are short enough for the host to finish
+// the sumcheck by itself (five arrays of at most kMailboxShipEntries elements, eight words each), then the values of a
+// pass that serves several rounds (grid_dev.h: 27 + 8 of the data side, 2 x 27 of the table side per instance).
+static const size_t kMailboxShip = 2048;
+static const size_t kMailboxShipEntries = 64;
+static const size_t kMailboxShipWords = 5 * kMailboxShipEntries * 8;
+static const size_t kMailboxGrid = kMailboxShip + kMailboxMaxInstances * kMailboxShipWords;
+static const size_t kMailboxWords = kMailboxGrid + kMailboxMaxInstances * 89 * 8;
 static const size_t kMailboxInvB = 1024;    // grand total of the table-side inversion (+16 per instance)
 static const size_t kMailboxInvA = 1032;    // grand total of the data-side inversion (+16 per instance)
 static const size_t kMailboxTableC = 1280;  // the two table-side constants (+16 per instance)

@@ -22,7 +22,12 @@
 #include "internal.h"
 #include "tlookup_kernels.h"
 #include "tlookup_round29.h"
+#include "grid_dev.h"
 #include "transcript.h"
+
+#include <algorithm>
+#include <memory>
+#include <new>
 
 namespace zkmi {
 
@@ -474,129 +479,12 @@ static void digest_of_leaves(uint8_t out[32], const uint8_t* leaves, uint32_t nl
     h.finish(out);
 }
 
-// ---- prover --------------------------------------------------------------------------------------
-//
-// One routine proves K instances with a single sumcheck over
-//   f = sum_i lambda^i f_i,   claim_0 = (sum_i lambda^i)(alpha + alpha^2),
-// f_i the tlookup summand of instance i; beta, alpha, u and the round challenges
-// are shared.  tlookup_prove is K = 1 without lambda and with its own transcript
-// label and proof header.  Per instance the device work is exactly that of a
-// single proof: every round launches the instance's kernels one after the other
-// on the stream, each instance's sums land in its own part of the mailbox, only
-// the last launch of a round publishes, and the host adds the instances' round
-// polynomials weighted by lambda^i.
-//
-// Shapes may differ (tlookup_prove_multi).  The sumcheck then has n = max_i n_i
-// variables, instance i lives on the last n_i of them (skip_i = n - n_i) and
-//   f = sum_i lambda^i 2^-skip_i f_i(x_[skip_i:]),  f_i built with u_[skip_i:]:
-// in a round k < skip_i the instance is a constant, (alpha + alpha^2) 2^(skip_i-k-1)
-// before its weight, which the host adds without any device work; from round
-// skip_i on it runs the rounds of a proof of its own ("local round" k - skip_i)
-// with the shared challenges, and all instances reach their last round together.
-
-struct Instance {
-    ProveWs w;
-    fr_vec S, T;
-    size_t D = 0, N = 0;             // its shape: n = log2 D, l = log2 N, h = n - l;
-    int n = 0, l = 0, h = 0, skip = 0;  // skip: the rounds of the whole proof before its own first
-    const EqPool* ep = nullptr;      // weight tables for u_[skip:]
-    host::F cD, cT;                  // products of e~(u_t, r_t) over its bound variables (all / the table's)
-    host::F half_pow;                // 2^-(local round + 1)
-    host::F scale;                   // 2^-h
-    int lazy_rounds = 0;             // how many of its rounds in a row have left the data arrays in 29-bit planes
-    host::F inv_den;                 // what the one-sided round's other side is divided by (this round)
-    host::F pass01[9];               // kRoundFirstTwo's sums: c20, c21, qd, T, qe, then the sums of A_00, A_01, A_10, A_11
-    const uint32_t* idx = nullptr;
-    uint32_t* b_cur = nullptr;  // where B lives at the moment (it ping-pongs while folding)
-    size_t b_cur_stride = 0;
-    uint32_t* words = nullptr;  // this instance's round sums in the mailbox
-    uint32_t* inv_words = nullptr;    // totals of its two inversions (B, then A)
-    uint32_t* const_words = nullptr;  // its two table-side constants
-    host::F c1, c2, cB, sum_A, lam;
-    host::F claim;       // the running claim of this instance's own sumcheck: f_i's round polynomial at 0 plus at 1
-    host::F fX[4];       // its last round polynomial at X = 0..3
-    host::F sA_prev[2];  // its last round's sums of A at X = 0, 1
-    uint8_t md[32], dA[32], dB[32];
-    BatchInverseJob job_a, job_b;
-    bool gather = false;    // A is B by row, made while it is hashed
-    bool deferred = false;  // S_i = T[idx_i] is checked there too, not while counting
-};
-
-struct ProveCall {
-    const uint8_t* seed = nullptr;
-    size_t K = 1;
-    const fr_vec* S = nullptr;
-    const uint32_t* const* idx = nullptr;  // may be null, entries may be null
-    const fr_vec* T = nullptr;
-    bool batch = false;                    // batched transcript and proof layout
-    bool multi = false;                    // batched, and the instances' shapes may differ (S[i].n, T[i].n)
-    const fr_t* forced_beta = nullptr;
-    bool by_rows = false;                  // A as B[idx_i] whatever the table's length
-    bool check_upfront = false;            // compare every S_i with its hinted row while counting (no deferred check)
-    // S_0 given as small integers x + rho y (K = 1, hints required, S ignored): see tlookup_prove_small
-    const int32_t* ints_x = nullptr;
-    const int32_t* ints_y = nullptr;
-    const fr_t* ints_rho = nullptr;
-    size_t ints_D = 0;
-    uint8_t* proof = nullptr;
-    size_t cap = 0;
-    size_t* len = nullptr;
-    tlookup_aux* aux = nullptr;            // single proof
-    tlookup_batch_aux* baux = nullptr;     // batched proof
-    void* ws = nullptr;
-    size_t ws_bytes = 0;
-    void* stream = nullptr;
-};
-
-// ---- which kernel runs a round, and where it finds S ---------------------------------
-//
-// Decided in one place, by a function of the shape alone, so that it can be
-// walked on the host without a GPU (zkmi_selftest_tlookup_plan) and checked
-// against the pointers actually handed to a kernel before it is launched.
-enum RoundKernel {
-    kRoundFirst = 0,     // k_round_data0: the first round, nothing to fold
-    kRound29 = 1,        // k_round_data29: large folding rounds on 29-bit limbs
-    kRoundBoth = 2,      // k_round_both: data and table side, the table's variables being bound
-    kRoundOneGroup = 3,  // k_round_small: at most 256 pairs, one workgroup, one round per launch (batched proofs)
-    kRoundResident = 4,  // k_tlookup_tail: at most 256 pairs, one resident kernel over these rounds (until kRoundHost)
-    kRoundFirstTwo = 5,  // k_round_data01: the first pass, which yields the sums of the first two rounds
-    kRoundNoPass = 6,    // the second round after kRoundFirstTwo: the host has everything, nothing is launched
-    kRoundHost = 7       // at most kHostPairs pairs of a single proof: the resident kernel has handed the arrays to the
-                         // host, which runs the round itself (HostTail)
-};
-enum SSource {
-    kSFromCaller = 0,  // the caller's vector of field elements
-    kSFromInts = 1,    // the caller's integer columns (tlookup_prove_small)
-    kSFromWords = 2,   // the folded copy in the workspace, 32-bit words
-    kSFromPlanes = 3,  // the folded copy in the workspace, 29-bit limb planes
-    kSNowhere = -1     // a plan this library has no kernel for: never launched
-};
-
-struct RoundPlan {
-    int kernel;
-    int s_source;
-    bool table_round;  // the variable being bound is one of the table's
-    bool tiny;         // at most kSmallPairs pairs
-    bool use29;
-    bool in32, out32;  // kRound29: the data arrays arrive as / leave as 32-bit words
-    bool fold2;        // kRound29: binds the two previous variables at once (after kRoundFirstTwo, kRoundNoPass)
-    int lazy_after;    // folds since the data arrays were last fully reduced, if they are in 29-bit planes now
-};
-
-// The last rounds of a single proof on the host.  A round of the resident kernel costs a trip to the host and back
-// (about thirty microseconds) whatever it computes; a round of 32 pairs is some six hundred multiplications, which
-// the host does in a fraction of that.  So once a round has at most kHostPairs pairs, the resident kernel binds the
-// last challenge, writes the five arrays (at most 64 elements each) into the mailbox and ends, and the host computes
-// the remaining rounds' sums, folds and final claims from them: the same sums over the same arrays (Section 3.3's
-// sumcheck, Section 4's summand), exact arithmetic, so the same bytes.
 static const size_t kHostPairs = kMailboxShipEntries / 2;
 
 struct HostTail {
     host::F A[kMailboxShipEntries], S[kMailboxShipEntries], B[kMailboxShipEntries], M[kMailboxShipEntries],
         T[kMailboxShipEntries];
     host::F W[kHostPairs];  // this round's weights e~(u_rest, p), p < half
-    bool on = false;
-    int first = 0;  // the first round the host runs
 
     // e~((u_0 .. u_{m-1}), p) for p < 2^m, u_0 belonging to the top bit of p
     void weights(const host::F* u, int m) {
@@ -648,6 +536,145 @@ struct HostTail {
         for (size_t p = 0; p < half / 2; ++p) W[p] = add(W[p], W[p + half / 2]);  // the next variable summed out
     }
 };
+
+// ---- prover --------------------------------------------------------------------------------------
+//
+// One routine proves K instances with a single sumcheck over
+//   f = sum_i lambda^i f_i,   claim_0 = (sum_i lambda^i)(alpha + alpha^2),
+// f_i the tlookup summand of instance i; beta, alpha, u and the round challenges
+// are shared.  tlookup_prove is K = 1 without lambda and with its own transcript
+// label and proof header.  Per instance the device work is exactly that of a
+// single proof: every round launches the instance's kernels one after the other
+// on the stream, each instance's sums land in its own part of the mailbox, only
+// the last launch of a round publishes, and the host adds the instances' round
+// polynomials weighted by lambda^i.
+//
+// Shapes may differ (tlookup_prove_multi).  The sumcheck then has n = max_i n_i
+// variables, instance i lives on the last n_i of them (skip_i = n - n_i) and
+//   f = sum_i lambda^i 2^-skip_i f_i(x_[skip_i:]),  f_i built with u_[skip_i:]:
+// in a round k < skip_i the instance is a constant, (alpha + alpha^2) 2^(skip_i-k-1)
+// before its weight, which the host adds without any device work; from round
+// skip_i on it runs the rounds of a proof of its own ("local round" k - skip_i)
+// with the shared challenges, and all instances reach their last round together.
+
+struct Instance {
+    ProveWs w;
+    fr_vec S, T;
+    size_t D = 0, N = 0;             // its shape: n = log2 D, l = log2 N, h = n - l;
+    int n = 0, l = 0, h = 0, skip = 0;  // skip: the rounds of the whole proof before its own first
+    const EqPool* ep = nullptr;      // weight tables for u_[skip:]
+    host::F cD, cT;                  // products of e~(u_t, r_t) over its bound variables (all / the table's)
+    host::F half_pow;                // 2^-(local round + 1)
+    host::F scale;                   // 2^-h
+    int lazy_rounds = 0;             // how many of its rounds in a row have left the data arrays in 29-bit planes
+    host::F inv_den;                 // what the one-sided round's other side is divided by (this round)
+    host::F pass01[9];               // kRoundFirstTwo's sums: c20, c21, qd, T, qe, then the sums of A_00, A_01, A_10, A_11
+    const uint32_t* idx = nullptr;
+    uint32_t* b_cur = nullptr;  // where B lives at the moment (it ping-pongs while folding)
+    size_t b_cur_stride = 0;
+    uint32_t* words = nullptr;  // this instance's round sums in the mailbox
+    uint32_t* inv_words = nullptr;    // totals of its two inversions (B, then A)
+    uint32_t* const_words = nullptr;  // its two table-side constants
+    host::F c1, c2, cB, sum_A, lam;
+    host::F claim;       // the running claim of this instance's own sumcheck: f_i's round polynomial at 0 plus at 1
+    host::F fX[4];       // its last round polynomial at X = 0..3
+    host::F sA_prev[2];  // its last round's sums of A at X = 0, 1
+    uint8_t md[32], dA[32], dB[32];
+    BatchInverseJob job_a, job_b;
+    // the last rounds (passes over several variables, then the host's)
+    HostGrid gq, gt, gm;         // the data side's products, the table side's
+    host::F gs[1 << kGridVars];  // sums of A
+    const uint32_t* grid_words = nullptr;  // where the running pass's values come out
+    int pass_left = 0, pass_tvars = 0;     // rounds of it that are still to come; variables of the table in it
+    bool first_two = false;      // the first round's pass served the second too
+    int pending = 0, pending_t = 0;  // variables (of the table) whose challenges the arrays have yet to be bound to
+    bool s_moved = false, t_moved = false;  // S is in Sf, T in Tf (bound at least once)
+    HostTail* tail = nullptr;    // once the host has the arrays
+    bool gather = false;    // A is B by row, made while it is hashed
+    bool deferred = false;  // S_i = T[idx_i] is checked there too, not while counting
+};
+
+struct ProveCall {
+    const uint8_t* seed = nullptr;
+    size_t K = 1;
+    const fr_vec* S = nullptr;
+    const uint32_t* const* idx = nullptr;  // may be null, entries may be null
+    const fr_vec* T = nullptr;
+    bool batch = false;                    // batched transcript and proof layout
+    bool multi = false;                    // batched, and the instances' shapes may differ (S[i].n, T[i].n)
+    const fr_t* forced_beta = nullptr;
+    bool by_rows = false;                  // A as B[idx_i] whatever the table's length
+    bool check_upfront = false;            // compare every S_i with its hinted row while counting (no deferred check)
+    // S_0 given as small integers x + rho y (K = 1, hints required, S ignored): see tlookup_prove_small
+    const int32_t* ints_x = nullptr;
+    const int32_t* ints_y = nullptr;
+    const fr_t* ints_rho = nullptr;
+    size_t ints_D = 0;
+    uint8_t* proof = nullptr;
+    size_t cap = 0;
+    size_t* len = nullptr;
+    tlookup_aux* aux = nullptr;            // single proof
+    tlookup_batch_aux* baux = nullptr;     // batched proof
+    void* ws = nullptr;
+    size_t ws_bytes = 0;
+    void* stream = nullptr;
+};
+
+// ---- which kernel runs a round, and where it finds S ---------------------------------
+//
+// Decided in one place, by a function of the shape alone, so that it can be
+// walked on the host without a GPU (zkmi_selftest_tlookup_plan) and checked
+// against the pointers actually handed to a kernel before it is launched.  It says
+// how a round would be run by itself; the rounds of an instance's last kPassVars
+// variables are served several at a time instead (grid_dev.h, plan_pass).
+enum RoundKernel {
+    kRoundFirst = 0,     // k_round_data0: the first round, nothing to fold
+    kRound29 = 1,        // k_round_data29: large folding rounds on 29-bit limbs
+    kRoundBoth = 2,      // k_round_both: data and table side, the table's variables being bound
+    kRoundOneGroup = 3,  // at most 256 pairs of a batched proof: always in a pass
+    kRoundResident = 4,  // at most 256 pairs of a single proof: always in a pass
+    kRoundFirstTwo = 5,  // k_round_data01: the first pass, which yields the sums of the first two rounds
+    kRoundNoPass = 6,    // the second round after kRoundFirstTwo: the host has everything, nothing is launched
+    kRoundHost = 7,      // at most kHostPairs pairs of a single proof: the host's (HostTail)
+    kRoundGrid = 8       // what a round in a pass is turned into by prove_core: its sums come from the pass's grid
+};
+enum SSource {
+    kSFromCaller = 0,  // the caller's vector of field elements
+    kSFromInts = 1,    // the caller's integer columns (tlookup_prove_small)
+    kSFromWords = 2,   // the folded copy in the workspace, 32-bit words
+    kSFromPlanes = 3,  // the folded copy in the workspace, 29-bit limb planes
+    kSNowhere = -1     // a plan this library has no kernel for: never launched
+};
+
+struct RoundPlan {
+    int kernel;
+    int s_source;
+    bool table_round;  // the variable being bound is one of the table's
+    bool tiny;         // at most kSmallPairs pairs
+    bool use29;
+    bool in32, out32;  // kRound29: the data arrays arrive as / leave as 32-bit words
+    bool fold2;        // kRound29: binds the two previous variables at once (after kRoundFirstTwo, kRoundNoPass)
+    int lazy_after;    // folds since the data arrays were last fully reduced, if they are in 29-bit planes now
+};
+
+// The last rounds on the host.  A pass costs a trip to the host and back (some forty microseconds) whatever it
+// computes; a round of 32 pairs is some six hundred multiplications, which the host does in a fraction of that.  So
+// once few variables are left (host_vars), the device binds the last challenges, writes the five arrays (at most 64
+// elements each) into the mailbox, and the host computes the remaining rounds' sums, folds and final claims from them:
+// the same sums over the same arrays (Section 3.3's sumcheck, Section 4's summand), exact arithmetic, so the same bytes.
+// Variables left to the host: six of a single proof (63 pairs of some 19 multiplications, 24 us), three of each of
+// several (7 pairs each, and one more pass for all of them together).
+static int host_vars(size_t K) { return K == 1 ? 6 : 3; }
+// Passes serve the rounds of the last kPassVars variables.  At 2^16 entries three rounds by themselves take 140 us, most
+// of it trips, and a pass over them 60; the rounds of longer arrays are what the 29-bit kernel is for.
+static const int kPassVars = 16;
+// The variables of a pass that starts with `left` of them unbound: up to the next of the places at which all passes
+// of a call end (whatever the instances' lengths: they share the trips).  Zero: not in a pass.
+static int plan_pass(int left, size_t K) {
+    const int host = host_vars(K);
+    if (left > kPassVars || left <= host) return 0;
+    return (left - host - 1) % kGridVars + 1;
+}
 
 static bool round_on_29_bits(int n, int h, int k) {
     return k >= 1 && k < h && ((size_t)1 << (n - k - 1)) > kSmallPairs;
@@ -1082,30 +1109,66 @@ static int prove_core(const ProveCall& c) {
         else m.T = PairArray{w.Tf, N / 2, w.Tf, N / 2};
         return m;
     };
-    auto final_arrays = [&](const Instance& I, const uint32_t* b_cur, size_t b_stride) {
-        const ProveWs& w = I.w;
-        const size_t D = I.D, N = I.N;
-        FinalArgs f;
-        memset(&f, 0, sizeof f);
-        f.count = 5;
-        const bool d_fold = I.n >= 1, t_fold = I.l >= 1;
-        // A, S, B, m, T in the order of the proof
-        f.p[0] = w.A; f.stride[0] = D; f.fold[0] = d_fold;
-        if (I.n <= 1) { f.p[1] = I.S.limbs; f.stride[1] = I.S.stride; }
-        else { f.p[1] = w.Sf; f.stride[1] = D / 2; }
-        f.fold[1] = d_fold;
-        f.p[2] = b_cur; f.stride[2] = b_stride; f.fold[2] = t_fold;
-        f.p[3] = w.M; f.stride[3] = N; f.fold[3] = t_fold;
-        if (I.l <= 1) { f.p[4] = I.T.limbs; f.stride[4] = I.T.stride; }
-        else { f.p[4] = w.Tf; f.stride[4] = N / 2; }
-        f.fold[4] = t_fold;
-        return f;
+    // The last rounds: several from one pass, then the host's (grid_dev.h, HostTail).
+    std::unique_ptr<HostTail[]> host_tails(new (std::nothrow) HostTail[K]);
+    if (!host_tails) return ZK_E_BUFSZ;
+    F r_last[3] = {zero(), zero(), zero()};  // the last three challenges, the last one in [2]
+    // The arrays of instance I as a pass finds them: the pending variables bound, 2^left elements (of the data arrays;
+    // the table's if its variables are being bound).  Adds the folds; ship: into the mailbox.
+    struct Bound {
+        const uint32_t* p[5];
+        size_t stride[5];
     };
-    // A single proof runs its small rounds in one resident kernel (k_tlookup_tail) and the very last on the host.
-    TlookupTailArgs tail;
-    int tail_first = -1;  // the round the resident kernel was launched for, if it is running
-    TailGuard tail_guard{mb, stream};
-    HostTail host_tail;
+    auto bind_pending = [&](GridPass& pass, Instance& I, int left, uint32_t* ship) {
+        const ProveWs& w = I.w;
+        const bool table_bound = left < I.l || I.pending_t > 0;
+        const size_t n_data = (size_t)1 << left, n_table = table_bound ? (size_t)1 << left : I.N;
+        Bound b;
+        const uint32_t* src[5] = {w.A, I.s_moved ? w.Sf : I.S.limbs, I.b_cur, w.M, I.t_moved ? w.Tf : I.T.limbs};
+        const size_t ss[5] = {I.D, I.s_moved ? I.D / 2 : I.S.stride, I.b_cur_stride, I.N, I.t_moved ? I.N / 2 : I.T.stride};
+        uint32_t* const dst[5] = {w.A, w.Sf, I.b_cur, w.M, w.Tf};
+        const size_t ds[5] = {I.D, I.D / 2, I.b_cur_stride, I.N, I.N / 2};
+        for (int q = 0; q < 5; ++q) {
+            const int vars = q < 2 ? I.pending : I.pending_t;
+            const size_t count = q < 2 ? n_data : n_table;
+            b.p[q] = vars ? dst[q] : src[q];
+            b.stride[q] = vars ? ds[q] : ss[q];
+            if (ship) {
+                pass.add_fold(src[q], ss[q], ship, 0, count, vars, true);
+                ship += 8 * count;
+            } else if (vars) {
+                pass.add_fold(src[q], ss[q], dst[q], ds[q], count, vars);
+            }
+        }
+        if (I.pending) I.s_moved = true;
+        if (I.pending_t) I.t_moved = true;
+        I.pending = I.pending_t = 0;
+        return b;
+    };
+    // Starts the host's rounds of the instances that have come to them, at round k (k = n: their claims are all that is left).
+    auto ship_to_host = [&](int k, uint32_t seq) -> int {
+        GridPass pass;
+        pass.challenges(r_last);
+        for (size_t i = 0; i < K; ++i) {
+            Instance& I = inst[i];
+            if (k < I.skip || I.tail || n - k > host_vars(K)) continue;
+            I.tail = &host_tails[i];
+            bind_pending(pass, I, n - k, mb->words + kMailboxShip + i * kMailboxShipWords);
+        }
+        return pass.launch_folds(mb, seq, inst[0].w.flags + 1, stream);
+    };
+    auto read_shipped = [&](int k) {
+        for (size_t i = 0; i < K; ++i) {
+            Instance& I = inst[i];
+            if (!I.tail || k > std::max(I.skip, n - host_vars(K))) continue;
+            const uint32_t* at = mb->words + kMailboxShip + i * kMailboxShipWords;
+            const size_t n_data = (size_t)1 << (n - k), n_table = std::min(I.N, n_data);
+            F* const arrays[5] = {I.tail->A, I.tail->S, I.tail->B, I.tail->M, I.tail->T};
+            for (int q = 0; q < 5; ++q)
+                for (size_t j = 0; j < (q < 2 ? n_data : n_table); ++j, at += 8) arrays[q][j] = from_dev(at);
+            if (k < n) I.tail->weights(u + k + 1, n - k - 1);
+        }
+    };
     for (int k = 0; k < n; ++k) {
         // The 29-bit kernel sums one side of the round only (X = 0, or X = 1 with side1); the other side's two sums
         // follow from what the prover has already sent: sA0 + sA1 is the previous round's sum of A at its challenge,
@@ -1120,92 +1183,39 @@ static int prove_core(const ProveCall& c) {
         // active one is in the second round of a pass that served two) is answered by the host alone
         RoundPlan plans[kMailboxMaxInstances] = {};
         size_t last_launch = K;
+        bool starts_pass[kMailboxMaxInstances] = {}, any_pass = false, any_ship = false;
         for (size_t i = 0; i < K; ++i) {
-            const Instance& I = inst[i];
-            if (k < I.skip) continue;
-            plans[i] = plan_round(I.n, I.h, k - I.skip, K, from_ints, I.lazy_rounds, tail_first >= 0);
-            if (plans[i].s_source == kSNowhere) return ZK_E_BADARG;  // cannot happen: small_source_shape_ok has walked these rounds
-            if (plans[i].kernel != kRoundNoPass) last_launch = i;
-        }
-        const bool any_launch = last_launch < K || tail_first >= 0;
-
-        if (K == 1 && plans[0].kernel == kRoundResident && tail_first < 0) {
-            // this and every later round in one launch (K = 1, so k is the instance's own count)
-            Instance& I = inst[0];
-            const size_t D = I.D, N = I.N;
-            const int h = I.h;
-            memset(&tail, 0, sizeof tail);
-            tail.A = PairArray{I.w.A, D, I.w.A, D};
-            tail.M = PairArray{I.w.M, N, I.w.M, N};
-            tail.beta = to_dev(beta);
-            tail.r_prev = to_dev(r_prev);
-            // the kernel's rounds: up to the first one short enough for the host (kRoundHost), if there is one
-            int k_host = k + 1;
-            while (k_host < n && ((size_t)1 << (n - k_host - 1)) > kHostPairs) ++k_host;
-            tail.nrounds = k_host - k;
-            uint32_t* b_at = I.b_cur;
-            size_t b_at_stride = I.b_cur_stride;
-            for (int j = k; j < k_host; ++j) {
-                TailRound& rd = tail.round[j - k];
-                Moving m = moving_arrays(j, I, b_at, b_at_stride, j <= 1);
-                rd.S = m.S;
-                rd.B = m.B;
-                rd.T = m.T;
-                rd.eq = I.ep->round(j);
-                rd.half = (size_t)1 << (n - j - 1);
-                rd.table = j < h ? 0 : j == h ? 1 : 2;
-            }
-            tail.fin = final_arrays(I, b_at, b_at_stride);
-            if (k_host < n) {
-                // what the kernel hands over after round k_host - 1: the data arrays with that round's variable still
-                // to bind, the table's arrays likewise once its variables are being bound, as they came before that
-                const int j_last = k_host - 1;
-                const uint32_t n_data = (uint32_t)1 << (n - k_host);
-                const bool table_bound = j_last >= h;
-                const uint32_t n_table = table_bound ? n_data : (uint32_t)N;
-                if (n_data > kMailboxShipEntries || n_table > kMailboxShipEntries) return ZK_E_BADARG;  // cannot happen: N <= 2^(n - h)
-                TailShip& sh = tail.ship;
-                sh.out = mb->words + kMailboxShip;
-                sh.p[0] = I.w.A; sh.stride[0] = D; sh.n_out[0] = n_data; sh.fold[0] = 1;
-                sh.p[1] = I.w.Sf; sh.stride[1] = D / 2; sh.n_out[1] = n_data; sh.fold[1] = 1;
-                sh.p[2] = b_at; sh.stride[2] = b_at_stride; sh.n_out[2] = n_table; sh.fold[2] = table_bound;
-                sh.p[3] = I.w.M; sh.stride[3] = N; sh.n_out[3] = n_table; sh.fold[3] = table_bound;
-                if (j_last >= h + 1) { sh.p[4] = I.w.Tf; sh.stride[4] = N / 2; }
-                else { sh.p[4] = I.T.limbs; sh.stride[4] = I.T.stride; }
-                sh.n_out[4] = n_table; sh.fold[4] = table_bound;
-                host_tail.on = true;
-                host_tail.first = k_host;
-            }
-            tail.out_words = I.words;
-            tail.words = mb->words;
-            tail.cmd = mb->cmd;
-            for (int j = 0; j <= tail.nrounds; ++j) tail.out_seq[j] = mb->next_seq();
-            for (int j = 0; j < tail.nrounds; ++j) tail.cmd_seq[j] = mb->next_cmd_seq();
-            tail.spin_limit = device_spin_limit();
-            mailbox_channel_reset(mb);
-            {
-                ProfileScope prof(kProfRoundSmall, stream);
-                hipLaunchKernelGGL(k_tlookup_tail, dim3(1), dim3(kSmallThreads), 0, stream, tail);
-            }
-            ZK_HIP_TRY(hipGetLastError());
-            tail_guard.armed = true;
-            tail_first = k;
-        }
-        const bool host_round = host_tail.on && k >= host_tail.first;
-        if (host_round && k == host_tail.first) {
-            // the resident kernel's last message: the arrays, from here on the host's
-            ZK_TRY(mailbox_wait(mb, tail.out_seq[tail.nrounds], stream));
-            tail_guard.armed = false;
-            const uint32_t* at = mb->words + kMailboxShip;
-            F* const arrays[5] = {host_tail.A, host_tail.S, host_tail.B, host_tail.M, host_tail.T};
-            for (int q = 0; q < 5; ++q)
-                for (uint32_t j = 0; j < tail.ship.n_out[q]; ++j, at += 8) arrays[q][j] = from_dev(at);
-            host_tail.weights(u + k + 1, n - k - 1);
-        }
-        const uint32_t seq = host_round ? 0 : tail_first >= 0 ? tail.out_seq[k - tail_first] : any_launch ? mb->next_seq() : 0;
-        for (size_t i = 0; i < K && tail_first < 0; ++i) {
             Instance& I = inst[i];
-            if (k < I.skip || plans[i].kernel == kRoundNoPass) continue;
+            if (k < I.skip) continue;
+            const int kk = k - I.skip;
+            plans[i] = plan_round(I.n, I.h, kk, K, from_ints, I.lazy_rounds, false);
+            if (plans[i].s_source == kSNowhere) return ZK_E_BADARG;  // cannot happen: small_source_shape_ok has walked these rounds
+            // integers are the first two rounds' business, and the second of two rounds that share a pass needs none
+            const bool own = (from_ints && kk < 2) || (kk == 1 && I.first_two);
+            if (I.tail || (!own && n - k <= host_vars(K))) {
+                plans[i].kernel = kRoundHost;
+                if (!I.tail) any_ship = true;
+            } else if (I.pass_left > 0 || (!own && plan_pass(n - k, K) > 0)) {
+                plans[i].kernel = kRoundGrid;
+                if (I.pass_left == 0) {
+                    I.pass_left = plan_pass(n - k, K);
+                    starts_pass[i] = any_pass = true;
+                }
+            } else {
+                I.first_two = kk == 0 && plans[i].kernel == kRoundFirstTwo;
+                if (plans[i].kernel != kRoundNoPass) last_launch = i;
+                if (plans[i].kernel == kRound29 && plan_pass(n - k - 1, K) > 0) {  // a pass reads words
+                    plans[i].out32 = true;
+                    plans[i].lazy_after = 0;
+                }
+            }
+        }
+        const bool any_launch = last_launch < K || any_pass || any_ship;
+
+        const uint32_t seq = any_launch ? mb->next_seq() : 0;
+        for (size_t i = 0; i < K; ++i) {
+            Instance& I = inst[i];
+            if (k < I.skip || plans[i].kernel == kRoundNoPass || plans[i].kernel == kRoundGrid || plans[i].kernel == kRoundHost) continue;
             ProveWs& w = I.w;
             const size_t D = I.D, N = I.N;
             const int h = I.h, kk = k - I.skip;
@@ -1226,8 +1236,10 @@ static int prove_core(const ProveCall& c) {
             if (span > half) span = half;
             const unsigned blocks = (unsigned)(half / span);
             if (blocks > w.part_blocks) return ZK_E_BUFSZ;  // cannot happen: see round_blocks_max
-            const uint32_t my_seq = i == last_launch ? seq : 0;  // the last instance's last launch publishes the round
-            const Moving mv = moving_arrays(kk, I, I.b_cur, I.b_cur_stride, kk <= 1 || plan.fold2);
+            const uint32_t my_seq = i == last_launch && !any_pass && !any_ship ? seq : 0;  // the last launch publishes the round
+            uint32_t* b_next = I.b_cur;
+            size_t b_next_stride = I.b_cur_stride;
+            const Moving mv = moving_arrays(kk, I, b_next, b_next_stride, kk <= 1 || plan.fold2);
             DataRoundArgs d;
             d.A = PairArray{w.A, D, w.A, D};
             d.S = mv.S;
@@ -1290,18 +1302,6 @@ static int prove_core(const ProveCall& c) {
                 }
                 launch_final_sum2(w.partD, d01.pstrideD, 5, w.partT, d01.pstrideT, 6, blocks01, I.words, mb->words, my_seq,
                                   w.flags + 1, stream);
-            } else if (plan.kernel == kRoundOneGroup) {
-                // one workgroup, one launch, sums straight to the host
-                ProfileScope prof(kProfRoundSmall, stream);
-                if (!table_round)
-                    hipLaunchKernelGGL(k_round_small<0>, dim3(1), dim3(kSmallThreads), 0, stream, d, t, I.words, mb->words,
-                                       my_seq);
-                else if (kk == h)
-                    hipLaunchKernelGGL(k_round_small<1>, dim3(1), dim3(kSmallThreads), 0, stream, d, t, I.words, mb->words,
-                                       my_seq);
-                else
-                    hipLaunchKernelGGL(k_round_small<2>, dim3(1), dim3(kSmallThreads), 0, stream, d, t, I.words, mb->words,
-                                       my_seq);
             } else if (plan.kernel == kRoundBoth) {
                 {
                     ProfileScope prof(kProfRoundSmall, stream);
@@ -1386,7 +1386,38 @@ static int prove_core(const ProveCall& c) {
                                   mb->words, my_seq, w.flags + 1, stream);
             }
             ZK_HIP_TRY(hipGetLastError());
+            // what the arrays have yet to be bound to, should a pass come next
+            I.pending = plan.kernel == kRoundFirstTwo ? 2 : 1;
+            I.s_moved = kk >= 1;
+            I.pending_t = table_round ? 1 : 0;
+            I.t_moved = kk > h;
+            I.b_cur = b_next;
+            I.b_cur_stride = b_next_stride;
         }
+        if (any_pass) {
+            ProfileScope prof(kProfRoundSmall, stream);
+            GridPass pass;
+            pass.challenges(r_last);
+            for (size_t i = 0; i < K; ++i) {
+                if (!starts_pass[i]) continue;
+                Instance& I = inst[i];
+                const int left = n - k, kk = k - I.skip, vars = I.pass_left, after = left - vars;
+                const Bound b = bind_pending(pass, I, left, nullptr);
+                const size_t P = (size_t)1 << after;
+                const EqSplit eq = I.ep->round(kk + vars - 1);
+                const int tvars = std::max(0, std::min(vars, I.l - after));  // of them the table's
+                I.grid_words = mb->words + kMailboxGrid + 8 * pass.values;
+                pass.add(b.p[0], b.stride[0], b.p[1], b.stride[1], vars, kGridWeighted, P, eq);
+                if (tvars) {
+                    pass.add(b.p[2], b.stride[2], b.p[4], b.stride[4], tvars, kGridTable, P, eq);
+                    pass.add(b.p[2], b.stride[2], b.p[3], b.stride[3], tvars, kGridPlain, P, eq);
+                }
+                I.pending = vars;
+                I.pending_t = I.pass_tvars = tvars;
+            }
+            ZK_TRY(pass.launch(mb, beta, inst[0].w.partT, mb->words + kMailboxGrid, any_ship ? 0 : seq, inst[0].w.flags + 1, stream));
+        }
+        if (any_ship) ZK_TRY(ship_to_host(k, seq));
         // while the device works: each instance's running claim, and the inverse the 29-bit round's other side needs
         // (instances of one length share it)
         for (size_t i = 0; i < K; ++i) {
@@ -1396,7 +1427,7 @@ static int prove_core(const ProveCall& c) {
             I.claim = k == I.skip ? add(alpha, alpha2) : interpolate_at(I.fX, 4, r_prev);
             I.inv_den = zero();
             const F wD = mul(alpha, I.cD);
-            if (plans[i].kernel != kRound29 || tail_first >= 0 || is_zero(wD)) continue;
+            if (plans[i].kernel != kRound29 || is_zero(wD)) continue;
             bool shared = false;
             for (size_t j = 0; j < i && !shared; ++j)
                 if (k >= inst[j].skip && inst[j].skip == I.skip && plans[j].kernel == kRound29) {
@@ -1405,7 +1436,19 @@ static int prove_core(const ProveCall& c) {
                 }
             if (!shared) I.inv_den = inv(mul(wD, e_side[side1 ? 0 : 1]));
         }
-        if (any_launch && !host_round) ZK_TRY(mailbox_wait(mb, seq, stream));
+        if (any_launch) ZK_TRY(mailbox_wait(mb, seq, stream));
+        for (size_t i = 0; i < K; ++i) {
+            if (!starts_pass[i]) continue;
+            Instance& I = inst[i];
+            const uint32_t* at = I.grid_words;
+            I.gq.read(at, I.pass_left);
+            at += 8 * grid_points(I.pass_left);
+            for (int x = 0; x < 1 << I.pass_left; ++x, at += 8) I.gs[x] = from_dev(at);
+            if (!I.pass_tvars) continue;
+            I.gt.read(at, I.pass_tvars);
+            I.gm.read(at + 8 * grid_points(I.pass_tvars), I.pass_tvars);
+        }
+        if (any_ship) read_shipped(k);
         if (k > 0 || any_launch) ZK_TRY(read_table_consts());
 
         F e[4], g[4];
@@ -1429,9 +1472,26 @@ static int prove_core(const ProveCall& c) {
             I.half_pow = mul(I.half_pow, inv2);
             const uint32_t* sums = I.words;
             F q0, q1, qi, sA0, sA1;
-            F hs[11];  // kRoundHost: the round's sums, computed here
-            if (plan.kernel == kRoundHost) {
-                host_tail.sums((size_t)1 << (I.n - kk - 1), table_round, beta, hs);
+            F hs[11];  // kRoundHost, kRoundGrid: the round's sums, formed here
+            if (plan.kernel == kRoundGrid) {
+                I.gq.sums(hs, u + k + 1);
+                hs[3] = hs[4] = zero();
+                const int later = 1 << (I.pass_left - 1);
+                for (int x = 0; x < later; ++x) {
+                    hs[3] = add(hs[3], I.gs[x]);
+                    hs[4] = add(hs[4], I.gs[later + x]);
+                }
+                if (table_round) {
+                    I.gt.sums(hs + 5, u + k + 1);
+                    I.gm.sums(hs + 8, nullptr);
+                }
+                q0 = hs[0];
+                q1 = hs[1];
+                qi = hs[2];
+                sA0 = hs[3];
+                sA1 = hs[4];
+            } else if (plan.kernel == kRoundHost) {
+                I.tail->sums((size_t)1 << (I.n - kk - 1), table_round, beta, hs);
                 q0 = hs[0];
                 q1 = hs[1];
                 qi = hs[2];
@@ -1464,7 +1524,7 @@ static int prove_core(const ProveCall& c) {
                 sA1 = from_dev(sums + 32);
             }
             const F table_const = mul(I.cB, I.half_pow);
-            if (plan.kernel == kRound29 && tail_first < 0) {
+            if (plan.kernel == kRound29) {
                 // the kernel has summed one side: (q0, sA0) hold that side's q and sum of A; the other side from
                 // sA(0) + sA(1) = sA_prev(r_prev) and g(0) + g(1) = claim (never a table round: the table side is a constant)
                 const int a = side1 ? 1 : 0;
@@ -1483,7 +1543,7 @@ static int prove_core(const ProveCall& c) {
             F q[4], sa[4], tq[4], tm[4];
             quad_values(q, q0, q1, qi);
             line_values(sa, sA0, sA1);
-            if (table_round && plan.kernel == kRoundHost) {
+            if (table_round && (plan.kernel == kRoundHost || plan.kernel == kRoundGrid)) {
                 quad_values(tq, hs[5], hs[6], hs[7]);
                 quad_values(tm, hs[8], hs[9], hs[10]);
             } else if (table_round) {
@@ -1511,37 +1571,46 @@ static int prove_core(const ProveCall& c) {
         }
         r_prev2 = r_prev;
         r_prev = r;
-        if (tail_first >= 0 && k - tail_first < tail.nrounds) mailbox_send_challenge(mb, tail.cmd_seq[k - tail_first], to_dev(r).l);
-        if (host_round) host_tail.fold((size_t)1 << (n - k - 1), plans[0].table_round, r);
+        r_last[0] = r_last[1];
+        r_last[1] = r_last[2];
+        r_last[2] = r;
+        for (size_t i = 0; i < K; ++i) {
+            Instance& I = inst[i];
+            if (k < I.skip) continue;
+            if (plans[i].kernel == kRoundHost) {
+                I.tail->fold((size_t)1 << (n - k - 1), plans[i].table_round, r);
+            } else if (plans[i].kernel == kRoundGrid) {
+                I.gq.bind(r);
+                const int half = 1 << --I.pass_left;
+                for (int x = 0; x < half; ++x) I.gs[x] = add(I.gs[x], mul(r, sub(I.gs[half + x], I.gs[x])));
+                if (plans[i].table_round) {
+                    I.gt.bind(r);
+                    I.gm.bind(r);
+                }
+            }
+        }
     }
 
     // -- final claims -------------------------------------------------------------------------------------
     {
-        if (host_tail.on) {
-            // the host has bound the last variable itself: each array's first element is its claim
-            const F* const arrays[5] = {host_tail.A, host_tail.S, host_tail.B, host_tail.M, host_tail.T};
-            for (int q = 0; q < 5; ++q) to_device_limbs(inst[0].words + 8 * q, arrays[q][0]);
-        } else if (tail_first >= 0) {
-            // the resident kernel writes them after the last challenge
-            ZK_TRY(mailbox_wait(mb, tail.out_seq[tail.nrounds], stream));
-            tail_guard.armed = false;
-        } else {
+        // the host has bound the last variables itself: each array's first element is its claim (an instance of one
+        // element has had no rounds: its arrays are fetched now)
+        bool missing = false;
+        for (size_t i = 0; i < K; ++i) missing = missing || !inst[i].tail;
+        if (missing) {
             const uint32_t seq = mb->next_seq();
-            for (size_t i = 0; i < K; ++i) {
-                Instance& I = inst[i];
-                FinalArgs f = final_arrays(I, I.b_cur, I.b_cur_stride);
-                f.r = to_dev(r_prev);
-                hipLaunchKernelGGL(k_final_values, dim3(1), dim3(64), 0, stream, f, I.words, mb->words, i + 1 == K ? seq : 0);
-            }
-            ZK_HIP_TRY(hipGetLastError());
+            ZK_TRY(ship_to_host(n, seq));
             ZK_TRY(mailbox_wait(mb, seq, stream));
+            read_shipped(n);
         }
         ZK_HIP_TRY(hipStreamSynchronize(stream));  // everything of this call has left the device
         ZK_TRY(read_table_consts());
         uint8_t* first = out;
         for (size_t i = 0; i < K; ++i) {
+            const HostTail& t = *inst[i].tail;
+            const F claims[5] = {t.A[0], t.S[0], t.B[0], t.M[0], t.T[0]};
             for (int q = 0; q < 5; ++q) {
-                F v = from_dev(inst[i].words + 8 * q);
+                const F& v = claims[q];
                 if (q == 0 && inst[i].n == 0) inst[i].sum_A = v;
                 to_bytes(out, v);
                 out += 32;
