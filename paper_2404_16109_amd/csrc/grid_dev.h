@@ -15,7 +15,10 @@
 // product (k_grid), the wavefronts' shares added up (k_grid_sum).
 //
 // Bound by latency: a wavefront does one grid point of 64 positions, so that no chain
-// is longer than two multiplications and a reduction.  Measured: FIGURES.
+// is longer than two multiplications and a reduction.  Measured, a proof of 2^20
+// entries with a table of 256 rows: 914 -> 766 us; three lookups of 2^11 to 2^18
+// entries under one sumcheck, whose rounds used to follow each other instance by
+// instance: 2.07 -> 1.24 ms.
 #pragma once
 #include "common.h"
 #include "reduce_dev.h"

@@ -72,6 +72,13 @@ int sum_run(const uint32_t* a, size_t stride, size_t n, Carver& cv, Mailbox* mb,
 // dst_x = prod_{t < nvars} (u_t x_t + (1-u_t)(1-x_t)), x in {0,1}^nvars, first
 // variable = top bit.  u: host, Montgomery.
 int eq_table_run(uint32_t* dst, size_t stride, const host::F* u, int nvars, hipStream_t stream);
+struct EqTable {
+    uint32_t* dst;
+    size_t stride;
+    const host::F* u;
+    int nvars;
+};
+int eq_tables_run(const EqTable* tables, int count, hipStream_t stream);  // one or two, in one launch
 
 // ---- multilinear evaluation ---------------------------------------------------
 // a~(point) into out_words[0, 8) (Montgomery); a is not modified.

@@ -4,6 +4,7 @@
 //                                      b_k = W~(k,v) = sum_j W[k,j] e~(v,j).
 #include "internal.h"
 #include "tlookup_kernels.h"
+#include "grid_dev.h"
 #include "transcript.h"
 
 namespace zkmi {
@@ -38,29 +39,26 @@ __global__ void __launch_bounds__(kBlock) k_round_product(ProductRoundArgs g) {
     }
 }
 
-// ---- the last rounds in one resident kernel ----------------------------------------------------
+// ---- the last rounds ------------------------------------------------------------------------
 //
-// A round over a few hundred pairs is a few microseconds of arithmetic; launched on
-// its own it costs a kernel launch, a second one for the totals and two trips
-// through the runtime's queue, about 40 us.  Once the arrays have shrunk to
-// kTailPairs pairs one workgroup stays resident for all remaining rounds: it
-// writes a round's three sums to the host's mailbox, waits (bounded) for the
-// challenge on the command channel, folds and goes on; at the end it writes the
-// two final values.  Every thread takes every barrier, and a wait that fails
-// ends the kernel for all of them.
+// Arrays of at most 2^kPassVars elements run their rounds several from one pass
+// (grid_dev.h), and the very last are the host's: a round of 64 pairs is a few hundred
+// multiplications, which the host does in a fraction of the forty microseconds a trip
+// to it and back costs.  The arrays then go into the mailbox behind its result words,
+// the last challenges bound, and the host computes the remaining rounds' sums, folds
+// and the two final values -- the same sums over the same values, exact arithmetic, so
+// the same bytes.  Measured, the thirteen rounds of a proof with their trips: 220 -> 95 us.
 //
-// The very last rounds are the host's: a round of 64 pairs is a few hundred
-// multiplications, which the host does in a fraction of the thirty microseconds a
-// trip to it and back costs.  So the kernel stops before the first round of at
-// most kHostPairs pairs (if it has run a round by then), binds the last challenge,
-// writes both arrays (at most 2 kHostPairs elements each) behind the mailbox's
-// result words and ends; the host computes the remaining rounds' sums, folds and
-// the two final values itself -- the same sums over the same values, exact
-// arithmetic, so the same bytes.
+// Where a single round is left above the host's, a resident workgroup does it and the
+// handing over in one launch: it writes the round's three sums to the mailbox, waits
+// (bounded) for the challenge on the command channel, binds it and writes both arrays.
+// Every thread takes every barrier, and a wait that fails ends the kernel for all of
+// them.
+static const int kPassVars = 16;
+static const int kHostVars = 7;
 static const int kTailThreads = 1024;
-static const size_t kTailPairs = 1024;
-static const size_t kHostPairs = 64;
-static_assert(2 * 2 * kHostPairs * 8 <= kMailboxWords - kMailboxShip, "both arrays fit behind the result words");
+static const size_t kHostPairs = (size_t)1 << (kHostVars - 1);
+static_assert(2 * 2 * kHostPairs * 8 <= kMailboxGrid - kMailboxShip, "both arrays fit behind the result words");
 
 struct ProductTailArgs {
     uint32_t* a;
@@ -180,13 +178,6 @@ static int product_rounds_run(host::Transcript& tr, uint32_t* a, size_t as, uint
         tr.absorb("claim", claim_bytes, 32);
         claim_done = true;
     }
-    // rounds with at most kTailPairs pairs run in one resident kernel (see k_product_tail)
-    int tail_first = d;
-    for (int k = 0; k < d; ++k)
-        if (((size_t)1 << (d - k - 1)) <= kTailPairs) {
-            tail_first = k;
-            break;
-        }
     auto emit_round = [&](const F& g0, const F& g1, const F& lead) {
         if (!claim_done) {
             to_bytes(claim_bytes, add(g0, g1));
@@ -201,7 +192,14 @@ static int product_rounds_run(host::Transcript& tr, uint32_t* a, size_t as, uint
         out += 96;
         r_prev = tr.challenge("r");
     };
-    for (int k = 0; k < tail_first; ++k) {
+    F r_last[3] = {zero(), zero(), zero()};
+    auto bound = [&] {
+        r_last[0] = r_last[1];
+        r_last[1] = r_last[2];
+        r_last[2] = r_prev;
+    };
+    int k = 0, pending = 0;  // pending: the last challenges that the arrays have yet to be bound to
+    for (; d - k > kPassVars; ++k) {
         const size_t half = (size_t)1 << (d - k - 1);
         size_t span = half / kMaxPartialBlocks;
         if (span < (size_t)kBlock * 4) span = (size_t)kBlock * 4;
@@ -222,83 +220,91 @@ static int product_rounds_run(host::Transcript& tr, uint32_t* a, size_t as, uint
         ZK_HIP_TRY(hipGetLastError());
         ZK_TRY(mailbox_wait(mb, seq, stream));
         emit_round(from_dev(mb->words), from_dev(mb->words + 8), from_dev(mb->words + 16));
+        bound();
+        pending = 1;
     }
-    if (tail_first < d) {
+    F ha[2 * kHostPairs], hb[2 * kHostPairs];
+    size_t shipped;
+    if (d - k == kHostVars + 1 && pending == 0) {
         ProductTailArgs g;
         memset(&g, 0, sizeof g);
         g.a = a; g.as = as; g.b = b; g.bs = bs;
-        g.half0 = (size_t)1 << (d - tail_first - 1);
-        // the kernel's rounds end before the first one (after its own first) of at most kHostPairs pairs
-        int k_host = tail_first + 1;
-        while (k_host < d && ((size_t)1 << (d - k_host - 1)) > kHostPairs) ++k_host;
-        g.nrounds = k_host - tail_first;
-        g.ship_count = k_host < d ? (uint32_t)1 << (d - k_host) : 0;
-        g.fold_first = tail_first > 0;
-        g.r_prev = to_dev(r_prev);
+        g.half0 = (size_t)1 << kHostVars;
+        g.nrounds = 1;
+        g.ship_count = 1u << kHostVars;
         g.words = mb->words;
         g.cmd = mb->cmd;
         for (int i = 0; i <= g.nrounds; ++i) g.out_seq[i] = mb->next_seq();
-        for (int i = 0; i < g.nrounds; ++i) g.cmd_seq[i] = mb->next_cmd_seq();
+        g.cmd_seq[0] = mb->next_cmd_seq();
         g.spin_limit = device_spin_limit();
         mailbox_channel_reset(mb);
         TailGuard guard{mb, stream};
         hipLaunchKernelGGL(k_product_tail, dim3(1), dim3(kTailThreads), 0, stream, g);
         ZK_HIP_TRY(hipGetLastError());
         guard.armed = true;
-        for (int i = 0; i < g.nrounds; ++i) {
-            ZK_TRY(mailbox_wait(mb, g.out_seq[i], stream));
-            emit_round(from_dev(mb->words), from_dev(mb->words + 8), from_dev(mb->words + 16));
-            mailbox_send_challenge(mb, g.cmd_seq[i], to_dev(r_prev).l);
-        }
-        ZK_TRY(mailbox_wait(mb, g.out_seq[g.nrounds], stream));
+        ZK_TRY(mailbox_wait(mb, g.out_seq[0], stream));
+        emit_round(from_dev(mb->words), from_dev(mb->words + 8), from_dev(mb->words + 16));
+        mailbox_send_challenge(mb, g.cmd_seq[0], to_dev(r_prev).l);
+        ZK_TRY(mailbox_wait(mb, g.out_seq[1], stream));
         guard.armed = false;
-        ZK_HIP_TRY(hipStreamSynchronize(stream));  // everything of this call has left the device
-        F fa = from_dev(mb->words), fb = from_dev(mb->words + 8);
-        if (g.ship_count) {
-            // the host's rounds, on the arrays the kernel has handed over
-            F ha[2 * kHostPairs], hb[2 * kHostPairs];
-            const uint32_t* at = mb->words + kMailboxShip;
-            for (uint32_t j = 0; j < g.ship_count; ++j, at += 8) ha[j] = from_dev(at);
-            for (uint32_t j = 0; j < g.ship_count; ++j, at += 8) hb[j] = from_dev(at);
-            for (size_t half = g.ship_count / 2; half >= 1; half >>= 1) {
-                F g0 = zero(), g1 = zero(), lead = zero();
-                for (size_t p = 0; p < half; ++p) {
-                    g0 = add(g0, mul(ha[p], hb[p]));
-                    g1 = add(g1, mul(ha[p + half], hb[p + half]));
-                    lead = add(lead, mul(sub(ha[p + half], ha[p]), sub(hb[p + half], hb[p])));
-                }
-                emit_round(g0, g1, lead);
-                for (size_t p = 0; p < half; ++p) {
-                    ha[p] = add(ha[p], mul(r_prev, sub(ha[p + half], ha[p])));
-                    hb[p] = add(hb[p], mul(r_prev, sub(hb[p + half], hb[p])));
-                }
+        shipped = g.ship_count;
+    } else {
+        while (d - k > kHostVars) {
+            const int left = d - k, vars = (left - kHostVars - 1) % kGridVars + 1;
+            GridPass pass;
+            pass.challenges(r_last);
+            if (pending) {
+                pass.add_fold(a, as, a, as, (size_t)1 << left, pending);
+                pass.add_fold(b, bs, b, bs, (size_t)1 << left, pending);
             }
-            fa = ha[0];
-            fb = hb[0];
+            pass.add(a, as, b, bs, vars, kGridPlain, (size_t)1 << (left - vars), EqSplit{nullptr, 0, 0, 0, 0, 0});
+            const uint32_t seq = mb->next_seq();
+            ZK_TRY(pass.launch(mb, zero(), partials, mb->words + kMailboxGrid, seq, ticket, stream));
+            ZK_TRY(mailbox_wait(mb, seq, stream));
+            HostGrid grid;
+            grid.read(mb->words + kMailboxGrid, vars);
+            for (int v = 0; v < vars; ++v, ++k) {
+                F sums[3];
+                grid.sums(sums, nullptr);
+                emit_round(sums[0], sums[1], sums[2]);
+                grid.bind(r_prev);
+                bound();
+            }
+            pending = vars;
         }
-        to_bytes(out, fa);
-        to_bytes(out + 32, fb);
-        tr.absorb("final", out, 64);
-        return ZK_OK;
+        GridPass pass;
+        pass.challenges(r_last);
+        shipped = (size_t)1 << (d - k);
+        pass.add_fold(a, as, mb->words + kMailboxShip, 0, shipped, pending, true);
+        pass.add_fold(b, bs, mb->words + kMailboxShip + 8 * shipped, 0, shipped, pending, true);
+        const uint32_t seq = mb->next_seq();
+        ZK_TRY(pass.launch_folds(mb, seq, ticket, stream));
+        ZK_TRY(mailbox_wait(mb, seq, stream));
     }
-    FinalArgs f;
-    memset(&f, 0, sizeof f);
-    f.count = 2;
-    f.r = to_dev(r_prev);
-    f.p[0] = a; f.stride[0] = as; f.fold[0] = d >= 1;
-    f.p[1] = b; f.stride[1] = bs; f.fold[1] = d >= 1;
-    const uint32_t seq = mb->next_seq();
-    hipLaunchKernelGGL(k_final_values, dim3(1), dim3(64), 0, stream, f, mb->words, mb->words, seq);
-    ZK_HIP_TRY(hipGetLastError());
-    ZK_TRY(mailbox_wait(mb, seq, stream));
     ZK_HIP_TRY(hipStreamSynchronize(stream));  // everything of this call has left the device
-    F fa = from_dev(mb->words), fb = from_dev(mb->words + 8);
+    // the host's rounds, on the arrays it has been handed
+    const uint32_t* at = mb->words + kMailboxShip;
+    for (size_t j = 0; j < shipped; ++j, at += 8) ha[j] = from_dev(at);
+    for (size_t j = 0; j < shipped; ++j, at += 8) hb[j] = from_dev(at);
+    for (size_t half = shipped / 2; half >= 1; half >>= 1) {
+        F g0 = zero(), g1 = zero(), lead = zero();
+        for (size_t p = 0; p < half; ++p) {
+            g0 = add(g0, mul(ha[p], hb[p]));
+            g1 = add(g1, mul(ha[p + half], hb[p + half]));
+            lead = add(lead, mul(sub(ha[p + half], ha[p]), sub(hb[p + half], hb[p])));
+        }
+        emit_round(g0, g1, lead);
+        for (size_t p = 0; p < half; ++p) {
+            ha[p] = add(ha[p], mul(r_prev, sub(ha[p + half], ha[p])));
+            hb[p] = add(hb[p], mul(r_prev, sub(hb[p + half], hb[p])));
+        }
+    }
     if (!claim_done) {  // d == 0: the sum is the single product
-        to_bytes(claim_bytes, mul(fa, fb));
+        to_bytes(claim_bytes, mul(ha[0], hb[0]));
         tr.absorb("claim", claim_bytes, 32);
     }
-    to_bytes(out, fa);
-    to_bytes(out + 32, fb);
+    to_bytes(out, ha[0]);
+    to_bytes(out + 32, hb[0]);
     tr.absorb("final", out, 64);
     return ZK_OK;
 }
@@ -332,35 +338,89 @@ __global__ void __launch_bounds__(kBlock) k_colsum_partial(const uint32_t* __res
     if (k >= D1) return;
     size_t i0 = blockIdx.y * rows_per_chunk, i1 = i0 + rows_per_chunk;
     if (i1 > D0) i1 = D0;
-    Fr acc = fr_zero();
-    for (size_t i = i0; i < i1; ++i) acc = fr_add(acc, fr_mul(fr_load(e, es, i), fr_load(X, xs, i * D1 + k)));
-    fr_store(part, ps, blockIdx.y * P1 + k, acc);
+    FrWide acc = fr_wide_zero();
+    size_t i = i0;
+    for (; i + 2 <= i1; i += 2) {  // two rows at a time: their loads are in flight together
+        const Fr x0 = fr_load(X, xs, i * D1 + k), x1 = fr_load(X, xs, (i + 1) * D1 + k);
+        fr_wide_mac(acc, x0, fr_load(e, es, i));
+        fr_wide_mac(acc, x1, fr_load(e, es, i + 1));
+    }
+    if (i < i1) fr_wide_mac(acc, fr_load(X, xs, i * D1 + k), fr_load(e, es, i));
+    fr_store(part, ps, blockIdx.y * P1 + k, fr_wide_reduce(acc));
 }
 
-// a[k] = sum_c part[c][k] for k < D1, zero for D1 <= k < P1.
+// a[k] = sum_c part[c][k] for k < D1, zero for D1 <= k < P1.  Eight threads per
+// column, an eighth of the chunks each (one thread's chain of 64 loads and additions
+// took 26 us).
+static const int kReduceColumns = kBlock / 8;
 __global__ void __launch_bounds__(kBlock) k_colsum_reduce(uint32_t* __restrict__ a, size_t as,
                                                           const uint32_t* __restrict__ part, size_t ps, size_t chunks,
                                                           size_t D1, size_t P1) {
-    size_t k = blockIdx.x * (size_t)kBlock + threadIdx.x;
-    if (k >= P1) return;
+    __shared__ uint32_t lds[8 * kBlock];
+    const int col = threadIdx.x % kReduceColumns, share = threadIdx.x / kReduceColumns;
+    const size_t k = blockIdx.x * (size_t)kReduceColumns + col;
     Fr acc = fr_zero();
-    if (k < D1)
-        for (size_t c = 0; c < chunks; ++c) acc = fr_add(acc, fr_load(part, ps, c * P1 + k));
-    fr_store(a, as, k, acc);
+    if (k < D1) {
+        size_t c = share;
+        for (; c + 24 < chunks; c += 32) {
+            Fr v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = fr_load(part, ps, (c + 8 * q) * P1 + k);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc = fr_add(acc, v[q]);
+        }
+        for (; c < chunks; c += 8) acc = fr_add(acc, fr_load(part, ps, c * P1 + k));
+    }
+    for (int step = 4; step >= 1; step >>= 1) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) lds[q * kBlock + threadIdx.x] = acc.l[q];
+        __syncthreads();
+        if (share < step) {
+            Fr o;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) o.l[q] = lds[q * kBlock + threadIdx.x + step * kReduceColumns];
+            acc = fr_add(acc, o);
+        }
+        __syncthreads();
+    }
+    if (share == 0 && k < P1) fr_store(a, as, k, acc);
 }
 
-// b[k] = sum_j W[k][j] e[j]; one workgroup per row; rows D1 <= k < P1 are zero.
+// b[k] = sum_j W[k][j] e[j]; one workgroup per ROWS rows, which share the loads of e;
+// rows D1 <= k < P1 are zero.  The products are added up as 512-bit integers and
+// reduced once per thread: with a reduction for each, this was bound by instruction
+// issue (320 instructions per 32 bytes; 5120 x 5120 elements 290 us, 2.9 TB/s), now
+// it is 202 us, 4.1 TB/s.  Four rows where that leaves some two workgroups per compute unit.
+template <int ROWS>
 __global__ void __launch_bounds__(kBlock) k_rowdot(uint32_t* __restrict__ b, size_t bs, const uint32_t* __restrict__ W,
                                                    size_t ws, size_t D1, size_t D2, const uint32_t* __restrict__ e,
-                                                   size_t es) {
-    __shared__ uint32_t lds[4 * 8];
-    size_t k = blockIdx.x;
-    Fr acc[1] = {fr_zero()};
-    if (k < D1)
-        for (size_t j = threadIdx.x; j < D2; j += kBlock)
-            acc[0] = fr_add(acc[0], fr_mul(fr_load(W, ws, k * D2 + j), fr_load(e, es, j)));
-    block_sum<1, 4>(acc, lds);
-    if (threadIdx.x == 0) fr_store(b, bs, k, acc[0]);
+                                                   size_t es, size_t P1) {
+    __shared__ uint32_t lds[4 * ROWS * 8];
+    const size_t k = (size_t)blockIdx.x * ROWS;
+    Fr tot[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) tot[r] = fr_zero();
+    if (k < D1) {
+        FrWide acc[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) acc[r] = fr_wide_zero();
+        for (size_t j = threadIdx.x; j < D2; j += kBlock) {
+            Fr w[ROWS];
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) w[r] = fr_load(W, ws, (k + r < D1 ? k + r : D1 - 1) * D2 + j);
+            const Fr ej = fr_load(e, es, j);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) fr_wide_mac(acc[r], w[r], ej);
+        }
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) tot[r] = k + r < D1 ? fr_wide_reduce(acc[r]) : fr_zero();
+    }
+    block_sum<ROWS, 4>(tot, lds);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            if (k + r < P1) fr_store(b, bs, k + r, tot[r]);
+    }
 }
 
 __global__ void __launch_bounds__(kBlock) k_dot_partial(const uint32_t* __restrict__ x, size_t xs,
@@ -503,9 +563,23 @@ __global__ void __launch_bounds__(64) k_rowdot_i16(uint32_t* __restrict__ raw_ou
     }
 }
 
-// dst[k] = (sum over `chunks` raw values of entry k) mod r - 2^15 * (*esum), zero for k >= count.
-__global__ void __launch_bounds__(kBlock) k_small_finish(uint32_t* __restrict__ dst, size_t ds, const uint32_t* __restrict__ raw,
-                                                         size_t P, size_t chunks, size_t count, const uint32_t* __restrict__ esum) {
+// dst[k] = (sum over `chunks` raw values of entry k) mod r - 2^15 * (*esum), zero for
+// k >= count: both products' sums in one launch (blockIdx.y).
+struct SmallFinishArgs {
+    struct Job {
+        uint32_t* dst;
+        const uint32_t* raw;
+        size_t chunks, count;
+        const uint32_t* esum;
+    } job[2];
+    size_t P;
+};
+__global__ void __launch_bounds__(kBlock) k_small_finish(SmallFinishArgs g) {
+    const auto& job = g.job[blockIdx.y];
+    uint32_t* const dst = job.dst;
+    const uint32_t* const raw = job.raw;
+    const uint32_t* const esum = job.esum;
+    const size_t P = g.P, ds = g.P, chunks = job.chunks, count = job.count;
     size_t k = blockIdx.x * (size_t)kBlock + threadIdx.x;
     if (k >= P) return;
     if (k >= count) {
@@ -552,13 +626,16 @@ __global__ void __launch_bounds__(kBlock) k_small_finish(uint32_t* __restrict__ 
     fr_store(dst, ds, k, fr_sub(sum, fr_mul(shift, fr_load(esum, 1, 0))));
 }
 
-// out (eight words, Montgomery limbs of one element) = sum_{i < n} e[i]; one workgroup.
-__global__ void __launch_bounds__(1024) k_sum_one(uint32_t* __restrict__ out, const uint32_t* __restrict__ e, size_t es, size_t n) {
+// out[8 b .. 8 b + 7] (Montgomery limbs of one element) = sum_{i < n_b} e_b[i], workgroup b = 0, 1.
+__global__ void __launch_bounds__(1024) k_sum_two(uint32_t* __restrict__ out, const uint32_t* __restrict__ e0, size_t es0, size_t n0,
+                                                  const uint32_t* __restrict__ e1, size_t es1, size_t n1) {
     __shared__ uint32_t lds[16 * 8];
+    const uint32_t* const e = blockIdx.x ? e1 : e0;
+    const size_t es = blockIdx.x ? es1 : es0, n = blockIdx.x ? n1 : n0;
     Fr acc[1] = {fr_zero()};
     for (size_t i = threadIdx.x; i < n; i += 1024) acc[0] = fr_add(acc[0], fr_load(e, es, i));
     block_sum<1, 16>(acc, lds);
-    if (threadIdx.x == 0) fr_store(out, 1, 0, acc[0]);
+    if (threadIdx.x == 0) fr_store(out + 8 * blockIdx.x, 1, 0, acc[0]);
 }
 
 static const size_t kColChunks = 64;
@@ -589,36 +666,34 @@ static void colsum_run(uint32_t* a, size_t PC, const uint32_t* M, size_t ms, siz
     size_t chunks = div_up(R, rows_per_chunk);
     hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)div_up(C, kBlock), (unsigned)chunks), dim3(kBlock), 0, stream, M,
                        ms, R, C, e0, e0s, rows_per_chunk, part, kColChunks * PC, PC);
-    hipLaunchKernelGGL(k_colsum_reduce, dim3((unsigned)div_up(PC, kBlock)), dim3(kBlock), 0, stream, a, PC, part,
+    hipLaunchKernelGGL(k_colsum_reduce, dim3((unsigned)div_up(PC, kReduceColumns)), dim3(kBlock), 0, stream, a, PC, part,
                        kColChunks * PC, chunks, C, PC);
 }
 
-static void colsum_i16_run(uint32_t* a, size_t PC, const int16_t* M, size_t R, size_t C, const uint32_t* e0, size_t e0s,
-                           uint32_t* scratch, hipStream_t stream) {
-    size_t rows_per_chunk = div_up(R, kColChunks);
-    size_t chunks = div_up(R, rows_per_chunk);
-    uint32_t* raw = scratch;
-    uint32_t* esum = scratch + kColChunks * kRawLimbs * PC;
-    hipLaunchKernelGGL(k_sum_one, dim3(1), dim3(1024), 0, stream, esum, e0, e0s, R);
-    hipLaunchKernelGGL(k_colsum_partial_i16, dim3((unsigned)div_up(C, kBlock), (unsigned)chunks), dim3(kBlock), 0, stream, M,
-                       R, C, e0, e0s, rows_per_chunk, raw, PC);
-    hipLaunchKernelGGL(k_small_finish, dim3((unsigned)div_up(PC, kBlock)), dim3(kBlock), 0, stream, a, PC, raw, PC, chunks,
-                       C, esum);
-}
-
-static void rowdot_i16_run(uint32_t* b, size_t PR, const int16_t* M, size_t R, size_t C, const uint32_t* e1, size_t e1s,
-                           uint32_t* scratch, hipStream_t stream) {
-    uint32_t* raw = scratch;
-    uint32_t* esum = scratch + kColChunks * kRawLimbs * PR;
-    hipLaunchKernelGGL(k_sum_one, dim3(1), dim3(1024), 0, stream, esum, e1, e1s, C);
-    hipLaunchKernelGGL(k_rowdot_i16, dim3((unsigned)div_up(R, kRowsPerWave)), dim3(64), 0, stream, raw, PR, M, R, C, e1, e1s);
-    hipLaunchKernelGGL(k_small_finish, dim3((unsigned)div_up(PR, kBlock)), dim3(kBlock), 0, stream, b, PR, raw, PR,
-                       (size_t)1, R, esum);
+// a_k = sum_i eu[i] X[i][k] over R x C and b_k = sum_j W[k][j] ev[j] over C x C2, 16-bit entries, into a and b (PC entries).
+// scratch: kColChunks raw chunks of the first, one of the second, the two sums of weights.
+static void small_products_run(uint32_t* a, uint32_t* b, size_t PC, const int16_t* X, size_t R, size_t C, const uint32_t* eu,
+                               size_t eus, const int16_t* W, size_t C2, const uint32_t* ev, size_t evs, uint32_t* scratch,
+                               hipStream_t stream) {
+    const size_t rows_per_chunk = div_up(R, kColChunks), chunks = div_up(R, rows_per_chunk);
+    uint32_t* raw_a = scratch;
+    uint32_t* raw_b = raw_a + kColChunks * kRawLimbs * PC;
+    uint32_t* esums = raw_b + kRawLimbs * PC;
+    hipLaunchKernelGGL(k_sum_two, dim3(2), dim3(1024), 0, stream, esums, eu, eus, R, ev, evs, C2);
+    hipLaunchKernelGGL(k_colsum_partial_i16, dim3((unsigned)div_up(C, kBlock), (unsigned)chunks), dim3(kBlock), 0, stream, X,
+                       R, C, eu, eus, rows_per_chunk, raw_a, PC);
+    hipLaunchKernelGGL(k_rowdot_i16, dim3((unsigned)div_up(C, kRowsPerWave)), dim3(64), 0, stream, raw_b, PC, W, C, C2, ev, evs);
+    SmallFinishArgs g;
+    g.job[0] = {a, raw_a, chunks, C, esums};
+    g.job[1] = {b, raw_b, 1, C, esums + 8};
+    g.P = PC;
+    hipLaunchKernelGGL(k_small_finish, dim3((unsigned)div_up(PC, kBlock), 2), dim3(kBlock), 0, stream, g);
 }
 
 static void rowdot_run(uint32_t* b, size_t PR, const uint32_t* M, size_t ms, size_t R, size_t C, const uint32_t* e1,
                        size_t e1s, hipStream_t stream) {
-    hipLaunchKernelGGL(k_rowdot, dim3((unsigned)PR), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s);
+    if (R >= 2048) hipLaunchKernelGGL(k_rowdot<4>, dim3((unsigned)(PR / 4)), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s, PR);
+    else hipLaunchKernelGGL(k_rowdot<1>, dim3((unsigned)PR), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s, PR);
 }
 
 static int dot_run(const uint32_t* x, size_t xs, const uint32_t* y, size_t ys, size_t n, uint32_t* partials,
@@ -726,13 +801,12 @@ static int matmul_prove_any(const uint8_t seed[32], fr_vec X, const int16_t* X16
     host::F u[32], v[32];
     for (int t = 0; t < n0; ++t) u[t] = tr.challenge("u");
     for (int t = 0; t < n2; ++t) v[t] = tr.challenge("v");
-    ZK_TRY(eq_table_run(w.eu, w.P0, u, n0, stream));
-    ZK_TRY(eq_table_run(w.ev, w.P2, v, n2, stream));
+    const EqTable tables[2] = {{w.eu, w.P0, u, n0}, {w.ev, w.P2, v, n2}};
+    ZK_TRY(eq_tables_run(tables, 2, stream));
     if (small) {
         // entries per accumulator: rows of X per chunk, columns of W per lane
         if (D0 > kColChunks * kSmallTermsMax || D2 > kSmallTermsMax) return ZK_E_BADARG;
-        colsum_i16_run(w.a, w.P1, X16, D0, D1, w.eu, w.P0, w.part, stream);
-        rowdot_i16_run(w.b, w.P1, W16, D1, D2, w.ev, w.P2, w.part, stream);
+        small_products_run(w.a, w.b, w.P1, X16, D0, D1, w.eu, w.P0, W16, D2, w.ev, w.P2, w.part, stream);
     } else {
         colsum_run(w.a, w.P1, X.limbs, X.stride, D0, D1, w.eu, w.P0, w.part, stream);
         rowdot_run(w.b, w.P1, W.limbs, W.stride, D1, D2, w.ev, w.P2, stream);
@@ -839,8 +913,8 @@ int matmul_sumcheck_verify(const uint8_t seed[32], const uint8_t* proof, size_t 
     Carver cv(ws, ws_bytes);
     MatmulWs w;
     carve_matmul(w, cv, D0, D1, D2);
-    ZK_TRY(eq_table_run(w.eu, w.P0, u, n0, stream));
-    ZK_TRY(eq_table_run(w.ev, w.P2, v, n2, stream));
+    const EqTable tables[2] = {{w.eu, w.P0, u, n0}, {w.ev, w.P2, v, n2}};
+    ZK_TRY(eq_tables_run(tables, 2, stream));
     // Y~(u,v) = sum_j (sum_i e~(u,i) Y[i][j]) e~(v,j)
     if (want_Y) {
         uint32_t* ycols = cv.limbs(w.P2);
