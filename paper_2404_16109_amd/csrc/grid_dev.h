@@ -33,7 +33,9 @@ static inline uint32_t grid_points(int vars) { return vars == 0 ? 1 : vars == 1 
 enum GridKind {
     kGridWeighted = 0,  // w_p X (Y + beta), with the sums of X over p too (one for every t in {0,1}^V)
     kGridTable = 1,     // w_p X (Y + beta)
-    kGridPlain = 2      // X Y
+    kGridPlain = 2,     // X Y
+    kGridLine = 3,      // w_p X at every t in {0,1}^V (it is linear in each t_i)
+    kGridRowLine = 4    // the same with the high factor of the weights alone (none: unweighted)
 };
 
 // X and Y: 2^vars * P elements each, position p of point c at c * P + p.
@@ -43,12 +45,15 @@ struct GridJob {
     size_t xs, ys;
     EqSplit eq;           // weights of the P positions
     uint32_t P;
-    uint32_t span;        // positions a wavefront takes: 64 or more, at most 2^eq.lbits
+    uint32_t span;        // positions a wavefront takes: 64 or more
     uint32_t chunks;      // wavefronts per sum
     uint32_t first_wave;  // in the launch
     uint32_t first_value;
     int vars, kind;
-    static uint32_t values(int vars, int kind) { return grid_points(vars) + (kind == kGridWeighted ? 1u << vars : 0u); }
+    int hi_by_lane;       // 64 positions do not share the high factor of their weights: every lane applies its own
+    static uint32_t values(int vars, int kind) {
+        return kind >= kGridLine ? 1u << vars : grid_points(vars) + (kind == kGridWeighted ? 1u << vars : 0u);
+    }
 };
 static const int kGridMaxJobs = 24;  // three products of eight instances
 struct GridArgs {
@@ -89,11 +94,25 @@ __device__ __forceinline__ Fr grid_share(const GridJob& g, const Fr& beta, uint3
         Fr a = grid_entry<NI>(g.x, g.xs, at, step), b = grid_entry<NI>(g.y, g.ys, at, step);
         if (g.kind != kGridPlain) {
             a = fr_mul(a, fr_load(g.eq.pool, g.eq.stride, g.eq.lo_off + (p & lo_mask)));
+            if (g.hi_by_lane) a = fr_mul(a, fr_load(g.eq.pool, g.eq.stride, g.eq.hi_off + (p >> g.eq.lbits)));
             if (NI == 0) b = fr_add(b, beta);
         }
         fr_wide_mac(acc, a, b);
     }
     return fr_wide_reduce(acc);
+}
+
+// One entry of X over the positions, weighted as its kind says.
+__device__ __forceinline__ Fr grid_line_share(const GridJob& g, uint32_t from, uint32_t to, uint32_t entry, bool weighted) {
+    Fr tot = fr_zero();
+    const uint32_t lo_mask = (1u << g.eq.lbits) - 1;
+    for (uint32_t p = from + (threadIdx.x & 63); p < to; p += 64) {
+        Fr a = fr_load(g.x, g.xs, (size_t)entry * g.P + p);
+        if (weighted && g.kind == kGridLine) a = fr_mul(a, fr_load(g.eq.pool, g.eq.stride, g.eq.lo_off + (p & lo_mask)));
+        if (weighted && g.hi_by_lane) a = fr_mul(a, fr_load(g.eq.pool, g.eq.stride, g.eq.hi_off + (p >> g.eq.lbits)));
+        tot = fr_add(tot, a);
+    }
+    return tot;
 }
 
 static __global__ void __launch_bounds__(kBlock) k_grid(GridArgs args) {
@@ -106,11 +125,14 @@ static __global__ void __launch_bounds__(kBlock) k_grid(GridArgs args) {
     const uint32_t from = chunk * g.span, to = from + g.span < g.P ? from + g.span : g.P;
     uint32_t points = 1;
     for (int v = 0; v < g.vars; ++v) points *= 3;
+    const bool line = g.kind >= kGridLine;
+    bool weighted = g.kind != kGridPlain;
     Fr tot;
-    if (value >= points) {  // a sum of X alone
-        tot = fr_zero();
-        for (uint32_t p = from + (threadIdx.x & 63); p < to; p += 64)
-            tot = fr_add(tot, fr_load(g.x, g.xs, (size_t)(value - points) * g.P + p));
+    if (line) {
+        tot = grid_line_share(g, from, to, value, true);
+    } else if (value >= points) {  // a sum of X alone
+        weighted = false;
+        tot = grid_line_share(g, from, to, value - points, false);
     } else {
         // the point's coordinates, the first variable's in the highest digit and on the top bit of the entry's index
         uint32_t base = 0, rest = value;
@@ -135,7 +157,7 @@ static __global__ void __launch_bounds__(kBlock) k_grid(GridArgs args) {
     }
     tot = wave_sum(tot);
     if ((threadIdx.x & 63) == 0) {
-        if (value < points && g.kind != kGridPlain && g.eq.has_hi)
+        if (weighted && g.eq.has_hi && !g.hi_by_lane)
             tot = fr_mul(tot, fr_load(g.eq.pool, g.eq.stride, g.eq.hi_off + (from >> g.eq.lbits)));
         uint4* out = (uint4*)args.partials + 2 * ((size_t)(g.first_value + value) * kGridChunks + chunk);
         out[0] = make_uint4(tot.l[0], tot.l[1], tot.l[2], tot.l[3]);
@@ -272,8 +294,9 @@ struct GridPass {
     // Returns the job's first value.
     uint32_t add(const uint32_t* x, size_t xs, const uint32_t* y, size_t ys, int vars, int kind, size_t P, const EqSplit& eq) {
         GridJob& g = grid.job[grid.njobs];
-        g = GridJob{x, y, xs, ys, eq, (uint32_t)P, 64, 1, grid.waves, values, vars, kind};
+        g = GridJob{x, y, xs, ys, eq, (uint32_t)P, 64, 1, grid.waves, values, vars, kind, 0};
         while ((size_t)g.span * kGridChunks < P) g.span *= 2;
+        g.hi_by_lane = eq.has_hi && g.span > (1u << eq.lbits);
         g.chunks = (uint32_t)div_up(P, g.span);
         sum.first_value[grid.njobs] = values;
         sum.chunks[grid.njobs++] = g.chunks;
@@ -325,6 +348,18 @@ struct GridPass {
     }
 };
 
+// The weights of `later` variables in {0,1}: e~(u, .) of the first `weighted` of them.
+static inline void grid_later_weights(host::F w[4], const host::F* u, int later, int weighted) {
+    using namespace host;
+    w[0] = one();
+    for (int t = 0; t < later; ++t)
+        for (int e = (1 << t) - 1; e >= 0; --e) {
+            const F hi = t < weighted ? mul(w[e], u[t]) : w[e];
+            w[2 * e] = t < weighted ? sub(w[e], hi) : w[e];
+            w[2 * e + 1] = hi;
+        }
+}
+
 // One product's grid on the host, coordinate by coordinate.
 struct HostGrid {
     host::F g[27];
@@ -339,13 +374,8 @@ struct HostGrid {
     void sums(host::F out[3], const host::F* u) const {
         using namespace host;
         const int later = vars - 1;
-        F w[4] = {one()};
-        for (int t = 0; u && t < later; ++t)
-            for (int e = (1 << t) - 1; e >= 0; --e) {
-                const F hi = mul(w[e], u[t]);
-                w[2 * e] = sub(w[e], hi);
-                w[2 * e + 1] = hi;
-            }
+        F w[4];
+        if (u) grid_later_weights(w, u, later, later);
         for (int X = 0; X < 3; ++X) {
             out[X] = zero();
             for (int x = 0; x < 1 << later; ++x) {
@@ -362,6 +392,34 @@ struct HostGrid {
         for (uint32_t i = 0; i < rest; ++i)
             g[i] = add(g[i], mul(r, add(sub(g[rest + i], g[i]), mul(rm, g[2 * rest + i]))));
         --vars;
+    }
+};
+
+// The same for a kGridLine.
+struct HostLine {
+    host::F g[1 << kGridVars];
+    int vars = 0;
+
+    void read(const uint32_t* words, int v) {
+        vars = v;
+        for (int i = 0; i < 1 << v; ++i) g[i] = from_dev(words + 8 * i);
+    }
+    // at 0 and 1, the later variables summed over {0,1}, the first `weighted` of them by e~(u, .)
+    void sums(host::F out[2], const host::F* u, int weighted) const {
+        using namespace host;
+        const int later = vars - 1;
+        F w[4];
+        grid_later_weights(w, u, later, weighted);
+        for (int X = 0; X < 2; ++X) {
+            out[X] = zero();
+            for (int x = 0; x < 1 << later; ++x)
+                out[X] = add(out[X], weighted > 0 ? mul(w[x], g[(X << later) + x]) : g[(X << later) + x]);
+        }
+    }
+    void bind(const host::F& r) {
+        using namespace host;
+        const int half = 1 << --vars;
+        for (int i = 0; i < half; ++i) g[i] = add(g[i], mul(r, sub(g[half + i], g[i])));
     }
 };
 

@@ -41,11 +41,22 @@
 #include "internal.h"
 #include "small_dev.h"
 #include "tlookup_kernels.h"
+#include "grid_dev.h"
 #include "transcript.h"
+
+#include <algorithm>
 
 namespace zkmi {
 
 static const int kLinkMaxK = 3;
+
+// The last rounds (from the third on, once at most kLinkPassVars variables are left, up
+// to two segments) come several from one pass (grid_dev.h): L and sY are linear in
+// every variable, Q is of degree two.  The last kLinkHostVars variables are the host's.
+// With three segments Q is of degree three, which the passes do not cover.  Measured,
+// 2^24 scores and two segments: 3.79 -> 3.33 ms.
+static const int kLinkPassVars = 16, kLinkHostVars = 6;
+static const uint32_t kLinkGridValues = 27 + 2 * 8;
 
 template <int K>
 struct LinkRoundArgs {
@@ -482,7 +493,7 @@ static void carve_link(LinkWs& w, Carver& cv, size_t D, size_t cols, int K) {
         w.mle_partials = cv.limbs((size_t)K << (n - lb));
     }
     w.part_blocks = link_blocks_max(log2_floor(D / cols), log2_floor(cols));
-    w.partials = cv.limbs(w.part_blocks * (K + 5));
+    w.partials = cv.limbs(std::max(w.part_blocks * (K + 5), (size_t)kLinkGridValues * kGridChunks));
     w.ticket = (uint32_t*)cv.take(256);
     w.fold = (SmallFoldConsts*)cv.take(sizeof(SmallFoldConsts) * 2);
 }
@@ -530,6 +541,65 @@ static SmallFoldConsts small_fold_consts(const host::F& scale, const host::F& rh
     to_device_limbs(k.minus_d, neg(d));
     return k;
 }
+
+// The rounds left to the host: the arrays, and the weights of the round to come, of all its later variables (w)
+// and of the row variables among them (rw).
+template <int K>
+struct LinkHost {
+    static const size_t kMax = (size_t)1 << kLinkHostVars;
+    host::F Y[kMax], Yk[K][kMax], w[kMax / 2], rw[kMax / 2];
+
+    // round t of n variables, the first nr of them row variables
+    void weights(const host::F* u, int t, int n, int nr) {
+        using namespace host;
+        w[0] = rw[0] = one();
+        for (int v = t + 1; v < n; ++v)
+            for (size_t e = (size_t)1 << (v - t - 1); e-- > 0;) {
+                const F hi = mul(w[e], u[v]), rhi = v < nr ? mul(rw[e], u[v]) : rw[e];
+                w[2 * e + 1] = hi;
+                w[2 * e] = sub(w[e], hi);
+                rw[2 * e + 1] = rhi;
+                rw[2 * e] = v < nr ? sub(rw[e], rhi) : rw[e];
+            }
+    }
+    void sums(size_t half, host::F L[2], host::F Q[K + 1], host::F s[2]) const {
+        using namespace host;
+        L[0] = L[1] = s[0] = s[1] = zero();
+        for (int X = 0; X <= K; ++X) Q[X] = zero();
+        for (size_t p = 0; p < half; ++p) {
+            for (int e = 0; e < 2; ++e) {
+                const F& y = Y[p + e * half];
+                L[e] = add(L[e], mul(w[p], y));
+                s[e] = add(s[e], mul(rw[p], y));
+            }
+            F f[K], d[K];
+            for (int k = 0; k < K; ++k) {
+                f[k] = Yk[k][p];
+                d[k] = sub(Yk[k][p + half], f[k]);
+            }
+            f[0] = mul(f[0], w[p]);
+            d[0] = mul(d[0], w[p]);
+            for (int X = 0; X <= K; ++X) {
+                F prod = f[0];
+                for (int k = 1; k < K; ++k) prod = mul(prod, f[k]);
+                Q[X] = add(Q[X], prod);
+                for (int k = 0; k < K; ++k) f[k] = add(f[k], d[k]);
+            }
+        }
+    }
+    void bind(size_t half, const host::F& r, bool next_is_row) {
+        using namespace host;
+        auto fold = [&](F* x) {
+            for (size_t p = 0; p < half; ++p) x[p] = add(x[p], mul(r, sub(x[p + half], x[p])));
+        };
+        fold(Y);
+        for (int k = 0; k < K; ++k) fold(Yk[k]);
+        for (size_t p = 0; p < half / 2; ++p) {  // the next variable summed out
+            w[p] = add(w[p], w[p + half / 2]);
+            if (next_is_row) rw[p] = add(rw[p], rw[p + half / 2]);
+        }
+    }
+};
 
 // small != null: the tensors come as integers (Zp, X, Y, Yk and bases are then unused).
 template <int K>
@@ -596,76 +666,153 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
     F c_rows = one(); // its value once the row variables are bound
     F r_prev = zero();
     F point[32];      // the challenges: where the final claims are
+    F r_last[3] = {zero(), zero(), zero()};  // the last three of them, the last one in [2]
+    int pending = 0;  // of them, those that the arrays in the workspace have yet to be bound to
+    int pass_left = 0;
+    HostGrid gq;
+    HostLine gl, gs, gq1;
+    LinkHost<K> tail;
+    bool on_host = false;
+    // the arrays with the pending challenges bound, into the mailbox and to the host
+    auto ship = [&](int t) -> int {
+        const size_t count = (size_t)1 << (n - t);
+        GridPass pass;
+        pass.challenges(r_last);
+        for (int q = 0; q <= K; ++q)
+            pass.add_fold(q ? w.Yk[q - 1] : w.Y, D / 2, mb->words + kMailboxShip + 8 * count * q, 0, count, pending, true);
+        const uint32_t seq = mb->next_seq();
+        ZK_TRY(pass.launch_folds(mb, seq, w.ticket, stream));
+        ZK_TRY(mailbox_wait(mb, seq, stream));
+        const uint32_t* at = mb->words + kMailboxShip;
+        for (int q = 0; q <= K; ++q)
+            for (size_t j = 0; j < count; ++j, at += 8) (q ? tail.Yk[q - 1] : tail.Y)[j] = from_dev(at);
+        if (t < n) tail.weights(u, t, n, nr);
+        on_host = true;
+        return ZK_OK;
+    };
     for (int t = 0; t < n; ++t) {
         const size_t half = (size_t)1 << (n - t - 1);
-        const EqSplit eq = lt.round(t);
-        const size_t span = link_span(t, nr, nc);
-        const unsigned blocks = (unsigned)(half / span);
-        if (blocks > w.part_blocks) return ZK_E_BUFSZ;
-        LinkRoundArgs<K> g;
-        memset(&g, 0, sizeof g);
-        // sources: the caller's tensors in the first two rounds, the workspace afterwards;
-        // Z' and the X^(k) are only read by the first round
-        const bool from_input = t <= 1 && !small;  // (the integer tensors have sources of their own)
-        if (t == 0 && !small) g.Z = PairArray{Zp.limbs, Zp.stride, nullptr, 0};
-        g.Y = PairArray{from_input ? Y.limbs : w.Y, from_input ? Y.stride : D / 2, w.Y, D / 2};
-        for (int k = 0; k < K; ++k) {
-            if (t == 0 && !small) g.X[k] = PairArray{X[k].limbs, X[k].stride, nullptr, 0};
-            g.Yk[k] = PairArray{from_input ? Yk[k].limbs : w.Yk[k], from_input ? Yk[k].stride : D / 2, w.Yk[k], D / 2};
-            g.base[k] = to_dev(base[k]);
-            g.scale_x[k] = equal(base[k], one()) ? 0 : 1;
-        }
-        g.alpha = to_dev(alpha);
-        g.half = half;
-        g.block_span = span;
-        g.r_prev = to_dev(r_prev);
-        g.eq = eq;
-        g.row_round = t < nr ? 1 : 0;
-        g.partials = w.partials;
-        g.pstride = w.part_blocks * NV;
-        if (small && t <= 1) {
-            g.Zs = small->Zp;
-            g.Ys = small->Y;
+        const int left = n - t;
+        F L0, L1, s0, s1, Q[NPTS];
+        if (K <= 2 && t >= 2 && left <= kLinkHostVars && pass_left == 0) {
+            if (!on_host) ZK_TRY(ship(t));
+            F L2[2], s2[2];
+            tail.sums(half, L2, Q, s2);
+            L0 = L2[0];
+            L1 = L2[1];
+            s0 = s2[0];
+            s1 = s2[1];
+        } else if (K <= 2 && t >= 2 && left <= kLinkPassVars) {
+            if (pass_left == 0) {
+                const int vars = pass_left = (left - kLinkHostVars - 1) % kGridVars + 1;
+                GridPass pass;
+                pass.challenges(r_last);
+                if (pending)
+                    for (int q = 0; q <= K; ++q)
+                        pass.add_fold(q ? w.Yk[q - 1] : w.Y, D / 2, q ? w.Yk[q - 1] : w.Y, D / 2, (size_t)1 << left, pending);
+                const EqSplit eq = lt.round(t + vars - 1);
+                const size_t P = (size_t)1 << (left - vars);
+                const uint32_t at_l = pass.add(w.Y, D / 2, nullptr, 0, vars, kGridLine, P, eq);
+                const uint32_t at_s = pass.add(w.Y, D / 2, nullptr, 0, vars, kGridRowLine, P, eq);
+                const uint32_t at_q = K == 1 ? pass.add(w.Yk[0], D / 2, nullptr, 0, vars, kGridLine, P, eq)
+                                             : pass.add(w.Yk[0], D / 2, w.Yk[K - 1], D / 2, vars, kGridTable, P, eq);
+                const uint32_t seq = mb->next_seq();
+                ZK_TRY(pass.launch(mb, zero(), w.partials, mb->words + kMailboxGrid, seq, w.ticket, stream));
+                ZK_TRY(mailbox_wait(mb, seq, stream));
+                gl.read(mb->words + kMailboxGrid + 8 * at_l, vars);
+                gs.read(mb->words + kMailboxGrid + 8 * at_s, vars);
+                if (K == 1) gq1.read(mb->words + kMailboxGrid + 8 * at_q, vars);
+                else gq.read(mb->words + kMailboxGrid + 8 * at_q, vars);
+                pending = vars;
+            }
+            const int later = pass_left - 1;
+            F o[3];
+            gl.sums(o, u + t + 1, later);
+            L0 = o[0];
+            L1 = o[1];
+            gs.sums(o, u + t + 1, std::max(0, std::min(later, nr - t - 1)));
+            s0 = o[0];
+            s1 = o[1];
+            if (K == 1) {
+                gq1.sums(Q, u + t + 1, later);
+            } else {
+                gq.sums(o, u + t + 1);
+                Q[0] = o[0];
+                Q[1] = o[1];
+                Q[K] = add(sub(add(o[1], o[1]), o[0]), add(o[2], o[2]));  // at 2, from the leading coefficient
+            }
+        } else {
+            const EqSplit eq = lt.round(t);
+            const size_t span = link_span(t, nr, nc);
+            const unsigned blocks = (unsigned)(half / span);
+            if (blocks > w.part_blocks) return ZK_E_BUFSZ;
+            LinkRoundArgs<K> g;
+            memset(&g, 0, sizeof g);
+            // sources: the caller's tensors in the first two rounds, the workspace afterwards;
+            // Z' and the X^(k) are only read by the first round
+            const bool from_input = t <= 1 && !small;  // (the integer tensors have sources of their own)
+            if (t == 0 && !small) g.Z = PairArray{Zp.limbs, Zp.stride, nullptr, 0};
+            g.Y = PairArray{from_input ? Y.limbs : w.Y, from_input ? Y.stride : D / 2, w.Y, D / 2};
             for (int k = 0; k < K; ++k) {
-                g.Xs[k] = small->X[k];
-                g.Yks[k] = small->Yk[k];
-                g.base_small[k] = small->bases[k];
+                if (t == 0 && !small) g.X[k] = PairArray{X[k].limbs, X[k].stride, nullptr, 0};
+                g.Yk[k] = PairArray{from_input ? Yk[k].limbs : w.Yk[k], from_input ? Yk[k].stride : D / 2, w.Yk[k], D / 2};
+                g.base[k] = to_dev(base[k]);
+                g.scale_x[k] = equal(base[k], one()) ? 0 : 1;
             }
-            g.fold = w.fold;
-            if (t == 1) {
-                LinkFoldConsts fc;
-                fc.c[0] = small_fold_consts(one(), r_prev);
-                fc.c[1] = small_fold_consts(alpha, r_prev);
-                hipLaunchKernelGGL(k_store_fold_consts, dim3(1), dim3(64), 0, stream, fc, w.fold, 2);
+            g.alpha = to_dev(alpha);
+            g.half = half;
+            g.block_span = span;
+            g.r_prev = to_dev(r_prev);
+            g.eq = eq;
+            g.row_round = t < nr ? 1 : 0;
+            g.partials = w.partials;
+            g.pstride = w.part_blocks * NV;
+            if (small && t <= 1) {
+                g.Zs = small->Zp;
+                g.Ys = small->Y;
+                for (int k = 0; k < K; ++k) {
+                    g.Xs[k] = small->X[k];
+                    g.Yks[k] = small->Yk[k];
+                    g.base_small[k] = small->bases[k];
+                }
+                g.fold = w.fold;
+                if (t == 1) {
+                    LinkFoldConsts fc;
+                    fc.c[0] = small_fold_consts(one(), r_prev);
+                    fc.c[1] = small_fold_consts(alpha, r_prev);
+                    hipLaunchKernelGGL(k_store_fold_consts, dim3(1), dim3(64), 0, stream, fc, w.fold, 2);
+                }
+                g.yk_bound = K == 1 ? 0xffffffffu : K == 2 ? 1u << 30 : 1u << 18;
+                const F two32 = from_u64((uint64_t)1 << 32);
+                g.raw_scale = to_dev(mul(two32, mul(two32, two32)));
+                g.bad = bad_word;
             }
-            g.yk_bound = K == 1 ? 0xffffffffu : K == 2 ? 1u << 30 : 1u << 18;
-            const F two32 = from_u64((uint64_t)1 << 32);
-            g.raw_scale = to_dev(mul(two32, mul(two32, two32)));
-            g.bad = bad_word;
-        }
-        if (small && t == 0) hipLaunchKernelGGL(k_link_round0_small<K>, dim3(blocks), dim3(kBlock), 0, stream, g);
-        else if (small && t == 1) hipLaunchKernelGGL((k_link_round<K, true, true, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
-        else if (t == 0) hipLaunchKernelGGL((k_link_round<K, false, true, false, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
-        else if (t == 1) hipLaunchKernelGGL((k_link_round<K, true, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
-        else hipLaunchKernelGGL((k_link_round<K, true, false>), dim3(blocks), dim3(kBlock), 0, stream, g);
-        const uint32_t seq = mb->next_seq();
-        launch_final_sum(w.partials, g.pstride, blocks, NV, mb->words, mb->words, seq, w.ticket, stream);
-        ZK_HIP_TRY(hipGetLastError());
-        ZK_TRY(mailbox_wait(mb, seq, stream));
-        if (small && t == 0) {
-            // what the first round found entry by entry
-            uint32_t bad = 0;
-            ZK_HIP_TRY(hipMemcpyAsync(&bad, bad_word, 4, hipMemcpyDeviceToHost, stream));
-            ZK_HIP_TRY(hipStreamSynchronize(stream));
-            if (bad & 2) return ZK_E_BADARG;  // an entry outside the ranges the integer path is written for
-            if (bad & 1) return ZK_E_REJECT;  // the tensors do not satisfy the relations
-        }
+            if (small && t == 0) hipLaunchKernelGGL(k_link_round0_small<K>, dim3(blocks), dim3(kBlock), 0, stream, g);
+            else if (small && t == 1) hipLaunchKernelGGL((k_link_round<K, true, true, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
+            else if (t == 0) hipLaunchKernelGGL((k_link_round<K, false, true, false, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
+            else if (t == 1) hipLaunchKernelGGL((k_link_round<K, true, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
+            else hipLaunchKernelGGL((k_link_round<K, true, false>), dim3(blocks), dim3(kBlock), 0, stream, g);
+            const uint32_t seq = mb->next_seq();
+            launch_final_sum(w.partials, g.pstride, blocks, NV, mb->words, mb->words, seq, w.ticket, stream);
+            ZK_HIP_TRY(hipGetLastError());
+            ZK_TRY(mailbox_wait(mb, seq, stream));
+            if (small && t == 0) {
+                // what the first round found entry by entry
+                uint32_t bad = 0;
+                ZK_HIP_TRY(hipMemcpyAsync(&bad, bad_word, 4, hipMemcpyDeviceToHost, stream));
+                ZK_HIP_TRY(hipStreamSynchronize(stream));
+                if (bad & 2) return ZK_E_BADARG;  // an entry outside the ranges the integer path is written for
+                if (bad & 1) return ZK_E_REJECT;  // the tensors do not satisfy the relations
+            }
 
-        F L0 = from_dev(mb->words), L1 = from_dev(mb->words + 8);
-        F Q[NPTS];
-        for (int pt = 0; pt <= K; ++pt) Q[pt] = from_dev(mb->words + 8 * (2 + pt));
+            L0 = from_dev(mb->words);
+            L1 = from_dev(mb->words + 8);
+            for (int pt = 0; pt <= K; ++pt) Q[pt] = from_dev(mb->words + 8 * (2 + pt));
+            s0 = from_dev(mb->words + 8 * (K + 3));
+            s1 = from_dev(mb->words + 8 * (K + 4));
+            pending = t >= 1 ? 1 : 0;
+        }
         Q[K + 1] = extrapolate_next(Q, K + 1);
-        F s0 = from_dev(mb->words + 8 * (K + 3)), s1 = from_dev(mb->words + 8 * (K + 4));
         F gX[NPTS];
         F e = sub(one(), u[t]), de = sub(u[t], e);  // e~(u_t, X) = (1-u_t) + X (2 u_t - 1)
         F L = L0, dL = sub(L1, L0), s = s0, ds = sub(s1, s0);
@@ -689,6 +836,18 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
         if (t == nr - 1) c_rows = c;
         r_prev = r;
         point[t] = r;
+        r_last[0] = r_last[1];
+        r_last[1] = r_last[2];
+        r_last[2] = r;
+        if (pass_left > 0) {
+            --pass_left;
+            gl.bind(r);
+            gs.bind(r);
+            if (K == 1) gq1.bind(r);
+            else gq.bind(r);
+        } else if (on_host) {
+            tail.bind(half, r, t + 1 < nr);
+        }
     }
 
     // -- final claims: Z' X^(0..K-1) Y Y^(0..K-1) at the point of the challenges -----------------
@@ -719,18 +878,10 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
         } else {
             // Y and the Y^(k) from the folded arrays; the X^(k) by evaluating the tensors at the point;
             // Z' from them (the linear relation holds as an identity of multilinear polynomials)
-            FinalArgs f;
-            memset(&f, 0, sizeof f);
-            f.count = K + 1;
-            f.r = to_dev(r_prev);
-            f.p[0] = w.Y; f.stride[0] = D / 2; f.fold[0] = 1;
-            for (int k = 0; k < K; ++k) { f.p[1 + k] = w.Yk[k]; f.stride[1 + k] = D / 2; f.fold[1 + k] = 1; }
-            uint32_t seq = mb->next_seq();
-            hipLaunchKernelGGL(k_final_values, dim3(1), dim3(64), 0, stream, f, mb->words, mb->words, seq);
-            ZK_HIP_TRY(hipGetLastError());
-            ZK_TRY(mailbox_wait(mb, seq, stream));
-            fin[1 + K] = mul(from_dev(mb->words), inv(alpha));  // scaled back
-            for (int k = 0; k < K; ++k) fin[2 + K + k] = from_dev(mb->words + 8 * (1 + k));
+            uint32_t seq;
+            if (!on_host) ZK_TRY(ship(n));
+            fin[1 + K] = mul(tail.Y[0], inv(alpha));  // scaled back
+            for (int k = 0; k < K; ++k) fin[2 + K + k] = tail.Yk[k][0];
 
             const int lb = n < kLinkMleLoBits ? n : kLinkMleLoBits;
             EqPoolArgs ea;
