@@ -82,6 +82,7 @@ struct LinkRoundArgs {
     // memory (as launch arguments they would crowd the scalar registers):
     // [0] scaled by 1 (the Y^(k)), [1] by alpha (Y)
     const SmallFoldConsts* fold;
+    int side;            // folding rounds: the X (0 or 1) at which L, Q and sY are summed
     uint64_t base_small[K];
     uint32_t yk_bound;   // segment outputs stay below it, so that products of K extrapolated factors fit 63 bits
     Fr raw_scale;        // 2^96: what turns a short-reduced raw sum into its Montgomery form
@@ -105,14 +106,9 @@ __device__ __forceinline__ void small_pair32(const uint32_t* __restrict__ in, si
     fr_store(dst.dst, dst.ds, p + half, x1);
 }
 
-// FOLD: bind the previous variable first and write the folded entries back.
-// SCALE: the sources hold unscaled X^(k) and Y (the first two rounds).
-// SMALL (with FOLD and SCALE, the second round): the sources are the integer tensors.
-// LIN: Z' and the X^(k) take part (the first round only, which never folds).
-template <int K, bool FOLD, bool SCALE, bool SMALL = false, bool LIN = false>
-static __global__ void __launch_bounds__(kBlock) k_link_round(LinkRoundArgs<K> g) {
-    static_assert(!SMALL || (FOLD && SCALE), "integer sources are read by the first two rounds only");
-    static_assert(!LIN || (!FOLD && !SMALL), "the linear relation is only summed in the first round");
+// The first round on field elements: nothing to fold, Z' and the X^(k) take part (the only round in which they do).
+template <int K>
+static __global__ void __launch_bounds__(kBlock) k_link_round0(LinkRoundArgs<K> g) {
     constexpr int NV = K + 5;
     __shared__ uint32_t lds[4 * NV * 8];
     Fr tot[NV];
@@ -122,37 +118,28 @@ static __global__ void __launch_bounds__(kBlock) k_link_round(LinkRoundArgs<K> g
     const size_t lo_mask = ((size_t)1 << g.eq.lbits) - 1;
     for (size_t p = start + threadIdx.x; p < start + g.block_span; p += kBlock) {
         const Fr w = fr_load(g.eq.pool, g.eq.stride, g.eq.lo_off + (p & lo_mask));
-        Fr lin0 = fr_zero(), lin1 = fr_zero();
-        if constexpr (LIN) load_pair<false>(g.Z, p, g.half, g.r_prev, lin0, lin1);
+        Fr lin0, lin1;
+        load_pair<false>(g.Z, p, g.half, g.r_prev, lin0, lin1);
         {
             Fr y0, y1;
-            if constexpr (SMALL) small_pair64((const int64_t*)g.Ys, p, g.half, g.fold[1], g.Y, y0, y1);
-            else load_pair<FOLD, !SCALE>(g.Y, p, g.half, g.r_prev, y0, y1);
-            if constexpr (SCALE && !SMALL) {
-                y0 = fr_mul(y0, g.alpha);
-                y1 = fr_mul(y1, g.alpha);
-                if constexpr (FOLD) {
-                    fr_store(g.Y.dst, g.Y.ds, p, y0);
-                    fr_store(g.Y.dst, g.Y.ds, p + g.half, y1);
-                }
-            }
+            load_pair<false>(g.Y, p, g.half, g.r_prev, y0, y1);
+            y0 = fr_mul(y0, g.alpha);
+            y1 = fr_mul(y1, g.alpha);
             tot[K + 3] = fr_add(tot[K + 3], y0);
             tot[K + 4] = fr_add(tot[K + 4], y1);
             lin0 = fr_add(lin0, y0);
             lin1 = fr_add(lin1, y1);
         }
-        if constexpr (LIN) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                Fr x0, x1;
-                load_pair<false>(g.X[k], p, g.half, g.r_prev, x0, x1);
-                if (g.scale_x[k]) {
-                    x0 = fr_mul(x0, g.base[k]);
-                    x1 = fr_mul(x1, g.base[k]);
-                }
-                lin0 = fr_add(lin0, x0);
-                lin1 = fr_add(lin1, x1);
+        for (int k = 0; k < K; ++k) {
+            Fr x0, x1;
+            load_pair<false>(g.X[k], p, g.half, g.r_prev, x0, x1);
+            if (g.scale_x[k]) {
+                x0 = fr_mul(x0, g.base[k]);
+                x1 = fr_mul(x1, g.base[k]);
             }
+            lin0 = fr_add(lin0, x0);
+            lin1 = fr_add(lin1, x1);
         }
         tot[0] = fr_add(tot[0], fr_mul(w, lin0));
         tot[1] = fr_add(tot[1], fr_mul(w, lin1));
@@ -161,8 +148,7 @@ static __global__ void __launch_bounds__(kBlock) k_link_round(LinkRoundArgs<K> g
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             Fr a0, a1;
-            if constexpr (SMALL) small_pair32(g.Yks[k], p, g.half, g.fold[0], g.Yk[k], a0, a1);
-            else load_pair<FOLD>(g.Yk[k], p, g.half, g.r_prev, a0, a1);
+            load_pair<false>(g.Yk[k], p, g.half, g.r_prev, a0, a1);
             if (k == 0) {
                 a0 = fr_mul(a0, w);
                 a1 = fr_mul(a1, w);
@@ -192,6 +178,85 @@ static __global__ void __launch_bounds__(kBlock) k_link_round(LinkRoundArgs<K> g
                 tot[K + 3] = fr_mul(tot[K + 3], hf);
                 tot[K + 4] = fr_mul(tot[K + 4], hf);
             }
+        }
+#pragma unroll
+        for (int q = 0; q < NV; ++q) fr_store(g.partials, g.pstride, (size_t)blockIdx.x * NV + q, tot[q]);
+    }
+}
+
+// A folding round: binds the previous variable, writes the folded entries back and
+// sums one side X = a of the round only,
+//     L(a), sY(a), Q(a), the leading coefficient of Q (K > 1), Q(2) (K = 3).
+// The other side follows on the host from the round before: with r its challenge,
+//     L_prev(r) = e~(u_t,0) L(0) + e~(u_t,1) L(1),   the same for Q, and for sY while a row variable is bound
+// (afterwards sY_prev(r) = sY(0) + sY(1)).  The weighted sums are added up as 512-bit
+// integers and reduced once per thread.  Bound by instruction issue: for two segments
+// eight multiplications and three unreduced products per pair, where both sides and
+// Q at 0, 1, 2 took thirteen.  Measured, 2^28 scores in two segments, the third round
+// (2^25 pairs): 5.27 -> 4.34 ms, 4.5 TB/s.
+// SCALE: the sources hold unscaled Y (the second round); SMALL: they are the integer
+// tensors (with SCALE).
+template <int K>
+struct LinkFoldValues {
+    static constexpr int count = K == 1 ? 3 : K + 2;  // L, sY, Q(a), lead, Q(2)
+};
+template <int K, bool SCALE, bool SMALL = false>
+static __global__ void __launch_bounds__(kBlock, K == 3 ? 2 : 3) k_link_round(LinkRoundArgs<K> g) {
+    static_assert(!SMALL || SCALE, "integer sources are read by the first two rounds only");
+    constexpr int NV = LinkFoldValues<K>::count;
+    __shared__ uint32_t lds[4 * NV * 8];
+    FrWide wide[NV - 1];  // L, Q(a), lead, Q(2)
+#pragma unroll
+    for (int q = 0; q < NV - 1; ++q) wide[q] = fr_wide_zero();
+    Fr sy = fr_zero();
+    const size_t start = blockIdx.x * g.block_span;
+    const size_t lo_mask = ((size_t)1 << g.eq.lbits) - 1;
+    for (size_t p = start + threadIdx.x; p < start + g.block_span; p += kBlock) {
+        const Fr w = fr_load(g.eq.pool, g.eq.stride, g.eq.lo_off + (p & lo_mask));
+        {
+            Fr y0, y1;
+            if constexpr (SMALL) small_pair64((const int64_t*)g.Ys, p, g.half, g.fold[1], g.Y, y0, y1);
+            else load_pair<true, !SCALE>(g.Y, p, g.half, g.r_prev, y0, y1);
+            if constexpr (SCALE && !SMALL) {
+                y0 = fr_mul(y0, g.alpha);
+                y1 = fr_mul(y1, g.alpha);
+                fr_store(g.Y.dst, g.Y.ds, p, y0);
+                fr_store(g.Y.dst, g.Y.ds, p + g.half, y1);
+            }
+            const Fr y = g.side ? y1 : y0;
+            sy = fr_add(sy, y);
+            fr_wide_mac(wide[0], w, y);
+        }
+        Fr at, lead, two;  // products of all factors but the last, at X = a, of the differences, at X = 2
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            Fr a0, a1;
+            if constexpr (SMALL) small_pair32(g.Yks[k], p, g.half, g.fold[0], g.Yk[k], a0, a1);
+            else load_pair<true>(g.Yk[k], p, g.half, g.r_prev, a0, a1);
+            const Fr d = fr_sub(a1, a0), x = g.side ? a1 : a0;
+            if (k + 1 < K) {
+                at = fr_mul(k == 0 ? w : at, x);
+                lead = fr_mul(k == 0 ? w : lead, d);
+                if constexpr (K == 3) two = fr_mul(k == 0 ? w : two, fr_add(a1, d));
+            } else {
+                fr_wide_mac(wide[1], k == 0 ? w : at, x);
+                if constexpr (K > 1) fr_wide_mac(wide[2], lead, d);
+                if constexpr (K == 3) fr_wide_mac(wide[3], two, fr_add(a1, d));
+            }
+        }
+    }
+    Fr tot[NV];
+    tot[0] = fr_wide_reduce(wide[0]);
+    tot[1] = sy;
+#pragma unroll
+    for (int q = 1; q < NV - 1; ++q) tot[q + 1] = fr_wide_reduce(wide[q]);
+    block_sum<NV, 4>(tot, lds);
+    if (threadIdx.x == 0) {
+        if (g.eq.has_hi) {
+            const Fr hf = fr_load(g.eq.pool, g.eq.stride, g.eq.hi_off + (start >> g.eq.lbits));
+#pragma unroll
+            for (int q = 0; q < NV; ++q)
+                if (q != 1 || g.row_round) tot[q] = fr_mul(tot[q], hf);
         }
 #pragma unroll
         for (int q = 0; q < NV; ++q) fr_store(g.partials, g.pstride, (size_t)blockIdx.x * NV + q, tot[q]);
@@ -521,6 +586,24 @@ static host::F extrapolate_next(const host::F* y, int npts) {
     return next;
 }
 
+// Value at x of the polynomial of degree < npts through y[j] at X = j (Newton's
+// forward differences: p(x) = sum_j (Delta^j y)(0) binom(x, j)).
+static host::F newton_at(const host::F* y, int npts, const host::F& x) {
+    using namespace host;
+    static const F inv_small[8] = {zero(), one(), inv(from_u64(2)), inv(from_u64(3)), inv(from_u64(4)),
+                                   inv(from_u64(5)), inv(from_u64(6)), inv(from_u64(7))};
+    F d[8];
+    for (int j = 0; j < npts; ++j) d[j] = y[j];
+    for (int level = 1; level < npts; ++level)
+        for (int j = npts - 1; j >= level; --j) d[j] = sub(d[j], d[j - 1]);
+    F acc = d[0], binom = one();
+    for (int j = 1; j < npts; ++j) {
+        binom = mul(mul(binom, sub(x, from_u64((uint64_t)(j - 1)))), inv_small[j]);
+        acc = add(acc, mul(d[j], binom));
+    }
+    return acc;
+}
+
 // The tensors as device arrays of integers (zkattn_link_prove_small).
 struct LinkSmallIn {
     const int64_t* Zp;
@@ -667,6 +750,7 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
     F r_prev = zero();
     F point[32];      // the challenges: where the final claims are
     F r_last[3] = {zero(), zero(), zero()};  // the last three of them, the last one in [2]
+    F prev_L[2], prev_s[2], prev_Q[K + 1];   // the last round's sums
     int pending = 0;  // of them, those that the arrays in the workspace have yet to be bound to
     int pass_left = 0;
     HostGrid gq;
@@ -767,6 +851,7 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
             g.row_round = t < nr ? 1 : 0;
             g.partials = w.partials;
             g.pstride = w.part_blocks * NV;
+            g.side = is_zero(u[t]) ? 1 : 0;  // the side that was not summed must carry weight
             if (small && t <= 1) {
                 g.Zs = small->Zp;
                 g.Ys = small->Y;
@@ -788,13 +873,17 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
                 g.bad = bad_word;
             }
             if (small && t == 0) hipLaunchKernelGGL(k_link_round0_small<K>, dim3(blocks), dim3(kBlock), 0, stream, g);
-            else if (small && t == 1) hipLaunchKernelGGL((k_link_round<K, true, true, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
-            else if (t == 0) hipLaunchKernelGGL((k_link_round<K, false, true, false, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
-            else if (t == 1) hipLaunchKernelGGL((k_link_round<K, true, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
-            else hipLaunchKernelGGL((k_link_round<K, true, false>), dim3(blocks), dim3(kBlock), 0, stream, g);
+            else if (small && t == 1) hipLaunchKernelGGL((k_link_round<K, true, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
+            else if (t == 0) hipLaunchKernelGGL(k_link_round0<K>, dim3(blocks), dim3(kBlock), 0, stream, g);
+            else if (t == 1) hipLaunchKernelGGL((k_link_round<K, true>), dim3(blocks), dim3(kBlock), 0, stream, g);
+            else hipLaunchKernelGGL((k_link_round<K, false>), dim3(blocks), dim3(kBlock), 0, stream, g);
             const uint32_t seq = mb->next_seq();
-            launch_final_sum(w.partials, g.pstride, blocks, NV, mb->words, mb->words, seq, w.ticket, stream);
+            launch_final_sum(w.partials, g.pstride, blocks, t == 0 ? NV : LinkFoldValues<K>::count, mb->words, mb->words, seq,
+                             w.ticket, stream);
             ZK_HIP_TRY(hipGetLastError());
+            // while the device works: what the other side is divided by
+            const F e_other = g.side ? sub(one(), u[t]) : u[t];
+            const F inv_other = t == 0 ? one() : inv(e_other);
             ZK_TRY(mailbox_wait(mb, seq, stream));
             if (small && t == 0) {
                 // what the first round found entry by entry
@@ -805,14 +894,45 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
                 if (bad & 1) return ZK_E_REJECT;  // the tensors do not satisfy the relations
             }
 
-            L0 = from_dev(mb->words);
-            L1 = from_dev(mb->words + 8);
-            for (int pt = 0; pt <= K; ++pt) Q[pt] = from_dev(mb->words + 8 * (2 + pt));
-            s0 = from_dev(mb->words + 8 * (K + 3));
-            s1 = from_dev(mb->words + 8 * (K + 4));
+            if (t == 0) {
+                L0 = from_dev(mb->words);
+                L1 = from_dev(mb->words + 8);
+                for (int pt = 0; pt <= K; ++pt) Q[pt] = from_dev(mb->words + 8 * (2 + pt));
+                s0 = from_dev(mb->words + 8 * (K + 3));
+                s1 = from_dev(mb->words + 8 * (K + 4));
+            } else {
+                // the round before at its challenge: its lines, and Q through its values at 0..K
+                F v[5];
+                for (int q = 0; q < LinkFoldValues<K>::count; ++q) v[q] = from_dev(mb->words + 8 * q);
+                const F e_side = sub(one(), e_other);
+                const F Lp = add(prev_L[0], mul(r_prev, sub(prev_L[1], prev_L[0])));
+                const F sp = add(prev_s[0], mul(r_prev, sub(prev_s[1], prev_s[0])));
+                const F Qp = newton_at(prev_Q, K + 1, r_prev);
+                const F L_other = mul(sub(Lp, mul(e_side, v[0])), inv_other);
+                const F s_other = t < nr ? mul(sub(sp, mul(e_side, v[1])), inv_other) : sub(sp, v[1]);
+                const F Q_other = mul(sub(Qp, mul(e_side, v[2])), inv_other);
+                L0 = g.side ? L_other : v[0];
+                L1 = g.side ? v[0] : L_other;
+                s0 = g.side ? s_other : v[1];
+                s1 = g.side ? v[1] : s_other;
+                Q[0] = g.side ? Q_other : v[2];
+                Q[1] = g.side ? v[2] : Q_other;
+                if (K == 2) Q[2] = add(sub(add(Q[1], Q[1]), Q[0]), add(v[3], v[3]));
+                if (K == 3) {
+                    Q[2] = v[4];
+                    // third difference: 6 times the leading coefficient
+                    const F c3 = add(add(v[3], v[3]), v[3]), d21 = sub(Q[2], Q[1]);
+                    Q[K] = add(add(add(add(d21, d21), d21), Q[0]), add(c3, c3));
+                }
+            }
             pending = t >= 1 ? 1 : 0;
         }
         Q[K + 1] = extrapolate_next(Q, K + 1);
+        prev_L[0] = L0;
+        prev_L[1] = L1;
+        prev_s[0] = s0;
+        prev_s[1] = s1;
+        for (int pt = 0; pt <= K; ++pt) prev_Q[pt] = Q[pt];
         F gX[NPTS];
         F e = sub(one(), u[t]), de = sub(u[t], e);  // e~(u_t, X) = (1-u_t) + X (2 u_t - 1)
         F L = L0, dL = sub(L1, L0), s = s0, ds = sub(s1, s0);
@@ -941,24 +1061,6 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
         tr.absorb("final", out, 32 * (2 * K + 2));
     }
     return ZK_OK;
-}
-
-// Value at x of the polynomial of degree < npts through y[j] at X = j (Newton's
-// forward differences: p(x) = sum_j (Delta^j y)(0) binom(x, j)).
-static host::F newton_at(const host::F* y, int npts, const host::F& x) {
-    using namespace host;
-    static const F inv_small[8] = {zero(), one(), inv(from_u64(2)), inv(from_u64(3)), inv(from_u64(4)),
-                                   inv(from_u64(5)), inv(from_u64(6)), inv(from_u64(7))};
-    F d[8];
-    for (int j = 0; j < npts; ++j) d[j] = y[j];
-    for (int level = 1; level < npts; ++level)
-        for (int j = npts - 1; j >= level; --j) d[j] = sub(d[j], d[j - 1]);
-    F acc = d[0], binom = one();
-    for (int j = 1; j < npts; ++j) {
-        binom = mul(mul(binom, sub(x, from_u64((uint64_t)(j - 1)))), inv_small[j]);
-        acc = add(acc, mul(d[j], binom));
-    }
-    return acc;
 }
 
 static int link_verify(const uint8_t seed[32], const uint8_t* proof, size_t len, size_t rows, size_t cols, int K,
