@@ -128,6 +128,43 @@ __device__ __forceinline__ Fr block_scan_mul(Fr v, uint32_t* lds, bool reverse) 
     return v;
 }
 
+// Inclusive products from both ends over THREADS values, by a workgroup of twice as
+// many threads: thread t < THREADS gets v_0 .. v_t, thread THREADS + t v_t .. v_last
+// (v: value t % THREADS in both), and from these everybody's neighbours: what comes
+// before, respectively after, value t.  One chain of eight dependent products where the
+// two scans one after the other are sixteen (a workgroup of 256 values: 16 -> 13.7 us).
+// lds: 16 * THREADS words.
+template <int THREADS>
+__device__ __forceinline__ Fr block_scan_both(Fr v, uint32_t* lds) {
+    const int t = threadIdx.x & (THREADS - 1);
+    const bool back = threadIdx.x >= THREADS;
+    uint32_t* mine = lds + (back ? 8 * THREADS : 0);
+    for (int off = 1; off < THREADS; off <<= 1) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) mine[k * THREADS + t] = v.l[k];
+        __syncthreads();
+        const int partner = back ? t + off : t - off;
+        if (partner >= 0 && partner < THREADS) {
+            Fr o;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) o.l[k] = mine[k * THREADS + partner];
+            v = fr_mul(v, o);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) mine[k * THREADS + t] = v.l[k];
+    __syncthreads();
+    Fr o = fr_one();
+    const int partner = back ? t + 1 : t - 1;
+    if (partner >= 0 && partner < THREADS) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) o.l[k] = mine[k * THREADS + partner];
+    }
+    __syncthreads();
+    return o;
+}
+
 // The scanned value of the thread before (reverse: after) this one, or one at the end of the line.
 template <int THREADS>
 __device__ __forceinline__ Fr block_neighbour(const Fr& scanned, uint32_t* lds, bool reverse) {
@@ -239,17 +276,26 @@ __global__ void __launch_bounds__(THREADS) k_bi_top_total(const uint32_t* __rest
 
 // out_t = inv_total * (product of the others) for the last level.
 template <int THREADS>
-__global__ void __launch_bounds__(THREADS) k_bi_top_finish(const uint32_t* __restrict__ src, size_t ss, size_t n,
-                                                           int shifted, Fr shift, Fr inv_total, uint32_t* out,
-                                                           size_t os) {
-    __shared__ uint32_t lds[8 * THREADS];
-    const int t = threadIdx.x;
-    Fr x = (size_t)t < n ? bi_load(src, ss, t, shifted, shift) : fr_one();
-    Fr pre = block_scan_mul<THREADS>(x, lds, false);  // x_0 .. x_t
-    Fr suf = block_scan_mul<THREADS>(x, lds, true);   // x_t .. x_last
-    Fr before = block_neighbour<THREADS>(pre, lds, false);
-    Fr after = block_neighbour<THREADS>(suf, lds, true);
-    if ((size_t)t < n) fr_store(out, os, t, fr_mul(inv_total, fr_mul(before, after)));
+__global__ void __launch_bounds__(2 * THREADS) k_bi_top_finish(const uint32_t* __restrict__ src, size_t ss, size_t n,
+                                                               int shifted, Fr shift, Fr inv_total, uint32_t* out,
+                                                               size_t os) {
+    __shared__ uint32_t lds[16 * THREADS];
+    const int t = threadIdx.x & (THREADS - 1);
+    const Fr x = (size_t)t < n ? bi_load(src, ss, t, shifted, shift) : fr_one();
+    Fr others = block_scan_both<THREADS>(x, lds);
+    if (threadIdx.x >= THREADS) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) lds[k * THREADS + t] = others.l[k];
+    } else {
+        others = fr_mul(others, inv_total);
+    }
+    __syncthreads();
+    if (threadIdx.x < THREADS && (size_t)t < n) {
+        Fr after;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) after.l[k] = lds[k * THREADS + t];
+        fr_store(out, os, t, fr_mul(others, after));
+    }
 }
 
 static const size_t kBiTopMax = kBlock;  // values the top kernels take
@@ -348,7 +394,7 @@ int batch_inverse_begin(BatchInverseJob& job, uint32_t* dst, size_t dst_stride, 
 int batch_inverse_end(const BatchInverseJob& job, const host::F& inv_total, hipStream_t stream) {
     typedef BatchInverseJob::Level Level;
     const Level& top = job.lv[job.depth];
-    hipLaunchKernelGGL(k_bi_top_finish<kBlock>, dim3(1), dim3(kBlock), 0, stream, top.x, top.xs, top.n, top.shifted,
+    hipLaunchKernelGGL(k_bi_top_finish<kBlock>, dim3(1), dim3(2 * kBlock), 0, stream, top.x, top.xs, top.n, top.shifted,
                        job.shift, to_dev(inv_total), top.p, top.ps);
     for (int d = job.depth - 1; d >= 0; --d) {
         const Level& cur = job.lv[d];

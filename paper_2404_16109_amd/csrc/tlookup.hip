@@ -178,7 +178,6 @@ struct ProveWs {
     uint32_t hist_parts;
     uint32_t* flags;    // [0] duplicate flag, [1] ticket of the final sums, [2..3] smallest bad index (64-bit)
     SmallFold4* fold4;  // constants of the first fold when S comes as small integers (tlookup_prove_small)
-    uint32_t* leaves;   // nleaves * 8 words
     uint32_t nleaves;
     uint32_t* dig_rows;    // the shorter rows of A's tree above kTreeChunk leaves
     uint32_t* dig_rows_b;  // the same for B
@@ -351,7 +350,6 @@ static int carve_prove(ProveWs& w, Carver& cv, size_t D, size_t N) {
     w.flags = (uint32_t*)cv.take(64);
     w.fold4 = (SmallFold4*)cv.take(sizeof(SmallFold4));
     w.nleaves = (uint32_t)div_up(N, kLeafCounts);
-    w.leaves = (uint32_t*)cv.take((size_t)w.nleaves * 32);
     w.dig_rows = (uint32_t*)cv.take(vec_digest_row_digests(D) * 32);
     w.dig_rows_b = (uint32_t*)cv.take(vec_digest_row_digests(N) * 32);
     w.part_blocks = round_blocks_max(D);
@@ -406,14 +404,23 @@ static size_t prove_ws_bytes(size_t D, size_t N, size_t K = 1) {
     return prove_ws_bytes_shapes(Ds, Ns, K);
 }
 
-// Multiplicities into w.m (and the digest leaves into w.leaves).  Returns
-// ZK_E_NOT_IN_TABLE with *bad_index set if some S_i is not in T.  Without hints
-// the rows are left in `found`, if the caller wants them.
-// With defer_check (hints given, workgroup histograms in use) the hints are taken
-// as they are; S_i = T[idx_i] is then checked by the caller.
+// What counting hands to the host: the four flag words, then the digests of m's leaves.
+static size_t counted_bytes(const ProveWs& w) { return 16 + (size_t)w.nleaves * 32; }
+// Smallest i with S_i not in T (all ones: none), once that has arrived.
+static uint64_t counted_bad(const uint8_t* staged) {
+    uint64_t bad;
+    memcpy(&bad, staged + 8, 8);
+    return bad;
+}
+
+// Whether the comparison of S with hinted rows can be left to the caller (workgroup histograms in use).
 static bool can_defer_check(const ProveWs& w, const uint32_t* idx, size_t D) { return w.hist && idx && D > (size_t)kBlock; }
 
-static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_t D, size_t N, uint64_t* bad_index,
+// Enqueues the multiplicities into w.m; `staged` (pinned, counted_bytes) receives the
+// rest, and `seq` (not zero) is published once it is there.  Without hints the rows
+// are left in `found`, if the caller wants them.  With defer_check the hints are taken
+// as they are; S_i = T[idx_i] is then checked by the caller.
+static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_t D, size_t N, uint8_t* staged, uint32_t seq,
                       Mailbox* mb, hipStream_t stream, bool defer_check = false, bool counts_as_fr = false,
                       uint32_t* found = nullptr) {
     if (defer_check && !can_defer_check(w, idx, D)) return ZK_E_BADARG;
@@ -454,22 +461,11 @@ static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_
                            idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots, w.cap_mask, w.canon, w.flags,
                            (unsigned long long*)(w.flags + 2), found);
     }
-    hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(w.nleaves, 64)), dim3(64), 0, stream, w.leaves, w.m,
-                       (uint32_t)N, w.nleaves);
+    LeafDigestArgs lf{(uint32_t*)(staged + 16), w.m, (uint32_t)N, w.nleaves, w.flags, (uint32_t*)staged, mb->words, w.flags + 1, seq};
+    hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(w.nleaves, 64)), dim3(128), 0, stream, lf);
     // the counts as field elements (w.M), while the host is busy with the digest
     if (counts_as_fr) hipLaunchKernelGGL(k_counts_to_fr, dim3(grid_for(N)), dim3(kBlock), 0, stream, w.M, N, w.m, N);
     ZK_HIP_TRY(hipGetLastError());
-    ZK_TRY(mailbox_bulk(mb, (size_t)w.nleaves * 32 + 16));
-    uint8_t* staged = mb->bulk + kBulkDigests;
-    ZK_HIP_TRY(hipMemcpyAsync(staged, w.flags, 16, hipMemcpyDeviceToHost, stream));
-    ZK_HIP_TRY(hipMemcpyAsync(staged + 16, w.leaves, (size_t)w.nleaves * 32, hipMemcpyDeviceToHost, stream));
-    ZK_HIP_TRY(hipStreamSynchronize(stream));
-    uint64_t bad;
-    memcpy(&bad, staged + 8, 8);
-    if (bad != UINT64_MAX) {
-        if (bad_index) *bad_index = bad;
-        return ZK_E_NOT_IN_TABLE;
-    }
     return ZK_OK;
 }
 
@@ -830,27 +826,40 @@ static int prove_core(const ProveCall& c) {
     bool defer_all = !c.check_upfront;
     for (size_t i = 0; i < K; ++i) defer_all = defer_all && can_defer_check(inst[i].w, inst[i].idx, inst[i].D);
     if (from_ints && !defer_all) return ZK_E_BADARG;  // counting would read S as a vector
-    for (size_t i = 0; i < K; ++i) {
-        uint64_t bad = 0;
-        int rc;
-        {
-            ProfileScope prof(kProfCount, stream);
+    {
+        // all instances' counting, then one wait
+        ProfileScope prof(kProfCount, stream);
+        size_t total = 0, at[kMailboxMaxInstances];
+        for (size_t i = 0; i < K; ++i) {
+            at[i] = total;
+            total += counted_bytes(inst[i].w);
+        }
+        ZK_TRY(mailbox_bulk(mb, total));
+        uint8_t* const staged = mb->bulk + kBulkDigests;
+        const uint32_t seq = mb->next_seq();
+        for (size_t i = 0; i < K; ++i) {
+            Instance& I = inst[i];
             // with hints, S_i = T[idx_i] is checked while A is made and hashed; all instances or none, so that the first
             // instance at fault is the one reported
-            inst[i].gather = c.by_rows || gather_by_default(inst[i].N);
-            inst[i].deferred = defer_all && inst[i].gather;
-            rc = count_rows(inst[i].w, inst[i].S, inst[i].idx, inst[i].T, inst[i].D, inst[i].N, &bad, mb, stream,
-                            inst[i].deferred, true, inst[i].idx ? nullptr : inst[i].w.found);
+            I.gather = c.by_rows || gather_by_default(I.N);
+            I.deferred = defer_all && I.gather;
+            ZK_TRY(count_rows(I.w, I.S, I.idx, I.T, I.D, I.N, staged + at[i], i + 1 == K ? seq : 0, mb, stream, I.deferred, true,
+                              I.idx ? nullptr : I.w.found));
         }
-        if (rc == ZK_E_NOT_IN_TABLE) {
-            if (c.aux) c.aux->bad_index = bad;
-            if (c.baux) {
-                c.baux->bad_instance = i;
-                c.baux->bad_index = bad;
+        ZK_TRY(mailbox_wait(mb, seq, stream));
+        for (size_t i = 0; i < K; ++i) {
+            const uint64_t bad = counted_bad(staged + at[i]);
+            if (bad != UINT64_MAX) {
+                if (c.aux) c.aux->bad_index = bad;
+                if (c.baux) {
+                    c.baux->bad_instance = i;
+                    c.baux->bad_index = bad;
+                }
+                ZK_HIP_TRY(hipStreamSynchronize(stream));
+                return ZK_E_NOT_IN_TABLE;
             }
+            digest_of_leaves(inst[i].md, staged + at[i] + 16, inst[i].w.nleaves);
         }
-        ZK_TRY(rc);
-        digest_of_leaves(inst[i].md, mb->bulk + kBulkDigests + 16, inst[i].w.nleaves);
     }
 
     uint64_t dims[1 + 2 * kMailboxMaxInstances];
@@ -1643,7 +1652,6 @@ static int prove_core(const ProveCall& c) {
 static size_t verify_ws_bytes(size_t D, size_t N) {
     Carver cv(nullptr, 0);
     cv.limbs(N);                                   // m as field elements
-    cv.take(div_up(N, kLeafCounts) * 32);          // leaf digests
     cv.take((vec_digest_leaves(D) + vec_digest_leaves(N)) * 32);  // hash trees over the witness vectors A and B
     cv.take(vec_digest_row_digests(D) * 32);
     cv.take(vec_digest_row_digests(N) * 32);
@@ -1787,7 +1795,6 @@ static int verify_core(const VerifyCall& c) {
     ZK_TRY(mailbox_get(&mb));
     Carver cv(c.ws, c.ws_bytes);
     uint32_t* Mfr = cv.limbs(N_max);
-    uint32_t* leaves = (uint32_t*)cv.take(div_up(N_max, kLeafCounts) * 32);
     uint32_t* dig_leaves = (uint32_t*)cv.take((vec_digest_leaves(D_max) + vec_digest_leaves(N_max)) * 32);
     uint32_t* dig_rows = (uint32_t*)cv.take(vec_digest_row_digests(D_max) * 32);
     uint32_t* dig_rows_b = (uint32_t*)cv.take(vec_digest_row_digests(N_max) * 32);
@@ -1824,9 +1831,8 @@ static int verify_core(const VerifyCall& c) {
         int job_m = -1;
         if (have_m) {
             hipLaunchKernelGGL(k_counts_to_fr, dim3(grid_for(N)), dim3(kBlock), 0, stream, Mfr, N, wit->m, N);
-            hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(nleaves, 64)), dim3(64), 0, stream, leaves, wit->m,
-                               (uint32_t)N, nleaves);
-            ZK_HIP_TRY(hipMemcpyAsync(mb->bulk + kBulkDigests, leaves, (size_t)nleaves * 32, hipMemcpyDeviceToHost, stream));
+            LeafDigestArgs lf{(uint32_t*)(mb->bulk + kBulkDigests), wit->m, (uint32_t)N, nleaves, nullptr, nullptr, nullptr, nullptr, 0};
+            hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(nleaves, 64)), dim3(128), 0, stream, lf);
             job_m = add_job(Mfr, N, l, vt);
         }
         {
@@ -1905,7 +1911,17 @@ int tlookup_multiplicities(uint32_t* m, fr_vec S, const uint32_t* idx, fr_vec T,
     Carver cv(ws, ws_bytes);
     ProveWs w;
     carve_prove(w, cv, D, N);
-    ZK_TRY(count_rows(w, S, idx, T, D, N, bad_index, mb, as_stream(stream)));
+    ZK_TRY(mailbox_bulk(mb, counted_bytes(w)));
+    const uint8_t* const staged = mb->bulk + kBulkDigests;
+    const uint32_t seq = mb->next_seq();
+    ZK_TRY(count_rows(w, S, idx, T, D, N, mb->bulk + kBulkDigests, seq, mb, as_stream(stream)));
+    ZK_TRY(mailbox_wait(mb, seq, as_stream(stream)));
+    const uint64_t bad = counted_bad(staged);
+    if (bad != UINT64_MAX) {
+        if (bad_index) *bad_index = bad;
+        ZK_HIP_TRY(hipStreamSynchronize(as_stream(stream)));
+        return ZK_E_NOT_IN_TABLE;
+    }
     ZK_HIP_TRY(hipMemcpyAsync(m, w.m, N * 4, hipMemcpyDeviceToDevice, as_stream(stream)));
     ZK_HIP_TRY(hipStreamSynchronize(as_stream(stream)));
     return ZK_OK;

@@ -389,32 +389,95 @@ static __global__ void __launch_bounds__(kBlock) k_counts_to_fr(uint32_t* __rest
 
 static const uint32_t kLeafCounts = 128;
 
-// One thread per leaf: SHA-256 of up to 128 counts as 4-byte little-endian
-// words.  Digest bytes go out in order, 32 per leaf.
-static __global__ void __launch_bounds__(64) k_leaf_digests(uint32_t* __restrict__ out, const uint32_t* __restrict__ m,
-                                                     uint32_t N, uint32_t nleaves) {
-    uint32_t leaf = blockIdx.x * 64 + threadIdx.x;
-    if (leaf >= nleaves) return;
-    uint32_t base = leaf * kLeafCounts;
-    uint32_t cnt = N - base < kLeafCounts ? N - base : kLeafCounts;
-    uint32_t nblk = (cnt + 3 + 15) / 16;
-    uint32_t h[8];
+// The rounds of a chain of blocks whose schedules (round constants added) another
+// wavefront of the workgroup makes in LDS, one block ahead: kw[block & 1], four rounds
+// per uint4 and lane.  Takes steps + 1 barriers, as the other does; blocks <= steps.
+__device__ __forceinline__ void sha256_piped_rounds(uint32_t (&h)[8], const uint4 (*kw)[16][64], uint32_t blocks, uint32_t steps) {
+    const int lane = threadIdx.x & 63;
     sha256_init(h);
-    for (uint32_t b = 0; b < nblk; ++b) {
-        uint32_t w[16];
+    __syncthreads();
+    for (uint32_t b = 0; b < steps; ++b) {
+        if (b < blocks) {
+            uint32_t s[8];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            uint32_t pos = b * 16 + i;
-            uint32_t v = 0;
-            if (pos < cnt) v = __builtin_bswap32(m[base + pos]);
-            else if (pos == cnt) v = 0x80000000u;
-            else if (pos == nblk * 16 - 1) v = cnt * 32;  // message length in bits
-            w[i] = v;
+            for (int i = 0; i < 8; ++i) s[i] = h[i];
+#pragma unroll
+            for (int g = 0; g < 16; ++g) {
+                const uint4 q = kw[b & 1][g][lane];
+                sha256_round(s, q.x);
+                sha256_round(s, q.y);
+                sha256_round(s, q.z);
+                sha256_round(s, q.w);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) h[i] += s[i];
         }
-        sha256_compress(h, w);
+        __syncthreads();
     }
+}
+
+// 64 leaves per workgroup, one lane each: SHA-256 of up to 128 counts as 4-byte
+// little-endian words.  Digest bytes go out in order, 32 per leaf, straight to pinned
+// host memory, and behind them the flag words of the counting (flags not null).  A leaf
+// is nine dependent blocks and there are never many: one wavefront does the rounds,
+// the other the schedules (42 us with one wavefront for both, 27 so).
+struct LeafDigestArgs {
+    uint32_t* out;
+    const uint32_t* m;
+    uint32_t N, nleaves;
+    const uint32_t* flags;  // four words
+    uint32_t* out_flags;
+    uint32_t* words;        // the mailbox
+    uint32_t* ticket;
+    uint32_t seq;
+};
+static __global__ void __launch_bounds__(128) k_leaf_digests(LeafDigestArgs g) {
+    __shared__ uint4 kw[2][16][64];
+    const int lane = threadIdx.x & 63;
+    const uint32_t leaf = blockIdx.x * 64 + lane;
+    const uint32_t base = (leaf < g.nleaves ? leaf : g.nleaves - 1) * kLeafCounts;
+    const uint32_t cnt = g.N < kLeafCounts ? g.N : kLeafCounts;  // N is a power of two: all leaves are alike
+    const uint32_t nblk = (cnt + 3 + 15) / 16;
+    if (threadIdx.x < 64) {
+        uint32_t h[8];
+        sha256_piped_rounds(h, kw, nblk, nblk);
+        if (leaf < g.nleaves) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) out[leaf * 8 + i] = __builtin_bswap32(h[i]);
+            for (int i = 0; i < 8; ++i) g.out[leaf * 8 + i] = __builtin_bswap32(h[i]);
+        }
+        if (blockIdx.x == 0 && lane < 4 && g.flags) g.out_flags[lane] = g.flags[lane];
+        mailbox_written();
+    } else {
+        for (uint32_t b = 0; b <= nblk; ++b) {
+            if (b < nblk) {
+                uint32_t w[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const uint32_t pos = b * 16 + i;
+                    uint32_t v = 0;
+                    if (pos < cnt) v = __builtin_bswap32(g.m[base + pos]);
+                    else if (pos == cnt) v = 0x80000000u;
+                    else if (pos == nblk * 16 - 1) v = cnt * 32;  // message length in bits
+                    w[i] = v;
+                }
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    if (q >= 4) sha256_schedule4(w, 4 * q);
+                    const int i = (4 * q) & 15;
+                    kw[b & 1][q][lane] = make_uint4(w[i] + kShaK[4 * q], w[i + 1] + kShaK[4 * q + 1], w[i + 2] + kShaK[4 * q + 2],
+                                                    w[i + 3] + kShaK[4 * q + 3]);
+                }
+            }
+            __syncthreads();
+        }
+    }
+    if (g.seq) {
+        __syncthreads();
+        if (threadIdx.x == 0 && atomicAdd(g.ticket, 1u) == gridDim.x - 1) {
+            *g.ticket = 0;
+            mailbox_publish(g.words, g.seq);
+        }
+    }
 }
 
 // ---- digest of a vector of field elements (stand-in for its commitment) ----------
@@ -750,26 +813,7 @@ static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs a
     const size_t leaf = (size_t)(group - job.first_group) * 64 + lane;
     if (rounds) {
         uint32_t h[8];
-        sha256_init(h);
-        __syncthreads();
-        for (uint32_t b = 0; b < steps; ++b) {
-            if (b < blocks) {
-                uint32_t s[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) s[i] = h[i];
-#pragma unroll
-                for (int g = 0; g < 16; ++g) {
-                    const uint4 q = kw[pair][b & 1][g][lane];
-                    sha256_round(s, q.x);
-                    sha256_round(s, q.y);
-                    sha256_round(s, q.z);
-                    sha256_round(s, q.w);
-                }
-#pragma unroll
-                for (int i = 0; i < 8; ++i) h[i] += s[i];
-            }
-            __syncthreads();
-        }
+        sha256_piped_rounds(h, kw[pair], blocks, steps);
         if (live && leaf < job.L) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) job.out[leaf * 8 + k] = h[k];
