@@ -445,21 +445,27 @@ static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_
         // equal chunks, as few passes per workgroup as the 16-bit counters allow
         const size_t passes = div_up(div_up(D, w.hist_parts), (size_t)kHistPass);
         const size_t per_block = align_up(div_up(D, w.hist_parts * passes), kHistThreads);
-        if (defer_check)
+        const bool find = !idx && found;
+        if (find) {
+            hipLaunchKernelGGL(k_find_rows, dim3((unsigned)div_up(D, kBlock)), dim3(kBlock), 0, stream, found, S.limbs, S.stride, D,
+                               w.rows, (uint32_t)N, w.slots, w.cap_mask, (unsigned long long*)(w.flags + 2));
+            idx = found;
+        }
+        if (defer_check || find)
             hipLaunchKernelGGL(k_count_lds<false>, dim3(w.hist_parts), dim3(kHistThreads), lds_bytes, stream, w.m, w.hist,
                                S.limbs, S.stride, D, per_block, idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots,
-                               w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2), found);
+                               w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2));
         else
             hipLaunchKernelGGL(k_count_lds<true>, dim3(w.hist_parts), dim3(kHistThreads), lds_bytes, stream, w.m, w.hist,
                                S.limbs, S.stride, D, per_block, idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots,
-                               w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2), found);
+                               w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2));
         const uint32_t group = 16;
         hipLaunchKernelGGL(k_hist_reduce, dim3((unsigned)div_up(N, kBlock), (unsigned)div_up(w.hist_parts, group)),
                            dim3(kBlock), 0, stream, w.m, w.hist, w.hist_parts, group, (uint32_t)N);
     } else {
         hipLaunchKernelGGL(k_count, dim3(grid_for(D, kBlock, 8192)), dim3(kBlock), 0, stream, w.m, S.limbs, S.stride, D,
                            idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots, w.cap_mask, w.canon, w.flags,
-                           (unsigned long long*)(w.flags + 2), found);
+                           (unsigned long long*)(w.flags + 2));
     }
     LeafDigestArgs lf{(uint32_t*)(staged + 16), w.m, (uint32_t)N, w.nleaves, w.flags, (uint32_t*)staged, mb->words, w.flags + 1, seq};
     hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(w.nleaves, 64)), dim3(128), 0, stream, lf);

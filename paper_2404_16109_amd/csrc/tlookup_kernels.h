@@ -94,6 +94,22 @@ static __global__ void __launch_bounds__(kBlock) k_canon_rows(uint32_t* __restri
     }
 }
 
+// The row of every S_i, for calls without hints (the smallest i that has none ends up in
+// *bad, its row is the table's length).  A kernel of its own: four dependent accesses
+// per element want wavefronts, and the counting's 128 KiB of LDS per workgroup leaves
+// four per SIMD (2^25 elements in 2^16 rows: 0.98 ms when the counting looked them up,
+// 0.87 ms here and there together).
+static __global__ void __launch_bounds__(kBlock) k_find_rows(uint32_t* __restrict__ found, const uint32_t* __restrict__ S, size_t ss,
+                                                      size_t D, const uint4* __restrict__ rows, uint32_t N,
+                                                      const uint32_t* __restrict__ slots, uint32_t cap_mask,
+                                                      unsigned long long* bad) {
+    const size_t i = blockIdx.x * (size_t)kBlock + threadIdx.x;
+    if (i >= D) return;
+    const uint32_t row = hash_find_rows(slots, cap_mask, rows, fr_load(S, ss, i));
+    found[i] = row == kEmptySlot ? N : row;
+    if (row == kEmptySlot) atomicMin(bad, (unsigned long long)i);
+}
+
 // A wavefront's running total for the row it keeps meeting (wave-uniform).
 // Long runs of one row (padding, saturated activations) would otherwise become
 // a stream of atomics to a single address, which the memory system serialises.
@@ -138,15 +154,13 @@ __device__ __forceinline__ void count_merged(uint32_t* m, uint32_t row, bool val
 }
 
 // m[row(S_i)] += 1.  With idx the row is given and only checked; without, it is
-// found through the hash (and left in `found`, if the caller wants it).  The
-// smallest offending i ends up in *bad.
+// found through the hash.  The smallest offending i ends up in *bad.
 static __global__ void __launch_bounds__(kBlock) k_count(uint32_t* m, const uint32_t* __restrict__ S, size_t ss, size_t D,
                                                   const uint32_t* __restrict__ idx, const uint32_t* __restrict__ T,
                                                   size_t ts, const uint4* __restrict__ rows, uint32_t N,
                                                   const uint32_t* __restrict__ slots,
                                                   uint32_t cap_mask, const uint32_t* __restrict__ canon,
-                                                  const uint32_t* __restrict__ dup_flag, unsigned long long* bad,
-                                                  uint32_t* __restrict__ found) {
+                                                  const uint32_t* __restrict__ dup_flag, unsigned long long* bad) {
     const bool dups = *dup_flag != 0;
     // every lane of a wavefront runs the same number of iterations, so the
     // cross-lane steps in count_merged see whole wavefronts
@@ -172,7 +186,6 @@ static __global__ void __launch_bounds__(kBlock) k_count(uint32_t* m, const uint
                 }
             } else {
                 row = hash_find_rows(slots, cap_mask, rows, v);
-                if (found) found[i] = row;
             }
             if (row == kEmptySlot) atomicMin(bad, (unsigned long long)i);
         }
@@ -204,8 +217,7 @@ static __global__ void __launch_bounds__(kHistThreads)
 k_count_lds(uint32_t* m, uint32_t* __restrict__ part, const uint32_t* __restrict__ S, size_t ss, size_t D,
             size_t chunk, const uint32_t* __restrict__ idx, const uint32_t* __restrict__ T, size_t ts,
             const uint4* __restrict__ rows, uint32_t N, const uint32_t* __restrict__ slots, uint32_t cap_mask,
-            const uint32_t* __restrict__ canon, const uint32_t* __restrict__ dup_flag, unsigned long long* bad,
-            uint32_t* __restrict__ found) {
+            const uint32_t* __restrict__ canon, const uint32_t* __restrict__ dup_flag, unsigned long long* bad) {
     extern __shared__ uint32_t hist[];  // (N+1)/2 words, two 16-bit counters each
     const uint32_t words = (N + 1) / 2;
     const bool dups = *dup_flag != 0;
@@ -256,10 +268,7 @@ k_count_lds(uint32_t* m, uint32_t* __restrict__ part, const uint32_t* __restrict
                     }
                     row[e] = r;
                 } else {
-                    if constexpr (CHECK_S) {
-                        row[e] = hash_find_rows(slots, cap_mask, rows, v[e]);
-                        if (found) found[i[e]] = row[e];
-                    }
+                    if constexpr (CHECK_S) row[e] = hash_find_rows(slots, cap_mask, rows, v[e]);
                 }
                 // without the comparison a hint out of range is left for the caller's check to report
                 if (CHECK_S && row[e] == kEmptySlot) atomicMin(bad, (unsigned long long)i[e]);
