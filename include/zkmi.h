@@ -18,11 +18,11 @@
  * entry point allocates device memory; `*_workspace_bytes` says how much
  * workspace a call needs.  The library does keep a little state of its own PER
  * HOST THREAD, allocated by that thread's first call that needs it and kept until
- * the process ends: 18 KiB of pinned host memory into which kernels write the
- * handful of sums a step returns (and, at the end of a single tlookup proof, the
- * five arrays of at most 64 elements from which the host finishes the rounds),
- * 64 bytes of coherent pinned memory through which a kernel that stays resident
- * over several sumcheck rounds receives each round's challenge, a pinned staging buffer for digest leaves that grows to the
+ * the process ends: 110 KiB of pinned host memory into which kernels write the
+ * handful of sums a step returns (and, towards the end of a proof, the arrays of at
+ * most 64 elements each from which the host finishes the rounds), 64 bytes of
+ * coherent pinned memory through which a kernel that stays resident over a sumcheck
+ * round receives the challenge, a pinned staging buffer for digest leaves that grows to the
  * largest table seen, and the event pool of zkmi_profile_*.  Calls from
  * different host threads share nothing; a thread's calls must not overlap.
  * zkmi_thread_init makes that allocation at a time of the caller's choosing and
@@ -518,10 +518,10 @@ int zkmi_thread_release(void);
  * For benchmarks: the library can time its own phases with HIP events recorded
  * on the caller's stream (so that kernels are timed where they are launched).
  * State is per host thread.  Phases: "total" (a whole tlookup_prove call),
- * "count" (multiplicities and digest leaves), "inverse" (both batch inversions),
- * "digest" (the hash trees over A and B), "round_small" (the kernels of the rounds
- * that are bound by latency: those that also bind a table variable and those of at
- * most 256 pairs, the resident kernel included),
+ * "count" (multiplicities and digest leaves), "inverse" (the batch inversions),
+ * "digest" (the hash trees over A and B; A is made there), "round_small" (the kernels
+ * of the rounds that are bound by latency: those that also bind a table variable and
+ * the passes that serve several rounds),
  * "round_data29" (the large folding rounds, which run on 29-bit limbs: one
  * record per launch of that kernel), "round_data" (the first round's kernel),
  * "round_table" (the table-side round kernel alone, which only runs when D = N).
@@ -534,25 +534,27 @@ int zkmi_profile_enable(int on);
 int zkmi_profile_reset(void);
 int zkmi_profile_query(const char* phase, uint64_t* records, double* total_ms);
 
-/* Self-test of the bounded wait in the kernels that stay resident over the last
- * sumcheck rounds and receive each round's challenge from the host: such a kernel
- * is started on a tiny input with a bound of a few polls and never answered.  It
+/* Self-test of the bounded wait in the kernel that stays resident over a sumcheck
+ * round and receives its challenge from the host: it is started on a tiny input with a bound of a few polls and never answered.  It
  * must publish its first round, then give up by itself and publish nothing more.
  * Then an abort is left in the channel, as a call that ends early leaves one, and
  * the kernel is started again and answered: it must run to its end.  ZK_OK if
  * both hold, ZK_E_HIP otherwise.  ws: device, at least 1 KiB. */
 int zkmi_selftest_resident_wait(void* ws, size_t ws_bytes, void* stream);
 
-/* Which kernel runs each sumcheck round of a tlookup proof of K instances of shape
- * (D, N), and where it reads S from, decided exactly as the prover decides it but
- * walked on the host alone: no GPU is touched.  from_ints != 0: the plan of
+/* Which kernel each sumcheck round of a tlookup proof of K instances of shape
+ * (D, N) is one for, and where it reads S from, decided as the prover decides it but
+ * walked on the host alone: no GPU is touched.  The prover runs a round by itself as
+ * told here while more than 16 variables are left; the rounds after that come several
+ * from one pass over the arrays (from integers, after the first two), whatever kernel
+ * they are one for.  from_ints != 0: the plan of
  * tlookup_prove_small (K = 1; ZK_E_BADARG for shapes that path does not take).
  * out (host): four integers per round -- kernel (0 first round, 1 large folding
- * round on 29-bit limbs, 2 data and table side together, 3 one workgroup per
- * round, 4 resident kernel, 5 the first pass when it serves the first two rounds,
- * 6 the second of those two: no kernel, 7 no kernel either: the resident kernel
- * has handed the arrays, at most 64 elements each, to the host, which runs the
- * round itself), source of S (0 the caller's
+ * round on 29-bit limbs, 2 data and table side together, 3 and 4 at
+ * most 256 pairs, of several instances or of one, 5 the first pass when it serves the first two rounds,
+ * 6 the second of those two: no kernel, 7 no kernel either: the
+ * host has been handed the arrays, at most 64 elements each, and runs the round
+ * itself), source of S (0 the caller's
  * vector, 1 the caller's integer columns, 2 folded 32-bit words in the workspace,
  * 3 folded 29-bit limb planes in the workspace), arrays arrive as 32-bit words,
  * arrays leave as 32-bit words (both only meaningful for kernel 1).  Returns the
