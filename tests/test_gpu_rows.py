@@ -31,7 +31,7 @@ def _instance(orc, zk, D, N, seed):
 
 
 @pytest.mark.parametrize("D,N", [(1, 1), (2, 1), (2, 2), (4, 2), (64, 64), (128, 16), (256, 256), (512, 4), (1 << 13, 512),
-                                 (1 << 14, 2)])
+                                 (1 << 14, 2), (1 << 18, 1 << 17)])
 def test_every_entry_point(zk, orc, D, N):
     seed = bytes([D % 251, N % 251]) * 16
     Sb, Tb, Sv, Tv, idx = _instance(orc, zk, D, N, D + N)
