@@ -130,7 +130,7 @@ static int eq_pool_build(EqPool& ep, const host::F* u, int n, Carver& cv, hipStr
     args.total = off;
     if (q > 64) return ZK_E_BADARG;
     if (off) {
-        hipLaunchKernelGGL(k_eq_pool, dim3(grid_for(off)), dim3(kBlock), 0, stream, ep.pool, ep.stride, args);
+        launch_eq_pool(ep.pool, ep.stride, args, stream);
         ZK_HIP_TRY(hipGetLastError());
     }
     return ZK_OK;

@@ -502,7 +502,7 @@ static int link_tables_build(LinkTables& lt, const host::F* u, int nr, int nc, C
     args.total = off;
     if (q > 64) return ZK_E_BADARG;
     args.scale = to_dev(host::one());
-    hipLaunchKernelGGL(k_eq_pool, dim3(grid_for(off)), dim3(kBlock), 0, stream, lt.pool, lt.stride, args);
+    launch_eq_pool(lt.pool, lt.stride, args, stream);
     ZK_HIP_TRY(hipGetLastError());
     return ZK_OK;
 }
@@ -1012,7 +1012,7 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
             ea.ntables = 2;
             ea.total = (uint32_t)w.mle_entries;
             ea.scale = to_dev(one());
-            hipLaunchKernelGGL(k_eq_pool, dim3(grid_for(ea.total)), dim3(kBlock), 0, stream, w.mle_tables, w.mle_entries, ea);
+            launch_eq_pool(w.mle_tables, w.mle_entries, ea, stream);
             const EqSplit eq{w.mle_tables, w.mle_entries, 0, 1u << lb, lb, 1};
             const unsigned blocks = 1u << (n - lb);
             if (small) {
