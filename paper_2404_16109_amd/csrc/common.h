@@ -179,7 +179,10 @@ inline host::F from_dev(const uint32_t limbs[8]) { return host::from_device_limb
 
 // Device side of the completion protocol.  Every thread that writes result words
 // calls mailbox_written() after its stores; one thread calls mailbox_publish()
-// once all writers are known to be done (same thread, or after a barrier).
+// once all writers are known to be done (same thread, or after a barrier).  A writer
+// fences for itself also where a later kernel publishes: that one's fences order its
+// own stores, and between two kernels of a stream the runtime need not make stores
+// visible to the host.
 __device__ __forceinline__ void mailbox_written() { __threadfence_system(); }
 __device__ __forceinline__ void mailbox_publish(uint32_t* words, uint32_t seq) {
     if (seq == 0) return;

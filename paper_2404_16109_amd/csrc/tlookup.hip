@@ -255,7 +255,7 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
             total += cnt[q];
             more = true;
         }
-        lv.job[q] = VecLeavesJob{j.v, j.stride, j.n, cnt[q], out, blocks, j.from};
+        lv.job[q] = VecLeavesJob{j.v, j.stride, j.n, cnt[q], out, blocks, j.from, out == host_row};
         in[q] = out;
         blocks += (uint32_t)div_up(cnt[q], 64);
     }
@@ -282,7 +282,7 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
             while (chunk < kTreeChunk && cnt[q] / chunk > kTreeHostRow) chunk *= 4;
             cnt[q] /= chunk;
             uint32_t* out = cnt[q] <= kTreeHostRow ? const_cast<uint32_t*>(jobs[q].host_row) : rows[q];
-            tr.job[tr.njobs++] = DigestTreeJob{in[q], out, chunk, blocks};
+            tr.job[tr.njobs++] = DigestTreeJob{in[q], out, chunk, blocks, out == jobs[q].host_row};
             in[q] = out;
             blocks += (uint32_t)cnt[q];
             if (cnt[q] > kTreeHostRow) {

@@ -533,6 +533,7 @@ struct VecLeavesJob {
     uint32_t* out;         // L digests; device memory, or pinned host memory if the host finishes the tree from here
     uint32_t first_group;  // of 64 leaves each
     LeafGather from;
+    int to_host;           // out is pinned host memory: fenced here, whichever launch publishes
 };
 static const int kDigestMaxJobs = 16;  // A and B of eight instances
 struct VecLeavesArgs {
@@ -734,7 +735,7 @@ __device__ __forceinline__ void leaf_by_lane(const VecLeavesArgs& args, const Ve
     sha256_compress(h, w);
 #pragma unroll
     for (int k = 0; k < 8; ++k) job.out[leaf * 8 + k] = h[k];
-    if (args.seq) mailbox_written();
+    if (job.to_host) mailbox_written();
 }
 
 // MODE: of the jobs that have rows.
@@ -826,7 +827,7 @@ static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs a
         if (live && leaf < job.L) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) job.out[leaf * 8 + k] = h[k];
-            if (args.seq) mailbox_written();
+            if (job.to_host) mailbox_written();
         }
     } else {
         if (MODE != kLeafPlain && job.from.rows) leaf_schedules<MODE>(args, job, live, leaf, blocks, steps, kw[pair]);
@@ -847,6 +848,7 @@ struct DigestTreeJob {
     uint32_t* out;
     uint32_t chunk;
     uint32_t first_block;
+    int to_host;  // as in VecLeavesJob
 };
 struct DigestTreeArgs {
     DigestTreeJob job[kDigestMaxJobs];
@@ -893,7 +895,7 @@ static __global__ void __launch_bounds__(kBlock) k_digest_tree(DigestTreeArgs ar
     }
     if (threadIdx.x < 8) {
         job.out[(size_t)b * 8 + threadIdx.x] = from_lds ? rows[cur][threadIdx.x] : base[threadIdx.x];
-        if (args.seq) mailbox_written();
+        if (job.to_host) mailbox_written();
     }
     if (args.seq == 0) return;
     __syncthreads();
