@@ -429,6 +429,13 @@ int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint
         const int s = mle_stage_count(jobs[q].nvars);
         if (s > most_stages) most_stages = s;
     }
+    if (most_stages == 0) {  // single elements are their own values: no scratch is asked for
+        for (int q = 0; q < njobs; ++q)
+            hipLaunchKernelGGL(k_emit, dim3(1), dim3(64), 0, stream, jobs[q].a, jobs[q].stride, (size_t)0, jobs[q].out_words,
+                               mb->words, q + 1 == njobs ? seq : 0u);
+        ZK_HIP_TRY(hipGetLastError());
+        return ZK_OK;
+    }
     targs.first[0] = 0;
     targs.first[1] = mle_table_entries(targs.nvars[0]);
     targs.total = targs.first[1] + (npoints == 2 ? mle_table_entries(targs.nvars[1]) : 0);
@@ -442,7 +449,7 @@ int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint
     uint32_t* ticket = (uint32_t*)cv.take(256);
     if (!targs.table || !ticket) return ZK_E_BUFSZ;
     launch_fill_u32(ticket, 1, 0u, stream);
-    if (targs.total) hipLaunchKernelGGL(k_mle_table, dim3(grid_for((size_t)targs.total * 32)), dim3(kBlock), 0, stream, targs);
+    hipLaunchKernelGGL(k_mle_table, dim3(grid_for((size_t)targs.total * 32)), dim3(kBlock), 0, stream, targs);
     // every job's last stage in the last launch, so that one flag stands for all
     ToepSource cur[kMleMaxJobs];
     int left[kMleMaxJobs];
@@ -453,14 +460,13 @@ int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint
         left[q] = jobs[q].nvars;
         table[q] = (const uint4*)(targs.table + (size_t)(point_of[q] ? targs.first[1] : 0) * kToepBytes);
     }
-    const int launches = most_stages > 0 ? most_stages : 1;
-    for (int step = 0; step < launches; ++step) {
+    for (int step = 0; step < most_stages; ++step) {
         MleStageArgs args;
         memset(&args, 0, sizeof args);
         uint32_t blocks = 0;
         for (int q = 0; q < njobs; ++q) {
-            const int s = mle_stage_count(jobs[q].nvars), t = step - (launches - s);
-            if (s == 0 && step == launches - 1) {  // a single element: its value
+            const int s = mle_stage_count(jobs[q].nvars), t = step - (most_stages - s);
+            if (s == 0 && step == most_stages - 1) {  // a single element: its value
                 hipLaunchKernelGGL(k_emit, dim3(1), dim3(64), 0, stream, jobs[q].a, jobs[q].stride, (size_t)0, jobs[q].out_words,
                                    mb->words, 0u);
                 continue;
@@ -489,14 +495,12 @@ int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint
             table[q] += (size_t)j.C * (kToepBytes / 16);
             blocks += (uint32_t)div_up(j.P, 128);
         }
-        if (step == launches - 1) {
+        if (step == most_stages - 1) {
             args.words = mb->words;
             args.ticket = ticket;
             args.seq = seq;
         }
-        if (args.njobs) hipLaunchKernelGGL(k_mle_stage, dim3(blocks), dim3(kBlock), 0, stream, args);
-        else if (seq) hipLaunchKernelGGL(k_emit, dim3(1), dim3(64), 0, stream, jobs[0].a, jobs[0].stride, (size_t)0,
-                                         jobs[0].out_words, mb->words, seq);
+        hipLaunchKernelGGL(k_mle_stage, dim3(blocks), dim3(kBlock), 0, stream, args);
     }
     ZK_HIP_TRY(hipGetLastError());
     return ZK_OK;

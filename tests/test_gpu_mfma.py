@@ -46,3 +46,15 @@ def test_mle_eval(zk, orc, nvars, values):
     for vec in (v, restrided(zk, v, n + 1)):
         rc, got = zk.fr_mle_eval(vec, point)
         assert rc == 0 and got == want
+
+
+@pytest.mark.parametrize("stride", [1, 3])
+def test_mle_eval_of_one_element(zk, orc, stride):
+    """No variables: the value is the element itself, and the call needs no workspace."""
+    import ctypes
+    for value in (0, 1, 5, R - 1):
+        v = restrided(zk, zk.vec_from_bytes(orc.to_bytes([value])), stride)
+        out = zk.binding.fr_t()
+        rc = zk.raw().fr_mle_eval(ctypes.byref(out), v.c, None, 0, None, 0, None)
+        assert rc == 0 and int.from_bytes(out, "little") == value
+        assert zk.fr_mle_eval(v, []) == (0, value)
