@@ -419,7 +419,10 @@ int batch_inverse_run(uint32_t* dst, size_t dst_stride, const uint32_t* src, siz
                                seq, stream, nullptr, 0, nullptr, 0, 0));
     ZK_TRY(mailbox_wait(mb, seq, stream));
     host::F total = from_dev(mb->words + kMailboxInvA);
-    if (host::is_zero(total)) return ZK_E_ZERO_DENOM;
+    if (host::is_zero(total)) {
+        ZK_HIP_TRY(hipStreamSynchronize(stream));  // error codes that depend on data come from an idle stream
+        return ZK_E_ZERO_DENOM;
+    }
     return batch_inverse_end(job, host::inv(total), stream);
 }
 

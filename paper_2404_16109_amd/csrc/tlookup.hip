@@ -928,7 +928,10 @@ static int prove_core(const ProveCall& c) {
         pre[0] = one();
         for (size_t q = 0; q < njobs; ++q) {
             tot[q] = from_dev(totals[q]);
-            if (is_zero(tot[q])) return ZK_E_ZERO_DENOM;
+            if (is_zero(tot[q])) {
+                ZK_HIP_TRY(hipStreamSynchronize(stream));
+                return ZK_E_ZERO_DENOM;
+            }
             pre[q + 1] = mul(pre[q], tot[q]);
         }
         F suffix_inv = inv(pre[njobs]);  // 1 / (tot_0 ... tot_q) while walking down
@@ -1048,6 +1051,7 @@ static int prove_core(const ProveCall& c) {
                     c.baux->bad_instance = i;
                     c.baux->bad_index = bad;
                 }
+                ZK_HIP_TRY(hipStreamSynchronize(stream));
                 return ZK_E_NOT_IN_TABLE;
             }
             inst[i].c1 = from_dev(inst[i].const_words);

@@ -739,7 +739,10 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
     tr.absorb("yhat", out + 32, 32);
     out += 64;
     const F alpha = tr.challenge("alpha");
-    if (is_zero(alpha)) return ZK_E_ZERO_DENOM;  // the scaled Y could not be scaled back (probability 1/|F|)
+    if (is_zero(alpha)) {  // the scaled Y could not be scaled back (probability 1/|F|)
+        ZK_HIP_TRY(hipStreamSynchronize(stream));
+        return ZK_E_ZERO_DENOM;
+    }
     F claim = mul(sqr(alpha), cy);
 
     LinkTables lt;

@@ -1,9 +1,12 @@
-"""What kernels hand to the host through pinned memory: digest rows that one launch writes and a later one publishes."""
+"""What kernels hand to the host through pinned memory: digest rows that one launch writes and a later one publishes,
+and what a call leaves behind when it ends in an error that depends on data."""
 import random
 
 import numpy as np
 import pytest
 import torch
+
+from tests.pyref import R
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +48,26 @@ def test_several_trees(zk, orc):
         for s, proof in zip(sets, want):
             rc, got, _ = zk.tlookup_prove_multi(seed, [m[2] for m in s], [m[4] for m in s], [m[3] for m in s])
             assert rc == 0 and got == proof
+
+
+def test_errors_that_depend_on_data_leave_the_stream_idle(zk):
+    """include/zkmi.h: such calls synchronise the stream before they return."""
+    D, N = 1 << 17, 1 << 8
+    Sb, Tb, S, T, idx = _instance(zk, D, N, 3)
+    bad = zk.Vec(D)
+    bad.data.copy_(S.data)
+    bad.data[:, 77] ^= 1
+    minus_t = R - int.from_bytes(Tb[5].tobytes(), "little")
+    zeros, out = zk.vec_from_bytes(np.zeros((1000, 32), dtype=np.uint8)), zk.Vec(1000)
+    ws = torch.empty(zk.tlookup_workspace_bytes(D, N), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        calls = {"hinted": (zk.ZK_E_NOT_IN_TABLE, lambda: zk.tlookup_prove(b"\1" * 32, bad, idx, T, ws=ws)[0]),
+                 "found": (zk.ZK_E_NOT_IN_TABLE, lambda: zk.tlookup_prove(b"\1" * 32, bad, None, T, ws=ws)[0]),
+                 "denominator": (zk.ZK_E_ZERO_DENOM, lambda: zk.tlookup_prove(b"\1" * 32, S, idx, T, ws=ws, forced_beta=minus_t)[0]),
+                 "inverse": (zk.ZK_E_ZERO_DENOM, lambda: zk.fr_batch_inverse(out, zeros))}
+        for name, (code, call) in calls.items():
+            for _ in range(10):
+                assert call() == code, name
+                assert stream.query(), name
