@@ -22,8 +22,9 @@
  * handful of sums a step returns (and, towards the end of a proof, the arrays of at
  * most 64 elements each from which the host finishes the rounds), 64 bytes of
  * coherent pinned memory through which a kernel that stays resident over a sumcheck
- * round receives the challenge, a pinned staging buffer for digest leaves that grows to the
- * largest table seen, and the event pool of zkmi_profile_*.  Calls from
+ * round receives the challenge, a pinned staging buffer that grows to the most a call
+ * has needed (128 KiB of digest rows, and a leaf digest of 32 bytes per 128 rows of all
+ * of the call's tables), and the event pool of zkmi_profile_*.  Calls from
  * different host threads share nothing; a thread's calls must not overlap.
  * zkmi_thread_init makes that allocation at a time of the caller's choosing and
  * zkmi_thread_release gives the pinned memory back (both are optional).
@@ -507,12 +508,16 @@ int zkattn_link_verify(const uint8_t seed[32], const uint8_t* proof, size_t len,
 
 /* The calling host thread's pinned state (see Ownership), for callers that want no
  * allocation inside their first proof: zkmi_thread_init allocates it now, with
- * the staging buffer sized for tables of up to max_table_rows rows (a longer
- * table later makes it grow once more); zkmi_thread_release frees it (a later
+ * the staging buffer sized for TLOOKUP_BATCH_MAX tables of max_table_rows rows each (a
+ * call whose tables are longer makes it grow once more); zkmi_thread_release frees it (a later
  * call allocates it again).  Neither may overlap another call of the same
  * thread.  Errors: ZK_E_HIP if the runtime refuses. */
 int zkmi_thread_init(size_t max_table_rows);
 int zkmi_thread_release(void);
+
+/* Self-test of that promise: where the calling thread's staging buffer is and how long
+ * (zeros: there is none).  A call that had to grow it moves it. */
+int zkmi_selftest_staging(uint64_t* address, uint64_t* bytes);
 
 /* ---- measurement support ------------------------------------------------------
  * For benchmarks: the library can time its own phases with HIP events recorded

@@ -100,6 +100,7 @@ def _load():
         "tlookup_multiplicities": (i32, [vp, fr_vec, vp, fr_vec, vp, sz, P(ctypes.c_uint64), vp]),
         "zkmi_thread_init": (i32, [sz]),
         "zkmi_thread_release": (i32, []),
+        "zkmi_selftest_staging": (i32, [P(ctypes.c_uint64), P(ctypes.c_uint64)]),
         "tlookup_proof_bytes": (sz, [sz]),
         "tlookup_prove": (i32, [vp, fr_vec, vp, fr_vec, vp, sz, P(sz), P(tlookup_aux), vp, sz, vp]),
         "tlookup_prove_by_rows": (i32, [vp, fr_vec, vp, fr_vec, vp, sz, P(sz), P(tlookup_aux), vp, sz, vp]),
@@ -150,7 +151,7 @@ def _load():
 
 
 _lib = _load()
-EXPORTS = ["zkmi_version", "zkmi_thread_init", "zkmi_thread_release", "zkmi_sha256", "zkmi_selftest_resident_wait", "zkmi_selftest_tlookup_plan", "zkmi_selftest_host_rounds", "zkmi_profile_enable", "zkmi_profile_reset", "zkmi_profile_query", "fr_constants", "fr_from_i32", "fr_from_canonical", "fr_to_canonical", "fr_add", "fr_sub",
+EXPORTS = ["zkmi_version", "zkmi_thread_init", "zkmi_thread_release", "zkmi_selftest_staging", "zkmi_sha256", "zkmi_selftest_resident_wait", "zkmi_selftest_tlookup_plan", "zkmi_selftest_host_rounds", "zkmi_profile_enable", "zkmi_profile_reset", "zkmi_profile_query", "fr_constants", "fr_from_i32", "fr_from_canonical", "fr_to_canonical", "fr_add", "fr_sub",
            "fr_mul", "fr_add_scalar", "fr_mul_scalar", "fr_axpy", "fr_batch_inverse_workspace_bytes",
            "fr_batch_inverse", "fr_sum_workspace_bytes", "fr_sum", "fr_sum_noalloc", "fr_eq_table", "fr_mle_eval_workspace_bytes",
            "fr_mle_eval", "tlookup_workspace_bytes", "tlookup_multiplicities", "tlookup_proof_bytes", "tlookup_prove",
@@ -262,6 +263,14 @@ def zkmi_thread_init(max_table_rows):
 
 def zkmi_thread_release():
     return _lib.zkmi_thread_release()
+
+
+def zkmi_selftest_staging():
+    """(address, bytes) of the calling thread's pinned staging buffer."""
+    address, size = ctypes.c_uint64(0), ctypes.c_uint64(0)
+    rc = _lib.zkmi_selftest_staging(ctypes.byref(address), ctypes.byref(size))
+    assert rc == ZK_OK, rc
+    return address.value, size.value
 
 
 def zkmi_profile_enable(on):

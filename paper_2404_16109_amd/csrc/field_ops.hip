@@ -238,11 +238,21 @@ int zkmi_sha256(const uint8_t* data, size_t len, uint8_t out[32], int use_sha_in
     return used;
 }
 
+static_assert(kMailboxMaxInstances == TLOOKUP_BATCH_MAX, "a call's tables");
+
 int zkmi_thread_init(size_t max_table_rows) {
     Mailbox* mb;
     ZK_TRY(mailbox_get(&mb));
-    // the staging buffer holds a table's leaf digests (one per 128 rows, 32 bytes each) and two status words
-    return mailbox_bulk(mb, div_up(max_table_rows ? max_table_rows : 1, (size_t)128) * 32 + 16);
+    // counting hands over the leaf digests of all of a call's tables (one per 128 rows, 32 bytes each) and four status
+    // words for each
+    return mailbox_bulk(mb, kMailboxMaxInstances * (div_up(max_table_rows ? max_table_rows : 1, (size_t)128) * 32 + 16));
+}
+
+int zkmi_selftest_staging(uint64_t* address, uint64_t* bytes) {
+    if (!address || !bytes) return ZK_E_BADARG;
+    *address = (uint64_t)(uintptr_t)t_mailbox.bulk;
+    *bytes = t_mailbox.bulk_bytes;
+    return ZK_OK;
 }
 
 int zkmi_thread_release(void) {

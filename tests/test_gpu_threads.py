@@ -98,3 +98,34 @@ def test_thread_state_can_be_made_and_given_back(zk, orc):
     assert got == [0, (0, want), 0, 0, (0, want), 0]
     # the main thread's own state is untouched by another thread's release
     assert zk.tlookup_prove(seed, S, idx, T)[:2] == (0, want)
+
+
+def test_thread_init_is_enough_for_a_full_batch(zk, orc):
+    """After zkmi_thread_init(rows) no proof with tables of up to that many rows allocates: the staging buffer is where
+    it was, also when all of a batch's tables are that long."""
+    N, K = 1 << 16, zk.TLOOKUP_BATCH_MAX
+    idx = torch.randint(0, N, (N,), dtype=torch.int32, device="cuda")
+    T = zk.Vec(N)
+    assert zk.fr_from_i32(T, torch.arange(N, dtype=torch.int32, device="cuda")) == 0
+    S = zk.Vec(N)
+    S.data.copy_(T.data.index_select(1, idx.long()))
+    torch.cuda.synchronize()
+    got = []
+
+    def worker():
+        try:
+            assert zk.zkmi_thread_init(N) == 0
+            got.append(zk.zkmi_selftest_staging())
+            got.append(zk.tlookup_prove_batch(b"\3" * 32, [S] * K, [idx] * K, [T] * K)[0])
+            got.append(zk.zkmi_selftest_staging())
+            got.append(zk.zkmi_thread_release())
+            got.append(zk.zkmi_selftest_staging())
+        except Exception as e:
+            got.append(repr(e))
+
+    t = threading.Thread(target=worker)
+    t.start()
+    t.join()
+    torch.cuda.synchronize()
+    assert len(got) == 5, got
+    assert got[0][0] != 0 and got[1:] == [0, got[0], 0, (0, 0)], got
