@@ -143,17 +143,26 @@ __global__ void __launch_bounds__(kFinalThreads) k_sum_finish_canonical(const ui
 
 // ---- eq tables ----------------------------------------------------------------
 
-// Up to two tables in one launch, one thread per entry: the factors of its first and
-// last four variables come from small tables the host has made, those in between are
-// multiplied up.  Two tables of 2^11 and 2^13 entries: 43 us as launches of their own with a
-// thread for sixteen entries, 9 us so.
+// Up to two tables in one launch.  The factors of an entry's first and last four
+// variables come from small tables the host has made, those in between are multiplied
+// up.
+//
+// A short table takes a thread per entry: its chain of products is what counts (two
+// tables of 2^11 and 2^13 entries: 43 us as launches of their own with a thread for
+// sixteen entries, 9 us so).  With many entries per lane it is the products themselves,
+// one per variable and entry: from kEqSharedVars variables on a thread makes the product
+// of all but the first four variables once for the sixteen entries that differ in those.
+// Measured, whole calls by entry and shared: 2^17 entries 17.3 and 23.9 us, 2^18 30.1 and
+// 25.2, 2^22 496 and 75, 2^25 4640 and 546 (bound by issue: some 2.4 products per entry).
 static const int kEqEdge = 4;
+static const int kEqSharedVars = 18;
 struct EqJob {
     uint32_t* dst;
     size_t stride;
     Fr u[32 - 2 * kEqEdge];  // the variables in between
     Fr top[1 << kEqEdge], low[1 << kEqEdge];
     int nvars, ntop, nlow;
+    int shared;  // a thread per entry of all but the first kEqEdge variables
     uint32_t blocks;
 };
 struct EqArgs {
@@ -164,16 +173,21 @@ __global__ void __launch_bounds__(kBlock) k_eq_table(EqArgs args) {
     const int second = blockIdx.x >= args.job[0].blocks;
     const EqJob& g = args.job[second];
     const size_t first = (blockIdx.x - (second ? args.job[0].blocks : 0u)) * (size_t)kBlock + threadIdx.x;
-    const size_t count = (size_t)1 << g.nvars;
+    const int rest = g.nvars - g.ntop;  // the variables behind the first few
+    const size_t count = (size_t)1 << (g.shared ? rest : g.nvars);
     const Fr one = fr_one();
     for (size_t x = first; x < count; x += (size_t)g.blocks * kBlock) {
-        Fr acc = g.top[x >> (g.nvars - g.ntop)];
-        if (g.nlow) acc = fr_mul(acc, g.low[x & ((1u << g.nlow) - 1)]);
+        Fr acc = g.shared ? g.low[x & ((1u << g.nlow) - 1)] : g.top[x >> rest];
+        if (!g.shared && g.nlow) acc = fr_mul(acc, g.low[x & ((1u << g.nlow) - 1)]);
         for (int t = g.ntop; t < g.nvars - g.nlow; ++t) {
             const unsigned bit = (unsigned)(x >> (g.nvars - 1 - t)) & 1u;
             acc = fr_mul(acc, bit ? g.u[t - g.ntop] : fr_sub(one, g.u[t - g.ntop]));
         }
-        fr_store(g.dst, g.stride, x, acc);
+        if (!g.shared) {
+            fr_store(g.dst, g.stride, x, acc);
+            continue;
+        }
+        for (int hi = 0; hi < 1 << kEqEdge; ++hi) fr_store(g.dst, g.stride, ((size_t)hi << rest) + x, fr_mul(acc, g.top[hi]));
     }
 }
 
@@ -208,7 +222,8 @@ int eq_tables_run(const EqTable* tables, int count, hipStream_t stream) {
         eq_edge(j.top, t.u, j.ntop);
         eq_edge(j.low, t.u + (t.nvars - j.nlow), j.nlow);
         for (int v = j.ntop; v < t.nvars - j.nlow; ++v) j.u[v - j.ntop] = to_dev(t.u[v]);
-        j.blocks = grid_for((size_t)1 << t.nvars);
+        j.shared = t.nvars >= kEqSharedVars;
+        j.blocks = grid_for((size_t)1 << (t.nvars - (j.shared ? kEqEdge : 0)));
         blocks += j.blocks;
     }
     hipLaunchKernelGGL(k_eq_table, dim3(blocks), dim3(kBlock), 0, stream, args);
