@@ -333,9 +333,12 @@ static int carve_prove(ProveWs& w, Carver& cv, size_t D, size_t N) {
     w.Sf = cv.limbs(D / 2 ? D / 2 : 1);
     w.A29 = (uint4*)cv.take((D / 2 ? D / 2 : 1) * 36);
     w.S29 = (uint4*)cv.take((D / 2 ? D / 2 : 1) * 36);
-    w.B = cv.limbs(N);
     w.Bf = cv.limbs(N / 2 ? N / 2 : 1);
     w.Tf = cv.limbs(N / 2 ? N / 2 : 1);
+    // B's rows are read by the hash of A only, before anything is folded: they lie where the folded arrays will be (Sf to
+    // Tf, one after the other: 52 D + 32 N bytes, and N <= D)
+    w.rows_b = (uint4*)w.Sf;
+    w.B = cv.limbs(N);
     w.M = cv.limbs(N);
     w.m = (uint32_t*)cv.take(N * 4);
     uint32_t cap = hash_capacity(N);
@@ -343,9 +346,6 @@ static int carve_prove(ProveWs& w, Carver& cv, size_t D, size_t N) {
     w.slots = (uint32_t*)cv.take((size_t)cap * 4);
     w.canon = (uint32_t*)cv.take(N * 4);
     w.rows = (uint4*)cv.take(N * 32);
-    // B's rows are read by the hash of A only.  A table too long to have them by default (tlookup_prove_by_rows) gets no
-    // room of its own if they fit where the folded arrays will be (Sf and A29: 34 D bytes, one after the other)
-    w.rows_b = gather_by_default(N) || 2 * N > D ? (uint4*)cv.take(N * 64) : (uint4*)w.Sf;
     w.found = gather_by_default(N) ? (uint32_t*)cv.take(D * 4) : nullptr;
     w.hist_parts = N <= kLdsHistMaxRows ? kHistParts : 0;
     w.hist = w.hist_parts ? (uint32_t*)cv.take((size_t)w.hist_parts * N * 4) : nullptr;

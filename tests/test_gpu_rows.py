@@ -74,3 +74,19 @@ def test_inversion_levels(zk, orc, n):
     want = np.zeros((n, 32), dtype=np.uint8)
     want[:, 0] = 1
     assert np.array_equal(zk.vec_to_bytes(p), want)
+
+
+# B's rows lie where the folded arrays will be: as long as they get
+@pytest.mark.parametrize("D,N", [(1 << 16, 1 << 16), (1 << 17, 1 << 17)])
+def test_rows_as_long_as_the_tensor(zk, orc, D, N):
+    seed = bytes([D % 251, N % 249]) * 16
+    rng = np.random.default_rng(N)
+    Tb = rng.integers(0, 256, size=(N, 32), dtype=np.uint8)
+    Tb[:, 31] &= 0x3F
+    rows = rng.integers(0, N, size=D)
+    S, T, idx = zk.vec_from_bytes(Tb[rows]), zk.vec_from_bytes(Tb), torch.from_numpy(rows.astype(np.int32)).cuda()
+    rc, want, _ = orc.tlookup_prove(seed, Tb[rows], Tb)
+    assert rc == 0
+    for call in (zk.tlookup_prove, zk.tlookup_prove_by_rows):
+        rc, proof, _ = call(seed, S, idx, T)
+        assert rc == 0 and proof == want

@@ -39,6 +39,14 @@ def test_sizes():
     assert zk.raw().matmul_proof_bytes(5120) == 64 + 13 * 96 + 64
 
 
+def test_workspace_of_tables_as_long_as_their_tensor():
+    """The most a prove can need per entry: some 238 bytes, of which the rows of B are no part (they lie where the folded
+    arrays will be)."""
+    import paper_2404_16109_amd as zk
+    for n in range(18, 31):
+        assert 200 << n < zk.tlookup_workspace_bytes(1 << n, 1 << n) <= (238 << n) + (3 << 20)
+
+
 def test_host_verifier_accepts_oracle_product_proofs(orc):
     """The library's host-only product-sumcheck verifier replays proofs written by
     the oracle: transcript, interpolation and field code of the two sides agree."""
