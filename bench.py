@@ -40,19 +40,23 @@ def fr_mul_executed_model(D, N):
     return 7 * D + 10 * N
 
 
+PASS_VARS = 16  # the rounds of the last 16 variables come several from one pass (csrc/grid_dev.h)
+
+
 def first_two_rounds_share_a_pass(D, N):
     """From a vector of field elements the first pass over A and S yields the sums of the first two rounds and folds
-    nothing; the first launch of k_round_data29 is then round 2, which binds two variables at once."""
+    nothing; what comes next (of the headline: round 2 in k_round_data29) binds two variables at once."""
     n, h = D.bit_length() - 1, (D // N).bit_length() - 1
-    return h >= 3 and (D >> 3) > 256
+    return n > PASS_VARS and h >= 3 and (D >> 3) > 256
 
 
 def rounds_on_29_bits(D, N, from_ints=False):
     """The rounds the dominant kernel (k_round_data29) runs: after the first (after the first two, when those share
-    a pass), before the table's variables, while more than 256 pairs remain."""
+    a pass), before the table's variables and before the rounds that come from passes; from integers it runs the second
+    round whatever the length, if more than 256 pairs remain."""
     n, h = D.bit_length() - 1, (D // N).bit_length() - 1
     first = 2 if not from_ints and first_two_rounds_share_a_pass(D, N) else 1
-    return [k for k in range(first, h) if (D >> (k + 1)) > 256]
+    return [k for k in range(first, h) if (D >> (k + 1)) > 256 and (n - k > PASS_VARS or (from_ints and k == 1))]
 
 
 def round29_work(D, N):

@@ -547,23 +547,26 @@ int zkmi_profile_query(const char* phase, uint64_t* records, double* total_ms);
  * both hold, ZK_E_HIP otherwise.  ws: device, at least 1 KiB. */
 int zkmi_selftest_resident_wait(void* ws, size_t ws_bytes, void* stream);
 
-/* Which kernel each sumcheck round of a tlookup proof of K instances of shape
- * (D, N) is one for, and where it reads S from, decided as the prover decides it but
- * walked on the host alone: no GPU is touched.  The prover runs a round by itself as
- * told here while more than 16 variables are left; the rounds after that come several
- * from one pass over the arrays (from integers, after the first two), whatever kernel
- * they are one for.  from_ints != 0: the plan of
- * tlookup_prove_small (K = 1; ZK_E_BADARG for shapes that path does not take).
- * out (host): four integers per round -- kernel (0 first round, 1 large folding
- * round on 29-bit limbs, 2 data and table side together, 3 and 4 at
- * most 256 pairs, of several instances or of one, 5 the first pass when it serves the first two rounds,
- * 6 the second of those two: no kernel, 7 no kernel either: the
- * host has been handed the arrays, at most 64 elements each, and runs the round
- * itself), source of S (0 the caller's
- * vector, 1 the caller's integer columns, 2 folded 32-bit words in the workspace,
- * 3 folded 29-bit limb planes in the workspace), arrays arrive as 32-bit words,
- * arrays leave as 32-bit words (both only meaningful for kernel 1).  Returns the
- * number of rounds, ZK_E_BUFSZ if cap_rounds is below it. */
+/* What computes each sumcheck round of an instance of shape (D, N) in a tlookup
+ * proof of K instances: the prover's own decisions, walked on the host alone (no GPU
+ * is touched).  They do not depend on the other instances' shapes (k counts the
+ * instance's own rounds).  from_ints != 0: the rounds of tlookup_prove_small (K = 1;
+ * ZK_E_BADARG for shapes that path does not take).
+ * out (host): four integers per round.
+ *   [0] kind: 0 the first round's kernel, 1 the kernel of large folding rounds on
+ *       29-bit limbs, 2 data and table side together, 5 the first pass when it serves
+ *       the first two rounds, 6 the second of those two (nothing is launched), 8 the
+ *       sums come from a pass over up to three variables, 7 the host's round (it has
+ *       the arrays, at most 64 elements each).
+ *   [1] where S is read: 0 the caller's vector, 1 the caller's integer columns,
+ *       2 folded 32-bit words in the workspace, 3 folded 29-bit limb planes in the
+ *       workspace, 4 nowhere (a later round of a pass, or of the host's).
+ *   [2] kind 1: the data arrays arrive as 32-bit words.  The first round of a pass: the
+ *       variables it serves, plus 8 times those of them that are the table's.
+ *   [3] kind 1: they leave as 32-bit words.  The first round of a pass and the first of
+ *       the host's: the last challenges that the data arrays are bound to before it, plus
+ *       8 times those that the table's are.
+ * Returns the number of rounds, ZK_E_BUFSZ if cap_rounds is below it. */
 int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int32_t* out, size_t cap_rounds);
 
 /* The rounds a single tlookup proof leaves to the host (kernel code 7 above), on

@@ -235,7 +235,7 @@ def zkmi_selftest_resident_wait():
 
 
 def zkmi_selftest_tlookup_plan(D, N, K=1, from_ints=False):
-    """Returns (rc, list of (kernel, s_source, in32, out32) per round); runs on the host only."""
+    """Returns (rc, the four integers of each round, see zkmi.h); runs on the host only."""
     out = (ctypes.c_int32 * (4 * 32))()
     rc = _lib.zkmi_selftest_tlookup_plan(D, N, K, 1 if from_ints else 0, out, 32)
     rounds = [tuple(out[4 * k:4 * k + 4]) for k in range(max(rc, 0))]

@@ -14,11 +14,12 @@
 // 2^-(k+1) * c_B while the variable being bound is not one of the table's, and
 // 2^-h (alpha^2 c'_k e~(u_k,X) qT(X) - bm(X)) afterwards.
 //
-// Which kernel computes a round's sums is decided by plan_round.  From a vector
-// of field elements the first pass over A and S yields the sums of the first TWO
-// rounds (round01_dev.h) and the third round's kernel binds both variables at
-// once; in the large folding rounds the kernel sums one side of the round (X = 0
-// or X = 1) and the other side follows here from the running claim.
+// What computes a round's sums is decided by plan_round.  From a vector of field
+// elements the first pass over A and S yields the sums of the first TWO rounds
+// (round01_dev.h) and the third round's kernel binds both variables at once; in the
+// large folding rounds the kernel sums one side of the round (X = 0 or X = 1) and
+// the other side follows here from the running claim; the rounds of the last
+// variables come several from one pass (grid_dev.h), the very last are the host's.
 #include "internal.h"
 #include "tlookup_kernels.h"
 #include "tlookup_round29.h"
@@ -561,6 +562,159 @@ struct HostTail {
 // skip_i on it runs the rounds of a proof of its own ("local round" k - skip_i)
 // with the shared challenges, and all instances reach their last round together.
 
+// ---- what runs a round, and where it finds the arrays ---------------------------------
+//
+// Decided in one place, by a function of the shape and of what the rounds before have
+// left behind, both plain numbers, so that the prover's schedule can be walked on the
+// host without a GPU (zkmi_selftest_tlookup_plan) and checked against the pointers
+// actually handed to a kernel before it is launched.
+enum RoundKind {
+    kRoundFirst = 0,     // k_round_data0: the first round, nothing to fold
+    kRound29 = 1,        // k_round_data29: large folding rounds on 29-bit limbs
+    kRoundBoth = 2,      // k_round_both: data and table side, the table's variables being bound
+    kRoundFirstTwo = 5,  // k_round_data01: the first pass, which yields the sums of the first two rounds
+    kRoundNoPass = 6,    // the second round after kRoundFirstTwo: the host has everything, nothing is launched
+    kRoundHost = 7,      // the host's (HostTail); the first of them fetches the arrays
+    kRoundGrid = 8       // its sums come from the grid of a pass over several variables; the first of them runs the pass
+};
+enum SSource {
+    kSFromCaller = 0,  // the caller's vector of field elements
+    kSFromInts = 1,    // the caller's integer columns (tlookup_prove_small)
+    kSFromWords = 2,   // the folded copy in the workspace, 32-bit words
+    kSFromPlanes = 3,  // the folded copy in the workspace, 29-bit limb planes
+    kSUnread = 4,      // the round reads no array
+    kSNowhere = -1     // a plan this library has no kernel for: never launched
+};
+
+// What the rounds of one instance so far have left behind.
+struct RoundState {
+    int lazy = 0;                           // folds since the data arrays were last fully reduced, if they are in 29-bit planes
+    int pending = 0, pending_t = 0;         // last challenges that the arrays (the table's) have yet to be bound to
+    bool s_moved = false, t_moved = false;  // S is in the workspace, T is (bound at least once)
+    bool first_two = false;                 // the round before was kRoundFirstTwo
+    int pass_left = 0;                      // rounds of the running pass that are still to come
+    bool on_host = false;
+};
+
+struct RoundPlan {
+    int kind;
+    int s_source;
+    bool table_round;  // the variable being bound is one of the table's
+    bool in32, out32;  // kRound29: the data arrays arrive as / leave as 32-bit words
+    bool fold2;        // kRound29: binds the two previous variables at once (after kRoundFirstTwo, kRoundNoPass)
+    // kRoundGrid, kRoundHost
+    bool starts;              // the pass, or the hand-over, is this round's
+    int vars, tvars;          // variables (of the table) the pass serves, when it starts
+    int left;                 // rounds of the pass from this one on
+    int bind, bind_t;         // challenges the arrays (the table's) are bound to before it, when it starts
+    bool s_moved, t_moved;    // where it finds S and T: the workspace or the caller's vectors
+};
+
+// The last rounds on the host.  A pass costs a trip to the host and back (some forty microseconds) whatever it
+// computes; a round of 32 pairs is some six hundred multiplications, which the host does in a fraction of that.  So
+// once few variables are left (host_vars), the device binds the last challenges, writes the five arrays (at most 64
+// elements each) into the mailbox, and the host computes the remaining rounds' sums, folds and final claims from them:
+// the same sums over the same arrays (Section 3.3's sumcheck, Section 4's summand), exact arithmetic, so the same bytes.
+// Variables left to the host: six of a single proof (63 pairs of some 19 multiplications, 24 us), three of each of
+// several (7 pairs each, and one more pass for all of them together).
+static int host_vars(size_t K) { return K == 1 ? 6 : 3; }
+// Passes serve the rounds of the last kPassVars variables.  At 2^16 entries three rounds by themselves take 140 us, most
+// of it trips, and a pass over them 60; the rounds of longer arrays are what the 29-bit kernel is for.
+static const int kPassVars = 16;
+// The variables of a pass that starts with `left` of them unbound: up to the next of the places at which all passes
+// of a call end (whatever the instances' lengths: they share the trips).  Zero: not in a pass.
+static int plan_pass(int left, size_t K) {
+    const int host = host_vars(K);
+    if (left > kPassVars || left <= host) return 0;
+    return (left - host - 1) % kGridVars + 1;
+}
+
+static const size_t kSmallPairs = 256;  // the 29-bit kernel's rounds have more pairs than this
+static bool round_on_29_bits(int n, int h, int k) {
+    return k >= 1 && k < h && ((size_t)1 << (n - k - 1)) > kSmallPairs;
+}
+
+// Whether the first pass over the data serves the first two rounds (round01_dev.h)
+// and both variables are bound at once afterwards: the three rounds must all bind data
+// variables only, and be long.
+static bool first_two_rounds_share_a_pass(int n, int h, bool from_ints) {
+    return !from_ints && h >= 3 && round_on_29_bits(n, h, 2);
+}
+
+// What a pass, or the hand-over to the host, finds and leaves.
+static void plan_bound(RoundPlan& pl, RoundState& st, int vars, int tvars) {
+    pl.starts = true;
+    pl.vars = vars;
+    pl.tvars = tvars;
+    pl.bind = st.pending;
+    pl.bind_t = st.pending_t;
+    pl.s_moved = st.s_moved;
+    pl.t_moved = st.t_moved;
+    pl.s_source = st.s_moved ? kSFromWords : kSFromCaller;
+    if (st.pending) st.s_moved = true;
+    if (st.pending_t) st.t_moved = true;
+    st.pending = vars;
+    st.pending_t = tvars;
+}
+
+// Round k of an instance of n variables, the last n - h of them the table's, in a call of K instances; moves the state on.
+static RoundPlan plan_round(int n, int h, int k, size_t K, bool from_ints, RoundState& st) {
+    RoundPlan pl{};
+    const int left = n - k;
+    pl.table_round = k >= h;
+    pl.s_source = kSUnread;
+    // integers are the first two rounds' business, and the second of two rounds that share a pass needs none
+    const bool own = (from_ints && k < 2) || st.first_two;
+    if (st.on_host || (!own && left <= host_vars(K))) {
+        pl.kind = kRoundHost;
+        if (!st.on_host) plan_bound(pl, st, 0, 0);
+        st.on_host = true;
+        return pl;
+    }
+    if (st.pass_left > 0 || (!own && plan_pass(left, K) > 0)) {
+        pl.kind = kRoundGrid;
+        if (st.pass_left == 0) {
+            const int vars = plan_pass(left, K), after = left - vars;
+            plan_bound(pl, st, vars, std::max(0, std::min(vars, n - h - after)));
+            st.pass_left = vars;
+        }
+        pl.left = st.pass_left--;
+        return pl;
+    }
+    if (st.first_two) {
+        pl.kind = kRoundNoPass;
+        st.first_two = false;
+        return pl;
+    }
+    pl.in32 = st.lazy == 0;
+    int lazy_after = 0;
+    if (k == 0) {
+        st.first_two = first_two_rounds_share_a_pass(n, h, from_ints);
+        pl.kind = st.first_two ? kRoundFirstTwo : kRoundFirst;
+        pl.s_source = from_ints ? kSFromInts : kSFromCaller;
+    } else if (pl.table_round) {
+        pl.kind = kRoundBoth;
+        pl.s_source = k > 1 ? kSFromWords : from_ints ? kSNowhere : kSFromCaller;
+    } else if (round_on_29_bits(n, h, k)) {
+        pl.kind = kRound29;
+        pl.fold2 = st.pending == 2;
+        // words for whatever is not a 29-bit round, and when the lazily reduced sums have grown enough
+        lazy_after = st.lazy + (pl.fold2 ? 2 : 1);
+        pl.out32 = !round_on_29_bits(n, h, k + 1) || plan_pass(left - 1, K) > 0 || lazy_after == kMaxLazyRounds;
+        if (pl.out32) lazy_after = 0;
+        pl.s_source = !pl.in32 ? kSFromPlanes : st.s_moved ? kSFromWords : from_ints ? kSFromInts : kSFromCaller;
+    } else {
+        pl.kind = kRoundFirst;
+        pl.s_source = kSNowhere;  // a short round in the middle: never of the shapes that are accepted
+    }
+    st.lazy = lazy_after;
+    st.pending = pl.kind == kRoundFirstTwo ? 2 : 1;
+    st.pending_t = pl.table_round ? 1 : 0;
+    st.s_moved = k >= 1;
+    st.t_moved = k > h;
+    return pl;
+}
+
 struct Instance {
     ProveWs w;
     fr_vec S, T;
@@ -570,7 +724,6 @@ struct Instance {
     host::F cD, cT;                  // products of e~(u_t, r_t) over its bound variables (all / the table's)
     host::F half_pow;                // 2^-(local round + 1)
     host::F scale;                   // 2^-h
-    int lazy_rounds = 0;             // how many of its rounds in a row have left the data arrays in 29-bit planes
     host::F inv_den;                 // what the one-sided round's other side is divided by (this round)
     host::F pass01[9];               // kRoundFirstTwo's sums: c20, c21, qd, T, qe, then the sums of A_00, A_01, A_10, A_11
     const uint32_t* idx = nullptr;
@@ -589,10 +742,7 @@ struct Instance {
     HostGrid gq, gt, gm;         // the data side's products, the table side's
     host::F gs[1 << kGridVars];  // sums of A
     const uint32_t* grid_words = nullptr;  // where the running pass's values come out
-    int pass_left = 0, pass_tvars = 0;     // rounds of it that are still to come; variables of the table in it
-    bool first_two = false;      // the first round's pass served the second too
-    int pending = 0, pending_t = 0;  // variables (of the table) whose challenges the arrays have yet to be bound to
-    bool s_moved = false, t_moved = false;  // S is in Sf, T in Tf (bound at least once)
+    RoundState state;            // what its rounds so far have left behind
     HostTail* tail = nullptr;    // once the host has the arrays
     bool gather = false;    // A is B by row, made while it is hashed
     bool deferred = false;  // S_i = T[idx_i] is checked there too, not while counting
@@ -624,114 +774,6 @@ struct ProveCall {
     void* stream = nullptr;
 };
 
-// ---- which kernel runs a round, and where it finds S ---------------------------------
-//
-// Decided in one place, by a function of the shape alone, so that it can be
-// walked on the host without a GPU (zkmi_selftest_tlookup_plan) and checked
-// against the pointers actually handed to a kernel before it is launched.  It says
-// how a round would be run by itself; the rounds of an instance's last kPassVars
-// variables are served several at a time instead (grid_dev.h, plan_pass).
-enum RoundKernel {
-    kRoundFirst = 0,     // k_round_data0: the first round, nothing to fold
-    kRound29 = 1,        // k_round_data29: large folding rounds on 29-bit limbs
-    kRoundBoth = 2,      // k_round_both: data and table side, the table's variables being bound
-    kRoundOneGroup = 3,  // at most 256 pairs of a batched proof: always in a pass
-    kRoundResident = 4,  // at most 256 pairs of a single proof: always in a pass
-    kRoundFirstTwo = 5,  // k_round_data01: the first pass, which yields the sums of the first two rounds
-    kRoundNoPass = 6,    // the second round after kRoundFirstTwo: the host has everything, nothing is launched
-    kRoundHost = 7,      // at most kHostPairs pairs of a single proof: the host's (HostTail)
-    kRoundGrid = 8       // what a round in a pass is turned into by prove_core: its sums come from the pass's grid
-};
-enum SSource {
-    kSFromCaller = 0,  // the caller's vector of field elements
-    kSFromInts = 1,    // the caller's integer columns (tlookup_prove_small)
-    kSFromWords = 2,   // the folded copy in the workspace, 32-bit words
-    kSFromPlanes = 3,  // the folded copy in the workspace, 29-bit limb planes
-    kSNowhere = -1     // a plan this library has no kernel for: never launched
-};
-
-struct RoundPlan {
-    int kernel;
-    int s_source;
-    bool table_round;  // the variable being bound is one of the table's
-    bool tiny;         // at most kSmallPairs pairs
-    bool use29;
-    bool in32, out32;  // kRound29: the data arrays arrive as / leave as 32-bit words
-    bool fold2;        // kRound29: binds the two previous variables at once (after kRoundFirstTwo, kRoundNoPass)
-    int lazy_after;    // folds since the data arrays were last fully reduced, if they are in 29-bit planes now
-};
-
-// The last rounds on the host.  A pass costs a trip to the host and back (some forty microseconds) whatever it
-// computes; a round of 32 pairs is some six hundred multiplications, which the host does in a fraction of that.  So
-// once few variables are left (host_vars), the device binds the last challenges, writes the five arrays (at most 64
-// elements each) into the mailbox, and the host computes the remaining rounds' sums, folds and final claims from them:
-// the same sums over the same arrays (Section 3.3's sumcheck, Section 4's summand), exact arithmetic, so the same bytes.
-// Variables left to the host: six of a single proof (63 pairs of some 19 multiplications, 24 us), three of each of
-// several (7 pairs each, and one more pass for all of them together).
-static int host_vars(size_t K) { return K == 1 ? 6 : 3; }
-// Passes serve the rounds of the last kPassVars variables.  At 2^16 entries three rounds by themselves take 140 us, most
-// of it trips, and a pass over them 60; the rounds of longer arrays are what the 29-bit kernel is for.
-static const int kPassVars = 16;
-// The variables of a pass that starts with `left` of them unbound: up to the next of the places at which all passes
-// of a call end (whatever the instances' lengths: they share the trips).  Zero: not in a pass.
-static int plan_pass(int left, size_t K) {
-    const int host = host_vars(K);
-    if (left > kPassVars || left <= host) return 0;
-    return (left - host - 1) % kGridVars + 1;
-}
-
-static bool round_on_29_bits(int n, int h, int k) {
-    return k >= 1 && k < h && ((size_t)1 << (n - k - 1)) > kSmallPairs;
-}
-
-// Whether the first pass over the data serves the first two rounds (round01_dev.h)
-// and the third round's kernel binds two variables at once: the three rounds must
-// all bind data variables only, and the third must be one of the 29-bit kernel's.
-static bool first_two_rounds_share_a_pass(int n, int h, bool from_ints) {
-    return !from_ints && h >= 3 && round_on_29_bits(n, h, 2);
-}
-
-// n = log2 D, h = log2(D/N); lazy_rounds: lazy_after of the round before;
-// resident_running: an earlier round has started the resident kernel.
-static RoundPlan plan_round(int n, int h, int k, size_t K, bool from_ints, int lazy_rounds, bool resident_running) {
-    RoundPlan pl;
-    const size_t half = (size_t)1 << (n - k - 1);
-    pl.table_round = k >= h;
-    pl.tiny = k > 0 && half <= kSmallPairs;
-    pl.use29 = round_on_29_bits(n, h, k);
-    pl.in32 = lazy_rounds == 0;
-    pl.out32 = pl.use29 && (!round_on_29_bits(n, h, k + 1) || lazy_rounds + 1 == kMaxLazyRounds);
-    pl.lazy_after = pl.use29 && !pl.out32 ? lazy_rounds + 1 : 0;
-    pl.fold2 = false;
-    if (first_two_rounds_share_a_pass(n, h, from_ints) && k <= 2) {
-        // rounds 0 and 1 from one pass that folds nothing, round 2 binds both their variables
-        pl.kernel = k == 0 ? kRoundFirstTwo : k == 1 ? kRoundNoPass : kRound29;
-        pl.use29 = k == 2;
-        pl.in32 = true;
-        pl.out32 = k == 2 && !round_on_29_bits(n, h, 3);
-        pl.fold2 = k == 2;
-        pl.lazy_after = k == 2 && !pl.out32 ? 2 : 0;
-        pl.s_source = kSFromCaller;
-        return pl;
-    }
-    if (resident_running && K == 1 && half <= kHostPairs) pl.kernel = kRoundHost;
-    else if (resident_running || (pl.tiny && K == 1 && n - k <= kTailRoundsMax)) pl.kernel = kRoundResident;
-    else if (pl.tiny) pl.kernel = kRoundOneGroup;
-    else if (pl.table_round && k > 0) pl.kernel = kRoundBoth;
-    else if (pl.use29) pl.kernel = kRound29;
-    else pl.kernel = kRoundFirst;
-    if (k <= 1) {
-        // S has not been folded yet (round 0) or is folded by this round's kernel (round 1): it is read where the
-        // caller left it.  Integers are read by the first round's kernel and by the 29-bit kernel only.
-        pl.s_source = from_ints ? kSFromInts : kSFromCaller;
-        if (from_ints && !((k == 0 && pl.kernel == kRoundFirst) || (k == 1 && pl.kernel == kRound29 && pl.in32)))
-            pl.s_source = kSNowhere;
-    } else {
-        pl.s_source = pl.kernel == kRound29 && !pl.in32 ? kSFromPlanes : kSFromWords;
-    }
-    return pl;
-}
-
 // Whether a lookup of this shape can read S as small integers all the way: the
 // multiplicities come from the hints alone (workgroup histograms), the first
 // round and the first fold are kernels of their own that read integers.
@@ -739,8 +781,9 @@ static bool small_source_shape_ok(size_t D, size_t N) {
     if (!is_pow2(D) || !is_pow2(N) || N > D || N > kLdsHistMaxRows || D <= (size_t)kBlock) return false;
     const int n = log2_floor(D), h = n - log2_floor(N);
     if (n < 2) return false;
-    const RoundPlan p0 = plan_round(n, h, 0, 1, true, 0, false);
-    const RoundPlan p1 = plan_round(n, h, 1, 1, true, p0.lazy_after, p0.kernel == kRoundResident);
+    RoundState st;
+    const RoundPlan p0 = plan_round(n, h, 0, 1, true, st);
+    const RoundPlan p1 = plan_round(n, h, 1, 1, true, st);
     return p0.s_source == kSFromInts && p1.s_source == kSFromInts;
 }
 
@@ -1134,23 +1177,23 @@ static int prove_core(const ProveCall& c) {
     std::unique_ptr<HostTail[]> host_tails(new (std::nothrow) HostTail[K]);
     if (!host_tails) return ZK_E_BUFSZ;
     F r_last[3] = {zero(), zero(), zero()};  // the last three challenges, the last one in [2]
-    // The arrays of instance I as a pass finds them: the pending variables bound, 2^left elements (of the data arrays;
-    // the table's if its variables are being bound).  Adds the folds; ship: into the mailbox.
+    // The arrays of instance I as a pass finds them: the pending variables bound as planned, 2^left elements (of the data
+    // arrays; the table's if its variables are being bound).  Adds the folds; ship: into the mailbox.
     struct Bound {
         const uint32_t* p[5];
         size_t stride[5];
     };
-    auto bind_pending = [&](GridPass& pass, Instance& I, int left, uint32_t* ship) {
+    auto bind_pending = [&](GridPass& pass, const Instance& I, const RoundPlan& plan, int left, uint32_t* ship) {
         const ProveWs& w = I.w;
-        const bool table_bound = left < I.l || I.pending_t > 0;
+        const bool table_bound = left < I.l;
         const size_t n_data = (size_t)1 << left, n_table = table_bound ? (size_t)1 << left : I.N;
         Bound b;
-        const uint32_t* src[5] = {w.A, I.s_moved ? w.Sf : I.S.limbs, I.b_cur, w.M, I.t_moved ? w.Tf : I.T.limbs};
-        const size_t ss[5] = {I.D, I.s_moved ? I.D / 2 : I.S.stride, I.b_cur_stride, I.N, I.t_moved ? I.N / 2 : I.T.stride};
+        const uint32_t* src[5] = {w.A, plan.s_moved ? w.Sf : I.S.limbs, I.b_cur, w.M, plan.t_moved ? w.Tf : I.T.limbs};
+        const size_t ss[5] = {I.D, plan.s_moved ? I.D / 2 : I.S.stride, I.b_cur_stride, I.N, plan.t_moved ? I.N / 2 : I.T.stride};
         uint32_t* const dst[5] = {w.A, w.Sf, I.b_cur, w.M, w.Tf};
         const size_t ds[5] = {I.D, I.D / 2, I.b_cur_stride, I.N, I.N / 2};
         for (int q = 0; q < 5; ++q) {
-            const int vars = q < 2 ? I.pending : I.pending_t;
+            const int vars = q < 2 ? plan.bind : plan.bind_t;
             const size_t count = q < 2 ? n_data : n_table;
             b.p[q] = vars ? dst[q] : src[q];
             b.stride[q] = vars ? ds[q] : ss[q];
@@ -1161,27 +1204,28 @@ static int prove_core(const ProveCall& c) {
                 pass.add_fold(src[q], ss[q], dst[q], ds[q], count, vars);
             }
         }
-        if (I.pending) I.s_moved = true;
-        if (I.pending_t) I.t_moved = true;
-        I.pending = I.pending_t = 0;
         return b;
     };
-    // Starts the host's rounds of the instances that have come to them, at round k (k = n: their claims are all that is left).
+    // Hands the arrays of the instances whose host rounds start at round k to the host (k = n, instances of one element:
+    // their claims are all that is left).
+    RoundPlan plans[kMailboxMaxInstances] = {};
+    auto ships = [&](size_t i, int k) {
+        return k < n ? k >= inst[i].skip && plans[i].kind == kRoundHost && plans[i].starts : !inst[i].tail;
+    };
     auto ship_to_host = [&](int k, uint32_t seq) -> int {
         GridPass pass;
         pass.challenges(r_last);
         for (size_t i = 0; i < K; ++i) {
-            Instance& I = inst[i];
-            if (k < I.skip || I.tail || n - k > host_vars(K)) continue;
-            I.tail = &host_tails[i];
-            bind_pending(pass, I, n - k, mb->words + kMailboxShip + i * kMailboxShipWords);
+            if (!ships(i, k)) continue;
+            bind_pending(pass, inst[i], k < n ? plans[i] : RoundPlan{}, n - k, mb->words + kMailboxShip + i * kMailboxShipWords);
         }
         return pass.launch_folds(mb, seq, inst[0].w.flags + 1, stream);
     };
     auto read_shipped = [&](int k) {
         for (size_t i = 0; i < K; ++i) {
+            if (!ships(i, k)) continue;
             Instance& I = inst[i];
-            if (!I.tail || k > std::max(I.skip, n - host_vars(K))) continue;
+            I.tail = &host_tails[i];
             const uint32_t* at = mb->words + kMailboxShip + i * kMailboxShipWords;
             const size_t n_data = (size_t)1 << (n - k), n_table = std::min(I.N, n_data);
             F* const arrays[5] = {I.tail->A, I.tail->S, I.tail->B, I.tail->M, I.tail->T};
@@ -1202,41 +1246,24 @@ static int prove_core(const ProveCall& c) {
         if (is_zero(e_side[1])) side1 = true;
         // the last instance that has kernels in this round publishes it; a round in which no instance has any (every
         // active one is in the second round of a pass that served two) is answered by the host alone
-        RoundPlan plans[kMailboxMaxInstances] = {};
         size_t last_launch = K;
-        bool starts_pass[kMailboxMaxInstances] = {}, any_pass = false, any_ship = false;
+        bool any_pass = false, any_ship = false;
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
             if (k < I.skip) continue;
-            const int kk = k - I.skip;
-            plans[i] = plan_round(I.n, I.h, kk, K, from_ints, I.lazy_rounds, false);
-            if (plans[i].s_source == kSNowhere) return ZK_E_BADARG;  // cannot happen: small_source_shape_ok has walked these rounds
-            // integers are the first two rounds' business, and the second of two rounds that share a pass needs none
-            const bool own = (from_ints && kk < 2) || (kk == 1 && I.first_two);
-            if (I.tail || (!own && n - k <= host_vars(K))) {
-                plans[i].kernel = kRoundHost;
-                if (!I.tail) any_ship = true;
-            } else if (I.pass_left > 0 || (!own && plan_pass(n - k, K) > 0)) {
-                plans[i].kernel = kRoundGrid;
-                if (I.pass_left == 0) {
-                    I.pass_left = plan_pass(n - k, K);
-                    starts_pass[i] = any_pass = true;
-                }
-            } else {
-                I.first_two = kk == 0 && plans[i].kernel == kRoundFirstTwo;
-                if (plans[i].kernel != kRoundNoPass) last_launch = i;
-                if (plans[i].kernel == kRound29 && plan_pass(n - k - 1, K) > 0) {  // a pass reads words
-                    plans[i].out32 = true;
-                    plans[i].lazy_after = 0;
-                }
-            }
+            const RoundPlan& plan = plans[i] = plan_round(I.n, I.h, k - I.skip, K, from_ints, I.state);
+            // cannot happen: small_source_shape_ok has walked these rounds
+            if (plan.s_source == kSNowhere || (from_ints && plan.s_source == kSFromCaller)) return ZK_E_BADARG;
+            if (plan.kind == kRoundHost) any_ship = any_ship || plan.starts;
+            else if (plan.kind == kRoundGrid) any_pass = any_pass || plan.starts;
+            else if (plan.kind != kRoundNoPass) last_launch = i;
         }
         const bool any_launch = last_launch < K || any_pass || any_ship;
 
         const uint32_t seq = any_launch ? mb->next_seq() : 0;
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
-            if (k < I.skip || plans[i].kernel == kRoundNoPass || plans[i].kernel == kRoundGrid || plans[i].kernel == kRoundHost) continue;
+            if (k < I.skip || plans[i].kind == kRoundNoPass || plans[i].kind == kRoundGrid || plans[i].kind == kRoundHost) continue;
             ProveWs& w = I.w;
             const size_t D = I.D, N = I.N;
             const int h = I.h, kk = k - I.skip;
@@ -1272,7 +1299,7 @@ static int prove_core(const ProveCall& c) {
             d.partials = w.partD;
             d.pstride = w.part_blocks * 5;
             memset(&d.ints, 0, sizeof d.ints);
-            if (plan.s_source == kSFromInts && plan.kernel == kRoundFirst) d.ints = ints_src;
+            if (plan.s_source == kSFromInts && plan.kind == kRoundFirst) d.ints = ints_src;
             // every kernel below reads S through d.S.src unless the plan says otherwise: no launch with nothing behind it
             if ((plan.s_source == kSFromCaller || plan.s_source == kSFromWords) && !d.S.src) return ZK_E_BADARG;
             if (plan.s_source == kSFromInts && !ints_src.x) return ZK_E_BADARG;
@@ -1289,7 +1316,7 @@ static int prove_core(const ProveCall& c) {
             t.partials = w.partT;
             t.pstride = w.part_blocks * 6;
 
-            if (plan.kernel == kRoundFirstTwo) {
+            if (plan.kind == kRoundFirstTwo) {
                 // one pass for this round and the next: nothing is folded, the weights are the next round's
                 const size_t quarter = half / 2;
                 const EqSplit eq1 = ep.round(kk + 1);
@@ -1323,7 +1350,7 @@ static int prove_core(const ProveCall& c) {
                 }
                 launch_final_sum2(w.partD, d01.pstrideD, 5, w.partT, d01.pstrideT, 6, blocks01, I.words, mb->words, my_seq,
                                   w.flags + 1, stream);
-            } else if (plan.kernel == kRoundBoth) {
+            } else if (plan.kind == kRoundBoth) {
                 {
                     ProfileScope prof(kProfRoundSmall, stream);
                     if (kk > h) hipLaunchKernelGGL(k_round_both<true>, dim3(blocks, 3), dim3(kBlock), 0, stream, d, t);
@@ -1331,7 +1358,7 @@ static int prove_core(const ProveCall& c) {
                 }
                 launch_final_sum2(w.partD, d.pstride, 5, w.partT, t.pstride, 6, blocks, I.words, mb->words, my_seq,
                                   w.flags + 1, stream);
-            } else if (plan.kernel == kRound29) {
+            } else if (plan.kind == kRound29) {
                 // as many pairs per workgroup as its weights' shared factor allows, but at least 512 workgroups while the
                 // round is large enough (measured: 1024 workgroups do the same, 2048 and workgroups of three or two
                 // wavefronts are slower)
@@ -1407,34 +1434,28 @@ static int prove_core(const ProveCall& c) {
                                   mb->words, my_seq, w.flags + 1, stream);
             }
             ZK_HIP_TRY(hipGetLastError());
-            // what the arrays have yet to be bound to, should a pass come next
-            I.pending = plan.kernel == kRoundFirstTwo ? 2 : 1;
-            I.s_moved = kk >= 1;
-            I.pending_t = table_round ? 1 : 0;
-            I.t_moved = kk > h;
             I.b_cur = b_next;
             I.b_cur_stride = b_next_stride;
         }
+        auto starts_pass = [&](size_t i) { return k >= inst[i].skip && plans[i].kind == kRoundGrid && plans[i].starts; };
         if (any_pass) {
             ProfileScope prof(kProfRoundSmall, stream);
             GridPass pass;
             pass.challenges(r_last);
             for (size_t i = 0; i < K; ++i) {
-                if (!starts_pass[i]) continue;
+                const RoundPlan& plan = plans[i];
+                if (!starts_pass(i)) continue;
                 Instance& I = inst[i];
-                const int left = n - k, kk = k - I.skip, vars = I.pass_left, after = left - vars;
-                const Bound b = bind_pending(pass, I, left, nullptr);
-                const size_t P = (size_t)1 << after;
-                const EqSplit eq = I.ep->round(kk + vars - 1);
-                const int tvars = std::max(0, std::min(vars, I.l - after));  // of them the table's
+                const int left = n - k, vars = plan.vars, tvars = plan.tvars;
+                const Bound b = bind_pending(pass, I, plan, left, nullptr);
+                const size_t P = (size_t)1 << (left - vars);
+                const EqSplit eq = I.ep->round(k - I.skip + vars - 1);
                 I.grid_words = mb->words + kMailboxGrid + 8 * pass.values;
                 pass.add(b.p[0], b.stride[0], b.p[1], b.stride[1], vars, kGridWeighted, P, eq);
                 if (tvars) {
                     pass.add(b.p[2], b.stride[2], b.p[4], b.stride[4], tvars, kGridTable, P, eq);
                     pass.add(b.p[2], b.stride[2], b.p[3], b.stride[3], tvars, kGridPlain, P, eq);
                 }
-                I.pending = vars;
-                I.pending_t = I.pass_tvars = tvars;
             }
             ZK_TRY(pass.launch(mb, beta, inst[0].w.partT, mb->words + kMailboxGrid, any_ship ? 0 : seq, inst[0].w.flags + 1, stream));
         }
@@ -1444,14 +1465,13 @@ static int prove_core(const ProveCall& c) {
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
             if (k < I.skip) continue;
-            I.lazy_rounds = plans[i].lazy_after;
             I.claim = k == I.skip ? add(alpha, alpha2) : interpolate_at(I.fX, 4, r_prev);
             I.inv_den = zero();
             const F wD = mul(alpha, I.cD);
-            if (plans[i].kernel != kRound29 || is_zero(wD)) continue;
+            if (plans[i].kind != kRound29 || is_zero(wD)) continue;
             bool shared = false;
             for (size_t j = 0; j < i && !shared; ++j)
-                if (k >= inst[j].skip && inst[j].skip == I.skip && plans[j].kernel == kRound29) {
+                if (k >= inst[j].skip && inst[j].skip == I.skip && plans[j].kind == kRound29) {
                     I.inv_den = inst[j].inv_den;  // same bound variables, same product of weights
                     shared = true;
                 }
@@ -1459,15 +1479,16 @@ static int prove_core(const ProveCall& c) {
         }
         if (any_launch) ZK_TRY(mailbox_wait(mb, seq, stream));
         for (size_t i = 0; i < K; ++i) {
-            if (!starts_pass[i]) continue;
+            if (!starts_pass(i)) continue;
             Instance& I = inst[i];
+            const int vars = plans[i].vars, tvars = plans[i].tvars;
             const uint32_t* at = I.grid_words;
-            I.gq.read(at, I.pass_left);
-            at += 8 * grid_points(I.pass_left);
-            for (int x = 0; x < 1 << I.pass_left; ++x, at += 8) I.gs[x] = from_dev(at);
-            if (!I.pass_tvars) continue;
-            I.gt.read(at, I.pass_tvars);
-            I.gm.read(at + 8 * grid_points(I.pass_tvars), I.pass_tvars);
+            I.gq.read(at, vars);
+            at += 8 * grid_points(vars);
+            for (int x = 0; x < 1 << vars; ++x, at += 8) I.gs[x] = from_dev(at);
+            if (!tvars) continue;
+            I.gt.read(at, tvars);
+            I.gm.read(at + 8 * grid_points(tvars), tvars);
         }
         if (any_ship) read_shipped(k);
         if (k > 0 || any_launch) ZK_TRY(read_table_consts());
@@ -1494,10 +1515,10 @@ static int prove_core(const ProveCall& c) {
             const uint32_t* sums = I.words;
             F q0, q1, qi, sA0, sA1;
             F hs[11];  // kRoundHost, kRoundGrid: the round's sums, formed here
-            if (plan.kernel == kRoundGrid) {
+            if (plan.kind == kRoundGrid) {
                 I.gq.sums(hs, u + k + 1);
                 hs[3] = hs[4] = zero();
-                const int later = 1 << (I.pass_left - 1);
+                const int later = 1 << (plan.left - 1);
                 for (int x = 0; x < later; ++x) {
                     hs[3] = add(hs[3], I.gs[x]);
                     hs[4] = add(hs[4], I.gs[later + x]);
@@ -1511,14 +1532,14 @@ static int prove_core(const ProveCall& c) {
                 qi = hs[2];
                 sA0 = hs[3];
                 sA1 = hs[4];
-            } else if (plan.kernel == kRoundHost) {
+            } else if (plan.kind == kRoundHost) {
                 I.tail->sums((size_t)1 << (I.n - kk - 1), table_round, beta, hs);
                 q0 = hs[0];
                 q1 = hs[1];
                 qi = hs[2];
                 sA0 = hs[3];
                 sA1 = hs[4];
-            } else if (plan.kernel == kRoundFirstTwo) {
+            } else if (plan.kind == kRoundFirstTwo) {
                 // the pass has summed, with the NEXT round's weights, what this round and the next are made of
                 // (round01_dev.h): this round's leading coefficient splits by the next variable
                 for (int q = 0; q < 9; ++q) I.pass01[q] = from_dev(sums + 8 * q);
@@ -1526,7 +1547,7 @@ static int prove_core(const ProveCall& c) {
                 qi = add(mul(sub(one(), u[k + 1]), I.pass01[0]), mul(u[k + 1], I.pass01[1]));
                 sA0 = add(I.pass01[5], I.pass01[6]);
                 sA1 = add(I.pass01[7], I.pass01[8]);
-            } else if (plan.kernel == kRoundNoPass) {
+            } else if (plan.kind == kRoundNoPass) {
                 // every sum of this round is a polynomial of degree two in the challenge r before it
                 const F& r = r_prev;
                 const F t = mul(r, sub(one(), r));
@@ -1545,7 +1566,7 @@ static int prove_core(const ProveCall& c) {
                 sA1 = from_dev(sums + 32);
             }
             const F table_const = mul(I.cB, I.half_pow);
-            if (plan.kernel == kRound29) {
+            if (plan.kind == kRound29) {
                 // the kernel has summed one side: (q0, sA0) hold that side's q and sum of A; the other side from
                 // sA(0) + sA(1) = sA_prev(r_prev) and g(0) + g(1) = claim (never a table round: the table side is a constant)
                 const int a = side1 ? 1 : 0;
@@ -1564,7 +1585,7 @@ static int prove_core(const ProveCall& c) {
             F q[4], sa[4], tq[4], tm[4];
             quad_values(q, q0, q1, qi);
             line_values(sa, sA0, sA1);
-            if (table_round && (plan.kernel == kRoundHost || plan.kernel == kRoundGrid)) {
+            if (table_round && (plan.kind == kRoundHost || plan.kind == kRoundGrid)) {
                 quad_values(tq, hs[5], hs[6], hs[7]);
                 quad_values(tm, hs[8], hs[9], hs[10]);
             } else if (table_round) {
@@ -1598,11 +1619,11 @@ static int prove_core(const ProveCall& c) {
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
             if (k < I.skip) continue;
-            if (plans[i].kernel == kRoundHost) {
+            if (plans[i].kind == kRoundHost) {
                 I.tail->fold((size_t)1 << (n - k - 1), plans[i].table_round, r);
-            } else if (plans[i].kernel == kRoundGrid) {
+            } else if (plans[i].kind == kRoundGrid) {
                 I.gq.bind(r);
-                const int half = 1 << --I.pass_left;
+                const int half = 1 << (plans[i].left - 1);
                 for (int x = 0; x < half; ++x) I.gs[x] = add(I.gs[x], mul(r, sub(I.gs[half + x], I.gs[x])));
                 if (plans[i].table_round) {
                     I.gt.bind(r);
@@ -2029,24 +2050,21 @@ int tlookup_prove_small(const uint8_t seed[32], const int32_t* X, const int32_t*
     return prove_single(seed, S, idx, T, nullptr, false, proof, cap, len, aux, ws, base, stream);
 }
 
-// The per-round plan of a proof of this shape, walked on the host (no GPU is
-// touched): four integers per round -- kernel, source of S, arrays arrive as
-// 32-bit words, arrays leave as 32-bit words.
+// The rounds of a proof of this shape, walked on the host (no GPU is touched): four
+// integers per round, see zkmi.h.
 int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int32_t* out, size_t cap_rounds) {
     if (!out || !is_pow2(D) || !is_pow2(N) || N > D || D > ((size_t)1 << 31) || K == 0 || K > kMailboxMaxInstances) return ZK_E_BADARG;
     const int n = log2_floor(D), h = n - log2_floor(N);
     if ((size_t)n > cap_rounds) return ZK_E_BUFSZ;
     if (from_ints && (K != 1 || !small_source_shape_ok(D, N))) return ZK_E_BADARG;
-    int lazy = 0;
-    bool resident = false;
+    RoundState st;
     for (int k = 0; k < n; ++k) {
-        const RoundPlan pl = plan_round(n, h, k, K, from_ints != 0, lazy, resident);
-        out[4 * k] = pl.kernel;
+        const RoundPlan pl = plan_round(n, h, k, K, from_ints != 0, st);
+        const bool several = pl.kind == kRoundGrid || pl.kind == kRoundHost;
+        out[4 * k] = pl.kind;
         out[4 * k + 1] = pl.s_source;
-        out[4 * k + 2] = pl.in32 ? 1 : 0;
-        out[4 * k + 3] = pl.out32 ? 1 : 0;
-        lazy = pl.lazy_after;
-        resident = resident || pl.kernel == kRoundResident;
+        out[4 * k + 2] = several ? pl.vars + 8 * pl.tvars : pl.in32 ? 1 : 0;
+        out[4 * k + 3] = several ? pl.bind + 8 * pl.bind_t : pl.out32 ? 1 : 0;
     }
     return n;
 }

@@ -1228,9 +1228,6 @@ static __global__ void __launch_bounds__(kBlock) k_round_both(DataRoundArgs d, T
     else round_table_block<FOLD_T, 2>(t, blockIdx.x, lds);
 }
 
-static const size_t kSmallPairs = 256;  // rounds of at most this many pairs are always served by passes (grid_dev.h)
-static const int kTailRoundsMax = 9;    // pairs go 256, 128, .., 1
-
 // Sums over the whole table, before any of its variables is bound:
 //   c1 = sum_j e'_j B_j (T_j + beta),  c2 = sum_j B_j M_j,
 // with e'_j = lo[j & mask] * hi[j >> lbits].

@@ -43,10 +43,11 @@ def test_work_models():
     assert pairs == sum(D >> (k + 1) for k in range(2, 9)) == D // 4 - D // 512
     # round 2 binds two variables (17 multiplications, 20 entries per pair), rounds 3..8 one (9 and 12)
     assert muls == 17 * (D >> 3) + 9 * (D // 8 - D // 512) and moved == 32 * (20 * (D >> 3) + 12 * (D // 8 - D // 512))
-    assert b.rounds_on_29_bits(1 << 12, 1 << 4) == [2]               # 512 pairs; 256 is the resident kernel's
-    assert b.rounds_on_29_bits(1 << 12, 1 << 4, from_ints=True) == [1, 2]
-    assert b.rounds_on_29_bits(1 << 12, 1 << 11) == []               # the table's variables start at the second round
-    assert b.rounds_on_29_bits(1 << 12, 1 << 10) == [1]              # ... at the third: no pass can serve two rounds
+    # the last 16 variables' rounds come from passes, except that integers are folded by the kernel written for them
+    assert b.rounds_on_29_bits(1 << 12, 1 << 4) == [] and b.rounds_on_29_bits(1 << 12, 1 << 4, from_ints=True) == [1]
+    assert b.rounds_on_29_bits(1 << 20, 1 << 8) == [2, 3]
+    assert b.rounds_on_29_bits(1 << 20, 1 << 19) == []               # the table's variables start at the second round
+    assert b.rounds_on_29_bits(1 << 20, 1 << 18) == [1]              # ... at the third: no pass can serve two rounds
     # nine multiplications of 112 multiply-adds per pair against 256 CUs x 64 lanes x 2.4 GHz
     assert (b.ROUND_DATA_FR_MUL_PER_PAIR_EVAL + b.ROUND_DATA_FR_MUL_PER_PAIR_FOLD, b.MADS_PER_FR_MUL) == (9, 112)
     assert b.PEAK_MAD_PER_S == 256 * 64 * 2.4e9
