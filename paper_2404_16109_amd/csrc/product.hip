@@ -49,11 +49,13 @@ __global__ void __launch_bounds__(kBlock) k_round_product(ProductRoundArgs g) {
 // and the two final values -- the same sums over the same values, exact arithmetic, so
 // the same bytes.  Measured, the thirteen rounds of a proof with their trips: 220 -> 95 us.
 //
-// Where a single round is left above the host's, a resident workgroup does it and the
-// handing over in one launch: it writes the round's three sums to the mailbox, waits
-// (bounded) for the challenge on the command channel, binds it and writes both arrays.
-// Every thread takes every barrier, and a wait that fails ends the kernel for all of
-// them.
+// Products of exactly 2^8 elements have one round more than the host takes.  A resident
+// workgroup does it and the handing over in one launch: it writes the round's three sums
+// to the mailbox, waits (bounded) for the challenge on the command channel, binds it and
+// writes both arrays.  Every thread takes every barrier, and a wait that fails ends the
+// kernel for all of them.  A pass over the one variable and a launch for the arrays are
+// the other way: 58 us instead of 57 for the product alone, 122 instead of 97 for a
+// matrix product of 100 x 200 x 100, where the pass's kernels queue behind the sums.
 static const int kPassVars = 16;
 static const int kHostVars = 7;
 static const int kTailThreads = 1024;
@@ -61,94 +63,78 @@ static const size_t kHostPairs = (size_t)1 << (kHostVars - 1);
 static_assert(2 * 2 * kHostPairs * 8 <= kMailboxGrid - kMailboxShip, "both arrays fit behind the result words");
 
 struct ProductTailArgs {
-    uint32_t* a;
+    const uint32_t* a;
     size_t as;
-    uint32_t* b;
+    const uint32_t* b;
     size_t bs;
-    size_t half0;       // pairs in the first of these rounds
-    int nrounds;        // rounds run here (>= 1)
-    int fold_first;     // the first of them binds the previous variable to r_prev
-    Fr r_prev;
-    uint32_t* words;    // mailbox: sums at words[0..24), final values at words[0..16)
+    uint32_t half;         // pairs: 2 half elements in each array, at most kTailThreads pairs
+    uint32_t* words;       // mailbox: the sums at words[0..24); half elements of a, then of b, with the round's variable
+                           // bound, eight words each, from words[kMailboxShip] on
     const uint32_t* cmd;
-    uint32_t out_seq[33];  // [i]: the sums of round i are there; [nrounds]: the final values are
-    uint32_t cmd_seq[32];  // [i]: the challenge of round i
+    uint32_t out_seq[2];   // the sums are there; the arrays are
+    uint32_t cmd_seq;      // the challenge
     uint32_t spin_limit;
-    // not zero: after the last round both arrays go to the host instead of the final values, ship_count elements
-    // of a, then of b, each with that round's variable bound, eight words per element from words[kMailboxShip] on
-    uint32_t ship_count;
 };
 
 static __global__ void __launch_bounds__(kTailThreads) k_product_tail(ProductTailArgs g) {
     __shared__ uint32_t lds[16 * 3 * 8];
     __shared__ uint32_t sh_r[8];
     __shared__ int sh_ok;
-    Fr r = g.r_prev;
-    bool fold = g.fold_first != 0;
-    size_t half = g.half0;
-    bool ok = true;
-    for (int i = 0; i < g.nrounds; ++i, half >>= 1) {
-        Fr tot[3] = {fr_zero(), fr_zero(), fr_zero()};
-        const size_t p = threadIdx.x;
-        if (p < half) {
-            const PairArray A{g.a, g.as, g.a, g.as}, B{g.b, g.bs, g.b, g.bs};
-            Fr a0, a1, b0, b1;
-            if (fold) {
-                load_pair<true>(A, p, half, r, a0, a1);
-                load_pair<true>(B, p, half, r, b0, b1);
-            } else {
-                load_pair<false>(A, p, half, r, a0, a1);
-                load_pair<false>(B, p, half, r, b0, b1);
-            }
-            tot[0] = fr_mul(a0, b0);
-            tot[1] = fr_mul(a1, b1);
-            tot[2] = fr_mul(fr_sub(a1, a0), fr_sub(b1, b0));
-        }
-        block_sum<3, 16>(tot, lds);
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q)
-#pragma unroll
-                for (int k = 0; k < 8; ++k) g.words[8 * q + k] = tot[q].l[k];
-            mailbox_written();
-            mailbox_publish(g.words, g.out_seq[i]);
-            uint32_t limbs[8];
-            const bool got = mailbox_receive_challenge(g.cmd, g.cmd_seq[i], g.spin_limit, limbs);
-            if (got) {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) sh_r[k] = limbs[k];
-            }
-            sh_ok = got ? 1 : 0;
-        }
-        __syncthreads();  // the folded entries written in this round are visible to the workgroup from here on
-        ok = sh_ok != 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) r.l[k] = __builtin_amdgcn_readfirstlane(sh_r[k]);
-        __syncthreads();  // sh_ok and sh_r are free to be written again
-        if (!ok) break;   // the same for every thread
-        fold = true;
+    Fr tot[3] = {fr_zero(), fr_zero(), fr_zero()};
+    if (threadIdx.x < g.half) {
+        const Fr a0 = fr_load(g.a, g.as, threadIdx.x), a1 = fr_load(g.a, g.as, threadIdx.x + g.half);
+        const Fr b0 = fr_load(g.b, g.bs, threadIdx.x), b1 = fr_load(g.b, g.bs, threadIdx.x + g.half);
+        tot[0] = fr_mul(a0, b0);
+        tot[1] = fr_mul(a1, b1);
+        tot[2] = fr_mul(fr_sub(a1, a0), fr_sub(b1, b0));
     }
-    if (ok && g.ship_count) {
-        for (uint32_t t = threadIdx.x; t < 2 * g.ship_count; t += kTailThreads) {
-            const bool first = t < g.ship_count;
-            const uint32_t* arr = first ? g.a : g.b;
-            const size_t stride = first ? g.as : g.bs;
-            const uint32_t j = first ? t : t - g.ship_count;
-            Fr v = fr_fold(fr_load(arr, stride, j), fr_load(arr, stride, j + g.ship_count), r);
+    block_sum<3, 16>(tot, lds);
+    if (threadIdx.x == 0) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) g.words[kMailboxShip + 8 * (size_t)t + k] = v.l[k];
-            mailbox_written();
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) g.words[8 * q + k] = tot[q].l[k];
+        mailbox_written();
+        mailbox_publish(g.words, g.out_seq[0]);
+        uint32_t limbs[8];
+        const bool got = mailbox_receive_challenge(g.cmd, g.cmd_seq, g.spin_limit, limbs);
+        if (got) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) sh_r[k] = limbs[k];
         }
-    } else if (ok && threadIdx.x < 2) {
-        const uint32_t* arr = threadIdx.x == 0 ? g.a : g.b;
-        const size_t stride = threadIdx.x == 0 ? g.as : g.bs;
-        Fr v = fr_fold(fr_load(arr, stride, 0), fr_load(arr, stride, 1), r);
+        sh_ok = got ? 1 : 0;
+    }
+    __syncthreads();
+    if (!sh_ok) return;  // the same for every thread
+    Fr r;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) g.words[8 * threadIdx.x + k] = v.l[k];
+    for (int k = 0; k < 8; ++k) r.l[k] = __builtin_amdgcn_readfirstlane(sh_r[k]);
+    for (uint32_t t = threadIdx.x; t < 2 * g.half; t += kTailThreads) {
+        const bool first = t < g.half;
+        const uint32_t* arr = first ? g.a : g.b;
+        const size_t stride = first ? g.as : g.bs;
+        const uint32_t j = first ? t : t - g.half;
+        const Fr v = fr_fold(fr_load(arr, stride, j), fr_load(arr, stride, j + g.half), r);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) g.words[kMailboxShip + 8 * (size_t)t + k] = v.l[k];
         mailbox_written();
     }
     __syncthreads();
-    if (ok && threadIdx.x == 0) mailbox_publish(g.words, g.out_seq[g.nrounds]);
+    if (threadIdx.x == 0) mailbox_publish(g.words, g.out_seq[1]);
+}
+
+// Launches it with fresh sequence numbers.
+static int product_tail_launch(ProductTailArgs& g, Mailbox* mb, uint32_t spin_limit, hipStream_t stream) {
+    g.words = mb->words;
+    g.cmd = mb->cmd;
+    g.out_seq[0] = mb->next_seq();
+    g.out_seq[1] = mb->next_seq();
+    g.cmd_seq = mb->next_cmd_seq();
+    g.spin_limit = spin_limit;
+    mailbox_channel_reset(mb);
+    hipLaunchKernelGGL(k_product_tail, dim3(1), dim3(kTailThreads), 0, stream, g);
+    ZK_HIP_TRY(hipGetLastError());
+    return ZK_OK;
 }
 
 static size_t product_scratch_bytes() {
@@ -225,29 +211,19 @@ static int product_rounds_run(host::Transcript& tr, uint32_t* a, size_t as, uint
     }
     F ha[2 * kHostPairs], hb[2 * kHostPairs];
     size_t shipped;
-    if (d - k == kHostVars + 1 && pending == 0) {
-        ProductTailArgs g;
-        memset(&g, 0, sizeof g);
+    if (d == kHostVars + 1) {
+        shipped = (size_t)1 << kHostVars;
+        ProductTailArgs g{};
         g.a = a; g.as = as; g.b = b; g.bs = bs;
-        g.half0 = (size_t)1 << kHostVars;
-        g.nrounds = 1;
-        g.ship_count = 1u << kHostVars;
-        g.words = mb->words;
-        g.cmd = mb->cmd;
-        for (int i = 0; i <= g.nrounds; ++i) g.out_seq[i] = mb->next_seq();
-        g.cmd_seq[0] = mb->next_cmd_seq();
-        g.spin_limit = device_spin_limit();
-        mailbox_channel_reset(mb);
+        g.half = (uint32_t)shipped;
         TailGuard guard{mb, stream};
-        hipLaunchKernelGGL(k_product_tail, dim3(1), dim3(kTailThreads), 0, stream, g);
-        ZK_HIP_TRY(hipGetLastError());
+        ZK_TRY(product_tail_launch(g, mb, device_spin_limit(), stream));
         guard.armed = true;
         ZK_TRY(mailbox_wait(mb, g.out_seq[0], stream));
         emit_round(from_dev(mb->words), from_dev(mb->words + 8), from_dev(mb->words + 16));
-        mailbox_send_challenge(mb, g.cmd_seq[0], to_dev(r_prev).l);
+        mailbox_send_challenge(mb, g.cmd_seq, to_dev(r_prev).l);
         ZK_TRY(mailbox_wait(mb, g.out_seq[1], stream));
         guard.armed = false;
-        shipped = g.ship_count;
     } else {
         while (d - k > kHostVars) {
             const int left = d - k, vars = (left - kHostVars - 1) % kGridVars + 1;
@@ -820,9 +796,8 @@ static int matmul_prove_any(const uint8_t seed[32], fr_vec X, const int16_t* X16
 }
 
 int zkmi_selftest_resident_wait(void* ws, size_t ws_bytes, void* stream_v) {
-    // The last rounds run in a kernel that waits for the host between rounds.  Here
-    // the host never answers: with a bound of a few polls the kernel must give up by
-    // itself, having published its first round's sums and nothing after them.
+    // The kernel waits for the host's answer to its sums.  Here the host never gives one: with a bound of a few polls
+    // the kernel must give up by itself, having published the sums and nothing after them.
     if (!ws || ws_bytes < 4 * 32 * 4 + 512) return ZK_E_BUFSZ;
     hipStream_t stream = as_stream(stream_v);
     Mailbox* mb;
@@ -832,41 +807,23 @@ int zkmi_selftest_resident_wait(void* ws, size_t ws_bytes, void* stream_v) {
     uint32_t* b = cv.limbs(4);
     launch_fill_u32(a, 32, 1u, stream);
     launch_fill_u32(b, 32, 1u, stream);
-    ProductTailArgs g;
-    memset(&g, 0, sizeof g);
+    ProductTailArgs g{};
     g.a = a; g.as = 4; g.b = b; g.bs = 4;
-    g.half0 = 2;
-    g.nrounds = 2;
-    g.fold_first = 0;
-    g.r_prev = to_dev(host::zero());
-    g.words = mb->words;
-    g.cmd = mb->cmd;
-    for (int i = 0; i <= g.nrounds; ++i) g.out_seq[i] = mb->next_seq();
-    for (int i = 0; i < g.nrounds; ++i) g.cmd_seq[i] = mb->next_cmd_seq();
-    g.spin_limit = 8;
-    mailbox_channel_reset(mb);
-    hipLaunchKernelGGL(k_product_tail, dim3(1), dim3(kTailThreads), 0, stream, g);
-    ZK_HIP_TRY(hipGetLastError());
-    ZK_TRY(mailbox_wait(mb, g.out_seq[0], stream));          // the first round's sums arrive
+    g.half = 2;
+    ZK_TRY(product_tail_launch(g, mb, 8, stream));
+    ZK_TRY(mailbox_wait(mb, g.out_seq[0], stream));          // the sums arrive
     ZK_HIP_TRY(hipStreamSynchronize(stream));                 // and the kernel ends without an answer
     const uint32_t flag = mb->words[kMailboxFlag];
     if (flag != g.out_seq[0]) return ZK_E_HIP;                // nothing was published after them
     // A call that ends early leaves an abort in the channel.  The next kernel must
     // not see it: this one is answered and has to run to its end.
     mailbox_send_abort(mb);
-    for (int i = 0; i <= g.nrounds; ++i) g.out_seq[i] = mb->next_seq();
-    for (int i = 0; i < g.nrounds; ++i) g.cmd_seq[i] = mb->next_cmd_seq();
-    g.spin_limit = device_spin_limit();
-    mailbox_channel_reset(mb);
     TailGuard guard{mb, stream};
-    hipLaunchKernelGGL(k_product_tail, dim3(1), dim3(kTailThreads), 0, stream, g);
-    ZK_HIP_TRY(hipGetLastError());
+    ZK_TRY(product_tail_launch(g, mb, device_spin_limit(), stream));
     guard.armed = true;
-    for (int i = 0; i < g.nrounds; ++i) {
-        ZK_TRY(mailbox_wait(mb, g.out_seq[i], stream));
-        mailbox_send_challenge(mb, g.cmd_seq[i], to_dev(host::one()).l);
-    }
-    ZK_TRY(mailbox_wait(mb, g.out_seq[g.nrounds], stream));
+    ZK_TRY(mailbox_wait(mb, g.out_seq[0], stream));
+    mailbox_send_challenge(mb, g.cmd_seq, to_dev(host::one()).l);
+    ZK_TRY(mailbox_wait(mb, g.out_seq[1], stream));
     guard.armed = false;
     ZK_HIP_TRY(hipStreamSynchronize(stream));
     return ZK_OK;
