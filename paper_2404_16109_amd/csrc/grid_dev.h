@@ -14,10 +14,13 @@
 // arrays with the last pass's variables bound (k_grid_fold), the 27 grid sums of every
 // product (k_grid), the wavefronts' shares added up (k_grid_sum).
 //
-// Bound by latency: a wavefront does one grid point of 64 positions, so that no chain
-// is longer than two multiplications and a reduction.  Measured, a proof of 2^20
-// entries with a table of 256 rows: 914 -> 766 us; three lookups of 2^11 to 2^18
-// entries under one sumcheck, whose rounds used to follow each other instance by
+// Bound by latency: a wavefront does one grid point of 64 positions, which keeps the
+// chain at two multiplications (three where the positions do not share their weights'
+// high factor) and a reduction.  A sum is at most 32 shares, so that one launch adds them
+// up: of more than 2^11 positions a wavefront takes more, one after the other (at most
+// sixteen times 64, of the 2^15 in a pass over one of sixteen variables).  Measured, a
+// proof of 2^20 entries with a table of 256 rows: 914 -> 766 us; three lookups of 2^11 to
+// 2^18 entries under one sumcheck, whose rounds used to follow each other instance by
 // instance: 2.07 -> 1.24 ms.
 #pragma once
 #include "common.h"

@@ -101,11 +101,4 @@ int mle_eval_run(const uint32_t* a, size_t stride, int nvars, const host::F* poi
 // p[0..n) = v (a kernel, so that it can sit in a captured graph).
 void launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t stream);
 
-// Copies the leading `n` elements of a limb-major vector.
-void launch_copy(uint32_t* dst, size_t ds, const uint32_t* src, size_t ss, size_t n, hipStream_t stream);
-
-// ---- product sumcheck rounds (shared by sumcheck_prove_product and matmul) ----
-// Runs d rounds over a, b (2^d elements each, folded in place), writing 3 values
-// per round and the two final values to `out` (canonical bytes) and driving the
-// transcript.  Needs product_rounds_scratch_bytes(n) of scratch.
 }  // namespace zkmi

@@ -236,20 +236,7 @@ int eq_table_run(uint32_t* dst, size_t stride, const host::F* u, int nvars, hipS
     return eq_tables_run(&t, 1, stream);
 }
 
-// ---- copy / fold / evaluation ----------------------------------------------------
-
-__global__ void __launch_bounds__(kBlock) k_copy(uint32_t* __restrict__ dst, size_t ds,
-                                                 const uint32_t* __restrict__ src, size_t ss, size_t n) {
-    for (size_t i = blockIdx.x * (size_t)kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) dst[k * ds + i] = src[k * ss + i];
-    }
-}
-
-void launch_copy(uint32_t* dst, size_t ds, const uint32_t* src, size_t ss, size_t n, hipStream_t stream) {
-    if (n == 0) return;
-    hipLaunchKernelGGL(k_copy, dim3(grid_for(n)), dim3(kBlock), 0, stream, dst, ds, src, ss, n);
-}
+// ---- evaluation ----------------------------------------------------------------------
 
 __global__ void k_emit(const uint32_t* __restrict__ a, size_t stride, size_t index, uint32_t* out, uint32_t* words, uint32_t seq) {
     if (threadIdx.x == 0) {

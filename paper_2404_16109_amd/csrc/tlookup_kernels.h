@@ -232,7 +232,6 @@ k_count_lds(uint32_t* m, uint32_t* __restrict__ part, const uint32_t* __restrict
         const size_t pass_end = pass_begin + chunk < D ? pass_begin + chunk : D;
         // whole wavefronts iterate together so that the cross-lane merge sees all 64
         // lanes; several elements per thread per trip keep more loads in flight
-        // (four when S is read as well, eight when only the hints are)
         constexpr int E = 8;
         for (size_t base = pass_begin; base < pass_end; base += E * kHistThreads) {
             size_t i[E];
@@ -370,10 +369,6 @@ static __global__ void __launch_bounds__(kBlock) k_rows_of(uint4* __restrict__ r
         at[2] = make_uint4(c.l[0], c.l[1], c.l[2], c.l[3]);
         at[3] = make_uint4(c.l[4], c.l[5], c.l[6], c.l[7]);
     }
-}
-
-static __global__ void __launch_bounds__(kBlock) k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
-    for (size_t i = blockIdx.x * (size_t)kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) p[i] = v;
 }
 
 // What counting starts from, in one launch: empty hash slots, zero counts, and the
@@ -1041,35 +1036,7 @@ struct DataRoundArgs {
 // qinf and the sums of A are computed (q0 and q1 stay zero and are set by the
 // host).
 // The three weighted sums are sums of products: they are accumulated as
-// unreduced 512-bit integers and reduced once per thread.  In the streaming
-// kernels the three 16-limb accumulators of a thread live in LDS (48 KiB per
-// workgroup, limb-major so that lanes hit distinct banks) and only pass through
-// registers while one product is added: holding them in registers would cost a
-// third of the kernel's occupancy.
-struct WideInLds {
-    // volatile: the accesses stay where they are written, so that at most one
-    // accumulator is in registers at a time
-    volatile uint32_t* base;  // [3][16][kBlock]
-    __device__ __forceinline__ void clear() {
-#pragma unroll
-        for (int k = 0; k < 48; ++k) base[k * kBlock + threadIdx.x] = 0;
-    }
-    __device__ __forceinline__ FrWide load(int which) const {
-        FrWide w;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) w.l[k] = base[(which * 16 + k) * kBlock + threadIdx.x];
-        return w;
-    }
-    __device__ __forceinline__ void mac(int which, const Fr& a, const Fr& b) {
-        FrWide w = load(which);
-        fr_wide_mac(w, a, b);
-#pragma unroll
-        for (int k = 0; k < 16; ++k) base[(which * 16 + k) * kBlock + threadIdx.x] = w.l[k];
-    }
-    __device__ __forceinline__ Fr finish(int which) const { return fr_wide_reduce(load(which)); }
-};
-
-// The same three accumulators in registers, for kernels with one pair per thread.
+// unreduced 512-bit integers, in registers, and reduced once per thread.
 struct WideInRegs {
     FrWide w[3];
     __device__ __forceinline__ void clear() {
@@ -1108,9 +1075,7 @@ __device__ __forceinline__ void data_pair(const DataRoundArgs& g, size_t p, size
 // all share the high-variable factor of their weight; it is applied once to the
 // workgroup's sums.
 template <bool FOLD>
-__device__ __forceinline__ void round_data_block(const DataRoundArgs& g, unsigned block, uint32_t* lds,
-                                                 uint32_t* wide_lds) {
-    (void)wide_lds;
+__device__ __forceinline__ void round_data_block(const DataRoundArgs& g, unsigned block, uint32_t* lds) {
     WideInRegs wide;
     wide.clear();
     Fr tot[5];
@@ -1143,7 +1108,7 @@ __device__ __forceinline__ void round_data_block(const DataRoundArgs& g, unsigne
 // serves the rounds that also bind a table variable.)
 static __global__ void __launch_bounds__(kBlock) k_round_data0(DataRoundArgs g) {
     __shared__ uint32_t lds[4 * 6 * 8];
-    round_data_block<false>(g, blockIdx.x, lds, nullptr);
+    round_data_block<false>(g, blockIdx.x, lds);
 }
 
 struct TableRoundArgs {
@@ -1223,7 +1188,7 @@ static __global__ void __launch_bounds__(kBlock) k_round_table(TableRoundArgs g)
 template <bool FOLD_T>
 static __global__ void __launch_bounds__(kBlock) k_round_both(DataRoundArgs d, TableRoundArgs t) {
     __shared__ uint32_t lds[4 * 6 * 8];
-    if (blockIdx.y == 0) round_data_block<true>(d, blockIdx.x, lds, nullptr);
+    if (blockIdx.y == 0) round_data_block<true>(d, blockIdx.x, lds);
     else if (blockIdx.y == 1) round_table_block<FOLD_T, 1>(t, blockIdx.x, lds);
     else round_table_block<FOLD_T, 2>(t, blockIdx.x, lds);
 }
