@@ -46,7 +46,7 @@ def _instances(orc, zk, rng, shapes, dup=False):
 
 
 SHAPES = [
-    [(1 << 10, 1 << 4)],                                # one instance alone (its small rounds in the resident kernel)
+    [(1 << 10, 1 << 4)],                                # one instance alone
     [(1, 1), (1, 1)],                                   # no round at all
     [(2, 1), (1, 1)],
     [(8, 2), (4, 4)],
@@ -56,8 +56,8 @@ SHAPES = [
     [(1 << 10, 1 << 10), (1 << 12, 1 << 12)],           # the shapes of LayerNorm's two lookups
     [(1 << 12, 1 << 4), (1 << 14, 1 << 6), (1 << 9, 1 << 9)],
     [(1 << 13, 1 << 5), (1 << 13, 1 << 9)],             # equal lengths, different tables
-    [(1 << 14, 1 << 10), (1 << 18, 1 << 6)],            # the long one runs rounds on 29-bit limbs while the short one waits
-    [(1 << 17, 1 << 7), (1 << 16, 1 << 5), (1 << 17, 1 << 12)],  # 29-bit rounds of instances that start at different rounds
+    [(1 << 14, 1 << 10), (1 << 18, 1 << 6)],            # the long one's first pass serves two rounds while the short one waits
+    [(1 << 17, 1 << 7), (1 << 16, 1 << 5), (1 << 17, 1 << 12)],  # such passes in instances that start at different rounds
 ]
 
 

@@ -35,7 +35,7 @@ def _instance(orc, zk, rng, D, N):
 
 def test_two_threads_prove_at_once(zk, orc):
     rng = random.Random(4242)
-    # two different lookups: one with rounds on 29-bit limbs and the resident kernel, one small
+    # two different lookups: one whose first pass serves two rounds, one that passes serve from the start
     cases = [_instance(orc, zk, rng, 1 << 17, 1 << 6), _instance(orc, zk, rng, 1 << 14, 1 << 9)]
     seeds = [rng.randbytes(32), rng.randbytes(32)]
     want = []

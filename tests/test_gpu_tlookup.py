@@ -73,10 +73,10 @@ def test_proof_bytes_equal_oracle(zk, orc, D, N, dup):
 
 def test_every_shape_up_to_2_pow_12(zk, orc):
     """All pairs (D, N) of powers of two with N <= D <= 2^12 and a few larger ones with
-    tiny tables: every place where the path changes (which rounds run on 29-bit limbs
-    and where such a run of rounds starts and ends, where the resident kernel takes
-    over, whether table and tensor are inverted as one vector, which rounds bind table
-    variables) moves with the shape."""
+    tiny tables: every place where the path of the short rounds changes (how many
+    variables each pass serves, which of them are the table's, where the host takes
+    over, how short the hash leaves and the inversion's levels get) moves with the
+    shape."""
     rng = random.Random(4242)
     shapes = [(1 << n, 1 << l) for n in range(13) for l in range(n + 1)]
     shapes += [(1 << 18, 1), (1 << 18, 2), (1 << 19, 1 << 3), (1 << 16, 1 << 16), (1 << 14, 1 << 13)]
@@ -251,8 +251,8 @@ def test_same_bytes_when_run_twice(zk, orc):
 
 
 def test_random_shapes_up_to_2_pow_18(zk, orc):
-    """Sixteen seeded shapes between 2^13 and 2^18 entries with any table length that fits (rounds on 29-bit limbs of
-    every length, the first pass serving two rounds or not, tables bound early or late): proofs equal to the oracle's,
+    """Sixteen seeded shapes between 2^13 and 2^18 entries with any table length that fits (passes from the first round
+    on or after it, the first pass serving two rounds or not, tables bound early or late): proofs equal to the oracle's,
     with and without row hints, and the same from the checked and the gathering entry points."""
     rng = random.Random(31415)
     for trial in range(16):

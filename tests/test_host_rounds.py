@@ -1,5 +1,5 @@
 """The rounds of a tlookup proof that the prover leaves to the host (at most 32
-pairs: the resident kernel hands the five arrays over and the host computes the
+pairs: the device hands the five arrays over and the host computes the
 sums, folds and final claims), checked here without a GPU against the sums'
 definitions written out on Python integers: Section 3.3's sumcheck round over
 the pairs (p, p + half), Section 4's summand split into the kernels' eleven sums,
