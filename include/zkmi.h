@@ -569,7 +569,7 @@ int zkmi_selftest_resident_wait(void* ws, size_t ws_bytes, void* stream);
  * Returns the number of rounds, ZK_E_BUFSZ if cap_rounds is below it. */
 int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int32_t* out, size_t cap_rounds);
 
-/* The rounds a single tlookup proof leaves to the host (kernel code 7 above), on
+/* The rounds a single tlookup proof leaves to the host (kind 7 above), on
  * arrays and challenges of the caller's choosing; no GPU is touched.  All
  * pointers are host memory, all elements canonical.  A, S: n_data elements
  * (2..64, a power of two); B, M, T: n_table elements (a power of two, at most

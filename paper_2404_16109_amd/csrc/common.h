@@ -83,8 +83,8 @@ struct Mailbox {
         seq = seq == 0xfffffffeu ? 1 : seq + 1;
         return seq;
     }
-    // The other direction: a kernel that stays resident over several sumcheck
-    // rounds reads each round's challenge from here.  Word 0 is the sequence
+    // The other direction: a kernel that stays resident over a sumcheck round reads
+    // the challenge from here.  Word 0 is the sequence
     // number of the challenge in words 1..8 (the host writes it last); kCmdAbort
     // tells a waiting kernel to give up.
     uint32_t* cmd = nullptr;    // kCmdWords uint32_t, coherent pinned memory

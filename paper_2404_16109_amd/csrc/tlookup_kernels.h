@@ -757,7 +757,10 @@ static __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
 // 205 us, in pairs 239); where every element is converted or built from integers first, whose long
 // chains one wavefront per SIMD waits out, the pairs are still ahead at twice as many
 // (the same without rows: 408 us, in pairs 235; 2^23 entries from integers, 1032
-// groups: 608 us, in pairs 425).  At 2^25 elements, 1079 us against 1145 in pairs.
+// groups: 608 us, in pairs 425).  At 2^25 elements from rows, 1079 us against 1145 in pairs.
+// Beyond 1040 groups, whole calls by lane and in pairs: a verification of 2^24 entries
+// 1.05 and 1.02 ms, of 2^25 1.70 and 1.70; a proof from integers of 2^24 2.67 and 2.49 ms,
+// of 2^25 4.45 and 4.08, so that for integers the line could lie higher still.
 static const uint32_t kPipedLeafGroups = 512, kPipedLeafGroupsConverting = 1040;
 template <int MODE>
 static bool leaves_in_pairs(uint32_t groups) {
