@@ -8,8 +8,8 @@
 //   up pass    : each thread receives the inverse of its own total and walks
 //                back over its elements: out_j = inv * prefix_{j-1}, inv *= x_j.
 //
-// A level that is short enough (<= 2^20 elements, a first level <= 2^17) is reduced
-// by whole workgroups instead: the threads' totals are multiplied up within the
+// A level that is short enough (<= 2^20 elements, a first level of 2561 to 2^17) is
+// reduced by whole workgroups instead: the threads' totals are multiplied up within the
 // workgroup (a scan in LDS), so the next level is 256*K times smaller and fits
 // the top.  That saves dependent launches, which is all the small levels cost:
 // eight for 2^25 elements instead of twelve, four for a table of 2^16.  (Longer
@@ -303,7 +303,13 @@ static const size_t kBiTopMax = kBlock;  // values the top kernels take
 // Whether level `depth` of length n is reduced by whole workgroups, how many
 // elements a thread then takes (as few as still leave the top at most kBiTopMax
 // values: the chain of products is what such a level costs), and the next level's length.
-static bool bi_by_workgroups(int depth, size_t n) { return n <= kBiTopMax * kBlock * (depth >= 1 ? kBiK : 2); }
+static bool bi_by_workgroups(int depth, size_t n) {
+    if (depth >= 1) return n <= kBiTopMax * kBlock * kBiK;
+    // the threads of one workgroup leave the top its 256 values straight away; their chain, one product per 256 elements
+    // there and two back, costs less than the workgroups' scans up to ten of them (whole calls by threads and by
+    // workgroups: 512 elements 57.6 and 76.4 us, 2048 71.4 and 77.3, 2560 76.0 and 77.9, 3072 80.5 and 78.2)
+    return n > (size_t)kBlock * 10 && n <= kBiTopMax * kBlock * 2;
+}
 static int bi_wg_per_thread(size_t n) {
     int per = 2;
     while (per < kBiK && div_up(n, (size_t)kBlock * per) > kBiTopMax) per *= 2;
