@@ -356,7 +356,10 @@ __global__ void __launch_bounds__(kBlock) k_mle_stage(MleStageArgs args) {
     }
     if (args.seq) {
         __syncthreads();
-        if (threadIdx.x == 0 && atomicAdd(args.ticket, 1u) == gridDim.x - 1) {
+        if (threadIdx.x != 0) return;
+        if (gridDim.x == 1) {  // one evaluation: nobody to wait for
+            mailbox_publish(args.words, args.seq);
+        } else if (atomicAdd(args.ticket, 1u) == gridDim.x - 1) {
             *args.ticket = 0;
             mailbox_publish(args.words, args.seq);
         }
@@ -450,7 +453,7 @@ int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint
     targs.table = (uint8_t*)cv.take((size_t)targs.total * kToepBytes);
     uint32_t* ticket = (uint32_t*)cv.take(256);
     if (!targs.table || !ticket) return ZK_E_BUFSZ;
-    launch_fill_u32(ticket, 1, 0u, stream);
+    if (njobs > 1) launch_fill_u32(ticket, 1, 0u, stream);
     hipLaunchKernelGGL(k_mle_table, dim3(grid_for((size_t)targs.total * 32)), dim3(kBlock), 0, stream, targs);
     // every job's last stage in the last launch, so that one flag stands for all
     ToepSource cur[kMleMaxJobs];
