@@ -1,0 +1,145 @@
+// Sums of products of field elements on the matrix cores.
+//
+// sum_p x_p y_p needs no reduction until its end, and in base 256 it is
+//   sum_(i,j) 2^(8 (i + j)) C_ij,   C_ij = sum_p (digit i of x_p) (digit j of y_p):
+// the 32 x 32 matrix C is a product of a 32 x P matrix of bytes with a P x 32 one,
+// and v_mfma_i32_32x32x32_i8 adds 32 positions p to it in 32 cycles.  64 products of
+// 256-bit integers so cost two matrix instructions, 64 cycles, beside which the vector
+// ALU is free; on the vector ALU they are 81 multiply-adds and the carries, 500 cycles.
+// What the vector ALU still does is a digit conversion per operand: sixteen
+// instructions, then two 16-byte stores to LDS and four transposing loads.
+//
+// Digits are balanced (-128..127), so that nothing has to be corrected afterwards:
+// the bytes of v + C0 with the top bit of each flipped, C0 = 128 (1 + 256 + ...).
+// Needs v + C0 < 2^256, i.e. v < 1.099 r: reduced elements, and products as f29_mul
+// leaves them (below r + r^2 / 2^261 < 1.015 r).
+//
+// Operands come one element per lane (lane = position).  A transposing LDS load gives
+// sixteen lanes that read eight rows of sixteen bytes one column each, so the digits
+// are staged as two planes (digits 0..15 and 16..31) of sixteen bytes per position:
+// stores and loads both run over consecutive addresses.  The staging area is a
+// wavefront's own; LDS instructions of one wavefront execute in order, so there are no
+// barriers in the loop.
+#pragma once
+#include "mfma_dev.h"
+#include "reduce_dev.h"
+
+namespace zkmi {
+
+typedef int v2i __attribute__((ext_vector_type(2)));
+
+static const int kOuterBatch = 64;         // positions a wavefront takes at a time
+static const int kOuterStage = 2048;       // bytes of LDS a wavefront stages one operand in
+static const size_t kOuterMaxSpan = 4096;  // positions per workgroup: outer_close's bound
+
+// One operand of 64 positions for two matrix instructions: lane l holds digit l % 32
+// of positions 32 s + 16 (l / 32) .. + 15 in half s.
+struct OuterOperand {
+    v4i half[2];
+};
+
+__device__ __forceinline__ void balanced_digits(uint32_t (&d)[8], const uint32_t (&v)[8]) {
+    uint32_t carry = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        uint32_t co;
+        d[j] = __builtin_addc(v[j], kFlip, carry, &co) ^ kFlip;
+        carry = co;
+    }
+}
+
+// digits: 32 bytes of this lane's position.
+__device__ __forceinline__ OuterOperand outer_stage(const uint32_t (&digits)[8], uint8_t* stage) {
+    const int lane = threadIdx.x & 63;
+    __builtin_amdgcn_wave_barrier();
+    *reinterpret_cast<uint4*>(stage + 16 * lane) = make_uint4(digits[0], digits[1], digits[2], digits[3]);
+    *reinterpret_cast<uint4*>(stage + 1024 + 16 * lane) = make_uint4(digits[4], digits[5], digits[6], digits[7]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint8_t* at = stage + ((lane >> 4) & 1) * 1024 + (lane >> 5) * 256 + (lane & 15) * 8;
+    OuterOperand o;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        typedef __attribute__((address_space(3))) v2i lds_v2i;
+        const v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(at + 512 * s));
+        const v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(at + 512 * s + 128));
+        o.half[s] = v4i{lo.x, lo.y, hi.x, hi.y};
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return o;
+}
+
+__device__ __forceinline__ OuterOperand outer_operand(const uint32_t (&v)[8], uint8_t* stage) {
+    uint32_t d[8];
+    balanced_digits(d, v);
+    return outer_stage(d, stage);
+}
+
+__device__ __forceinline__ void outer_mac(v16i& acc, const OuterOperand& a, const OuterOperand& b) {
+    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a.half[0], b.half[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a.half[1], b.half[1], acc, 0, 0, 0);
+}
+
+__device__ __forceinline__ void outer_clear(v16i& acc) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0;
+}
+
+// The sums of a workgroup of four wavefronts.  `sums`: N * 1024 words of LDS (may
+// overlap the staging areas).  Columns are taken in groups of GROUP lanes, each the
+// digits of one value: 32 (field elements) or 8 (64-bit integers, four to an
+// operand).  Calls out(q, group, x) in one lane for every sum of accumulator q,
+//   x = sum_(i,j) 2^(8 (i + j)) C_ij / 2^256 mod r, reduced.
+// A column sum_i 2^(8 i) C_ij is below 2^(8 31) 256/255 * 2^14 positions < 2^20 r in
+// magnitude for kOuterMaxSpan positions, which is what the bias makes up for.
+template <int N, int GROUP, class Out>
+__device__ __forceinline__ void outer_close(const v16i (&acc)[N], int* sums, Out&& out) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sums[(q * 16 + r) * 64 + lane] = acc[q][r];
+    }
+    __syncthreads();
+    if (wave != 0) {
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) atomicAdd(&sums[(q * 16 + r) * 64 + lane], acc[q][r]);
+    }
+    __syncthreads();
+    ToepBias bias;  // 2^20 r
+    constexpr uint32_t r32[8] = {ZK_R0, ZK_R1, ZK_R2, ZK_R3, ZK_R4, ZK_R5, ZK_R6, ZK_R7};
+#pragma unroll
+    for (int k = 0; k < 9; ++k) bias.w[k] = (k < 8 ? r32[k] << 20 : 0u) | (k > 0 ? r32[k - 1] >> 12 : 0u);
+    // two accumulators at a time: lanes 0..31 take the columns of the first, the others those of the second
+#pragma unroll 1
+    for (int q = 2 * wave; q < N; q += 8) {
+        const int q1 = q + 1 < N ? q + 1 : q;
+        v16i a, b;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            a[r] = sums[(q * 16 + r) * 64 + lane];
+            b[r] = sums[(q1 * 16 + r) * 64 + lane];
+        }
+        Fr v = toeplitz_finish(a, b, bias);
+        Fr pw;
+        const int at = lane & (GROUP - 1);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) pw.l[j] = (at >> 2) == j ? 1u << (8 * (at & 3)) : 0u;
+        v = fr_mul(v, pw);
+        v = dpp_add_step<0x111, 0xf>(v);
+        v = dpp_add_step<0x112, 0xf>(v);
+        v = dpp_add_step<0x114, 0xf>(v);
+        if constexpr (GROUP == 32) {
+            v = dpp_add_step<0x118, 0xf>(v);
+            v = dpp_add_step<0x142, 0xa>(v);
+        }
+        const int which = lane < 32 ? q : q + 1;
+        if (which < N && at == GROUP - 1) out(which, (lane & 31) / GROUP, v);
+    }
+}
+
+}  // namespace zkmi

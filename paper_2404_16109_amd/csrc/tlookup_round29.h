@@ -24,27 +24,6 @@
 
 namespace zkmi {
 
-// `count` elements of nine 29-bit limbs in three planes: limbs 0..3 of element i
-// as one uint4 at base[i], limbs 4..7 at base[count + i], limb 8 as a word at
-// ((uint32_t*)(base + 2 count))[i] (a wavefront reads 1 KiB, 1 KiB and 256 B, each
-// contiguous).  36 * count bytes.
-struct Planes29 {
-    uint4* base;
-    size_t count;
-};
-
-__device__ __forceinline__ F29 planes29_load(const Planes29& a, size_t i) {
-    const uint4 u = a.base[i], v = a.base[a.count + i];
-    const uint32_t top = reinterpret_cast<const uint32_t*>(a.base + 2 * a.count)[i];
-    return F29{{u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w, top}};
-}
-
-__device__ __forceinline__ void planes29_store(const Planes29& a, size_t i, const F29& x) {
-    a.base[i] = make_uint4(x.l[0], x.l[1], x.l[2], x.l[3]);
-    a.base[a.count + i] = make_uint4(x.l[4], x.l[5], x.l[6], x.l[7]);
-    reinterpret_cast<uint32_t*>(a.base + 2 * a.count)[i] = x.l[8];
-}
-
 // One of the two arrays a round folds.  It arrives as eight planes of 32-bit
 // words (fully reduced: the first of a run of such rounds) or in `planes`, and
 // leaves in `planes` (in place) or as fully reduced words (the last of a run).

@@ -42,6 +42,7 @@
 #include "small_dev.h"
 #include "tlookup_kernels.h"
 #include "grid_dev.h"
+#include "link_long.h"
 #include "transcript.h"
 
 #include <algorithm>
@@ -507,6 +508,161 @@ static int link_tables_build(LinkTables& lt, const host::F* u, int nr, int nc, C
     return ZK_OK;
 }
 
+// ---- the long rounds' weights and passes (link_long.h) ----------------------------------------
+//
+// Tensors of more than kLinkPassVars variables, one or two segments: passes over two
+// variables (three of the integers first) until at most kLinkPassVars are left.  Each has
+// its high tables; the low ones are the same for all.
+static bool link_long(int n, int K) { return n > kLinkPassVars && K <= 2; }
+static int link_long_vars(int t, bool ints) { return ints && t == 0 ? kLongIntVars : kLongVars; }
+
+struct LongTables {
+    uint32_t* pool = nullptr;
+    size_t stride = 0;
+    uint4* pool29 = nullptr;
+    uint32_t lo = 0, rlo = 0;
+    uint32_t hi[32], rhi[32];  // by the pass's first variable
+    int n = 0, nr = 0;
+
+    static int row_low_vars(int n, int nr) { return nr > n - kLongLo ? nr - (n - kLongLo) : 0; }
+    static int high_vars(int n, int t, int vars) { return n - kLongLo - t - vars; }
+    static int row_high_vars(int n, int nr, int t, int vars) {
+        const int v = std::min(nr, n - kLongLo) - t - vars;
+        return v > 0 ? v : 0;
+    }
+    static size_t entries(int n, int nr, bool ints) {
+        size_t total = ((size_t)2 << kLongLo) + ((size_t)1 << row_low_vars(n, nr));
+        for (int t = 0; n - t > kLinkPassVars; t += link_long_vars(t, ints)) {
+            const int v = link_long_vars(t, ints);
+            total += ((size_t)1 << high_vars(n, t, v)) + ((size_t)1 << row_high_vars(n, nr, t, v));
+        }
+        return total;
+    }
+    static size_t bytes(int n, int nr, bool ints) {
+        Carver cv(nullptr, 0);
+        cv.limbs(entries(n, nr, ints));
+        cv.take((size_t)36 << kLongLo);
+        return cv.used();
+    }
+    int build(const host::F* u, int n_, int nr_, bool ints, Carver& cv, hipStream_t stream) {
+        n = n_;
+        nr = nr_;
+        stride = entries(n, nr, ints);
+        pool = cv.limbs(stride);
+        pool29 = (uint4*)cv.take((size_t)36 << kLongLo);
+        if (!pool || !pool29) return ZK_E_BUFSZ;
+        EqPoolArgs args;
+        memset(&args, 0, sizeof args);
+        for (int t = 0; t < n; ++t) args.u[t] = to_dev(u[t]);
+        uint32_t off = 0;
+        auto table = [&](int var0, int nvars) {
+            const int q = args.ntables++;
+            args.offset[q] = off;
+            args.var0[q] = (uint8_t)var0;
+            args.nvars[q] = (uint8_t)nvars;
+            off += 1u << nvars;
+            return args.offset[q];
+        };
+        lo = table(n - kLongLo, kLongLo);
+        rlo = table(n - kLongLo, row_low_vars(n, nr));
+        for (int t = 0; n - t > kLinkPassVars; t += link_long_vars(t, ints)) {
+            const int v = link_long_vars(t, ints);
+            hi[t] = table(t + v, high_vars(n, t, v));
+            rhi[t] = table(t + v, row_high_vars(n, nr, t, v));
+        }
+        args.scale = to_dev(host::from_u64(32));
+        args.pool29 = pool29;
+        args.count29 = (size_t)1 << kLongLo;
+        args.first29 = off;
+        args.scaled[args.ntables] = 1;
+        table(n - kLongLo, kLongLo);
+        args.total = off;
+        launch_eq_pool(pool, stride, args, stream);
+        ZK_HIP_TRY(hipGetLastError());
+        return ZK_OK;
+    }
+    // of the pass that serves `vars` variables from t on
+    LongWeights weights(int t, int vars) const {
+        LongWeights w;
+        w.pool = pool;
+        w.stride = stride;
+        w.lo29 = Planes29{pool29, (size_t)1 << kLongLo};
+        w.lo = lo;
+        w.rlo = rlo;
+        w.hi = hi[t];
+        w.rhi = rhi[t];
+        w.rlo_shift = kLongLo - row_low_vars(n, nr);
+        w.rhi_shift = high_vars(n, t, vars) - row_high_vars(n, nr, t, vars);
+        w.lo_mask = (1u << kLongLo) - 1;
+        return w;
+    }
+};
+
+// Positions per workgroup: as many as the weights' high factor and the sums allow, but at
+// least 1024 workgroups while a wavefront has a batch for itself.
+static size_t long_span(size_t P) {
+    size_t span = P / 1024;
+    if (span < (size_t)4 * kOuterBatch) span = (size_t)4 * kOuterBatch;
+    return span < kOuterMaxSpan ? span : kOuterMaxSpan;
+}
+// Most partial values of a pass: the integers' first, or nine classes and four t of five sums.
+static const size_t kLongValues = 16 + kLongMixed;
+static size_t long_partials(int n) {
+    return link_long(n, 1) ? ((size_t)1 << (n - kLongVars)) / long_span((size_t)1 << (n - kLongVars)) * kLongValues : 0;
+}
+
+// C0 s mod r (C0: 0x80 in each of the low `bytes` bytes) plus 4096 m r.
+static ToepBias long_bias(const host::F& s, int bytes, uint32_t m) {
+    using namespace host;
+    fr_t c0;
+    memset(&c0, 0, sizeof c0);
+    memset(&c0, 0x80, (size_t)bytes);
+    if (bytes == 32) {  // C0 - r
+        static const uint32_t w[8] = {0x8080807fu, 0x80808081u, 0x80822481u, 0x2cc2dc7du, 0x76dea87bu, 0x4d46a878u, 0x56e30338u, 0x0c92d92du};
+        memcpy(&c0, w, sizeof w);
+    }
+    const fr_t v = to_canonical(mul(from_canonical(c0), s));
+    uint32_t c[8];
+    memcpy(c, &v, sizeof c);
+    static const uint32_t r32[8] = {ZK_R0, ZK_R1, ZK_R2, ZK_R3, ZK_R4, ZK_R5, ZK_R6, ZK_R7};
+    ToepBias b;
+    uint64_t acc = 0;
+    for (int k = 0; k < 8; ++k) {
+        acc += (uint64_t)r32[k] * (4096u * m) + c[k];
+        b.w[k] = (uint32_t)acc;
+        acc >>= 32;
+    }
+    b.w[8] = (uint32_t)acc;
+    return b;
+}
+
+// e~(r, c) over the last `vars` challenges, the last one in r[2], times s.
+static void long_constants(host::F* e, const host::F r[3], int vars, const host::F& s) {
+    using namespace host;
+    e[0] = s;
+    for (int v = 0; v < vars; ++v)
+        for (int c = (1 << v) - 1; c >= 0; --c) {
+            const F hi = mul(e[c], r[3 - vars + v]);
+            e[2 * c] = sub(e[c], hi);
+            e[2 * c + 1] = hi;
+        }
+}
+
+// Class sums (per variable: 0, 1, mixed) to values on {0, 1, inf}: inf = 0 + 1 - mixed.
+static void long_classes_to_grid(HostGrid& g) {
+    using namespace host;
+    const int count = (int)grid_points(g.vars);
+    for (int step = 1; step < count; step *= 3)
+        for (int i = 0; i < count; ++i)
+            if (i / step % 3 == 2) g.g[i] = sub(add(g.g[i - 2 * step], g.g[i - step]), g.g[i]);
+}
+
+static unsigned long_fold_blocks(size_t P) {
+    const size_t b = P / 512;
+    return (unsigned)(b < 1 ? 1 : b > 1024 ? 1024 : b);
+}
+static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+
 // ---- prover -----------------------------------------------------------------------------------
 
 static size_t link_proof_len(int n, int K) { return 64 + (size_t)n * (K + 2) * 32 + (size_t)(2 * K + 2) * 32; }
@@ -558,7 +714,7 @@ static void carve_link(LinkWs& w, Carver& cv, size_t D, size_t cols, int K) {
         w.mle_partials = cv.limbs((size_t)K << (n - lb));
     }
     w.part_blocks = link_blocks_max(log2_floor(D / cols), log2_floor(cols));
-    w.partials = cv.limbs(std::max(w.part_blocks * (K + 5), (size_t)kLinkGridValues * kGridChunks));
+    w.partials = cv.limbs(std::max({w.part_blocks * (K + 5), (size_t)kLinkGridValues * kGridChunks, long_partials(log2_floor(D))}));
     w.ticket = (uint32_t*)cv.take(256);
     w.fold = (SmallFoldConsts*)cv.take(sizeof(SmallFoldConsts) * 2);
 }
@@ -567,7 +723,9 @@ static size_t link_ws_bytes(size_t rows, size_t cols, int K) {
     Carver cv(nullptr, 0);
     LinkWs w;
     carve_link(w, cv, rows * cols, cols, K);
-    cv.limbs(LinkTables::entries(log2_floor(rows), log2_floor(cols)));
+    const int nr = log2_floor(rows), n = nr + log2_floor(cols);
+    cv.limbs(LinkTables::entries(nr, n - nr));
+    if (link_long(n, K)) cv.take(std::max(LongTables::bytes(n, nr, false), LongTables::bytes(n, nr, true)));
     cv.take(mle_scratch_bytes(log2_floor(rows)));
     return cv.used();
 }
@@ -747,6 +905,9 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
 
     LinkTables lt;
     ZK_TRY(link_tables_build(lt, u, nr, nc, cv, stream));
+    const bool long_rounds = link_long(n, K);
+    LongTables lw;
+    if (long_rounds) ZK_TRY(lw.build(u, n, nr, small != nullptr, cv, stream));
 
     F c = one();      // prod_{s<t} e~(u_s, r_s)
     F c_rows = one(); // its value once the row variables are bound
@@ -756,6 +917,7 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
     F prev_L[2], prev_s[2], prev_Q[K + 1];   // the last round's sums
     int pending = 0;  // of them, those that the arrays in the workspace have yet to be bound to
     int pass_left = 0;
+    bool passes = false;  // a pass of grid_dev.h has run
     HostGrid gq;
     HostLine gl, gs, gq1;
     LinkHost<K> tail;
@@ -777,10 +939,191 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
         on_host = true;
         return ZK_OK;
     };
+    // The long rounds' passes (link_long.h).  The arrays, 2^left elements each, with the pending challenges bound:
+    bool moved = false;  // they are in the workspace, Y scaled by alpha
+    const F two256 = F{{kRR[0], kRR[1], kRR[2], kRR[3]}};
+    auto long_fold = [&](int left) -> int {
+        if constexpr (K <= 2) {
+            const size_t P = (size_t)1 << left;
+            const dim3 grid(long_fold_blocks(P), K + 1);
+            if (small && !moved) {
+                LongFoldIntsArgs f;
+                memset(&f, 0, sizeof f);
+                f.Y = small->Y;
+                f.vec[0] = aligned16(small->Y);
+                f.dst[0] = w.Y;
+                for (int k = 0; k < K; ++k) {
+                    f.Yk[k] = small->Yk[k];
+                    f.vec[1 + k] = aligned16(small->Yk[k]);
+                    f.dst[1 + k] = w.Yk[k];
+                }
+                f.ds = D / 2;
+                f.P = P;
+                for (int s = 0; s < 2; ++s) {
+                    const F scale = s ? mul(alpha, two256) : two256;
+                    F e[1 << kLongIntVars];
+                    long_constants(e, r_last, kLongIntVars, scale);
+                    for (int c = 0; c < 1 << kLongIntVars; ++c) f.e[s][c] = to_dev(e[c]);
+                    f.bias[s] = long_bias(scale, s ? 8 : 4, 2);
+                }
+                hipLaunchKernelGGL(k_long_fold_ints, grid, dim3(kBlock), 0, stream, f);
+            } else {
+                LongFoldArgs f;
+                memset(&f, 0, sizeof f);
+                for (int q = 0; q <= K; ++q) {
+                    uint32_t* const dst = q ? w.Yk[q - 1] : w.Y;
+                    const fr_vec in = moved ? fr_vec{dst, D / 2, D / 2} : q ? Yk[q - 1] : Y;
+                    f.job[q] = LongFoldJob{in.limbs, in.stride, dst, D / 2, aligned16(in.limbs) && in.stride % 4 == 0, q == 0 && !moved};
+                }
+                f.P = P;
+                for (int s = 0; s < 2; ++s) {
+                    const F scale = s ? alpha : one();
+                    F e[1 << kLongVars];
+                    long_constants(e, r_last, kLongVars, scale);
+                    for (int c = 0; c < 1 << kLongVars; ++c) f.e[s][c] = to_dev(e[c]);
+                    f.bias[s] = long_bias(scale, 32, 1 << kLongVars);
+                }
+                hipLaunchKernelGGL(k_long_fold, grid, dim3(kBlock), 0, stream, f);
+            }
+            ZK_HIP_TRY(hipGetLastError());
+            moved = true;
+            pending = 0;
+        }
+        return ZK_OK;
+    };
+    // the sums of the pass that starts at round t
+    auto long_pass = [&](int t) -> int {
+        if constexpr (K <= 2) {
+            const bool ints = small && t == 0, first = t == 0;
+            const int left = n - t, vars = link_long_vars(t, small != nullptr);
+            if (pending) ZK_TRY(long_fold(left));
+            const size_t P = (size_t)1 << (left - vars), span = long_span(P);
+            const unsigned blocks = (unsigned)(P / span);
+            const LongWeights weights = lw.weights(t, vars);
+            const uint32_t seq = mb->next_seq();
+            int lines = 0;  // arrays summed by themselves
+            if (ints) {
+                LongIntsArgs a;
+                memset(&a, 0, sizeof a);
+                a.Z = small->Zp;
+                a.Y = small->Y;
+                for (int k = 0; k < K; ++k) {
+                    a.X[k] = small->X[k];
+                    a.Yk[k] = small->Yk[k];
+                    a.base[k] = small->bases[k];
+                }
+                a.yk_bound = K == 1 ? 0xffffffffu : 1u << 30;
+                a.P = P;
+                a.span = span;
+                a.w = weights;
+                a.partials = w.partials;
+                const int nv = K == 2 ? 16 + kLongMixed : 16;
+                a.pstride = (size_t)blocks * nv;
+                a.bad = bad_word;
+                hipLaunchKernelGGL((k_long_ints<K == 1 ? 1 : 2>), dim3(blocks), dim3(kBlock), 0, stream, a);
+                launch_final_sum(w.partials, a.pstride, blocks, nv, mb->words, mb->words, seq, w.ticket, stream);
+            } else {
+                auto vec_of = [&](int q) { return q ? (moved ? fr_vec{w.Yk[q - 1], D / 2, D / 2} : Yk[q - 1]) : moved ? fr_vec{w.Y, D / 2, D / 2} : Y; };
+                fr_vec arrays[4] = {vec_of(0)};
+                lines = 1;
+                if (first) {
+                    arrays[lines++] = Zp;
+                    for (int k = 0; k < K; ++k) arrays[lines++] = X[k];
+                }
+                if (K == 1) arrays[lines++] = vec_of(1);
+                uint32_t* line_partials = w.partials;
+                if (K == 2) {
+                    LongGridArgs a;
+                    memset(&a, 0, sizeof a);
+                    const fr_vec x = vec_of(1), y = vec_of(2);
+                    a.x = x.limbs;
+                    a.xs = x.stride;
+                    a.y = y.limbs;
+                    a.ys = y.stride;
+                    a.P = P;
+                    a.span = span;
+                    a.w = weights;
+                    a.partials = w.partials;
+                    a.pstride = (size_t)blocks * 9;
+                    line_partials += 8 * a.pstride;
+                    hipLaunchKernelGGL(k_long_grid, dim3(blocks), dim3(kBlock), 0, stream, a);
+                }
+                const int nl = 4 * (lines + 1);
+                auto launch_lines = [&](auto args) {
+                    for (int q = 0; q < lines; ++q) {
+                        args.a[q] = arrays[q].limbs;
+                        args.as[q] = arrays[q].stride;
+                    }
+                    args.P = P;
+                    args.span = span;
+                    args.w = weights;
+                    args.partials = line_partials;
+                    args.pstride = (size_t)blocks * nl;
+                    return args;
+                };
+                const dim3 grid(blocks, 4);
+                if (lines == 1) hipLaunchKernelGGL(k_long_lines<1>, grid, dim3(kBlock), 0, stream, launch_lines(LongLinesArgs<1>()));
+                else if (lines == 2) hipLaunchKernelGGL(k_long_lines<2>, grid, dim3(kBlock), 0, stream, launch_lines(LongLinesArgs<2>()));
+                else hipLaunchKernelGGL(k_long_lines<4>, grid, dim3(kBlock), 0, stream, launch_lines(LongLinesArgs<4>()));
+                launch_final_sum2(w.partials, (size_t)blocks * 9, K == 2 ? 9 : 0, line_partials, (size_t)blocks * nl, nl, blocks,
+                                  mb->words, mb->words, seq, w.ticket, stream);
+            }
+            ZK_HIP_TRY(hipGetLastError());
+            ZK_TRY(mailbox_wait(mb, seq, stream));
+            gl.vars = gs.vars = gq.vars = gq1.vars = vars;
+            if (ints) {
+                // what the pass found entry by entry
+                uint32_t bad = 0;
+                ZK_HIP_TRY(hipMemcpyAsync(&bad, bad_word, 4, hipMemcpyDeviceToHost, stream));
+                ZK_HIP_TRY(hipStreamSynchronize(stream));
+                if (bad & 2) return ZK_E_BADARG;  // an entry outside the ranges the integer path is written for
+                if (bad & 1) return ZK_E_REJECT;  // the tensors do not satisfy the relations
+                // sums for v - 0x80..80, integers times weights in Montgomery form, divided by 2^256: the weights w add up to one,
+                // the row weights to the number of column positions
+                const F flip = from_u64(0x8080808080808080ull);
+                F columns = one();
+                for (int v = std::max(nr, vars); v < n; ++v) columns = add(columns, columns);
+                auto value = [&](int q) { return mul(from_dev(mb->words + 8 * q), two256); };
+                const int nw = K == 2 ? 8 + kLongMixed : 8;
+                for (int c = 0; c < 8; ++c) {
+                    const F y = add(value(c), flip);
+                    gl.g[c] = mul(alpha, y);
+                    gs.g[c] = mul(alpha, add(value(nw + c), mul(columns, flip)));
+                    gq1.g[c] = y;
+                    gq.g[9 * (c >> 2) + 3 * ((c >> 1) & 1) + (c & 1)] = y;
+                }
+                if (K == 2) {
+                    constexpr LongMixedClasses mixed;
+                    for (int m = 0; m < kLongMixed; ++m) gq.g[mixed.id[m]] = add(value(8 + m), flip);
+                    long_classes_to_grid(gq);
+                }
+            } else {
+                if (K == 2) {
+                    for (int i = 0; i < 9; ++i) gq.g[i] = from_dev(mb->words + 8 * i);
+                    long_classes_to_grid(gq);
+                }
+                const uint32_t* at = mb->words + (K == 2 ? 72 : 0);
+                for (int c = 0; c < 4; ++c, at += 8 * (lines + 1)) {
+                    F y = from_dev(at), s = from_dev(at + 8 * lines);
+                    if (K == 1) gq1.g[c] = from_dev(at + 8 * (lines - 1));
+                    if (first) {
+                        y = add(mul(alpha, y), from_dev(at + 8));
+                        s = mul(alpha, s);
+                        for (int k = 0; k < K; ++k) y = add(y, mul(base[k], from_dev(at + 8 * (2 + k))));
+                    }
+                    gl.g[c] = y;
+                    gs.g[c] = s;
+                }
+            }
+            pass_left = pending = vars;
+        }
+        return ZK_OK;
+    };
     for (int t = 0; t < n; ++t) {
         const size_t half = (size_t)1 << (n - t - 1);
         const int left = n - t;
         F L0, L1, s0, s1, Q[NPTS];
+        if (long_rounds && pass_left == 0 && left > kLinkPassVars) ZK_TRY(long_pass(t));
         if (K <= 2 && t >= 2 && left <= kLinkHostVars && pass_left == 0) {
             if (!on_host) ZK_TRY(ship(t));
             F L2[2], s2[2];
@@ -789,8 +1132,10 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
             L1 = L2[1];
             s0 = s2[0];
             s1 = s2[1];
-        } else if (K <= 2 && t >= 2 && left <= kLinkPassVars) {
+        } else if (K <= 2 && (pass_left > 0 || (t >= 2 && left <= kLinkPassVars))) {
             if (pass_left == 0) {
+                if (long_rounds && pending && !passes) ZK_TRY(long_fold(left));
+                passes = true;
                 const int vars = pass_left = (left - kLinkHostVars - 1) % kGridVars + 1;
                 GridPass pass;
                 pass.challenges(r_last);

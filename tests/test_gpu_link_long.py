@@ -1,0 +1,91 @@
+"""The linking sumcheck's long rounds (csrc/link_long.h), which start at 2^17 scores: rows of one entry to all of them, so
+that row variables end before, inside and behind a pass and the low weight tables, one and two segments, vectors and
+integers that allow no 16-byte loads, field elements over the whole range, integers at their largest.  Exact arithmetic:
+equality with the oracle."""
+import random
+
+import numpy as np
+import pytest
+import torch
+
+from tests.test_gpu_link import small_on_device, small_oracle_proof, small_witness, to_device
+from tests.test_oracle_link import make_witness
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def zk():
+    import paper_2404_16109_amd as zk
+    assert torch.cuda.is_available()
+    return zk
+
+
+def shifted(zk, v):
+    """The same vector where no plane starts at a multiple of four words."""
+    out = zk.Vec(v.n, stride=v.n + 5)
+    out.data = torch.empty(8 * (v.n + 5) + 1, dtype=torch.int32, device="cuda")[1:].view(8, v.n + 5)
+    out.data[:, :v.n] = v.data[:, :v.n]
+    return out
+
+
+@pytest.mark.parametrize("log_rows,log_cols,K,aligned", [
+    (17, 0, 2, True), (15, 2, 1, True), (12, 5, 2, False), (9, 8, 2, True), (7, 10, 1, False), (6, 11, 2, True), (5, 12, 2, True),
+    (4, 13, 1, True), (1, 16, 2, True), (0, 17, 2, True), (10, 8, 2, True), (7, 11, 2, False)])
+def test_vectors(zk, orc, log_rows, log_cols, K, aligned):
+    rows, cols = 1 << log_rows, 1 << log_cols
+    rng = random.Random(1000 * log_rows + 10 * log_cols + K)
+    w = make_witness(rng, rows, cols, K, digit_bits=4, small_tables=False)
+    seed = rng.randbytes(32)
+    to = orc.to_bytes
+    rc, want, _ = orc.zkattn_link_prove(seed, to(w[0]), [to(a) for a in w[1]], to(w[2]), [to(a) for a in w[3]], to(w[4]), to(w[5]), rows, cols)
+    assert rc == 0
+    Zp, X, Y, Yk, yhat, bases = to_device(zk, orc, w)
+    if not aligned:
+        Zp, X, Y, Yk = shifted(zk, Zp), [shifted(zk, a) for a in X], shifted(zk, Y), [shifted(zk, a) for a in Yk]
+    rc, got = zk.zkattn_link_prove(seed, Zp, X, Y, Yk, yhat, bases, rows, cols)
+    assert rc == zk.ZK_OK and got == want
+    # a relation broken in one entry
+    for v in (Zp, X[-1], Y, Yk[0]):
+        pos = rng.randrange(rows * cols)
+        keep = v.data[0, pos].clone()
+        v.data[0, pos] ^= 1
+        assert zk.zkattn_link_prove(seed, Zp, X, Y, Yk, yhat, bases, rows, cols)[0] == zk.ZK_E_REJECT
+        v.data[0, pos] = keep
+
+
+@pytest.mark.parametrize("log_rows,log_cols,K,out_bits,aligned", [
+    (17, 0, 2, 30, True), (14, 3, 1, 32, True), (12, 5, 2, 30, False), (6, 11, 2, 16, True), (5, 12, 1, 16, False),
+    (2, 15, 2, 30, True), (0, 17, 1, 20, True), (7, 11, 2, 29, True), (10, 9, 2, 30, False)])
+def test_integers(zk, orc, log_rows, log_cols, K, out_bits, aligned):
+    rows, cols = 1 << log_rows, 1 << log_cols
+    gen = np.random.default_rng(100 * log_rows + log_cols + K)
+    w = list(small_witness(gen, rows, cols, K, 8, out_bits))
+    if out_bits >= 30:  # segment outputs at the largest that is accepted, side by side in all eight entries of a position
+        top = (1 << out_bits) - 1 - (out_bits == 32)
+        at = np.arange(8) * (rows * cols // 8) + 3
+        w[3] = [np.minimum(a, top) for a in w[3]]
+        for a in w[3]:
+            a[at] = top
+        w[2] = w[3][0] if K == 1 else w[3][0] * w[3][1]
+        w[4] = [sum(int(v) for v in row) for row in w[2].reshape(rows, cols)]
+    seed = bytes([log_rows, log_cols, K, out_bits]) * 8
+    rc, want, _ = small_oracle_proof(orc, seed, w, rows, cols)
+    assert rc == 0
+    Zp, X, Y, Yk, yhat, bases = small_on_device(zk, orc, w)
+    if not aligned:
+        shift = lambda t: torch.cat([t[:1], t])[1:]
+        Zp, X, Y, Yk = shift(Zp), [shift(a) for a in X], shift(Y), [shift(a) for a in Yk]
+    rc, got = zk.zkattn_link_prove_small(seed, Zp, X, Y, Yk, yhat, bases, rows, cols)
+    assert rc == zk.ZK_OK and got == want
+    for t, rc_want in ((Zp, zk.ZK_E_REJECT), (X[0], zk.ZK_E_REJECT), (Y, zk.ZK_E_REJECT), (Yk[-1], zk.ZK_E_REJECT)):
+        pos = int(gen.integers(0, rows * cols))
+        keep = t[pos].clone()
+        t[pos] = keep ^ 1
+        assert zk.zkattn_link_prove_small(seed, Zp, X, Y, Yk, yhat, bases, rows, cols)[0] == rc_want
+        t[pos] = keep
+    if K == 2:
+        keep = Yk[0][5].clone()
+        Yk[0][5] = 1 << 30
+        assert zk.zkattn_link_prove_small(seed, Zp, X, Y, Yk, yhat, bases, rows, cols)[0] == zk.ZK_E_BADARG
+        Yk[0][5] = keep
