@@ -12,7 +12,9 @@
 // (outer_dev.h).  Between passes the arrays are bound to V challenges at once, also there
 // (k_long_fold: a few constants per output, mfma_dev.h), so both kinds of kernel are
 // bound by HBM.  A fold of V variables reads the arrays once where V rounds read them V
-// times.
+// times.  Measured, two segments: 2^24 scores from vectors 3.17 -> 1.93 ms, 2^28 from
+// integers 20.9 -> 6.15 ms.  Two variables over field elements because their nine classes
+// of sums fit a wavefront's registers (27 do not) with another wavefront beside it.
 #pragma once
 #include "outer_dev.h"
 #include "tlookup_kernels.h"
@@ -30,15 +32,45 @@ struct LongWeights {
     const uint32_t* pool;  // w_p = lo[p & 4095] hi[p >> 12], rw_p = rlo[(p & 4095) >> rlo_shift] rhi[p >> (12 + rhi_shift)]
     size_t stride;
     Planes29 lo29;         // lo times 2^261
-    uint32_t lo, rlo, hi, rhi;
-    int rlo_shift, rhi_shift;
-    uint32_t lo_mask;
+    const uint4* lo_ops;   // lo and rlo of all 4096 places as operands
+    const uint4* rlo_ops;
+    uint32_t hi, rhi;
+    int rhi_shift;
 
     __device__ __forceinline__ Fr high(size_t p) const { return fr_load(pool, stride, hi + (p >> kLongLo)); }
     __device__ __forceinline__ Fr row_high(size_t p) const { return fr_load(pool, stride, rhi + ((p >> kLongLo) >> rhi_shift)); }
-    __device__ __forceinline__ Fr low(size_t p) const { return fr_load(pool, stride, lo + (p & lo_mask)); }
-    __device__ __forceinline__ Fr row_low(size_t p) const { return fr_load(pool, stride, rlo + ((p & lo_mask) >> rlo_shift)); }
+    __device__ __forceinline__ F29 low29(size_t p) const { return planes29_load(lo29, p & (((size_t)1 << kLongLo) - 1)); }
+    // of the 64 positions from p on
+    __device__ __forceinline__ OuterOperand low(size_t p) const { return outer_saved(lo_ops, (p >> 6) & ((1 << kLongLo) / 64 - 1)); }
+    __device__ __forceinline__ OuterOperand row_low(size_t p) const { return outer_saved(rlo_ops, (p >> 6) & ((1 << kLongLo) / 64 - 1)); }
 };
+
+// The low tables as operands: workgroup b makes four of them, of lo or (blockIdx.y) rlo.
+static __global__ void __launch_bounds__(kBlock) k_long_operands(const uint32_t* pool, size_t stride, uint32_t lo, uint32_t rlo,
+                                                                 int rlo_shift, uint4* lo_ops, uint4* rlo_ops) {
+    __shared__ __attribute__((aligned(16))) uint8_t stage[4 * kOuterStage];
+    const uint32_t p = blockIdx.x * kBlock + threadIdx.x, wave = threadIdx.x >> 6;
+    const Fr v = fr_load(pool, stride, blockIdx.y ? rlo + (p >> rlo_shift) : lo + p);
+    outer_save(blockIdx.y ? rlo_ops : lo_ops, blockIdx.x * 4 + wave, outer_operand(v.l, stage + wave * kOuterStage));
+}
+
+// Adds up a value's `count` partial sums, one workgroup per value.
+static __global__ void __launch_bounds__(kBlock) k_long_total(const uint32_t* partials, size_t pstride, unsigned count, uint32_t* out_words,
+                                                              uint32_t* words, uint32_t seq, uint32_t* ticket) {
+    __shared__ uint32_t lds[4 * 8];
+    Fr acc[1] = {fr_zero()};
+    for (unsigned b = threadIdx.x; b < count; b += kBlock) acc[0] = fr_add(acc[0], fr_load(partials, pstride, (size_t)blockIdx.x * count + b));
+    block_sum<1, 4>(acc, lds);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) out_words[8 * blockIdx.x + k] = acc[0].l[k];
+        mailbox_written();
+        if (atomicAdd(ticket, 1u) == gridDim.x - 1) {
+            *ticket = 0;
+            mailbox_publish(words, seq);
+        }
+    }
+}
 
 // The products of two arrays of 4 P elements by class (class 3 a + b: a, b = 0, 1 or 2
 // for mixed in the first and the second variable).  A workgroup takes `span` positions,
@@ -50,88 +82,102 @@ struct LongGridArgs {
     size_t xs, ys;
     size_t P, span;
     LongWeights w;
-    uint32_t* partials;  // nine per workgroup
+    uint32_t* partials;  // value q of workgroup b at q gridDim.x + b (as in all kernels here)
     size_t pstride;
 };
 
-__device__ __forceinline__ void long_load(uint32_t (&v)[8], const uint32_t* p, size_t stride, size_t i) {
-    const Fr x = fr_load(p, stride, i);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = x.l[k];
-}
-
+// Entries are asked for four ahead of their use: Y's of the next positions as X's are
+// taken, X's as Y's are staged.  At 2^24 entries 274 us, 3.9 TB/s (328 with entries asked
+// for where they are used); issue and HBM about equal.
 static __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) k_long_grid(LongGridArgs g) {
-    __shared__ __attribute__((aligned(16))) int sums[9 * 1024];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint8_t* stage = (uint8_t*)sums + wave * kOuterStage;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[4 * 5 * kOuterStage];  // per wavefront Y's four operands and one of X
+    static_assert(sizeof lds >= 9 * 4096, "outer_close's sums");
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint8_t* const stage = lds + wave * 5 * kOuterStage;
+    uint8_t* const stage_x = stage + 4 * kOuterStage;
     v16i acc[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) outer_clear(acc[q]);
-    const size_t start = blockIdx.x * g.span, share = g.span / 4;
+    const size_t start = blockIdx.x * g.span, share = g.span / 4, end = start + (wave + 1) * share;
+    size_t p = start + wave * share;  // of the wavefront's first lane
+    uint32_t v[4][8];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) outer_load(v[c], g.y, g.ys, c * g.P + p);
 #pragma unroll 1
-    for (size_t p = start + wave * share + lane; p < start + (wave + 1) * share; p += kOuterBatch) {
-        OuterOperand b[4];
+    for (; p < end; p += kOuterBatch) {
+        const size_t next = p + kOuterBatch < end ? p + kOuterBatch : p;
+        const F29 w = g.w.low29(p + (threadIdx.x & 63));
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            uint32_t v[8];
-            long_load(v, g.y, g.ys, c * g.P + p);
-            b[c] = outer_operand(v, stage);
+            uint32_t d[8];
+            balanced_digits(d, v[c]);
+            outer_put(d, stage + c * kOuterStage);
+            outer_load(v[c], g.x, g.xs, c * g.P + p);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        const F29 w = planes29_load(g.w.lo29, p & g.w.lo_mask);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            uint32_t v[8];
-            long_load(v, g.x, g.xs, c * g.P + p);
-            f29_pack(v, f29_mul(f29_unpack(v), w));  // below 1.015 r
-            const OuterOperand a = outer_operand(v, stage);
+            uint32_t x[8];
+            f29_pack(x, f29_mul(f29_unpack(v[c]), w));  // below 1.015 r
+            outer_load(v[c], g.y, g.ys, c * g.P + next);
+            __builtin_amdgcn_sched_barrier(0);
+            const OuterOperand a = outer_operand(x, stage_x);
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 const int hi = (c >> 1) == (d >> 1) ? c >> 1 : 2, lo = (c & 1) == (d & 1) ? c & 1 : 2;
-                outer_mac(acc[3 * hi + lo], a, b[d]);
+                outer_mac(acc[3 * hi + lo], a, outer_get(stage + d * kOuterStage));
             }
         }
     }
-    outer_close<9, 32>(acc, sums, [&](int q, int, const Fr& v) {
-        fr_store(g.partials, g.pstride, (size_t)blockIdx.x * 9 + q, fr_mul(v, g.w.high(start)));
+    outer_close<9, 32>(acc, (int*)lds, [&](int q, int, const Fr& x) {
+        fr_store(g.partials, g.pstride, (size_t)q * gridDim.x + blockIdx.x, fr_mul(x, g.w.high(start)));
     });
 }
 
 // The weighted sums of NA arrays of 4 P elements at the four t, and the first array's
-// with the row weights.  Workgroup (b, t).
+// with the row weights.  Workgroup (b, t).  Four arrays of 2^24 entries 372 us, 5.8 TB/s (637
+// with entries asked for where they are used, by flat loads, and weights staged each time).
 template <int NA>
 struct LongLinesArgs {
     const uint32_t* a[NA];
     size_t as[NA];
     size_t P, span;
     LongWeights w;
-    uint32_t* partials;  // 4 (NA + 1) per b: those of t = 0, ..
+    uint32_t* partials;  // values (NA + 1) t + ..
     size_t pstride;
 };
 
 template <int NA>
 static __global__ void __launch_bounds__(kBlock) k_long_lines(LongLinesArgs<NA> g) {
     __shared__ __attribute__((aligned(16))) int sums[(NA + 1) * 1024];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* stage = (uint8_t*)sums + wave * kOuterStage;
     v16i acc[NA + 1];
 #pragma unroll
     for (int q = 0; q <= NA; ++q) outer_clear(acc[q]);
-    const size_t start = blockIdx.x * g.span, share = g.span / 4, t = blockIdx.y;
+    const size_t start = blockIdx.x * g.span, share = g.span / 4, t = blockIdx.y, end = start + (wave + 1) * share;
+    size_t p = start + wave * share;  // of the wavefront's first lane
+    uint32_t v[NA][8];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) outer_load(v[q], g.a[q], g.as[q], t * g.P + p);
 #pragma unroll 1
-    for (size_t p = start + wave * share + lane; p < start + (wave + 1) * share; p += kOuterBatch) {
-        const OuterOperand w = outer_operand(g.w.low(p).l, stage), rw = outer_operand(g.w.row_low(p).l, stage);
+    for (; p < end; p += kOuterBatch) {
+        const size_t next = p + kOuterBatch < end ? p + kOuterBatch : p;
+        const OuterOperand w = g.w.low(p), rw = g.w.row_low(p);
 #pragma unroll
         for (int q = 0; q < NA; ++q) {
-            uint32_t v[8];
-            long_load(v, g.a[q], g.as[q], t * g.P + p);
-            const OuterOperand b = outer_operand(v, stage);
+            uint32_t d[8];
+            balanced_digits(d, v[q]);
+            outer_load(v[q], g.a[q], g.as[q], t * g.P + next);  // asked for a turn ahead
+            __builtin_amdgcn_sched_barrier(0);
+            const OuterOperand b = outer_stage(d, stage);
             outer_mac(acc[q], w, b);
             if (q == 0) outer_mac(acc[NA], rw, b);
         }
     }
-    outer_close<NA + 1, 32>(acc, sums, [&](int q, int, const Fr& v) {
+    outer_close<NA + 1, 32>(acc, sums, [&](int q, int, const Fr& x) {
         const Fr f = q == NA ? g.w.row_high(start) : g.w.high(start);
-        fr_store(g.partials, g.pstride, ((size_t)blockIdx.x * 4 + t) * (NA + 1) + q, fr_mul(v, f));
+        fr_store(g.partials, g.pstride, (t * (NA + 1) + q) * gridDim.x + blockIdx.x, fr_mul(x, f));
     });
 }
 
@@ -142,7 +188,8 @@ static __global__ void __launch_bounds__(kBlock) k_long_lines(LongLinesArgs<NA> 
 // sums of up to eight products below 2^60, exact in 64 bits.  Four 64-bit integers make
 // one operand of 32 digits: the whole pass is nine accumulators.  Their digits go in as
 // d - 128 (top bit flipped): the sums come out for v - 0x8080808080808080, which the host
-// puts right, the weights' sums being known.  Bound by HBM.
+// puts right, the weights' sums being known.  Bound by HBM: 2^28 entries 1.56 ms, 5.5 TB/s
+// (3.55 with entries asked for where they are used; 3.39 for one round by the vector ALU).
 struct LongIntsArgs {
     const int64_t* Z;
     const uint64_t* Y;
@@ -152,7 +199,7 @@ struct LongIntsArgs {
     uint32_t yk_bound;
     size_t P, span;
     LongWeights w;
-    uint32_t* partials;  // 8 + 19 (two segments) + 8 per workgroup: with w at t = 0..7, the mixed classes, with rw at t = 0..7
+    uint32_t* partials;  // 8 + 19 (two segments) + 8 values: with w at t = 0..7, the mixed classes, with rw at t = 0..7
     size_t pstride;
     uint32_t* bad;       // device word: 1 = a relation fails somewhere, 2 = an entry is out of range
 };
@@ -197,43 +244,77 @@ __device__ __forceinline__ void long_mixed_digits(uint32_t (&d)[8], const uint32
     else long_flip64(d + 6, 0);
 }
 
+// One entry of every tensor.
+template <int K>
+struct LongIntsEntry {
+    uint64_t z, y;
+    uint32_t x[K], yk[K];
+
+    // of this lane, the first lane's being entry `first`
+    template <class T>
+    static __device__ __forceinline__ T at(const T* p, size_t first) {
+        typedef const __attribute__((address_space(1))) T* global;
+        global q = (global)p + first;
+        asm("" : "+s"(q));
+        return q[threadIdx.x & 63];
+    }
+    __device__ __forceinline__ void load(const LongIntsArgs& g, size_t first) {
+        z = (uint64_t)at(g.Z, first);
+        y = at(g.Y, first);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            x[k] = at(g.X[k], first);
+            yk[k] = at(g.Yk[k], first);
+        }
+    }
+    __device__ __forceinline__ uint32_t check(const LongIntsArgs& g) const {
+        const int64_t zlim = (int64_t)1 << 62, zs = (int64_t)z;
+        uint32_t bad = zs <= -zlim || zs >= zlim || y >= (uint64_t)zlim ? 2u : 0u;
+        __int128 lin = zs;
+        uint64_t prod = 1;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            lin += (__int128)g.base[k] * x[k];
+            if (yk[k] >= g.yk_bound) bad |= 2;
+            prod *= yk[k];  // below 2^60 when every factor is in range (else the entry is reported anyway)
+        }
+        if (lin != 0 || prod != y) bad |= 1;
+        return bad;
+    }
+};
+
+// Entries are asked for four ahead of their use.
 template <int K>
 static __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) k_long_ints(LongIntsArgs g) {
     constexpr int NW = K == 2 ? 7 : 2, N = NW + 2, NV = K == 2 ? 16 + kLongMixed : 16;
     __shared__ __attribute__((aligned(16))) int sums[N * 1024];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* stage = (uint8_t*)sums + wave * kOuterStage;
     v16i acc[N];
 #pragma unroll
     for (int q = 0; q < N; ++q) outer_clear(acc[q]);
     uint32_t bad = 0;
-    const int64_t zlim = (int64_t)1 << 62;
-    const size_t start = blockIdx.x * g.span, share = g.span / 4;
+    const size_t start = blockIdx.x * g.span, share = g.span / 4, end = start + (wave + 1) * share;
+    size_t p = start + wave * share;  // of the wavefront's first lane
+    LongIntsEntry<K> e[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) e[t].load(g, t * g.P + p);
 #pragma unroll 1
-    for (size_t p = start + wave * share + lane; p < start + (wave + 1) * share; p += kOuterBatch) {
+    for (; p < end; p += kOuterBatch) {
+        const size_t next = p + kOuterBatch < end ? p + kOuterBatch : p;
+        const OuterOperand w = g.w.low(p), rw = g.w.row_low(p);
         uint32_t yk[K][8];
-        const OuterOperand w = outer_operand(g.w.low(p).l, stage), rw = outer_operand(g.w.row_low(p).l, stage);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             uint32_t d[8];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int t = 4 * h + e;
-                const size_t i = t * g.P + p;
-                const int64_t z = g.Z[i];
-                const uint64_t y = g.Y[i];
-                if (z <= -zlim || z >= zlim || y >= (uint64_t)zlim) bad |= 2;
-                __int128 lin = z;
-                uint64_t prod = 1;
+            for (int t = 0; t < 4; ++t) {
+                bad |= e[t].check(g);
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    lin += (__int128)g.base[k] * g.X[k][i];
-                    yk[k][t] = g.Yk[k][i];
-                    if (yk[k][t] >= g.yk_bound) bad |= 2;
-                    prod *= yk[k][t];
-                }
-                if (lin != 0 || prod != y) bad |= 1;
-                long_flip64(d + 2 * e, y);
+                for (int k = 0; k < K; ++k) yk[k][4 * h + t] = e[t].yk[k];
+                long_flip64(d + 2 * t, e[t].y);
+                e[t].load(g, h == 0 ? (4 + t) * g.P + p : t * g.P + next);
+                __builtin_amdgcn_sched_barrier(0);
             }
             const OuterOperand b = outer_stage(d, stage);
             outer_mac(acc[h], w, b);
@@ -258,15 +339,123 @@ static __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per
         const bool row = q >= NW;
         const int value = row ? NV - 8 + 4 * (q - NW) + slot : 4 * q + slot;
         if (!row && value >= NV - 8) return;  // the place the mixed classes leave free
-        fr_store(g.partials, g.pstride, (size_t)blockIdx.x * NV + value, fr_mul(v, row ? g.w.row_high(start) : g.w.high(start)));
+        fr_store(g.partials, g.pstride, (size_t)value * gridDim.x + blockIdx.x, fr_mul(v, row ? g.w.row_high(start) : g.w.high(start)));
     });
+}
+
+// ---- the X^(k) at the final point ------------------------------------------------------------
+//
+// X^(k)~(v) = sum_(i,j) hi_i lo_j X^(k)[4096 i + j], a sum over j for every i.  Bound by HBM: two
+// tensors of 2^24 vectors' entries 223 us, 4.8 TB/s (267 on the vector ALU), of 2^28 integers
+// 410 us, 5.2 TB/s (1475).
+struct LongEvalArgs {
+    const uint32_t* src[3];  // by blockIdx.y
+    size_t stride[3];        // (of vectors)
+    const uint4* lo_ops;
+    const uint32_t* pool;
+    size_t pool_stride;
+    uint32_t hi;
+    uint32_t* partials;      // of tensor k, workgroup b: k gridDim.x + b
+    size_t pstride;
+
+    __device__ __forceinline__ Fr high(size_t i) const { return fr_load(pool, pool_stride, hi + i); }
+    __device__ __forceinline__ void store(const Fr& x) const { fr_store(partials, pstride, (size_t)blockIdx.y * gridDim.x + blockIdx.x, x); }
+};
+
+// Of vectors: a workgroup takes one i.
+static __global__ void __launch_bounds__(kBlock) k_long_eval(LongEvalArgs g) {
+    __shared__ __attribute__((aligned(16))) int sums[2 * 1024];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint8_t* stage = (uint8_t*)sums + wave * kOuterStage;
+    v16i acc[1];
+    outer_clear(acc[0]);
+    constexpr uint32_t share = (1u << kLongLo) / 4;
+    const uint32_t start = wave * share, end = start + share;
+    const uint32_t* const src = g.src[blockIdx.y] + ((size_t)blockIdx.x << kLongLo);
+    const size_t stride = g.stride[blockIdx.y];
+    uint32_t v[2][8];  // asked for two batches ahead
+    outer_load(v[0], src, stride, start);
+    outer_load(v[1], src, stride, start + kOuterBatch);
+#pragma unroll 1
+    for (uint32_t p = start; p < end; p += 2 * kOuterBatch) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const uint32_t at = p + q * kOuterBatch, next = at + 2 * kOuterBatch < end ? at + 2 * kOuterBatch : at;
+            const OuterOperand w = outer_saved(g.lo_ops, at >> 6);
+            uint32_t d[8];
+            balanced_digits(d, v[q]);
+            outer_load(v[q], src, stride, next);
+            __builtin_amdgcn_sched_barrier(0);
+            outer_mac(acc[0], w, outer_stage(d, stage));
+        }
+    }
+    outer_close<1, 32>(acc, sums, [&](int, int, const Fr& x) { g.store(fr_mul(x, g.high(blockIdx.x))); });
+}
+
+// Of integers: the entries of eight values of i at one j are an operand (four digits
+// each, taken as d - 128); a workgroup takes 8 NA values of i.
+template <int NA>
+static __global__ void __launch_bounds__(kBlock) k_long_eval_ints(LongEvalArgs g) {
+    typedef const __attribute__((address_space(1))) uint32_t* global_words;
+    __shared__ __attribute__((aligned(16))) int sums[(NA < 2 ? 2 : NA) * 1024];
+    __shared__ uint32_t rows[8 * NA][8];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint8_t* stage = (uint8_t*)sums + wave * kOuterStage;
+    v16i acc[NA];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) outer_clear(acc[q]);
+    const size_t first = (size_t)blockIdx.x * 8 * NA;
+    const global_words from = (global_words)g.src[blockIdx.y] + (first << kLongLo);
+    constexpr uint32_t share = (1u << kLongLo) / 4;
+    const uint32_t start = wave * share, end = start + share;
+    uint32_t v[NA][8];  // asked for a turn ahead
+    auto load = [&](int q, uint32_t p) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            global_words at = from + (((size_t)8 * q + s) << kLongLo) + p;
+            asm("" : "+s"(at));
+            v[q][s] = at[lane];
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < NA; ++q) load(q, start);
+#pragma unroll 1
+    for (uint32_t p = start; p < end; p += kOuterBatch) {
+        const uint32_t next = p + kOuterBatch < end ? p + kOuterBatch : p;
+        const OuterOperand w = outer_saved(g.lo_ops, p >> 6);
+#pragma unroll
+        for (int q = 0; q < NA; ++q) {
+            uint32_t d[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) d[s] = v[q][s] ^ kFlip;
+            load(q, next);
+            __builtin_amdgcn_sched_barrier(0);
+            outer_mac(acc[q], w, outer_stage(d, stage));
+        }
+    }
+    outer_close<NA, 4>(acc, sums, [&](int q, int slot, const Fr& x) {
+        const Fr f = fr_mul(x, g.high(first + 8 * q + slot));
+#pragma unroll
+        for (int k = 0; k < 8; ++k) rows[8 * q + slot][k] = f.l[k];
+    });
+    __syncthreads();
+    if (wave == 0) {
+        Fr f = fr_zero();
+        if (lane < 8 * NA) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) f.l[k] = rows[lane][k];
+        }
+        f = wave_sum(f);
+        if (lane == 0) g.store(f);
+    }
 }
 
 // ---- folds -----------------------------------------------------------------------------------
 //
 // dst_p = sum_c e_c src_(c P + p), p < P (a multiple of 128).  A wavefront makes 128
 // outputs at a time, the constants' matrices staying in its registers; blockIdx.y is the
-// array.  dst may be src.
+// array.  dst may be src.  Three arrays of 2^24 entries 386 us, 5.2 TB/s; from 2^28 integers
+// (three variables) 1.42 ms, 5.3 TB/s.
 struct LongFoldJob {
     const uint32_t* src;
     size_t ss;

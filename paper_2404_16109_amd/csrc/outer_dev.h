@@ -48,14 +48,33 @@ __device__ __forceinline__ void balanced_digits(uint32_t (&d)[8], const uint32_t
     }
 }
 
-// digits: 32 bytes of this lane's position.
-__device__ __forceinline__ OuterOperand outer_stage(const uint32_t (&digits)[8], uint8_t* stage) {
+// The words of element first + lane (first the same in all lanes, its plane addresses in
+// scalar registers, stepped from one to the next).  Global, not flat, accesses: a flat load
+// also counts as an LDS instruction, so that every wait for staged digits would wait for it.
+__device__ __forceinline__ void outer_load(uint32_t (&v)[8], const uint32_t* p, size_t stride, size_t first) {
+    typedef const __attribute__((address_space(1))) uint32_t* global_words;
+    global_words q = (global_words)p + first;
+    const uint32_t lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        asm("" : "+s"(q));
+        v[k] = q[lane];
+        q += stride;
+    }
+}
+
+// digits: 32 bytes of this lane's position.  A fence of the wavefront's own accesses and
+// no instruction: it keeps the compiler from mixing the lanes' stores with the loads.
+__device__ __forceinline__ void outer_put(const uint32_t (&digits)[8], uint8_t* stage) {
     const int lane = threadIdx.x & 63;
-    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
     *reinterpret_cast<uint4*>(stage + 16 * lane) = make_uint4(digits[0], digits[1], digits[2], digits[3]);
     *reinterpret_cast<uint4*>(stage + 1024 + 16 * lane) = make_uint4(digits[4], digits[5], digits[6], digits[7]);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+}
+
+__device__ __forceinline__ OuterOperand outer_get(const uint8_t* stage) {
+    const int lane = threadIdx.x & 63;
     const uint8_t* at = stage + ((lane >> 4) & 1) * 1024 + (lane >> 5) * 256 + (lane & 15) * 8;
     OuterOperand o;
 #pragma unroll
@@ -65,14 +84,30 @@ __device__ __forceinline__ OuterOperand outer_stage(const uint32_t (&digits)[8],
         const v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i*)(at + 512 * s + 128));
         o.half[s] = v4i{lo.x, lo.y, hi.x, hi.y};
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     return o;
+}
+
+__device__ __forceinline__ OuterOperand outer_stage(const uint32_t (&digits)[8], uint8_t* stage) {
+    outer_put(digits, stage);
+    return outer_get(stage);
 }
 
 __device__ __forceinline__ OuterOperand outer_operand(const uint32_t (&v)[8], uint8_t* stage) {
     uint32_t d[8];
     balanced_digits(d, v);
     return outer_stage(d, stage);
+}
+
+// Operands made beforehand: those of positions 64 b .. 64 b + 63 at table[128 b ..).
+__device__ __forceinline__ void outer_save(uint4* table, size_t b, const OuterOperand& o) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) table[(2 * b + s) * 64 + lane] = make_uint4(o.half[s].x, o.half[s].y, o.half[s].z, o.half[s].w);
+}
+__device__ __forceinline__ OuterOperand outer_saved(const uint4* table, size_t b) {
+    typedef const __attribute__((address_space(1))) v4i* global_v4i;
+    const global_v4i at = (global_v4i)table + 128 * b + (threadIdx.x & 63);
+    return OuterOperand{{at[0], at[64]}};
 }
 
 __device__ __forceinline__ void outer_mac(v16i& acc, const OuterOperand& a, const OuterOperand& b) {
@@ -87,8 +122,8 @@ __device__ __forceinline__ void outer_clear(v16i& acc) {
 
 // The sums of a workgroup of four wavefronts.  `sums`: N * 1024 words of LDS (may
 // overlap the staging areas).  Columns are taken in groups of GROUP lanes, each the
-// digits of one value: 32 (field elements) or 8 (64-bit integers, four to an
-// operand).  Calls out(q, group, x) in one lane for every sum of accumulator q,
+// digits of one value: 32 (field elements), 8 or 4 (64- or 32-bit integers, four or
+// eight to an operand).  Calls out(q, group, x) in one lane for every sum of accumulator q,
 //   x = sum_(i,j) 2^(8 (i + j)) C_ij / 2^256 mod r, reduced.
 // A column sum_i 2^(8 i) C_ij is below 2^(8 31) 256/255 * 2^14 positions < 2^20 r in
 // magnitude for kOuterMaxSpan positions, which is what the bias makes up for.
@@ -132,7 +167,7 @@ __device__ __forceinline__ void outer_close(const v16i (&acc)[N], int* sums, Out
         v = fr_mul(v, pw);
         v = dpp_add_step<0x111, 0xf>(v);
         v = dpp_add_step<0x112, 0xf>(v);
-        v = dpp_add_step<0x114, 0xf>(v);
+        if constexpr (GROUP >= 8) v = dpp_add_step<0x114, 0xf>(v);
         if constexpr (GROUP == 32) {
             v = dpp_add_step<0x118, 0xf>(v);
             v = dpp_add_step<0x142, 0xa>(v);

@@ -520,7 +520,8 @@ struct LongTables {
     uint32_t* pool = nullptr;
     size_t stride = 0;
     uint4* pool29 = nullptr;
-    uint32_t lo = 0, rlo = 0;
+    uint4* lo_ops = nullptr;
+    uint4* rlo_ops = nullptr;
     uint32_t hi[32], rhi[32];  // by the pass's first variable
     int n = 0, nr = 0;
 
@@ -542,6 +543,7 @@ struct LongTables {
         Carver cv(nullptr, 0);
         cv.limbs(entries(n, nr, ints));
         cv.take((size_t)36 << kLongLo);
+        for (int q = 0; q < 2; ++q) cv.take((size_t)32 << kLongLo);
         return cv.used();
     }
     int build(const host::F* u, int n_, int nr_, bool ints, Carver& cv, hipStream_t stream) {
@@ -550,7 +552,9 @@ struct LongTables {
         stride = entries(n, nr, ints);
         pool = cv.limbs(stride);
         pool29 = (uint4*)cv.take((size_t)36 << kLongLo);
-        if (!pool || !pool29) return ZK_E_BUFSZ;
+        lo_ops = (uint4*)cv.take((size_t)32 << kLongLo);
+        rlo_ops = (uint4*)cv.take((size_t)32 << kLongLo);
+        if (!pool || !pool29 || !lo_ops || !rlo_ops) return ZK_E_BUFSZ;
         EqPoolArgs args;
         memset(&args, 0, sizeof args);
         for (int t = 0; t < n; ++t) args.u[t] = to_dev(u[t]);
@@ -563,8 +567,7 @@ struct LongTables {
             off += 1u << nvars;
             return args.offset[q];
         };
-        lo = table(n - kLongLo, kLongLo);
-        rlo = table(n - kLongLo, row_low_vars(n, nr));
+        const uint32_t lo = table(n - kLongLo, kLongLo), rlo = table(n - kLongLo, row_low_vars(n, nr));
         for (int t = 0; n - t > kLinkPassVars; t += link_long_vars(t, ints)) {
             const int v = link_long_vars(t, ints);
             hi[t] = table(t + v, high_vars(n, t, v));
@@ -578,6 +581,8 @@ struct LongTables {
         table(n - kLongLo, kLongLo);
         args.total = off;
         launch_eq_pool(pool, stride, args, stream);
+        hipLaunchKernelGGL(k_long_operands, dim3((1 << kLongLo) / kBlock, 2), dim3(kBlock), 0, stream, pool, stride, lo, rlo,
+                           kLongLo - row_low_vars(n, nr), lo_ops, rlo_ops);
         ZK_HIP_TRY(hipGetLastError());
         return ZK_OK;
     }
@@ -587,13 +592,11 @@ struct LongTables {
         w.pool = pool;
         w.stride = stride;
         w.lo29 = Planes29{pool29, (size_t)1 << kLongLo};
-        w.lo = lo;
-        w.rlo = rlo;
+        w.lo_ops = lo_ops;
+        w.rlo_ops = rlo_ops;
         w.hi = hi[t];
         w.rhi = rhi[t];
-        w.rlo_shift = kLongLo - row_low_vars(n, nr);
         w.rhi_shift = high_vars(n, t, vars) - row_high_vars(n, nr, t, vars);
-        w.lo_mask = (1u << kLongLo) - 1;
         return w;
     }
 };
@@ -667,7 +670,8 @@ static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 static size_t link_proof_len(int n, int K) { return 64 + (size_t)n * (K + 2) * 32 + (size_t)(2 * K + 2) * 32; }
 
-static const int kLinkMleLoBits = 12;  // low table of the final point's weights: up to this many variables
+static const int kLongEvalVars = kLongLo + 3;  // from here on on the matrix cores: eight values of the high index are an operand
+static const int kLinkMleLoBits = kLongLo;  // low table of the final point's weights: up to this many variables
 
 struct LinkWs {
     uint32_t* Y;
@@ -675,6 +679,7 @@ struct LinkWs {
     uint32_t* mle_tables;    // 2^lb + 2^(n - lb) entries, lb = min(n, kLinkMleLoBits)
     uint32_t* mle_partials;  // K 2^(n - lb) entries
     size_t mle_entries;
+    uint4* mle_ops;          // the low table as operands (tensors of kLongEvalVars variables or more)
     uint32_t* partials;
     uint32_t* ticket;
     SmallFoldConsts* fold;  // 2 + K sets of constants of the integer path
@@ -712,6 +717,7 @@ static void carve_link(LinkWs& w, Carver& cv, size_t D, size_t cols, int K) {
         w.mle_entries = ((size_t)1 << lb) + ((size_t)1 << (n - lb));
         w.mle_tables = cv.limbs(w.mle_entries);
         w.mle_partials = cv.limbs((size_t)K << (n - lb));
+        w.mle_ops = n >= kLongEvalVars ? (uint4*)cv.take((size_t)32 << kLongLo) : nullptr;
     }
     w.part_blocks = link_blocks_max(log2_floor(D / cols), log2_floor(cols));
     w.partials = cv.limbs(std::max({w.part_blocks * (K + 5), (size_t)kLinkGridValues * kGridChunks, long_partials(log2_floor(D))}));
@@ -1021,7 +1027,7 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
                 a.pstride = (size_t)blocks * nv;
                 a.bad = bad_word;
                 hipLaunchKernelGGL((k_long_ints<K == 1 ? 1 : 2>), dim3(blocks), dim3(kBlock), 0, stream, a);
-                launch_final_sum(w.partials, a.pstride, blocks, nv, mb->words, mb->words, seq, w.ticket, stream);
+                hipLaunchKernelGGL(k_long_total, dim3(nv), dim3(kBlock), 0, stream, w.partials, a.pstride, blocks, mb->words, mb->words, seq, w.ticket);
             } else {
                 auto vec_of = [&](int q) { return q ? (moved ? fr_vec{w.Yk[q - 1], D / 2, D / 2} : Yk[q - 1]) : moved ? fr_vec{w.Y, D / 2, D / 2} : Y; };
                 fr_vec arrays[4] = {vec_of(0)};
@@ -1031,7 +1037,9 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
                     for (int k = 0; k < K; ++k) arrays[lines++] = X[k];
                 }
                 if (K == 1) arrays[lines++] = vec_of(1);
-                uint32_t* line_partials = w.partials;
+                // the classes' sums first, then those of the lines
+                const int nq = K == 2 ? 9 : 0, nl = 4 * (lines + 1);
+                const size_t pstride = (size_t)blocks * (nq + nl);
                 if (K == 2) {
                     LongGridArgs a;
                     memset(&a, 0, sizeof a);
@@ -1044,11 +1052,9 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
                     a.span = span;
                     a.w = weights;
                     a.partials = w.partials;
-                    a.pstride = (size_t)blocks * 9;
-                    line_partials += 8 * a.pstride;
+                    a.pstride = pstride;
                     hipLaunchKernelGGL(k_long_grid, dim3(blocks), dim3(kBlock), 0, stream, a);
                 }
-                const int nl = 4 * (lines + 1);
                 auto launch_lines = [&](auto args) {
                     for (int q = 0; q < lines; ++q) {
                         args.a[q] = arrays[q].limbs;
@@ -1057,16 +1063,15 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
                     args.P = P;
                     args.span = span;
                     args.w = weights;
-                    args.partials = line_partials;
-                    args.pstride = (size_t)blocks * nl;
+                    args.partials = w.partials + (size_t)blocks * nq;
+                    args.pstride = pstride;
                     return args;
                 };
                 const dim3 grid(blocks, 4);
                 if (lines == 1) hipLaunchKernelGGL(k_long_lines<1>, grid, dim3(kBlock), 0, stream, launch_lines(LongLinesArgs<1>()));
                 else if (lines == 2) hipLaunchKernelGGL(k_long_lines<2>, grid, dim3(kBlock), 0, stream, launch_lines(LongLinesArgs<2>()));
                 else hipLaunchKernelGGL(k_long_lines<4>, grid, dim3(kBlock), 0, stream, launch_lines(LongLinesArgs<4>()));
-                launch_final_sum2(w.partials, (size_t)blocks * 9, K == 2 ? 9 : 0, line_partials, (size_t)blocks * nl, nl, blocks,
-                                  mb->words, mb->words, seq, w.ticket, stream);
+                hipLaunchKernelGGL(k_long_total, dim3(nq + nl), dim3(kBlock), 0, stream, w.partials, pstride, blocks, mb->words, mb->words, seq, w.ticket);
             }
             ZK_HIP_TRY(hipGetLastError());
             ZK_TRY(mailbox_wait(mb, seq, stream));
@@ -1363,7 +1368,29 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
             launch_eq_pool(w.mle_tables, w.mle_entries, ea, stream);
             const EqSplit eq{w.mle_tables, w.mle_entries, 0, 1u << lb, lb, 1};
             const unsigned blocks = 1u << (n - lb);
-            if (small) {
+            seq = mb->next_seq();
+            if (n >= kLongEvalVars) {
+                hipLaunchKernelGGL(k_long_operands, dim3((1 << kLongLo) / kBlock, 1), dim3(kBlock), 0, stream, w.mle_tables, w.mle_entries,
+                                   0u, 0u, 0, w.mle_ops, w.mle_ops);
+                LongEvalArgs a;
+                memset(&a, 0, sizeof a);
+                for (int k = 0; k < K; ++k) {
+                    a.src[k] = small ? small->X[k] : X[k].limbs;
+                    a.stride[k] = small ? 0 : X[k].stride;
+                }
+                a.lo_ops = w.mle_ops;
+                a.pool = w.mle_tables;
+                a.pool_stride = w.mle_entries;
+                a.hi = 1u << lb;
+                a.partials = w.mle_partials;
+                // integers: 32 (8) values of the high index per workgroup
+                const unsigned per = !small ? 1 : n >= kLongLo + 11 ? 32 : 8, groups = blocks / per;
+                a.pstride = (size_t)K * groups;
+                if (!small) hipLaunchKernelGGL(k_long_eval, dim3(groups, K), dim3(kBlock), 0, stream, a);
+                else if (per == 32) hipLaunchKernelGGL(k_long_eval_ints<4>, dim3(groups, K), dim3(kBlock), 0, stream, a);
+                else hipLaunchKernelGGL(k_long_eval_ints<1>, dim3(groups, K), dim3(kBlock), 0, stream, a);
+                hipLaunchKernelGGL(k_long_total, dim3(K), dim3(kBlock), 0, stream, w.mle_partials, a.pstride, groups, mb->words, mb->words, seq, w.ticket);
+            } else if (small) {
                 LinkMleArgs<true> a;
                 memset(&a, 0, sizeof a);
                 for (int k = 0; k < K; ++k) a.src[k] = small->X[k];
@@ -1374,6 +1401,7 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
                 a.partials = w.mle_partials;
                 a.pstride = (size_t)K * blocks;
                 hipLaunchKernelGGL(k_link_mle<true>, dim3(blocks, K), dim3(kBlock), 0, stream, a);
+                launch_final_sum(w.mle_partials, (size_t)K * blocks, blocks, K, mb->words, mb->words, seq, w.ticket, stream);
             } else {
                 LinkMleArgs<false> a;
                 memset(&a, 0, sizeof a);
@@ -1383,15 +1411,16 @@ static int link_prove_k(const uint8_t seed[32], fr_vec Zp, const fr_vec* X, fr_v
                 a.partials = w.mle_partials;
                 a.pstride = (size_t)K * blocks;
                 hipLaunchKernelGGL(k_link_mle<false>, dim3(blocks, K), dim3(kBlock), 0, stream, a);
+                launch_final_sum(w.mle_partials, (size_t)K * blocks, blocks, K, mb->words, mb->words, seq, w.ticket, stream);
             }
-            seq = mb->next_seq();
-            launch_final_sum(w.mle_partials, (size_t)K * blocks, blocks, K, mb->words, mb->words, seq, w.ticket, stream);
             ZK_HIP_TRY(hipGetLastError());
             ZK_TRY(mailbox_wait(mb, seq, stream));
             ZK_HIP_TRY(hipStreamSynchronize(stream));  // everything of this call has left the device
             fin[0] = zero();
             for (int k = 0; k < K; ++k) {
                 fin[1 + k] = from_dev(mb->words + 8 * k);
+                if (small && n >= kLongEvalVars)  // integers times weights in Montgomery form, divided by 2^256, of X - 0x80808080
+                    fin[1 + k] = add(mul(fin[1 + k], two256), from_u64(0x80808080u));
                 fin[0] = sub(fin[0], mul(base[k], fin[1 + k]));
             }
         }
