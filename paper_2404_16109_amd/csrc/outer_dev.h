@@ -120,6 +120,13 @@ __device__ __forceinline__ void outer_clear(v16i& acc) {
     for (int r = 0; r < 16; ++r) acc[r] = 0;
 }
 
+// An operand whose column n is one at every position and whose other columns are zero:
+// outer_mac(acc, x, outer_column(n)) adds up x's digits in column n.
+__device__ __forceinline__ OuterOperand outer_column(int n) {
+    const int v = (int)(threadIdx.x & 31) == n ? 0x01010101 : 0;
+    return OuterOperand{{v4i{v, v, v, v}, v4i{v, v, v, v}}};
+}
+
 // The sums of a workgroup of four wavefronts.  `sums`: N * 1024 words of LDS (may
 // overlap the staging areas).  Columns are taken in groups of GROUP lanes, each the
 // digits of one value: 32 (field elements), 8 or 4 (64- or 32-bit integers, four or
@@ -127,7 +134,9 @@ __device__ __forceinline__ void outer_clear(v16i& acc) {
 //   x = sum_(i,j) 2^(8 (i + j)) C_ij / 2^256 mod r, reduced.
 // A column sum_i 2^(8 i) C_ij is below 2^(8 31) 256/255 * 2^14 positions < 2^20 r in
 // magnitude for kOuterMaxSpan positions, which is what the bias makes up for.
-template <int N, int GROUP, class Out>
+// SUMS: the last accumulator's columns are values by themselves (outer_column): out(N - 1,
+// column, sum_i 2^(8 i) C_ij mod r) for every column.
+template <int N, int GROUP, bool SUMS = false, class Out>
 __device__ __forceinline__ void outer_close(const v16i (&acc)[N], int* sums, Out&& out) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     __syncthreads();
@@ -164,6 +173,11 @@ __device__ __forceinline__ void outer_close(const v16i (&acc)[N], int* sums, Out
         const int at = lane & (GROUP - 1);
 #pragma unroll
         for (int j = 0; j < 8; ++j) pw.l[j] = (at >> 2) == j ? 1u << (8 * (at & 3)) : 0u;
+        const int which = lane < 32 ? q : q + 1;
+        if constexpr (SUMS) {
+            const Fr column = v;
+            if (which == N - 1) out(which, lane & 31, column);
+        }
         v = fr_mul(v, pw);
         v = dpp_add_step<0x111, 0xf>(v);
         v = dpp_add_step<0x112, 0xf>(v);
@@ -172,8 +186,7 @@ __device__ __forceinline__ void outer_close(const v16i (&acc)[N], int* sums, Out
             v = dpp_add_step<0x118, 0xf>(v);
             v = dpp_add_step<0x142, 0xa>(v);
         }
-        const int which = lane < 32 ? q : q + 1;
-        if (which < N && at == GROUP - 1) out(which, (lane & 31) / GROUP, v);
+        if (which < (SUMS ? N - 1 : N) && at == GROUP - 1) out(which, (lane & 31) / GROUP, v);
     }
 }
 

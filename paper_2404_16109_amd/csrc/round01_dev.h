@@ -1,9 +1,8 @@
-// What one thread of the FIRST pass of the tlookup sumcheck computes when that pass
-// serves the first two rounds at once (Section 4, second form of the identity;
-// Section 3.3 for the protocol), as plain functions on 29-bit limbs; the kernel
-// (tlookup_round29.h) adds loads and the sums across lanes.  No device-only
-// construct: the same schedule runs on the host, where it is checked against big
-// integers at its bounds.
+// The FIRST pass of the tlookup sumcheck when it serves the first two rounds at once
+// (Section 4, second form of the identity; Section 3.3 for the protocol): which sums
+// it takes and why they are enough, and its schedule on 29-bit limbs for one thread as
+// plain functions, checked on the host against big integers at its bounds.  The library
+// takes the same sums on the matrix cores (k_round_first_two in tlookup_round29.h).
 //
 // Why one pass is enough for two rounds.  The first round binds x_0, the second
 // x_1.  A "quad" is the four entries of an array whose indices differ in those two

@@ -572,7 +572,7 @@ enum RoundKind {
     kRoundFirst = 0,     // k_round_data0: the first round, nothing to fold
     kRound29 = 1,        // k_round_data29: large folding rounds on 29-bit limbs
     kRoundBoth = 2,      // k_round_both: data and table side, the table's variables being bound
-    kRoundFirstTwo = 5,  // k_round_data01: the first pass, which yields the sums of the first two rounds
+    kRoundFirstTwo = 5,  // k_round_first_two: the first pass, which yields the sums of the first two rounds
     kRoundNoPass = 6,    // the second round after kRoundFirstTwo: the host has everything, nothing is launched
     kRoundHost = 7,      // the host's (HostTail); the first of them fetches the arrays
     kRoundGrid = 8       // its sums come from the grid of a pass over several variables; the first of them runs the pass
@@ -1146,6 +1146,7 @@ static int prove_core(const ProveCall& c) {
     // (tlookup_round29.h).  Between two of them the arrays stay in 29-bit planes,
     // unreduced, for at most kMaxLazyRounds rounds in a row.
     const F29 beta29 = f29_unpack(to_dev(beta).l);
+    const F inv32 = mul(inv2, mul(sqr(inv2), sqr(inv2)));
     // Where local round kk reads and writes the arrays that change place: S comes from
     // the caller's vector until it has been folded once, T likewise, and B alternates
     // between its two buffers on every fold (it has two readers).  b_cur: where B is
@@ -1344,9 +1345,10 @@ static int prove_core(const ProveCall& c) {
                 d01.pstrideD = w.part_blocks * 5;
                 d01.partT = w.partT;
                 d01.pstrideT = w.part_blocks * 6;
+                d01.beta = to_dev(beta);
                 {
                     ProfileScope prof(kProfRoundData, stream);
-                    hipLaunchKernelGGL(k_round_data01, dim3(blocks01), dim3(kBlock), 0, stream, d01);
+                    hipLaunchKernelGGL(k_round_first_two, dim3(blocks01), dim3(kBlock), 0, stream, d01);
                 }
                 launch_final_sum2(w.partD, d01.pstrideD, 5, w.partT, d01.pstrideT, 6, blocks01, I.words, mb->words, my_seq,
                                   w.flags + 1, stream);
@@ -1543,6 +1545,7 @@ static int prove_core(const ProveCall& c) {
                 // the pass has summed, with the NEXT round's weights, what this round and the next are made of
                 // (round01_dev.h): this round's leading coefficient splits by the next variable
                 for (int q = 0; q < 9; ++q) I.pass01[q] = from_dev(sums + 8 * q);
+                for (int q = 0; q < 5; ++q) I.pass01[q] = add(mul(I.pass01[q], inv32), from_u64(q < 4 ? 2 : 4));
                 q0 = q1 = one();
                 qi = add(mul(sub(one(), u[k + 1]), I.pass01[0]), mul(u[k + 1], I.pass01[1]));
                 sA0 = add(I.pass01[5], I.pass01[6]);

@@ -1,6 +1,6 @@
 // Data side of the large rounds of the tlookup sumcheck (Section 4, the second form
 // of the identity; Section 3.3 for the protocol), on 29-bit limbs: the first pass,
-// which serves the first two rounds (k_round_data01, schedule in round01_dev.h), and
+// which serves the first two rounds (k_round_first_two, on the matrix cores), and
 // the large folding rounds (k_round_data29, schedule in round29_dev.h).
 //
 // These kernels move data at close to the rate of a plain copy only if their
@@ -10,13 +10,14 @@
 // weighted entries of A, and the sums q0 = sum w A0 (S0+beta), qinf = sum w (A1-A0)(S1-S0)
 // and sA0 = sum A0; the round's other two sums, q1 and sA1, follow on the host from
 // the running claim and from the previous round's sums of A.  The first of these
-// rounds after k_round_data01 binds two variables at once (FOLD2).
+// rounds after k_round_first_two binds two variables at once (FOLD2).
 //
 // Arrays between such rounds hold 29-bit limbs, normalized but not reduced: every
 // fold adds up to 2 r to the bound on the values (they start below r), which is
 // why at most kMaxLazyRounds folds happen before a round writes fully reduced
 // 32-bit words again.
 #pragma once
+#include "outer_dev.h"
 #include "round01_dev.h"
 #include "round29_dev.h"
 #include "small_dev.h"
@@ -230,68 +231,124 @@ struct DataRound01Args {
     size_t pstrideD;
     uint32_t* partT;
     size_t pstrideT;
+    Fr beta;  // (k_round_first_two)
 };
 
-__device__ __forceinline__ F29 words29_load(const uint32_t* base, size_t stride, size_t i) {
-    uint32_t w[8];
+// The sums are taken on the matrix cores (outer_dev.h).  With X_c = w A_c and S_c the
+// products X_c S_d, c != d, are added up by class,
+//   M_x0 = X_00 S_10 + X_10 S_00,  M_x1 (c, d = 01, 11),  M_0x (00, 01),  M_1x (10, 11),
+//   M_xx = X_00 S_11 + X_11 S_00 + X_01 S_10 + X_10 S_01,
+// and with W_c = sum w A_c and sum w A_c (S_c + beta) = 1 (before any fold)
+//   c20 = 2 - beta (W_00 + W_10) - M_x0,  c21, qd, T likewise with M_x1, M_0x, M_1x,
+//   qe = 4 - beta sum W - M_x0 - M_x1 - M_0x - M_1x + M_xx.
+// partD gets these without the constants 2 and 4 and times 2^5 (w is in the form for two
+// 29-bit products).  On the vector ALU remain four multiplications per quad and A's sums,
+// some 1250 instructions (on the vector ALU alone the pass took 2300, round01_dev.h, and two
+// wavefronts per SIMD kept it 70 % busy); entries are asked for four ahead of their use.
+// Issue and HBM bind about equally: 2^25 entries 760 -> 520 us, 4.1 TB/s; a proof of 2^20
+// entries in all 731 -> 709 us, one of 2^17 524 -> 500.
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) k_round_first_two(DataRound01Args g) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[4 * 5 * kOuterStage];  // per wavefront S's four operands and one of A
+    static_assert(sizeof lds >= 6 * 4096, "outer_close's sums");
+    __shared__ uint32_t vals[9][8];     // M_x0, M_x1, M_0x, M_1x, M_xx, W_00, W_01, W_10, W_11
+    __shared__ uint32_t sums_a[4][4][9];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint8_t* const stage = lds + wave * 5 * kOuterStage;
+    uint8_t* const stage_x = stage + 4 * kOuterStage;
+    v16i acc[6];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = base[k * stride + i];
-    return f29_unpack(w);
-}
-
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) k_round_data01(DataRound01Args g) {
-    __shared__ uint32_t lds[4 * 9 * 9];
-    Round01Sums sums;
-    round01_begin(sums);
-    const size_t start = blockIdx.x * g.block_span;
+    for (int q = 0; q < 6; ++q) outer_clear(acc[q]);
+    F29 sa0 = f29_zero(), sa1 = sa0, sa2 = sa0, sa3 = sa0;
+    const size_t start = blockIdx.x * g.block_span, share = g.block_span / 4, end = start + (wave + 1) * share;
     const size_t lo_mask = ((size_t)1 << g.lbits) - 1;
-    for (size_t p = start + threadIdx.x; p < start + g.block_span; p += kBlock) {
-        // A's entries first and done with before S's are loaded: with both in flight the registers do not suffice
-        Round01Weighted x;
-        {
-            F29 a[4];
+    size_t p = start + wave * share;  // of the wavefront's first lane
+    uint32_t v[4][8];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) a[c] = words29_load(g.A, g.as, p + c * g.quarter);
-            const F29 w = planes29_load(g.weights, g.lo_off + (p & lo_mask));
-            round01_quad_a(sums, a, w, x);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        {
-            F29 s[4];
+    for (int c = 0; c < 4; ++c) outer_load(v[c], g.S, g.ss, c * g.quarter + p);
+#pragma unroll 1
+    for (size_t stop = p; p < end;) {
+        // A's sums are normalized after seven turns: that many additions fit a limb
+        stop = stop + 7 * kOuterBatch < end ? stop + 7 * kOuterBatch : end;
+#pragma unroll 1
+        for (; p < stop; p += kOuterBatch) {
+            const size_t next = p + kOuterBatch < end ? p + kOuterBatch : p;
+            const F29 w = planes29_load(g.weights, g.lo_off + ((p + lane) & lo_mask));
 #pragma unroll
-            for (int c = 0; c < 4; ++c) s[c] = words29_load(g.S, g.ss, p + c * g.quarter);
-            round01_quad_s(sums, s, x);
+            for (int c = 0; c < 4; ++c) {
+                uint32_t d[8];
+                balanced_digits(d, v[c]);
+                outer_put(d, stage + c * kOuterStage);
+                outer_load(v[c], g.A, g.as, c * g.quarter + p);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const F29 a = f29_unpack(v[c]);
+                outer_load(v[c], g.S, g.ss, c * g.quarter + next);
+                F29& sum = c == 0 ? sa0 : c == 1 ? sa1 : c == 2 ? sa2 : sa3;
+                sum = f29_add(sum, a);
+                uint32_t x[8];
+                f29_pack(x, f29_mul(a, w));  // below 1.015 r
+                __builtin_amdgcn_sched_barrier(0);
+                const OuterOperand xo = outer_operand(x, stage_x);
+                outer_mac(acc[5], xo, outer_column(c));
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    if (d == c) continue;
+                    const int cls = (c ^ d) == 2 ? (c & 1) : (c ^ d) == 1 ? 2 + (c >> 1) : 4;
+                    outer_mac(acc[cls], xo, outer_get(stage + d * kOuterStage));
+                }
+            }
         }
+        sa0 = f29_normalize(sa0);
+        sa1 = f29_normalize(sa1);
+        sa2 = f29_normalize(sa2);
+        sa3 = f29_normalize(sa3);
     }
-    F29 tot[9];
-    round01_end(sums, tot);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) {
-        tot[q] = f29_shrink(wave_sum29(tot[q]));  // below 128 r, then below 2.9 r
+    for (int c = 0; c < 4; ++c) {
+        const F29 t = f29_shrink(wave_sum29(f29_shrink(c == 0 ? sa0 : c == 1 ? sa1 : c == 2 ? sa2 : sa3)));  // at most 16 entries per thread, 1024 a wavefront
         if (lane == 0) {
 #pragma unroll
-            for (int k = 0; k < 9; ++k) lds[(wave * 9 + q) * 9 + k] = tot[q].l[k];
+            for (int k = 0; k < 9; ++k) sums_a[wave][c][k] = t.l[k];
         }
     }
-    __syncthreads();
-    if (threadIdx.x < 9) {
-        const int q = threadIdx.x;
-        F29 v = f29_zero();
-        for (int w = 0; w < 4; ++w) {
+    outer_close<6, 32, true>(acc, (int*)lds, [&](int q, int column, const Fr& x) {
+        if (q == 5 && column >= 4) return;
+        const int at = q == 5 ? 5 + column : q;
 #pragma unroll
-            for (int k = 0; k < 9; ++k) v.l[k] += lds[(w * 9 + q) * 9 + k];
+        for (int k = 0; k < 8; ++k) vals[at][k] = x.l[k];
+    });
+    __syncthreads();
+    const int q = threadIdx.x;
+    if (q < 5) {
+        auto value = [&](int i) {
+            Fr f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) f.l[k] = vals[i][k];
+            return f;
+        };
+        // c20: W_00 + W_10, c21: W_01 + W_11, qd: W_00 + W_01, T: W_10 + W_11, qe: all
+        Fr w = q < 2 ? fr_add(value(5 + q), value(7 + q)) : fr_add(value(q == 3 ? 7 : 5), value(q == 3 ? 8 : 6));
+        Fr m = value(q == 4 ? 0 : q);
+        if (q == 4) {
+            w = fr_add(w, fr_add(value(7), value(8)));
+            m = fr_sub(fr_add(fr_add(m, value(1)), fr_add(value(2), value(3))), value(4));
         }
-        Fr out;
-        f29_canonical(out.l, f29_normalize(v));  // below 12 r < 2^261
-        if (q < 5) {
-            if (g.has_hi) out = fr_mul(out, fr_load(g.hi_pool, g.hi_stride, g.hi_off + (start >> g.lbits)));
-            fr_store(g.partD, g.pstrideD, (size_t)blockIdx.x * 5 + q, out);
-        } else {
-            fr_store(g.partT, g.pstrideT, (size_t)blockIdx.x * 6 + (q - 5), out);
+        Fr out = fr_sub(fr_zero(), fr_add(fr_mul(w, g.beta), m));
+        if (g.has_hi) out = fr_mul(out, fr_load(g.hi_pool, g.hi_stride, g.hi_off + (start >> g.lbits)));
+        fr_store(g.partD, g.pstrideD, (size_t)blockIdx.x * 5 + q, out);
+    } else if (q < 11) {
+        Fr out = fr_zero();
+        if (q < 9) {
+            F29 t = f29_zero();
+            for (int s = 0; s < 4; ++s) {
+#pragma unroll
+                for (int k = 0; k < 9; ++k) t.l[k] += sums_a[s][q - 5][k];
+            }
+            f29_canonical(out.l, f29_normalize(t));
         }
-    } else if (threadIdx.x < 11) {
-        fr_store(g.partT, g.pstrideT, (size_t)blockIdx.x * 6 + (threadIdx.x - 5), fr_zero());
+        fr_store(g.partT, g.pstrideT, (size_t)blockIdx.x * 6 + (q - 5), out);
     }
 }
 

@@ -1,0 +1,52 @@
+"""The pass that serves the first two rounds (k_round_first_two): workgroups of 256 to 4096 positions, with and without a
+high weight factor, vectors whose planes start anywhere.  Exact arithmetic: equality with the oracle, or with the proof
+from the integers, whose first rounds are other kernels."""
+import numpy as np
+import pytest
+import torch
+
+from tests.test_gpu_link_long import shifted
+from tests.test_tlookup_plan import FIRST_TWO
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def zk():
+    import paper_2404_16109_amd as zk
+    assert torch.cuda.is_available()
+    return zk
+
+
+@pytest.mark.parametrize("logD,logN", [(17, 3), (17, 8), (18, 4)])
+def test_against_the_oracle(zk, orc, logD, logN):
+    assert zk.zkmi_selftest_tlookup_plan(1 << logD, 1 << logN, 1, False)[1][0][0] == FIRST_TWO
+    rng = np.random.default_rng(logD * 100 + logN)
+    Tb = rng.integers(0, 256, size=(1 << logN, 32), dtype=np.uint8)
+    Tb[:, 31] &= 0x3F
+    Tb[0] = np.frombuffer((0x73eda753299d7d483339d80809a1d80553bda402fffe5bfeffffffff00000000).to_bytes(32, "little"), np.uint8)  # r - 1
+    rows = rng.integers(0, 1 << logN, size=1 << logD)
+    rows[: 1 << (logD - 2)] = 0
+    seed = bytes([logD, logN]) * 16
+    rc, want, _ = orc.tlookup_prove(seed, Tb[rows], Tb)
+    assert rc == 0
+    S, T = shifted(zk, zk.vec_from_bytes(Tb[rows])), zk.vec_from_bytes(Tb)
+    rc, got, _ = zk.tlookup_prove(seed, S, torch.from_numpy(rows.astype(np.int32)).cuda(), T)
+    assert rc == 0 and got == want
+
+
+@pytest.mark.parametrize("logD,logN", [(21, 9), (22, 16), (23, 16), (24, 10)])
+def test_against_the_integers(zk, logD, logN):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(logD)
+    N, D = 1 << logN, 1 << logD
+    tx = torch.arange(N, dtype=torch.int32, device="cuda") - N // 2
+    T = zk.Vec(N)
+    assert zk.fr_from_i32(T, tx) == 0
+    idx = torch.randint(0, N, (D,), generator=g, device="cuda", dtype=torch.int32)
+    S = zk.Vec(D, stride=D + 3)
+    S.data[:, :D] = T.data.index_select(1, idx.long())
+    seed = bytes([logD, logN, 3, 4]) * 8
+    rc, proof, _ = zk.tlookup_prove(seed, S, idx, T)
+    rc_i, from_ints, _ = zk.tlookup_prove_small(seed, tx[idx.long()].contiguous(), None, None, idx, T)
+    assert rc == 0 and rc_i == 0 and from_ints == proof
