@@ -63,6 +63,20 @@ __device__ __forceinline__ void outer_load(uint32_t (&v)[8], const uint32_t* p, 
     }
 }
 
+// The same of the first `count` lanes' elements; the lanes after them read the last of those.
+__device__ __forceinline__ void outer_load_part(uint32_t (&v)[8], const uint32_t* p, size_t stride, size_t first, uint32_t count) {
+    typedef const __attribute__((address_space(1))) uint32_t* global_words;
+    global_words q = (global_words)p + first;
+    uint32_t lane = threadIdx.x & 63;
+    if (lane >= count) lane = count - 1;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        asm("" : "+s"(q));
+        v[k] = q[lane];
+        q += stride;
+    }
+}
+
 // digits: 32 bytes of this lane's position.  A fence of the wavefront's own accesses and
 // no instruction: it keeps the compiler from mixing the lanes' stores with the loads.
 __device__ __forceinline__ void outer_put(const uint32_t (&digits)[8], uint8_t* stage) {

@@ -5,6 +5,7 @@
 #include "internal.h"
 #include "tlookup_kernels.h"
 #include "grid_dev.h"
+#include "outer_dev.h"
 #include "transcript.h"
 
 namespace zkmi {
@@ -362,40 +363,88 @@ __global__ void __launch_bounds__(kBlock) k_colsum_reduce(uint32_t* __restrict__
     if (share == 0 && k < P1) fr_store(a, as, k, acc);
 }
 
-// b[k] = sum_j W[k][j] e[j]; one workgroup per ROWS rows, which share the loads of e;
-// rows D1 <= k < P1 are zero.  The products are added up as 512-bit integers and
-// reduced once per thread: with a reduction for each, this was bound by instruction
-// issue (320 instructions per 32 bytes; 5120 x 5120 elements 290 us, 2.9 TB/s), now
-// it is 202 us, 4.1 TB/s.  Four rows where that leaves some two workgroups per compute unit.
-template <int ROWS>
+// b[k] = sum_j W[k][j] e[j]; rows D1 <= k < P1 are zero.  One workgroup per row: matrices
+// so small that what counts is the length of a workgroup's chain.
+__global__ void __launch_bounds__(kBlock) k_rowdot_short(uint32_t* __restrict__ b, size_t bs, const uint32_t* __restrict__ W,
+                                                         size_t ws, size_t D1, size_t D2, const uint32_t* __restrict__ e,
+                                                         size_t es) {
+    __shared__ uint32_t lds[4 * 8];
+    const size_t k = blockIdx.x;
+    Fr tot[1] = {fr_zero()};
+    if (k < D1) {
+        FrWide acc = fr_wide_zero();
+        for (size_t j = threadIdx.x; j < D2; j += kBlock) fr_wide_mac(acc, fr_load(W, ws, k * D2 + j), fr_load(e, es, j));
+        tot[0] = fr_wide_reduce(acc);
+    }
+    block_sum<1, 4>(tot, lds);
+    if (threadIdx.x == 0) fr_store(b, bs, k, tot[0]);
+}
+
+// The same for longer ones.  A workgroup takes four rows, its
+// wavefronts every fourth batch of 64 columns; the products are added up on the matrix
+// cores (outer_dev.h), 4096 columns between two reductions.  Bound by HBM: 5120 x 5120
+// elements 150 us, 5.6 TB/s (202 with 512-bit sums on the vector ALU, 290 with a reduction for every
+// product).
+static const int kDotRows = 4;
 __global__ void __launch_bounds__(kBlock) k_rowdot(uint32_t* __restrict__ b, size_t bs, const uint32_t* __restrict__ W,
                                                    size_t ws, size_t D1, size_t D2, const uint32_t* __restrict__ e,
                                                    size_t es, size_t P1) {
-    __shared__ uint32_t lds[4 * ROWS * 8];
-    const size_t k = (size_t)blockIdx.x * ROWS;
-    Fr tot[ROWS];
+    __shared__ __attribute__((aligned(16))) int sums[kDotRows * 1024];
+    __shared__ uint32_t tot[kDotRows][8];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint8_t* const stage = (uint8_t*)sums + wave * kOuterStage;
+    const size_t k = (size_t)blockIdx.x * kDotRows;
+    if (threadIdx.x < kDotRows * 8) tot[threadIdx.x >> 3][threadIdx.x & 7] = 0;
+    size_t row[kDotRows];
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) tot[r] = fr_zero();
-    if (k < D1) {
-        FrWide acc[ROWS];
+    for (int r = 0; r < kDotRows; ++r) row[r] = (k + r < D1 ? k + r : D1 - 1) * D2;
+#pragma unroll 1
+    for (size_t j0 = 0; j0 < D2 && k < D1; j0 += kOuterMaxSpan) {
+        const size_t end = D2 - j0 < kOuterMaxSpan ? D2 : j0 + kOuterMaxSpan;
+        v16i acc[kDotRows];
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) acc[r] = fr_wide_zero();
-        for (size_t j = threadIdx.x; j < D2; j += kBlock) {
-            Fr w[ROWS];
+        for (int r = 0; r < kDotRows; ++r) outer_clear(acc[r]);
+        size_t j = j0 + (size_t)wave * kOuterBatch;
+        if (j < end) {
+            auto count = [&](size_t at) { return (uint32_t)(end - at < (size_t)kOuterBatch ? end - at : (size_t)kOuterBatch); };
+            uint32_t v[kDotRows][8], ev[8];  // asked for a turn ahead
+            outer_load_part(ev, e, es, j, count(j));
 #pragma unroll
-            for (int r = 0; r < ROWS; ++r) w[r] = fr_load(W, ws, (k + r < D1 ? k + r : D1 - 1) * D2 + j);
-            const Fr ej = fr_load(e, es, j);
+            for (int r = 0; r < kDotRows; ++r) outer_load_part(v[r], W, ws, row[r] + j, count(j));
+#pragma unroll 1
+            for (; j < end; j += 4 * kOuterBatch) {
+                const size_t next = j + 4 * kOuterBatch < end ? j + 4 * kOuterBatch : j;
+                uint32_t d[8];
+                balanced_digits(d, ev);
+                if ((threadIdx.x & 63) >= count(j)) {
 #pragma unroll
-            for (int r = 0; r < ROWS; ++r) fr_wide_mac(acc[r], w[r], ej);
+                    for (int q = 0; q < 8; ++q) d[q] = 0;
+                }
+                outer_load_part(ev, e, es, next, count(next));
+                __builtin_amdgcn_sched_barrier(0);
+                const OuterOperand w = outer_stage(d, stage);
+#pragma unroll
+                for (int r = 0; r < kDotRows; ++r) {
+                    balanced_digits(d, v[r]);
+                    outer_load_part(v[r], W, ws, row[r] + next, count(next));
+                    __builtin_amdgcn_sched_barrier(0);
+                    outer_mac(acc[r], w, outer_stage(d, stage));
+                }
+            }
         }
+        outer_close<kDotRows, 32>(acc, sums, [&](int r, int, const Fr& x) {
+            Fr t;
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) tot[r] = k + r < D1 ? fr_wide_reduce(acc[r]) : fr_zero();
+            for (int q = 0; q < 8; ++q) t.l[q] = tot[r][q];
+            t = fr_add(t, x);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) tot[r][q] = t.l[q];
+        });
     }
-    block_sum<ROWS, 4>(tot, lds);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r)
-            if (k + r < P1) fr_store(b, bs, k + r, tot[r]);
+    __syncthreads();
+    if (threadIdx.x < kDotRows * 8) {
+        const size_t r = threadIdx.x >> 3, q = threadIdx.x & 7;
+        if (k + r < P1) b[q * bs + k + r] = k + r < D1 ? tot[r][q] : 0u;
     }
 }
 
@@ -668,8 +717,9 @@ static void small_products_run(uint32_t* a, uint32_t* b, size_t PC, const int16_
 
 static void rowdot_run(uint32_t* b, size_t PR, const uint32_t* M, size_t ms, size_t R, size_t C, const uint32_t* e1,
                        size_t e1s, hipStream_t stream) {
-    if (R >= 2048) hipLaunchKernelGGL(k_rowdot<4>, dim3((unsigned)(PR / 4)), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s, PR);
-    else hipLaunchKernelGGL(k_rowdot<1>, dim3((unsigned)PR), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s, PR);
+    // alike at 2000 x 64 (144 us for a whole proof both ways); 100 x 33: 58 and 61, 777 x 1000: 130 and 127, 1000 x 3000: 151 and 145
+    if (R * C < (size_t)1 << 17) hipLaunchKernelGGL(k_rowdot_short, dim3((unsigned)PR), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s);
+    else hipLaunchKernelGGL(k_rowdot, dim3((unsigned)div_up(PR, kDotRows)), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s, PR);
 }
 
 static int dot_run(const uint32_t* x, size_t xs, const uint32_t* y, size_t ys, size_t n, uint32_t* partials,

@@ -1,0 +1,40 @@
+"""The rows' products of a matrix proof on the matrix cores (k_rowdot): a batch of 64 columns that is not full, more columns
+than two reductions lie apart, rows that do not fill a workgroup, a matrix whose planes start anywhere; and the smaller
+matrices beside them.  The proof's verifier recomputes the values from the matrices on other paths; equality with the
+oracle where that is quick."""
+import numpy as np
+import pytest
+import torch
+
+from tests.test_gpu_link_long import shifted
+
+pytestmark = pytest.mark.gpu
+R = 0x73eda753299d7d483339d80809a1d80553bda402fffe5bfeffffffff00000001
+
+
+@pytest.fixture(scope="module")
+def zk():
+    import paper_2404_16109_amd as zk
+    assert torch.cuda.is_available()
+    return zk
+
+
+@pytest.mark.parametrize("D0,D1,D2", [(1, 128, 1024), (2, 257, 511), (3, 33, 4097), (1, 15, 8737), (2, 130, 4096), (1, 131, 1000)])
+def test_against_the_definition(zk, D0, D1, D2):
+    """Rows of the largest field element and of small ones: b_k is read off the proof of a matrix with one row of X per k."""
+    rng = np.random.default_rng(D1 * 10000 + D2)
+    Wb = rng.integers(0, 256, size=(D1 * D2, 32), dtype=np.uint8)
+    Wb[:, 31] &= 0x3F
+    Wb[: D2] = np.frombuffer((R - 1).to_bytes(32, "little"), np.uint8)
+    Xb = rng.integers(0, 256, size=(D0 * D1, 32), dtype=np.uint8)
+    Xb[:, 31] &= 0x3F
+    X, W = zk.vec_from_bytes(Xb), shifted(zk, zk.vec_from_bytes(Wb))
+    seed = bytes([D0, D1 % 251, D2 % 251, 9]) * 8
+    rc, proof = zk.matmul_sumcheck_prove(seed, X, D0, D1, W, D2)
+    assert rc == 0
+    # Y = X W by the definition: the claim is Y~ at the point, recomputed column by column
+    x = [[int.from_bytes(Xb[i * D1 + k].tobytes(), "little") for k in range(D1)] for i in range(D0)]
+    w = [int.from_bytes(Wb[i].tobytes(), "little") for i in range(D1 * D2)]
+    y = [sum(x[i][k] * w[k * D2 + j] for k in range(D1)) % R for i in range(D0) for j in range(D2)]
+    Y = zk.vec_from_bytes(np.frombuffer(b"".join(v.to_bytes(32, "little") for v in y), np.uint8).reshape(-1, 32))
+    assert zk.matmul_sumcheck_verify(seed, proof, D0, D1, D2, Y=Y, X=X, W=W) == 0
