@@ -258,28 +258,57 @@ __global__ void __launch_bounds__(kBlock) k_bi_up_wg(const uint32_t* __restrict_
     }
 }
 
-// Grand total of the last level (n <= THREADS) to total_words (Montgomery limbs).
-template <int THREADS>
-__global__ void __launch_bounds__(THREADS) k_bi_top_total(const uint32_t* __restrict__ src, size_t ss, size_t n,
-                                                          int shifted, Fr shift, uint32_t* total_words,
-                                                          uint32_t* flag_words, uint32_t seq) {
+// The last levels of all inversions of a call, a workgroup each: its chain of eight products
+// is what such a level costs (three inversions one after the other 24 and 38 us, together 8
+// and 13).
+struct BiTop {
+    const uint32_t* src;
+    size_t ss, n;
+    int shifted;
+    uint32_t* total_words;
+    uint32_t* out;
+    size_t os;
+    Fr inv_total;
+};
+template <int NJ>
+struct BiTopArgs {
+    BiTop job[NJ];
+    Fr shift;
+    uint32_t* flag_words;
+    uint32_t* ticket;  // (more than one job)
+    uint32_t seq;
+};
+
+// Grand totals of the last levels (n <= THREADS) to total_words (Montgomery limbs).
+template <int THREADS, int NJ>
+__global__ void __launch_bounds__(THREADS) k_bi_top_total(BiTopArgs<NJ> args) {
     __shared__ uint32_t lds[8 * THREADS];
-    Fr x = threadIdx.x < n ? bi_load(src, ss, threadIdx.x, shifted, shift) : fr_one();
+    const BiTop& g = args.job[NJ == 1 ? 0 : blockIdx.x];
+    Fr x = threadIdx.x < g.n ? bi_load(g.src, g.ss, threadIdx.x, g.shifted, args.shift) : fr_one();
     Fr p = block_scan_mul<THREADS>(x, lds, false);
     if (threadIdx.x == THREADS - 1) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) total_words[k] = p.l[k];
+        for (int k = 0; k < 8; ++k) g.total_words[k] = p.l[k];
         mailbox_written();
-        mailbox_publish(flag_words, seq);
+        if (gridDim.x == 1) {
+            mailbox_publish(args.flag_words, args.seq);
+        } else if (atomicAdd(args.ticket, 1u) == gridDim.x - 1) {
+            *args.ticket = 0;
+            mailbox_publish(args.flag_words, args.seq);
+        }
     }
 }
 
-// out_t = inv_total * (product of the others) for the last level.
-template <int THREADS>
-__global__ void __launch_bounds__(2 * THREADS) k_bi_top_finish(const uint32_t* __restrict__ src, size_t ss, size_t n,
-                                                               int shifted, Fr shift, Fr inv_total, uint32_t* out,
-                                                               size_t os) {
+// out_t = inv_total * (product of the others) for the last levels.
+template <int THREADS, int NJ>
+__global__ void __launch_bounds__(2 * THREADS) k_bi_top_finish(BiTopArgs<NJ> args) {
     __shared__ uint32_t lds[16 * THREADS];
+    const BiTop& g = args.job[NJ == 1 ? 0 : blockIdx.x];
+    const uint32_t* __restrict__ const src = g.src;
+    const size_t ss = g.ss, n = g.n, os = g.os;
+    const int shifted = g.shifted;
+    const Fr shift = args.shift, inv_total = g.inv_total;
+    uint32_t* const out = g.out;
     const int t = threadIdx.x & (THREADS - 1);
     const Fr x = (size_t)t < n ? bi_load(src, ss, t, shifted, shift) : fr_one();
     Fr others = block_scan_both<THREADS>(x, lds);
@@ -361,8 +390,7 @@ bool batch_inverse_can_join(size_t n1, size_t n2) {
 }
 
 int batch_inverse_begin(BatchInverseJob& job, uint32_t* dst, size_t dst_stride, const uint32_t* src, size_t src_stride,
-                        size_t n, const host::F& shift, Carver& cv, uint32_t* total_words, uint32_t* flag_words,
-                        uint32_t seq, hipStream_t stream, uint32_t* dst2, size_t dst2_stride, const uint32_t* src2,
+                        size_t n, const host::F& shift, Carver& cv, uint32_t* total_words, hipStream_t stream, uint32_t* dst2, size_t dst2_stride, const uint32_t* src2,
                         size_t src2_stride, size_t n2) {
     typedef BatchInverseJob::Level Level;
     if (n2 && !batch_inverse_can_join(n, n2)) return ZK_E_BADARG;
@@ -373,6 +401,7 @@ int batch_inverse_begin(BatchInverseJob& job, uint32_t* dst, size_t dst_stride, 
     job.src2_stride = src2_stride;
     job.dst2 = dst2;
     job.dst2_stride = dst2_stride;
+    job.total_words = total_words;
     int shifted0 = host::is_zero(shift) ? 0 : 1;
     job.lv[0] = Level{src, src_stride, dst, dst_stride, n + n2, shifted0};
     while (job.lv[job.depth].n > kBiTopMax) {
@@ -390,27 +419,65 @@ int batch_inverse_begin(BatchInverseJob& job, uint32_t* dst, size_t dst_stride, 
         ++job.depth;
         job.lv[job.depth] = Level{x, m, p, m, m, 0};
     }
-    const Level& top = job.lv[job.depth];
-    hipLaunchKernelGGL(k_bi_top_total<kBlock>, dim3(1), dim3(kBlock), 0, stream, top.x, top.xs, top.n, top.shifted,
-                       job.shift, total_words, flag_words, seq);
     ZK_HIP_TRY(hipGetLastError());
     return ZK_OK;
 }
 
-int batch_inverse_end(const BatchInverseJob& job, const host::F& inv_total, hipStream_t stream) {
+template <int NJ>
+static BiTopArgs<NJ> bi_tops(const BatchInverseJob* const* jobs, int njobs) {
+    BiTopArgs<NJ> args;
+    memset(&args, 0, sizeof args);
+    args.shift = jobs[0]->shift;
+    for (int q = 0; q < njobs; ++q) {
+        const BatchInverseJob::Level& top = jobs[q]->lv[jobs[q]->depth];
+        BiTop& g = args.job[q];
+        g.src = top.x;
+        g.ss = top.xs;
+        g.n = top.n;
+        g.shifted = top.shifted;
+        g.total_words = jobs[q]->total_words;
+        g.out = top.p;
+        g.os = top.ps;
+    }
+    return args;
+}
+
+int batch_inverse_totals(const BatchInverseJob* const* jobs, int njobs, uint32_t* flag_words, uint32_t seq, uint32_t* ticket,
+                         hipStream_t stream) {
+    if (njobs < 1 || njobs > kBatchInverseMaxJobs || (njobs > 1 && !ticket)) return ZK_E_BADARG;
+    const auto launch = [&](auto args) {
+        args.flag_words = flag_words;
+        args.ticket = ticket;
+        args.seq = seq;
+        hipLaunchKernelGGL((k_bi_top_total<kBlock, sizeof args.job / sizeof(BiTop)>), dim3(njobs), dim3(kBlock), 0, stream, args);
+    };
+    if (njobs == 1) launch(bi_tops<1>(jobs, 1));  // (few arguments where few do)
+    else launch(bi_tops<kBatchInverseMaxJobs>(jobs, njobs));
+    ZK_HIP_TRY(hipGetLastError());
+    return ZK_OK;
+}
+
+int batch_inverse_end(const BatchInverseJob* const* jobs, const host::F* inv_totals, int njobs, hipStream_t stream) {
     typedef BatchInverseJob::Level Level;
-    const Level& top = job.lv[job.depth];
-    hipLaunchKernelGGL(k_bi_top_finish<kBlock>, dim3(1), dim3(2 * kBlock), 0, stream, top.x, top.xs, top.n, top.shifted,
-                       job.shift, to_dev(inv_total), top.p, top.ps);
-    for (int d = job.depth - 1; d >= 0; --d) {
-        const Level& cur = job.lv[d];
-        const Level& up = job.lv[d + 1];
-        const unsigned blocks = (unsigned)div_up(cur.n, (size_t)kBlock * kBiK);
-        if (bi_by_workgroups(d, cur.n))
-            bi_launch_wg_level(false, stream, cur, job.shift, up.p, up.ps);
-        else
-            hipLaunchKernelGGL(k_bi_up, dim3(blocks), dim3(kBlock), 0, stream, cur.x, cur.xs, cur.n, cur.shifted, job.shift,
-                               cur.p, cur.ps, up.p, up.ps, cur.p, cur.ps, bi_second_of(job, d));
+    if (njobs < 1 || njobs > kBatchInverseMaxJobs) return ZK_E_BADARG;
+    const auto launch = [&](auto args) {
+        for (int q = 0; q < njobs; ++q) args.job[q].inv_total = to_dev(inv_totals[q]);
+        hipLaunchKernelGGL((k_bi_top_finish<kBlock, sizeof args.job / sizeof(BiTop)>), dim3(njobs), dim3(2 * kBlock), 0, stream, args);
+    };
+    if (njobs == 1) launch(bi_tops<1>(jobs, 1));
+    else launch(bi_tops<kBatchInverseMaxJobs>(jobs, njobs));
+    for (int q = 0; q < njobs; ++q) {
+        const BatchInverseJob& job = *jobs[q];
+        for (int d = job.depth - 1; d >= 0; --d) {
+            const Level& cur = job.lv[d];
+            const Level& up = job.lv[d + 1];
+            const unsigned blocks = (unsigned)div_up(cur.n, (size_t)kBlock * kBiK);
+            if (bi_by_workgroups(d, cur.n))
+                bi_launch_wg_level(false, stream, cur, job.shift, up.p, up.ps);
+            else
+                hipLaunchKernelGGL(k_bi_up, dim3(blocks), dim3(kBlock), 0, stream, cur.x, cur.xs, cur.n, cur.shifted, job.shift,
+                                   cur.p, cur.ps, up.p, up.ps, cur.p, cur.ps, bi_second_of(job, d));
+        }
     }
     ZK_HIP_TRY(hipGetLastError());
     return ZK_OK;
@@ -421,15 +488,18 @@ int batch_inverse_run(uint32_t* dst, size_t dst_stride, const uint32_t* src, siz
     if (n == 0) return ZK_OK;
     BatchInverseJob job;
     uint32_t seq = mb->next_seq();
-    ZK_TRY(batch_inverse_begin(job, dst, dst_stride, src, src_stride, n, shift, cv, mb->words + kMailboxInvA, mb->words,
-                               seq, stream, nullptr, 0, nullptr, 0, 0));
+    ZK_TRY(batch_inverse_begin(job, dst, dst_stride, src, src_stride, n, shift, cv, mb->words + kMailboxInvA,
+                               stream, nullptr, 0, nullptr, 0, 0));
+    const BatchInverseJob* const jobs[1] = {&job};
+    ZK_TRY(batch_inverse_totals(jobs, 1, mb->words, seq, nullptr, stream));
     ZK_TRY(mailbox_wait(mb, seq, stream));
     host::F total = from_dev(mb->words + kMailboxInvA);
     if (host::is_zero(total)) {
         ZK_HIP_TRY(hipStreamSynchronize(stream));  // error codes that depend on data come from an idle stream
         return ZK_E_ZERO_DENOM;
     }
-    return batch_inverse_end(job, host::inv(total), stream);
+    const host::F inv_total = host::inv(total);
+    return batch_inverse_end(jobs, &inv_total, 1, stream);
 }
 
 }  // namespace zkmi

@@ -13,10 +13,12 @@ size_t batch_inverse_scratch_bytes(size_t n);
 int batch_inverse_run(uint32_t* dst, size_t dst_stride, const uint32_t* src, size_t src_stride, size_t n,
                       const host::F& shift, Carver& cv, Mailbox* mb, hipStream_t stream);
 
-// The same in two halves, so that several inversions can share one wait:
-// `begin` runs the down passes and leaves the grand total (Montgomery limbs) at
-// total_words, publishing `seq` if it is not zero; `end` takes the inverse of
-// that total and runs the up passes.
+// The same in parts, so that several inversions (of one shift) can share launches and one
+// wait: `begin` runs an inversion's down passes, `totals` leaves all grand totals
+// (Montgomery limbs) at their total_words and publishes `seq` (`ticket`: one zeroed word
+// of device memory, left zero; may be null for one job), `end` takes the inverses of those
+// totals and runs the up passes.
+static const int kBatchInverseMaxJobs = 16;
 struct BatchInverseJob {
     struct Level {
         const uint32_t* x;
@@ -35,15 +37,17 @@ struct BatchInverseJob {
     size_t src2_stride = 0;
     uint32_t* dst2 = nullptr;
     size_t dst2_stride = 0;
+    uint32_t* total_words = nullptr;
 };
 // src2 (n2 elements, may be none: n2 = 0) is inverted into dst2 by the same passes,
 // shifted like src; needs batch_inverse_can_join(n, n2) and scratch for n + n2 elements.
 bool batch_inverse_can_join(size_t n, size_t n2);
 int batch_inverse_begin(BatchInverseJob& job, uint32_t* dst, size_t dst_stride, const uint32_t* src, size_t src_stride,
-                        size_t n, const host::F& shift, Carver& cv, uint32_t* total_words, uint32_t* flag_words,
-                        uint32_t seq, hipStream_t stream, uint32_t* dst2, size_t dst2_stride, const uint32_t* src2,
+                        size_t n, const host::F& shift, Carver& cv, uint32_t* total_words, hipStream_t stream, uint32_t* dst2, size_t dst2_stride, const uint32_t* src2,
                         size_t src2_stride, size_t n2);
-int batch_inverse_end(const BatchInverseJob& job, const host::F& inv_total, hipStream_t stream);
+int batch_inverse_totals(const BatchInverseJob* const* jobs, int njobs, uint32_t* flag_words, uint32_t seq, uint32_t* ticket,
+                         hipStream_t stream);
+int batch_inverse_end(const BatchInverseJob* const* jobs, const host::F* inv_totals, int njobs, hipStream_t stream);
 
 // ---- sums -----------------------------------------------------------------
 // Partial sums buffer for reductions: up to kMaxPartialBlocks blocks.

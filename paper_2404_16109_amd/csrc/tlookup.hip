@@ -419,25 +419,56 @@ static uint64_t counted_bad(const uint8_t* staged) {
 // Whether the comparison of S with hinted rows can be left to the caller (workgroup histograms in use).
 static bool can_defer_check(const ProveWs& w, const uint32_t* idx, size_t D) { return w.hist && idx && D > (size_t)kBlock; }
 
-// Enqueues the multiplicities into w.m; `staged` (pinned, counted_bytes) receives the
-// rest, and `seq` (not zero) is published once it is there.  Without hints the rows
-// are left in `found`, if the caller wants them.  With defer_check the hints are taken
-// as they are; S_i = T[idx_i] is then checked by the caller.
-static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_t D, size_t N, uint8_t* staged, uint32_t seq,
-                      Mailbox* mb, hipStream_t stream, bool defer_check = false, bool counts_as_fr = false,
-                      uint32_t* found = nullptr) {
-    if (defer_check && !can_defer_check(w, idx, D)) return ZK_E_BADARG;
-    uint32_t cap = w.cap_mask + 1;
-    hipLaunchKernelGGL(k_count_init, dim3(grid_for((size_t)cap + N + 4)), dim3(kBlock), 0, stream, w.slots, (size_t)cap, w.m,
-                       N, w.flags);
-    hipLaunchKernelGGL(k_hash_build, dim3(grid_for(N)), dim3(kBlock), 0, stream, w.slots, w.cap_mask, T.limbs, T.stride,
-                       (uint32_t)N, w.flags);
-    hipLaunchKernelGGL(k_canon_rows, dim3(grid_for(N)), dim3(kBlock), 0, stream, w.canon, w.rows, w.slots, w.cap_mask,
-                       T.limbs, T.stride, (uint32_t)N);
-    if (w.hist) {
+// One tensor's counting.
+struct CountJob {
+    ProveWs* w;
+    fr_vec S;
+    const uint32_t* idx;
+    fr_vec T;
+    size_t D, N;
+    uint8_t* staged;   // pinned, counted_bytes: receives the digests of m's leaves and the flags
+    bool defer_check;  // the hints are taken as they are; S_i = T[idx_i] is then checked by the caller
+    uint32_t* found;   // without hints the rows are left here, if the caller wants them
+};
+
+static TableJob table_job(const ProveWs& w, const fr_vec& T, size_t N) {
+    return TableJob{T.limbs, T.stride, (uint32_t)N, w.slots, w.cap_mask, w.flags, w.canon, w.rows, w.m, w.hist, w.hist_parts, w.M, w.B, nullptr};
+}
+
+// Enqueues the multiplicities of up to kMaxTables tensors into their w.m; `seq` (not zero)
+// is published once all that they stage is there.
+template <int NT>
+static int count_rows_of(const CountJob* jobs, int njobs, uint32_t seq, Mailbox* mb, hipStream_t stream, bool counts_as_fr) {
+    TableJobs<NT> tables{};
+    LeafDigestArgs<NT> lf{};
+    size_t most = 0;
+    uint32_t most_leaves = 0, most_parts = 0;
+    for (int q = 0; q < njobs; ++q) {
+        const CountJob& j = jobs[q];
+        if (j.defer_check && !can_defer_check(*j.w, j.idx, j.D)) return ZK_E_BADARG;
+        tables.job[q] = table_job(*j.w, j.T, j.N);
+        lf.job[q] = LeafDigestJob{(uint32_t*)(j.staged + 16), j.w->m, (uint32_t)j.N, j.w->nleaves, j.w->flags, (uint32_t*)j.staged};
+        most = std::max(most, j.N);
+        most_leaves = std::max(most_leaves, j.w->nleaves);
+        most_parts = std::max(most_parts, j.w->hist_parts);
+    }
+    const unsigned ny = (unsigned)njobs;
+    hipLaunchKernelGGL(k_count_init<NT>, dim3(grid_for(hash_capacity(most) + most + 4), ny), dim3(kBlock), 0, stream, tables);
+    hipLaunchKernelGGL(k_hash_build<NT>, dim3(grid_for(most), ny), dim3(kBlock), 0, stream, tables);
+    hipLaunchKernelGGL(k_canon_rows<NT>, dim3(grid_for(most), ny), dim3(kBlock), 0, stream, tables);
+    for (int q = 0; q < njobs; ++q) {
+        const CountJob& j = jobs[q];
+        const ProveWs& w = *j.w;
+        const uint32_t* idx = j.idx;
+        if (!w.hist) {
+            hipLaunchKernelGGL(k_count, dim3(grid_for(j.D, kBlock, 8192)), dim3(kBlock), 0, stream, w.m, j.S.limbs, j.S.stride, j.D,
+                               idx, j.T.limbs, j.T.stride, w.rows, (uint32_t)j.N, w.slots, w.cap_mask, w.canon, w.flags,
+                               (unsigned long long*)(w.flags + 2));
+            continue;
+        }
         // LDS histograms: every workgroup takes a contiguous share of S
         static thread_local bool lds_limit_raised = false;
-        const size_t lds_bytes = ((N + 1) / 2) * 4;
+        const size_t lds_bytes = ((j.N + 1) / 2) * 4;
         if (!lds_limit_raised) {
             ZK_HIP_TRY(hipFuncSetAttribute((const void*)k_count_lds<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)(((kLdsHistMaxRows + 1) / 2) * 4)));
@@ -446,36 +477,43 @@ static int count_rows(ProveWs& w, fr_vec S, const uint32_t* idx, fr_vec T, size_
             lds_limit_raised = true;
         }
         // equal chunks, as few passes per workgroup as the 16-bit counters allow
-        const size_t passes = div_up(div_up(D, w.hist_parts), (size_t)kHistPass);
-        const size_t per_block = align_up(div_up(D, w.hist_parts * passes), kHistThreads);
-        const bool find = !idx && found;
+        const size_t passes = div_up(div_up(j.D, w.hist_parts), (size_t)kHistPass);
+        const size_t per_block = align_up(div_up(j.D, w.hist_parts * passes), kHistThreads);
+        const bool find = !idx && j.found;
         if (find) {
-            hipLaunchKernelGGL(k_find_rows, dim3((unsigned)div_up(D, kBlock)), dim3(kBlock), 0, stream, found, S.limbs, S.stride, D,
-                               w.rows, (uint32_t)N, w.slots, w.cap_mask, (unsigned long long*)(w.flags + 2));
-            idx = found;
+            hipLaunchKernelGGL(k_find_rows, dim3((unsigned)div_up(j.D, kBlock)), dim3(kBlock), 0, stream, j.found, j.S.limbs, j.S.stride, j.D,
+                               w.rows, (uint32_t)j.N, w.slots, w.cap_mask, (unsigned long long*)(w.flags + 2));
+            idx = j.found;
         }
-        if (defer_check || find)
+        if (j.defer_check || find)
             hipLaunchKernelGGL(k_count_lds<false>, dim3(w.hist_parts), dim3(kHistThreads), lds_bytes, stream, w.m, w.hist,
-                               S.limbs, S.stride, D, per_block, idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots,
+                               j.S.limbs, j.S.stride, j.D, per_block, idx, j.T.limbs, j.T.stride, w.rows, (uint32_t)j.N, w.slots,
                                w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2));
         else
             hipLaunchKernelGGL(k_count_lds<true>, dim3(w.hist_parts), dim3(kHistThreads), lds_bytes, stream, w.m, w.hist,
-                               S.limbs, S.stride, D, per_block, idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots,
+                               j.S.limbs, j.S.stride, j.D, per_block, idx, j.T.limbs, j.T.stride, w.rows, (uint32_t)j.N, w.slots,
                                w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2));
-        const uint32_t group = 16;
-        hipLaunchKernelGGL(k_hist_reduce, dim3((unsigned)div_up(N, kBlock), (unsigned)div_up(w.hist_parts, group)),
-                           dim3(kBlock), 0, stream, w.m, w.hist, w.hist_parts, group, (uint32_t)N);
-    } else {
-        hipLaunchKernelGGL(k_count, dim3(grid_for(D, kBlock, 8192)), dim3(kBlock), 0, stream, w.m, S.limbs, S.stride, D,
-                           idx, T.limbs, T.stride, w.rows, (uint32_t)N, w.slots, w.cap_mask, w.canon, w.flags,
-                           (unsigned long long*)(w.flags + 2));
     }
-    LeafDigestArgs lf{(uint32_t*)(staged + 16), w.m, (uint32_t)N, w.nleaves, w.flags, (uint32_t*)staged, mb->words, w.flags + 1, seq};
-    hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(w.nleaves, 64)), dim3(128), 0, stream, lf);
+    if (most_parts) {
+        const uint32_t group = 16;
+        size_t rows = 0;  // of the tables that have histograms
+        for (int q = 0; q < njobs; ++q)
+            if (jobs[q].w->hist) rows = std::max(rows, jobs[q].N);
+        hipLaunchKernelGGL(k_hist_reduce<NT>, dim3((unsigned)div_up(rows, kBlock), (unsigned)div_up(most_parts, group), ny), dim3(kBlock), 0,
+                           stream, tables, group);
+    }
+    lf.words = mb->words;
+    lf.ticket = jobs[0].w->flags + 1;
+    lf.seq = seq;
+    hipLaunchKernelGGL(k_leaf_digests<NT>, dim3((unsigned)div_up(most_leaves, 64), ny), dim3(128), 0, stream, lf);
     // the counts as field elements (w.M), while the host is busy with the digest
-    if (counts_as_fr) hipLaunchKernelGGL(k_counts_to_fr, dim3(grid_for(N)), dim3(kBlock), 0, stream, w.M, N, w.m, N);
+    if (counts_as_fr) hipLaunchKernelGGL(k_counts_to_fr<NT>, dim3(grid_for(most), ny), dim3(kBlock), 0, stream, tables);
     ZK_HIP_TRY(hipGetLastError());
     return ZK_OK;
+}
+static int count_rows(const CountJob* jobs, int njobs, uint32_t seq, Mailbox* mb, hipStream_t stream, bool counts_as_fr = false) {
+    return njobs == 1 ? count_rows_of<1>(jobs, 1, seq, mb, stream, counts_as_fr)
+                      : count_rows_of<kMaxTables>(jobs, njobs, seq, mb, stream, counts_as_fr);
 }
 
 static void digest_of_leaves(uint8_t out[32], const uint8_t* leaves, uint32_t nleaves) {
@@ -888,15 +926,16 @@ static int prove_core(const ProveCall& c) {
         ZK_TRY(mailbox_bulk(mb, total));
         uint8_t* const staged = mb->bulk + kBulkDigests;
         const uint32_t seq = mb->next_seq();
+        CountJob counts[kMailboxMaxInstances];
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
             // with hints, S_i = T[idx_i] is checked while A is made and hashed; all instances or none, so that the first
             // instance at fault is the one reported
             I.gather = c.by_rows || gather_by_default(I.N);
             I.deferred = defer_all && I.gather;
-            ZK_TRY(count_rows(I.w, I.S, I.idx, I.T, I.D, I.N, staged + at[i], i + 1 == K ? seq : 0, mb, stream, I.deferred, true,
-                              I.idx ? nullptr : I.w.found));
+            counts[i] = CountJob{&I.w, I.S, I.idx, I.T, I.D, I.N, staged + at[i], I.deferred, I.idx ? nullptr : I.w.found};
         }
+        ZK_TRY(count_rows(counts, (int)K, seq, mb, stream, true));
         ZK_TRY(mailbox_wait(mb, seq, stream));
         for (size_t i = 0; i < K; ++i) {
             const uint64_t bad = counted_bad(staged + at[i]);
@@ -943,28 +982,28 @@ static int prove_core(const ProveCall& c) {
         ProfileScope prof(kProfInverse, stream);
         Carver inv_cv = cv;
         const uint32_t seq = mb->next_seq();
-        BatchInverseJob* jobs[2 * kMailboxMaxInstances];
+        const BatchInverseJob* jobs[2 * kMailboxMaxInstances];
         const uint32_t* totals[2 * kMailboxMaxInstances];
         size_t njobs = 0;
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
             const size_t D = I.D, N = I.N;
-            const uint32_t last = i + 1 == K ? seq : 0;
             const bool joined = !I.gather && batch_inverse_can_join(D, N);
             if (!joined) {
-                ZK_TRY(batch_inverse_begin(I.job_b, I.w.B, N, I.T.limbs, I.T.stride, N, beta, inv_cv, I.inv_words, mb->words,
-                                           I.gather ? last : 0, stream, nullptr, 0, nullptr, 0, 0));
+                ZK_TRY(batch_inverse_begin(I.job_b, I.w.B, N, I.T.limbs, I.T.stride, N, beta, inv_cv, I.inv_words, stream,
+                                           nullptr, 0, nullptr, 0, 0));
                 jobs[njobs] = &I.job_b;
                 totals[njobs++] = I.inv_words;
             }
             if (!I.gather) {
                 ZK_TRY(batch_inverse_begin(I.job_a, I.w.A, D, I.S.limbs, I.S.stride, D, beta, inv_cv, I.inv_words + 8,
-                                           mb->words, last, stream, joined ? I.w.B : nullptr, N, I.T.limbs, I.T.stride,
+                                           stream, joined ? I.w.B : nullptr, N, I.T.limbs, I.T.stride,
                                            joined ? N : 0));
                 jobs[njobs] = &I.job_a;
                 totals[njobs++] = I.inv_words + 8;
             }
         }
+        ZK_TRY(batch_inverse_totals(jobs, (int)njobs, mb->words, seq, inst[0].w.flags + 1, stream));
         ZK_TRY(mailbox_wait(mb, seq, stream));
         // inverse of each total from one inversion of their product
         F tot[2 * kMailboxMaxInstances], pre[2 * kMailboxMaxInstances + 1];
@@ -979,14 +1018,20 @@ static int prove_core(const ProveCall& c) {
         }
         F suffix_inv = inv(pre[njobs]);  // 1 / (tot_0 ... tot_q) while walking down
         for (size_t q = njobs; q-- > 0;) {
-            F inv_q = mul(suffix_inv, pre[q]);
+            pre[q] = mul(suffix_inv, pre[q]);
             suffix_inv = mul(suffix_inv, tot[q]);
-            ZK_TRY(batch_inverse_end(*jobs[q], inv_q, stream));
         }
-        for (size_t i = 0; i < K; ++i)
-            if (inst[i].gather)
-                hipLaunchKernelGGL(k_rows_of, dim3(grid_for(inst[i].N)), dim3(kBlock), 0, stream, inst[i].w.rows_b, inst[i].w.B,
-                                   inst[i].N, (uint32_t)inst[i].N);
+        ZK_TRY(batch_inverse_end(jobs, pre, (int)njobs, stream));
+        TableJobs<kMaxTables> tables{};
+        size_t rows = 0;
+        for (size_t i = 0; i < K; ++i) {
+            tables.job[i] = table_job(inst[i].w, inst[i].T, inst[i].N);
+            if (!inst[i].gather) continue;
+            tables.job[i].rows_b = inst[i].w.rows_b;
+            rows = std::max(rows, inst[i].N);
+        }
+        if (rows && K == 1) hipLaunchKernelGGL(k_rows_of<1>, dim3(grid_for(rows)), dim3(kBlock), 0, stream, TableJobs<1>{{tables.job[0]}});
+        else if (rows) hipLaunchKernelGGL(k_rows_of<kMaxTables>, dim3(grid_for(rows), (unsigned)K), dim3(kBlock), 0, stream, tables);
         ZK_HIP_TRY(hipGetLastError());
     }
 
@@ -1055,31 +1100,37 @@ static int prove_core(const ProveCall& c) {
     // c1 = sum_j e'_j B_j (T_j+beta), c2 = sum_j m_j B_j.  e' = e~(u_[h:], .) is the
     // weight table of "round h-1" (remaining variables h .. n-1); with h = 0 no
     // round needs the constant, only c2 is reported.
-    for (size_t i = 0; i < K; ++i) {
-        Instance& I = inst[i];
-        const size_t N = I.N;
-        const int h = I.h;
-        const EqPool& ep = *I.ep;
-        TableConstArgs a;
-        a.B = I.w.B; a.bs = N;
-        a.T = I.T.limbs; a.ts = I.T.stride;
-        a.M = I.w.M; a.ms = N;
-        a.N = N;
-        a.beta = to_dev(beta);
-        if (h >= 1) {
-            a.eq = ep.round(h - 1);
-        } else {
-            // weights unused for the reported sum; point at the one-entry table
-            a.eq = EqSplit{ep.pool, ep.stride, ep.suffix_off[0], 0, 0, 0};
+    {
+        TableConstJobs<kMaxTables> jobs;
+        memset(&jobs, 0, sizeof jobs);
+        jobs.beta = to_dev(beta);
+        unsigned blocks = 1;
+        for (size_t i = 0; i < K; ++i) {
+            const Instance& I = inst[i];
+            const EqPool& ep = *I.ep;
+            TableConstArgs& a = jobs.job[i];
+            a.B = I.w.B; a.bs = I.N;
+            a.T = I.T.limbs; a.ts = I.T.stride;
+            a.M = I.w.M; a.ms = I.N;
+            a.N = I.N;
+            if (I.h >= 1) {
+                a.eq = ep.round(I.h - 1);
+            } else {
+                // weights unused for the reported sum; point at the one-entry table
+                a.eq = EqSplit{ep.pool, ep.stride, ep.suffix_off[0], 0, 0, 0};
+            }
+            // the instances' partial sums side by side: value 2 i + q of a workgroup
+            a.partials = inst[0].w.partT + 2 * i;
+            a.pstride = inst[0].w.part_blocks * 6;
+            a.bad = I.w.flags + 2;
+            a.bad_words = mb->words + kMailboxBad + 2 * i;
+            blocks = std::max(blocks, grid_for(I.N, kBlock, kMaxPartialBlocks / 4));
         }
-        a.partials = I.w.partT;
-        a.pstride = I.w.part_blocks * 6;
-        a.bad = I.w.flags + 2;
-        a.bad_words = mb->words + kMailboxBad + 2 * i;
-        unsigned blocks = grid_for(N, kBlock * 4, kMaxPartialBlocks);
-        hipLaunchKernelGGL(k_table_const, dim3(blocks), dim3(kBlock), 0, stream, a);
+        jobs.values = 2 * (uint32_t)K;
+        if (K == 1) hipLaunchKernelGGL(k_table_const<1>, dim3(blocks), dim3(kBlock), 0, stream, TableConstJobs<1>{{jobs.job[0]}, jobs.beta, jobs.values});
+        else hipLaunchKernelGGL(k_table_const<kMaxTables>, dim3(blocks, (unsigned)K), dim3(kBlock), 0, stream, jobs);
         // read back together with the first round's sums (or the final values)
-        launch_final_sum(I.w.partT, a.pstride, blocks, 2, I.const_words, mb->words, 0, I.w.flags + 1, stream);
+        launch_final_sum(inst[0].w.partT, inst[0].w.part_blocks * 6, blocks, 2 * (int)K, inst[0].const_words, mb->words, 0, inst[0].w.flags + 1, stream);
         ZK_HIP_TRY(hipGetLastError());
     }
     bool table_consts_read = false;
@@ -1866,9 +1917,14 @@ static int verify_core(const VerifyCall& c) {
         const int job_b = have_b ? add_job(wit->B.limbs, wit->B.stride, l, vt) : -1;
         int job_m = -1;
         if (have_m) {
-            hipLaunchKernelGGL(k_counts_to_fr, dim3(grid_for(N)), dim3(kBlock), 0, stream, Mfr, N, wit->m, N);
-            LeafDigestArgs lf{(uint32_t*)(mb->bulk + kBulkDigests), wit->m, (uint32_t)N, nleaves, nullptr, nullptr, nullptr, nullptr, 0};
-            hipLaunchKernelGGL(k_leaf_digests, dim3((unsigned)div_up(nleaves, 64)), dim3(128), 0, stream, lf);
+            TableJobs<1> tables{};
+            tables.job[0].N = (uint32_t)N;
+            tables.job[0].m = const_cast<uint32_t*>(wit->m);  // only read
+            tables.job[0].M = Mfr;
+            hipLaunchKernelGGL(k_counts_to_fr<1>, dim3(grid_for(N)), dim3(kBlock), 0, stream, tables);
+            LeafDigestArgs<1> lf{};
+            lf.job[0] = LeafDigestJob{(uint32_t*)(mb->bulk + kBulkDigests), wit->m, (uint32_t)N, nleaves, nullptr, nullptr};
+            hipLaunchKernelGGL(k_leaf_digests<1>, dim3((unsigned)div_up(nleaves, 64)), dim3(128), 0, stream, lf);
             job_m = add_job(Mfr, N, l, vt);
         }
         {
@@ -1950,7 +2006,8 @@ int tlookup_multiplicities(uint32_t* m, fr_vec S, const uint32_t* idx, fr_vec T,
     ZK_TRY(mailbox_bulk(mb, counted_bytes(w)));
     const uint8_t* const staged = mb->bulk + kBulkDigests;
     const uint32_t seq = mb->next_seq();
-    ZK_TRY(count_rows(w, S, idx, T, D, N, mb->bulk + kBulkDigests, seq, mb, as_stream(stream)));
+    const CountJob job{&w, S, idx, T, D, N, mb->bulk + kBulkDigests, false, nullptr};
+    ZK_TRY(count_rows(&job, 1, seq, mb, as_stream(stream)));
     ZK_TRY(mailbox_wait(mb, seq, as_stream(stream)));
     const uint64_t bad = counted_bad(staged);
     if (bad != UINT64_MAX) {

@@ -27,13 +27,46 @@ __device__ __forceinline__ uint32_t fr_hash(const Fr& a) {
     return h ^ (h >> 15);
 }
 
+// What the kernels that work on tables need of each; blockIdx.y is the table.  The tables of
+// a call share launches: three short ones took three times as long one after the other
+// (counting and inverse of three tables of 2^10 to 2^16 rows: XXX us).
+struct TableJob {
+    const uint32_t* T;
+    size_t ts;
+    uint32_t N;
+    uint32_t* slots;    // hash of T
+    uint32_t cap_mask;
+    uint32_t* flags;
+    uint32_t* canon;
+    uint4* rows;
+    uint32_t* m;        // counts
+    const uint32_t* hist;  // the workgroups' histograms
+    uint32_t hist_parts;   // (none: zero)
+    uint32_t* M;        // counts as field elements
+    const uint32_t* B;
+    uint4* rows_b;      // null: B's rows are not asked for
+};
+// (Calls with one table pass one, whose pointers the compiler can see to be global: through
+// an array they are flat, and flat loads share a counter with the LDS; the counts' leaves
+// took 28 instead of 25 us.)
+static const int kMaxTables = 8;
+template <int NT>
+struct TableJobs {
+    TableJob job[NT];
+};
+
 // Every row j claims the first slot of its probe sequence that is empty or holds
 // a row with the same value; equal values meet in one slot and the lowest row
 // wins.  Slots never empty again and the value class of a slot never changes, so
 // all rows of one value walk the same sequence to the same slot.
-static __global__ void __launch_bounds__(kBlock) k_hash_build(uint32_t* slots, uint32_t cap_mask,
-                                                       const uint32_t* __restrict__ T, size_t ts, uint32_t N,
-                                                       uint32_t* dup_flag) {
+template <int NT>
+static __global__ void __launch_bounds__(kBlock) k_hash_build(TableJobs<NT> tables) {
+    const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.y];
+    uint32_t* const slots = g.slots;
+    const uint32_t* __restrict__ const T = g.T;
+    uint32_t* const dup_flag = g.flags;
+    const uint32_t cap_mask = g.cap_mask, N = g.N;
+    const size_t ts = g.ts;
     for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < N; j += gridDim.x * kBlock) {
         Fr v = fr_load(T, ts, j);
         uint32_t pos = fr_hash(v) & cap_mask;
@@ -83,9 +116,15 @@ __device__ __forceinline__ uint32_t hash_find_rows(const uint32_t* __restrict__ 
 // canon[j] = lowest row with the value of row j; rows[j] = row j of T as eight
 // consecutive words, so that a lookup by row number is one 32-byte access
 // instead of eight accesses to eight limb planes.
-static __global__ void __launch_bounds__(kBlock) k_canon_rows(uint32_t* __restrict__ canon, uint4* __restrict__ rows,
-                                                       const uint32_t* __restrict__ slots, uint32_t cap_mask,
-                                                       const uint32_t* __restrict__ T, size_t ts, uint32_t N) {
+template <int NT>
+static __global__ void __launch_bounds__(kBlock) k_canon_rows(TableJobs<NT> tables) {
+    const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.y];
+    uint32_t* __restrict__ const canon = g.canon;
+    uint4* __restrict__ const rows = g.rows;
+    const uint32_t* __restrict__ const slots = g.slots;
+    const uint32_t* __restrict__ const T = g.T;
+    const uint32_t cap_mask = g.cap_mask, N = g.N;
+    const size_t ts = g.ts;
     for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < N; j += gridDim.x * kBlock) {
         Fr v = fr_load(T, ts, j);
         canon[j] = hash_find(slots, cap_mask, T, ts, v);
@@ -343,8 +382,12 @@ k_count_lds(uint32_t* m, uint32_t* __restrict__ part, const uint32_t* __restrict
 // m[j] += sum over workgroups of their histograms; blockIdx.y selects a group of
 // `group` histograms, so that the additions of one row are spread over several
 // threads.
-static __global__ void __launch_bounds__(kBlock) k_hist_reduce(uint32_t* __restrict__ m, const uint32_t* __restrict__ part,
-                                                        uint32_t nparts, uint32_t group, uint32_t N) {
+template <int NT>
+static __global__ void __launch_bounds__(kBlock) k_hist_reduce(TableJobs<NT> tables, uint32_t group) {
+    const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.z];
+    uint32_t* __restrict__ const m = g.m;
+    const uint32_t* __restrict__ const part = g.hist;
+    const uint32_t nparts = g.hist_parts, N = g.N;
     uint32_t j = blockIdx.x * kBlock + threadIdx.x;
     if (j >= N) return;
     uint32_t b0 = blockIdx.y * group, b1 = b0 + group < nparts ? b0 + group : nparts;
@@ -356,8 +399,13 @@ static __global__ void __launch_bounds__(kBlock) k_hist_reduce(uint32_t* __restr
 // Row j of B as sixteen consecutive words, so that reading it by number is one
 // 64-byte access: the element, then its canonical value as the hash takes it
 // (big-endian bytes of little-endian words).
-static __global__ void __launch_bounds__(kBlock) k_rows_of(uint4* __restrict__ rows, const uint32_t* __restrict__ B,
-                                                    size_t bs, uint32_t N) {
+template <int NT>
+static __global__ void __launch_bounds__(kBlock) k_rows_of(TableJobs<NT> tables) {
+    const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.y];
+    uint4* __restrict__ const rows = g.rows_b;
+    const uint32_t* __restrict__ const B = g.B;
+    const uint32_t N = rows ? g.N : 0;
+    const size_t bs = g.N;
     for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < N; j += gridDim.x * kBlock) {
         const Fr v = fr_load(B, bs, j);
         Fr c = fr_from_mont(v);
@@ -373,8 +421,13 @@ static __global__ void __launch_bounds__(kBlock) k_rows_of(uint4* __restrict__ r
 
 // What counting starts from, in one launch: empty hash slots, zero counts, and the
 // four flag words (duplicate flag and ticket zero, smallest bad index all ones).
-static __global__ void __launch_bounds__(kBlock) k_count_init(uint32_t* __restrict__ slots, size_t cap,
-                                                       uint32_t* __restrict__ m, size_t N, uint32_t* __restrict__ flags) {
+template <int NT>
+static __global__ void __launch_bounds__(kBlock) k_count_init(TableJobs<NT> tables) {
+    const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.y];
+    uint32_t* __restrict__ const slots = g.slots;
+    uint32_t* __restrict__ const m = g.m;
+    uint32_t* __restrict__ const flags = g.flags;
+    const size_t cap = (size_t)g.cap_mask + 1, N = g.N;
     const size_t total = cap + N + 4;
     for (size_t i = blockIdx.x * (size_t)kBlock + threadIdx.x; i < total; i += (size_t)gridDim.x * kBlock) {
         if (i < cap) slots[i] = kEmptySlot;
@@ -383,10 +436,11 @@ static __global__ void __launch_bounds__(kBlock) k_count_init(uint32_t* __restri
     }
 }
 
-static __global__ void __launch_bounds__(kBlock) k_counts_to_fr(uint32_t* __restrict__ dst, size_t ds,
-                                                         const uint32_t* __restrict__ m, size_t N) {
-    for (size_t j = blockIdx.x * (size_t)kBlock + threadIdx.x; j < N; j += (size_t)gridDim.x * kBlock)
-        fr_store(dst, ds, j, fr_from_u32(m[j]));
+template <int NT>
+static __global__ void __launch_bounds__(kBlock) k_counts_to_fr(TableJobs<NT> tables) {
+    const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.y];
+    for (size_t j = blockIdx.x * (size_t)kBlock + threadIdx.x; j < g.N; j += (size_t)gridDim.x * kBlock)
+        fr_store(g.M, g.N, j, fr_from_u32(g.m[j]));
 }
 
 // ---- SHA-256 of the leaves of m ---------------------------------------------------
@@ -425,23 +479,30 @@ __device__ __forceinline__ void sha256_piped_rounds(uint32_t (&h)[8], const uint
 // host memory, and behind them the flag words of the counting (flags not null).  A leaf
 // is nine dependent blocks and there are never many: one wavefront does the rounds,
 // the other the schedules (42 us with one wavefront for both, 27 so).
-struct LeafDigestArgs {
+struct LeafDigestJob {
     uint32_t* out;
     const uint32_t* m;
     uint32_t N, nleaves;
     const uint32_t* flags;  // four words
     uint32_t* out_flags;
+};
+template <int NT>
+struct LeafDigestArgs {
+    LeafDigestJob job[NT];  // by blockIdx.y
     uint32_t* words;        // the mailbox
     uint32_t* ticket;
     uint32_t seq;
 };
-static __global__ void __launch_bounds__(128) k_leaf_digests(LeafDigestArgs g) {
+template <int NT>
+static __global__ void __launch_bounds__(128) k_leaf_digests(LeafDigestArgs<NT> args) {
     __shared__ uint4 kw[2][16][64];
+    const LeafDigestJob& g = args.job[NT == 1 ? 0 : blockIdx.y];
     const int lane = threadIdx.x & 63;
     const uint32_t leaf = blockIdx.x * 64 + lane;
+    const bool any = blockIdx.x * 64 < g.nleaves;
     const uint32_t base = (leaf < g.nleaves ? leaf : g.nleaves - 1) * kLeafCounts;
     const uint32_t cnt = g.N < kLeafCounts ? g.N : kLeafCounts;  // N is a power of two: all leaves are alike
-    const uint32_t nblk = (cnt + 3 + 15) / 16;
+    const uint32_t nblk = any ? (cnt + 3 + 15) / 16 : 0;
     if (threadIdx.x < 64) {
         uint32_t h[8];
         sha256_piped_rounds(h, kw, nblk, nblk);
@@ -475,11 +536,11 @@ static __global__ void __launch_bounds__(128) k_leaf_digests(LeafDigestArgs g) {
             __syncthreads();
         }
     }
-    if (g.seq) {
+    if (args.seq) {
         __syncthreads();
-        if (threadIdx.x == 0 && atomicAdd(g.ticket, 1u) == gridDim.x - 1) {
-            *g.ticket = 0;
-            mailbox_publish(g.words, g.seq);
+        if (threadIdx.x == 0 && atomicAdd(args.ticket, 1u) == gridDim.x * gridDim.y - 1) {
+            *args.ticket = 0;
+            mailbox_publish(args.words, args.seq);
         }
     }
 }
@@ -1225,16 +1286,25 @@ struct TableConstArgs {
     const uint32_t* T; size_t ts;
     const uint32_t* M; size_t ms;
     size_t N;
-    Fr beta;
     EqSplit eq;
-    uint32_t* partials;  // 2 values per workgroup
+    uint32_t* partials;  // this table's two values of a workgroup
     size_t pstride;
     const uint32_t* bad;   // two words on their way to the host: the smallest index the hash of A has found at fault
     uint32_t* bad_words;
 };
 
-static __global__ void __launch_bounds__(kBlock) k_table_const(TableConstArgs g) {
+template <int NT>
+struct TableConstJobs {
+    TableConstArgs job[NT];  // by blockIdx.y
+    Fr beta;
+    uint32_t values;  // partial sums per workgroup: two of every table
+};
+
+template <int NT>
+static __global__ void __launch_bounds__(kBlock) k_table_const(TableConstJobs<NT> jobs) {
     __shared__ uint32_t lds[4 * 2 * 8];
+    const TableConstArgs& g = jobs.job[NT == 1 ? 0 : blockIdx.y];
+    const Fr beta = jobs.beta;
     if (blockIdx.x == 0 && threadIdx.x < 2) {
         g.bad_words[threadIdx.x] = g.bad[threadIdx.x];
         mailbox_written();
@@ -1245,13 +1315,13 @@ static __global__ void __launch_bounds__(kBlock) k_table_const(TableConstArgs g)
         Fr b = fr_load(g.B, g.bs, j), t = fr_load(g.T, g.ts, j), m = fr_load(g.M, g.ms, j);
         Fr w = fr_load(g.eq.pool, g.eq.stride, g.eq.lo_off + (j & lo_mask));
         if (g.eq.has_hi) w = fr_mul(w, fr_load(g.eq.pool, g.eq.stride, g.eq.hi_off + (j >> g.eq.lbits)));
-        tot[0] = fr_add(tot[0], fr_mul(fr_mul(w, b), fr_add(t, g.beta)));
+        tot[0] = fr_add(tot[0], fr_mul(fr_mul(w, b), fr_add(t, beta)));
         tot[1] = fr_add(tot[1], fr_mul(b, m));
     }
     block_sum<2, 4>(tot, lds);
     if (threadIdx.x == 0) {
-        fr_store(g.partials, g.pstride, (size_t)blockIdx.x * 2, tot[0]);
-        fr_store(g.partials, g.pstride, (size_t)blockIdx.x * 2 + 1, tot[1]);
+        fr_store(g.partials, g.pstride, (size_t)blockIdx.x * jobs.values, tot[0]);
+        fr_store(g.partials, g.pstride, (size_t)blockIdx.x * jobs.values + 1, tot[1]);
     }
 }
 
