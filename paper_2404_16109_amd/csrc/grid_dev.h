@@ -16,12 +16,13 @@
 //
 // Bound by latency: a wavefront does one grid point of 64 positions, which keeps the
 // chain at two multiplications (three where the positions do not share their weights'
-// high factor) and a reduction.  A sum is at most 32 shares, so that one launch adds them
-// up: of more than 2^11 positions a wavefront takes more, one after the other (at most
-// sixteen times 64, of the 2^15 in a pass over one of sixteen variables).  Measured, a
-// proof of 2^20 entries with a table of 256 rows: 914 -> 766 us; three lookups of 2^11 to
-// 2^18 entries under one sumcheck, whose rounds used to follow each other instance by
-// instance: 2.07 -> 1.24 ms.
+// high factor) and a reduction.  A sum is at most 128 shares (fewer where several instances
+// share the room for them), so that one launch adds them up: of more than 2^13 positions a
+// wavefront takes more, one after the other (four times 64 of the 2^15 in a pass over one of
+// sixteen variables; with 32 shares, sixteen times, that pass took 38 us instead of 16).
+// Measured, a proof of 2^20 entries with a table of 256 rows: 914 -> 766 us; three lookups
+// of 2^11 to 2^18 entries under one sumcheck, whose rounds used to follow each other
+// instance by instance: 2.07 -> 1.24 ms.
 #pragma once
 #include "common.h"
 #include "reduce_dev.h"
@@ -29,7 +30,7 @@
 namespace zkmi {
 
 static const int kGridVars = 3;
-static const uint32_t kGridChunks = 32;  // most shares a sum is made of
+static const uint32_t kGridChunks = 128;  // most shares a sum is made of (GridPass may be told fewer)
 
 static inline uint32_t grid_points(int vars) { return vars == 0 ? 1 : vars == 1 ? 3 : vars == 2 ? 9 : 27; }
 
@@ -63,7 +64,8 @@ struct GridArgs {
     GridJob job[kGridMaxJobs];
     int njobs;
     uint32_t waves;
-    uint32_t* partials;  // value v, share c: eight words at 8 (kGridChunks v + c)
+    uint32_t* partials;  // value v, share c: eight words at 8 (most_chunks v + c)
+    uint32_t most_chunks;
     Fr beta;
 };
 
@@ -162,43 +164,49 @@ static __global__ void __launch_bounds__(kBlock) k_grid(GridArgs args) {
     if ((threadIdx.x & 63) == 0) {
         if (weighted && g.eq.has_hi && !g.hi_by_lane)
             tot = fr_mul(tot, fr_load(g.eq.pool, g.eq.stride, g.eq.hi_off + (from >> g.eq.lbits)));
-        uint4* out = (uint4*)args.partials + 2 * ((size_t)(g.first_value + value) * kGridChunks + chunk);
+        uint4* out = (uint4*)args.partials + 2 * ((size_t)(g.first_value + value) * args.most_chunks + chunk);
         out[0] = make_uint4(tot.l[0], tot.l[1], tot.l[2], tot.l[3]);
         out[1] = make_uint4(tot.l[4], tot.l[5], tot.l[6], tot.l[7]);
     }
 }
 
-// Value v's shares added up, to words 8 v .. 8 v + 7 of `out` (pinned host memory):
-// 32 lanes per value.
+// Value v's shares added up, to words 8 v .. 8 v + 7 of `out` (pinned host memory): LANES
+// lanes per value, 32 where that is as many as there are shares (fewer workgroups, each of
+// which fences its results for the host).
 struct GridSumArgs {
     uint32_t first_value[kGridMaxJobs];  // of each job,
     uint32_t chunks[kGridMaxJobs];       // and its shares
     int njobs;
     uint32_t values;
     const uint32_t* partials;
+    uint32_t most_chunks;
     uint32_t* out;
     uint32_t* words;   // the mailbox
     uint32_t* ticket;
     uint32_t seq;
 };
 
+template <int LANES>
 static __global__ void __launch_bounds__(kBlock) k_grid_sum(GridSumArgs args) {
-    const uint32_t value = blockIdx.x * (kBlock / 32) + (threadIdx.x >> 5), lane = threadIdx.x & 31;
+    const uint32_t value = blockIdx.x * (kBlock / LANES) + threadIdx.x / LANES, lane = threadIdx.x % LANES;
     const bool live = value < args.values;
     int q = 0;
     while (q + 1 < args.njobs && value >= args.first_value[q + 1]) ++q;
     Fr v = fr_zero();
-    if (live && lane < args.chunks[q]) {
-        const uint4* at = (const uint4*)args.partials + 2 * ((size_t)value * kGridChunks + lane);
-        const uint4 lo = at[0], hi = at[1];
-        v = Fr{{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}};
+    if (live) {
+        for (uint32_t c = lane; c < args.chunks[q]; c += LANES) {
+            const uint4* at = (const uint4*)args.partials + 2 * ((size_t)value * args.most_chunks + c);
+            const uint4 lo = at[0], hi = at[1];
+            v = fr_add(v, Fr{{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}});
+        }
     }
     v = dpp_add_step<0x111, 0xf>(v);
     v = dpp_add_step<0x112, 0xf>(v);
     v = dpp_add_step<0x114, 0xf>(v);
     v = dpp_add_step<0x118, 0xf>(v);
     v = dpp_add_step<0x142, 0xa>(v);  // the sum of 32 lanes is in their last
-    if (live && lane == 31) {
+    if constexpr (LANES == 64) v = dpp_add_step<0x143, 0xc>(v);
+    if (live && lane == LANES - 1) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) args.out[8 * value + k] = v.l[k];
         mailbox_written();
@@ -284,10 +292,12 @@ struct GridPass {
     GridFoldArgs fold;
     uint32_t values = 0, fold_blocks = 0;
 
-    GridPass() {
+    // most_chunks: shares per sum the partial sums have room for
+    explicit GridPass(uint32_t most_chunks = kGridChunks) {
         memset(&grid, 0, sizeof grid);
         memset(&sum, 0, sizeof sum);
         memset(&fold, 0, sizeof fold);
+        grid.most_chunks = sum.most_chunks = most_chunks;
     }
     // Binds the `vars` (0..3) last challenges: n elements from src into dst.
     void add_fold(const uint32_t* src, size_t ss, uint32_t* dst, size_t ds, size_t n, int vars, bool rows = false) {
@@ -298,7 +308,7 @@ struct GridPass {
     uint32_t add(const uint32_t* x, size_t xs, const uint32_t* y, size_t ys, int vars, int kind, size_t P, const EqSplit& eq) {
         GridJob& g = grid.job[grid.njobs];
         g = GridJob{x, y, xs, ys, eq, (uint32_t)P, 64, 1, grid.waves, values, vars, kind, 0};
-        while ((size_t)g.span * kGridChunks < P) g.span *= 2;
+        while ((size_t)g.span * grid.most_chunks < P) g.span *= 2;
         g.hi_by_lane = eq.has_hi && g.span > (1u << eq.lbits);
         g.chunks = (uint32_t)div_up(P, g.span);
         sum.first_value[grid.njobs] = values;
@@ -345,7 +355,11 @@ struct GridPass {
         sum.ticket = ticket;
         sum.seq = seq;
         hipLaunchKernelGGL(k_grid, dim3((grid.waves + 3) / 4), dim3(kBlock), 0, stream, grid);
-        hipLaunchKernelGGL(k_grid_sum, dim3((values + 7) / 8), dim3(kBlock), 0, stream, sum);
+        uint32_t most = 0;
+        for (int q = 0; q < sum.njobs; ++q)
+            if (sum.chunks[q] > most) most = sum.chunks[q];
+        if (most <= 32) hipLaunchKernelGGL(k_grid_sum<32>, dim3((values + 7) / 8), dim3(kBlock), 0, stream, sum);
+        else hipLaunchKernelGGL(k_grid_sum<64>, dim3((values + 3) / 4), dim3(kBlock), 0, stream, sum);
         ZK_HIP_TRY(hipGetLastError());
         return ZK_OK;
     }

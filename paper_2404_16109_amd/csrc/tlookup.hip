@@ -1493,7 +1493,7 @@ static int prove_core(const ProveCall& c) {
         auto starts_pass = [&](size_t i) { return k >= inst[i].skip && plans[i].kind == kRoundGrid && plans[i].starts; };
         if (any_pass) {
             ProfileScope prof(kProfRoundSmall, stream);
-            GridPass pass;
+            GridPass pass(K <= 2 ? kGridChunks : K <= 4 ? kGridChunks / 2 : kGridChunks / 4);  // 89 values an instance in 6 * 4096 places
             pass.challenges(r_last);
             for (size_t i = 0; i < K; ++i) {
                 const RoundPlan& plan = plans[i];
