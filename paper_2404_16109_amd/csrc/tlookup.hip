@@ -209,7 +209,9 @@ static size_t vec_digest_row_digests(size_t n) {
 // Enqueues the hash trees over up to kDigestMaxJobs vectors (n elements each, powers
 // of two): their last rows (at most kTreeHostRow digests) go to pinned host memory,
 // and the last launch publishes `seq` if it is not zero (`ticket`: one zeroed word of
-// device memory, left zero).  The host then finishes each tree (vec_digest_finish).
+// device memory, left zero).  The host then finishes each tree (vec_digest_finish); of up
+// to kHostLeaves leaves in all it gets the bytes and hashes them itself, if it has the
+// instructions for it.
 // leaves: room for the sum of vec_digest_leaves(n); rows: vec_digest_row_digests(n)
 // digests each.
 struct VecDigestJob {
@@ -219,6 +221,8 @@ struct VecDigestJob {
     LeafGather from;
     const uint32_t* host_row = nullptr;  // set by the launch: the row handed to the host
     uint32_t host_count = 0;
+    const uint8_t* shipped = nullptr;    // or the leaves' bytes, leaf_bytes each
+    size_t leaf_bytes = 0;
 };
 
 template <int MODE>
@@ -226,6 +230,11 @@ static void launch_leaves(const VecLeavesArgs& lv, hipStream_t stream) {
     if (leaves_in_pairs<MODE>(lv.groups))
         hipLaunchKernelGGL(k_vec_leaves_piped<MODE>, dim3((lv.groups + 1) / 2), dim3(256), 0, stream, lv);
     else hipLaunchKernelGGL(k_vec_leaves<MODE>, dim3(lv.groups), dim3(64), 0, stream, lv);
+}
+
+template <int MODE>
+static void launch_leaves_to_host(const VecLeavesArgs& lv, hipStream_t stream) {
+    hipLaunchKernelGGL(k_leaves_to_host<MODE>, dim3((unsigned)div_up(lv.groups, kBlock)), dim3(kBlock), 0, stream, lv);
 }
 
 // The jobs that have rows (LeafGather) all compare them with S, or all with the
@@ -265,6 +274,30 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
     int mode = kLeafPlain;
     for (int q = 0; q < njobs; ++q)
         if (jobs[q].from.rows) mode = jobs[q].from.S ? kLeafRowsCheck : ints ? kLeafRowsInts : kLeafRows;
+    size_t all_leaves = 0;
+    for (int q = 0; q < njobs; ++q) all_leaves += cnt[q];
+    if (all_leaves <= kHostLeaves && host::Sha256::use_sha_instructions()) {
+        static_assert(kHostLeaves * kVecLeaf * 32 <= kBulkDigests, "the leaves take the place of the digests");
+        uint32_t elements = 0;
+        for (int q = 0; q < njobs; ++q) {
+            VecDigestJob& j = jobs[q];
+            uint8_t* const at = mb->bulk + (size_t)elements * 32;
+            lv.job[q].out = (uint32_t*)at;
+            lv.job[q].first_group = elements;
+            j.shipped = at;
+            j.leaf_bytes = j.n / cnt[q] * 32;
+            j.host_count = (uint32_t)cnt[q];
+            elements += (uint32_t)j.n;
+        }
+        lv.groups = elements;
+        lv.seq = seq;
+        if (mode == kLeafRowsCheck) launch_leaves_to_host<kLeafRowsCheck>(lv, stream);
+        else if (mode == kLeafRowsInts) launch_leaves_to_host<kLeafRowsInts>(lv, stream);
+        else if (mode == kLeafRows) launch_leaves_to_host<kLeafRows>(lv, stream);
+        else launch_leaves_to_host<kLeafPlain>(lv, stream);
+        ZK_HIP_TRY(hipGetLastError());
+        return ZK_OK;
+    }
     if (mode == kLeafRowsCheck) launch_leaves<kLeafRowsCheck>(lv, stream);
     else if (mode == kLeafRowsInts) launch_leaves<kLeafRowsInts>(lv, stream);
     else if (mode == kLeafRows) launch_leaves<kLeafRows>(lv, stream);
@@ -304,7 +337,8 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
 static void vec_digest_finish(uint8_t out[32], const VecDigestJob& job) {
     uint8_t row[kTreeHostRow * 32];
     uint32_t cnt = job.host_count;
-    for (uint32_t i = 0; i < cnt * 8; ++i) {
+    if (job.shipped) host::Sha256::hash_each(row, job.shipped, job.leaf_bytes, cnt);
+    for (uint32_t i = 0; i < cnt * 8 && !job.shipped; ++i) {
         const uint32_t v = __builtin_bswap32(job.host_row[i]);  // hash-state words: big-endian words of the digest's bytes
         memcpy(row + 4 * i, &v, 4);
     }

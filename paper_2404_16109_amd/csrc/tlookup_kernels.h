@@ -895,6 +895,49 @@ static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs a
     leaves_done(args);
 }
 
+// Very few leaves: a leaf is a chain of 65 blocks, 140 us here whatever their number, and
+// 3 us on a host with SHA instructions, two at a time.  A thread makes, converts and checks
+// one element as above and writes its bytes to pinned host memory (`out`), one leaf's
+// after another's; the host hashes them (vec_digest_finish).  `first_group` and `groups`
+// count elements here.  Measured, whole proofs with hints: 2^10 entries in 2^8 rows (10
+// leaves) 425 -> 300 us, 2^11 in 2^11 (32 leaves) 467 -> 367; verifying the former 260 ->
+// 141.  32 leaves are what the digests' part of the pinned memory holds.
+static const size_t kHostLeaves = 32;
+template <int MODE>
+static __global__ void __launch_bounds__(kBlock) k_leaves_to_host(VecLeavesArgs args) {
+    const uint32_t g = blockIdx.x * kBlock + threadIdx.x;
+    if (g < args.groups) {
+        const VecLeavesJob& job = leaves_job(args, g);
+        const size_t i = g - job.first_group;
+        Fr x;
+        if (MODE != kLeafPlain && job.from.rows) {
+            const uint32_t row = job.from.rows[i], r = row < job.from.N ? row : 0u;
+            fr_store(job.v, job.stride, i, fr_load_row<4, 0>(job.from.B, r));
+            x = fr_load_row<4, 2>(job.from.B, r);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x.l[k] = __builtin_bswap32(x.l[k]);
+            if constexpr (MODE >= kLeafRowsCheck) {
+                const Fr t = fr_load_row<2, 0>(job.from.T, r);
+                Fr s;
+                if constexpr (MODE == kLeafRowsInts) small_source_load(s.l, args.ints, i);
+                else s = fr_load(job.from.S, job.from.ss, i);
+                uint32_t diff = row ^ r;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) diff |= s.l[k] ^ t.l[k];
+                if (diff) atomicMin(job.from.bad, (unsigned long long)i);
+            }
+        } else {
+            x = fr_from_mont(fr_load(job.v, job.stride, i));
+        }
+        const size_t cnt = job.n / job.L, leaf = i % job.L, at = i / job.L;
+        uint4* out = (uint4*)job.out + 2 * (leaf * cnt + at);
+        out[0] = make_uint4(x.l[0], x.l[1], x.l[2], x.l[3]);
+        out[1] = make_uint4(x.l[4], x.l[5], x.l[6], x.l[7]);
+        mailbox_written();
+    }
+    leaves_done(args);
+}
+
 // One step up the trees: workgroup b of a job reduces digests [b*chunk,
 // (b+1)*chunk) of `in` to one (chunk a power of four, at most kTreeChunk) and writes
 // it to out[8b..8b+8).  The last rows of a tree are the host's: a level costs some 8

@@ -69,32 +69,35 @@ public:
         put_state(out);
     }
 
-    // One row of a hash tree: out[i] = SHA-256 of in[4 i .. 4 i + 3], digests of 32 bytes.  out may be in.
-    static void hash_fours(uint8_t* out, const uint8_t* in, uint32_t nodes) {
-        uint32_t i = 0;
+    // out[i] = SHA-256 of the `bytes` bytes at in + i bytes (bytes >= 32).  out may be in.
+    static void hash_each(uint8_t* out, const uint8_t* in, size_t bytes, size_t count) {
+        size_t i = 0;
 #if defined(__x86_64__)
-        if (use_sha_instructions()) {
+        if (use_sha_instructions() && bytes % 64 == 0) {
             uint8_t pad[64] = {0x80};
-            pad[62] = 0x04;  // 1024 bits
-            for (; i + 2 <= nodes; i += 2) {
+            for (int k = 0; k < 8; ++k) pad[56 + k] = (uint8_t)((uint64_t)bytes * 8 >> (56 - 8 * k));
+            for (; i + 2 <= count; i += 2) {
                 Sha256 x, y;
                 uint32_t (*const h[2])[8] = {&x.h_, &y.h_};
-                const uint8_t* p = in + (size_t)i * 128;
-                for (int part = 0; part < 3; ++part) {
-                    const uint8_t* const b[2] = {part < 2 ? p + 64 * part : pad, part < 2 ? p + 128 + 64 * part : pad};
+                const uint8_t* p = in + i * bytes;
+                for (size_t at = 0; at <= bytes; at += 64) {
+                    const uint8_t* const b[2] = {at < bytes ? p + at : pad, at < bytes ? p + bytes + at : pad};
                     blocks_shani<2>(h, b);
                 }
-                x.put_state(out + (size_t)i * 32);
-                y.put_state(out + (size_t)i * 32 + 32);
+                x.put_state(out + i * 32);
+                y.put_state(out + i * 32 + 32);
             }
         }
 #endif
-        for (; i < nodes; ++i) {
+        for (; i < count; ++i) {
             Sha256 h;
-            h.update(in + (size_t)i * 128, 128);
-            h.finish(out + (size_t)i * 32);
+            h.update(in + i * bytes, bytes);
+            h.finish(out + i * 32);
         }
     }
+
+    // One row of a hash tree: out[i] = SHA-256 of in[4 i .. 4 i + 3], digests of 32 bytes.  out may be in.
+    static void hash_fours(uint8_t* out, const uint8_t* in, uint32_t nodes) { hash_each(out, in, 128, nodes); }
 
     // Tests can switch the instruction-set path off to compare the two.
     static bool& use_sha_instructions() {
