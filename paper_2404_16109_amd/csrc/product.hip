@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(kBlock) k_colsum_reduce(uint32_t* __restrict__
 }
 
 // b[k] = sum_j W[k][j] e[j]; rows D1 <= k < P1 are zero.  One workgroup per row: matrices
-// so small that what counts is the length of a workgroup's chain.
+// of few rows, or so small that what counts is the length of a workgroup's chain.
 __global__ void __launch_bounds__(kBlock) k_rowdot_short(uint32_t* __restrict__ b, size_t bs, const uint32_t* __restrict__ W,
                                                          size_t ws, size_t D1, size_t D2, const uint32_t* __restrict__ e,
                                                          size_t es) {
@@ -380,7 +380,7 @@ __global__ void __launch_bounds__(kBlock) k_rowdot_short(uint32_t* __restrict__ 
     if (threadIdx.x == 0) fr_store(b, bs, k, tot[0]);
 }
 
-// The same for longer ones.  A workgroup takes four rows, its
+// The same for larger ones (rowdot_run).  A workgroup takes four rows, its
 // wavefronts every fourth batch of 64 columns; the products are added up on the matrix
 // cores (outer_dev.h), 4096 columns between two reductions.  Bound by HBM: 5120 x 5120
 // elements 150 us, 5.6 TB/s (202 with 512-bit sums on the vector ALU, 290 with a reduction for every
@@ -717,8 +717,12 @@ static void small_products_run(uint32_t* a, uint32_t* b, size_t PC, const int16_
 
 static void rowdot_run(uint32_t* b, size_t PR, const uint32_t* M, size_t ms, size_t R, size_t C, const uint32_t* e1,
                        size_t e1s, hipStream_t stream) {
-    // alike at 2000 x 64 (144 us for a whole proof both ways); 100 x 33: 58 and 61, 777 x 1000: 130 and 127, 1000 x 3000: 151 and 145
-    if (R * C < (size_t)1 << 17) hipLaunchKernelGGL(k_rowdot_short, dim3((unsigned)PR), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s);
+    // A workgroup of k_rowdot does four rows: of few rows it leaves compute units idle, of short ones there is nothing to
+    // gain.  Whole proofs, a workgroup per row and four rows per workgroup: 512 x 32768: 262 and 275 us, 128 x 32768: 163
+    // and 225, 768 x 32768: 334 and 306, 1024 x 4096: 144 and 136, 1024 x 1024: 117 and 113, 768 x 1024: 114 and 118,
+    // 1024 x 128: alike
+    if (R < 768 || R * C < (size_t)1 << 20)
+        hipLaunchKernelGGL(k_rowdot_short, dim3((unsigned)PR), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s);
     else hipLaunchKernelGGL(k_rowdot, dim3((unsigned)div_up(PR, kDotRows)), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s, PR);
 }
 

@@ -38,6 +38,12 @@
 // Y is multiplied by alpha on the way: in the first round on the fly, in the
 // second when the folded array is first written; from then on the array holds
 // the scaled values (the final claim is scaled back on the host).
+//
+// Of one and two segments and more than kLinkPassVars variables these sums do not come
+// round by round: a pass yields those of the next two rounds (of the next three from
+// integers), and one fold binds their variables (link_long.h; the host scales the first
+// pass's sums of Y, the first fold the array).
+// The kernels below serve three segments and shorter proofs.
 #include "internal.h"
 #include "small_dev.h"
 #include "tlookup_kernels.h"

@@ -19,7 +19,8 @@ def zk():
     return zk
 
 
-@pytest.mark.parametrize("D0,D1,D2", [(1, 128, 1024), (2, 257, 511), (3, 33, 4097), (1, 15, 8737), (2, 130, 4096), (1, 131, 1000)])
+@pytest.mark.parametrize("D0,D1,D2", [(1, 128, 1024), (2, 257, 511), (3, 33, 4097), (1, 15, 8737), (2, 130, 4096), (1, 131, 1000),
+                                      (1, 768, 1366), (1, 767, 1368), (1, 1023, 1026), (1, 769, 4099)])
 def test_against_the_definition(zk, D0, D1, D2):
     """Rows of the largest field element and of small ones: b_k is read off the proof of a matrix with one row of X per k."""
     rng = np.random.default_rng(D1 * 10000 + D2)
