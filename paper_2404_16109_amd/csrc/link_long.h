@@ -92,6 +92,7 @@ struct LongGridArgs {
 static __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) k_long_grid(LongGridArgs g) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[4 * 5 * kOuterStage];  // per wavefront Y's four operands and one of X
     static_assert(sizeof lds >= 9 * 4096, "outer_close's sums");
+    static_assert(4 * kOuterMaxSpan <= kOuterMaxProducts, "a position adds four products to the class that is mixed twice");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* const stage = lds + wave * 5 * kOuterStage;
     uint8_t* const stage_x = stage + 4 * kOuterStage;

@@ -23,6 +23,7 @@
 // vector ALU.
 #pragma once
 #include "fr_dev.h"
+#include "limbs_dev.h"
 
 namespace zkmi {
 
@@ -80,36 +81,12 @@ __device__ __forceinline__ void limbs_of_pair(int64_t (&out)[8], const int64_t (
     }
 }
 
-// What a sum over C constants e_c is short of when the elements' digits go in as
-// d - 128: C0 sum_c e_c mod r, plus the multiple of r that keeps the result from
+// The bias of a sum over C constants e_c: what it is short of when the elements' digits go
+// in as d - 128, C0 sum_c e_c mod r, plus the multiple of r that keeps the result from
 // being negative (a column sum is at least -C * 32 * 128 * 128, so 4096 C r do).
-struct ToepBias {
-    uint32_t w[9];
-};
-
-// V = sum_q limb_q 2^(32 q) + bias, known to lie in [0, 2^20 r), to V mod r.
 __device__ __forceinline__ Fr limbs_reduce(const int64_t (&limb)[8], const ToepBias& bias) {
     uint32_t w[8];
-    int64_t c = 0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        c += limb[q] + (int64_t)(uint64_t)bias.w[q];
-        w[q] = (uint32_t)c;
-        c >>= 32;
-    }
-    c += bias.w[8];
-    // quotient by floor(V / 2^248) * floor(2^280 / r) / 2^32: at most one too small (the two truncations cost less
-    // than 1/115 + 2^27/2^32 of r), so V - q r < 2 r; subtracted as q (2^256 - r) modulo 2^256
-    const uint32_t t = ((uint32_t)c << 8) | (w[7] >> 24);
-    const uint32_t q = __umulhi(t, 0x02355094u);
-    constexpr uint32_t nr[8] = {0xffffffffu, 0x00000000u, 0x0001a401u, 0xac425bfdu, 0xf65e27fau, 0xccc627f7u, 0xd66282b7u, 0x8c1258acu};
-    uint64_t acc = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        acc += (uint64_t)q * nr[j] + w[j];
-        w[j] = (uint32_t)acc;
-        acc >>= 32;
-    }
+    limbs_reduce_words(w, limb, bias);
     return fr_reduce_once(w);
 }
 

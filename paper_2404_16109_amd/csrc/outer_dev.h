@@ -30,7 +30,6 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 
 static const int kOuterBatch = 64;         // positions a wavefront takes at a time
 static const int kOuterStage = 2048;       // bytes of LDS a wavefront stages one operand in
-static const size_t kOuterMaxSpan = 4096;  // positions per workgroup: outer_close's bound
 
 // One operand of 64 positions for two matrix instructions: lane l holds digit l % 32
 // of positions 32 s + 16 (l / 32) .. + 15 in half s.
@@ -146,8 +145,8 @@ __device__ __forceinline__ OuterOperand outer_column(int n) {
 // digits of one value: 32 (field elements), 8 or 4 (64- or 32-bit integers, four or
 // eight to an operand).  Calls out(q, group, x) in one lane for every sum of accumulator q,
 //   x = sum_(i,j) 2^(8 (i + j)) C_ij / 2^256 mod r, reduced.
-// A column sum_i 2^(8 i) C_ij is below 2^(8 31) 256/255 * 2^14 positions < 2^20 r in
-// magnitude for kOuterMaxSpan positions, which is what the bias makes up for.
+// An accumulator may hold kOuterMaxProducts products per column (limbs_dev.h): callers
+// assert their positions per workgroup times products per position.
 // SUMS: the last accumulator's columns are values by themselves (outer_column): out(N - 1,
 // column, sum_i 2^(8 i) C_ij mod r) for every column.
 template <int N, int GROUP, bool SUMS = false, class Out>
@@ -168,10 +167,7 @@ __device__ __forceinline__ void outer_close(const v16i (&acc)[N], int* sums, Out
             for (int r = 0; r < 16; ++r) atomicAdd(&sums[(q * 16 + r) * 64 + lane], acc[q][r]);
     }
     __syncthreads();
-    ToepBias bias;  // 2^20 r
-    constexpr uint32_t r32[8] = {ZK_R0, ZK_R1, ZK_R2, ZK_R3, ZK_R4, ZK_R5, ZK_R6, ZK_R7};
-#pragma unroll
-    for (int k = 0; k < 9; ++k) bias.w[k] = (k < 8 ? r32[k] << 20 : 0u) | (k > 0 ? r32[k - 1] >> 12 : 0u);
+    const ToepBias bias = outer_bias();
     // two accumulators at a time: lanes 0..31 take the columns of the first, the others those of the second
 #pragma unroll 1
     for (int q = 2 * wave; q < N; q += 8) {

@@ -250,6 +250,7 @@ struct DataRound01Args {
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) k_round_first_two(DataRound01Args g) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[4 * 5 * kOuterStage];  // per wavefront S's four operands and one of A
     static_assert(sizeof lds >= 6 * 4096, "outer_close's sums");
+    static_assert(4 * (size_t)kBlock * kRound01MaxQuads <= kOuterMaxProducts, "a position adds four products to M_xx");
     __shared__ uint32_t vals[9][8];     // M_x0, M_x1, M_0x, M_1x, M_xx, W_00, W_01, W_10, W_11
     __shared__ uint32_t sums_a[4][4][9];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -1,6 +1,7 @@
 // Host build of the 29-bit-limb field arithmetic (csrc/fr29_dev.h) with a C
 // interface, so that tests can compare it with Python's big integers.  Compiled
 // with g++ by tests/test_fr29_host.py; nothing here runs on a GPU.
+#include "../../paper_2404_16109_amd/csrc/limbs_dev.h"
 #include "../../paper_2404_16109_amd/csrc/round01_dev.h"
 #include "../../paper_2404_16109_amd/csrc/round29_dev.h"
 
@@ -115,6 +116,19 @@ void c_fold2(const uint32_t* y, const uint32_t* r_first, const uint32_t* r, cons
 void c_mul3_add(const uint32_t* v, uint32_t* out) {
     f29_out(out, f29_mul3_add(f29_of(v), f29_of(v + 9), f29_of(v + 18), f29_of(v + 27), f29_of(v + 36), f29_of(v + 45), f29_of(v + 54)));
 }
+// A column of sums of byte products as outer_close (outer_dev.h) turns it into a value: columns[i] counts 2^(8 i).
+// out: eight words, below 2 r.
+void c_outer_column(const int32_t* columns, uint32_t* out) {
+    int64_t limb[8];
+    for (int q = 0; q < 8; ++q) {
+        limb[q] = 0;
+        for (int t = 0; t < 4; ++t) limb[q] += (int64_t)columns[4 * q + t] * (1 << (8 * t));
+    }
+    uint32_t w[8];
+    limbs_reduce_words(w, limb, outer_bias());
+    for (int q = 0; q < 8; ++q) out[q] = w[q];
+}
+uint64_t c_outer_most_products() { return kOuterMaxProducts; }
 void c_canonical(const uint32_t* l, uint32_t* w) { F29 a; for (int i = 0; i < 9; ++i) a.l[i] = l[i]; f29_canonical(w, a); }
 void c_canonical_big(const uint32_t* l, uint32_t* w) { F29 a; for (int i = 0; i < 9; ++i) a.l[i] = l[i]; f29_canonical_big(w, a); }
 }

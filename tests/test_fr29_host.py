@@ -415,3 +415,31 @@ def test_fold2_binds_two_variables(lib):
         assert value_of(out) % R == (lo + (hi - lo) * r1 * inv) % R
         # within what two single folds may add: below its first entry + 2.8 r, normalized
         assert value_of(out) < y[0] + 2.8 * R and all(int(v) <= M29 for v in out[:8])
+
+
+def _balanced_digits(x):
+    """The 32 digits -128..127 of x < 2^256 - C0, C0 = 0x80 in every byte."""
+    c0 = int.from_bytes(b"\x80" * 32, "little")
+    return [d - 128 for d in (x + c0).to_bytes(32, "little")]
+
+
+def test_columns_of_products_at_their_bounds(lib):
+    """A column of an accumulator is sum_p x_p d_p over up to 16384 products: as large as x_p and d_p can be, all alike, in
+    both directions, and where the sum is near zero."""
+    lib.c_outer_most_products.restype = ctypes.c_uint64
+    most = lib.c_outer_most_products()
+    assert most == 16384
+    top = R + R * R // 2 ** 261                # what f29_mul leaves at most
+    rng = random.Random(31)
+    cases = [([top], [d], most) for d in (-128, -127, -1, 0, 1, 127)]                  # (x's, digits, times each)
+    cases += [([R - 1], [-128], most), ([R // 2], [-128], most), ([0], [-128], most), ([1], [127], most)]
+    for _ in range(200):
+        k = rng.choice([1, 2, 4, 8])
+        cases.append(([rng.randrange(top) for _ in range(k)], [rng.choice([-128, 127, rng.randrange(-128, 128)]) for _ in range(k)],
+                      most // k))
+    for xs, ds, times in cases:
+        columns = np.array([times * sum(_balanced_digits(x)[i] * d for x, d in zip(xs, ds)) for i in range(32)], np.int32)
+        out = np.zeros(8, np.uint32)
+        lib.c_outer_column(ptr(columns), ptr(out))
+        got, want = words_value(out), times * sum(x * d for x, d in zip(xs, ds))
+        assert got < 2 * R and got % R == want % R, (xs, ds)

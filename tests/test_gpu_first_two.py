@@ -50,3 +50,31 @@ def test_against_the_integers(zk, logD, logN):
     rc, proof, _ = zk.tlookup_prove(seed, S, idx, T)
     rc_i, from_ints, _ = zk.tlookup_prove_small(seed, tx[idx.long()].contiguous(), None, None, idx, T)
     assert rc == 0 and rc_i == 0 and from_ints == proof
+
+
+@pytest.mark.parametrize("logD,value,runs", [(23, 256, "everywhere"), (23, 65536, "everywhere"), (23, 65535, "everywhere"),
+                                             (24, 256, "places"), (22, 256, "everywhere"), (23, -256, "everywhere")])
+def test_tensors_of_one_value(zk, logD, value, runs):
+    """Entries that are alike, in all four quarters of a workgroup's places: the sums over a place's four products are as
+    large as they get (256 and 65536 have a digit -128 in the form vectors hold)."""
+    N, D = 1 << 8, 1 << logD
+    assert zk.zkmi_selftest_tlookup_plan(D, N, 1, False)[1][0][0] == FIRST_TWO
+    g = torch.Generator(device="cuda")
+    g.manual_seed(logD)
+    tx = torch.arange(N, dtype=torch.int32, device="cuda") * 3 - N
+    tx[7] = value
+    T = zk.Vec(N)
+    assert zk.fr_from_i32(T, tx) == 0
+    if runs == "everywhere":
+        idx = torch.full((D,), 7, dtype=torch.int32, device="cuda")
+    else:
+        idx = torch.randint(0, N, (4, D >> 2), generator=g, device="cuda", dtype=torch.int32)
+        idx[:, 4096 * 5:4096 * 45] = 7
+        idx = idx.reshape(-1).contiguous()
+    S = zk.Vec(D)
+    S.data[:, :D] = T.data.index_select(1, idx.long())
+    seed = bytes([logD, value & 0xFF, (value >> 8) & 0xFF, 5]) * 8
+    rc, proof, _ = zk.tlookup_prove(seed, S, idx, T)
+    rc_i, from_ints, _ = zk.tlookup_prove_small(seed, tx[idx.long()].contiguous(), None, None, idx, T)
+    assert rc == 0 and rc_i == 0 and from_ints == proof
+    assert zk.tlookup_verify(seed, proof, T, D)[0] == 0

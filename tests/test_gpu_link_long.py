@@ -89,3 +89,53 @@ def test_integers(zk, orc, log_rows, log_cols, K, out_bits, aligned):
         Yk[0][5] = 1 << 30
         assert zk.zkattn_link_prove_small(seed, Zp, X, Y, Yk, yhat, bases, rows, cols)[0] == zk.ZK_E_BADARG
         Yk[0][5] = keep
+
+
+def constant_output_tensors(log_rows, log_cols, value):
+    """Two segments, the second of which has one output: Y^(2) is `value` everywhere."""
+    import paper_2404_16109_amd as zk
+    rows, cols = 1 << log_rows, 1 << log_cols
+    D = rows * cols
+    g = torch.Generator(device="cuda")
+    g.manual_seed(100 * log_rows + log_cols)
+    X = [torch.randint(0, 1 << 16, (D,), generator=g, device="cuda", dtype=torch.int32), torch.zeros(D, dtype=torch.int32, device="cuda")]
+    Yk = [torch.randint(0, 1 << 16, (D,), generator=g, device="cuda", dtype=torch.int32),
+          torch.full((D,), value, dtype=torch.int32, device="cuda")]
+    Y = Yk[0].long() * value
+    canon = torch.zeros((rows, 4), dtype=torch.int64, device="cuda")
+    canon[:, 0] = Y.reshape(rows, cols).sum(dim=1)
+    yhat = zk.Vec(rows)
+    assert zk.fr_from_canonical(yhat, canon) == 0
+    return -X[0].long(), X, Y, Yk, yhat, [1, 1 << 16]
+
+
+@pytest.mark.parametrize("log_rows,log_cols,value", [(13, 11, 256), (14, 10, 65536), (13, 11, 3)])
+def test_vectors_of_one_value(zk, log_rows, log_cols, value):
+    """From 2^24 scores on a workgroup takes 4096 positions; entries that are alike make the sums over a position's four
+    products as large as they get.  The proof from the integers takes other sums first, and shorter ones after that."""
+    rows, cols = 1 << log_rows, 1 << log_cols
+    Zp, X, Y, Yk, yhat, bases = constant_output_tensors(log_rows, log_cols, value)
+    seed = bytes([log_rows, log_cols, value & 0xFF, 7]) * 8
+    rc, want = zk.zkattn_link_prove_small(seed, Zp, X, Y, Yk, yhat, bases, rows, cols)
+    assert rc == zk.ZK_OK
+
+    def vec(t):
+        v = zk.Vec(t.numel())
+        assert zk.fr_from_i32(v, t) == 0
+        return v
+    X, Yk = [vec(x) for x in X], [vec(y) for y in Yk]
+    Zp, Y = zk.Vec(rows * cols), zk.Vec(rows * cols)
+    assert zk.fr_mul_scalar(Zp, X[0], zk.synth.BLS12_381_R - 1) == 0 and zk.fr_mul(Y, Yk[0], Yk[1]) == 0
+    rc, got = zk.zkattn_link_prove(seed, Zp, X, Y, Yk, yhat, bases, rows, cols)
+    assert rc == zk.ZK_OK and got == want
+    assert zk.zkattn_link_verify(seed, got, rows, cols, bases, yhat=yhat)[0] == zk.ZK_OK
+
+
+def test_integers_of_one_value(zk):
+    """From 2^27 scores on the second pass, over the folded arrays, has workgroups of 4096 positions."""
+    rows, cols = 1 << 16, 1 << 11
+    Zp, X, Y, Yk, yhat, bases = constant_output_tensors(16, 11, 256)
+    seed = bytes([16, 11, 7, 8]) * 8
+    rc, proof = zk.zkattn_link_prove_small(seed, Zp, X, Y, Yk, yhat, bases, rows, cols)
+    assert rc == zk.ZK_OK
+    assert zk.zkattn_link_verify(seed, proof, rows, cols, bases, yhat=yhat)[0] == zk.ZK_OK
