@@ -141,7 +141,8 @@ __device__ __forceinline__ OuterOperand outer_column(int n) {
 }
 
 // The sums of a workgroup of four wavefronts.  `sums`: N * 1024 words of LDS (may
-// overlap the staging areas).  Columns are taken in groups of GROUP lanes, each the
+// overlap the staging areas; they are still being read when the first wavefronts return,
+// so that a caller who stages or closes again waits at a barrier first).  Columns are taken in groups of GROUP lanes, each the
 // digits of one value: 32 (field elements), 8 or 4 (64- or 32-bit integers, four or
 // eight to an operand).  Calls out(q, group, x) in one lane for every sum of accumulator q,
 //   x = sum_(i,j) 2^(8 (i + j)) C_ij / 2^256 mod r, reduced.

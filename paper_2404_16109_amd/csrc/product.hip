@@ -440,8 +440,8 @@ __global__ void __launch_bounds__(kBlock) k_rowdot(uint32_t* __restrict__ b, siz
 #pragma unroll
             for (int q = 0; q < 8; ++q) tot[r][q] = t.l[q];
         });
+        __syncthreads();  // the sums are read: the next columns are staged where they lie
     }
-    __syncthreads();
     if (threadIdx.x < kDotRows * 8) {
         const size_t r = threadIdx.x >> 3, q = threadIdx.x & 7;
         if (k + r < P1) b[q * bs + k + r] = k + r < D1 ? tot[r][q] : 0u;

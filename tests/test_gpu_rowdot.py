@@ -1,7 +1,7 @@
-"""The rows' products of a matrix proof on the matrix cores (k_rowdot): a batch of 64 columns that is not full, more columns
-than two reductions lie apart, rows that do not fill a workgroup, a matrix whose planes start anywhere; and the smaller
-matrices beside them.  The proof's verifier recomputes the values from the matrices on other paths; equality with the
-oracle where that is quick."""
+"""The rows' products of a matrix proof: on the matrix cores (k_rowdot, from 768 rows and 2^20 elements on) with a batch of 64
+columns that is not full, columns for one, two and three reductions (4096 to each) of which the later ones keep one or all four
+wavefronts busy, rows that do not fill a workgroup, a matrix whose planes start anywhere; and the smaller matrices beside them
+(k_rowdot_short).  Checked against the product by the definition, or for equality with the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -39,3 +39,18 @@ def test_against_the_definition(zk, D0, D1, D2):
     y = [sum(x[i][k] * w[k * D2 + j] for k in range(D1)) % R for i in range(D0) for j in range(D2)]
     Y = zk.vec_from_bytes(np.frombuffer(b"".join(v.to_bytes(32, "little") for v in y), np.uint8).reshape(-1, 32))
     assert zk.matmul_sumcheck_verify(seed, proof, D0, D1, D2, Y=Y, X=X, W=W) == 0
+
+
+@pytest.mark.parametrize("D0,D1,D2", [(2, 768, 4400), (1, 769, 4096 + 256), (1, 1023, 5120), (1, 770, 8192 + 70), (1, 771, 8192 + 300)])
+def test_columns_for_several_reductions(zk, orc, D0, D1, D2):
+    """All four wavefronts have columns behind the first 4096: what they stage lies where the sums before were."""
+    rng = np.random.default_rng(D1 * 10000 + D2)
+    X, W = (rng.integers(-(1 << 40), 1 << 40, size=s) for s in ((D0, D1), (D1, D2)))
+    seed = bytes([D0, D1 % 251, D2 % 251, 10]) * 8
+    rc, want, _ = orc.matmul_sumcheck_prove(seed, X, W)
+    assert rc == 0
+    vx, vw = zk.vec_from_bytes(orc.fr_from_i64(X.reshape(-1))), zk.vec_from_bytes(orc.fr_from_i64(W.reshape(-1)))
+    for w in (vw, shifted(zk, vw)):
+        rc, got = zk.matmul_sumcheck_prove(seed, vx, D0, D1, w, D2)
+        assert rc == 0 and got == want
+        assert zk.matmul_sumcheck_verify(seed, got, D0, D1, D2, X=vx, W=w) == 0
