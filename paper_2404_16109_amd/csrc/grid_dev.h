@@ -64,8 +64,8 @@ struct GridArgs {
     GridJob job[kGridMaxJobs];
     int njobs;
     uint32_t waves;
-    uint32_t* partials;  // value v, share c: eight words at 8 (most_chunks v + c)
-    uint32_t most_chunks;
+    uint32_t* partials;  // value v, share c: eight words at 8 (shares v + c)
+    uint32_t shares;     // of the job that has most
     Fr beta;
 };
 
@@ -164,7 +164,7 @@ static __global__ void __launch_bounds__(kBlock) k_grid(GridArgs args) {
     if ((threadIdx.x & 63) == 0) {
         if (weighted && g.eq.has_hi && !g.hi_by_lane)
             tot = fr_mul(tot, fr_load(g.eq.pool, g.eq.stride, g.eq.hi_off + (from >> g.eq.lbits)));
-        uint4* out = (uint4*)args.partials + 2 * ((size_t)(g.first_value + value) * args.most_chunks + chunk);
+        uint4* out = (uint4*)args.partials + 2 * ((size_t)(g.first_value + value) * args.shares + chunk);
         out[0] = make_uint4(tot.l[0], tot.l[1], tot.l[2], tot.l[3]);
         out[1] = make_uint4(tot.l[4], tot.l[5], tot.l[6], tot.l[7]);
     }
@@ -179,7 +179,7 @@ struct GridSumArgs {
     int njobs;
     uint32_t values;
     const uint32_t* partials;
-    uint32_t most_chunks;
+    uint32_t shares;
     uint32_t* out;
     uint32_t* words;   // the mailbox
     uint32_t* ticket;
@@ -193,10 +193,15 @@ static __global__ void __launch_bounds__(kBlock) k_grid_sum(GridSumArgs args) {
     int q = 0;
     while (q + 1 < args.njobs && value >= args.first_value[q + 1]) ++q;
     Fr v = fr_zero();
-    if (live) {
-        for (uint32_t c = lane; c < args.chunks[q]; c += LANES) {
-            const uint4* at = (const uint4*)args.partials + 2 * ((size_t)value * args.most_chunks + c);
-            const uint4 lo = at[0], hi = at[1];
+    const uint4* at = (const uint4*)args.partials + 2 * ((size_t)value * args.shares + lane);
+    if (live && lane < args.chunks[q]) {
+        const uint4 lo = at[0], hi = at[1];
+        v = Fr{{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}};
+    }
+    if constexpr (LANES == 64) {
+        static_assert(kGridChunks <= 128, "two shares to a lane");
+        if (live && lane + 64 < args.chunks[q]) {
+            const uint4 lo = at[128], hi = at[129];
             v = fr_add(v, Fr{{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}});
         }
     }
@@ -291,13 +296,12 @@ struct GridPass {
     GridSumArgs sum;
     GridFoldArgs fold;
     uint32_t values = 0, fold_blocks = 0;
+    const uint32_t most_chunks;  // shares per sum the partial sums have room for
 
-    // most_chunks: shares per sum the partial sums have room for
-    explicit GridPass(uint32_t most_chunks = kGridChunks) {
+    explicit GridPass(uint32_t most = kGridChunks) : most_chunks(most) {
         memset(&grid, 0, sizeof grid);
         memset(&sum, 0, sizeof sum);
         memset(&fold, 0, sizeof fold);
-        grid.most_chunks = sum.most_chunks = most_chunks;
     }
     // Binds the `vars` (0..3) last challenges: n elements from src into dst.
     void add_fold(const uint32_t* src, size_t ss, uint32_t* dst, size_t ds, size_t n, int vars, bool rows = false) {
@@ -308,11 +312,12 @@ struct GridPass {
     uint32_t add(const uint32_t* x, size_t xs, const uint32_t* y, size_t ys, int vars, int kind, size_t P, const EqSplit& eq) {
         GridJob& g = grid.job[grid.njobs];
         g = GridJob{x, y, xs, ys, eq, (uint32_t)P, 64, 1, grid.waves, values, vars, kind, 0};
-        while ((size_t)g.span * grid.most_chunks < P) g.span *= 2;
+        while ((size_t)g.span * most_chunks < P) g.span *= 2;
         g.hi_by_lane = eq.has_hi && g.span > (1u << eq.lbits);
         g.chunks = (uint32_t)div_up(P, g.span);
         sum.first_value[grid.njobs] = values;
         sum.chunks[grid.njobs++] = g.chunks;
+        if (g.chunks > grid.shares) grid.shares = g.chunks;
         const uint32_t count = GridJob::values(vars, kind);
         grid.waves += count * g.chunks;
         values += count;
@@ -350,15 +355,13 @@ struct GridPass {
         sum.njobs = grid.njobs;
         sum.values = values;
         sum.partials = partials;
+        sum.shares = grid.shares;
         sum.out = out;
         sum.words = mb->words;
         sum.ticket = ticket;
         sum.seq = seq;
         hipLaunchKernelGGL(k_grid, dim3((grid.waves + 3) / 4), dim3(kBlock), 0, stream, grid);
-        uint32_t most = 0;
-        for (int q = 0; q < sum.njobs; ++q)
-            if (sum.chunks[q] > most) most = sum.chunks[q];
-        if (most <= 32) hipLaunchKernelGGL(k_grid_sum<32>, dim3((values + 7) / 8), dim3(kBlock), 0, stream, sum);
+        if (grid.shares <= 32) hipLaunchKernelGGL(k_grid_sum<32>, dim3((values + 7) / 8), dim3(kBlock), 0, stream, sum);
         else hipLaunchKernelGGL(k_grid_sum<64>, dim3((values + 3) / 4), dim3(kBlock), 0, stream, sum);
         ZK_HIP_TRY(hipGetLastError());
         return ZK_OK;
