@@ -221,7 +221,7 @@ struct VecDigestJob {
     LeafGather from;
     const uint32_t* host_row = nullptr;  // set by the launch: the row handed to the host
     uint32_t host_count = 0;
-    const uint8_t* shipped = nullptr;    // or the leaves' bytes, leaf_bytes each
+    uint8_t* shipped = nullptr;          // or the leaves' bytes, leaf_bytes each
     size_t leaf_bytes = 0;
 };
 
@@ -333,11 +333,15 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
 }
 
 // The rest of a tree, from the row the device has handed over: consecutive fours
-// (a last pair in twos) down to one digest.
+// (a last pair in twos) down to one digest.  Leaves' bytes are the caller's witness: they do
+// not stay in memory that outlives the call (1 us for 32 leaves).
 static void vec_digest_finish(uint8_t out[32], const VecDigestJob& job) {
     uint8_t row[kTreeHostRow * 32];
     uint32_t cnt = job.host_count;
-    if (job.shipped) host::Sha256::hash_each(row, job.shipped, job.leaf_bytes, cnt);
+    if (job.shipped) {
+        host::Sha256::hash_each(row, job.shipped, job.leaf_bytes, cnt);
+        memset(job.shipped, 0, job.leaf_bytes * cnt);
+    }
     for (uint32_t i = 0; i < cnt * 8 && !job.shipped; ++i) {
         const uint32_t v = __builtin_bswap32(job.host_row[i]);  // hash-state words: big-endian words of the digest's bytes
         memcpy(row + 4 * i, &v, 4);
@@ -1969,11 +1973,9 @@ static int verify_core(const VerifyCall& c) {
             ZK_HIP_TRY(hipStreamSynchronize(stream));
         }
         auto value_is = [&](int job, const F& want) { return equal(from_dev(mb->words + 8 * job), want); };
-        auto digest_is = [&](int tree, const uint8_t* want) {
-            uint8_t got[32];
-            vec_digest_finish(got, trees[tree]);
-            return memcmp(got, want, 32) == 0;
-        };
+        uint8_t tree_digests[2][32];  // of all trees, also where a value is rejected first: finishing clears the leaves' bytes
+        for (int q = 0; q < ntrees; ++q) vec_digest_finish(tree_digests[q], trees[q]);
+        auto digest_is = [&](int tree, const uint8_t* want) { return memcmp(tree_digests[tree], want, 32) == 0; };
         if (!value_is(job_t, f[4])) return ZK_E_REJECT;
         if (!wit) continue;
         if (wit->S.limbs && !have_s) return ZK_E_BADARG;
