@@ -16,7 +16,7 @@
 //
 // What computes a round's sums is decided by plan_round.  From a vector of field
 // elements the first pass over A and S yields the sums of the first TWO rounds
-// (round01_dev.h) and the third round's kernel binds both variables at once; in the
+// (k_round_first_two) and the third round's kernel binds both variables at once; in the
 // large folding rounds the kernel sums one side of the round (X = 0 or X = 1) and
 // the other side follows here from the running claim; the rounds of the last
 // variables come several from one pass (grid_dev.h), the very last are the host's.
@@ -710,7 +710,7 @@ static bool round_on_29_bits(int n, int h, int k) {
     return k >= 1 && k < h && ((size_t)1 << (n - k - 1)) > kSmallPairs;
 }
 
-// Whether the first pass over the data serves the first two rounds (round01_dev.h)
+// Whether the first pass over the data serves the first two rounds (k_round_first_two)
 // and both variables are bound at once afterwards: the three rounds must all bind data
 // variables only, and be long.
 static bool first_two_rounds_share_a_pass(int n, int h, bool from_ints) {
@@ -1632,7 +1632,7 @@ static int prove_core(const ProveCall& c) {
                 sA1 = hs[4];
             } else if (plan.kind == kRoundFirstTwo) {
                 // the pass has summed, with the NEXT round's weights, what this round and the next are made of
-                // (round01_dev.h): this round's leading coefficient splits by the next variable
+                // (k_round_first_two): this round's leading coefficient splits by the next variable
                 for (int q = 0; q < 9; ++q) I.pass01[q] = from_dev(sums + 8 * q);
                 for (int q = 0; q < 5; ++q) I.pass01[q] = add(mul(I.pass01[q], inv32), from_u64(q < 4 ? 2 : 4));
                 q0 = q1 = one();

@@ -18,7 +18,6 @@
 // 32-bit words again.
 #pragma once
 #include "outer_dev.h"
-#include "round01_dev.h"
 #include "round29_dev.h"
 #include "small_dev.h"
 #include "tlookup_kernels.h"
@@ -205,8 +204,30 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 
     }
 }
 
-// ---- the first pass, serving the first two rounds (round01_dev.h) -------------------
+// ---- the first pass, serving the first two rounds ------------------------------------
 //
+// The first round binds x_0, the second x_1.  A "quad" is the four entries of an array
+// whose indices differ in those two bits only: y_c at p + c Q, c = 2 x_0 + x_1, Q a
+// quarter of the array's length.  After the first challenge r the second round's pair is
+//   (y'_0, y'_1) = (y_00 + r (y_10 - y_00), y_01 + r (y_11 - y_01)),
+// so each of its sums is a polynomial of degree two in r whose coefficients are
+// sums over the quads that do not depend on r.  With w the second round's weight
+// of the quad, B(x, y) = sum w x y, and because A_i (S_i + beta) = 1 holds exactly
+// for every entry before any folding (so B(A_c, S_c + beta) = sum w = 1):
+//   q(0)  = 1 - r (1 - r) B(A_10 - A_00, S_10 - S_00)          [c20]
+//   q(1)  = 1 - r (1 - r) B(A_11 - A_01, S_11 - S_01)          [c21]
+//   q_inf = qd + r (T - qd - qe) + r^2 qe, with
+//           qd = B(A_01 - A_00, S_01 - S_00),  T = B(A_11 - A_10, S_11 - S_10),
+//           qe = B(A_11 - A_01 - A_10 + A_00, S_11 - S_01 - S_10 + S_00)
+//   sA(x_1) = sum A_0x + r (sum A_1x - sum A_0x)
+// and the first round's own leading coefficient is (1 - u_1) c20 + u_1 c21.  The
+// pass therefore gives five sums of products and the four sums of A, the host
+// forms both rounds' messages, and the next pass over the data binds two
+// variables at once.
+//
+// Entries are fully reduced (below r); w is normalized and below r.
+static constexpr int kRound01MaxQuads = 16;  // quads per thread (the sums of A are normalized after every seven)
+
 // Workgroup b covers the quads p in [b * block_span, (b + 1) * block_span) of the
 // first quarter of the arrays (entries at p + c * quarter, c = 0..3), at most
 // kRound01MaxQuads per thread.  Weights are the SECOND round's (its pairs are
@@ -231,7 +252,7 @@ struct DataRound01Args {
     size_t pstrideD;
     uint32_t* partT;
     size_t pstrideT;
-    Fr beta;  // (k_round_first_two)
+    Fr beta;
 };
 
 // The sums are taken on the matrix cores (outer_dev.h).  With X_c = w A_c and S_c the
@@ -243,7 +264,7 @@ struct DataRound01Args {
 //   qe = 4 - beta sum W - M_x0 - M_x1 - M_0x - M_1x + M_xx.
 // partD gets these without the constants 2 and 4 and times 2^5 (w is in the form for two
 // 29-bit products).  On the vector ALU remain four multiplications per quad and A's sums,
-// some 1250 instructions (on the vector ALU alone the pass took 2300, round01_dev.h, and two
+// some 1250 instructions (on the vector ALU alone the pass took 2300 and two
 // wavefronts per SIMD kept it 70 % busy); entries are asked for four ahead of their use.
 // Issue and HBM bind about equally: 2^25 entries 760 -> 520 us, 4.1 TB/s; a proof of 2^20
 // entries in all 731 -> 709 us, one of 2^17 524 -> 500.

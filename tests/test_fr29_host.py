@@ -289,67 +289,7 @@ def test_round29_eight_lazy_rounds_in_a_row(lib):
     assert max(value_of(v) for v in vals) < 17 * R
 
 
-def _round01_thread(lib, entries, weights):
-    quads = len(weights)
-    e = np.concatenate([np.concatenate(q) for q in entries]).astype(np.uint32)
-    w = np.concatenate(weights).astype(np.uint32)
-    out = np.zeros(81, np.uint32)
-    peak = ctypes.c_uint64(0)
-    lib.c_round01_thread(quads, ptr(e), ptr(w), ptr(out), ctypes.byref(peak))
-    return out.reshape(9, 9), peak.value
-
-
-def _check_round01_thread(lib, entries, weights):
-    """The per-thread schedule of the first pass when it serves two rounds, against Python integers: the five sums of
-    products and the four sums of A, and every bound the kernel's sums across lanes rely on."""
-    inv = pow(2, -261, R)
-    out, peak = _round01_thread(lib, entries, weights)
-    want = [0] * 9
-    for quad, w in zip(entries, weights):
-        a = [value_of(v) for v in quad[:4]]
-        s = [value_of(v) for v in quad[4:]]
-        wv = value_of(w)
-        B = lambda x, y: x * wv * inv * y
-        want[0] += B(a[2] - a[0], s[2] - s[0])
-        want[1] += B(a[3] - a[1], s[3] - s[1])
-        want[2] += B(a[1] - a[0], s[1] - s[0])
-        want[3] += B(a[3] - a[2], s[3] - s[2])
-        want[4] += B(a[3] - a[1] - a[2] + a[0], s[3] - s[1] - s[2] + s[0])
-        for c in range(4):
-            want[5 + c] += a[c]
-    got = [value_of(out[q]) for q in range(9)]
-    for q in range(9):
-        assert got[q] % R == (want[q] * inv if q < 5 else want[q]) % R, q
-    # what the sums over a wavefront (64 lanes) and then over four wavefronts need
-    assert all(g < 2 * R for g in got) and all(int(v) <= M29 for q in range(9) for v in out[q][:8])
-    assert peak <= 2 ** 32 - 8               # no lazy limb wrapped before a normalization
-    return peak
-
-
-def test_round01_thread_schedule_at_its_bounds(lib):
-    """Sixteen quads per thread (the most the prover gives one), every entry the largest a reduced element can be or
-    zero, so that every difference is at an extreme, with the largest weight: the worst case for the accumulators of
-    the first pass."""
-    rmax = limbs_of(R - 1)
-    zero = arr([0] * 9)
-    worst = 0
-    patterns = [[rmax] * 8,
-                [zero, rmax, rmax, zero, rmax, zero, zero, rmax],
-                [rmax, zero, zero, rmax, zero, rmax, rmax, zero],
-                [zero, zero, rmax, rmax, rmax, rmax, zero, zero],
-                [rmax, zero, rmax, zero, zero, rmax, zero, rmax]]
-    for pat in patterns:
-        worst = max(worst, _check_round01_thread(lib, [pat] * 16, [rmax] * 16), _check_round01_thread(lib, [pat] * 7, [rmax] * 7),
-                    _check_round01_thread(lib, [pat] * 14, [rmax] * 14))
-    assert worst > 2 ** 31                   # the test does reach the region the bound is about
-    rng = random.Random(21)
-    for quads in (1, 2, 3, 5, 8, 9, 15, 16):
-        entries = [[limbs_of(rng.randrange(R)) for _ in range(8)] for _ in range(quads)]
-        weights = [limbs_of(rng.randrange(R)) for _ in range(quads)]
-        _check_round01_thread(lib, entries, weights)
-
-
-def test_round01_sums_give_the_second_round(lib):
+def test_round01_sums_give_the_second_round():
     """With A_c (S_c + beta) = 1 for every entry, the second round's sums after a first challenge r are the polynomials
     in r that the prover forms from the pass's sums: checked here on Python integers against folding first."""
     rng = random.Random(22)
@@ -374,6 +314,42 @@ def test_round01_sums_give_the_second_round(lib):
     t = r * (1 - r)
     assert q0 == (wsum - t * c20) % R and q1 == (wsum - t * c21) % R     # the weights of a whole round sum to one
     assert qinf == (qd + r * (T - qd - qe) + r * r * qe) % R
+
+
+def test_round01_class_sums_give_the_pass_sums():
+    """What the first pass adds up (products w A_c S_d of c != d by class, and w A_c) gives its five sums as the kernel and the
+    host form them: 2^5 from the weights' form and 2^-256 from the products' on the device, the constants 2 and 4 and 2^-5 on
+    the host, each workgroup with the high factor of its weights."""
+    rng = random.Random(23)
+    beta = rng.randrange(R)
+    inv256, inv32 = pow(2, -256, R), pow(32, -1, R)
+    got, want, wsum = [0] * 5, [0] * 5, 0
+    for _ in range(3):                                                   # workgroups
+        high = rng.randrange(R)
+        M, W = [0] * 5, [0] * 4
+        for _ in range(4):                                               # quads
+            S = [rng.randrange(R) for _ in range(4)]
+            A = [pow(beta + s, -1, R) for s in S]
+            low = rng.randrange(R)
+            w = low * high % R
+            wsum += w
+            d = lambda y, i, j: y[i] - y[j]
+            for q, (i, j) in enumerate([(2, 0), (3, 1), (1, 0), (3, 2)]):  # c20, c21, qd, T
+                want[q] += w * d(A, i, j) * d(S, i, j)
+            want[4] += w * (A[3] - A[1] - A[2] + A[0]) * (S[3] - S[1] - S[2] + S[0])
+            x = [a * low * 32 % R for a in A]                            # of x 2^256 and s 2^256 a sum is x s 2^512 2^-256
+            for c in range(4):
+                W[c] += x[c]
+                for e in range(4):
+                    if e != c:
+                        M[(c & 1) if c ^ e == 2 else 2 + (c >> 1) if c ^ e == 1 else 4] += x[c] * 2 ** 256 * S[e] * 2 ** 256 * inv256
+        pairs = [(0, 2), (1, 3), (0, 1), (2, 3)]
+        for q in range(5):
+            weights = W[pairs[q][0]] + W[pairs[q][1]] if q < 4 else sum(W)
+            mixed = M[q] if q < 4 else M[0] + M[1] + M[2] + M[3] - M[4]
+            got[q] -= high * (beta * weights * 2 ** 256 + mixed)
+    for q in range(5):
+        assert (got[q] * inv32 * inv256 + (2 if q < 4 else 4) * wsum - want[q]) % R == 0, q
 
 
 def test_mul3_add_is_three_products_under_one_reduction(lib):
