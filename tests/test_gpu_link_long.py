@@ -1,7 +1,8 @@
 """The linking sumcheck's long rounds (csrc/link_long.h), which start at 2^17 scores: rows of one entry to all of them, so
-that row variables end before, inside and behind a pass and the low weight tables, one and two segments, vectors and
-integers that allow no 16-byte loads, field elements over the whole range, integers at their largest.  Exact arithmetic:
-equality with the oracle."""
+that row variables end before, inside and behind a pass and the low weight tables, one pass and two or three of them (from 2^19
+scores on, 2^20 of integers, the later ones over arrays that were bound in place), one and two segments, vectors and integers
+that allow no 16-byte loads, field elements over the whole range, integers at their largest.  Exact arithmetic: equality with the
+oracle."""
 import random
 
 import numpy as np
@@ -31,7 +32,10 @@ def shifted(zk, v):
 
 @pytest.mark.parametrize("log_rows,log_cols,K,aligned", [
     (17, 0, 2, True), (15, 2, 1, True), (12, 5, 2, False), (9, 8, 2, True), (7, 10, 1, False), (6, 11, 2, True), (5, 12, 2, True),
-    (4, 13, 1, True), (1, 16, 2, True), (0, 17, 2, True), (10, 8, 2, True), (7, 11, 2, False)])
+    (4, 13, 1, True), (1, 16, 2, True), (0, 17, 2, True), (10, 8, 2, True), (7, 11, 2, False),
+    # the second pass starts at variable 2: rows end before it, where it starts, inside, behind it
+    (1, 18, 1, True), (2, 17, 1, False), (3, 16, 1, True), (16, 3, 1, True),
+    (0, 19, 2, True), (2, 17, 2, True), (3, 16, 2, False), (19, 0, 2, True), (5, 16, 1, True)])
 def test_vectors(zk, orc, log_rows, log_cols, K, aligned):
     rows, cols = 1 << log_rows, 1 << log_cols
     rng = random.Random(1000 * log_rows + 10 * log_cols + K)
@@ -56,7 +60,9 @@ def test_vectors(zk, orc, log_rows, log_cols, K, aligned):
 
 @pytest.mark.parametrize("log_rows,log_cols,K,out_bits,aligned", [
     (17, 0, 2, 30, True), (14, 3, 1, 32, True), (12, 5, 2, 30, False), (6, 11, 2, 16, True), (5, 12, 1, 16, False),
-    (2, 15, 2, 30, True), (0, 17, 1, 20, True), (7, 11, 2, 29, True), (10, 9, 2, 30, False)])
+    (2, 15, 2, 30, True), (0, 17, 1, 20, True), (7, 11, 2, 29, True), (10, 9, 2, 30, False),
+    # the second pass starts at variable 3
+    (2, 18, 1, 32, True), (4, 16, 1, 20, False), (17, 3, 1, 30, True), (1, 19, 2, 30, True), (3, 17, 2, 29, False), (4, 16, 2, 30, True)])
 def test_integers(zk, orc, log_rows, log_cols, K, out_bits, aligned):
     rows, cols = 1 << log_rows, 1 << log_cols
     gen = np.random.default_rng(100 * log_rows + log_cols + K)
