@@ -718,9 +718,9 @@ static void small_products_run(uint32_t* a, uint32_t* b, size_t PC, const int16_
 static void rowdot_run(uint32_t* b, size_t PR, const uint32_t* M, size_t ms, size_t R, size_t C, const uint32_t* e1,
                        size_t e1s, hipStream_t stream) {
     // A workgroup of k_rowdot does four rows: of few rows it leaves compute units idle, of short ones there is nothing to
-    // gain.  Whole proofs, a workgroup per row and four rows per workgroup: 512 x 32768: 262 and 275 us, 128 x 32768: 163
-    // and 225, 768 x 32768: 334 and 306, 1024 x 4096: 144 and 136, 1024 x 1024: 117 and 113, 768 x 1024: 114 and 118,
-    // 1024 x 128: alike
+    // gain.  Whole proofs with eight rows of X, a workgroup per row of W and four rows per workgroup: 128 x 32768: 164 and
+    // 228 us, 512 x 32768: 266 and 281, 768 x 32768: 313 and 289, 5120 x 5120: 314 and 289, 1024 x 4096: 142 and 132,
+    // 1024 x 1024: 119 and 116, 768 x 1024: alike, 1024 x 128: alike
     if (R < 768 || R * C < (size_t)1 << 20)
         hipLaunchKernelGGL(k_rowdot_short, dim3((unsigned)PR), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s);
     else hipLaunchKernelGGL(k_rowdot, dim3((unsigned)div_up(PR, kDotRows)), dim3(kBlock), 0, stream, b, PR, M, ms, R, C, e1, e1s, PR);

@@ -28,8 +28,8 @@ __device__ __forceinline__ uint32_t fr_hash(const Fr& a) {
 }
 
 // What the kernels that work on tables need of each; blockIdx.y is the table.  The tables of
-// a call share launches: three short ones took three times as long one after the other
-// (counting and inverse of three tables of 2^10 to 2^16 rows: XXX us).
+// a call share launches: short ones took as long one after the other as launches do (three
+// tables of 2^10 to 2^16 rows: counting 262 -> 142 us, inversions 160 -> 115, with the trips).
 struct TableJob {
     const uint32_t* T;
     size_t ts;
