@@ -1162,6 +1162,8 @@ static int prove_core(const ProveCall& c) {
             a.pstride = inst[0].w.part_blocks * 6;
             a.bad = I.w.flags + 2;
             a.bad_words = mb->words + kMailboxBad + 2 * i;
+            // a row per thread while there is room (against four: 2^16 rows 16 -> 8 us, 2^8, 2^20 and 2^22 alike); the
+            // 16 values of eight tables take partT's 6 kMaxPartialBlocks places at a quarter of the workgroups
             blocks = std::max(blocks, grid_for(I.N, kBlock, kMaxPartialBlocks / 4));
         }
         jobs.values = 2 * (uint32_t)K;
