@@ -570,6 +570,18 @@ int zkmi_selftest_resident_wait(void* ws, size_t ws_bytes, void* stream);
  * Returns the number of rounds, ZK_E_BUFSZ if cap_rounds is below it. */
 int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int32_t* out, size_t cap_rounds);
 
+/* The same where the long rounds read the rows of the table instead of S and A: tables
+ * of up to 2^16 rows, tensors of 2^19 entries or more and at least eight times the
+ * table's, as a vector with or without row numbers or as integers (the plan above is
+ * that of all others).  Four integers per round as above, but
+ *   [0] may be 9: the first round of a long pass, which serves this round and, if it
+ *       says two variables, the next (of kind 8);
+ *   [1] may be 5: the rows of the table; 3 are the passes' own planes;
+ *   [2], [3] of kind 9: the variables it serves; the challenges it binds, plus 8 if it
+ *       leaves words.
+ * ZK_E_BADARG for shapes whose rounds do not. */
+int zkmi_selftest_tlookup_rows_plan(size_t D, size_t N, size_t K, int32_t* out, size_t cap_rounds);
+
 /* The rounds a single tlookup proof leaves to the host (kind 7 above), on
  * arrays and challenges of the caller's choosing; no GPU is touched.  All
  * pointers are host memory, all elements canonical.  A, S: n_data elements

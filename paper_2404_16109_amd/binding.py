@@ -74,6 +74,7 @@ def _load():
         "zkmi_sha256": (i32, [ctypes.c_char_p, sz, ctypes.c_char_p, i32]),
         "zkmi_selftest_resident_wait": (i32, [vp, sz, vp]),
         "zkmi_selftest_tlookup_plan": (i32, [sz, sz, sz, i32, P(ctypes.c_int32), sz]),
+        "zkmi_selftest_tlookup_rows_plan": (i32, [sz, sz, sz, P(ctypes.c_int32), sz]),
         "zkmi_selftest_host_rounds": (i32, [P(fr_t)] * 5 + [sz, sz, P(fr_t), P(fr_t), P(fr_t), P(fr_t), P(fr_t)]),
         "zkmi_profile_enable": (i32, [i32]),
         "zkmi_profile_reset": (i32, []),
@@ -151,7 +152,7 @@ def _load():
 
 
 _lib = _load()
-EXPORTS = ["zkmi_version", "zkmi_thread_init", "zkmi_thread_release", "zkmi_selftest_staging", "zkmi_sha256", "zkmi_selftest_resident_wait", "zkmi_selftest_tlookup_plan", "zkmi_selftest_host_rounds", "zkmi_profile_enable", "zkmi_profile_reset", "zkmi_profile_query", "fr_constants", "fr_from_i32", "fr_from_canonical", "fr_to_canonical", "fr_add", "fr_sub",
+EXPORTS = ["zkmi_version", "zkmi_thread_init", "zkmi_thread_release", "zkmi_selftest_staging", "zkmi_sha256", "zkmi_selftest_resident_wait", "zkmi_selftest_tlookup_plan", "zkmi_selftest_tlookup_rows_plan", "zkmi_selftest_host_rounds", "zkmi_profile_enable", "zkmi_profile_reset", "zkmi_profile_query", "fr_constants", "fr_from_i32", "fr_from_canonical", "fr_to_canonical", "fr_add", "fr_sub",
            "fr_mul", "fr_add_scalar", "fr_mul_scalar", "fr_axpy", "fr_batch_inverse_workspace_bytes",
            "fr_batch_inverse", "fr_sum_workspace_bytes", "fr_sum", "fr_sum_noalloc", "fr_eq_table", "fr_mle_eval_workspace_bytes",
            "fr_mle_eval", "tlookup_workspace_bytes", "tlookup_multiplicities", "tlookup_proof_bytes", "tlookup_prove",
@@ -240,6 +241,13 @@ def zkmi_selftest_tlookup_plan(D, N, K=1, from_ints=False):
     rc = _lib.zkmi_selftest_tlookup_plan(D, N, K, 1 if from_ints else 0, out, 32)
     rounds = [tuple(out[4 * k:4 * k + 4]) for k in range(max(rc, 0))]
     return rc, rounds
+
+
+def zkmi_selftest_tlookup_rows_plan(D, N, K=1):
+    """The same where the long rounds read the table's rows."""
+    out = (ctypes.c_int32 * (4 * 32))()
+    rc = _lib.zkmi_selftest_tlookup_rows_plan(D, N, K, out, 32)
+    return rc, [tuple(out[4 * k:4 * k + 4]) for k in range(max(rc, 0))]
 
 
 def zkmi_selftest_host_rounds(A, S, B, M, T, u_rest, beta, challenges):

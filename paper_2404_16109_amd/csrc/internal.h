@@ -64,9 +64,10 @@ void launch_final_sum(const uint32_t* partials, size_t pstride, unsigned nblocks
 
 // Same for two partial arrays at once: nv1 values per block from the first, then
 // nv2 from the second (nv2 may be 0); totals at out_words[8q..], first array first.
+// note: two words of device memory that go out beside them, to note_out, if not null.
 void launch_final_sum2(const uint32_t* part1, size_t pstride1, int nv1, const uint32_t* part2, size_t pstride2, int nv2,
                        unsigned nblocks, uint32_t* out_words, uint32_t* words, uint32_t seq, uint32_t* ticket,
-                       hipStream_t stream);
+                       hipStream_t stream, const uint32_t* note = nullptr, uint32_t* note_out = nullptr);
 
 // sum_i a_i into mailbox words [0, 8).
 size_t sum_scratch_bytes(size_t n);

@@ -54,24 +54,6 @@ static __global__ void __launch_bounds__(kBlock) k_long_operands(const uint32_t*
     outer_save(blockIdx.y ? rlo_ops : lo_ops, blockIdx.x * 4 + wave, outer_operand(v.l, stage + wave * kOuterStage));
 }
 
-// Adds up a value's `count` partial sums, one workgroup per value.
-static __global__ void __launch_bounds__(kBlock) k_long_total(const uint32_t* partials, size_t pstride, unsigned count, uint32_t* out_words,
-                                                              uint32_t* words, uint32_t seq, uint32_t* ticket) {
-    __shared__ uint32_t lds[4 * 8];
-    Fr acc[1] = {fr_zero()};
-    for (unsigned b = threadIdx.x; b < count; b += kBlock) acc[0] = fr_add(acc[0], fr_load(partials, pstride, (size_t)blockIdx.x * count + b));
-    block_sum<1, 4>(acc, lds);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) out_words[8 * blockIdx.x + k] = acc[0].l[k];
-        mailbox_written();
-        if (atomicAdd(ticket, 1u) == gridDim.x - 1) {
-            *ticket = 0;
-            mailbox_publish(words, seq);
-        }
-    }
-}
-
 // The products of two arrays of 4 P elements by class (class 3 a + b: a, b = 0, 1 or 2
 // for mixed in the first and the second variable).  A workgroup takes `span` positions,
 // its wavefronts a quarter each.  Per position four multiplications by the weight remain

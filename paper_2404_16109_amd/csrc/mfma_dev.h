@@ -62,11 +62,14 @@ __device__ __forceinline__ void toeplitz_store(uint8_t* matrix, const uint32_t (
 
 // acc of a tile of 32 elements (lane l: element l % 32, rows 8 g + 4 (l / 32) + t for
 // g, t = 0..3, i.e. digits 0..3 of limbs g' = 2 g + l / 32) -> four limbs, 64 bits signed.
+// As multiply-adds by powers the compiler cannot see through: four instructions a limb,
+// where shifts, sign extensions and 64-bit additions are twelve.
 __device__ __forceinline__ void digits_to_limbs(int64_t (&limb)[4], const v16i& acc) {
+    int unit = 1, d1 = 1 << 8, d2 = 1 << 16, d3 = 1 << 24;
+    asm("" : "+s"(unit), "+s"(d1), "+s"(d2), "+s"(d3));
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-        limb[g] = (int64_t)acc[4 * g] + (int64_t)acc[4 * g + 1] * (1 << 8) + (int64_t)acc[4 * g + 2] * (1 << 16) +
-                  (int64_t)acc[4 * g + 3] * (1 << 24);
+        limb[g] = ((((int64_t)acc[4 * g] * unit + (int64_t)acc[4 * g + 1] * d1) + (int64_t)acc[4 * g + 2] * d2) + (int64_t)acc[4 * g + 3] * d3);
 }
 
 // Two tiles' half limbs -> all eight limbs of one element per lane: lanes 0..31 get

@@ -100,6 +100,28 @@ __device__ __forceinline__ OuterOperand outer_get(const uint8_t* stage) {
     return o;
 }
 
+// Sixteen bytes from `from` (each lane its own) to LDS, lane l's at lds + 16 l, without a trip
+// through registers; not waited for (vector_loads_done).  Inline, as the compiler would wait
+// for it at the next LDS access of whatever address; its own waits count too few loads in
+// flight and so are never too short.
+__device__ __forceinline__ void load_to_lds(const void* from, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(from), "s"(lds) : "memory", "m0");
+}
+// The same from a place all lanes share and an offset of each.
+__device__ __forceinline__ void load_to_lds(const void* from, uint32_t offset, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(from), "s"(lds) : "memory", "m0");
+}
+// Where in LDS p lies, as those take it: uniform.
+__device__ __forceinline__ uint32_t lds_place(const uint8_t* p) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)p);
+}
+// Waits until at most LATER of this wavefront's vector memory accesses are on their way: they
+// complete in order, so all but the last LATER are done.
+template <int LATER = 0>
+__device__ __forceinline__ void vector_loads_done() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LATER) : "memory"); }
+// This wavefront's LDS reads so far have come back: what they read may be overwritten.
+__device__ __forceinline__ void lds_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 __device__ __forceinline__ OuterOperand outer_stage(const uint32_t (&digits)[8], uint8_t* stage) {
     outer_put(digits, stage);
     return outer_get(stage);
@@ -150,6 +172,9 @@ __device__ __forceinline__ OuterOperand outer_column(int n) {
 // assert their positions per workgroup times products per position.
 // SUMS: the last accumulator's columns are values by themselves (outer_column): out(N - 1,
 // column, sum_i 2^(8 i) C_ij mod r) for every column.
+template <int N, int GROUP, bool SUMS, class Out>
+__device__ __forceinline__ void outer_values(const int* sums, Out&& out);
+
 template <int N, int GROUP, bool SUMS = false, class Out>
 __device__ __forceinline__ void outer_close(const v16i (&acc)[N], int* sums, Out&& out) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -168,10 +193,27 @@ __device__ __forceinline__ void outer_close(const v16i (&acc)[N], int* sums, Out
             for (int r = 0; r < 16; ++r) atomicAdd(&sums[(q * 16 + r) * 64 + lane], acc[q][r]);
     }
     __syncthreads();
+    outer_values<N, GROUP, SUMS>(sums, out);
+}
+
+// The second half of it: from the workgroup's sums in LDS (accumulator q's at 1024 q), for
+// workgroups of any number of wavefronts.  outer_sums_clear (all threads, between barriers) and
+// outer_sums_add make such sums of accumulators that the wavefronts hold different ones of.
+template <int N>
+__device__ __forceinline__ void outer_sums_clear(int* sums) {
+    for (unsigned k = threadIdx.x; k < N * 1024; k += blockDim.x) sums[k] = 0;
+}
+__device__ __forceinline__ void outer_sums_add(int* sums, int q, const v16i& acc) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) atomicAdd(&sums[(q * 16 + r) * 64 + (threadIdx.x & 63)], acc[r]);
+}
+template <int N, int GROUP, bool SUMS, class Out>
+__device__ __forceinline__ void outer_values(const int* sums, Out&& out) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const ToepBias bias = outer_bias();
     // two accumulators at a time: lanes 0..31 take the columns of the first, the others those of the second
 #pragma unroll 1
-    for (int q = 2 * wave; q < N; q += 8) {
+    for (int q = 2 * wave; q < N; q += blockDim.x / 32) {
         const int q1 = q + 1 < N ? q + 1 : q;
         v16i a, b;
 #pragma unroll

@@ -40,7 +40,8 @@ static const int kFinalThreads = 1024;
 __global__ void __launch_bounds__(kFinalThreads) k_final_sum2(const uint32_t* __restrict__ part1, size_t pstride1, int nv1,
                                                               const uint32_t* __restrict__ part2, size_t pstride2, int nv2,
                                                               unsigned nblocks, uint32_t* out_words, uint32_t* words,
-                                                              uint32_t seq, uint32_t* ticket) {
+                                                              uint32_t seq, uint32_t* ticket, const uint32_t* note,
+                                                              uint32_t* note_out) {
     __shared__ uint32_t lds[16 * 8];
     const int q = blockIdx.x;
     const bool first = q < nv1;
@@ -54,6 +55,10 @@ __global__ void __launch_bounds__(kFinalThreads) k_final_sum2(const uint32_t* __
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) out_words[8 * q + k] = acc[0].l[k];
+        if (note && q == 0) {
+            note_out[0] = note[0];
+            note_out[1] = note[1];
+        }
         mailbox_written();
         if (seq != 0) {
             unsigned done = atomicAdd(ticket, 1u);
@@ -67,9 +72,9 @@ __global__ void __launch_bounds__(kFinalThreads) k_final_sum2(const uint32_t* __
 
 void launch_final_sum2(const uint32_t* part1, size_t pstride1, int nv1, const uint32_t* part2, size_t pstride2, int nv2,
                        unsigned nblocks, uint32_t* out_words, uint32_t* words, uint32_t seq, uint32_t* ticket,
-                       hipStream_t stream) {
+                       hipStream_t stream, const uint32_t* note, uint32_t* note_out) {
     hipLaunchKernelGGL(k_final_sum2, dim3(nv1 + nv2), dim3(kFinalThreads), 0, stream, part1, pstride1, nv1, part2, pstride2,
-                       nv2, nblocks, out_words, words, seq, ticket);
+                       nv2, nblocks, out_words, words, seq, ticket, note, note_out);
 }
 
 void launch_final_sum(const uint32_t* partials, size_t pstride, unsigned nblocks, int nv, uint32_t* out_words,

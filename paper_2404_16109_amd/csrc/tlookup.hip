@@ -23,7 +23,9 @@
 #include "internal.h"
 #include "tlookup_kernels.h"
 #include "tlookup_round29.h"
+#include "tlookup_rows.h"
 #include "grid_dev.h"
+#include "long_host.h"
 #include "transcript.h"
 
 #include <algorithm>
@@ -238,7 +240,7 @@ static void launch_leaves_to_host(const VecLeavesArgs& lv, hipStream_t stream) {
 }
 
 // The jobs that have rows (LeafGather) all compare them with S, or all with the
-// integers, or none: by `ints` and whether they have an S.
+// integers, or none: by `ints` and whether they have an S; those that are only hashed do not.
 static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Mailbox* mb, uint32_t seq, uint32_t* ticket,
                              hipStream_t stream, const SmallSource* ints = nullptr) {
     if (njobs < 1 || njobs > kDigestMaxJobs) return ZK_E_BADARG;
@@ -272,11 +274,15 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
     lv.seq = more ? 0 : seq;
     lv.groups = blocks;
     int mode = kLeafPlain;
-    for (int q = 0; q < njobs; ++q)
-        if (jobs[q].from.rows) mode = jobs[q].from.S ? kLeafRowsCheck : ints ? kLeafRowsInts : kLeafRows;
+    for (int q = 0; q < njobs; ++q) {
+        const LeafGather& from = jobs[q].from;
+        if (from.hash_only && mode == kLeafPlain) mode = kLeafRowsHash;
+        else if (from.rows && !from.hash_only) mode = from.S ? kLeafRowsCheck : ints ? kLeafRowsInts : kLeafRows;
+    }
     size_t all_leaves = 0;
     for (int q = 0; q < njobs; ++q) all_leaves += cnt[q];
     if (all_leaves <= kHostLeaves && host::Sha256::use_sha_instructions()) {
+        if (mode == kLeafRowsHash) return ZK_E_BADARG;  // cannot happen: those have thousands of leaves
         static_assert(kHostLeaves * kVecLeaf * 32 <= kBulkDigests, "the leaves take the place of the digests");
         uint32_t elements = 0;
         for (int q = 0; q < njobs; ++q) {
@@ -301,6 +307,7 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
     if (mode == kLeafRowsCheck) launch_leaves<kLeafRowsCheck>(lv, stream);
     else if (mode == kLeafRowsInts) launch_leaves<kLeafRowsInts>(lv, stream);
     else if (mode == kLeafRows) launch_leaves<kLeafRows>(lv, stream);
+    else if (mode == kLeafRowsHash) launch_leaves<kLeafRowsHash>(lv, stream);
     else launch_leaves<kLeafPlain>(lv, stream);
     // up the trees, all rows in one launch, a factor of up to kTreeChunk per launch
     while (more) {
@@ -470,7 +477,7 @@ struct CountJob {
 };
 
 static TableJob table_job(const ProveWs& w, const fr_vec& T, size_t N) {
-    return TableJob{T.limbs, T.stride, (uint32_t)N, w.slots, w.cap_mask, w.flags, w.canon, w.rows, w.m, w.hist, w.hist_parts, w.M, w.B, nullptr};
+    return TableJob{T.limbs, T.stride, (uint32_t)N, w.slots, w.cap_mask, w.flags, w.canon, w.rows, w.m, w.hist, w.hist_parts, w.M, w.B, nullptr, nullptr, nullptr};
 }
 
 // Enqueues the multiplicities of up to kMaxTables tensors into their w.m; `seq` (not zero)
@@ -618,6 +625,14 @@ struct HostTail {
     }
 };
 
+// Positions per workgroup of a long pass (k_round_pair): as many as its weights' shared factor and its sums allow, but
+// at least 512 workgroups, two per compute unit, while a batch of 64 is left for each.
+static size_t pair_span(size_t P) {
+    size_t span = P / 512;
+    if (span < (size_t)kOuterBatch) span = (size_t)kOuterBatch;
+    return span < kOuterMaxSpan ? span : kOuterMaxSpan;
+}
+
 // ---- prover --------------------------------------------------------------------------------------
 //
 // One routine proves K instances with a single sumcheck over
@@ -651,7 +666,8 @@ enum RoundKind {
     kRoundFirstTwo = 5,  // k_round_first_two: the first pass, which yields the sums of the first two rounds
     kRoundNoPass = 6,    // the second round after kRoundFirstTwo: the host has everything, nothing is launched
     kRoundHost = 7,      // the host's (HostTail); the first of them fetches the arrays
-    kRoundGrid = 8       // its sums come from the grid of a pass over several variables; the first of them runs the pass
+    kRoundGrid = 8,      // its sums come from the grid of a pass over several variables; the first of them runs the pass
+    kRoundPair = 9       // the first round of a long pass over two variables (tlookup_rows.h); a second one is a kRoundGrid
 };
 enum SSource {
     kSFromCaller = 0,  // the caller's vector of field elements
@@ -659,6 +675,7 @@ enum SSource {
     kSFromWords = 2,   // the folded copy in the workspace, 32-bit words
     kSFromPlanes = 3,  // the folded copy in the workspace, 29-bit limb planes
     kSUnread = 4,      // the round reads no array
+    kSFromRows = 5,    // the rows of the table (tlookup_rows.h)
     kSNowhere = -1     // a plan this library has no kernel for: never launched
 };
 
@@ -676,9 +693,9 @@ struct RoundPlan {
     int kind;
     int s_source;
     bool table_round;  // the variable being bound is one of the table's
-    bool in32, out32;  // kRound29: the data arrays arrive as / leave as 32-bit words
+    bool in32, out32;  // kRound29: the data arrays arrive as / leave as 32-bit words (kRoundPair: leave)
     bool fold2;        // kRound29: binds the two previous variables at once (after kRoundFirstTwo, kRoundNoPass)
-    // kRoundGrid, kRoundHost
+    // kRoundGrid, kRoundPair, kRoundHost
     bool starts;              // the pass, or the hand-over, is this round's
     int vars, tvars;          // variables (of the table) the pass serves, when it starts
     int left;                 // rounds of the pass from this one on
@@ -717,6 +734,14 @@ static bool first_two_rounds_share_a_pass(int n, int h, bool from_ints) {
     return !from_ints && h >= 3 && round_on_29_bits(n, h, 2);
 }
 
+// Whether the long rounds read the table's rows (tlookup_rows.h): the first pass serves two rounds and a pass over two
+// variables follows, which needs three variables beyond those the last passes serve.  (With one or two, 2^17 and 2^18
+// entries, the first of the last passes binds the first two variables, from vectors.)  Tables of up to 2^16 rows: the
+// caches hold their rows, and all their variables are among the last ones.
+static bool rounds_by_row(int n, int h) {
+    return first_two_rounds_share_a_pass(n, h, false) && n - 2 > kPassVars && n - h <= kPassVars;
+}
+
 // What a pass, or the hand-over to the host, finds and leaves.
 static void plan_bound(RoundPlan& pl, RoundState& st, int vars, int tvars) {
     pl.starts = true;
@@ -734,13 +759,14 @@ static void plan_bound(RoundPlan& pl, RoundState& st, int vars, int tvars) {
 }
 
 // Round k of an instance of n variables, the last n - h of them the table's, in a call of K instances; moves the state on.
-static RoundPlan plan_round(int n, int h, int k, size_t K, bool from_ints, RoundState& st) {
+// by_row: the entries are rows of the table (rounds_by_row), whatever the caller's tensor is.
+static RoundPlan plan_round(int n, int h, int k, size_t K, bool from_ints, RoundState& st, bool by_row = false) {
     RoundPlan pl{};
     const int left = n - k;
     pl.table_round = k >= h;
     pl.s_source = kSUnread;
     // integers are the first two rounds' business, and the second of two rounds that share a pass needs none
-    const bool own = (from_ints && k < 2) || st.first_two;
+    const bool own = (from_ints && !by_row && k < 2) || st.first_two;
     if (st.on_host || (!own && left <= host_vars(K))) {
         pl.kind = kRoundHost;
         if (!st.on_host) plan_bound(pl, st, 0, 0);
@@ -762,12 +788,23 @@ static RoundPlan plan_round(int n, int h, int k, size_t K, bool from_ints, Round
         st.first_two = false;
         return pl;
     }
+    if (by_row && k > 0) {
+        // two variables, of which the second may be one of the last passes' (that many fewer for them) if it is not the
+        // table's; one where it is
+        plan_bound(pl, st, std::min(2, h - k), 0);
+        pl.kind = kRoundPair;
+        pl.s_source = k == 2 ? kSFromRows : kSFromPlanes;
+        pl.out32 = left - pl.vars <= kPassVars;
+        st.pass_left = pl.vars;
+        pl.left = st.pass_left--;
+        return pl;
+    }
     pl.in32 = st.lazy == 0;
     int lazy_after = 0;
     if (k == 0) {
-        st.first_two = first_two_rounds_share_a_pass(n, h, from_ints);
+        st.first_two = by_row || first_two_rounds_share_a_pass(n, h, from_ints);
         pl.kind = st.first_two ? kRoundFirstTwo : kRoundFirst;
-        pl.s_source = from_ints ? kSFromInts : kSFromCaller;
+        pl.s_source = by_row ? kSFromRows : from_ints ? kSFromInts : kSFromCaller;
     } else if (pl.table_round) {
         pl.kind = kRoundBoth;
         pl.s_source = k > 1 ? kSFromWords : from_ints ? kSNowhere : kSFromCaller;
@@ -821,7 +858,17 @@ struct Instance {
     RoundState state;            // what its rounds so far have left behind
     HostTail* tail = nullptr;    // once the host has the arrays
     bool gather = false;    // A is B by row, made while it is hashed
-    bool deferred = false;  // S_i = T[idx_i] is checked there too, not while counting
+    bool by_row = false;    // A and S are the table's rows until a challenge has bound them (tlookup_rows.h): A is only hashed
+    bool deferred = false;  // S_i = T[idx_i] is checked there too (by_row: in the first pass), not while counting
+    bool unchecked = false; // that first pass has not run yet
+
+    const uint32_t* rows() const { return idx ? idx : w.found; }
+    // Where the rows lie: those of the two passes behind the folded planes of A and S, what the hash of A reads where the
+    // words of folded S will be (rounds_by_row: N <= D / 8, so 8 D, 8 D and 4 D bytes at most).
+    uint4* rows_first() const { return w.A29 + D / 2; }
+    uint4* rows_pair() const { return w.S29 + D / 2; }
+    uint4* rows_hash() const { return (uint4*)w.Sf; }
+    DigitPlanes planes(uint4* base) const { return DigitPlanes{base, D / 4}; }
 };
 
 struct ProveCall {
@@ -971,6 +1018,8 @@ static int prove_core(const ProveCall& c) {
             // instance at fault is the one reported
             I.gather = c.by_rows || gather_by_default(I.N);
             I.deferred = defer_all && I.gather;
+            I.by_row = I.gather && rounds_by_row(I.n, I.h);
+            I.unchecked = I.by_row && I.deferred;
             counts[i] = CountJob{&I.w, I.S, I.idx, I.T, I.D, I.N, staged + at[i], I.deferred, I.idx ? nullptr : I.w.found};
         }
         ZK_TRY(count_rows(counts, (int)K, seq, mb, stream, true));
@@ -1065,7 +1114,11 @@ static int prove_core(const ProveCall& c) {
         for (size_t i = 0; i < K; ++i) {
             tables.job[i] = table_job(inst[i].w, inst[i].T, inst[i].N);
             if (!inst[i].gather) continue;
-            tables.job[i].rows_b = inst[i].w.rows_b;
+            tables.job[i].rows_b = inst[i].by_row ? inst[i].rows_first() : inst[i].w.rows_b;
+            if (inst[i].by_row) {
+                tables.job[i].rows_pair = inst[i].rows_pair();
+                tables.job[i].rows_hash = inst[i].rows_hash();
+            }
             rows = std::max(rows, inst[i].N);
         }
         if (rows && K == 1) hipLaunchKernelGGL(k_rows_of<1>, dim3(grid_for(rows)), dim3(kBlock), 0, stream, TableJobs<1>{{tables.job[0]}});
@@ -1084,12 +1137,13 @@ static int prove_core(const ProveCall& c) {
             Instance& I = inst[i];
             LeafGather from;
             if (I.gather) {
-                from.rows = I.idx ? I.idx : I.w.found;
+                from.rows = I.rows();
                 from.T = I.w.rows;
-                from.B = I.w.rows_b;
+                from.B = I.by_row ? I.rows_hash() : I.w.rows_b;
                 from.N = (uint32_t)I.N;
                 from.bad = (unsigned long long*)(I.w.flags + 2);
-                if (I.deferred) {
+                from.hash_only = I.by_row;
+                if (I.deferred && !I.by_row) {
                     from.S = I.S.limbs;  // null with integers
                     from.ss = I.S.stride;
                 }
@@ -1174,20 +1228,43 @@ static int prove_core(const ProveCall& c) {
         ZK_HIP_TRY(hipGetLastError());
     }
     bool table_consts_read = false;
-    auto read_table_consts = [&]() -> int {
-        if (table_consts_read) return ZK_OK;
-        for (size_t i = 0; i < K; ++i) {
+    // What the comparisons of S with its rows have found, in the words that came with the last sums: the first instance
+    // at fault is the one reported, so that the earlier ones whose first pass is yet to come are looked through now.
+    auto report_bad = [&]() -> int {
+        auto bad_of = [&](size_t i) {
             uint64_t bad;
             memcpy(&bad, mb->words + kMailboxBad + 2 * i, 8);
-            if (bad != UINT64_MAX) {  // found while A was made (LeafGather)
-                if (c.aux) c.aux->bad_index = bad;
-                if (c.baux) {
-                    c.baux->bad_instance = i;
-                    c.baux->bad_index = bad;
-                }
-                ZK_HIP_TRY(hipStreamSynchronize(stream));
-                return ZK_E_NOT_IN_TABLE;
-            }
+            return bad;
+        };
+        size_t at = 0;
+        while (at < K && bad_of(at) == UINT64_MAX) ++at;
+        if (at == K) return ZK_OK;
+        uint64_t bad = bad_of(at);
+        for (size_t i = 0; i < at; ++i) {
+            Instance& I = inst[i];
+            if (!I.unchecked) continue;
+            uint8_t* const staged = mb->bulk + kBulkDigests;  // there was room for all instances' digests of m
+            const CountJob job{&I.w, I.S, I.idx, I.T, I.D, I.N, staged, false, nullptr};
+            const uint32_t seq = mb->next_seq();
+            ZK_TRY(count_rows(&job, 1, seq, mb, stream));
+            ZK_TRY(mailbox_wait(mb, seq, stream));
+            if (counted_bad(staged) == UINT64_MAX) continue;
+            at = i;
+            bad = counted_bad(staged);
+            break;
+        }
+        if (c.aux) c.aux->bad_index = bad;
+        if (c.baux) {
+            c.baux->bad_instance = at;
+            c.baux->bad_index = bad;
+        }
+        ZK_HIP_TRY(hipStreamSynchronize(stream));
+        return ZK_E_NOT_IN_TABLE;
+    };
+    auto read_table_consts = [&]() -> int {
+        if (table_consts_read) return ZK_OK;
+        ZK_TRY(report_bad());
+        for (size_t i = 0; i < K; ++i) {
             inst[i].c1 = from_dev(inst[i].const_words);
             inst[i].c2 = from_dev(inst[i].const_words + 8);
             inst[i].cB = sub(mul(alpha2, inst[i].c1), inst[i].c2);
@@ -1343,7 +1420,7 @@ static int prove_core(const ProveCall& c) {
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
             if (k < I.skip) continue;
-            const RoundPlan& plan = plans[i] = plan_round(I.n, I.h, k - I.skip, K, from_ints, I.state);
+            const RoundPlan& plan = plans[i] = plan_round(I.n, I.h, k - I.skip, K, from_ints, I.state, I.by_row);
             // cannot happen: small_source_shape_ok has walked these rounds
             if (plan.s_source == kSNowhere || (from_ints && plan.s_source == kSFromCaller)) return ZK_E_BADARG;
             if (plan.kind == kRoundHost) any_ship = any_ship || plan.starts;
@@ -1351,6 +1428,8 @@ static int prove_core(const ProveCall& c) {
             else if (plan.kind != kRoundNoPass) last_launch = i;
         }
         const bool any_launch = last_launch < K || any_pass || any_ship;
+        size_t pairs = 0;  // long passes over two variables: their values come out behind those of the short passes
+        auto passes = [](const RoundPlan& pl) { return pl.kind == kRoundGrid || pl.kind == kRoundPair; };
 
         const uint32_t seq = any_launch ? mb->next_seq() : 0;
         for (size_t i = 0; i < K; ++i) {
@@ -1417,7 +1496,7 @@ static int prove_core(const ProveCall& c) {
                 if (span01 > (size_t)kBlock * kRound01MaxQuads) span01 = (size_t)kBlock * kRound01MaxQuads;
                 if (span01 > quarter) span01 = quarter;
                 const unsigned blocks01 = (unsigned)(quarter / span01);
-                if (blocks01 > w.part_blocks || span01 > ((size_t)1 << eq1.lbits) || !I.S.limbs) return ZK_E_BADARG;  // cannot happen
+                if (blocks01 > w.part_blocks || span01 > ((size_t)1 << eq1.lbits) || (!I.S.limbs && !I.by_row)) return ZK_E_BADARG;  // cannot happen
                 DataRound01Args d01;
                 d01.A = w.A;
                 d01.as = D;
@@ -1439,10 +1518,70 @@ static int prove_core(const ProveCall& c) {
                 d01.beta = to_dev(beta);
                 {
                     ProfileScope prof(kProfRoundData, stream);
-                    hipLaunchKernelGGL(k_round_first_two, dim3(blocks01), dim3(kBlock), 0, stream, d01);
+                    if (I.by_row) {
+                        FirstTwoRowsArgs rows;
+                        rows.sums = d01;
+                        rows.rows = I.rows();
+                        rows.table = I.rows_first();
+                        rows.N = (uint32_t)N;
+                        rows.bad = (unsigned long long*)(w.flags + 2);
+                        rows.ints = ints_src;
+                        if (!I.deferred) hipLaunchKernelGGL(k_first_two_rows<kRowsTrusted>, dim3(blocks01), dim3(kBlock), 0, stream, rows);
+                        else if (from_ints) hipLaunchKernelGGL(k_first_two_rows<kRowsCheckInts>, dim3(blocks01), dim3(kBlock), 0, stream, rows);
+                        else hipLaunchKernelGGL(k_first_two_rows<kRowsCheckWords>, dim3(blocks01), dim3(kBlock), 0, stream, rows);
+                        I.unchecked = false;
+                    } else {
+                        hipLaunchKernelGGL(k_round_first_two, dim3(blocks01), dim3(kBlock), 0, stream, d01);
+                    }
                 }
+                const bool checked = I.by_row && I.deferred;
                 launch_final_sum2(w.partD, d01.pstrideD, 5, w.partT, d01.pstrideT, 6, blocks01, I.words, mb->words, my_seq,
-                                  w.flags + 1, stream);
+                                  w.flags + 1, stream, checked ? w.flags + 2 : nullptr, mb->words + kMailboxBad + 2 * i);
+            } else if (plan.kind == kRoundPair) {
+                // binds the last two challenges, sums what this round and the next need
+                PairArgs pr;
+                memset(&pr, 0, sizeof pr);
+                const EqSplit eq1 = ep.round(kk + 1);
+                pr.rows = I.rows();
+                pr.table = I.rows_pair();
+                pr.N = (uint32_t)N;
+                pr.a = I.planes(w.A29);
+                pr.s = I.planes(w.S29);
+                pr.aw = w.A;
+                pr.aws = D;
+                pr.sw = w.Sf;
+                pr.sws = D / 2;
+                pr.P = half / 2;
+                pr.span = pair_span(pr.P);
+                const unsigned pair_blocks = (unsigned)(pr.P / pr.span);
+                pr.pstride = (size_t)pair_blocks * kPairValues;
+                // cannot happen
+                if (plan.bind != 2 || pr.span > ((size_t)1 << eq1.lbits) || pr.pstride > w.part_blocks * 5) return ZK_E_BADARG;
+                F e[4];
+                long_constants(e, r_last, 2, one());
+                for (int q = 0; q < 4; ++q) pr.e[q] = to_dev(e[q]);
+                pr.bias = long_bias(zero(), 32, 4);
+                pr.weights = Planes29{ep.pool29, ep.count29};
+                pr.lo_off = ep.suffix29_off[eq1.lbits];
+                pr.lbits = eq1.lbits;
+                pr.has_hi = eq1.has_hi;
+                pr.hi_pool = ep.pool;
+                pr.hi_stride = ep.stride;
+                pr.hi_off = eq1.hi_off;
+                pr.beta = to_dev(beta);
+                pr.partials = w.partD;
+                {
+                    ProfileScope prof(kProfRound29, stream);
+                    const bool from_rows = plan.s_source == kSFromRows;
+                    if (from_rows && out32) hipLaunchKernelGGL((k_round_pair<true, true>), dim3(pair_blocks), dim3(kPairThreads), 0, stream, pr);
+                    else if (from_rows) hipLaunchKernelGGL((k_round_pair<true, false>), dim3(pair_blocks), dim3(kPairThreads), 0, stream, pr);
+                    else if (out32) hipLaunchKernelGGL((k_round_pair<false, true>), dim3(pair_blocks), dim3(kPairThreads), 0, stream, pr);
+                    else hipLaunchKernelGGL((k_round_pair<false, false>), dim3(pair_blocks), dim3(kPairThreads), 0, stream, pr);
+                }
+                uint32_t* const pair_words = mb->words + kMailboxGrid + 8 * 89 * (kMailboxMaxInstances - ++pairs);
+                I.grid_words = pair_words;
+                hipLaunchKernelGGL(k_long_total, dim3(kPairValues), dim3(kBlock), 0, stream, w.partD, pr.pstride, pair_blocks, pair_words,
+                                   mb->words, my_seq, w.flags + 1);
             } else if (plan.kind == kRoundBoth) {
                 {
                     ProfileScope prof(kProfRoundSmall, stream);
@@ -1583,8 +1722,27 @@ static int prove_core(const ProveCall& c) {
             I.gt.read(at, tvars);
             I.gm.read(at + 8 * grid_points(tvars), tvars);
         }
+        for (size_t i = 0; i < K; ++i) {
+            if (k < inst[i].skip || plans[i].kind != kRoundPair) continue;
+            Instance& I = inst[i];
+            I.gq.read(I.grid_words, 2);
+            for (int q = 0; q < 9; ++q) I.gq.g[q] = mul(I.gq.g[q], inv32);
+            long_classes_to_grid(I.gq);
+            for (int x = 0; x < 4; ++x) I.gs[x] = from_dev(I.grid_words + 8 * (9 + x));
+            if (plans[i].vars == 2) continue;
+            // this round alone: the next variable is the table's too
+            F h3[3];
+            for (int X = 0; X < 3; ++X)
+                h3[X] = add(I.gq.g[3 * X], mul(u[k + 1], sub(I.gq.g[3 * X + 1], I.gq.g[3 * X])));
+            for (int X = 0; X < 3; ++X) I.gq.g[X] = h3[X];
+            I.gq.vars = 1;
+            for (int x = 0; x < 2; ++x) I.gs[x] = add(I.gs[2 * x], I.gs[2 * x + 1]);
+        }
         if (any_ship) read_shipped(k);
         if (k > 0 || any_launch) ZK_TRY(read_table_consts());
+        // (what a first pass that came after those has found)
+        for (size_t i = 0; i < K; ++i)
+            if (k > 0 && k == inst[i].skip && inst[i].by_row) ZK_TRY(report_bad());
 
         F e[4], g[4];
         line_values(e, e_side[0], e_side[1]);
@@ -1608,7 +1766,7 @@ static int prove_core(const ProveCall& c) {
             const uint32_t* sums = I.words;
             F q0, q1, qi, sA0, sA1;
             F hs[11];  // kRoundHost, kRoundGrid: the round's sums, formed here
-            if (plan.kind == kRoundGrid) {
+            if (passes(plan)) {
                 I.gq.sums(hs, u + k + 1);
                 hs[3] = hs[4] = zero();
                 const int later = 1 << (plan.left - 1);
@@ -1679,7 +1837,7 @@ static int prove_core(const ProveCall& c) {
             F q[4], sa[4], tq[4], tm[4];
             quad_values(q, q0, q1, qi);
             line_values(sa, sA0, sA1);
-            if (table_round && (plan.kind == kRoundHost || plan.kind == kRoundGrid)) {
+            if (table_round && (plan.kind == kRoundHost || passes(plan))) {
                 quad_values(tq, hs[5], hs[6], hs[7]);
                 quad_values(tm, hs[8], hs[9], hs[10]);
             } else if (table_round) {
@@ -1715,7 +1873,7 @@ static int prove_core(const ProveCall& c) {
             if (k < I.skip) continue;
             if (plans[i].kind == kRoundHost) {
                 I.tail->fold((size_t)1 << (n - k - 1), plans[i].table_round, r);
-            } else if (plans[i].kind == kRoundGrid) {
+            } else if (passes(plans[i])) {
                 I.gq.bind(r);
                 const int half = 1 << (plans[i].left - 1);
                 for (int x = 0; x < half; ++x) I.gs[x] = add(I.gs[x], mul(r, sub(I.gs[half + x], I.gs[x])));
@@ -2150,21 +2308,33 @@ int tlookup_prove_small(const uint8_t seed[32], const int32_t* X, const int32_t*
 
 // The rounds of a proof of this shape, walked on the host (no GPU is touched): four
 // integers per round, see zkmi.h.
-int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int32_t* out, size_t cap_rounds) {
-    if (!out || !is_pow2(D) || !is_pow2(N) || N > D || D > ((size_t)1 << 31) || K == 0 || K > kMailboxMaxInstances) return ZK_E_BADARG;
+static int selftest_plan(size_t D, size_t N, size_t K, bool from_ints, bool by_row, int32_t* out, size_t cap_rounds) {
     const int n = log2_floor(D), h = n - log2_floor(N);
     if ((size_t)n > cap_rounds) return ZK_E_BUFSZ;
-    if (from_ints && (K != 1 || !small_source_shape_ok(D, N))) return ZK_E_BADARG;
     RoundState st;
     for (int k = 0; k < n; ++k) {
-        const RoundPlan pl = plan_round(n, h, k, K, from_ints != 0, st);
-        const bool several = pl.kind == kRoundGrid || pl.kind == kRoundHost;
+        const RoundPlan pl = plan_round(n, h, k, K, from_ints, st, by_row);
+        const bool several = pl.kind == kRoundGrid || pl.kind == kRoundHost, pair = pl.kind == kRoundPair;
         out[4 * k] = pl.kind;
         out[4 * k + 1] = pl.s_source;
-        out[4 * k + 2] = several ? pl.vars + 8 * pl.tvars : pl.in32 ? 1 : 0;
-        out[4 * k + 3] = several ? pl.bind + 8 * pl.bind_t : pl.out32 ? 1 : 0;
+        out[4 * k + 2] = pair ? pl.vars : several ? pl.vars + 8 * pl.tvars : pl.in32 ? 1 : 0;
+        out[4 * k + 3] = pair ? pl.bind + (pl.out32 ? 8 : 0) : several ? pl.bind + 8 * pl.bind_t : pl.out32 ? 1 : 0;
     }
     return n;
+}
+static bool selftest_shape_ok(size_t D, size_t N, size_t K, const int32_t* out) {
+    return out && is_pow2(D) && is_pow2(N) && N <= D && D <= ((size_t)1 << 31) && K != 0 && K <= kMailboxMaxInstances;
+}
+
+int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int32_t* out, size_t cap_rounds) {
+    if (!selftest_shape_ok(D, N, K, out)) return ZK_E_BADARG;
+    if (from_ints && (K != 1 || !small_source_shape_ok(D, N))) return ZK_E_BADARG;
+    return selftest_plan(D, N, K, from_ints != 0, false, out, cap_rounds);
+}
+
+int zkmi_selftest_tlookup_rows_plan(size_t D, size_t N, size_t K, int32_t* out, size_t cap_rounds) {
+    if (!selftest_shape_ok(D, N, K, out) || !gather_by_default(N) || !rounds_by_row(log2_floor(D), log2_floor(D) - log2_floor(N))) return ZK_E_BADARG;
+    return selftest_plan(D, N, K, false, true, out, cap_rounds);
 }
 
 // The host's rounds (HostTail) on arrays and challenges of the caller's choosing: no GPU is touched.

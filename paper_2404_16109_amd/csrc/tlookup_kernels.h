@@ -45,6 +45,8 @@ struct TableJob {
     uint32_t* M;        // counts as field elements
     const uint32_t* B;
     uint4* rows_b;      // null: B's rows are not asked for
+    uint4* rows_hash;   // not null: B's canonical values by themselves, and what the rounds read by row:
+    uint4* rows_pair;   // (tlookup_rows.h)
 };
 // (Calls with one table pass one, whose pointers the compiler can see to be global: through
 // an array they are flat, and flat loads share a counter with the LDS; the counts' leaves
@@ -398,7 +400,21 @@ static __global__ void __launch_bounds__(kBlock) k_hist_reduce(TableJobs<NT> tab
 
 // Row j of B as sixteen consecutive words, so that reading it by number is one
 // 64-byte access: the element, then its canonical value as the hash takes it
-// (big-endian bytes of little-endian words).
+// (big-endian bytes of little-endian words).  Where A itself is not asked for, only its
+// hash (rows_hash not null), the hash's values lie by themselves, 32 bytes each, and the
+// rows are those the rounds read by row: T's balanced digits (outer_dev.h) and B's words
+// for the first pass (rows_b), both elements' digits for the second (rows_pair).
+__device__ __forceinline__ void row_digits(uint4* at, const Fr& v) {
+    uint32_t d[8], carry = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        uint32_t co;
+        d[k] = __builtin_addc(v.l[k], 0x80808080u, carry, &co) ^ 0x80808080u;
+        carry = co;
+    }
+    at[0] = make_uint4(d[0], d[1], d[2], d[3]);
+    at[1] = make_uint4(d[4], d[5], d[6], d[7]);
+}
 template <int NT>
 static __global__ void __launch_bounds__(kBlock) k_rows_of(TableJobs<NT> tables) {
     const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.y];
@@ -411,11 +427,19 @@ static __global__ void __launch_bounds__(kBlock) k_rows_of(TableJobs<NT> tables)
         Fr c = fr_from_mont(v);
 #pragma unroll
         for (int k = 0; k < 8; ++k) c.l[k] = __builtin_bswap32(c.l[k]);
-        uint4* at = rows + 4 * (size_t)j;
-        at[0] = make_uint4(v.l[0], v.l[1], v.l[2], v.l[3]);
-        at[1] = make_uint4(v.l[4], v.l[5], v.l[6], v.l[7]);
-        at[2] = make_uint4(c.l[0], c.l[1], c.l[2], c.l[3]);
-        at[3] = make_uint4(c.l[4], c.l[5], c.l[6], c.l[7]);
+        uint4 *words = rows + 4 * (size_t)j, *hash = words + 2;
+        if (g.rows_hash) {
+            const Fr t = fr_load(g.T, g.ts, j);
+            row_digits(words, t);
+            row_digits(g.rows_pair + 4 * (size_t)j, v);
+            row_digits(g.rows_pair + 4 * (size_t)j + 2, t);
+            words += 2;
+            hash = g.rows_hash + 2 * (size_t)j;
+        }
+        words[0] = make_uint4(v.l[0], v.l[1], v.l[2], v.l[3]);
+        words[1] = make_uint4(v.l[4], v.l[5], v.l[6], v.l[7]);
+        hash[0] = make_uint4(c.l[0], c.l[1], c.l[2], c.l[3]);
+        hash[1] = make_uint4(c.l[4], c.l[5], c.l[6], c.l[7]);
     }
 }
 
@@ -572,15 +596,17 @@ enum LeafMode {
     kLeafPlain = 0,      // the vector is there
     kLeafRows = 1,       // made by row, the rows known to be right
     kLeafRowsCheck = 2,  // made by row, S compared with T's rows
-    kLeafRowsInts = 3    // the same with S_i from VecLeavesArgs::ints
+    kLeafRowsInts = 3,   // the same with S_i from VecLeavesArgs::ints
+    kLeafRowsHash = 4    // made by row, only hashed: the rounds read B by row themselves (LeafGather::hash_only)
 };
 struct LeafGather {
     const uint32_t* rows = nullptr;    // row numbers; null: the vector itself is hashed
     const uint32_t* S = nullptr;       // what kLeafRowsCheck compares
     size_t ss = 0;
     const uint4* T = nullptr;          // N rows, two uint4 each (k_canon_rows)
-    const uint4* B = nullptr;          // N rows, four uint4 each (k_rows_of)
+    const uint4* B = nullptr;          // N rows, four uint4 each, or (hash_only) two: the words of the hash (k_rows_of)
     uint32_t N = 0;
+    int hash_only = 0;
     unsigned long long* bad = nullptr; // smallest i with S_i != T[row_i] or row_i >= N
 };
 struct VecLeavesJob {
@@ -634,6 +660,7 @@ __device__ __forceinline__ Fr fr_load_row(const uint4* table, uint32_t r) {
 // during which the loads can be on the way.
 template <int MODE>
 struct LeafBlocks {
+    static constexpr bool kChecks = MODE == kLeafRowsCheck || MODE == kLeafRowsInts;
     VecLeavesJob job;
     uint32_t lane_bytes;  // four times the leaf's number: there are at most 2^24 leaves
     uint32_t cnt;
@@ -654,6 +681,8 @@ struct LeafBlocks {
     __device__ __forceinline__ void fetch(Fr& x, Fr& y, uint32_t i, uint32_t row) {
         if constexpr (MODE == kLeafPlain) {
             x = fr_load_lane(job.v, job.stride, i * job.L, lane_bytes);
+        } else if constexpr (MODE == kLeafRowsHash) {
+            x = fr_load_row<2, 0>(job.from.B, in_table(row));
         } else {
             y = fr_load_row<4, 0>(job.from.B, in_table(row));
             x = fr_load_row<4, 2>(job.from.B, in_table(row));
@@ -661,12 +690,12 @@ struct LeafBlocks {
     }
     // A's element on its way to memory
     __device__ __forceinline__ void write(const Fr& x, uint32_t i) {
-        if (MODE == kLeafPlain || !live) return;
+        if (MODE == kLeafPlain || MODE == kLeafRowsHash || !live) return;
 #pragma unroll
         for (int k = 0; k < 8; ++k) *at_lane(job.v, i * job.L + k * job.stride, lane_bytes) = x.l[k];
     }
     __device__ __forceinline__ void check_ask(const SmallSource& ints, Check& c, uint32_t i, uint32_t row) {
-        if constexpr (MODE >= kLeafRowsCheck) c.t = fr_load_row<2, 0>(job.from.T, in_table(row));
+        if constexpr (kChecks) c.t = fr_load_row<2, 0>(job.from.T, in_table(row));
         if constexpr (MODE == kLeafRowsCheck) c.s = fr_load_lane(job.from.S, job.from.ss, i * job.L, lane_bytes);
         if constexpr (MODE == kLeafRowsInts) {
             c.s.l[0] = *at_lane(ints.x, i * job.L, lane_bytes);
@@ -674,7 +703,7 @@ struct LeafBlocks {
         }
     }
     __device__ __forceinline__ void check(const SmallSource& ints, const Check& c, uint32_t i, uint32_t row) {
-        if constexpr (MODE >= kLeafRowsCheck) {
+        if constexpr (kChecks) {
             Fr s = c.s;
             if constexpr (MODE == kLeafRowsInts) small_combine32(s.l, (int32_t)c.s.l[0], (int32_t)c.s.l[1], ints);
             uint32_t diff = 0;
@@ -684,7 +713,7 @@ struct LeafBlocks {
         }
     }
     __device__ __forceinline__ void report() {
-        if (MODE >= kLeafRowsCheck && live && first_bad < cnt)
+        if (kChecks && live && first_bad < cnt)
             atomicMin(job.from.bad, (unsigned long long)(first_bad * job.L + lane_bytes / 4));
     }
     __device__ __forceinline__ void words(uint32_t* w, const Fr& el) {
@@ -794,13 +823,15 @@ __device__ __forceinline__ void leaf_by_lane(const VecLeavesArgs& args, const Ve
     if (job.to_host) mailbox_written();
 }
 
-// MODE: of the jobs that have rows.
+// MODE: of the jobs that have rows, but for those of which only the hash is asked for (kLeafRowsHash:
+// there are no others).
 template <int MODE>
 static __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) k_vec_leaves(VecLeavesArgs args) {
     const VecLeavesJob& job = leaves_job(args, blockIdx.x);
     const size_t leaf = (size_t)(blockIdx.x - job.first_group) * 64 + threadIdx.x;
     if (leaf < job.L) {
-        if (MODE != kLeafPlain && job.from.rows) leaf_by_lane<MODE>(args, job, leaf);
+        if (MODE != kLeafPlain && job.from.hash_only) leaf_by_lane<kLeafRowsHash>(args, job, leaf);
+        else if (MODE != kLeafPlain && MODE != kLeafRowsHash && job.from.rows) leaf_by_lane<MODE>(args, job, leaf);
         else leaf_by_lane<kLeafPlain>(args, job, leaf);
     }
     leaves_done(args);
@@ -889,7 +920,8 @@ static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs a
             if (job.to_host) mailbox_written();
         }
     } else {
-        if (MODE != kLeafPlain && job.from.rows) leaf_schedules<MODE>(args, job, live, leaf, blocks, steps, kw[pair]);
+        if (MODE != kLeafPlain && job.from.hash_only) leaf_schedules<kLeafRowsHash>(args, job, live, leaf, blocks, steps, kw[pair]);
+        else if (MODE != kLeafPlain && MODE != kLeafRowsHash && job.from.rows) leaf_schedules<MODE>(args, job, live, leaf, blocks, steps, kw[pair]);
         else leaf_schedules<kLeafPlain>(args, job, live, leaf, blocks, steps, kw[pair]);
     }
     leaves_done(args);
@@ -1365,6 +1397,24 @@ static __global__ void __launch_bounds__(kBlock) k_table_const(TableConstJobs<NT
     if (threadIdx.x == 0) {
         fr_store(g.partials, g.pstride, (size_t)blockIdx.x * jobs.values, tot[0]);
         fr_store(g.partials, g.pstride, (size_t)blockIdx.x * jobs.values + 1, tot[1]);
+    }
+}
+
+// Adds up a value's `count` partial sums, one workgroup per value.
+static __global__ void __launch_bounds__(kBlock) k_long_total(const uint32_t* partials, size_t pstride, unsigned count, uint32_t* out_words,
+                                                              uint32_t* words, uint32_t seq, uint32_t* ticket) {
+    __shared__ uint32_t lds[4 * 8];
+    Fr acc[1] = {fr_zero()};
+    for (unsigned b = threadIdx.x; b < count; b += kBlock) acc[0] = fr_add(acc[0], fr_load(partials, pstride, (size_t)blockIdx.x * count + b));
+    block_sum<1, 4>(acc, lds);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) out_words[8 * blockIdx.x + k] = acc[0].l[k];
+        mailbox_written();
+        if (atomicAdd(ticket, 1u) == gridDim.x - 1) {
+            *ticket = 0;
+            mailbox_publish(words, seq);
+        }
     }
 }
 

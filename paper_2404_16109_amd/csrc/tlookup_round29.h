@@ -128,8 +128,10 @@ __device__ __forceinline__ void fold_pair29_ints(const DataRound29Args& g, size_
 
 // Sums of lazy values over a wavefront: limbs are added lane to lane (data-parallel
 // moves, as in reduce_dev.h) and carried every second step, before they can
-// outgrow their words.  v: normalized, below 8 r; the result, in every lane, is
-// normalized and below 64 times that (below 2^264, which is about 565 r).
+// outgrow their words.  v: normalized, below 8 r; the result, in lane 63, is
+// normalized and below 64 times that (below 2^264, which is about 565 r).  (Not
+// spread to all lanes: what is the same in all of them goes on in the scalar ALU,
+// where a multiplication is seven hundred instructions, 2 us.)
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ F29 dpp_add29(const F29& v) {
     F29 o;
@@ -149,10 +151,7 @@ __device__ __forceinline__ F29 wave_sum29(F29 v) {
     v = dpp_add29<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
     v = dpp_add29<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
     v = f29_normalize(v);
-    F29 out;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) out.l[k] = (uint32_t)__builtin_amdgcn_readlane((int)v.l[k], 63);
-    return out;
+    return v;
 }
 
 template <bool IN32, bool OUT32, bool INTS = false, bool FOLD2 = false>
@@ -180,7 +179,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         tot[q] = f29_shrink(wave_sum29(tot[q]));  // below 77 r, 166 r, 403 r, then below 2.1 r, 3.4 r, 6.7 r
-        if (lane == 0) {
+        if (lane == 63) {
 #pragma unroll
             for (int k = 0; k < 9; ++k) lds[(wave * 3 + q) * 9 + k] = tot[q].l[k];
         }
@@ -268,14 +267,77 @@ struct DataRound01Args {
 // wavefronts per SIMD kept it 70 % busy); entries are asked for four ahead of their use.
 // Issue and HBM bind about equally: 2^25 entries 760 -> 520 us, 4.1 TB/s; a proof of 2^20
 // entries in all 731 -> 709 us, one of 2^17 524 -> 500.
+struct FirstTwoValues {
+    uint32_t vals[9][8];  // M_x0, M_x1, M_0x, M_1x, M_xx, W_00, W_01, W_10, W_11
+    uint32_t sums_a[4][4][9];
+};
+template <int STAGE>
+struct FirstTwoShared {
+    uint8_t lds[STAGE] __attribute__((aligned(16)));  // the wavefronts' operands
+    FirstTwoValues values;
+    static_assert(STAGE >= 6 * 4096, "outer_close's sums");
+};
+static_assert(4 * (size_t)kBlock * kRound01MaxQuads <= kOuterMaxProducts, "a position adds four products to M_xx");
+
+// The class of X_c S_d, c != d.
+__device__ constexpr int first_two_class(int c, int d) { return (c ^ d) == 2 ? (c & 1) : (c ^ d) == 1 ? 2 + (c >> 1) : 4; }
+
+// A wavefront's sum of A_c, at most 32 entries per lane: `part` of the workgroup's.
+__device__ __forceinline__ void first_two_line(FirstTwoValues& values, int part, int c, const F29& sa) {
+    const F29 t = f29_shrink(wave_sum29(f29_shrink(f29_normalize(sa))));
+    if ((threadIdx.x & 63) == 63) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) values.sums_a[part][c][k] = t.l[k];
+    }
+}
+
+// Takes a workgroup's closed sums: the classes, and W by column.
+__device__ __forceinline__ void first_two_value(FirstTwoValues& values, int q, int column, const Fr& x) {
+    if (q == 5 && column >= 4) return;
+    const int at = q == 5 ? 5 + column : q;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) values.vals[at][k] = x.l[k];
+}
+
+// The results, once all of that is there; A's sums are of PARTS parts.
+template <int PARTS>
+__device__ __forceinline__ void first_two_finish(const DataRound01Args& g, const FirstTwoValues& values, size_t start) {
+    const int q = threadIdx.x;
+    if (q < 5) {
+        auto value = [&](int i) {
+            Fr f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) f.l[k] = values.vals[i][k];
+            return f;
+        };
+        // c20: W_00 + W_10, c21: W_01 + W_11, qd: W_00 + W_01, T: W_10 + W_11, qe: all
+        Fr w = q < 2 ? fr_add(value(5 + q), value(7 + q)) : fr_add(value(q == 3 ? 7 : 5), value(q == 3 ? 8 : 6));
+        Fr m = value(q == 4 ? 0 : q);
+        if (q == 4) {
+            w = fr_add(w, fr_add(value(7), value(8)));
+            m = fr_sub(fr_add(fr_add(m, value(1)), fr_add(value(2), value(3))), value(4));
+        }
+        Fr out = fr_sub(fr_zero(), fr_add(fr_mul(w, g.beta), m));
+        if (g.has_hi) out = fr_mul(out, fr_load(g.hi_pool, g.hi_stride, g.hi_off + (start >> g.lbits)));
+        fr_store(g.partD, g.pstrideD, (size_t)blockIdx.x * 5 + q, out);
+    } else if (q < 11) {
+        Fr out = fr_zero();
+        if (q < 9) {
+            F29 t = f29_zero();
+            for (int s = 0; s < PARTS; ++s) {
+#pragma unroll
+                for (int k = 0; k < 9; ++k) t.l[k] += values.sums_a[s][q - 5][k];
+            }
+            f29_canonical(out.l, f29_normalize(t));
+        }
+        fr_store(g.partT, g.pstrideT, (size_t)blockIdx.x * 6 + (q - 5), out);
+    }
+}
+
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) k_round_first_two(DataRound01Args g) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[4 * 5 * kOuterStage];  // per wavefront S's four operands and one of A
-    static_assert(sizeof lds >= 6 * 4096, "outer_close's sums");
-    static_assert(4 * (size_t)kBlock * kRound01MaxQuads <= kOuterMaxProducts, "a position adds four products to M_xx");
-    __shared__ uint32_t vals[9][8];     // M_x0, M_x1, M_0x, M_1x, M_xx, W_00, W_01, W_10, W_11
-    __shared__ uint32_t sums_a[4][4][9];
+    __shared__ FirstTwoShared<4 * 5 * kOuterStage> sh;  // per wavefront S's four operands and one of A
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint8_t* const stage = lds + wave * 5 * kOuterStage;
+    uint8_t* const stage = sh.lds + wave * 5 * kOuterStage;
     uint8_t* const stage_x = stage + 4 * kOuterStage;
     v16i acc[6];
 #pragma unroll
@@ -315,11 +377,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 
                 const OuterOperand xo = outer_operand(x, stage_x);
                 outer_mac(acc[5], xo, outer_column(c));
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    if (d == c) continue;
-                    const int cls = (c ^ d) == 2 ? (c & 1) : (c ^ d) == 1 ? 2 + (c >> 1) : 4;
-                    outer_mac(acc[cls], xo, outer_get(stage + d * kOuterStage));
-                }
+                for (int d = 0; d < 4; ++d)
+                    if (d != c) outer_mac(acc[first_two_class(c, d)], xo, outer_get(stage + d * kOuterStage));
             }
         }
         sa0 = f29_normalize(sa0);
@@ -327,51 +386,13 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 
         sa2 = f29_normalize(sa2);
         sa3 = f29_normalize(sa3);
     }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const F29 t = f29_shrink(wave_sum29(f29_shrink(c == 0 ? sa0 : c == 1 ? sa1 : c == 2 ? sa2 : sa3)));  // at most 16 entries per thread, 1024 a wavefront
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < 9; ++k) sums_a[wave][c][k] = t.l[k];
-        }
-    }
-    outer_close<6, 32, true>(acc, (int*)lds, [&](int q, int column, const Fr& x) {
-        if (q == 5 && column >= 4) return;
-        const int at = q == 5 ? 5 + column : q;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) vals[at][k] = x.l[k];
-    });
+    first_two_line(sh.values, wave, 0, sa0);
+    first_two_line(sh.values, wave, 1, sa1);
+    first_two_line(sh.values, wave, 2, sa2);
+    first_two_line(sh.values, wave, 3, sa3);
+    outer_close<6, 32, true>(acc, (int*)sh.lds, [&](int q, int column, const Fr& x) { first_two_value(sh.values, q, column, x); });
     __syncthreads();
-    const int q = threadIdx.x;
-    if (q < 5) {
-        auto value = [&](int i) {
-            Fr f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) f.l[k] = vals[i][k];
-            return f;
-        };
-        // c20: W_00 + W_10, c21: W_01 + W_11, qd: W_00 + W_01, T: W_10 + W_11, qe: all
-        Fr w = q < 2 ? fr_add(value(5 + q), value(7 + q)) : fr_add(value(q == 3 ? 7 : 5), value(q == 3 ? 8 : 6));
-        Fr m = value(q == 4 ? 0 : q);
-        if (q == 4) {
-            w = fr_add(w, fr_add(value(7), value(8)));
-            m = fr_sub(fr_add(fr_add(m, value(1)), fr_add(value(2), value(3))), value(4));
-        }
-        Fr out = fr_sub(fr_zero(), fr_add(fr_mul(w, g.beta), m));
-        if (g.has_hi) out = fr_mul(out, fr_load(g.hi_pool, g.hi_stride, g.hi_off + (start >> g.lbits)));
-        fr_store(g.partD, g.pstrideD, (size_t)blockIdx.x * 5 + q, out);
-    } else if (q < 11) {
-        Fr out = fr_zero();
-        if (q < 9) {
-            F29 t = f29_zero();
-            for (int s = 0; s < 4; ++s) {
-#pragma unroll
-                for (int k = 0; k < 9; ++k) t.l[k] += sums_a[s][q - 5][k];
-            }
-            f29_canonical(out.l, f29_normalize(t));
-        }
-        fr_store(g.partT, g.pstrideT, (size_t)blockIdx.x * 6 + (q - 5), out);
-    }
+    first_two_finish<4>(g, sh.values, start);
 }
 
 }  // namespace zkmi
