@@ -1149,7 +1149,13 @@ static int prove_core(const ProveCall& c) {
                 }
             }
             jobs[2 * i] = VecDigestJob{I.w.A, I.D, I.D, I.w.dig_rows, from};
-            jobs[2 * i + 1] = VecDigestJob{I.w.B, I.N, I.N, I.w.dig_rows_b, LeafGather()};
+            LeafGather table;
+            if (I.by_row) {  // B's canonical values are there for A's sake
+                table.B = I.rows_hash();
+                table.N = (uint32_t)I.N;
+                table.hash_only = 1;
+            }
+            jobs[2 * i + 1] = VecDigestJob{I.w.B, I.N, I.N, I.w.dig_rows_b, table};
         }
         ZK_TRY(vec_digest_launch(jobs, 2 * (int)K, dig_leaves, mb, seq, inst[0].w.flags + 1, stream,
                                  from_ints ? &ints_src : nullptr));

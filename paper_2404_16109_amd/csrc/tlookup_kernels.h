@@ -600,7 +600,7 @@ enum LeafMode {
     kLeafRowsHash = 4    // made by row, only hashed: the rounds read B by row themselves (LeafGather::hash_only)
 };
 struct LeafGather {
-    const uint32_t* rows = nullptr;    // row numbers; null: the vector itself is hashed
+    const uint32_t* rows = nullptr;    // row numbers; null: the vector itself is hashed (hash_only: all rows in order)
     const uint32_t* S = nullptr;       // what kLeafRowsCheck compares
     size_t ss = 0;
     const uint4* T = nullptr;          // N rows, two uint4 each (k_canon_rows)
@@ -675,7 +675,9 @@ struct LeafBlocks {
     };
 
     __device__ __forceinline__ uint32_t row_number(uint32_t i) const {
-        return MODE == kLeafPlain ? 0u : *at_lane(job.from.rows, i * job.L, lane_bytes);
+        if (MODE == kLeafPlain) return 0u;
+        if (MODE == kLeafRowsHash && !job.from.rows) return i * (uint32_t)job.L + lane_bytes / 4;  // the table's own rows
+        return *at_lane(job.from.rows, i * job.L, lane_bytes);
     }
     __device__ __forceinline__ uint32_t in_table(uint32_t row) const { return row < job.from.N ? row : 0u; }
     __device__ __forceinline__ void fetch(Fr& x, Fr& y, uint32_t i, uint32_t row) {
@@ -850,12 +852,16 @@ static __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
 // chains one wavefront per SIMD waits out, the pairs are still ahead at twice as many
 // (the same without rows: 408 us, in pairs 235; 2^23 entries from integers, 1032
 // groups: 608 us, in pairs 425).  At 2^25 elements from rows, 1079 us against 1145 in pairs.
+// Where A is only hashed (kLeafRowsHash; the table's leaves then come ready too, where they were
+// converted: at 2^20 entries 137 us -> 125, at 2^22 224 -> 184): by lane 184 us at 520 groups, in pairs 220;
+// at 1025, just above a wavefront per SIMD, 364 and 323; at 2056 484 and 521.
 // Beyond 1040 groups, whole calls by lane and in pairs: a verification of 2^24 entries
 // 1.05 and 1.02 ms, of 2^25 1.70 and 1.70; a proof from integers of 2^24 2.67 and 2.49 ms,
 // of 2^25 4.45 and 4.08, so that for integers the line could lie higher still.
 static const uint32_t kPipedLeafGroups = 512, kPipedLeafGroupsConverting = 1040;
 template <int MODE>
 static bool leaves_in_pairs(uint32_t groups) {
+    if (MODE == kLeafRowsHash && groups > 1024) return groups <= kPipedLeafGroupsConverting;
     return groups <= (MODE == kLeafPlain || MODE == kLeafRowsInts ? kPipedLeafGroupsConverting : kPipedLeafGroups);
 }
 
