@@ -97,14 +97,6 @@ __device__ __forceinline__ void sha256_rounds(uint32_t (&s)[8], uint32_t (&w)[16
     }
 }
 
-// The state between two rounds as it stands: keeps the compiler from moving the
-// rounds before this behind what follows it.
-__device__ __forceinline__ void sha256_pin(uint32_t (&s)[8], uint32_t (&w)[16]) {
-    asm volatile("" : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7]));
-    asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]),
-                 "+v"(w[8]), "+v"(w[9]), "+v"(w[10]), "+v"(w[11]), "+v"(w[12]), "+v"(w[13]), "+v"(w[14]), "+v"(w[15]));
-}
-
 // h <- compress(h, w).  w holds the block as sixteen big-endian words and is used
 // as the rolling message schedule (its contents are gone afterwards).
 __device__ __forceinline__ void sha256_compress(uint32_t (&h)[8], uint32_t (&w)[16]) {

@@ -304,9 +304,8 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
         ZK_HIP_TRY(hipGetLastError());
         return ZK_OK;
     }
-    if (mode == kLeafRowsCheck) launch_leaves<kLeafRowsCheck>(lv, stream);
-    else if (mode == kLeafRowsInts) launch_leaves<kLeafRowsInts>(lv, stream);
-    else if (mode == kLeafRows) launch_leaves<kLeafRows>(lv, stream);
+    if (mode == kLeafRowsCheck || mode == kLeafRowsInts) return ZK_E_BADARG;  // cannot happen: k_make_a or the rounds compare
+    if (mode == kLeafRows) launch_leaves<kLeafRows>(lv, stream);
     else if (mode == kLeafRowsHash) launch_leaves<kLeafRowsHash>(lv, stream);
     else launch_leaves<kLeafPlain>(lv, stream);
     // up the trees, all rows in one launch, a factor of up to kTreeChunk per launch
@@ -1133,30 +1132,43 @@ static int prove_core(const ProveCall& c) {
         ProfileScope prof(kProfDigest, stream);
         const uint32_t seq = mb->next_seq();
         VecDigestJob jobs[2 * kMailboxMaxInstances];
+        size_t all_leaves = 0;
+        for (size_t i = 0; i < K; ++i) all_leaves += vec_digest_leaves(inst[i].D) + vec_digest_leaves(inst[i].N);
+        MakeAJobs<kMailboxMaxInstances> make{};
+        size_t made = 0, longest = 0;
+        if (from_ints) make.ints = ints_src;
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
-            LeafGather from;
+            LeafGather from, table;
             if (I.gather) {
                 from.rows = I.rows();
                 from.T = I.w.rows;
-                from.B = I.by_row ? I.rows_hash() : I.w.rows_b;
+                from.B = I.w.rows_b;
                 from.N = (uint32_t)I.N;
                 from.bad = (unsigned long long*)(I.w.flags + 2);
-                from.hash_only = I.by_row;
                 if (I.deferred && !I.by_row) {
                     from.S = I.S.limbs;  // null with integers
                     from.ss = I.S.stride;
                 }
+                const bool apart = !I.by_row && I.D <= kMadeApart && all_leaves > kHostLeaves;
+                if (apart) {
+                    const int check = !I.deferred ? kLeafRows : from_ints ? kLeafRowsInts : kLeafRowsCheck;
+                    make.job[made++] = MakeAJob{I.w.A, I.D, I.D, from, check};
+                    longest = std::max(longest, I.D);
+                }
+                if (apart || I.by_row) {
+                    from.S = nullptr;
+                    from.B = I.by_row ? I.rows_hash() : I.w.rows_b + 2;
+                    from.hash_only = I.by_row ? 2 : 4;
+                    table = from;  // B's canonical values are there for A's sake
+                    table.rows = nullptr;
+                }
             }
             jobs[2 * i] = VecDigestJob{I.w.A, I.D, I.D, I.w.dig_rows, from};
-            LeafGather table;
-            if (I.by_row) {  // B's canonical values are there for A's sake
-                table.B = I.rows_hash();
-                table.N = (uint32_t)I.N;
-                table.hash_only = 1;
-            }
             jobs[2 * i + 1] = VecDigestJob{I.w.B, I.N, I.N, I.w.dig_rows_b, table};
         }
+        if (made == 1) hipLaunchKernelGGL(k_make_a<1>, dim3(grid_for(longest)), dim3(kBlock), 0, stream, MakeAJobs<1>{{make.job[0]}, make.ints});
+        else if (made) hipLaunchKernelGGL(k_make_a<kMailboxMaxInstances>, dim3(grid_for(longest), (unsigned)made), dim3(kBlock), 0, stream, make);
         ZK_TRY(vec_digest_launch(jobs, 2 * (int)K, dig_leaves, mb, seq, inst[0].w.flags + 1, stream,
                                  from_ints ? &ints_src : nullptr));
         ZK_TRY(mailbox_wait(mb, seq, stream));

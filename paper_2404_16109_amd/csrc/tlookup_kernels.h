@@ -584,28 +584,30 @@ static const uint32_t kVecLeaf = 128;
 // blocks whatever the vector's length: one after the other, short vectors would
 // cost as much as long ones).
 //
-// A lookup's A need not be there yet.  S_i is the table's row rho_i, so A_i =
-// 1/(beta + S_i) is B[rho_i]: with a LeafGather the same pass reads B by row, writes
-// A, hashes it and, where the rows are the caller's hints, compares every S_i with
-// T[rho_i].  The hash is bound by instruction issue, so the 68 bytes per element this
-// moves ride under it, and the inversion of D elements (three multiplications and 160
-// bytes per element) becomes one of N.  For tables of up to 2^16 rows, whose row-major
-// copies (96 bytes per row) the caches hold.  Measured at 2^25 elements and 2^16 rows,
-// inversion and leaves: 2.32 ms (1.21 and 1.11) -> 1.14 ms (0.06 and 1.08).
+// A lookup's A need not be there.  S_i is the table's row rho_i, so A_i = 1/(beta + S_i) is
+// B[rho_i]: with a LeafGather the hash reads B's canonical values by row (kLeafRowsHash), and
+// the inversion of D elements (three multiplications and 160 bytes per element) becomes one of
+// N.  For tables of up to 2^16 rows, whose row-major copies the caches hold.  Measured at 2^25
+// elements and 2^16 rows, inversion and leaves: 2.32 ms (1.21 and 1.11) -> 0.89 ms (0.06 and
+// 0.83).  What else reads A by row, and compares S with T's rows: the long rounds
+// (tlookup_rows.h), or, for shorter tensors (2^18 entries or fewer, kMadeApart), k_make_a, which
+// writes A.  (While the hash wrote A and compared, its chain was the longer by it: 2^20 entries
+// 153 us, now 126; 2^18 entries 155, now 126 and 8.)  Longer tables by row (tlookup_prove_by_rows)
+// keep the hash that writes A (kLeafRows), where that rides under the hash's issue.
 enum LeafMode {
     kLeafPlain = 0,      // the vector is there
-    kLeafRows = 1,       // made by row, the rows known to be right
-    kLeafRowsCheck = 2,  // made by row, S compared with T's rows
-    kLeafRowsInts = 3,   // the same with S_i from VecLeavesArgs::ints
-    kLeafRowsHash = 4    // made by row, only hashed: the rounds read B by row themselves (LeafGather::hash_only)
+    kLeafRows = 1,       // made by row and written, the rows known to be right
+    kLeafRowsCheck = 2,  // made by row, S compared with T's rows (k_make_a, k_leaves_to_host)
+    kLeafRowsInts = 3,   // the same with S_i from integers
+    kLeafRowsHash = 4    // made by row, only hashed (LeafGather::hash_only)
 };
 struct LeafGather {
     const uint32_t* rows = nullptr;    // row numbers; null: the vector itself is hashed (hash_only: all rows in order)
     const uint32_t* S = nullptr;       // what kLeafRowsCheck compares
     size_t ss = 0;
     const uint4* T = nullptr;          // N rows, two uint4 each (k_canon_rows)
-    const uint4* B = nullptr;          // N rows, four uint4 each, or (hash_only) two: the words of the hash (k_rows_of)
-    uint32_t N = 0;
+    const uint4* B = nullptr;          // N rows, four uint4 each (k_rows_of), or (hash_only) the words of the hash, two in
+    uint32_t N = 0;                    // every hash_only uint4 (two or four)
     int hash_only = 0;
     unsigned long long* bad = nullptr; // smallest i with S_i != T[row_i] or row_i >= N
 };
@@ -625,7 +627,7 @@ struct VecLeavesArgs {
     uint32_t* words;   // the mailbox, if this launch is the last to write results (seq != 0)
     uint32_t* ticket;
     uint32_t seq;
-    SmallSource ints;  // of the job that asks for it
+    SmallSource ints;  // k_leaves_to_host: of the job that asks for it
 };
 
 // The pointers of a job come out of an array, so the compiler does not know that
@@ -660,19 +662,13 @@ __device__ __forceinline__ Fr fr_load_row(const uint4* table, uint32_t r) {
 // during which the loads can be on the way.
 template <int MODE>
 struct LeafBlocks {
-    static constexpr bool kChecks = MODE == kLeafRowsCheck || MODE == kLeafRowsInts;
     VecLeavesJob job;
     uint32_t lane_bytes;  // four times the leaf's number: there are at most 2^24 leaves
     uint32_t cnt;
     bool live;            // lanes past the last leaf read what the last one reads and write nothing
-    uint32_t row0, row1;    // row numbers of the two elements held,
-    uint32_t next0, next1;  // and of the two after them
-    uint32_t first_bad;     // the leaf's first element that is not its row
+    uint32_t next0, next1;  // row numbers of the two elements after those held
     Fr x0, x1;              // with rows: in the words of the hash (y: the elements themselves)
     Fr y0, y1;
-    struct Check {          // of an element's S with its row
-        Fr s, t;            // with integers, s holds the two of them
-    };
 
     __device__ __forceinline__ uint32_t row_number(uint32_t i) const {
         if (MODE == kLeafPlain) return 0u;
@@ -684,7 +680,7 @@ struct LeafBlocks {
         if constexpr (MODE == kLeafPlain) {
             x = fr_load_lane(job.v, job.stride, i * job.L, lane_bytes);
         } else if constexpr (MODE == kLeafRowsHash) {
-            x = fr_load_row<2, 0>(job.from.B, in_table(row));
+            x = fr_load_row<1, 0>(job.from.B, in_table(row) * (uint32_t)job.from.hash_only);
         } else {
             y = fr_load_row<4, 0>(job.from.B, in_table(row));
             x = fr_load_row<4, 2>(job.from.B, in_table(row));
@@ -695,28 +691,6 @@ struct LeafBlocks {
         if (MODE == kLeafPlain || MODE == kLeafRowsHash || !live) return;
 #pragma unroll
         for (int k = 0; k < 8; ++k) *at_lane(job.v, i * job.L + k * job.stride, lane_bytes) = x.l[k];
-    }
-    __device__ __forceinline__ void check_ask(const SmallSource& ints, Check& c, uint32_t i, uint32_t row) {
-        if constexpr (kChecks) c.t = fr_load_row<2, 0>(job.from.T, in_table(row));
-        if constexpr (MODE == kLeafRowsCheck) c.s = fr_load_lane(job.from.S, job.from.ss, i * job.L, lane_bytes);
-        if constexpr (MODE == kLeafRowsInts) {
-            c.s.l[0] = *at_lane(ints.x, i * job.L, lane_bytes);
-            c.s.l[1] = ints.y ? *at_lane(ints.y, i * job.L, lane_bytes) : 0u;
-        }
-    }
-    __device__ __forceinline__ void check(const SmallSource& ints, const Check& c, uint32_t i, uint32_t row) {
-        if constexpr (kChecks) {
-            Fr s = c.s;
-            if constexpr (MODE == kLeafRowsInts) small_combine32(s.l, (int32_t)c.s.l[0], (int32_t)c.s.l[1], ints);
-            uint32_t diff = 0;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) diff |= s.l[k] ^ c.t.l[k];
-            if ((diff || row >= job.from.N) && i < first_bad) first_bad = i;
-        }
-    }
-    __device__ __forceinline__ void report() {
-        if (kChecks && live && first_bad < cnt)
-            atomicMin(job.from.bad, (unsigned long long)(first_bad * job.L + lane_bytes / 4));
     }
     __device__ __forceinline__ void words(uint32_t* w, const Fr& el) {
         const Fr x = MODE == kLeafPlain ? fr_from_mont(el) : el;
@@ -730,21 +704,17 @@ struct LeafBlocks {
         lane_bytes = (uint32_t)(live ? which : j.L - 1) * 4;
         cnt = (uint32_t)(j.n / j.L);  // kVecLeaf, or all n (a power of two) when n < kVecLeaf
         const uint32_t last = cnt - 1;  // short vectors: places past the end read the last element again
-        row0 = row_number(0);
-        row1 = row_number(last < 1 ? last : 1);
+        const uint32_t row0 = row_number(0), row1 = row_number(last < 1 ? last : 1);
         next0 = row_number(last < 2 ? last : 2);
         next1 = row_number(last < 3 ? last : 3);
-        first_bad = 0xffffffffu;
         fetch(x0, y0, 0, row0);
         fetch(x1, y1, last < 1 ? last : 1, row1);
     }
     __device__ __forceinline__ uint32_t blocks() const { return cnt / 2 + 1; }  // the last holds the padding
-    // The words of elements 2b and 2b+1; what follows is asked for before work() runs
-    // (the block's rounds, or the making of its schedule; in two halves), and the
-    // elements' checks ride on its halves: all at once their words took more registers
-    // than four wavefronts per SIMD leave (and spilled: 1.9 ms instead of 1.1 at 2^25 elements).
-    template <class First, class Second>
-    __device__ __forceinline__ void data_block(const SmallSource& ints, uint32_t (&w)[16], uint32_t b, First&& first, Second&& second) {
+    // The words of elements 2b and 2b+1; what follows is asked for before work() runs (the
+    // block's rounds, or the making of its schedule).
+    template <class Work>
+    __device__ __forceinline__ void data_block(uint32_t (&w)[16], uint32_t b, Work&& work) {
         write(y0, 2 * b);
         write(y1, 2 * b + 1);
         words(w, x0);
@@ -753,29 +723,15 @@ struct LeafBlocks {
         const uint32_t end = cnt - 2, i = 2 * b + 2 < end ? 2 * b + 2 : end, ii = i + 2 < end ? i + 2 : end;
         fetch(x0, y0, i, next0);
         fetch(x1, y1, i + 1, next1);
-        const uint32_t after0 = row_number(ii), after1 = row_number(ii + 1);
-        Check c;
-        check_ask(ints, c, 2 * b, row0);
+        next0 = row_number(ii);
+        next1 = row_number(ii + 1);
         __builtin_amdgcn_sched_barrier(0);  // asked for here, not where they are used
-        first();
+        work();
         __builtin_amdgcn_sched_barrier(0);
-        check(ints, c, 2 * b, row0);
-        check_ask(ints, c, 2 * b + 1, row1);
-        __builtin_amdgcn_sched_barrier(0);
-        second();
-        __builtin_amdgcn_sched_barrier(0);
-        check(ints, c, 2 * b + 1, row1);
-        row0 = next0;
-        row1 = next1;
-        next0 = after0;
-        next1 = after1;
     }
-    __device__ __forceinline__ void last_block(const SmallSource& ints, uint32_t (&w)[16]) {
+    __device__ __forceinline__ void last_block(uint32_t (&w)[16]) {
         if (cnt == 1) {  // a vector of one element shares its block with the padding
-            Check c;
-            check_ask(ints, c, 0, row0);
             write(y0, 0);
-            check(ints, c, 0, row0);
             words(w, x0);
         }
         const int pad = cnt == 1 ? 8 : 0;
@@ -802,7 +758,7 @@ __device__ __forceinline__ void leaves_done(const VecLeavesArgs& args) {
 
 // Many leaves: one lane does all of a leaf.  Bound by instruction issue.
 template <int MODE>
-__device__ __forceinline__ void leaf_by_lane(const VecLeavesArgs& args, const VecLeavesJob& job, size_t leaf) {
+__device__ __forceinline__ void leaf_by_lane(const VecLeavesJob& job, size_t leaf) {
     LeafBlocks<MODE> src;
     src.begin(job, leaf);
     uint32_t h[8];
@@ -813,12 +769,11 @@ __device__ __forceinline__ void leaf_by_lane(const VecLeavesArgs& args, const Ve
         uint32_t s[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) s[i] = h[i];
-        src.data_block(args.ints, w, b, [&] { sha256_rounds<0, 32>(s, w); sha256_pin(s, w); }, [&] { sha256_rounds<32, 64>(s, w); });
+        src.data_block(w, b, [&] { sha256_rounds<0, 64>(s, w); });
 #pragma unroll
         for (int i = 0; i < 8; ++i) h[i] += s[i];
     }
-    src.last_block(args.ints, w);
-    src.report();
+    src.last_block(w);
     sha256_compress(h, w);
 #pragma unroll
     for (int k = 0; k < 8; ++k) job.out[leaf * 8 + k] = h[k];
@@ -832,9 +787,9 @@ static __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
     const VecLeavesJob& job = leaves_job(args, blockIdx.x);
     const size_t leaf = (size_t)(blockIdx.x - job.first_group) * 64 + threadIdx.x;
     if (leaf < job.L) {
-        if (MODE != kLeafPlain && job.from.hash_only) leaf_by_lane<kLeafRowsHash>(args, job, leaf);
-        else if (MODE != kLeafPlain && MODE != kLeafRowsHash && job.from.rows) leaf_by_lane<MODE>(args, job, leaf);
-        else leaf_by_lane<kLeafPlain>(args, job, leaf);
+        if (MODE != kLeafPlain && job.from.hash_only) leaf_by_lane<kLeafRowsHash>(job, leaf);
+        else if (MODE != kLeafPlain && MODE != kLeafRowsHash && job.from.rows) leaf_by_lane<MODE>(job, leaf);
+        else leaf_by_lane<kLeafPlain>(job, leaf);
     }
     leaves_done(args);
 }
@@ -846,56 +801,44 @@ static __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
 // a block costs the rounds' 900 instructions.  A workgroup is two such pairs, one
 // wavefront per SIMD: two workgroups of one pair each were seen to share two SIMDs and
 // leave two idle.  Measured at 2^20 elements (8192 leaves): 220 -> 140 us.  Above
-// kPipedLeafGroups the wavefronts share SIMDs.  Where the words come ready from B's
-// rows one lane per leaf is then as fast (a tensor of 2^22 with its table, 520 groups:
-// 205 us, in pairs 239); where every element is converted or built from integers first, whose long
-// chains one wavefront per SIMD waits out, the pairs are still ahead at twice as many
-// (the same without rows: 408 us, in pairs 235; 2^23 entries from integers, 1032
-// groups: 608 us, in pairs 425).  At 2^25 elements from rows, 1079 us against 1145 in pairs.
-// Where A is only hashed (kLeafRowsHash; the table's leaves then come ready too, where they were
-// converted: at 2^20 entries 137 us -> 125, at 2^22 224 -> 184): by lane 184 us at 520 groups, in pairs 220;
-// at 1025, just above a wavefront per SIMD, 364 and 323; at 2056 484 and 521.
-// Beyond 1040 groups, whole calls by lane and in pairs: a verification of 2^24 entries
-// 1.05 and 1.02 ms, of 2^25 1.70 and 1.70; a proof from integers of 2^24 2.67 and 2.49 ms,
-// of 2^25 4.45 and 4.08, so that for integers the line could lie higher still.
+// kPipedLeafGroups the wavefronts share SIMDs.  Where the words come ready one lane per leaf is
+// then faster (kLeafRowsHash, a tensor of 2^22 with its table, 520 groups: 184 us, in pairs 220;
+// at 2056 groups 484 and 521), but for the places just above a wavefront per SIMD (1025 groups:
+// 364 and 323); where every element is converted first, whose long chain one wavefront per SIMD
+// waits out, the pairs are still ahead at 1032 (520 groups without rows: 408 us, in pairs 235).
+// Beyond 1040 groups, whole verifications by lane and in pairs: 2^24 entries 1.05 and 1.02 ms,
+// 2^25 1.70 and 1.70.
 static const uint32_t kPipedLeafGroups = 512, kPipedLeafGroupsConverting = 1040;
 template <int MODE>
 static bool leaves_in_pairs(uint32_t groups) {
     if (MODE == kLeafRowsHash && groups > 1024) return groups <= kPipedLeafGroupsConverting;
-    return groups <= (MODE == kLeafPlain || MODE == kLeafRowsInts ? kPipedLeafGroupsConverting : kPipedLeafGroups);
+    return groups <= (MODE == kLeafPlain ? kPipedLeafGroupsConverting : kPipedLeafGroups);
 }
 
 // The second wavefront's part: the schedules of all blocks of its lanes' leaves.
 template <int MODE>
-__device__ __forceinline__ void leaf_schedules(const VecLeavesArgs& args, const VecLeavesJob& job, bool live, size_t leaf,
-                                               uint32_t blocks, uint32_t steps, uint4 (*kw)[16][64]) {
+__device__ __forceinline__ void leaf_schedules(const VecLeavesJob& job, bool live, size_t leaf, uint32_t blocks, uint32_t steps,
+                                               uint4 (*kw)[16][64]) {
     const int lane = threadIdx.x & 63;
     LeafBlocks<MODE> src;
     if (live) src.begin(job, leaf);
     for (uint32_t b = 0; b <= steps; ++b) {  // one barrier more than blocks, as the wavefront of the rounds takes
         if (b < blocks) {
             uint32_t w[16];
-            const auto four_words = [&](int g) {
-                if (g >= 4) sha256_schedule4(w, 4 * g);
-                const int i = (4 * g) & 15;
-                kw[b & 1][g][lane] = make_uint4(w[i] + kShaK[4 * g], w[i + 1] + kShaK[4 * g + 1], w[i + 2] + kShaK[4 * g + 2],
-                                                w[i + 3] + kShaK[4 * g + 3]);
-            };
-            const auto first_half = [&] {
+            const auto schedule = [&] {
 #pragma unroll
-                for (int g = 0; g < 8; ++g) four_words(g);
-            };  // (stores to LDS: they stay where they are)
-            const auto second_half = [&] {
-#pragma unroll
-                for (int g = 8; g < 16; ++g) four_words(g);
+                for (int g = 0; g < 16; ++g) {
+                    if (g >= 4) sha256_schedule4(w, 4 * g);
+                    const int i = (4 * g) & 15;
+                    kw[b & 1][g][lane] = make_uint4(w[i] + kShaK[4 * g], w[i + 1] + kShaK[4 * g + 1], w[i + 2] + kShaK[4 * g + 2],
+                                                    w[i + 3] + kShaK[4 * g + 3]);
+                }
             };
             if (b + 1 < blocks) {
-                src.data_block(args.ints, w, b, first_half, second_half);
+                src.data_block(w, b, schedule);
             } else {
-                src.last_block(args.ints, w);
-                src.report();
-                first_half();
-                second_half();
+                src.last_block(w);
+                schedule();
             }
         }
         __syncthreads();
@@ -926,11 +869,42 @@ static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs a
             if (job.to_host) mailbox_written();
         }
     } else {
-        if (MODE != kLeafPlain && job.from.hash_only) leaf_schedules<kLeafRowsHash>(args, job, live, leaf, blocks, steps, kw[pair]);
-        else if (MODE != kLeafPlain && MODE != kLeafRowsHash && job.from.rows) leaf_schedules<MODE>(args, job, live, leaf, blocks, steps, kw[pair]);
-        else leaf_schedules<kLeafPlain>(args, job, live, leaf, blocks, steps, kw[pair]);
+        if (MODE != kLeafPlain && job.from.hash_only) leaf_schedules<kLeafRowsHash>(job, live, leaf, blocks, steps, kw[pair]);
+        else if (MODE != kLeafPlain && MODE != kLeafRowsHash && job.from.rows) leaf_schedules<MODE>(job, live, leaf, blocks, steps, kw[pair]);
+        else leaf_schedules<kLeafPlain>(job, live, leaf, blocks, steps, kw[pair]);
     }
     leaves_done(args);
+}
+
+// A by row, S (or integers) compared with T's rows: a thread per element, blockIdx.y the instance.
+struct MakeAJob {
+    uint32_t* A;
+    size_t stride, D;
+    LeafGather from;  // B: four uint4 per row
+    int check;        // kLeafRows, kLeafRowsCheck, kLeafRowsInts
+};
+static const size_t kMadeApart = (size_t)1 << 18;
+template <int NT>
+struct MakeAJobs {
+    MakeAJob job[NT];
+    SmallSource ints;
+};
+template <int NT>
+static __global__ void __launch_bounds__(kBlock) k_make_a(MakeAJobs<NT> jobs) {
+    const MakeAJob& g = jobs.job[NT == 1 ? 0 : blockIdx.y];
+    for (size_t i = blockIdx.x * (size_t)kBlock + threadIdx.x; i < g.D; i += (size_t)gridDim.x * kBlock) {
+        const uint32_t row = g.from.rows[i], r = row < g.from.N ? row : 0u;
+        fr_store(g.A, g.stride, i, fr_load_row<4, 0>(g.from.B, r));
+        if (g.check == kLeafRows) continue;
+        const Fr t = fr_load_row<2, 0>(g.from.T, r);
+        Fr s;
+        if (g.check == kLeafRowsInts) small_source_load(s.l, jobs.ints, i);
+        else s = fr_load(g.from.S, g.from.ss, i);
+        uint32_t diff = row ^ r;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) diff |= s.l[k] ^ t.l[k];
+        if (diff) atomicMin(g.from.bad, (unsigned long long)i);
+    }
 }
 
 // Very few leaves: a leaf is a chain of 65 blocks, 140 us here whatever their number, and
