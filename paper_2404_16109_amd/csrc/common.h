@@ -138,10 +138,13 @@ static const size_t kMailboxShip = 2048;
 static const size_t kMailboxShipEntries = 64;
 static const size_t kMailboxShipWords = 5 * kMailboxShipEntries * 8;
 static const size_t kMailboxGrid = kMailboxShip + kMailboxMaxInstances * kMailboxShipWords;
-static const size_t kMailboxWords = kMailboxGrid + kMailboxMaxInstances * 89 * 8;
+// The shares of the table side's sum over a table of up to 2^16 rows (k_rows_of), which the host adds up.
+static const size_t kMailboxTableShares = 256;
+static const size_t kMailboxTableSums = kMailboxGrid + kMailboxMaxInstances * 89 * 8;
+static const size_t kMailboxWords = kMailboxTableSums + kMailboxMaxInstances * kMailboxTableShares * 8;
 static const size_t kMailboxInvB = 1024;    // grand total of the table-side inversion (+16 per instance)
 static const size_t kMailboxInvA = 1032;    // grand total of the data-side inversion (+16 per instance)
-static const size_t kMailboxTableC = 1280;  // the two table-side constants (+16 per instance)
+static const size_t kMailboxTableC = 1280;  // that sum of longer tables (+8 per instance)
 static const size_t kMailboxBad = 1408;     // smallest index whose element is not its hinted row, all ones if none (+2 per instance)
 
 // The staging buffer (Mailbox::bulk) starts with the rows of digests the host

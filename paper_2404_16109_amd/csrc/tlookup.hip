@@ -242,11 +242,12 @@ static void launch_leaves_to_host(const VecLeavesArgs& lv, hipStream_t stream) {
 // The jobs that have rows (LeafGather) all compare them with S, or all with the
 // integers, or none: by `ints` and whether they have an S; those that are only hashed do not.
 static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Mailbox* mb, uint32_t seq, uint32_t* ticket,
-                             hipStream_t stream, const SmallSource* ints = nullptr) {
+                             hipStream_t stream, const SmallSource* ints = nullptr, const BadWords& bad = BadWords{}) {
     if (njobs < 1 || njobs > kDigestMaxJobs) return ZK_E_BADARG;
     ZK_TRY(mailbox_bulk(mb, 0));
     VecLeavesArgs lv{};
     if (ints) lv.ints = *ints;
+    lv.bad = bad;
     lv.njobs = njobs;
     lv.words = mb->words;
     lv.ticket = ticket;
@@ -314,6 +315,7 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
         memset(&tr, 0, sizeof tr);
         tr.words = mb->words;
         tr.ticket = ticket;
+        tr.bad = bad;
         blocks = 0;
         more = false;
         for (int q = 0; q < njobs; ++q) {
@@ -476,7 +478,7 @@ struct CountJob {
 };
 
 static TableJob table_job(const ProveWs& w, const fr_vec& T, size_t N) {
-    return TableJob{T.limbs, T.stride, (uint32_t)N, w.slots, w.cap_mask, w.flags, w.canon, w.rows, w.m, w.hist, w.hist_parts, w.M, w.B, nullptr, nullptr, nullptr};
+    return TableJob{T.limbs, T.stride, (uint32_t)N, w.slots, w.cap_mask, w.flags, w.canon, w.rows, w.m, w.hist, w.hist_parts, w.M, w.B, nullptr, nullptr, nullptr, nullptr, 0, 0};
 }
 
 // Enqueues the multiplicities of up to kMaxTables tensors into their w.m; `seq` (not zero)
@@ -843,8 +845,7 @@ struct Instance {
     size_t b_cur_stride = 0;
     uint32_t* words = nullptr;  // this instance's round sums in the mailbox
     uint32_t* inv_words = nullptr;    // totals of its two inversions (B, then A)
-    uint32_t* const_words = nullptr;  // its two table-side constants
-    host::F c1, c2, cB, sum_A, lam;
+    host::F sum_mB, cB, sum_A, lam;
     host::F claim;       // the running claim of this instance's own sumcheck: f_i's round polynomial at 0 plus at 1
     host::F fX[4];       // its last round polynomial at X = 0..3
     host::F sA_prev[2];  // its last round's sums of A at X = 0, 1
@@ -983,8 +984,7 @@ static int prove_core(const ProveCall& c) {
         I.b_cur_stride = I.N;
         I.words = mb->words + kMailboxSlot * i;
         I.inv_words = mb->words + kMailboxInvB + 16 * i;
-        I.const_words = mb->words + kMailboxTableC + 16 * i;
-        I.c1 = I.c2 = I.cB = I.sum_A = zero();
+        I.sum_mB = I.cB = I.sum_A = zero();
         I.cD = I.cT = I.half_pow = one();
         I.inv_den = zero();
         I.scale = one();
@@ -1056,6 +1056,8 @@ static int prove_core(const ProveCall& c) {
     Transcript tr(c.multi ? "zkmi/tlookup-multi/v1" : c.batch ? "zkmi/tlookup-batch/v2" : "zkmi/tlookup/v2", c.seed, dims, ndims);
     for (size_t i = 0; i < K; ++i) tr.absorb("m", inst[i].md, 32);
 
+    unsigned table_shares = 0;  // of the table side's sums, where the host adds them up
+
     // -- Prove: beta, inverse vectors ---------------------------------------------------------------
     F beta = tr.challenge("beta");
     if (c.forced_beta) beta = from_canonical(*c.forced_beta);
@@ -1110,20 +1112,65 @@ static int prove_core(const ProveCall& c) {
         ZK_TRY(batch_inverse_end(jobs, pre, (int)njobs, stream));
         TableJobs<kMaxTables> tables{};
         size_t rows = 0;
+        for (size_t i = 0; i < K; ++i) rows = std::max(rows, inst[i].N);
+        // shares of the sums of B m: the host's to add up, unless there are long tables
+        const bool long_tables = rows > kLdsHistMaxRows;
+        table_shares = grid_for(rows, kBlock, long_tables ? kMaxPartialBlocks / 4 : kMailboxTableShares);
         for (size_t i = 0; i < K; ++i) {
-            tables.job[i] = table_job(inst[i].w, inst[i].T, inst[i].N);
+            TableJob& t = tables.job[i] = table_job(inst[i].w, inst[i].T, inst[i].N);
+            t.sums = long_tables ? inst[0].w.partT + i : mb->words + kMailboxTableSums + i * kMailboxTableShares * 8;
+            t.sum_stride = long_tables ? inst[0].w.part_blocks * 6 : 0;
+            t.sum_step = (uint32_t)K;
             if (!inst[i].gather) continue;
-            tables.job[i].rows_b = inst[i].by_row ? inst[i].rows_first() : inst[i].w.rows_b;
+            t.rows_b = inst[i].by_row ? inst[i].rows_first() : inst[i].w.rows_b;
             if (inst[i].by_row) {
-                tables.job[i].rows_pair = inst[i].rows_pair();
-                tables.job[i].rows_hash = inst[i].rows_hash();
+                t.rows_pair = inst[i].rows_pair();
+                t.rows_hash = inst[i].rows_hash();
             }
-            rows = std::max(rows, inst[i].N);
         }
-        if (rows && K == 1) hipLaunchKernelGGL(k_rows_of<1>, dim3(grid_for(rows)), dim3(kBlock), 0, stream, TableJobs<1>{{tables.job[0]}});
-        else if (rows) hipLaunchKernelGGL(k_rows_of<kMaxTables>, dim3(grid_for(rows), (unsigned)K), dim3(kBlock), 0, stream, tables);
+        if (K == 1) hipLaunchKernelGGL(k_rows_of<1>, dim3(table_shares), dim3(kBlock), 0, stream, TableJobs<1>{{tables.job[0]}});
+        else hipLaunchKernelGGL(k_rows_of<kMaxTables>, dim3(table_shares, (unsigned)K), dim3(kBlock), 0, stream, tables);
+        if (long_tables) {
+            launch_final_sum(inst[0].w.partT, inst[0].w.part_blocks * 6, table_shares, (int)K, mb->words + kMailboxTableC, mb->words, 0,
+                             inst[0].w.flags + 1, stream);
+            table_shares = 0;
+        }
         ZK_HIP_TRY(hipGetLastError());
     }
+
+    // What the comparisons of S with its rows have found, in the words that came with the last sums: the first instance
+    // at fault is the one reported, so that the earlier ones whose first pass is yet to come are looked through now.
+    auto report_bad = [&]() -> int {
+        auto bad_of = [&](size_t i) {
+            uint64_t bad;
+            memcpy(&bad, mb->words + kMailboxBad + 2 * i, 8);
+            return bad;
+        };
+        size_t at = 0;
+        while (at < K && bad_of(at) == UINT64_MAX) ++at;
+        if (at == K) return ZK_OK;
+        uint64_t bad = bad_of(at);
+        for (size_t i = 0; i < at; ++i) {
+            Instance& I = inst[i];
+            if (!I.unchecked) continue;
+            uint8_t* const staged = mb->bulk + kBulkDigests;  // there was room for all instances' digests of m
+            const CountJob job{&I.w, I.S, I.idx, I.T, I.D, I.N, staged, false, nullptr};
+            const uint32_t seq = mb->next_seq();
+            ZK_TRY(count_rows(&job, 1, seq, mb, stream));
+            ZK_TRY(mailbox_wait(mb, seq, stream));
+            if (counted_bad(staged) == UINT64_MAX) continue;
+            at = i;
+            bad = counted_bad(staged);
+            break;
+        }
+        if (c.aux) c.aux->bad_index = bad;
+        if (c.baux) {
+            c.baux->bad_instance = at;
+            c.baux->bad_index = bad;
+        }
+        ZK_HIP_TRY(hipStreamSynchronize(stream));
+        return ZK_E_NOT_IN_TABLE;
+    };
 
     // The prover sends A and B before the sumcheck (Protocol 1, tlookup-Prove): their
     // digests, standing in for the commitments, enter the transcript before alpha
@@ -1169,8 +1216,12 @@ static int prove_core(const ProveCall& c) {
         }
         if (made == 1) hipLaunchKernelGGL(k_make_a<1>, dim3(grid_for(longest)), dim3(kBlock), 0, stream, MakeAJobs<1>{{make.job[0]}, make.ints});
         else if (made) hipLaunchKernelGGL(k_make_a<kMailboxMaxInstances>, dim3(grid_for(longest), (unsigned)made), dim3(kBlock), 0, stream, make);
+        BadWords bad{};
+        bad.count = (int)K;
+        bad.to = mb->words + kMailboxBad;
+        for (size_t i = 0; i < K; ++i) bad.from[i] = (const unsigned long long*)(inst[i].w.flags + 2);
         ZK_TRY(vec_digest_launch(jobs, 2 * (int)K, dig_leaves, mb, seq, inst[0].w.flags + 1, stream,
-                                 from_ints ? &ints_src : nullptr));
+                                 from_ints ? &ints_src : nullptr, bad));
         ZK_TRY(mailbox_wait(mb, seq, stream));
         for (size_t i = 0; i < K; ++i) {
             vec_digest_finish(inst[i].dA, jobs[2 * i]);
@@ -1178,6 +1229,7 @@ static int prove_core(const ProveCall& c) {
             tr.absorb("A", inst[i].dA, 32);
             tr.absorb("B", inst[i].dB, 32);
         }
+        ZK_TRY(report_bad());  // (after the leaves' bytes have been cleared)
     }
 
     F alpha = tr.challenge("alpha");
@@ -1196,6 +1248,15 @@ static int prove_core(const ProveCall& c) {
         }
     }
 
+    // The table side while none of its variables is bound: alpha^2 sum_j e'_j B_j (T_j + beta) - sum_j m_j B_j, the first
+    // sum being one (k_rows_of).
+    for (size_t i = 0; i < K; ++i) {
+        const uint32_t* at = mb->words + kMailboxTableSums + i * kMailboxTableShares * 8;
+        inst[i].sum_mB = table_shares ? zero() : from_dev(mb->words + kMailboxTableC + 8 * i);
+        for (unsigned q = 0; q < table_shares; ++q) inst[i].sum_mB = add(inst[i].sum_mB, from_dev(at + 8 * q));
+        inst[i].cB = sub(alpha2, inst[i].sum_mB);
+    }
+
     // weight tables: instance i uses u_[skip_i:], so instances of one length share a pool
     EqPool pools[kMailboxMaxInstances];
     for (size_t i = 0; i < K; ++i) {
@@ -1205,91 +1266,6 @@ static int prove_core(const ProveCall& c) {
         ZK_TRY(eq_pool_build(pools[i], u + inst[i].skip, inst[i].n, cv, stream));
         inst[i].ep = &pools[i];
     }
-
-    // -- table-side constants ---------------------------------------------------------------------
-    // c1 = sum_j e'_j B_j (T_j+beta), c2 = sum_j m_j B_j.  e' = e~(u_[h:], .) is the
-    // weight table of "round h-1" (remaining variables h .. n-1); with h = 0 no
-    // round needs the constant, only c2 is reported.
-    {
-        TableConstJobs<kMaxTables> jobs;
-        memset(&jobs, 0, sizeof jobs);
-        jobs.beta = to_dev(beta);
-        unsigned blocks = 1;
-        for (size_t i = 0; i < K; ++i) {
-            const Instance& I = inst[i];
-            const EqPool& ep = *I.ep;
-            TableConstArgs& a = jobs.job[i];
-            a.B = I.w.B; a.bs = I.N;
-            a.T = I.T.limbs; a.ts = I.T.stride;
-            a.M = I.w.M; a.ms = I.N;
-            a.N = I.N;
-            if (I.h >= 1) {
-                a.eq = ep.round(I.h - 1);
-            } else {
-                // weights unused for the reported sum; point at the one-entry table
-                a.eq = EqSplit{ep.pool, ep.stride, ep.suffix_off[0], 0, 0, 0};
-            }
-            // the instances' partial sums side by side: value 2 i + q of a workgroup
-            a.partials = inst[0].w.partT + 2 * i;
-            a.pstride = inst[0].w.part_blocks * 6;
-            a.bad = I.w.flags + 2;
-            a.bad_words = mb->words + kMailboxBad + 2 * i;
-            // a row per thread while there is room (against four: 2^16 rows 16 -> 8 us, 2^8, 2^20 and 2^22 alike); the
-            // 16 values of eight tables take partT's 6 kMaxPartialBlocks places at a quarter of the workgroups
-            blocks = std::max(blocks, grid_for(I.N, kBlock, kMaxPartialBlocks / 4));
-        }
-        jobs.values = 2 * (uint32_t)K;
-        if (K == 1) hipLaunchKernelGGL(k_table_const<1>, dim3(blocks), dim3(kBlock), 0, stream, TableConstJobs<1>{{jobs.job[0]}, jobs.beta, jobs.values});
-        else hipLaunchKernelGGL(k_table_const<kMaxTables>, dim3(blocks, (unsigned)K), dim3(kBlock), 0, stream, jobs);
-        // read back together with the first round's sums (or the final values)
-        launch_final_sum(inst[0].w.partT, inst[0].w.part_blocks * 6, blocks, 2 * (int)K, inst[0].const_words, mb->words, 0, inst[0].w.flags + 1, stream);
-        ZK_HIP_TRY(hipGetLastError());
-    }
-    bool table_consts_read = false;
-    // What the comparisons of S with its rows have found, in the words that came with the last sums: the first instance
-    // at fault is the one reported, so that the earlier ones whose first pass is yet to come are looked through now.
-    auto report_bad = [&]() -> int {
-        auto bad_of = [&](size_t i) {
-            uint64_t bad;
-            memcpy(&bad, mb->words + kMailboxBad + 2 * i, 8);
-            return bad;
-        };
-        size_t at = 0;
-        while (at < K && bad_of(at) == UINT64_MAX) ++at;
-        if (at == K) return ZK_OK;
-        uint64_t bad = bad_of(at);
-        for (size_t i = 0; i < at; ++i) {
-            Instance& I = inst[i];
-            if (!I.unchecked) continue;
-            uint8_t* const staged = mb->bulk + kBulkDigests;  // there was room for all instances' digests of m
-            const CountJob job{&I.w, I.S, I.idx, I.T, I.D, I.N, staged, false, nullptr};
-            const uint32_t seq = mb->next_seq();
-            ZK_TRY(count_rows(&job, 1, seq, mb, stream));
-            ZK_TRY(mailbox_wait(mb, seq, stream));
-            if (counted_bad(staged) == UINT64_MAX) continue;
-            at = i;
-            bad = counted_bad(staged);
-            break;
-        }
-        if (c.aux) c.aux->bad_index = bad;
-        if (c.baux) {
-            c.baux->bad_instance = at;
-            c.baux->bad_index = bad;
-        }
-        ZK_HIP_TRY(hipStreamSynchronize(stream));
-        return ZK_E_NOT_IN_TABLE;
-    };
-    auto read_table_consts = [&]() -> int {
-        if (table_consts_read) return ZK_OK;
-        ZK_TRY(report_bad());
-        for (size_t i = 0; i < K; ++i) {
-            inst[i].c1 = from_dev(inst[i].const_words);
-            inst[i].c2 = from_dev(inst[i].const_words + 8);
-            inst[i].cB = sub(mul(alpha2, inst[i].c1), inst[i].c2);
-        }
-        table_consts_read = true;
-        return ZK_OK;
-    };
 
     // -- header -----------------------------------------------------------------------------------------
     uint8_t* out = c.proof;
@@ -1757,10 +1733,8 @@ static int prove_core(const ProveCall& c) {
             for (int x = 0; x < 2; ++x) I.gs[x] = add(I.gs[2 * x], I.gs[2 * x + 1]);
         }
         if (any_ship) read_shipped(k);
-        if (k > 0 || any_launch) ZK_TRY(read_table_consts());
-        // (what a first pass that came after those has found)
         for (size_t i = 0; i < K; ++i)
-            if (k > 0 && k == inst[i].skip && inst[i].by_row) ZK_TRY(report_bad());
+            if (k == inst[i].skip && inst[i].by_row) ZK_TRY(report_bad());
 
         F e[4], g[4];
         line_values(e, e_side[0], e_side[1]);
@@ -1916,7 +1890,6 @@ static int prove_core(const ProveCall& c) {
             read_shipped(n);
         }
         ZK_HIP_TRY(hipStreamSynchronize(stream));  // everything of this call has left the device
-        ZK_TRY(read_table_consts());
         uint8_t* first = out;
         for (size_t i = 0; i < K; ++i) {
             const HostTail& t = *inst[i].tail;
@@ -1934,7 +1907,7 @@ static int prove_core(const ProveCall& c) {
         c.aux->beta = to_canonical(beta);
         c.aux->alpha = to_canonical(alpha);
         c.aux->sum_A = to_canonical(inst[0].sum_A);
-        c.aux->sum_mB = to_canonical(inst[0].c2);
+        c.aux->sum_mB = to_canonical(inst[0].sum_mB);
         c.aux->bad_index = 0;
     }
     if (c.baux) {
@@ -1944,7 +1917,7 @@ static int prove_core(const ProveCall& c) {
         c.baux->lambda = to_canonical(lambda);
         for (size_t i = 0; i < K; ++i) {
             c.baux->sum_A[i] = to_canonical(inst[i].sum_A);
-            c.baux->sum_mB[i] = to_canonical(inst[i].c2);
+            c.baux->sum_mB[i] = to_canonical(inst[i].sum_mB);
         }
     }
     return ZK_OK;

@@ -47,6 +47,9 @@ struct TableJob {
     uint4* rows_b;      // null: B's rows are not asked for
     uint4* rows_hash;   // not null: B's canonical values by themselves, and what the rounds read by row:
     uint4* rows_pair;   // (tlookup_rows.h)
+    uint32_t* sums;     // k_rows_of's sums of B M: a workgroup's eight words at 8 blockIdx.x,
+    size_t sum_stride;  // or (not zero) limb planes of this stride, a workgroup's value at sum_step blockIdx.x
+    uint32_t sum_step;
 };
 // (Calls with one table pass one, whose pointers the compiler can see to be global: through
 // an array they are flat, and flat loads share a counter with the LDS; the counts' leaves
@@ -415,15 +418,23 @@ __device__ __forceinline__ void row_digits(uint4* at, const Fr& v) {
     at[0] = make_uint4(d[0], d[1], d[2], d[3]);
     at[1] = make_uint4(d[4], d[5], d[6], d[7]);
 }
+//
+// On the way the table side's sum over the whole table, sum_j m_j B_j.  (The other one,
+// sum_j e'_j B_j (T_j + beta), is one: B is exact and the weights sum to one.  Both by a kernel
+// of their own, after the point was drawn, took 8 to 12 us and another 4 for their last step.)
 template <int NT>
 static __global__ void __launch_bounds__(kBlock) k_rows_of(TableJobs<NT> tables) {
+    __shared__ uint32_t lds[4 * 8];
     const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.y];
     uint4* __restrict__ const rows = g.rows_b;
     const uint32_t* __restrict__ const B = g.B;
-    const uint32_t N = rows ? g.N : 0;
+    const uint32_t N = g.N;
     const size_t bs = g.N;
+    Fr sum[1] = {fr_zero()};
     for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < N; j += gridDim.x * kBlock) {
         const Fr v = fr_load(B, bs, j);
+        sum[0] = fr_add(sum[0], fr_mul(v, fr_load(g.M, bs, j)));
+        if (!rows) continue;
         Fr c = fr_from_mont(v);
 #pragma unroll
         for (int k = 0; k < 8; ++k) c.l[k] = __builtin_bswap32(c.l[k]);
@@ -440,6 +451,16 @@ static __global__ void __launch_bounds__(kBlock) k_rows_of(TableJobs<NT> tables)
         words[1] = make_uint4(v.l[4], v.l[5], v.l[6], v.l[7]);
         hash[0] = make_uint4(c.l[0], c.l[1], c.l[2], c.l[3]);
         hash[1] = make_uint4(c.l[4], c.l[5], c.l[6], c.l[7]);
+    }
+    block_sum<1, 4>(sum, lds);
+    if (threadIdx.x == 0) {
+        if (g.sum_stride) {
+            fr_store(g.sums, g.sum_stride, (size_t)blockIdx.x * g.sum_step, sum[0]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) g.sums[8 * blockIdx.x + k] = sum[0].l[k];
+            mailbox_written();
+        }
     }
 }
 
@@ -580,6 +601,21 @@ static __global__ void __launch_bounds__(128) k_leaf_digests(LeafDigestArgs<NT> 
 // digest's bytes).
 static const uint32_t kVecLeaf = 128;
 
+// The smallest indices found at fault while A was made: they go to the host with the digests.
+struct BadWords {
+    const unsigned long long* from[8];  // of each instance
+    int count;
+    uint32_t* to;                       // two words each
+};
+// By the thread that publishes, once all workgroups are done.
+__device__ __forceinline__ void bad_words_publish(const BadWords& b) {
+    for (int i = 0; i < b.count; ++i) {
+        const unsigned long long v = __hip_atomic_load(b.from[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        b.to[2 * i] = (uint32_t)v;
+        b.to[2 * i + 1] = (uint32_t)(v >> 32);
+    }
+}
+
 // All vectors of a call are hashed by one launch (a leaf is a chain of 65 dependent
 // blocks whatever the vector's length: one after the other, short vectors would
 // cost as much as long ones).
@@ -628,6 +664,7 @@ struct VecLeavesArgs {
     uint32_t* ticket;
     uint32_t seq;
     SmallSource ints;  // k_leaves_to_host: of the job that asks for it
+    BadWords bad;
 };
 
 // The pointers of a job come out of an array, so the compiler does not know that
@@ -752,6 +789,7 @@ __device__ __forceinline__ void leaves_done(const VecLeavesArgs& args) {
     __syncthreads();
     if (threadIdx.x == 0 && atomicAdd(args.ticket, 1u) == gridDim.x - 1) {
         *args.ticket = 0;
+        bad_words_publish(args.bad);
         mailbox_publish(args.words, args.seq);
     }
 }
@@ -970,6 +1008,7 @@ struct DigestTreeArgs {
     uint32_t* words;
     uint32_t* ticket;
     uint32_t seq;
+    BadWords bad;
 };
 
 static __global__ void __launch_bounds__(kBlock) k_digest_tree(DigestTreeArgs args) {
@@ -1015,6 +1054,7 @@ static __global__ void __launch_bounds__(kBlock) k_digest_tree(DigestTreeArgs ar
     __syncthreads();
     if (threadIdx.x == 0 && atomicAdd(args.ticket, 1u) == gridDim.x - 1) {
         *args.ticket = 0;
+        bad_words_publish(args.bad);
         mailbox_publish(args.words, args.seq);
     }
 }
@@ -1331,53 +1371,6 @@ static __global__ void __launch_bounds__(kBlock) k_round_both(DataRoundArgs d, T
     if (blockIdx.y == 0) round_data_block<true>(d, blockIdx.x, lds);
     else if (blockIdx.y == 1) round_table_block<FOLD_T, 1>(t, blockIdx.x, lds);
     else round_table_block<FOLD_T, 2>(t, blockIdx.x, lds);
-}
-
-// Sums over the whole table, before any of its variables is bound:
-//   c1 = sum_j e'_j B_j (T_j + beta),  c2 = sum_j B_j M_j,
-// with e'_j = lo[j & mask] * hi[j >> lbits].
-struct TableConstArgs {
-    const uint32_t* B; size_t bs;
-    const uint32_t* T; size_t ts;
-    const uint32_t* M; size_t ms;
-    size_t N;
-    EqSplit eq;
-    uint32_t* partials;  // this table's two values of a workgroup
-    size_t pstride;
-    const uint32_t* bad;   // two words on their way to the host: the smallest index the hash of A has found at fault
-    uint32_t* bad_words;
-};
-
-template <int NT>
-struct TableConstJobs {
-    TableConstArgs job[NT];  // by blockIdx.y
-    Fr beta;
-    uint32_t values;  // partial sums per workgroup: two of every table
-};
-
-template <int NT>
-static __global__ void __launch_bounds__(kBlock) k_table_const(TableConstJobs<NT> jobs) {
-    __shared__ uint32_t lds[4 * 2 * 8];
-    const TableConstArgs& g = jobs.job[NT == 1 ? 0 : blockIdx.y];
-    const Fr beta = jobs.beta;
-    if (blockIdx.x == 0 && threadIdx.x < 2) {
-        g.bad_words[threadIdx.x] = g.bad[threadIdx.x];
-        mailbox_written();
-    }
-    Fr tot[2] = {fr_zero(), fr_zero()};
-    const size_t lo_mask = ((size_t)1 << g.eq.lbits) - 1;
-    for (size_t j = blockIdx.x * (size_t)kBlock + threadIdx.x; j < g.N; j += (size_t)gridDim.x * kBlock) {
-        Fr b = fr_load(g.B, g.bs, j), t = fr_load(g.T, g.ts, j), m = fr_load(g.M, g.ms, j);
-        Fr w = fr_load(g.eq.pool, g.eq.stride, g.eq.lo_off + (j & lo_mask));
-        if (g.eq.has_hi) w = fr_mul(w, fr_load(g.eq.pool, g.eq.stride, g.eq.hi_off + (j >> g.eq.lbits)));
-        tot[0] = fr_add(tot[0], fr_mul(fr_mul(w, b), fr_add(t, beta)));
-        tot[1] = fr_add(tot[1], fr_mul(b, m));
-    }
-    block_sum<2, 4>(tot, lds);
-    if (threadIdx.x == 0) {
-        fr_store(g.partials, g.pstride, (size_t)blockIdx.x * jobs.values, tot[0]);
-        fr_store(g.partials, g.pstride, (size_t)blockIdx.x * jobs.values + 1, tot[1]);
-    }
 }
 
 // Adds up a value's `count` partial sums, one workgroup per value.
