@@ -18,14 +18,14 @@
  * entry point allocates device memory; `*_workspace_bytes` says how much
  * workspace a call needs.  The library does keep a little state of its own PER
  * HOST THREAD, allocated by that thread's first call that needs it and kept until
- * the process ends: 110 KiB of pinned host memory into which kernels write the
+ * the process ends: 175 KiB of pinned host memory into which kernels write the
  * handful of sums a step returns (and, towards the end of a proof, the arrays of at
  * most 64 elements each from which the host finishes the rounds), 64 bytes of
  * coherent pinned memory through which a kernel that stays resident over a sumcheck
  * round receives the challenge, a pinned staging buffer that grows to the most a call
  * has needed (128 KiB of digest rows, or of the bytes of up to 32 leaves, cleared once
  * they are hashed; and a leaf digest of 32 bytes per 128 rows of all of the call's
- * tables), and the event pool of zkmi_profile_*.  Calls from
+ * tables or, where those have few rows, their counts, likewise cleared), and the event pool of zkmi_profile_*.  Calls from
  * different host threads share nothing; a thread's calls must not overlap.
  * zkmi_thread_init makes that allocation at a time of the caller's choosing and
  * zkmi_thread_release gives the pinned memory back (both are optional).

@@ -244,8 +244,10 @@ int zkmi_thread_init(size_t max_table_rows) {
     Mailbox* mb;
     ZK_TRY(mailbox_get(&mb));
     // counting hands over the leaf digests of all of a call's tables (one per 128 rows, 32 bytes each) and four status
-    // words for each
-    return mailbox_bulk(mb, kMailboxMaxInstances * (div_up(max_table_rows ? max_table_rows : 1, (size_t)128) * 32 + 16));
+    // words for each, or, of few rows in all (2^13 for one table, kHostCountLeaves), the counts themselves
+    const size_t digests = kMailboxMaxInstances * (div_up(max_table_rows ? max_table_rows : 1, (size_t)128) * 32 + 16);
+    const size_t counts = kMailboxMaxInstances * 32 + ((size_t)4 << 13);
+    return mailbox_bulk(mb, digests > counts ? digests : counts);
 }
 
 int zkmi_selftest_staging(uint64_t* address, uint64_t* bytes) {

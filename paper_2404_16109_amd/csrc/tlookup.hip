@@ -453,8 +453,11 @@ static size_t prove_ws_bytes(size_t D, size_t N, size_t K = 1) {
     return prove_ws_bytes_shapes(Ds, Ns, K);
 }
 
-// What counting hands to the host: the four flag words, then the digests of m's leaves.
-static size_t counted_bytes(const ProveWs& w) { return 16 + (size_t)w.nleaves * 32; }
+// What counting hands to the host: the four flag words, then the digests of m's leaves or, if there are few (host_counts),
+// the counts.
+static size_t counted_bytes(const ProveWs& w, size_t N) {
+    return 16 + std::max((size_t)w.nleaves * 32, w.nleaves <= kHostCountLeaves ? (N * 4 + 15) / 16 * 16 : 0);
+}
 // Smallest i with S_i not in T (all ones: none), once that has arrived.
 static uint64_t counted_bad(const uint8_t* staged) {
     uint64_t bad;
@@ -481,27 +484,44 @@ static TableJob table_job(const ProveWs& w, const fr_vec& T, size_t N) {
     return TableJob{T.limbs, T.stride, (uint32_t)N, w.slots, w.cap_mask, w.flags, w.canon, w.rows, w.m, w.hist, w.hist_parts, w.M, w.B, nullptr, nullptr, nullptr, nullptr, 0, 0};
 }
 
+// Whether the host hashes the leaves of m of these tables: they are few, the counts come from workgroups' histograms.
+static bool host_counts(const CountJob* jobs, int njobs) {
+    uint32_t leaves = 0;
+    for (int q = 0; q < njobs; ++q) {
+        if (!jobs[q].w->hist) return false;
+        leaves += jobs[q].w->nleaves;
+    }
+    return leaves <= kHostCountLeaves && host::Sha256::use_sha_instructions();
+}
+
 // Enqueues the multiplicities of up to kMaxTables tensors into their w.m; `seq` (not zero)
 // is published once all that they stage is there.
 template <int NT>
 static int count_rows_of(const CountJob* jobs, int njobs, uint32_t seq, Mailbox* mb, hipStream_t stream, bool counts_as_fr) {
-    TableJobs<NT> tables{};
+    CountsOutArgs<NT> out{};
+    TableJobs<NT>& tables = out.tables;
     LeafDigestArgs<NT> lf{};
     size_t most = 0;
     uint32_t most_leaves = 0, most_parts = 0;
+    const bool to_host = host_counts(jobs, njobs);
     for (int q = 0; q < njobs; ++q) {
         const CountJob& j = jobs[q];
         if (j.defer_check && !can_defer_check(*j.w, j.idx, j.D)) return ZK_E_BADARG;
         tables.job[q] = table_job(*j.w, j.T, j.N);
+        out.out[q] = (uint32_t*)j.staged;
         lf.job[q] = LeafDigestJob{(uint32_t*)(j.staged + 16), j.w->m, (uint32_t)j.N, j.w->nleaves, j.w->flags, (uint32_t*)j.staged};
         most = std::max(most, j.N);
         most_leaves = std::max(most_leaves, j.w->nleaves);
         most_parts = std::max(most_parts, j.w->hist_parts);
     }
     const unsigned ny = (unsigned)njobs;
-    hipLaunchKernelGGL(k_count_init<NT>, dim3(grid_for(hash_capacity(most) + most + 4), ny), dim3(kBlock), 0, stream, tables);
-    hipLaunchKernelGGL(k_hash_build<NT>, dim3(grid_for(most), ny), dim3(kBlock), 0, stream, tables);
-    hipLaunchKernelGGL(k_canon_rows<NT>, dim3(grid_for(most), ny), dim3(kBlock), 0, stream, tables);
+    if (most <= kSmallTable) {
+        hipLaunchKernelGGL(k_table_small<NT>, dim3(1, ny), dim3(1024), 0, stream, tables);
+    } else {
+        hipLaunchKernelGGL(k_count_init<NT>, dim3(grid_for(hash_capacity(most) + most + 4), ny), dim3(kBlock), 0, stream, tables);
+        hipLaunchKernelGGL(k_hash_build<NT>, dim3(grid_for(most), ny), dim3(kBlock), 0, stream, tables);
+        hipLaunchKernelGGL(k_canon_rows<NT>, dim3(grid_for(most), ny), dim3(kBlock), 0, stream, tables);
+    }
     for (int q = 0; q < njobs; ++q) {
         const CountJob& j = jobs[q];
         const ProveWs& w = *j.w;
@@ -540,6 +560,14 @@ static int count_rows_of(const CountJob* jobs, int njobs, uint32_t seq, Mailbox*
                                j.S.limbs, j.S.stride, j.D, per_block, idx, j.T.limbs, j.T.stride, w.rows, (uint32_t)j.N, w.slots,
                                w.cap_mask, w.canon, w.flags, (unsigned long long*)(w.flags + 2));
     }
+    if (to_host) {
+        out.words = mb->words;
+        out.ticket = jobs[0].w->flags + 1;
+        out.seq = seq;
+        hipLaunchKernelGGL(k_counts_out<NT>, dim3((unsigned)div_up(most, 64), ny), dim3(1024), 0, stream, out);
+        ZK_HIP_TRY(hipGetLastError());
+        return ZK_OK;
+    }
     if (most_parts) {
         const uint32_t group = 16;
         size_t rows = 0;  // of the tables that have histograms
@@ -566,6 +594,23 @@ static void digest_of_leaves(uint8_t out[32], const uint8_t* leaves, uint32_t nl
     host::Sha256 h;
     h.update(leaves, (size_t)nleaves * 32);
     h.finish(out);
+}
+
+// Counts are the caller's witness: they do not stay in memory that outlives the call.
+static void forget_counts(const CountJob* jobs, int njobs) {
+    if (!host_counts(jobs, njobs)) return;
+    for (int q = 0; q < njobs; ++q) memset(jobs[q].staged + 16, 0, jobs[q].N * 4);
+}
+
+// The digest of m from what counting has staged.
+static void digest_of_counts(uint8_t out[32], const CountJob& j, bool to_host) {
+    if (!to_host) {
+        digest_of_leaves(out, j.staged + 16, j.w->nleaves);
+        return;
+    }
+    uint8_t leaves[kHostCountLeaves * 32];
+    host::Sha256::hash_each(leaves, j.staged + 16, std::min(j.N, (size_t)kLeafCounts) * 4, j.w->nleaves);
+    digest_of_leaves(out, leaves, j.w->nleaves);
 }
 
 static const size_t kHostPairs = kMailboxShipEntries / 2;
@@ -1005,7 +1050,7 @@ static int prove_core(const ProveCall& c) {
         size_t total = 0, at[kMailboxMaxInstances];
         for (size_t i = 0; i < K; ++i) {
             at[i] = total;
-            total += counted_bytes(inst[i].w);
+            total += counted_bytes(inst[i].w, inst[i].N);
         }
         ZK_TRY(mailbox_bulk(mb, total));
         uint8_t* const staged = mb->bulk + kBulkDigests;
@@ -1031,11 +1076,13 @@ static int prove_core(const ProveCall& c) {
                     c.baux->bad_instance = i;
                     c.baux->bad_index = bad;
                 }
+                forget_counts(counts, (int)K);
                 ZK_HIP_TRY(hipStreamSynchronize(stream));
                 return ZK_E_NOT_IN_TABLE;
             }
-            digest_of_leaves(inst[i].md, staged + at[i] + 16, inst[i].w.nleaves);
+            digest_of_counts(inst[i].md, counts[i], host_counts(counts, (int)K));
         }
+        forget_counts(counts, (int)K);
     }
 
     uint64_t dims[1 + 2 * kMailboxMaxInstances];
@@ -1158,6 +1205,7 @@ static int prove_core(const ProveCall& c) {
             const uint32_t seq = mb->next_seq();
             ZK_TRY(count_rows(&job, 1, seq, mb, stream));
             ZK_TRY(mailbox_wait(mb, seq, stream));
+            forget_counts(&job, 1);
             if (counted_bad(staged) == UINT64_MAX) continue;
             at = i;
             bad = counted_bad(staged);
@@ -2190,12 +2238,13 @@ int tlookup_multiplicities(uint32_t* m, fr_vec S, const uint32_t* idx, fr_vec T,
     Carver cv(ws, ws_bytes);
     ProveWs w;
     carve_prove(w, cv, D, N);
-    ZK_TRY(mailbox_bulk(mb, counted_bytes(w)));
+    ZK_TRY(mailbox_bulk(mb, counted_bytes(w, N)));
     const uint8_t* const staged = mb->bulk + kBulkDigests;
     const uint32_t seq = mb->next_seq();
     const CountJob job{&w, S, idx, T, D, N, mb->bulk + kBulkDigests, false, nullptr};
     ZK_TRY(count_rows(&job, 1, seq, mb, as_stream(stream)));
     ZK_TRY(mailbox_wait(mb, seq, as_stream(stream)));
+    forget_counts(&job, 1);
     const uint64_t bad = counted_bad(staged);
     if (bad != UINT64_MAX) {
         if (bad_index) *bad_index = bad;

@@ -60,6 +60,11 @@ struct TableJobs {
     TableJob job[NT];
 };
 
+// How far apart the slots are that a value looks at one after the other: odd, so that it comes
+// to all of them.  (Next to each other, full stretches of the half full table grow, and
+// wavefronts wait for the longest.)
+__device__ __forceinline__ uint32_t hash_step(uint32_t hash) { return (hash >> 12) | 1u; }
+
 // Every row j claims the first slot of its probe sequence that is empty or holds
 // a row with the same value; equal values meet in one slot and the lowest row
 // wins.  Slots never empty again and the value class of a slot never changes, so
@@ -74,7 +79,8 @@ static __global__ void __launch_bounds__(kBlock) k_hash_build(TableJobs<NT> tabl
     const size_t ts = g.ts;
     for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < N; j += gridDim.x * kBlock) {
         Fr v = fr_load(T, ts, j);
-        uint32_t pos = fr_hash(v) & cap_mask;
+        const uint32_t hash = fr_hash(v), by = hash_step(hash);
+        uint32_t pos = hash & cap_mask;
         for (uint32_t step = 0; step <= cap_mask; ++step) {
             uint32_t cur = atomicCAS(&slots[pos], kEmptySlot, j);
             if (cur == kEmptySlot) break;  // claimed
@@ -83,7 +89,7 @@ static __global__ void __launch_bounds__(kBlock) k_hash_build(TableJobs<NT> tabl
                 atomicOr(dup_flag, 1u);
                 break;
             }
-            pos = (pos + 1) & cap_mask;
+            pos = (pos + by) & cap_mask;
         }
     }
 }
@@ -91,12 +97,13 @@ static __global__ void __launch_bounds__(kBlock) k_hash_build(TableJobs<NT> tabl
 // Row of the table holding value v (lowest row of equal ones), or kEmptySlot.
 __device__ __forceinline__ uint32_t hash_find(const uint32_t* __restrict__ slots, uint32_t cap_mask,
                                               const uint32_t* __restrict__ T, size_t ts, const Fr& v) {
-    uint32_t pos = fr_hash(v) & cap_mask;
+    const uint32_t hash = fr_hash(v), by = hash_step(hash);
+    uint32_t pos = hash & cap_mask;
     for (uint32_t step = 0; step <= cap_mask; ++step) {
         uint32_t cur = slots[pos];
         if (cur == kEmptySlot) return kEmptySlot;
         if (fr_equal(fr_load(T, ts, cur), v)) return cur;
-        pos = (pos + 1) & cap_mask;
+        pos = (pos + by) & cap_mask;
     }
     return kEmptySlot;
 }
@@ -105,7 +112,8 @@ __device__ __forceinline__ uint32_t hash_find(const uint32_t* __restrict__ slots
 // is one 32-byte access instead of eight words from eight limb planes.
 __device__ __forceinline__ uint32_t hash_find_rows(const uint32_t* __restrict__ slots, uint32_t cap_mask,
                                                    const uint4* __restrict__ rows, const Fr& v) {
-    uint32_t pos = fr_hash(v) & cap_mask;
+    const uint32_t hash = fr_hash(v), by = hash_step(hash);
+    uint32_t pos = hash & cap_mask;
     for (uint32_t step = 0; step <= cap_mask; ++step) {
         uint32_t cur = slots[pos];
         if (cur == kEmptySlot) return kEmptySlot;
@@ -113,7 +121,7 @@ __device__ __forceinline__ uint32_t hash_find_rows(const uint32_t* __restrict__ 
         const uint32_t diff = (lo.x ^ v.l[0]) | (lo.y ^ v.l[1]) | (lo.z ^ v.l[2]) | (lo.w ^ v.l[3]) |
                               (hi.x ^ v.l[4]) | (hi.y ^ v.l[5]) | (hi.z ^ v.l[6]) | (hi.w ^ v.l[7]);
         if (diff == 0) return cur;
-        pos = (pos + 1) & cap_mask;
+        pos = (pos + by) & cap_mask;
     }
     return kEmptySlot;
 }
@@ -136,6 +144,45 @@ static __global__ void __launch_bounds__(kBlock) k_canon_rows(TableJobs<NT> tabl
         rows[2 * j] = make_uint4(v.l[0], v.l[1], v.l[2], v.l[3]);
         rows[2 * j + 1] = make_uint4(v.l[4], v.l[5], v.l[6], v.l[7]);
     }
+}
+
+// All that counting starts from (k_count_init, k_hash_build, k_canon_rows) for tables of few
+// rows, a workgroup each, the hash in LDS until it is done: 2^8 rows 20 us in three launches,
+// 10 in this one.
+static const size_t kSmallTable = 2048;
+template <int NT>
+static __global__ void __launch_bounds__(1024) k_table_small(TableJobs<NT> tables) {
+    __shared__ uint32_t slots[2 * kSmallTable];
+    __shared__ uint32_t dup;
+    const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.y];
+    const uint32_t cap_mask = g.cap_mask, N = g.N;  // at most kSmallTable rows, twice as many slots
+    const uint32_t* __restrict__ const T = g.T;
+    for (uint32_t i = threadIdx.x; i <= cap_mask; i += 1024) slots[i] = kEmptySlot;
+    for (uint32_t j = threadIdx.x; j < N; j += 1024) g.m[j] = 0;
+    if (threadIdx.x == 0) dup = 0;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < N; j += 1024) {
+        const Fr v = fr_load(T, g.ts, j);
+        g.rows[2 * j] = make_uint4(v.l[0], v.l[1], v.l[2], v.l[3]);
+        g.rows[2 * j + 1] = make_uint4(v.l[4], v.l[5], v.l[6], v.l[7]);
+        const uint32_t hash = fr_hash(v), by = hash_step(hash);
+        uint32_t pos = hash & cap_mask;
+        for (uint32_t step = 0; step <= cap_mask; ++step) {
+            const uint32_t cur = atomicCAS(&slots[pos], kEmptySlot, j);
+            if (cur == kEmptySlot) break;  // claimed
+            if (fr_equal(fr_load(T, g.ts, cur), v)) {
+                atomicMin(&slots[pos], j);
+                dup = 1;
+                break;
+            }
+            pos = (pos + by) & cap_mask;
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i <= cap_mask; i += 1024) g.slots[i] = slots[i];
+    if (threadIdx.x < 4) g.flags[threadIdx.x] = threadIdx.x == 0 ? dup : threadIdx.x == 1 ? 0u : 0xffffffffu;
+    // without duplicates every row is its value's lowest
+    for (uint32_t j = threadIdx.x; j < N; j += 1024) g.canon[j] = dup ? hash_find(slots, cap_mask, T, g.ts, fr_load(T, g.ts, j)) : j;
 }
 
 // The row of every S_i, for calls without hints (the smallest i that has none ends up in
@@ -488,9 +535,56 @@ static __global__ void __launch_bounds__(kBlock) k_counts_to_fr(TableJobs<NT> ta
         fr_store(g.M, g.N, j, fr_from_u32(g.m[j]));
 }
 
+// The last step of counting where the host hashes m: the workgroups' histograms added up,
+// the counts as they are and as field elements, and to pinned memory, behind the flags (in one
+// launch what k_hist_reduce, k_leaf_digests and k_counts_to_fr do in three).  A workgroup takes
+// 64 rows, sixteen threads each.
+template <int NT>
+struct CountsOutArgs {
+    TableJobs<NT> tables;
+    uint32_t* out[NT];  // four flag words, then the counts
+    uint32_t* words;    // the mailbox
+    uint32_t* ticket;
+    uint32_t seq;
+};
+template <int NT>
+static __global__ void __launch_bounds__(1024) k_counts_out(CountsOutArgs<NT> args) {
+    __shared__ uint32_t sums[16][64];
+    const int t = NT == 1 ? 0 : blockIdx.y;
+    const TableJob& g = args.tables.job[t];
+    const uint32_t lane = threadIdx.x & 63, group = threadIdx.x >> 6, j = blockIdx.x * 64 + lane;
+    uint32_t acc = 0;
+    if (j < g.N) {
+#pragma unroll 8
+        for (uint32_t b = group; b < g.hist_parts; b += 16) acc += g.hist[(size_t)b * g.N + j];
+    }
+    sums[group][lane] = acc;
+    __syncthreads();
+    if (threadIdx.x < 64 && j < g.N) {
+        acc = g.m[j];  // long runs of one row
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc += sums[q][lane];
+        g.m[j] = acc;
+        fr_store(g.M, g.N, j, fr_from_u32(acc));
+        args.out[t][4 + j] = acc;
+        if (j < 4) args.out[t][j] = g.flags[j];
+        if (g.N < 4 && j == 0)
+            for (uint32_t q = g.N; q < 4; ++q) args.out[t][q] = g.flags[q];
+        mailbox_written();
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(args.ticket, 1u) == gridDim.x * gridDim.y - 1) {
+        *args.ticket = 0;
+        mailbox_publish(args.words, args.seq);
+    }
+}
+
 // ---- SHA-256 of the leaves of m ---------------------------------------------------
 
 static const uint32_t kLeafCounts = 128;
+// Up to this many leaves of a call the host hashes: 0.25 us each with SHA instructions, where the
+// device takes 26 us for any number (and up to 27 for 512).
+static const uint32_t kHostCountLeaves = 64;
 
 // The rounds of a chain of blocks whose schedules (round constants added) another
 // wavefront of the workgroup makes in LDS, one block ahead: kw[block & 1], four rounds
