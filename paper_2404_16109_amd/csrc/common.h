@@ -138,8 +138,8 @@ static const size_t kMailboxShip = 2048;
 static const size_t kMailboxShipEntries = 64;
 static const size_t kMailboxShipWords = 5 * kMailboxShipEntries * 8;
 static const size_t kMailboxGrid = kMailboxShip + kMailboxMaxInstances * kMailboxShipWords;
-// The shares of the table side's sum over a table of up to 2^16 rows (k_rows_of), which the host adds up.
-static const size_t kMailboxTableShares = 256;
+// The shares of the table side's sum over a table of up to 2^16 rows (k_table_sum), which the host adds up.
+static const size_t kMailboxTableShares = 128;
 static const size_t kMailboxTableSums = kMailboxGrid + kMailboxMaxInstances * 89 * 8;
 static const size_t kMailboxWords = kMailboxTableSums + kMailboxMaxInstances * kMailboxTableShares * 8;
 static const size_t kMailboxInvB = 1024;    // grand total of the table-side inversion (+16 per instance)

@@ -481,7 +481,7 @@ struct CountJob {
 };
 
 static TableJob table_job(const ProveWs& w, const fr_vec& T, size_t N) {
-    return TableJob{T.limbs, T.stride, (uint32_t)N, w.slots, w.cap_mask, w.flags, w.canon, w.rows, w.m, w.hist, w.hist_parts, w.M, w.B, nullptr, nullptr, nullptr, nullptr, 0, 0};
+    return TableJob{T.limbs, T.stride, (uint32_t)N, w.slots, w.cap_mask, w.flags, w.canon, w.rows, w.m, w.hist, w.hist_parts, w.M, w.B, nullptr, nullptr, nullptr};
 }
 
 // Whether the host hashes the leaves of m of these tables: they are few, the counts come from workgroups' histograms.
@@ -1159,29 +1159,18 @@ static int prove_core(const ProveCall& c) {
         ZK_TRY(batch_inverse_end(jobs, pre, (int)njobs, stream));
         TableJobs<kMaxTables> tables{};
         size_t rows = 0;
-        for (size_t i = 0; i < K; ++i) rows = std::max(rows, inst[i].N);
-        // shares of the sums of B m: the host's to add up, unless there are long tables
-        const bool long_tables = rows > kLdsHistMaxRows;
-        table_shares = grid_for(rows, kBlock, long_tables ? kMaxPartialBlocks / 4 : kMailboxTableShares);
         for (size_t i = 0; i < K; ++i) {
             TableJob& t = tables.job[i] = table_job(inst[i].w, inst[i].T, inst[i].N);
-            t.sums = long_tables ? inst[0].w.partT + i : mb->words + kMailboxTableSums + i * kMailboxTableShares * 8;
-            t.sum_stride = long_tables ? inst[0].w.part_blocks * 6 : 0;
-            t.sum_step = (uint32_t)K;
             if (!inst[i].gather) continue;
+            rows = std::max(rows, inst[i].N);
             t.rows_b = inst[i].by_row ? inst[i].rows_first() : inst[i].w.rows_b;
             if (inst[i].by_row) {
                 t.rows_pair = inst[i].rows_pair();
                 t.rows_hash = inst[i].rows_hash();
             }
         }
-        if (K == 1) hipLaunchKernelGGL(k_rows_of<1>, dim3(table_shares), dim3(kBlock), 0, stream, TableJobs<1>{{tables.job[0]}});
-        else hipLaunchKernelGGL(k_rows_of<kMaxTables>, dim3(table_shares, (unsigned)K), dim3(kBlock), 0, stream, tables);
-        if (long_tables) {
-            launch_final_sum(inst[0].w.partT, inst[0].w.part_blocks * 6, table_shares, (int)K, mb->words + kMailboxTableC, mb->words, 0,
-                             inst[0].w.flags + 1, stream);
-            table_shares = 0;
-        }
+        if (rows && K == 1) hipLaunchKernelGGL(k_rows_of<1>, dim3(grid_for(rows)), dim3(kBlock), 0, stream, TableJobs<1>{{tables.job[0]}});
+        else if (rows) hipLaunchKernelGGL(k_rows_of<kMaxTables>, dim3(grid_for(rows), (unsigned)K), dim3(kBlock), 0, stream, tables);
         ZK_HIP_TRY(hipGetLastError());
     }
 
@@ -1270,6 +1259,24 @@ static int prove_core(const ProveCall& c) {
         for (size_t i = 0; i < K; ++i) bad.from[i] = (const unsigned long long*)(inst[i].w.flags + 2);
         ZK_TRY(vec_digest_launch(jobs, 2 * (int)K, dig_leaves, mb, seq, inst[0].w.flags + 1, stream,
                                  from_ints ? &ints_src : nullptr, bad));
+        // the table side's sums, in the time the host takes: read with the first round's (shares, the host's to add up,
+        // unless there are long tables)
+        TableSumJobs sums;
+        memset(&sums, 0, sizeof sums);
+        size_t rows = 0;
+        for (size_t i = 0; i < K; ++i) rows = std::max(rows, inst[i].N);
+        const bool long_tables = rows > kLdsHistMaxRows;
+        const unsigned shares = grid_for(rows, kBlock, long_tables ? kMaxPartialBlocks / 4 : kMailboxTableShares);
+        for (size_t i = 0; i < K; ++i)
+            sums.job[i] = TableSumJob{inst[i].w.B, inst[i].w.M, inst[i].N,
+                                      long_tables ? inst[0].w.partT + i : mb->words + kMailboxTableSums + i * kMailboxTableShares * 8,
+                                      long_tables ? inst[0].w.part_blocks * 6 : 0, (uint32_t)K};
+        hipLaunchKernelGGL(k_table_sum, dim3(shares, (unsigned)K), dim3(kBlock), 0, stream, sums);
+        if (long_tables)
+            launch_final_sum(inst[0].w.partT, inst[0].w.part_blocks * 6, shares, (int)K, mb->words + kMailboxTableC, mb->words, 0,
+                             inst[0].w.flags + 1, stream);
+        table_shares = long_tables ? 0 : shares;
+        ZK_HIP_TRY(hipGetLastError());
         ZK_TRY(mailbox_wait(mb, seq, stream));
         for (size_t i = 0; i < K; ++i) {
             vec_digest_finish(inst[i].dA, jobs[2 * i]);
@@ -1297,13 +1304,17 @@ static int prove_core(const ProveCall& c) {
     }
 
     // The table side while none of its variables is bound: alpha^2 sum_j e'_j B_j (T_j + beta) - sum_j m_j B_j, the first
-    // sum being one (k_rows_of).
-    for (size_t i = 0; i < K; ++i) {
-        const uint32_t* at = mb->words + kMailboxTableSums + i * kMailboxTableShares * 8;
-        inst[i].sum_mB = table_shares ? zero() : from_dev(mb->words + kMailboxTableC + 8 * i);
-        for (unsigned q = 0; q < table_shares; ++q) inst[i].sum_mB = add(inst[i].sum_mB, from_dev(at + 8 * q));
-        inst[i].cB = sub(alpha2, inst[i].sum_mB);
-    }
+    // sum being one (k_table_sum).  Its shares are there once anything enqueued after them is.
+    bool table_sums_read = false;
+    auto read_table_sums = [&] {
+        for (size_t i = 0; i < K && !table_sums_read; ++i) {
+            const uint32_t* at = mb->words + kMailboxTableSums + i * kMailboxTableShares * 8;
+            inst[i].sum_mB = table_shares ? zero() : from_dev(mb->words + kMailboxTableC + 8 * i);
+            for (unsigned q = 0; q < table_shares; ++q) inst[i].sum_mB = add(inst[i].sum_mB, from_dev(at + 8 * q));
+            inst[i].cB = sub(alpha2, inst[i].sum_mB);
+        }
+        table_sums_read = true;
+    };
 
     // weight tables: instance i uses u_[skip_i:], so instances of one length share a pool
     EqPool pools[kMailboxMaxInstances];
@@ -1781,6 +1792,7 @@ static int prove_core(const ProveCall& c) {
             for (int x = 0; x < 2; ++x) I.gs[x] = add(I.gs[2 * x], I.gs[2 * x + 1]);
         }
         if (any_ship) read_shipped(k);
+        if (any_launch) read_table_sums();
         for (size_t i = 0; i < K; ++i)
             if (k == inst[i].skip && inst[i].by_row) ZK_TRY(report_bad());
 
@@ -1938,6 +1950,7 @@ static int prove_core(const ProveCall& c) {
             read_shipped(n);
         }
         ZK_HIP_TRY(hipStreamSynchronize(stream));  // everything of this call has left the device
+        read_table_sums();
         uint8_t* first = out;
         for (size_t i = 0; i < K; ++i) {
             const HostTail& t = *inst[i].tail;

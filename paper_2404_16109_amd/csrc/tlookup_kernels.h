@@ -47,9 +47,6 @@ struct TableJob {
     uint4* rows_b;      // null: B's rows are not asked for
     uint4* rows_hash;   // not null: B's canonical values by themselves, and what the rounds read by row:
     uint4* rows_pair;   // (tlookup_rows.h)
-    uint32_t* sums;     // k_rows_of's sums of B M: a workgroup's eight words at 8 blockIdx.x,
-    size_t sum_stride;  // or (not zero) limb planes of this stride, a workgroup's value at sum_step blockIdx.x
-    uint32_t sum_step;
 };
 // (Calls with one table pass one, whose pointers the compiler can see to be global: through
 // an array they are flat, and flat loads share a counter with the LDS; the counts' leaves
@@ -465,23 +462,15 @@ __device__ __forceinline__ void row_digits(uint4* at, const Fr& v) {
     at[0] = make_uint4(d[0], d[1], d[2], d[3]);
     at[1] = make_uint4(d[4], d[5], d[6], d[7]);
 }
-//
-// On the way the table side's sum over the whole table, sum_j m_j B_j.  (The other one,
-// sum_j e'_j B_j (T_j + beta), is one: B is exact and the weights sum to one.  Both by a kernel
-// of their own, after the point was drawn, took 8 to 12 us and another 4 for their last step.)
 template <int NT>
 static __global__ void __launch_bounds__(kBlock) k_rows_of(TableJobs<NT> tables) {
-    __shared__ uint32_t lds[4 * 8];
     const TableJob& g = tables.job[NT == 1 ? 0 : blockIdx.y];
     uint4* __restrict__ const rows = g.rows_b;
     const uint32_t* __restrict__ const B = g.B;
-    const uint32_t N = g.N;
+    const uint32_t N = rows ? g.N : 0;
     const size_t bs = g.N;
-    Fr sum[1] = {fr_zero()};
     for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < N; j += gridDim.x * kBlock) {
         const Fr v = fr_load(B, bs, j);
-        sum[0] = fr_add(sum[0], fr_mul(v, fr_load(g.M, bs, j)));
-        if (!rows) continue;
         Fr c = fr_from_mont(v);
 #pragma unroll
         for (int k = 0; k < 8; ++k) c.l[k] = __builtin_bswap32(c.l[k]);
@@ -498,16 +487,6 @@ static __global__ void __launch_bounds__(kBlock) k_rows_of(TableJobs<NT> tables)
         words[1] = make_uint4(v.l[4], v.l[5], v.l[6], v.l[7]);
         hash[0] = make_uint4(c.l[0], c.l[1], c.l[2], c.l[3]);
         hash[1] = make_uint4(c.l[4], c.l[5], c.l[6], c.l[7]);
-    }
-    block_sum<1, 4>(sum, lds);
-    if (threadIdx.x == 0) {
-        if (g.sum_stride) {
-            fr_store(g.sums, g.sum_stride, (size_t)blockIdx.x * g.sum_step, sum[0]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) g.sums[8 * blockIdx.x + k] = sum[0].l[k];
-            mailbox_written();
-        }
     }
 }
 
@@ -1465,6 +1444,38 @@ static __global__ void __launch_bounds__(kBlock) k_round_both(DataRoundArgs d, T
     if (blockIdx.y == 0) round_data_block<true>(d, blockIdx.x, lds);
     else if (blockIdx.y == 1) round_table_block<FOLD_T, 1>(t, blockIdx.x, lds);
     else round_table_block<FOLD_T, 2>(t, blockIdx.x, lds);
+}
+
+// The table side's sum over the whole table, sum_j m_j B_j, while the host is busy with the
+// digests.  (The other one, sum_j e'_j B_j (T_j + beta), is one: B is exact and the weights sum
+// to one.)  Shares by workgroup: eight words at 8 blockIdx.x of `out`, pinned host memory, or
+// (stride not zero) element step blockIdx.x of limb planes.
+struct TableSumJob {
+    const uint32_t* B;
+    const uint32_t* M;
+    size_t N;
+    uint32_t* out;
+    size_t stride;
+    uint32_t step;
+};
+struct TableSumJobs {
+    TableSumJob job[kMaxTables];  // by blockIdx.y
+};
+static __global__ void __launch_bounds__(kBlock) k_table_sum(TableSumJobs jobs) {
+    __shared__ uint32_t lds[4 * 8];
+    const TableSumJob& g = jobs.job[blockIdx.y];
+    Fr sum[1] = {fr_zero()};
+    for (size_t j = blockIdx.x * (size_t)kBlock + threadIdx.x; j < g.N; j += (size_t)gridDim.x * kBlock)
+        sum[0] = fr_add(sum[0], fr_mul(fr_load(g.B, g.N, j), fr_load(g.M, g.N, j)));
+    block_sum<1, 4>(sum, lds);
+    if (threadIdx.x != 0) return;
+    if (g.stride) {
+        fr_store(g.out, g.stride, (size_t)blockIdx.x * g.step, sum[0]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) g.out[8 * blockIdx.x + k] = sum[0].l[k];
+        mailbox_written();
+    }
 }
 
 // Adds up a value's `count` partial sums, one workgroup per value.
