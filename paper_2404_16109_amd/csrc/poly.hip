@@ -4,6 +4,7 @@
 
 #include "internal.h"
 #include "mfma_dev.h"
+#include "mle_dev.h"
 #include "reduce_dev.h"
 
 namespace zkmi {
@@ -300,65 +301,9 @@ __global__ void __launch_bounds__(kBlock) k_mle_table(MleTableArgs args) {
     toeplitz_store(args.table + (size_t)entry * kToepBytes, digits, (int)(g & 31));
 }
 
-// One stage of up to kMleMaxJobs evaluations: workgroup b of a job makes outputs
-// 128 b .. 128 b + 127, its wavefronts sharing the constants (each adds a quarter of
-// them up; the column sums meet in LDS), so that the short last stages are not one
-// wavefront's chain of 64 loads.
-struct MleStageJob {
-    ToepSource src;
-    uint32_t* dst;
-    size_t dst_stride;
-    size_t P;
-    const uint4* table;
-    uint32_t C;
-    uint32_t first_block;
-    ToepBias bias;
-};
-struct MleStageArgs {
-    MleStageJob job[kMleMaxJobs];
-    int njobs;
-    uint32_t* words;   // the mailbox, if this launch publishes
-    uint32_t* ticket;
-    uint32_t seq;
-};
-
 __global__ void __launch_bounds__(kBlock) k_mle_stage(MleStageArgs args) {
-    __shared__ int part[4][4][16][64];  // [from wavefront][tile][row][lane]
-    int q = 0;
-    while (q + 1 < args.njobs && blockIdx.x >= args.job[q + 1].first_block) ++q;
-    const MleStageJob& job = args.job[q];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 31;
-    const size_t base = (size_t)(blockIdx.x - job.first_block) * 128;
-    v16i acc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[j][r] = 0;
-    const unsigned c0 = job.C * wave / 4, c1 = job.C * (wave + 1) / 4;
-    if (job.src.vec) toeplitz_accumulate<true>(acc, job.src, job.P, base, job.table, c0, c1);
-    else toeplitz_accumulate<false>(acc, job.src, job.P, base, job.table, c0, c1);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) part[wave][j][r][lane] = acc[j][r];
-    __syncthreads();
-    if (wave < 2) {
-        // tiles (wave, wave + 2) with 16-byte places: lanes 0..31 then hold element 4 i + wave, the others 4 i + 2 + wave;
-        // otherwise tiles (2 wave, 2 wave + 1): element 64 wave + lane
-        const int ta = job.src.vec ? wave : 2 * wave, tb = job.src.vec ? wave + 2 : 2 * wave + 1;
-        v16i a, b;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            a[r] = part[0][ta][r][lane] + part[1][ta][r][lane] + part[2][ta][r][lane] + part[3][ta][r][lane];
-            b[r] = part[0][tb][r][lane] + part[1][tb][r][lane] + part[2][tb][r][lane] + part[3][tb][r][lane];
-        }
-        const Fr v = toeplitz_finish(a, b, job.bias);
-        const size_t e = job.src.vec ? base + 4 * (size_t)i + 2 * (lane >> 5) + wave : base + 64 * (size_t)wave + lane;
-        if (e < job.P) {
-            fr_store(job.dst, job.dst_stride, e, v);
-            if (args.seq) mailbox_written();
-        }
-    }
+    __shared__ MleParts part;
+    mle_stage_block(args, blockIdx.x, part);
     if (args.seq) {
         __syncthreads();
         if (threadIdx.x != 0) return;
@@ -417,7 +362,7 @@ static ToepBias mle_bias(uint32_t C) {
     return b;
 }
 
-int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint32_t seq, hipStream_t stream) {
+int mle_eval_begin(MlePlan& plan, const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint32_t seq, hipStream_t stream) {
     if (njobs < 1 || njobs > kMleMaxJobs) return ZK_E_BADARG;
     // the points: at most two different ones (a lookup's tensor and its table)
     MleTableArgs targs;
@@ -439,13 +384,13 @@ int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint
         const int s = mle_stage_count(jobs[q].nvars);
         if (s > most_stages) most_stages = s;
     }
-    if (most_stages == 0) {  // single elements are their own values: no scratch is asked for
-        for (int q = 0; q < njobs; ++q)
-            hipLaunchKernelGGL(k_emit, dim3(1), dim3(64), 0, stream, jobs[q].a, jobs[q].stride, (size_t)0, jobs[q].out_words,
-                               mb->words, q + 1 == njobs ? seq : 0u);
-        ZK_HIP_TRY(hipGetLastError());
-        return ZK_OK;
-    }
+    if (most_stages > kMleMaxSteps) return ZK_E_BADARG;
+    memset(&plan, 0, sizeof plan);
+    plan.steps = most_stages;
+    plan.njobs = njobs;
+    plan.seq = seq;
+    for (int q = 0; q < njobs; ++q) plan.jobs[q] = jobs[q];
+    if (most_stages == 0) return ZK_OK;  // single elements are their own values: no scratch is asked for
     targs.first[0] = 0;
     targs.first[1] = mle_table_entries(targs.nvars[0]);
     targs.total = targs.first[1] + (npoints == 2 ? mle_table_entries(targs.nvars[1]) : 0);
@@ -471,16 +416,10 @@ int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint
         table[q] = (const uint4*)(targs.table + (size_t)(point_of[q] ? targs.first[1] : 0) * kToepBytes);
     }
     for (int step = 0; step < most_stages; ++step) {
-        MleStageArgs args;
-        memset(&args, 0, sizeof args);
-        uint32_t blocks = 0;
+        MleStageArgs& args = plan.step[step];
+        uint32_t& blocks = plan.blocks[step];
         for (int q = 0; q < njobs; ++q) {
             const int s = mle_stage_count(jobs[q].nvars), t = step - (most_stages - s);
-            if (s == 0 && step == most_stages - 1) {  // a single element: its value
-                hipLaunchKernelGGL(k_emit, dim3(1), dim3(64), 0, stream, jobs[q].a, jobs[q].stride, (size_t)0, jobs[q].out_words,
-                                   mb->words, 0u);
-                continue;
-            }
             if (s == 0 || t < 0) continue;
             const int vars = mle_stage_vars(jobs[q].nvars, s, t);
             left[q] -= vars;
@@ -510,10 +449,32 @@ int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint
             args.ticket = ticket;
             args.seq = seq;
         }
-        hipLaunchKernelGGL(k_mle_stage, dim3(blocks), dim3(kBlock), 0, stream, args);
     }
     ZK_HIP_TRY(hipGetLastError());
     return ZK_OK;
+}
+
+int mle_eval_rest(const MlePlan& plan, int first, Mailbox* mb, hipStream_t stream) {
+    for (int step = first; step + 1 < plan.steps; ++step)
+        hipLaunchKernelGGL(k_mle_stage, dim3(plan.blocks[step]), dim3(kBlock), 0, stream, plan.step[step]);
+    for (int q = 0; q < plan.njobs; ++q) {  // a single element: its value
+        const MleJob& j = plan.jobs[q];
+        if (j.nvars == 0)
+            hipLaunchKernelGGL(k_emit, dim3(1), dim3(64), 0, stream, j.a, j.stride, (size_t)0, j.out_words, mb->words,
+                               plan.steps == 0 && q + 1 == plan.njobs ? plan.seq : 0u);
+    }
+    if (plan.steps) {
+        const int last = plan.steps - 1;
+        hipLaunchKernelGGL(k_mle_stage, dim3(plan.blocks[last]), dim3(kBlock), 0, stream, plan.step[last]);
+    }
+    ZK_HIP_TRY(hipGetLastError());
+    return ZK_OK;
+}
+
+int mle_eval_launch(const MleJob* jobs, int njobs, Carver& cv, Mailbox* mb, uint32_t seq, hipStream_t stream) {
+    MlePlan plan;
+    ZK_TRY(mle_eval_begin(plan, jobs, njobs, cv, mb, seq, stream));
+    return mle_eval_rest(plan, 0, mb, stream);
 }
 
 int mle_eval_run(const uint32_t* a, size_t stride, int nvars, const host::F* point, Carver& cv, Mailbox* mb,

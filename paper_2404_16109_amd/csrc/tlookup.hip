@@ -239,10 +239,19 @@ static void launch_leaves_to_host(const VecLeavesArgs& lv, hipStream_t stream) {
     hipLaunchKernelGGL(k_leaves_to_host<MODE>, dim3((unsigned)div_up(lv.groups, kBlock)), dim3(kBlock), 0, stream, lv);
 }
 
+// What may run in the launch of a verification's leaves.
+struct LeavesBeside {
+    LeafDigestJob counts;
+    const MleStageArgs* stage;
+    uint32_t stage_blocks;
+    bool launched;  // it has: leaves in pairs
+};
+
 // The jobs that have rows (LeafGather) all compare them with S, or all with the
 // integers, or none: by `ints` and whether they have an S; those that are only hashed do not.
 static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Mailbox* mb, uint32_t seq, uint32_t* ticket,
-                             hipStream_t stream, const SmallSource* ints = nullptr, const BadWords& bad = BadWords{}) {
+                             hipStream_t stream, const SmallSource* ints = nullptr, const BadWords& bad = BadWords{},
+                             LeavesBeside* beside = nullptr) {
     if (njobs < 1 || njobs > kDigestMaxJobs) return ZK_E_BADARG;
     ZK_TRY(mailbox_bulk(mb, 0));
     VecLeavesArgs lv{};
@@ -308,7 +317,17 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
     if (mode == kLeafRowsCheck || mode == kLeafRowsInts) return ZK_E_BADARG;  // cannot happen: k_make_a or the rounds compare
     if (mode == kLeafRows) launch_leaves<kLeafRows>(lv, stream);
     else if (mode == kLeafRowsHash) launch_leaves<kLeafRowsHash>(lv, stream);
-    else launch_leaves<kLeafPlain>(lv, stream);
+    else if (beside && leaves_in_pairs<kLeafPlain>(lv.groups)) {
+        LeavesBesideArgs args;
+        memset(&args, 0, sizeof args);
+        args.leaves = lv;
+        args.counts = beside->counts;
+        args.count_blocks = (uint32_t)div_up(beside->counts.nleaves, 128);
+        args.stage = *beside->stage;
+        if (lv.seq || args.stage.seq) return ZK_E_BADARG;  // cannot happen: neither is the last
+        hipLaunchKernelGGL(k_leaves_beside, dim3((lv.groups + 1) / 2 + args.count_blocks + beside->stage_blocks), dim3(kBlock), 0, stream, args);
+        beside->launched = true;
+    } else launch_leaves<kLeafPlain>(lv, stream);
     // up the trees, all rows in one launch, a factor of up to kTreeChunk per launch
     while (more) {
         DigestTreeArgs tr;
@@ -2154,7 +2173,6 @@ static int verify_core(const VerifyCall& c) {
         int ntrees = 0;
         if (have_a) trees[ntrees++] = VecDigestJob{wit->A.limbs, wit->A.stride, D, dig_rows, LeafGather()};
         if (have_b) trees[ntrees++] = VecDigestJob{wit->B.limbs, wit->B.stride, N, dig_rows_b, LeafGather()};
-        if (ntrees) ZK_TRY(vec_digest_launch(trees, ntrees, dig_leaves, mb, 0, dig_ticket, stream));
         MleJob jobs[kMleMaxJobs];
         int njobs = 0;
         auto add_job = [&](const uint32_t* a, size_t stride, int nv, const F* pt) {
@@ -2172,15 +2190,22 @@ static int verify_core(const VerifyCall& c) {
             tables.job[0].m = const_cast<uint32_t*>(wit->m);  // only read
             tables.job[0].M = Mfr;
             hipLaunchKernelGGL(k_counts_to_fr<1>, dim3(grid_for(N)), dim3(kBlock), 0, stream, tables);
-            LeafDigestArgs<1> lf{};
-            lf.job[0] = LeafDigestJob{(uint32_t*)(mb->bulk + kBulkDigests), wit->m, (uint32_t)N, nleaves, nullptr, nullptr};
-            hipLaunchKernelGGL(k_leaf_digests<1>, dim3((unsigned)div_up(nleaves, 64)), dim3(128), 0, stream, lf);
             job_m = add_job(Mfr, N, l, vt);
         }
         {
             Carver scratch = cv;
             const uint32_t seq = mb->next_seq();
-            ZK_TRY(mle_eval_launch(jobs, njobs, scratch, mb, seq, stream));
+            MlePlan plan;
+            ZK_TRY(mle_eval_begin(plan, jobs, njobs, scratch, mb, seq, stream));
+            LeafDigestArgs<1> lf{};
+            if (have_m) lf.job[0] = LeafDigestJob{(uint32_t*)(mb->bulk + kBulkDigests), wit->m, (uint32_t)N, nleaves, nullptr, nullptr};
+            LeavesBeside beside{lf.job[0], &plan.step[0], plan.blocks[0], false};
+            if (ntrees)
+                ZK_TRY(vec_digest_launch(trees, ntrees, dig_leaves, mb, 0, dig_ticket, stream, nullptr, BadWords{},
+                                         plan.steps > 1 ? &beside : nullptr));
+            if (have_m && !beside.launched)
+                hipLaunchKernelGGL(k_leaf_digests<1>, dim3((unsigned)div_up(nleaves, 64)), dim3(128), 0, stream, lf);
+            ZK_TRY(mle_eval_rest(plan, beside.launched ? 1 : 0, mb, stream));
             ZK_TRY(mailbox_wait(mb, seq, stream));
             ZK_HIP_TRY(hipStreamSynchronize(stream));
         }

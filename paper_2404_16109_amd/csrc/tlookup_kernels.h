@@ -6,6 +6,7 @@
 #include "common.h"
 #include "reduce_dev.h"
 #include "fr29_dev.h"
+#include "mle_dev.h"
 #include "sha256_dev.h"
 #include "small_dev.h"
 
@@ -611,24 +612,20 @@ struct LeafDigestArgs {
     uint32_t* ticket;
     uint32_t seq;
 };
-template <int NT>
-static __global__ void __launch_bounds__(128) k_leaf_digests(LeafDigestArgs<NT> args) {
-    __shared__ uint4 kw[2][16][64];
-    const LeafDigestJob& g = args.job[NT == 1 ? 0 : blockIdx.y];
+// By two wavefronts, `rounds` the first: the 64 leaves from `first` on, of nblk blocks (0: none).
+__device__ __forceinline__ void count_leaves(const LeafDigestJob& g, uint32_t first, uint32_t nblk, bool rounds, uint4 (*kw)[16][64]) {
     const int lane = threadIdx.x & 63;
-    const uint32_t leaf = blockIdx.x * 64 + lane;
-    const bool any = blockIdx.x * 64 < g.nleaves;
+    const uint32_t leaf = first + lane;
     const uint32_t base = (leaf < g.nleaves ? leaf : g.nleaves - 1) * kLeafCounts;
     const uint32_t cnt = g.N < kLeafCounts ? g.N : kLeafCounts;  // N is a power of two: all leaves are alike
-    const uint32_t nblk = any ? (cnt + 3 + 15) / 16 : 0;
-    if (threadIdx.x < 64) {
+    if (rounds) {
         uint32_t h[8];
         sha256_piped_rounds(h, kw, nblk, nblk);
         if (leaf < g.nleaves) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) g.out[leaf * 8 + i] = __builtin_bswap32(h[i]);
         }
-        if (blockIdx.x == 0 && lane < 4 && g.flags) g.out_flags[lane] = g.flags[lane];
+        if (first == 0 && lane < 4 && g.flags) g.out_flags[lane] = g.flags[lane];
         mailbox_written();
     } else {
         for (uint32_t b = 0; b <= nblk; ++b) {
@@ -654,6 +651,15 @@ static __global__ void __launch_bounds__(128) k_leaf_digests(LeafDigestArgs<NT> 
             __syncthreads();
         }
     }
+}
+__device__ __forceinline__ uint32_t count_leaf_blocks(const LeafDigestJob& g) {
+    return ((g.N < kLeafCounts ? g.N : kLeafCounts) + 3 + 15) / 16;
+}
+template <int NT>
+static __global__ void __launch_bounds__(128) k_leaf_digests(LeafDigestArgs<NT> args) {
+    __shared__ uint4 kw[2][16][64];
+    const LeafDigestJob& g = args.job[NT == 1 ? 0 : blockIdx.y];
+    count_leaves(g, blockIdx.x * 64, blockIdx.x * 64 < g.nleaves ? count_leaf_blocks(g) : 0, threadIdx.x < 64, kw);
     if (args.seq) {
         __syncthreads();
         if (threadIdx.x == 0 && atomicAdd(args.ticket, 1u) == gridDim.x * gridDim.y - 1) {
@@ -956,14 +962,14 @@ __device__ __forceinline__ void leaf_schedules(const VecLeavesJob& job, bool liv
     }
 }
 
+typedef uint4 PipedSchedules[2][2][16][64];  // [pair][buffer][four rounds][lane]
 template <int MODE>
-static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs args) {
-    __shared__ uint4 kw[2][2][16][64];  // [pair][buffer][four rounds][lane]
+__device__ __forceinline__ void piped_leaves(const VecLeavesArgs& args, uint32_t block, PipedSchedules& kw) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pair = wave >> 1;
     const bool rounds = (wave & 1) == 0;
     // both pairs take the same number of barriers: as many as the longer leaf of the two needs
-    const uint32_t group = 2 * blockIdx.x + pair, other = 2 * blockIdx.x + (pair ^ 1);
+    const uint32_t group = 2 * block + pair, other = 2 * block + (pair ^ 1);
     const bool live = group < args.groups;
     const VecLeavesJob& job = leaves_job(args, live ? group : args.groups - 1);
     const VecLeavesJob& job2 = leaves_job(args, other < args.groups ? other : args.groups - 1);
@@ -984,7 +990,45 @@ static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs a
         else if (MODE != kLeafPlain && MODE != kLeafRowsHash && job.from.rows) leaf_schedules<MODE>(job, live, leaf, blocks, steps, kw[pair]);
         else leaf_schedules<kLeafPlain>(job, live, leaf, blocks, steps, kw[pair]);
     }
+}
+template <int MODE>
+static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs args) {
+    __shared__ PipedSchedules kw;
+    piped_leaves<MODE>(args, blockIdx.x, kw);
     leaves_done(args);
+}
+
+// A verification's leaves in pairs, and in the same launch what does not depend on them: the leaves of m
+// and the first stage of the evaluations, which reads all that the tensors hold.  A leaf's chain keeps one
+// wavefront per SIMD and takes its 230 us whatever runs in the other places: half of a compute unit's
+// LDS is a workgroup's here, so that one of the evaluation's has room beside one of the hash's, and
+// reads in the chain's time what took 60 us after it.  A verification of 2^22 entries in 2^16 rows against
+// all tensors: 502 -> 421 us.  Longer tensors' leaves, one per lane, have no chain to hide behind.
+struct LeavesBesideArgs {
+    VecLeavesArgs leaves;
+    LeafDigestJob counts;  // m's; nleaves 0: none
+    uint32_t count_blocks;
+    MleStageArgs stage;    // publishes nothing
+};
+static __global__ void __launch_bounds__(kBlock) k_leaves_beside(LeavesBesideArgs args) {
+    __shared__ union {
+        PipedSchedules kw;
+        MleParts part;
+    } sh;
+    static_assert(sizeof(PipedSchedules) == sizeof(MleParts) && kBlock == 256, "");
+    const uint32_t leaf_blocks = (args.leaves.groups + 1) / 2;
+    uint32_t block = blockIdx.x;
+    if (block < leaf_blocks) {
+        piped_leaves<kLeafPlain>(args.leaves, block, sh.kw);
+        return;
+    }
+    block -= leaf_blocks;
+    if (block < args.count_blocks) {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pair = wave >> 1;
+        count_leaves(args.counts, 128 * block + 64 * pair, count_leaf_blocks(args.counts), (wave & 1) == 0, sh.kw[pair]);
+        return;
+    }
+    mle_stage_block(args.stage, block - args.count_blocks, sh.part);
 }
 
 // A by row, S (or integers) compared with T's rows: a thread per element, blockIdx.y the instance.
