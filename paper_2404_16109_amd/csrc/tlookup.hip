@@ -244,7 +244,7 @@ struct LeavesBeside {
     LeafDigestJob counts;
     const MleStageArgs* stage;
     uint32_t stage_blocks;
-    bool launched;  // it has: leaves in pairs
+    bool launched;  // it has: the leaves are not the host's
 };
 
 // The jobs that have rows (LeafGather) all compare them with S, or all with the
@@ -317,7 +317,7 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
     if (mode == kLeafRowsCheck || mode == kLeafRowsInts) return ZK_E_BADARG;  // cannot happen: k_make_a or the rounds compare
     if (mode == kLeafRows) launch_leaves<kLeafRows>(lv, stream);
     else if (mode == kLeafRowsHash) launch_leaves<kLeafRowsHash>(lv, stream);
-    else if (beside && leaves_in_pairs<kLeafPlain>(lv.groups)) {
+    else if (beside) {
         LeavesBesideArgs args;
         memset(&args, 0, sizeof args);
         args.leaves = lv;

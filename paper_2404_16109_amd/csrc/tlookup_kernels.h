@@ -923,8 +923,8 @@ static __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
 // at 2056 groups 484 and 521), but for the places just above a wavefront per SIMD (1025 groups:
 // 364 and 323); where every element is converted first, whose long chain one wavefront per SIMD
 // waits out, the pairs are still ahead at 1032 (520 groups without rows: 408 us, in pairs 235).
-// Beyond 1040 groups, whole verifications by lane and in pairs: 2^24 entries 1.05 and 1.02 ms,
-// 2^25 1.70 and 1.70.
+// Beyond 1040 groups, whole verifications by lane and in pairs, when nothing shared their launch: 2^24 entries 1.05
+// and 1.02 ms, 2^25 1.70 and 1.70.
 static const uint32_t kPipedLeafGroups = 512, kPipedLeafGroupsConverting = 1040;
 template <int MODE>
 static bool leaves_in_pairs(uint32_t groups) {
@@ -1003,7 +1003,9 @@ static __global__ void __launch_bounds__(256) k_vec_leaves_piped(VecLeavesArgs a
 // wavefront per SIMD and takes its 230 us whatever runs in the other places: half of a compute unit's
 // LDS is a workgroup's here, so that one of the evaluation's has room beside one of the hash's, and
 // reads in the chain's time what took 60 us after it.  A verification of 2^22 entries in 2^16 rows against
-// all tensors: 502 -> 421 us.  Longer tensors' leaves, one per lane, have no chain to hide behind.
+// all tensors: 502 -> 421 us.  Also where a lane per leaf is as fast for the hash by itself: 2^24 entries 1031 -> 798
+// us, 2^25 1682 -> 1480, 2^26 2997 -> 2761.  The leaves come first: with the others spread among them
+// where not all are resident at once 2^24 entries take 1966 us.
 struct LeavesBesideArgs {
     VecLeavesArgs leaves;
     LeafDigestJob counts;  // m's; nleaves 0: none

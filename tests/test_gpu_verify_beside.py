@@ -1,7 +1,7 @@
 """Verifications against all witness tensors, in which the evaluations' first stage and the leaves of m share a launch with the
 leaves of A and B (csrc/tlookup_kernels.h, k_leaves_beside): one and several stages on either side, a table as long as the
-tensor, leaves of m that do not fill a wavefront, vectors that no wide load can read, and lengths whose leaves go one per lane
-(2^24), where they do not.  Every tensor altered by itself is rejected."""
+tensor, leaves of m that do not fill a wavefront, vectors that no wide load can read, and more leaves than are
+resident at once (2^24).  Every tensor altered by itself is rejected."""
 import pytest
 import torch
 
