@@ -74,6 +74,24 @@ def round29_work(D, N):
     return pairs, muls, moved
 
 
+def rounds_by_row(D, N):
+    """The long rounds read the table's rows, and from the third on a pass over two variables (k_round_pair) serves two
+    rounds: tables of up to 2^16 rows, at least three variables beyond those of the last passes."""
+    n = D.bit_length() - 1
+    return first_two_rounds_share_a_pass(D, N) and n - 2 > PASS_VARS and N <= 1 << PASS_VARS
+
+
+def pair_bytes(D, N):
+    """Bytes that all launches of k_round_pair in one prove cannot avoid: row numbers read, A and S bound by two variables
+    written by the first (the table's rows are in the caches); both read at their length and written at a quarter of it
+    by the others."""
+    n, h = D.bit_length() - 1, (D // N).bit_length() - 1
+    moved, left = 4 * D + 64 * D // 4, D // 4
+    for _ in range(4, min(h, n - PASS_VARS), 2):
+        moved, left = moved + 64 * (left + left // 4), left // 4
+    return moved
+
+
 def measured_traffic():
     """HBM bytes per launch of the dominant kernel from the committed rocprofv3
     counter summary, if there is one (lines `FETCH_BYTES_PER_LAUNCH=` /
@@ -510,11 +528,14 @@ def main():
         rc, recs, total_ms = zk.zkmi_profile_query(name)
         phases[name] = {"records": recs, "ms_per_step": total_ms / psteps}
 
-    # the dominant kernel: k_round_data29, one launch per large folding round
+    # the dominant kernel of the large folding rounds: k_round_pair, two rounds a launch, or (longer tables) k_round_data29
     rd = phases["round_data29"]
     launches = rd["records"] / psteps
     avg_launch_s = rd["ms_per_step"] * 1e-3 / max(launches, 1)
     pairs29, muls29, moved29 = round29_work(D, N)
+    by_row = rounds_by_row(D, N)
+    if by_row:
+        moved29 = pair_bytes(D, N)
     mads_per_launch = muls29 * MADS_PER_FR_MUL / max(launches, 1)
     bytes_per_launch = moved29 / max(launches, 1)
     alu = mads_per_launch / avg_launch_s if avg_launch_s > 0 else 0.0
@@ -540,11 +561,13 @@ def main():
     if whole["hbm_bytes_measured"]:
         whole["hbm_frac_measured"] = whole["hbm_bytes_measured"] / (ms * 1e-3) / PEAK_HBM_BYTES_PER_S
     # every phase of the prove against the HBM roof, by the bytes it cannot avoid (per element of S: the hints read
-    # once while counting and once more with S while A is made, hashed and written; A and S read by the pass that serves
-    # the first two rounds; the folding rounds by round29_work; the inversion is the table's)
-    phase_bytes = {"count": 4 * D, "inverse": 64 * N, "digest": 68 * D, "round_data": 64 * D, "round_data29": moved29}
+    # once while counting, once by the hash and once with S by the pass that serves the first two rounds and compares them,
+    # or, of longer tables, once with S while A is made, hashed and written, and A and S by that pass; the inversion is
+    # the table's)
+    phase_bytes = {"count": 4 * D, "inverse": 64 * N, "digest": (4 if by_row else 68) * D,
+                   "round_data": (36 if by_row else 64) * D, "round_data29": moved29}
     phase_bound = {"count": "LDS atomics", "inverse": "latency", "digest": "alu (SHA-256 instruction issue)",
-                   "round_data": "alu (two wavefronts per SIMD)", "round_data29": "hbm and alu, balanced"}
+                   "round_data": "alu (two wavefronts per SIMD)" + (" and row loads" if by_row else ""), "round_data29": "issue and hbm" if by_row else "hbm and alu, balanced"}
     whole["phases"] = {
         k: {"ms": round(phases[k]["ms_per_step"], 4), "algorithmic_bytes": b, "bound": phase_bound[k],
             "hbm_frac": (b / (phases[k]["ms_per_step"] * 1e-3) / PEAK_HBM_BYTES_PER_S) if phases[k]["ms_per_step"] > 0 else None}
@@ -564,8 +587,9 @@ def main():
                    "fr_mul_executed_model": fr_mul_executed_model(D, N)},
         "phases_ms": {k: round(v["ms_per_step"], 4) for k, v in phases.items()},
         "commitment_standin_ms": round(phases["digest"]["ms_per_step"], 4),
-        "roofline": {"bound": "hbm" if hbm / PEAK_HBM_BYTES_PER_S >= alu / PEAK_MAD_PER_S else "alu",
-                     "kernel": "k_round_data29 (the large folding rounds, %d launches per prove)" % len(rounds_on_29_bits(D, N)),
+        # k_round_pair's folds and sums are on the matrix cores: its multiplications are no load of the vector ALU
+        "roofline": {"bound": "hbm" if by_row or hbm / PEAK_HBM_BYTES_PER_S >= alu / PEAK_MAD_PER_S else "alu",
+                     "kernel": "%s (the large folding rounds, %d launches per prove)" % ("k_round_pair" if by_row else "k_round_data29", launches),
                      "achieved": hbm / 1e9, "peak": PEAK_HBM_BYTES_PER_S / 1e9, "unit": "GB/s",
                      "frac": hbm / PEAK_HBM_BYTES_PER_S, "traffic": traffic,
                      "launches_per_step": launches, "avg_launch_ms": avg_launch_s * 1e3,
