@@ -542,10 +542,10 @@ def main():
     hbm = bytes_per_launch / avg_launch_s if avg_launch_s > 0 else 0.0
     traffic = measured_traffic()
     # the whole prove against both roofs: 112 multiply-adds per multiplication that is made, and the bytes that must
-    # move even with perfect fusion (hints; S read and A written; every round's arrays read once and written at half
-    # size: the fixed model's 292 per element of S less the prefix products of an inversion that is not made)
+    # move: by row those of the phases below, otherwise the fixed model's 292 per element of S less the prefix products
+    # of an inversion that is not made (hints; S read and A written; every round's arrays read once and written at half size)
     whole_mads = fr_mul_executed_model(D, N) * MADS_PER_FR_MUL
-    whole_bytes = (WHOLE_PROVE_BYTES_PER_ELEMENT - 32) * D
+    whole_bytes = 4 * D + 64 * N + 40 * D + moved29 if by_row else (WHOLE_PROVE_BYTES_PER_ELEMENT - 32) * D
     kernels_ms = sum(phases[k]["ms_per_step"] for k in names if k != "total")
     total_ms = phases["total"]["ms_per_step"]
     whole = {
