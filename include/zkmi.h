@@ -603,7 +603,7 @@ int zkmi_selftest_host_rounds(const fr_t* A, const fr_t* S, const fr_t* B, const
  * the transcript is built on, exported so that it can be checked on its own.
  * use_sha_instructions: 0 = the portable compression function, 1 = the x86 SHA
  * extensions if the processor has them (what the library uses by default),
- * else the portable one.  Returns 1 if the instruction path was used, 0 if not,
+ * else the portable one; of this call alone, whatever runs beside it.  Returns 1 if the instruction path was used, 0 if not,
  * ZK_E_BADARG on null pointers. */
 int zkmi_sha256(const uint8_t* data, size_t len, uint8_t out[32], int use_sha_instructions);
 

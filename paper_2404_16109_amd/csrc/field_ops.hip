@@ -227,15 +227,11 @@ int zkmi_version(void) { return 100; }
 
 int zkmi_sha256(const uint8_t* data, size_t len, uint8_t out[32], int use_sha_instructions) {
     if ((!data && len) || !out) return ZK_E_BADARG;
-    bool& flag = host::Sha256::use_sha_instructions();
-    const bool available = flag;
-    flag = available && use_sha_instructions != 0;
-    const int used = flag ? 1 : 0;
-    host::Sha256 h;
+    const bool by_instructions = use_sha_instructions != 0 && host::Sha256::has_instructions();
+    host::Sha256 h(by_instructions);
     h.update(data, len);
     h.finish(out);
-    flag = available;
-    return used;
+    return by_instructions ? 1 : 0;
 }
 
 static_assert(kMailboxMaxInstances == TLOOKUP_BATCH_MAX, "a call's tables");

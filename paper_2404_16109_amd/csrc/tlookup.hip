@@ -291,7 +291,7 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
     }
     size_t all_leaves = 0;
     for (int q = 0; q < njobs; ++q) all_leaves += cnt[q];
-    if (all_leaves <= kHostLeaves && host::Sha256::use_sha_instructions()) {
+    if (all_leaves <= kHostLeaves && host::Sha256::has_instructions()) {
         if (mode == kLeafRowsHash) return ZK_E_BADARG;  // cannot happen: those have thousands of leaves
         static_assert(kHostLeaves * kVecLeaf * 32 <= kBulkDigests, "the leaves take the place of the digests");
         uint32_t elements = 0;
@@ -504,25 +504,25 @@ static TableJob table_job(const ProveWs& w, const fr_vec& T, size_t N) {
 }
 
 // Whether the host hashes the leaves of m of these tables: they are few, the counts come from workgroups' histograms.
+// Decided once: what counting stages, how it is read and whether it is cleared go by the same value.
 static bool host_counts(const CountJob* jobs, int njobs) {
     uint32_t leaves = 0;
     for (int q = 0; q < njobs; ++q) {
         if (!jobs[q].w->hist) return false;
         leaves += jobs[q].w->nleaves;
     }
-    return leaves <= kHostCountLeaves && host::Sha256::use_sha_instructions();
+    return leaves <= kHostCountLeaves && host::Sha256::has_instructions();
 }
 
 // Enqueues the multiplicities of up to kMaxTables tensors into their w.m; `seq` (not zero)
-// is published once all that they stage is there.
+// is published once all that they stage is there.  to_host: host_counts' answer, for all of the call's tables.
 template <int NT>
-static int count_rows_of(const CountJob* jobs, int njobs, uint32_t seq, Mailbox* mb, hipStream_t stream, bool counts_as_fr) {
+static int count_rows_of(const CountJob* jobs, int njobs, bool to_host, uint32_t seq, Mailbox* mb, hipStream_t stream, bool counts_as_fr) {
     CountsOutArgs<NT> out{};
     TableJobs<NT>& tables = out.tables;
     LeafDigestArgs<NT> lf{};
     size_t most = 0;
     uint32_t most_leaves = 0, most_parts = 0;
-    const bool to_host = host_counts(jobs, njobs);
     for (int q = 0; q < njobs; ++q) {
         const CountJob& j = jobs[q];
         if (j.defer_check && !can_defer_check(*j.w, j.idx, j.D)) return ZK_E_BADARG;
@@ -604,9 +604,10 @@ static int count_rows_of(const CountJob* jobs, int njobs, uint32_t seq, Mailbox*
     ZK_HIP_TRY(hipGetLastError());
     return ZK_OK;
 }
-static int count_rows(const CountJob* jobs, int njobs, uint32_t seq, Mailbox* mb, hipStream_t stream, bool counts_as_fr = false) {
-    return njobs == 1 ? count_rows_of<1>(jobs, 1, seq, mb, stream, counts_as_fr)
-                      : count_rows_of<kMaxTables>(jobs, njobs, seq, mb, stream, counts_as_fr);
+static int count_rows(const CountJob* jobs, int njobs, bool to_host, uint32_t seq, Mailbox* mb, hipStream_t stream,
+                      bool counts_as_fr = false) {
+    return njobs == 1 ? count_rows_of<1>(jobs, 1, to_host, seq, mb, stream, counts_as_fr)
+                      : count_rows_of<kMaxTables>(jobs, njobs, to_host, seq, mb, stream, counts_as_fr);
 }
 
 static void digest_of_leaves(uint8_t out[32], const uint8_t* leaves, uint32_t nleaves) {
@@ -616,8 +617,8 @@ static void digest_of_leaves(uint8_t out[32], const uint8_t* leaves, uint32_t nl
 }
 
 // Counts are the caller's witness: they do not stay in memory that outlives the call.
-static void forget_counts(const CountJob* jobs, int njobs) {
-    if (!host_counts(jobs, njobs)) return;
+static void forget_counts(const CountJob* jobs, int njobs, bool to_host) {
+    if (!to_host) return;
     for (int q = 0; q < njobs; ++q) memset(jobs[q].staged + 16, 0, jobs[q].N * 4);
 }
 
@@ -1085,7 +1086,8 @@ static int prove_core(const ProveCall& c) {
             I.unchecked = I.by_row && I.deferred;
             counts[i] = CountJob{&I.w, I.S, I.idx, I.T, I.D, I.N, staged + at[i], I.deferred, I.idx ? nullptr : I.w.found};
         }
-        ZK_TRY(count_rows(counts, (int)K, seq, mb, stream, true));
+        const bool to_host = host_counts(counts, (int)K);
+        ZK_TRY(count_rows(counts, (int)K, to_host, seq, mb, stream, true));
         ZK_TRY(mailbox_wait(mb, seq, stream));
         for (size_t i = 0; i < K; ++i) {
             const uint64_t bad = counted_bad(staged + at[i]);
@@ -1095,13 +1097,13 @@ static int prove_core(const ProveCall& c) {
                     c.baux->bad_instance = i;
                     c.baux->bad_index = bad;
                 }
-                forget_counts(counts, (int)K);
+                forget_counts(counts, (int)K, to_host);
                 ZK_HIP_TRY(hipStreamSynchronize(stream));
                 return ZK_E_NOT_IN_TABLE;
             }
-            digest_of_counts(inst[i].md, counts[i], host_counts(counts, (int)K));
+            digest_of_counts(inst[i].md, counts[i], to_host);
         }
-        forget_counts(counts, (int)K);
+        forget_counts(counts, (int)K, to_host);
     }
 
     uint64_t dims[1 + 2 * kMailboxMaxInstances];
@@ -1211,9 +1213,8 @@ static int prove_core(const ProveCall& c) {
             uint8_t* const staged = mb->bulk + kBulkDigests;  // there was room for all instances' digests of m
             const CountJob job{&I.w, I.S, I.idx, I.T, I.D, I.N, staged, false, nullptr};
             const uint32_t seq = mb->next_seq();
-            ZK_TRY(count_rows(&job, 1, seq, mb, stream));
+            ZK_TRY(count_rows(&job, 1, false, seq, mb, stream));  // (its digests: their room is there whatever the call staged)
             ZK_TRY(mailbox_wait(mb, seq, stream));
-            forget_counts(&job, 1);
             if (counted_bad(staged) == UINT64_MAX) continue;
             at = i;
             bad = counted_bad(staged);
@@ -2280,9 +2281,10 @@ int tlookup_multiplicities(uint32_t* m, fr_vec S, const uint32_t* idx, fr_vec T,
     const uint8_t* const staged = mb->bulk + kBulkDigests;
     const uint32_t seq = mb->next_seq();
     const CountJob job{&w, S, idx, T, D, N, mb->bulk + kBulkDigests, false, nullptr};
-    ZK_TRY(count_rows(&job, 1, seq, mb, as_stream(stream)));
+    const bool to_host = host_counts(&job, 1);
+    ZK_TRY(count_rows(&job, 1, to_host, seq, mb, as_stream(stream)));
     ZK_TRY(mailbox_wait(mb, seq, as_stream(stream)));
-    forget_counts(&job, 1);
+    forget_counts(&job, 1, to_host);
     const uint64_t bad = counted_bad(staged);
     if (bad != UINT64_MAX) {
         if (bad_index) *bad_index = bad;

@@ -21,7 +21,8 @@ namespace host {
 
 class Sha256 {
 public:
-    Sha256() { reset(); }
+    // by_instructions: with the x86 SHA extensions (only where the processor has them).
+    explicit Sha256(bool by_instructions = has_instructions()) : by_instructions_(by_instructions) { reset(); }
 
     void reset() {
         static const uint32_t init[8] = {0x6a09e667u, 0xbb67ae85u, 0x3c6ef372u, 0xa54ff53au,
@@ -73,7 +74,7 @@ public:
     static void hash_each(uint8_t* out, const uint8_t* in, size_t bytes, size_t count) {
         size_t i = 0;
 #if defined(__x86_64__)
-        if (use_sha_instructions() && bytes % 64 == 0) {
+        if (has_instructions() && bytes % 64 == 0) {
             uint8_t pad[64] = {0x80};
             for (int k = 0; k < 8; ++k) pad[56 + k] = (uint8_t)((uint64_t)bytes * 8 >> (56 - 8 * k));
             for (; i + 2 <= count; i += 2) {
@@ -99,14 +100,13 @@ public:
     // One row of a hash tree: out[i] = SHA-256 of in[4 i .. 4 i + 3], digests of 32 bytes.  out may be in.
     static void hash_fours(uint8_t* out, const uint8_t* in, uint32_t nodes) { hash_each(out, in, 128, nodes); }
 
-    // Tests can switch the instruction-set path off to compare the two.
-    static bool& use_sha_instructions() {
+    static bool has_instructions() {
 #if defined(__x86_64__)
-        static bool on = __builtin_cpu_supports("sha") && __builtin_cpu_supports("sse4.1") && __builtin_cpu_supports("ssse3");
+        static const bool has = __builtin_cpu_supports("sha") && __builtin_cpu_supports("sse4.1") && __builtin_cpu_supports("ssse3");
 #else
-        static bool on = false;
+        static const bool has = false;
 #endif
-        return on;
+        return has;
     }
 
 private:
@@ -191,7 +191,7 @@ private:
 
     void block(const uint8_t* b) {
 #if defined(__x86_64__)
-        if (use_sha_instructions()) {
+        if (by_instructions_) {
             block_shani(b);
             return;
         }
@@ -222,6 +222,7 @@ private:
     uint8_t buf_[64];
     size_t fill_;
     uint64_t total_;
+    bool by_instructions_;
 };
 
 inline void put_le64(uint8_t out[8], uint64_t x) {

@@ -100,6 +100,27 @@ def test_library_sha256_both_paths_match_hashlib():
     assert used_any == cpu_has_sha
 
 
+def test_a_hash_without_the_instructions_is_that_calls_alone():
+    """Calls of other threads that overlap one that asks for the portable compression function keep their own choice."""
+    import hashlib
+    import threading
+    import time
+    import paper_2404_16109_amd as zk
+    instructions = zk.zkmi_sha256(b"", use_sha_instructions=True)[0]
+    data = bytes(1 << 25)
+    got = []
+    slow = threading.Thread(target=lambda: got.append(zk.zkmi_sha256(data, use_sha_instructions=False)))
+    slow.start()
+    used = []
+    while slow.is_alive():
+        used.append(zk.zkmi_sha256(b"abc", use_sha_instructions=True))
+        time.sleep(0.002)
+    slow.join()
+    assert got == [(0, hashlib.sha256(data).digest())]
+    assert len(used) > 2 and set(used) == {(instructions, hashlib.sha256(b"abc").digest())}
+    assert zk.zkmi_sha256(b"abc", use_sha_instructions=True)[0] == instructions
+
+
 def test_host_verifier_accepts_oracle_link_proofs(orc):
     """The library's verifier of the zkAttn linking sumcheck, without tensors (no
     GPU involved), replays proofs written by the oracle and rejects corrupted ones."""
