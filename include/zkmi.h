@@ -582,6 +582,21 @@ int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int3
  * ZK_E_BADARG for shapes whose rounds do not. */
 int zkmi_selftest_tlookup_rows_plan(size_t D, size_t N, size_t K, int32_t* out, size_t cap_rounds);
 
+/* Who makes, compares and hashes the vectors of a tlookup proof of K instances of shapes
+ * (D[i], N[i]), with row numbers (hints[i] != 0) or without: the prover's own decisions, no
+ * GPU is touched.  how: 0 as tlookup_prove and _small (with hints), _batch and _multi,
+ * 1 as tlookup_prove_checked, 2 as tlookup_prove_by_rows (hints required).
+ * sha_instructions: whether the host has them.  out (host): 2 + 2 K integers.
+ *   [0] the host hashes the leaves of A and B, else the device.
+ *   [1] the host hashes the leaves of m, else the device.
+ *   [2 + 2 i] A is made by: 0 an inversion of its own, 1 what hashes it or, if the host
+ *       does, ships it there, 2 a kernel apart, 3 nobody (it is hashed from the table's
+ *       rows, and so are the long rounds).
+ *   [3 + 2 i] S is compared with the hinted rows there (3: by the first pass), else while
+ *       counting. */
+int zkmi_selftest_tlookup_hashes(const size_t* D, const size_t* N, const int32_t* hints, size_t K, int how, int sha_instructions,
+                                 int32_t* out);
+
 /* The rounds a single tlookup proof leaves to the host (kind 7 above), on
  * arrays and challenges of the caller's choosing; no GPU is touched.  All
  * pointers are host memory, all elements canonical.  A, S: n_data elements
@@ -606,6 +621,10 @@ int zkmi_selftest_host_rounds(const fr_t* A, const fr_t* S, const fr_t* B, const
  * else the portable one; of this call alone, whatever runs beside it.  Returns 1 if the instruction path was used, 0 if not,
  * ZK_E_BADARG on null pointers. */
 int zkmi_sha256(const uint8_t* data, size_t len, uint8_t out[32], int use_sha_instructions);
+
+/* For tests: from now on (on != 0) the calling thread's calls go the way they go on a
+ * processor without SHA instructions; 0 takes that back.  Results are the same. */
+int zkmi_selftest_without_sha_instructions(int on);
 
 /* Library version (major * 100 + minor). */
 int zkmi_version(void);

@@ -75,6 +75,8 @@ def _load():
         "zkmi_selftest_resident_wait": (i32, [vp, sz, vp]),
         "zkmi_selftest_tlookup_plan": (i32, [sz, sz, sz, i32, P(ctypes.c_int32), sz]),
         "zkmi_selftest_tlookup_rows_plan": (i32, [sz, sz, sz, P(ctypes.c_int32), sz]),
+        "zkmi_selftest_tlookup_hashes": (i32, [P(sz), P(sz), P(ctypes.c_int32), sz, i32, i32, P(ctypes.c_int32)]),
+        "zkmi_selftest_without_sha_instructions": (i32, [i32]),
         "zkmi_selftest_host_rounds": (i32, [P(fr_t)] * 5 + [sz, sz, P(fr_t), P(fr_t), P(fr_t), P(fr_t), P(fr_t)]),
         "zkmi_profile_enable": (i32, [i32]),
         "zkmi_profile_reset": (i32, []),
@@ -152,7 +154,8 @@ def _load():
 
 
 _lib = _load()
-EXPORTS = ["zkmi_version", "zkmi_thread_init", "zkmi_thread_release", "zkmi_selftest_staging", "zkmi_sha256", "zkmi_selftest_resident_wait", "zkmi_selftest_tlookup_plan", "zkmi_selftest_tlookup_rows_plan", "zkmi_selftest_host_rounds", "zkmi_profile_enable", "zkmi_profile_reset", "zkmi_profile_query", "fr_constants", "fr_from_i32", "fr_from_canonical", "fr_to_canonical", "fr_add", "fr_sub",
+EXPORTS = ["zkmi_version", "zkmi_thread_init", "zkmi_thread_release", "zkmi_selftest_staging", "zkmi_sha256", "zkmi_selftest_resident_wait", "zkmi_selftest_tlookup_plan", "zkmi_selftest_tlookup_rows_plan", "zkmi_selftest_tlookup_hashes",
+           "zkmi_selftest_without_sha_instructions", "zkmi_selftest_host_rounds", "zkmi_profile_enable", "zkmi_profile_reset", "zkmi_profile_query", "fr_constants", "fr_from_i32", "fr_from_canonical", "fr_to_canonical", "fr_add", "fr_sub",
            "fr_mul", "fr_add_scalar", "fr_mul_scalar", "fr_axpy", "fr_batch_inverse_workspace_bytes",
            "fr_batch_inverse", "fr_sum_workspace_bytes", "fr_sum", "fr_sum_noalloc", "fr_eq_table", "fr_mle_eval_workspace_bytes",
            "fr_mle_eval", "tlookup_workspace_bytes", "tlookup_multiplicities", "tlookup_proof_bytes", "tlookup_prove",
@@ -248,6 +251,20 @@ def zkmi_selftest_tlookup_rows_plan(D, N, K=1):
     out = (ctypes.c_int32 * (4 * 32))()
     rc = _lib.zkmi_selftest_tlookup_rows_plan(D, N, K, out, 32)
     return rc, [tuple(out[4 * k:4 * k + 4]) for k in range(max(rc, 0))]
+
+
+def zkmi_selftest_tlookup_hashes(shapes, hints=None, how=0, sha_instructions=True):
+    """(rc, leaves of A and B by the host, leaves of m by the host, [(who makes A, S compared there)]) of instances (D, N);
+    runs on the host only."""
+    K = len(shapes)
+    out = (ctypes.c_int32 * (2 + 2 * K))()
+    rc = _lib.zkmi_selftest_tlookup_hashes((ctypes.c_size_t * K)(*(s[0] for s in shapes)), (ctypes.c_size_t * K)(*(s[1] for s in shapes)),
+                                           (ctypes.c_int32 * K)(*(hints or [1] * K)), K, how, 1 if sha_instructions else 0, out)
+    return rc, bool(out[0]), bool(out[1]), [(out[2 + 2 * i], bool(out[3 + 2 * i])) for i in range(K)]
+
+
+def zkmi_selftest_without_sha_instructions(on):
+    return _lib.zkmi_selftest_without_sha_instructions(1 if on else 0)
 
 
 def zkmi_selftest_host_rounds(A, S, B, M, T, u_rest, beta, challenges):

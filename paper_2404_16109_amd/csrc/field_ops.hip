@@ -234,6 +234,11 @@ int zkmi_sha256(const uint8_t* data, size_t len, uint8_t out[32], int use_sha_in
     return by_instructions ? 1 : 0;
 }
 
+int zkmi_selftest_without_sha_instructions(int on) {
+    host::Sha256::without_instructions() = on != 0;
+    return ZK_OK;
+}
+
 static_assert(kMailboxMaxInstances == TLOOKUP_BATCH_MAX, "a call's tables");
 
 int zkmi_thread_init(size_t max_table_rows) {

@@ -211,9 +211,8 @@ static size_t vec_digest_row_digests(size_t n) {
 // Enqueues the hash trees over up to kDigestMaxJobs vectors (n elements each, powers
 // of two): their last rows (at most kTreeHostRow digests) go to pinned host memory,
 // and the last launch publishes `seq` if it is not zero (`ticket`: one zeroed word of
-// device memory, left zero).  The host then finishes each tree (vec_digest_finish); of up
-// to kHostLeaves leaves in all it gets the bytes and hashes them itself, if it has the
-// instructions for it.
+// device memory, left zero).  The host then finishes each tree (vec_digest_finish); to_host
+// (host_leaves): it gets the leaves' bytes and hashes them itself.
 // leaves: room for the sum of vec_digest_leaves(n); rows: vec_digest_row_digests(n)
 // digests each.
 struct VecDigestJob {
@@ -226,6 +225,9 @@ struct VecDigestJob {
     uint8_t* shipped = nullptr;          // or the leaves' bytes, leaf_bytes each
     size_t leaf_bytes = 0;
 };
+
+// Whether the host hashes a call's leaves: they are few, and it has the instructions for it.
+static bool host_leaves(size_t leaves, bool sha_instructions) { return leaves <= kHostLeaves && sha_instructions; }
 
 template <int MODE>
 static void launch_leaves(const VecLeavesArgs& lv, hipStream_t stream) {
@@ -249,7 +251,7 @@ struct LeavesBeside {
 
 // The jobs that have rows (LeafGather) all compare them with S, or all with the
 // integers, or none: by `ints` and whether they have an S; those that are only hashed do not.
-static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Mailbox* mb, uint32_t seq, uint32_t* ticket,
+static int vec_digest_launch(VecDigestJob* jobs, int njobs, bool to_host, uint32_t* leaves, Mailbox* mb, uint32_t seq, uint32_t* ticket,
                              hipStream_t stream, const SmallSource* ints = nullptr, const BadWords& bad = BadWords{},
                              LeavesBeside* beside = nullptr) {
     if (njobs < 1 || njobs > kDigestMaxJobs) return ZK_E_BADARG;
@@ -289,10 +291,8 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
         if (from.hash_only && mode == kLeafPlain) mode = kLeafRowsHash;
         else if (from.rows && !from.hash_only) mode = from.S ? kLeafRowsCheck : ints ? kLeafRowsInts : kLeafRows;
     }
-    size_t all_leaves = 0;
-    for (int q = 0; q < njobs; ++q) all_leaves += cnt[q];
-    if (all_leaves <= kHostLeaves && host::Sha256::has_instructions()) {
-        if (mode == kLeafRowsHash) return ZK_E_BADARG;  // cannot happen: those have thousands of leaves
+    if (to_host) {
+        if (mode == kLeafRowsHash) return ZK_E_BADARG;  // cannot happen: what the host hashes is made on its way there (hash_plan)
         static_assert(kHostLeaves * kVecLeaf * 32 <= kBulkDigests, "the leaves take the place of the digests");
         uint32_t elements = 0;
         for (int q = 0; q < njobs; ++q) {
@@ -314,7 +314,7 @@ static int vec_digest_launch(VecDigestJob* jobs, int njobs, uint32_t* leaves, Ma
         ZK_HIP_TRY(hipGetLastError());
         return ZK_OK;
     }
-    if (mode == kLeafRowsCheck || mode == kLeafRowsInts) return ZK_E_BADARG;  // cannot happen: k_make_a or the rounds compare
+    if (mode == kLeafRowsCheck || mode == kLeafRowsInts) return ZK_E_BADARG;  // cannot happen: k_make_a or the rounds compare (hash_plan)
     if (mode == kLeafRows) launch_leaves<kLeafRows>(lv, stream);
     else if (mode == kLeafRowsHash) launch_leaves<kLeafRowsHash>(lv, stream);
     else if (beside) {
@@ -485,7 +485,7 @@ static uint64_t counted_bad(const uint8_t* staged) {
 }
 
 // Whether the comparison of S with hinted rows can be left to the caller (workgroup histograms in use).
-static bool can_defer_check(const ProveWs& w, const uint32_t* idx, size_t D) { return w.hist && idx && D > (size_t)kBlock; }
+static bool can_defer_check(size_t D, size_t N, bool hints) { return N <= kLdsHistMaxRows && hints && D > (size_t)kBlock; }
 
 // One tensor's counting.
 struct CountJob {
@@ -503,15 +503,15 @@ static TableJob table_job(const ProveWs& w, const fr_vec& T, size_t N) {
     return TableJob{T.limbs, T.stride, (uint32_t)N, w.slots, w.cap_mask, w.flags, w.canon, w.rows, w.m, w.hist, w.hist_parts, w.M, w.B, nullptr, nullptr, nullptr};
 }
 
-// Whether the host hashes the leaves of m of these tables: they are few, the counts come from workgroups' histograms.
-// Decided once: what counting stages, how it is read and whether it is cleared go by the same value.
-static bool host_counts(const CountJob* jobs, int njobs) {
-    uint32_t leaves = 0;
-    for (int q = 0; q < njobs; ++q) {
-        if (!jobs[q].w->hist) return false;
-        leaves += jobs[q].w->nleaves;
+// Whether the host hashes a call's leaves of m: they are few, the counts come from workgroups' histograms.  Decided once:
+// what counting stages, how it is read and whether it is cleared go by the same value.
+static bool host_counts(const size_t* N, size_t K, bool sha_instructions) {
+    size_t leaves = 0;
+    for (size_t i = 0; i < K; ++i) {
+        if (N[i] > kLdsHistMaxRows) return false;
+        leaves += div_up(N[i], kLeafCounts);
     }
-    return leaves <= kHostCountLeaves && host::Sha256::has_instructions();
+    return leaves <= kHostCountLeaves && sha_instructions;
 }
 
 // Enqueues the multiplicities of up to kMaxTables tensors into their w.m; `seq` (not zero)
@@ -525,7 +525,7 @@ static int count_rows_of(const CountJob* jobs, int njobs, bool to_host, uint32_t
     uint32_t most_leaves = 0, most_parts = 0;
     for (int q = 0; q < njobs; ++q) {
         const CountJob& j = jobs[q];
-        if (j.defer_check && !can_defer_check(*j.w, j.idx, j.D)) return ZK_E_BADARG;
+        if (j.defer_check && !can_defer_check(j.D, j.N, j.idx != nullptr)) return ZK_E_BADARG;
         tables.job[q] = table_job(*j.w, j.T, j.N);
         out.out[q] = (uint32_t*)j.staged;
         lf.job[q] = LeafDigestJob{(uint32_t*)(j.staged + 16), j.w->m, (uint32_t)j.N, j.w->nleaves, j.w->flags, (uint32_t*)j.staged};
@@ -922,9 +922,10 @@ struct Instance {
     const uint32_t* grid_words = nullptr;  // where the running pass's values come out
     RoundState state;            // what its rounds so far have left behind
     HostTail* tail = nullptr;    // once the host has the arrays
-    bool gather = false;    // A is B by row, made while it is hashed
-    bool by_row = false;    // A and S are the table's rows until a challenge has bound them (tlookup_rows.h): A is only hashed
-    bool deferred = false;  // S_i = T[idx_i] is checked there too (by_row: in the first pass), not while counting
+    bool gather = false;    // A is B by row (all but kAInverted)
+    bool by_row = false;    // A and S are the table's rows until a challenge has bound them (tlookup_rows.h): kANever
+    bool apart = false;     // kAApart
+    bool deferred = false;  // S_i = T[idx_i] is checked where A is made (by_row: in the first pass), not while counting
     bool unchecked = false; // that first pass has not run yet
 
     const uint32_t* rows() const { return idx ? idx : w.found; }
@@ -935,6 +936,44 @@ struct Instance {
     uint4* rows_hash() const { return (uint4*)w.Sf; }
     DigitPlanes planes(uint4* base) const { return DigitPlanes{base, D / 4}; }
 };
+
+// Who makes, compares and hashes what of a call: decided once, from its shapes and options, and all launches go by it.
+// With hints S_i = T[idx_i] is compared where A is made from the rows; all instances or none, so that the first instance
+// at fault is the one reported.
+enum AMaker {
+    kAInverted = 0,     // the inversion of beta + S
+    kAWhileHashed = 1,  // the leaves' hash, or what ships the leaves to the host: writes A, in the latter case compares too
+    kAApart = 2,        // k_make_a, which compares; the hash only hashes
+    kANever = 3         // rounds by row: hashed from the rows, compared by the first pass
+};
+struct HashPlan {
+    bool leaves_to_host, counts_to_host;
+    struct {
+        AMaker maker;
+        bool deferred;  // compared where A is made (kANever: by the first pass), not while counting
+    } of[kMailboxMaxInstances];
+};
+static HashPlan hash_plan(const size_t* D, const size_t* N, const bool* hints, size_t K, bool check_upfront, bool by_rows,
+                          bool sha_instructions) {
+    HashPlan p;
+    size_t leaves = 0;
+    bool defer_all = !check_upfront;
+    for (size_t i = 0; i < K; ++i) {
+        leaves += vec_digest_leaves(D[i]) + vec_digest_leaves(N[i]);
+        defer_all = defer_all && can_defer_check(D[i], N[i], hints[i]);
+    }
+    p.leaves_to_host = host_leaves(leaves, sha_instructions);
+    p.counts_to_host = host_counts(N, K, sha_instructions);
+    for (size_t i = 0; i < K; ++i) {
+        const int n = log2_floor(D[i]), h = n - log2_floor(N[i]);
+        p.of[i].maker = !(by_rows || gather_by_default(N[i])) ? kAInverted
+                        : rounds_by_row(n, h)                 ? kANever
+                        : p.leaves_to_host || D[i] > kMadeApart ? kAWhileHashed
+                                                                : kAApart;
+        p.of[i].deferred = defer_all && p.of[i].maker != kAInverted;
+    }
+    return p;
+}
 
 struct ProveCall {
     const uint8_t* seed = nullptr;
@@ -1061,9 +1100,18 @@ static int prove_core(const ProveCall& c) {
     ProfileScope prof_total(kProfTotal, stream);
 
     // -- Prep: multiplicities and their digests -------------------------------------------------
-    bool defer_all = !c.check_upfront;
-    for (size_t i = 0; i < K; ++i) defer_all = defer_all && can_defer_check(inst[i].w, inst[i].idx, inst[i].D);
-    if (from_ints && !defer_all) return ZK_E_BADARG;  // counting would read S as a vector
+    bool hints[kMailboxMaxInstances];
+    for (size_t i = 0; i < K; ++i) hints[i] = inst[i].idx != nullptr;
+    const HashPlan who = hash_plan(Ds, Ns, hints, K, c.check_upfront, c.by_rows, Sha256::has_instructions());
+    for (size_t i = 0; i < K; ++i) {
+        Instance& I = inst[i];
+        I.gather = who.of[i].maker != kAInverted;
+        I.by_row = who.of[i].maker == kANever;
+        I.apart = who.of[i].maker == kAApart;
+        I.deferred = who.of[i].deferred;
+        I.unchecked = I.by_row && I.deferred;
+    }
+    if (from_ints && !inst[0].deferred) return ZK_E_BADARG;  // counting would read S as a vector
     {
         // all instances' counting, then one wait
         ProfileScope prof(kProfCount, stream);
@@ -1078,15 +1126,9 @@ static int prove_core(const ProveCall& c) {
         CountJob counts[kMailboxMaxInstances];
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
-            // with hints, S_i = T[idx_i] is checked while A is made and hashed; all instances or none, so that the first
-            // instance at fault is the one reported
-            I.gather = c.by_rows || gather_by_default(I.N);
-            I.deferred = defer_all && I.gather;
-            I.by_row = I.gather && rounds_by_row(I.n, I.h);
-            I.unchecked = I.by_row && I.deferred;
             counts[i] = CountJob{&I.w, I.S, I.idx, I.T, I.D, I.N, staged + at[i], I.deferred, I.idx ? nullptr : I.w.found};
         }
-        const bool to_host = host_counts(counts, (int)K);
+        const bool to_host = who.counts_to_host;
         ZK_TRY(count_rows(counts, (int)K, to_host, seq, mb, stream, true));
         ZK_TRY(mailbox_wait(mb, seq, stream));
         for (size_t i = 0; i < K; ++i) {
@@ -1236,8 +1278,6 @@ static int prove_core(const ProveCall& c) {
         ProfileScope prof(kProfDigest, stream);
         const uint32_t seq = mb->next_seq();
         VecDigestJob jobs[2 * kMailboxMaxInstances];
-        size_t all_leaves = 0;
-        for (size_t i = 0; i < K; ++i) all_leaves += vec_digest_leaves(inst[i].D) + vec_digest_leaves(inst[i].N);
         MakeAJobs<kMailboxMaxInstances> make{};
         size_t made = 0, longest = 0;
         if (from_ints) make.ints = ints_src;
@@ -1254,13 +1294,12 @@ static int prove_core(const ProveCall& c) {
                     from.S = I.S.limbs;  // null with integers
                     from.ss = I.S.stride;
                 }
-                const bool apart = !I.by_row && I.D <= kMadeApart && all_leaves > kHostLeaves;
-                if (apart) {
+                if (I.apart) {
                     const int check = !I.deferred ? kLeafRows : from_ints ? kLeafRowsInts : kLeafRowsCheck;
                     make.job[made++] = MakeAJob{I.w.A, I.D, I.D, from, check};
                     longest = std::max(longest, I.D);
                 }
-                if (apart || I.by_row) {
+                if (I.apart || I.by_row) {
                     from.S = nullptr;
                     from.B = I.by_row ? I.rows_hash() : I.w.rows_b + 2;
                     from.hash_only = I.by_row ? 2 : 4;
@@ -1277,7 +1316,7 @@ static int prove_core(const ProveCall& c) {
         bad.count = (int)K;
         bad.to = mb->words + kMailboxBad;
         for (size_t i = 0; i < K; ++i) bad.from[i] = (const unsigned long long*)(inst[i].w.flags + 2);
-        ZK_TRY(vec_digest_launch(jobs, 2 * (int)K, dig_leaves, mb, seq, inst[0].w.flags + 1, stream,
+        ZK_TRY(vec_digest_launch(jobs, 2 * (int)K, who.leaves_to_host, dig_leaves, mb, seq, inst[0].w.flags + 1, stream,
                                  from_ints ? &ints_src : nullptr, bad));
         // the table side's sums, in the time the host takes: read with the first round's (shares, the host's to add up,
         // unless there are long tables)
@@ -2201,9 +2240,10 @@ static int verify_core(const VerifyCall& c) {
             LeafDigestArgs<1> lf{};
             if (have_m) lf.job[0] = LeafDigestJob{(uint32_t*)(mb->bulk + kBulkDigests), wit->m, (uint32_t)N, nleaves, nullptr, nullptr};
             LeavesBeside beside{lf.job[0], &plan.step[0], plan.blocks[0], false};
+            const size_t leaves = (have_a ? vec_digest_leaves(D) : 0) + (have_b ? vec_digest_leaves(N) : 0);
             if (ntrees)
-                ZK_TRY(vec_digest_launch(trees, ntrees, dig_leaves, mb, 0, dig_ticket, stream, nullptr, BadWords{},
-                                         plan.steps > 1 ? &beside : nullptr));
+                ZK_TRY(vec_digest_launch(trees, ntrees, host_leaves(leaves, Sha256::has_instructions()), dig_leaves, mb, 0, dig_ticket,
+                                         stream, nullptr, BadWords{}, plan.steps > 1 ? &beside : nullptr));
             if (have_m && !beside.launched)
                 hipLaunchKernelGGL(k_leaf_digests<1>, dim3((unsigned)div_up(nleaves, 64)), dim3(128), 0, stream, lf);
             ZK_TRY(mle_eval_rest(plan, beside.launched ? 1 : 0, mb, stream));
@@ -2281,7 +2321,7 @@ int tlookup_multiplicities(uint32_t* m, fr_vec S, const uint32_t* idx, fr_vec T,
     const uint8_t* const staged = mb->bulk + kBulkDigests;
     const uint32_t seq = mb->next_seq();
     const CountJob job{&w, S, idx, T, D, N, mb->bulk + kBulkDigests, false, nullptr};
-    const bool to_host = host_counts(&job, 1);
+    const bool to_host = host_counts(&N, 1, host::Sha256::has_instructions());
     ZK_TRY(count_rows(&job, 1, to_host, seq, mb, as_stream(stream)));
     ZK_TRY(mailbox_wait(mb, seq, as_stream(stream)));
     forget_counts(&job, 1, to_host);
@@ -2415,6 +2455,25 @@ int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int3
 int zkmi_selftest_tlookup_rows_plan(size_t D, size_t N, size_t K, int32_t* out, size_t cap_rounds) {
     if (!selftest_shape_ok(D, N, K, out) || !gather_by_default(N) || !rounds_by_row(log2_floor(D), log2_floor(D) - log2_floor(N))) return ZK_E_BADARG;
     return selftest_plan(D, N, K, false, true, out, cap_rounds);
+}
+
+// Who makes, compares and hashes what (hash_plan), see zkmi.h.
+int zkmi_selftest_tlookup_hashes(const size_t* D, const size_t* N, const int32_t* hints, size_t K, int how, int sha_instructions,
+                                 int32_t* out) {
+    if (!D || !N || !hints || !out || K == 0 || K > kMailboxMaxInstances || how < 0 || how > 2) return ZK_E_BADARG;
+    bool given[kMailboxMaxInstances];
+    for (size_t i = 0; i < K; ++i) {
+        if (!selftest_shape_ok(D[i], N[i], K, out) || (how == 2 && !hints[i])) return ZK_E_BADARG;
+        given[i] = hints[i] != 0;
+    }
+    const HashPlan p = hash_plan(D, N, given, K, how == 1, how == 2, sha_instructions != 0);
+    out[0] = p.leaves_to_host;
+    out[1] = p.counts_to_host;
+    for (size_t i = 0; i < K; ++i) {
+        out[2 + 2 * i] = p.of[i].maker;
+        out[3 + 2 * i] = p.of[i].deferred;
+    }
+    return ZK_OK;
 }
 
 // The host's rounds (HostTail) on arrays and challenges of the caller's choosing: no GPU is touched.

@@ -100,13 +100,19 @@ public:
     // One row of a hash tree: out[i] = SHA-256 of in[4 i .. 4 i + 3], digests of 32 bytes.  out may be in.
     static void hash_fours(uint8_t* out, const uint8_t* in, uint32_t nodes) { hash_each(out, in, 128, nodes); }
 
+    // Whether this thread's hashes go by the instructions.
     static bool has_instructions() {
 #if defined(__x86_64__)
         static const bool has = __builtin_cpu_supports("sha") && __builtin_cpu_supports("sse4.1") && __builtin_cpu_supports("ssse3");
 #else
         static const bool has = false;
 #endif
-        return has;
+        return has && !without_instructions();
+    }
+    // Of the calling thread: tests set it, to see what its calls do on other processors.
+    static bool& without_instructions() {
+        static thread_local bool set = false;
+        return set;
     }
 
 private:
