@@ -151,6 +151,8 @@ static const size_t kMailboxBad = 1408;     // smallest index whose element is n
 // finishes hash trees from (sixteen vectors, 256 digests each); what other copies
 // need follows.
 static const size_t kBulkDigests = 16 * 256 * 32;
+// Most bytes of counts that a call's tables hand over in place of their leaves' digests (host_counts).
+static const size_t kBulkCounts = (size_t)4 << 13;
 
 int mailbox_get(Mailbox** out);
 int mailbox_bulk(Mailbox* mb, size_t bytes);  // room for `bytes` at bulk + kBulkDigests

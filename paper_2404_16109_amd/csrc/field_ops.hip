@@ -245,9 +245,9 @@ int zkmi_thread_init(size_t max_table_rows) {
     Mailbox* mb;
     ZK_TRY(mailbox_get(&mb));
     // counting hands over the leaf digests of all of a call's tables (one per 128 rows, 32 bytes each) and four status
-    // words for each, or, of few rows in all (2^13 for one table, kHostCountLeaves), the counts themselves
+    // words for each, or, of few rows in all, the counts themselves
     const size_t digests = kMailboxMaxInstances * (div_up(max_table_rows ? max_table_rows : 1, (size_t)128) * 32 + 16);
-    const size_t counts = kMailboxMaxInstances * 32 + ((size_t)4 << 13);
+    const size_t counts = kMailboxMaxInstances * 16 + kBulkCounts;
     return mailbox_bulk(mb, digests > counts ? digests : counts);
 }
 

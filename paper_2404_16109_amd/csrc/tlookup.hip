@@ -472,11 +472,13 @@ static size_t prove_ws_bytes(size_t D, size_t N, size_t K = 1) {
     return prove_ws_bytes_shapes(Ds, Ns, K);
 }
 
-// What counting hands to the host: the four flag words, then the digests of m's leaves or, if there are few (host_counts),
-// the counts.
-static size_t counted_bytes(const ProveWs& w, size_t N) {
-    return 16 + std::max((size_t)w.nleaves * 32, w.nleaves <= kHostCountLeaves ? (N * 4 + 15) / 16 * 16 : 0);
+// What counting hands to the host: the four flag words, then the digests of m's leaves or (host_counts) the counts, for
+// which there is then room beside that of digests.  A call's, of tables no longer than those zkmi_thread_init was told of,
+// fits what that has reserved.
+static size_t counted_bytes(const ProveWs& w, size_t N, bool to_host) {
+    return 16 + std::max((size_t)w.nleaves * 32, to_host ? align_up(N * 4, 16) : 0);
 }
+static_assert(kHostCountLeaves * kLeafCounts * 4 == kBulkCounts, "");
 // Smallest i with S_i not in T (all ones: none), once that has arrived.
 static uint64_t counted_bad(const uint8_t* staged) {
     uint64_t bad;
@@ -494,7 +496,7 @@ struct CountJob {
     const uint32_t* idx;
     fr_vec T;
     size_t D, N;
-    uint8_t* staged;   // pinned, counted_bytes: receives the digests of m's leaves and the flags
+    uint8_t* staged;   // pinned, counted_bytes: receives the flags and the digests of m's leaves or the counts
     bool defer_check;  // the hints are taken as they are; S_i = T[idx_i] is then checked by the caller
     uint32_t* found;   // without hints the rows are left here, if the caller wants them
 };
@@ -1118,7 +1120,7 @@ static int prove_core(const ProveCall& c) {
         size_t total = 0, at[kMailboxMaxInstances];
         for (size_t i = 0; i < K; ++i) {
             at[i] = total;
-            total += counted_bytes(inst[i].w, inst[i].N);
+            total += counted_bytes(inst[i].w, inst[i].N, who.counts_to_host);
         }
         ZK_TRY(mailbox_bulk(mb, total));
         uint8_t* const staged = mb->bulk + kBulkDigests;
@@ -2317,11 +2319,11 @@ int tlookup_multiplicities(uint32_t* m, fr_vec S, const uint32_t* idx, fr_vec T,
     Carver cv(ws, ws_bytes);
     ProveWs w;
     carve_prove(w, cv, D, N);
-    ZK_TRY(mailbox_bulk(mb, counted_bytes(w, N)));
+    const bool to_host = host_counts(&N, 1, host::Sha256::has_instructions());
+    ZK_TRY(mailbox_bulk(mb, counted_bytes(w, N, to_host)));
     const uint8_t* const staged = mb->bulk + kBulkDigests;
     const uint32_t seq = mb->next_seq();
     const CountJob job{&w, S, idx, T, D, N, mb->bulk + kBulkDigests, false, nullptr};
-    const bool to_host = host_counts(&N, 1, host::Sha256::has_instructions());
     ZK_TRY(count_rows(&job, 1, to_host, seq, mb, as_stream(stream)));
     ZK_TRY(mailbox_wait(mb, seq, as_stream(stream)));
     forget_counts(&job, 1, to_host);

@@ -129,3 +129,53 @@ def test_thread_init_is_enough_for_a_full_batch(zk, orc):
     torch.cuda.synchronize()
     assert len(got) == 5, got
     assert got[0][0] != 0 and got[1:] == [0, got[0], 0, (0, 0)], got
+
+
+# Tables whose counts the host hashes and whose leaves' digests are handed over, and batches of either that cross the 64 leaves
+# between the two (one of 2^13 rows, two of 2^12, four of 2^11)
+@pytest.mark.parametrize("logN,K", [(3, 8), (10, 8), (11, 4), (11, 8), (12, 1), (12, 2), (12, 4), (13, 1), (13, 2), (13, 8), (14, 1), (14, 8)])
+def test_thread_init_is_enough_for_short_tables(zk, logN, K):
+    """The same at the lengths where counts or digests are staged, for proofs that are made, proofs that are refused while
+    counting, and proofs whose earlier instances are looked through again once a later one is at fault."""
+    N, D = 1 << logN, 1 << max(logN, 9)
+    T = zk.Vec(N)
+    assert zk.fr_from_i32(T, torch.arange(N, dtype=torch.int32, device="cuda")) == 0
+
+    def tensor(n):
+        idx = torch.randint(0, N, (n,), dtype=torch.int32, device="cuda")
+        S = zk.Vec(n)
+        S.data.copy_(T.data[:, :N].index_select(1, idx.long()))
+        return S, idx
+
+    S, idx = tensor(D)
+    bad, _ = tensor(D)
+    bad.data.copy_(S.data[:, :D])
+    bad.data[0, 3] ^= 1
+    long_S, long_idx = tensor(1 << 19) if K > 1 else (None, None)
+    torch.cuda.synchronize()
+    got = []
+
+    def worker():
+        try:
+            assert zk.zkmi_thread_init(N) == 0
+            place = zk.zkmi_selftest_staging()
+            assert place[0] != 0
+            assert zk.tlookup_prove_batch(b"\3" * 32, [S] * K, [idx] * K, [T] * K)[0] == 0
+            got.append(zk.zkmi_selftest_staging() == place)
+            assert zk.tlookup_prove_batch(b"\3" * 32, [S] * (K - 1) + [bad], [None] * K, [T] * K)[0] == zk.ZK_E_NOT_IN_TABLE
+            got.append(zk.zkmi_selftest_staging() == place)
+            assert zk.tlookup_multiplicities(S, idx, T)[0] == 0
+            got.append(zk.zkmi_selftest_staging() == place)
+            if K > 1:
+                rc, _, info = zk.tlookup_prove_multi(b"\3" * 32, [long_S] * (K - 1) + [bad], [long_idx] * (K - 1) + [idx], [T] * K)
+                assert rc == zk.ZK_E_NOT_IN_TABLE and (info["bad_instance"], info["bad_index"]) == (K - 1, 3)
+                got.append(zk.zkmi_selftest_staging() == place)
+            assert zk.zkmi_thread_release() == 0
+        except Exception as e:
+            got.append(repr(e))
+
+    t = threading.Thread(target=worker)
+    t.start()
+    t.join()
+    torch.cuda.synchronize()
+    assert got == [True] * (4 if K > 1 else 3), got
