@@ -553,33 +553,31 @@ int zkmi_selftest_resident_wait(void* ws, size_t ws_bytes, void* stream);
  * is touched).  They do not depend on the other instances' shapes (k counts the
  * instance's own rounds).  from_ints != 0: the rounds of tlookup_prove_small (K = 1;
  * ZK_E_BADARG for shapes that path does not take).
+ * Tables of up to 2^16 rows, tensors of 2^19 entries or more and at least eight times the
+ * table's: the long rounds read the rows of the table instead of S and A, the same with or
+ * without row numbers or from integers.
  * out (host): four integers per round.
  *   [0] kind: 0 the first round's kernel, 1 the kernel of large folding rounds on
  *       29-bit limbs, 2 data and table side together, 5 the first pass when it serves
  *       the first two rounds, 6 the second of those two (nothing is launched), 8 the
  *       sums come from a pass over up to three variables, 7 the host's round (it has
- *       the arrays, at most 64 elements each).
+ *       the arrays, at most 64 elements each), 9 the first round of a long pass, which
+ *       serves this round and, if it says two variables, the next (of kind 8).
  *   [1] where S is read: 0 the caller's vector, 1 the caller's integer columns,
- *       2 folded 32-bit words in the workspace, 3 folded 29-bit limb planes in the
- *       workspace, 4 nowhere (a later round of a pass, or of the host's).
+ *       2 folded 32-bit words in the workspace, 3 folded planes in the workspace (of kind
+ *       1: 29-bit limbs, of kind 9: digits), 4 nowhere (a later round of a pass, or of the
+ *       host's), 5 the rows of the table.
  *   [2] kind 1: the data arrays arrive as 32-bit words.  The first round of a pass: the
  *       variables it serves, plus 8 times those of them that are the table's.
  *   [3] kind 1: they leave as 32-bit words.  The first round of a pass and the first of
  *       the host's: the last challenges that the data arrays are bound to before it, plus
- *       8 times those that the table's are.
+ *       8 times those that the table's are (kind 9, which binds none of the table's: plus
+ *       8 if it leaves words).
  * Returns the number of rounds, ZK_E_BUFSZ if cap_rounds is below it. */
 int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int32_t* out, size_t cap_rounds);
 
-/* The same where the long rounds read the rows of the table instead of S and A: tables
- * of up to 2^16 rows, tensors of 2^19 entries or more and at least eight times the
- * table's, as a vector with or without row numbers or as integers (the plan above is
- * that of all others).  Four integers per round as above, but
- *   [0] may be 9: the first round of a long pass, which serves this round and, if it
- *       says two variables, the next (of kind 8);
- *   [1] may be 5: the rows of the table; 3 are the passes' own planes;
- *   [2], [3] of kind 9: the variables it serves; the challenges it binds, plus 8 if it
- *       leaves words.
- * ZK_E_BADARG for shapes whose rounds do not. */
+/* The same of the shapes whose long rounds read the rows of the table; ZK_E_BADARG for
+ * others. */
 int zkmi_selftest_tlookup_rows_plan(size_t D, size_t N, size_t K, int32_t* out, size_t cap_rounds);
 
 /* Who makes, compares and hashes the vectors of a tlookup proof of K instances of shapes

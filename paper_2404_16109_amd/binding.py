@@ -247,7 +247,7 @@ def zkmi_selftest_tlookup_plan(D, N, K=1, from_ints=False):
 
 
 def zkmi_selftest_tlookup_rows_plan(D, N, K=1):
-    """The same where the long rounds read the table's rows."""
+    """The same of shapes whose long rounds read the table's rows (others: ZK_E_BADARG)."""
     out = (ctypes.c_int32 * (4 * 32))()
     rc = _lib.zkmi_selftest_tlookup_rows_plan(D, N, K, out, 32)
     return rc, [tuple(out[4 * k:4 * k + 4]) for k in range(max(rc, 0))]

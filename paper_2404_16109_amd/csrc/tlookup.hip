@@ -827,13 +827,13 @@ static void plan_bound(RoundPlan& pl, RoundState& st, int vars, int tvars) {
 }
 
 // Round k of an instance of n variables, the last n - h of them the table's, in a call of K instances; moves the state on.
-// by_row: the entries are rows of the table (rounds_by_row), whatever the caller's tensor is.
-static RoundPlan plan_round(int n, int h, int k, size_t K, bool from_ints, RoundState& st, bool by_row = false) {
+static RoundPlan plan_round(int n, int h, int k, size_t K, bool from_ints, RoundState& st) {
     RoundPlan pl{};
+    const bool by_row = rounds_by_row(n, h);  // the entries are rows of the table, whatever the caller's tensor is
     const int left = n - k;
     pl.table_round = k >= h;
     pl.s_source = kSUnread;
-    // integers are the first two rounds' business, and the second of two rounds that share a pass needs none
+    // integers are the first two rounds' business (but by row), and the second of two rounds that share a pass needs none
     const bool own = (from_ints && !by_row && k < 2) || st.first_two;
     if (st.on_host || (!own && left <= host_vars(K))) {
         pl.kind = kRoundHost;
@@ -1004,12 +1004,14 @@ struct ProveCall {
 };
 
 // Whether a lookup of this shape can read S as small integers all the way: the
-// multiplicities come from the hints alone (workgroup histograms), the first
-// round and the first fold are kernels of their own that read integers.
+// multiplicities come from the hints alone (workgroup histograms); by row the first pass
+// compares integers with the rows, otherwise the first round and the first fold are kernels
+// of their own that read integers.
 static bool small_source_shape_ok(size_t D, size_t N) {
     if (!is_pow2(D) || !is_pow2(N) || N > D || N > kLdsHistMaxRows || D <= (size_t)kBlock) return false;
     const int n = log2_floor(D), h = n - log2_floor(N);
     if (n < 2) return false;
+    if (rounds_by_row(n, h)) return true;
     RoundState st;
     const RoundPlan p0 = plan_round(n, h, 0, 1, true, st);
     const RoundPlan p1 = plan_round(n, h, 1, 1, true, st);
@@ -1534,7 +1536,7 @@ static int prove_core(const ProveCall& c) {
         for (size_t i = 0; i < K; ++i) {
             Instance& I = inst[i];
             if (k < I.skip) continue;
-            const RoundPlan& plan = plans[i] = plan_round(I.n, I.h, k - I.skip, K, from_ints, I.state, I.by_row);
+            const RoundPlan& plan = plans[i] = plan_round(I.n, I.h, k - I.skip, K, from_ints, I.state);
             // cannot happen: small_source_shape_ok has walked these rounds
             if (plan.s_source == kSNowhere || (from_ints && plan.s_source == kSFromCaller)) return ZK_E_BADARG;
             if (plan.kind == kRoundHost) any_ship = any_ship || plan.starts;
@@ -1755,11 +1757,11 @@ static int prove_core(const ProveCall& c) {
                 }
                 {
                     ProfileScope prof(kProfRound29, stream);
-                    if (plan.fold2 && (ints_round || !in32)) return ZK_E_BADARG;  // cannot happen: see plan_round
+                    // cannot happen, see plan_round (integers are folded with 17 or fewer variables left: passes follow)
+                    if ((plan.fold2 && (ints_round || !in32)) || (ints_round && !out32)) return ZK_E_BADARG;
                     if (plan.fold2 && out32) hipLaunchKernelGGL((k_round_data29<true, true, false, true>), dim3(blocks29), dim3(threads29), 0, stream, d29);
                     else if (plan.fold2) hipLaunchKernelGGL((k_round_data29<true, false, false, true>), dim3(blocks29), dim3(threads29), 0, stream, d29);
-                    else if (ints_round && out32) hipLaunchKernelGGL((k_round_data29<true, true, true>), dim3(blocks29), dim3(threads29), 0, stream, d29);
-                    else if (ints_round) hipLaunchKernelGGL((k_round_data29<true, false, true>), dim3(blocks29), dim3(threads29), 0, stream, d29);
+                    else if (ints_round) hipLaunchKernelGGL((k_round_data29<true, true, true>), dim3(blocks29), dim3(threads29), 0, stream, d29);
                     else if (in32 && out32) hipLaunchKernelGGL((k_round_data29<true, true>), dim3(blocks29), dim3(threads29), 0, stream, d29);
                     else if (in32) hipLaunchKernelGGL((k_round_data29<true, false>), dim3(blocks29), dim3(threads29), 0, stream, d29);
                     else if (out32) hipLaunchKernelGGL((k_round_data29<false, true>), dim3(blocks29), dim3(threads29), 0, stream, d29);
@@ -2430,12 +2432,12 @@ int tlookup_prove_small(const uint8_t seed[32], const int32_t* X, const int32_t*
 
 // The rounds of a proof of this shape, walked on the host (no GPU is touched): four
 // integers per round, see zkmi.h.
-static int selftest_plan(size_t D, size_t N, size_t K, bool from_ints, bool by_row, int32_t* out, size_t cap_rounds) {
+static int selftest_plan(size_t D, size_t N, size_t K, bool from_ints, int32_t* out, size_t cap_rounds) {
     const int n = log2_floor(D), h = n - log2_floor(N);
     if ((size_t)n > cap_rounds) return ZK_E_BUFSZ;
     RoundState st;
     for (int k = 0; k < n; ++k) {
-        const RoundPlan pl = plan_round(n, h, k, K, from_ints, st, by_row);
+        const RoundPlan pl = plan_round(n, h, k, K, from_ints, st);
         const bool several = pl.kind == kRoundGrid || pl.kind == kRoundHost, pair = pl.kind == kRoundPair;
         out[4 * k] = pl.kind;
         out[4 * k + 1] = pl.s_source;
@@ -2451,12 +2453,12 @@ static bool selftest_shape_ok(size_t D, size_t N, size_t K, const int32_t* out) 
 int zkmi_selftest_tlookup_plan(size_t D, size_t N, size_t K, int from_ints, int32_t* out, size_t cap_rounds) {
     if (!selftest_shape_ok(D, N, K, out)) return ZK_E_BADARG;
     if (from_ints && (K != 1 || !small_source_shape_ok(D, N))) return ZK_E_BADARG;
-    return selftest_plan(D, N, K, from_ints != 0, false, out, cap_rounds);
+    return selftest_plan(D, N, K, from_ints != 0, out, cap_rounds);
 }
 
 int zkmi_selftest_tlookup_rows_plan(size_t D, size_t N, size_t K, int32_t* out, size_t cap_rounds) {
-    if (!selftest_shape_ok(D, N, K, out) || !gather_by_default(N) || !rounds_by_row(log2_floor(D), log2_floor(D) - log2_floor(N))) return ZK_E_BADARG;
-    return selftest_plan(D, N, K, false, true, out, cap_rounds);
+    if (!selftest_shape_ok(D, N, K, out) || !rounds_by_row(log2_floor(D), log2_floor(D) - log2_floor(N))) return ZK_E_BADARG;
+    return selftest_plan(D, N, K, false, out, cap_rounds);
 }
 
 // Who makes, compares and hashes what (hash_plan), see zkmi.h.

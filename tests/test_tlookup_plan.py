@@ -4,12 +4,13 @@ relies on: a round never has a source of S the library has no kernel for, intege
 written for them, a round reads the layout the round before it has written (words before every pass and before the
 host's rounds), and every challenge is bound exactly once.  From a vector of field elements the first pass may serve
 the first two rounds (FIRST_TWO, then NO_PASS: nothing launched), after which two variables are bound at once from the
-caller's arrays.  The rounds of the last 16 variables come up to three from one pass (GRID); the last six of a single
+caller's arrays.  Of long tensors with tables of up to 2^16 rows these rounds read the table's rows instead, from vectors
+and from integers alike, and passes over two variables (PAIR) follow.  The rounds of the last 16 variables come up to three from one pass (GRID); the last six of a single
 proof, three of each of several, are the host's (HOST)."""
 import pytest
 
-FIRST, R29, BOTH, FIRST_TWO, NO_PASS, HOST, GRID = 0, 1, 2, 5, 6, 7, 8
-CALLER, INTS, WORDS, PLANES, UNREAD = 0, 1, 2, 3, 4
+FIRST, R29, BOTH, FIRST_TWO, NO_PASS, HOST, GRID, PAIR = 0, 1, 2, 5, 6, 7, 8, 9
+CALLER, INTS, WORDS, PLANES, UNREAD, ROWS = 0, 1, 2, 3, 4, 5
 MAX_LAZY = 8  # folds in a row whose results stay unreduced in 29-bit planes
 
 
@@ -22,7 +23,9 @@ def _check(rounds, n, h, K, from_ints=False):
     """Follows the arrays through the rounds: what layout S and A are in, how many of the last challenges they (and the
     table's arrays) have yet to be bound to."""
     host = 6 if K == 1 else 3
-    layout, pending, pending_t, lazy = INTS if from_ints else CALLER, 0, 0, 0
+    by_row = n >= 19 and n - h <= 16 and h >= 3
+    from_ints = from_ints and not by_row
+    layout, pending, pending_t, lazy = ROWS if by_row else INTS if from_ints else CALLER, 0, 0, 0
     left_in_pass = t_in_pass = 0
     on_host = False
     for k, (kind, src, a, b) in enumerate(rounds):
@@ -53,7 +56,13 @@ def _check(rounds, n, h, K, from_ints=False):
             if pending:
                 layout = WORDS
             pending, pending_t, left_in_pass = vars_, tvars, vars_ - 1
+        elif kind == PAIR:
+            assert by_row and k >= 2 and left > 16 and k + a <= h and 1 <= a <= 2, where
+            assert b == pending + (8 if left - a <= 16 else 0) and pending == 2 and pending_t == 0, where
+            layout = WORDS if b >= 8 else PLANES
+            pending, left_in_pass = a, a - 1
         else:
+            assert not by_row or kind == FIRST_TWO, where
             assert left > 16 or (from_ints and k < 2) or rounds[0][0] == FIRST_TWO and k < 2, where
             if kind == R29:
                 assert not table and a == (layout != PLANES) and (1 << (left - 1)) > 256, where
@@ -98,15 +107,21 @@ def test_plan_of_the_headline_shape_matches_the_bench_model():
     import paper_2404_16109_amd as zk
     for from_ints in (False, True):
         rc, rounds = _plan(zk, 1 << 25, 1 << 16, from_ints=from_ints)
-        assert rc == 25
+        assert rc == 25 and bench.rounds_by_row(1 << 25, 1 << 16)
+        assert rounds[0][:2] == (FIRST_TWO, ROWS) and rounds[1][0] == NO_PASS
+        # rounds 2 to 8 by passes over two variables, from the rows, then from planes, the last over one and into words
+        assert [r[0] for r in rounds[2:9]] == [PAIR, GRID] * 3 + [PAIR]
+        assert [r for r in rounds if r[0] == PAIR] == [(PAIR, ROWS, 2, 2), (PAIR, PLANES, 2, 2), (PAIR, PLANES, 2, 2), (PAIR, PLANES, 1, 10)]
         assert [r[0] for r in rounds[9:]] == [GRID] * 10 + [HOST] * 6
-        # the first 29-bit round arrives as words (or integers), round 8 leaves as words for the pass that follows
-        first29 = 1 if from_ints else 2
-        assert rounds[first29][2] == 1 and rounds[8][3] == 1 and all(r[3] == 0 for r in rounds[first29:8])
-        assert (rounds[0][0], rounds[1][0]) == ((FIRST, R29) if from_ints else (FIRST_TWO, NO_PASS))
         assert rounds[9] == (GRID, WORDS, 1 + 8 * 1, 1) and rounds[10] == (GRID, WORDS, 3 + 8 * 3, 1 + 8 * 1)
         assert rounds[19] == (HOST, WORDS, 0, 3 + 8 * 3)
         _check(rounds, 25, 9, 1, from_ints)
+    # twice as many rows: the 29-bit kernel's rounds
+    rc, rounds = _plan(zk, 1 << 25, 1 << 17)
+    assert rc == 25 and not bench.rounds_by_row(1 << 25, 1 << 17)
+    assert [r[0] for r in rounds[:9]] == [FIRST_TWO, NO_PASS] + [R29] * 6 + [BOTH] and rounds[0][1] == CALLER
+    assert rounds[2][2] == 1 and rounds[7][3] == 1 and all(r[3] == 0 for r in rounds[2:7])
+    _check(rounds, 25, 8, 1)
 
 
 def test_29_bit_rounds_are_those_of_the_bench_model():
@@ -117,7 +132,9 @@ def test_29_bit_rounds_are_those_of_the_bench_model():
             for from_ints in (False, True):
                 rc, rounds = _plan(zk, 1 << n, 1 << l, from_ints=from_ints)
                 if rc == n:
-                    want = bench.rounds_on_29_bits(1 << n, 1 << l, from_ints)
+                    by_row = bench.rounds_by_row(1 << n, 1 << l)
+                    assert by_row == (PAIR in [r[0] for r in rounds])
+                    want = [] if by_row else bench.rounds_on_29_bits(1 << n, 1 << l, from_ints)
                     assert [k for k, r in enumerate(rounds) if r[0] == R29] == want, (n, l, from_ints)
                     assert from_ints or n == 0 or (rounds[0][0] == FIRST_TWO) == bench.first_two_rounds_share_a_pass(1 << n, 1 << l)
 
@@ -130,8 +147,12 @@ def test_where_passes_meet_what_runs_before_them():
     rounds = _plan(zk, 1 << 18, 1 << 3)[1]
     assert [r[0] for r in rounds[:4]] == [FIRST_TWO, NO_PASS, GRID, GRID] and rounds[2] == (GRID, CALLER, 1, 2)
     # after a 29-bit round, which leaves words although another could follow by its length
+    rounds = _plan(zk, 1 << 18, 1 << 3, from_ints=True)[1]
+    assert [r[0] for r in rounds[:3]] == [FIRST, R29, GRID] and rounds[1][2:] == (1, 1)
+    # after a long pass, which may serve a round that a short one could; it leaves words
     rounds = _plan(zk, 1 << 19, 1 << 3)[1]
-    assert [r[0] for r in rounds[:4]] == [FIRST_TWO, NO_PASS, R29, GRID] and rounds[2][2:] == (1, 1)
+    assert [r[0] for r in rounds[:5]] == [FIRST_TWO, NO_PASS, PAIR, GRID, GRID]
+    assert rounds[2] == (PAIR, ROWS, 2, 10) and rounds[4] == (GRID, WORDS, 3, 2)
     # after rounds that bind table variables
     rounds = _plan(zk, 1 << 19, 1 << 18)[1]
     assert [r[0] for r in rounds[:4]] == [FIRST, BOTH, BOTH, GRID] and rounds[3] == (GRID, WORDS, 1 + 8, 1 + 8)
@@ -160,8 +181,9 @@ def test_every_shape_has_something_for_every_round():
                 assert rc == zk.ZK_E_BADARG and not takes_ints
                 continue
             assert takes_ints and N <= 1 << 16 and D >= 4 * N and D > 1024
-            assert rounds[0][:2] == (FIRST, INTS) and rounds[1][:3] == (R29, INTS, 1)
-            assert all(r[1] in (WORDS, PLANES, UNREAD) for r in rounds[2:])
+            if rounds[0][1] != ROWS:
+                assert rounds[0][:2] == (FIRST, INTS) and rounds[1] == (R29, INTS, 1, 1)
+                assert all(r[1] in (WORDS, UNREAD) for r in rounds[2:])
             _check(rounds, n, n - l, 1, True)
 
 
