@@ -1,12 +1,13 @@
-"""The pass that serves the first two rounds (k_round_first_two): workgroups of 256 to 4096 positions, with and without a
-high weight factor, vectors whose planes start anywhere.  Exact arithmetic: equality with the oracle, or with the proof
-from the integers, whose first rounds are other kernels."""
+"""The pass that serves the first two rounds, from vectors (k_round_first_two: tensors of 2^17 and 2^18 entries, tables of
+more than 2^16 rows) and by row (k_first_two_rows): workgroups of 256 to 4096 positions, with and without a high weight
+factor, vectors whose planes start anywhere.  Exact arithmetic: equality with the oracle, or a proof that the verifier accepts
+against the tensor, whose evaluations are kernels of their own; by row also equality with the proof from the integers."""
 import numpy as np
 import pytest
 import torch
 
 from tests.test_gpu_link_long import shifted
-from tests.test_tlookup_plan import FIRST_TWO
+from tests.test_tlookup_plan import CALLER, FIRST_TWO
 
 pytestmark = pytest.mark.gpu
 
@@ -50,6 +51,7 @@ def test_against_the_integers(zk, logD, logN):
     rc, proof, _ = zk.tlookup_prove(seed, S, idx, T)
     rc_i, from_ints, _ = zk.tlookup_prove_small(seed, tx[idx.long()].contiguous(), None, None, idx, T)
     assert rc == 0 and rc_i == 0 and from_ints == proof
+    assert zk.tlookup_verify(seed, proof, T, D, S=S)[0] == 0
 
 
 @pytest.mark.parametrize("logD,value,runs", [(23, 256, "everywhere"), (23, 65536, "everywhere"), (23, 65535, "everywhere"),
@@ -78,3 +80,28 @@ def test_tensors_of_one_value(zk, logD, value, runs):
     rc_i, from_ints, _ = zk.tlookup_prove_small(seed, tx[idx.long()].contiguous(), None, None, idx, T)
     assert rc == 0 and rc_i == 0 and from_ints == proof
     assert zk.tlookup_verify(seed, proof, T, D)[0] == 0
+
+
+@pytest.mark.parametrize("logD,logN,value", [(21, 17, None), (22, 18, None), (23, 17, 256), (23, 17, -256), (23, 17, 65535), (24, 17, 65536)])
+def test_long_tables(zk, logD, logN, value):
+    """The same from vectors: random entries, or runs of one value in all four quarters of a workgroup's places."""
+    N, D = 1 << logN, 1 << logD
+    assert zk.zkmi_selftest_tlookup_plan(D, N, 1, False)[1][0][:2] == (FIRST_TWO, CALLER)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(logD)
+    tx = torch.arange(N, dtype=torch.int32, device="cuda") * 3 - N
+    if value is not None:
+        tx[7] = value
+    T = zk.Vec(N)
+    assert zk.fr_from_i32(T, tx) == 0
+    idx = torch.randint(0, N, (4, D >> 2), generator=g, device="cuda", dtype=torch.int32)
+    if value is not None:
+        idx[:, :(D >> 2) - 4096 * 5] = 7
+    idx = idx.reshape(-1).contiguous()
+    S = zk.Vec(D, stride=D + 3)
+    S.data[:, :D] = T.data.index_select(1, idx.long())
+    seed = bytes([logD, logN, 6, (value or 0) & 0xFF]) * 8
+    rc, proof, _ = zk.tlookup_prove(seed, S, idx, T)
+    assert rc == 0 and zk.tlookup_verify(seed, proof, T, D, S=S)[0] == 0
+    rc, by_rows, _ = zk.tlookup_prove_by_rows(seed, S, idx, T)
+    assert rc == 0 and by_rows == proof

@@ -1,6 +1,6 @@
-"""The kernels that run rounds by themselves while more than 16 variables are left: the 29-bit kernel from the caller's
-words, after the pass that serves two rounds, from planes and from integers, into planes and into words; the rounds that
-bind table variables; and all of these side by side in instances that begin at different rounds.  Which of them a shape
+"""The kernels that run rounds while more than 16 variables are left: the 29-bit kernel from the caller's words, after the
+pass that serves two rounds, from planes and from integers, into planes and into words (of long tensors, with tables of more
+than 2^16 rows); the long passes by row (with shorter tables); the rounds that bind table variables; and all of these side by side in instances that begin at different rounds.  Which of them a shape
 runs is written beside it and checked against the library's own schedule.  Exact arithmetic: equality with the oracle,
 or with the proof from the vector where that has been compared."""
 import random
@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 import torch
 
-from tests.test_tlookup_plan import BOTH, FIRST, FIRST_TWO, GRID, NO_PASS, R29
+from tests.test_tlookup_plan import BOTH, FIRST, FIRST_TWO, GRID, NO_PASS, PAIR, R29, UNREAD
 
 pytestmark = pytest.mark.gpu
 
@@ -31,15 +31,18 @@ def _instance(zk, logD, logN, seed):
 
 
 def _kinds(zk, logD, logN, K=1, from_ints=False):
-    """What runs the rounds before the first pass; of the 29-bit kernel also how the arrays arrive and leave."""
-    rounds = zk.zkmi_selftest_tlookup_plan(1 << logD, 1 << logN, K, from_ints)[1]
+    """What runs the rounds before the first of the last passes; of the 29-bit kernel also how the arrays arrive and leave."""
+    rounds = [r for r in zk.zkmi_selftest_tlookup_plan(1 << logD, 1 << logN, K, from_ints)[1] if r[:2] != (GRID, UNREAD)]
     long = rounds[:[r[0] for r in rounds].index(GRID)]
     return [r[0] if r[0] != R29 else ("words" if r[2] else "planes", "words" if r[3] else "planes") for r in long]
 
 
 @pytest.mark.parametrize("logD,logN,want", [
     (18, 16, [FIRST, ("words", "words")]),
-    (20, 8, [FIRST_TWO, NO_PASS, ("words", "planes"), ("planes", "words")]),
+    (20, 8, [FIRST_TWO, NO_PASS, PAIR]),
+    (20, 17, [FIRST_TWO, NO_PASS, ("words", "words"), BOTH]),
+    (21, 17, [FIRST_TWO, NO_PASS, ("words", "planes"), ("planes", "words"), BOTH]),
+    (22, 17, [FIRST_TWO, NO_PASS, ("words", "planes"), ("planes", "planes"), ("planes", "words"), BOTH]),
     (20, 18, [FIRST, ("words", "words"), BOTH, BOTH]),
     (18, 18, [FIRST, BOTH]),
 ])
@@ -55,10 +58,10 @@ def test_single(zk, orc, logD, logN, want):
 
 
 def test_instances_that_begin_at_different_rounds(zk, orc):
-    shapes = [(20, 6), (19, 4), (18, 16), (17, 16)]
-    assert [_kinds(zk, d, n, K=4) for d, n in shapes] == [
-        [FIRST_TWO, NO_PASS, ("words", "planes"), ("planes", "words")], [FIRST_TWO, NO_PASS, ("words", "words")],
-        [FIRST, ("words", "words")], [FIRST]]
+    shapes = [(20, 6), (19, 4), (18, 16), (17, 16), (20, 17)]
+    assert [_kinds(zk, d, n, K=5) for d, n in shapes] == [
+        [FIRST_TWO, NO_PASS, PAIR], [FIRST_TWO, NO_PASS, PAIR], [FIRST, ("words", "words")], [FIRST],
+        [FIRST_TWO, NO_PASS, ("words", "words"), BOTH]]
     made = [_instance(zk, d, n, 7 * d + n) for d, n in shapes]
     seed = random.Random(5).randbytes(32)
     rc, want, _ = orc.tlookup_multi_prove(seed, [m[0] for m in made], [m[1] for m in made])
@@ -68,8 +71,8 @@ def test_instances_that_begin_at_different_rounds(zk, orc):
 
 @pytest.mark.parametrize("logD,logN,want", [
     (18, 10, [FIRST, ("words", "words")]),
-    (20, 10, [FIRST, ("words", "planes"), ("planes", "planes"), ("planes", "words")]),
-    (20, 16, [FIRST, ("words", "planes"), ("planes", "planes"), ("planes", "words")]),
+    (20, 10, [FIRST_TWO, NO_PASS, PAIR]),
+    (20, 16, [FIRST_TWO, NO_PASS, PAIR]),
 ])
 def test_from_integers(zk, logD, logN, want):
     assert _kinds(zk, logD, logN, from_ints=True) == want
