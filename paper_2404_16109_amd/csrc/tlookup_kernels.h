@@ -918,17 +918,21 @@ static __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
 // a block costs the rounds' 900 instructions.  A workgroup is two such pairs, one
 // wavefront per SIMD: two workgroups of one pair each were seen to share two SIMDs and
 // leave two idle.  Measured at 2^20 elements (8192 leaves): 220 -> 140 us.  Above
-// kPipedLeafGroups the wavefronts share SIMDs.  Where the words come ready one lane per leaf is
-// then faster (kLeafRowsHash, a tensor of 2^22 with its table, 520 groups: 184 us, in pairs 220;
-// at 2056 groups 484 and 521), but for the places just above a wavefront per SIMD (1025 groups:
-// 364 and 323); where every element is converted first, whose long chain one wavefront per SIMD
-// waits out, the pairs are still ahead at 1032 (520 groups without rows: 408 us, in pairs 235).
-// Beyond 1040 groups, whole verifications by lane and in pairs, when nothing shared their launch: 2^24 entries 1.05
-// and 1.02 ms, 2^25 1.70 and 1.70.
+// kPipedLeafGroups the wavefronts share SIMDs.  Where every element is converted first, whose long
+// chain one wavefront per SIMD waits out, the pairs are still ahead at 1032 groups (520 groups without
+// rows: 408 us, in pairs 235).  Beyond 1040, whole verifications by lane and in pairs, when nothing shared
+// their launch: 2^24 entries 1.05 and 1.02 ms, 2^25 1.70 and 1.70.
+//
+// Where the words come ready (kLeafRowsHash), one tensor's leaves or several's, us by lane and in pairs:
+//   513 to 675 groups 178 to 181 and 200 to 204; 770 to 997 by lane 182 to 188 or, in most runs, 316 to 341
+//   (wavefronts meet on SIMDs while others idle), in pairs 203 to 209; 1025 to 1476 323 to 332 and 294 to 311;
+//   1538 326 and 387, 1667 325 and 404 (three workgroups of pairs per compute unit are 1536 groups); 2050
+//   473 and 469, 2563 478 and 551, 3074 636 and 637.
 static const uint32_t kPipedLeafGroups = 512, kPipedLeafGroupsConverting = 1040;
+static const uint32_t kPipedLeafGroupsHashFrom = 768, kPipedLeafGroupsHash = 1536;
 template <int MODE>
 static bool leaves_in_pairs(uint32_t groups) {
-    if (MODE == kLeafRowsHash && groups > 1024) return groups <= kPipedLeafGroupsConverting;
+    if (MODE == kLeafRowsHash && groups > kPipedLeafGroupsHashFrom) return groups <= kPipedLeafGroupsHash;
     return groups <= (MODE == kLeafPlain ? kPipedLeafGroupsConverting : kPipedLeafGroups);
 }
 

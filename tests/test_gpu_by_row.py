@@ -110,3 +110,31 @@ def test_the_first_instance_at_fault_is_reported(zk):
             bad.append(v)
         rc, _, info = zk.tlookup_prove_multi(b"\x07" * 32, bad, idx, T)
         assert rc == zk.ZK_E_NOT_IN_TABLE and (info["bad_instance"], info["bad_index"]) == (at_fault[0], 77 + at_fault[0])
+
+
+# groups of 64 leaves: 675 (a lane per leaf), 803, 1154, 1476 (pairs of wavefronts), 1538 (a lane)
+@pytest.mark.parametrize("logs", [(22, 20, 18), (22, 21, 18), (23, 20), (23, 21, 20, 19), (23, 22)], ids=str)
+def test_digests_of_several_tensors(zk, logs):
+    """The digests of A and B, made from rows by either kernel, are those of the vectors that a verification hashes."""
+    N = 1 << 10
+    g = torch.Generator(device="cuda")
+    g.manual_seed(sum(logs))
+    T = zk.Vec(N)
+    assert zk.fr_from_i32(T, torch.arange(N, dtype=torch.int32, device="cuda") * 5 - N) == 0
+    idx = [torch.randint(0, N, (1 << n,), generator=g, device="cuda", dtype=torch.int32) for n in logs]
+    S = [zk.Vec(1 << n) for n in logs]
+    for s, i in zip(S, idx):
+        s.data[:, :s.n] = T.data[:, :N].index_select(1, i.long())
+    rc, proof, info = zk.tlookup_prove_multi(b"\x09" * 32, S, idx, [T] * len(S))
+    assert rc == 0
+
+    def inverses(v):
+        plus, out = zk.Vec(v.n), zk.Vec(v.n)
+        assert zk.fr_add_scalar(plus, v, info["beta"]) == 0 and zk.fr_batch_inverse(out, plus) == 0
+        return out
+
+    A, B = [inverses(s) for s in S], [inverses(T)] * len(S)
+    check = lambda: zk.tlookup_verify_multi(b"\x09" * 32, proof, [T] * len(S), [s.n for s in S], S=S, A=A, B=B)[0]
+    assert check() == 0
+    A[-1].data[2, A[-1].n - 1] ^= 1
+    assert check() == zk.ZK_E_REJECT
