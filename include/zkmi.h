@@ -18,7 +18,7 @@
  * entry point allocates device memory; `*_workspace_bytes` says how much
  * workspace a call needs.  The library does keep a little state of its own PER
  * HOST THREAD, allocated by that thread's first call that needs it and kept until
- * the process ends: 175 KiB of pinned host memory into which kernels write the
+ * the process ends: 142 KiB of pinned host memory into which kernels write the
  * handful of sums a step returns (and, towards the end of a proof, the arrays of at
  * most 64 elements each from which the host finishes the rounds), 64 bytes of
  * coherent pinned memory through which a kernel that stays resident over a sumcheck
@@ -218,16 +218,18 @@ int tlookup_multiplicities(uint32_t* m, fr_vec S, const uint32_t* idx, fr_vec T,
  * S not in T is ZK_E_NOT_IN_TABLE with aux->bad_index the smallest such i, as in
  * tlookup_multiplicities.  With idx given (and D > 256, N <= 2^16) the prover does
  * not compare every S_i with T[idx_i] while counting: it counts from idx alone and
- * compares while it hashes A, of which it knows by then that A_i = 1/(beta+S_i) is
+ * compares where it makes A, of which it knows by then that A_i = 1/(beta+S_i) is
  * the table-side inverse B[idx_i] if S_i is that row (for N <= 2^16 only the N table
- * entries are inverted, with or without hints).  The check is exact either way. */
+ * entries are inverted, with or without hints), or, of tensors of 2^19 entries and
+ * more whose A is only hashed, in the pass over S that serves the first two rounds
+ * (zkmi_selftest_tlookup_hashes says which).  The check is exact either way. */
 size_t tlookup_proof_bytes(size_t D);
 int tlookup_prove(const uint8_t seed[32], fr_vec S, const uint32_t* idx, fr_vec T, uint8_t* proof, size_t cap,
                   size_t* len, tlookup_aux* aux, void* ws, size_t ws_bytes, void* stream);
 
 /* tlookup_prove with every S_i compared with its hinted row T[idx_i] before
  * anything else is done (while counting), as tlookup_multiplicities does, instead
- * of while A is hashed: the same proof, byte for byte, for callers who want a wrong
+ * of later: the same proof, byte for byte, for callers who want a wrong
  * hint reported before any challenge is drawn.  Costs one more pass over S (36
  * instead of 4 bytes per element while counting); timed beside the headline by the
  * benchmark.  Without idx it is tlookup_prove. */
@@ -243,7 +245,9 @@ int tlookup_prove_checked(const uint8_t seed[32], fr_vec S, const uint32_t* idx,
  * byte for byte; S is never written out: the comparison with the hinted rows and the
  * first round read eight bytes per entry instead of thirty-two and build S_i from them
  * (two 32x256-bit products and a two-step reduction), the first fold takes the four
- * integers of an entry pair straight to a reduced field element.  Row hints idx
+ * integers of an entry pair straight to a reduced field element (of tensors of 2^19
+ * entries and more, at least eight times the table, the pass that serves the first two
+ * rounds compares, and what is folded are the table's rows).  Row hints idx
  * are required (for a range check idx_i = X_i - min T).  Shapes with N > 2^16,
  * D < 4 N or D <= 1024 have no such path: S is written out first, into D * 32
  * further bytes of workspace (tlookup_small_workspace_bytes accounts for them).
@@ -525,11 +529,13 @@ int zkmi_selftest_staging(uint64_t* address, uint64_t* bytes);
  * on the caller's stream (so that kernels are timed where they are launched).
  * State is per host thread.  Phases: "total" (a whole tlookup_prove call),
  * "count" (multiplicities and digest leaves), "inverse" (the batch inversions),
- * "digest" (the hash trees over A and B; A is made there), "round_small" (the kernels
- * of the rounds that are bound by latency: those that also bind a table variable and
- * the passes that serve several rounds),
- * "round_data29" (the large folding rounds, which run on 29-bit limbs: one
- * record per launch of that kernel), "round_data" (the first round's kernel),
+ * "digest" (the hash trees over A and B, and what makes A where it is made from the
+ * table's rows), "round_small" (the kernels of the rounds that are bound by latency: those
+ * that also bind a table variable and the passes over the last variables),
+ * "round_data29" (the large folding rounds: one record per launch of the kernel that reads
+ * the table's rows, or what it has left of them, and serves two rounds or, where the rounds
+ * do not go by row, of the one that runs on 29-bit limbs), "round_data" (the first
+ * round's kernel, or that of the first two; by row it also compares S with its rows),
  * "round_table" (the table-side round kernel alone, which only runs when D = N).
  * A phase that waits for the host in its middle (count, inverse, digest) is
  * timed from its first launch to its last, the wait included.

@@ -142,6 +142,7 @@ static const size_t kMailboxGrid = kMailboxShip + kMailboxMaxInstances * kMailbo
 static const size_t kMailboxTableShares = 128;
 static const size_t kMailboxTableSums = kMailboxGrid + kMailboxMaxInstances * 89 * 8;
 static const size_t kMailboxWords = kMailboxTableSums + kMailboxMaxInstances * kMailboxTableShares * 8;
+static_assert(kMailboxWords * sizeof(uint32_t) / 1024 == 142, "the figure that the public header states");
 static const size_t kMailboxInvB = 1024;    // grand total of the table-side inversion (+16 per instance)
 static const size_t kMailboxInvA = 1032;    // grand total of the data-side inversion (+16 per instance)
 static const size_t kMailboxTableC = 1280;  // that sum of longer tables (+8 per instance)

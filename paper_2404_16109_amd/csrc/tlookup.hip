@@ -401,7 +401,7 @@ static int carve_prove(ProveWs& w, Carver& cv, size_t D, size_t N) {
     w.S29 = (uint4*)cv.take((D / 2 ? D / 2 : 1) * 36);
     w.Bf = cv.limbs(N / 2 ? N / 2 : 1);
     w.Tf = cv.limbs(N / 2 ? N / 2 : 1);
-    // B's rows are read by the hash of A only, before anything is folded: they lie where the folded arrays will be (Sf to
+    // B's rows are read by what makes and hashes A only, before anything is folded: they lie where the folded arrays will be (Sf to
     // Tf, one after the other: 52 D + 32 N bytes, and N <= D)
     w.rows_b = (uint4*)w.Sf;
     w.B = cv.limbs(N);
@@ -729,9 +729,9 @@ static size_t pair_span(size_t P) {
 // actually handed to a kernel before it is launched.
 enum RoundKind {
     kRoundFirst = 0,     // k_round_data0: the first round, nothing to fold
-    kRound29 = 1,        // k_round_data29: large folding rounds on 29-bit limbs
+    kRound29 = 1,        // k_round_data29: large folding rounds on 29-bit limbs (where the rounds do not go by row)
     kRoundBoth = 2,      // k_round_both: data and table side, the table's variables being bound
-    kRoundFirstTwo = 5,  // k_round_first_two: the first pass, which yields the sums of the first two rounds
+    kRoundFirstTwo = 5,  // k_round_first_two or, by row, k_first_two_rows: yields the sums of the first two rounds
     kRoundNoPass = 6,    // the second round after kRoundFirstTwo: the host has everything, nothing is launched
     kRoundHost = 7,      // the host's (HostTail); the first of them fetches the arrays
     kRoundGrid = 8,      // its sums come from the grid of a pass over several variables; the first of them runs the pass
@@ -741,7 +741,7 @@ enum SSource {
     kSFromCaller = 0,  // the caller's vector of field elements
     kSFromInts = 1,    // the caller's integer columns (tlookup_prove_small)
     kSFromWords = 2,   // the folded copy in the workspace, 32-bit words
-    kSFromPlanes = 3,  // the folded copy in the workspace, 29-bit limb planes
+    kSFromPlanes = 3,  // the folded copy in the workspace, planes of 29-bit limbs (kRound29) or of digits (kRoundPair)
     kSUnread = 4,      // the round reads no array
     kSFromRows = 5,    // the rows of the table (tlookup_rows.h)
     kSNowhere = -1     // a plan this library has no kernel for: never launched

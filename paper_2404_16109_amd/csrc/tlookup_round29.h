@@ -265,8 +265,9 @@ struct DataRound01Args {
 // 29-bit products).  On the vector ALU remain four multiplications per quad and A's sums,
 // some 1250 instructions (on the vector ALU alone the pass took 2300 and two
 // wavefronts per SIMD kept it 70 % busy); entries are asked for four ahead of their use.
-// Issue and HBM bind about equally: 2^25 entries 760 -> 520 us, 4.1 TB/s; a proof of 2^20
-// entries in all 731 -> 709 us, one of 2^17 524 -> 500.
+// Issue and HBM bind about equally: 2^25 entries 760 -> 520 us, 4.1 TB/s; a proof of 2^17
+// entries in all 524 -> 500 us.  (Tensors of 2^19 entries and more with tables of up to 2^16
+// rows take k_first_two_rows.)
 struct FirstTwoValues {
     uint32_t vals[9][8];  // M_x0, M_x1, M_0x, M_1x, M_xx, W_00, W_01, W_10, W_11
     uint32_t sums_a[4][4][9];
