@@ -12,8 +12,9 @@ The work model behind `value` is fixed (it does not follow the
 implementation): 10 field multiplications per element of S and per table row
 (3 for the batched inversion, 5 to evaluate a round's sums per pair and 2 to
 fold it, pairs summing to D over all rounds).  The prover inverts the N table
-entries only and reads A off them by row; `fr_mul_executed_model` counts without
-the three multiplications per element that this saves.
+entries only, and its long rounds read the table's rows, with folds and sums on the
+matrix cores; `fr_mul_executed_model` counts the multiplications that are left to
+the vector ALU.
 """
 import argparse
 import json
@@ -29,6 +30,7 @@ MADS_PER_FR_MUL = 112                   # 64 for the 8x8-limb product + 48 for t
 ROUND_DATA_FR_MUL_PER_PAIR_EVAL = 5     # two to weight A0, A1, three products
 ROUND_DATA_FR_MUL_PER_PAIR_FOLD = 4     # two arrays, two folded entries per pair
 PEAK_HBM_BYTES_PER_S = 8e12             # MI355X HBM3E, published
+PEAK_INT8_OPS_PER_S = 5e15              # dense, published: multiply and add counted apart
 WHOLE_PROVE_BYTES_PER_ELEMENT = 292     # hints 4 + inversion 96 + 192 (every version of A and S counted once, when a round reads it)
 
 
@@ -37,7 +39,16 @@ def fr_mul_model(D, N):
 
 
 def fr_mul_executed_model(D, N):
-    return 7 * D + 10 * N
+    """Multiplications on the vector ALU.  By row: one per element of S in the first pass, which weights A, and those of
+    k_round_pair; otherwise the fixed model's, without the inversion of A where it is read off B by row."""
+    if rounds_by_row(D, N):
+        return D + PAIR_FR_MUL_PER_POSITION * pair_positions(D, N) + 10 * N
+    return (7 if a_by_row(N) else 10) * D + 10 * N
+
+
+def a_by_row(N):
+    """A is B by row, and S is compared with the hinted rows beside it: the tables whose rows the caches hold."""
+    return N <= 1 << 16
 
 
 PASS_VARS = 16  # the rounds of the last 16 variables come several from one pass (csrc/grid_dev.h)
@@ -45,13 +56,13 @@ PASS_VARS = 16  # the rounds of the last 16 variables come several from one pass
 
 def first_two_rounds_share_a_pass(D, N):
     """From a vector of field elements the first pass over A and S yields the sums of the first two rounds and folds
-    nothing; what comes next (of the headline: round 2 in k_round_data29) binds two variables at once."""
+    nothing; what comes next (k_round_pair by row, otherwise round 2 in k_round_data29) binds two variables at once."""
     n, h = D.bit_length() - 1, (D // N).bit_length() - 1
     return n > PASS_VARS and h >= 3 and (D >> 3) > 256
 
 
 def rounds_on_29_bits(D, N, from_ints=False):
-    """The rounds the dominant kernel (k_round_data29) runs: after the first (after the first two, when those share
+    """The rounds that k_round_data29 runs where they do not go by row: after the first (after the first two, when those share
     a pass), before the table's variables and before the rounds that come from passes; from integers it runs the second
     round whatever the length, if more than 256 pairs remain."""
     n, h = D.bit_length() - 1, (D // N).bit_length() - 1
@@ -60,7 +71,7 @@ def rounds_on_29_bits(D, N, from_ints=False):
 
 
 def round29_work(D, N):
-    """(pairs, algorithmic field multiplications, algorithmic bytes) of all launches of k_round_data29 in one prove.
+    """Where the rounds do not go by row: (pairs, algorithmic field multiplications, algorithmic bytes) of all launches of k_round_data29 in one prove.
     Per pair a round folds four entries of A and four of S into two of each (4 multiplications, 12 entries of 32 B
     moved), weights two entries and forms three products: 9 multiplications.  The round that binds two variables at
     once folds sixteen entries into four (12 multiplications, 20 entries moved): 17."""
@@ -81,13 +92,28 @@ def rounds_by_row(D, N):
     return first_two_rounds_share_a_pass(D, N) and n - 2 > PASS_VARS and N <= 1 << PASS_VARS
 
 
+# Of a position of k_round_pair (sixteen entries of A and of S that bind to four each): the four entries of A weighted on
+# the vector ALU; on the matrix cores eight outputs of four constants and sixteen products, 32 x 32 bytes each.
+PAIR_FR_MUL_PER_POSITION = 4
+PAIR_INT8_OPS_PER_POSITION = 2 * (8 * 4 + 16) * 32 * 32
+
+
+def pair_launches(D, N):
+    """The first rounds of the long passes over two variables."""
+    n, h = D.bit_length() - 1, (D // N).bit_length() - 1
+    return range(2, min(h, n - PASS_VARS), 2)
+
+
+def pair_positions(D, N):
+    return sum(D >> (k + 2) for k in pair_launches(D, N))
+
+
 def pair_bytes(D, N):
     """Bytes that all launches of k_round_pair in one prove cannot avoid: row numbers read, A and S bound by two variables
     written by the first (the table's rows are in the caches); both read at their length and written at a quarter of it
     by the others."""
-    n, h = D.bit_length() - 1, (D // N).bit_length() - 1
     moved, left = 4 * D + 64 * D // 4, D // 4
-    for _ in range(4, min(h, n - PASS_VARS), 2):
+    for _ in pair_launches(D, N)[1:]:
         moved, left = moved + 64 * (left + left // 4), left // 4
     return moved
 
@@ -532,20 +558,25 @@ def main():
     rd = phases["round_data29"]
     launches = rd["records"] / psteps
     avg_launch_s = rd["ms_per_step"] * 1e-3 / max(launches, 1)
-    pairs29, muls29, moved29 = round29_work(D, N)
+    _, muls29, moved29 = round29_work(D, N)
     by_row = rounds_by_row(D, N)
+    int8_ops = 0  # on the matrix cores
     if by_row:
-        moved29 = pair_bytes(D, N)
+        muls29, moved29 = PAIR_FR_MUL_PER_POSITION * pair_positions(D, N), pair_bytes(D, N)
+        int8_ops = PAIR_INT8_OPS_PER_POSITION * pair_positions(D, N)
     mads_per_launch = muls29 * MADS_PER_FR_MUL / max(launches, 1)
     bytes_per_launch = moved29 / max(launches, 1)
     alu = mads_per_launch / avg_launch_s if avg_launch_s > 0 else 0.0
     hbm = bytes_per_launch / avg_launch_s if avg_launch_s > 0 else 0.0
-    traffic = measured_traffic()
+    matrix = int8_ops / max(launches, 1) / avg_launch_s if avg_launch_s > 0 else 0.0
+    shares = {"hbm": hbm / PEAK_HBM_BYTES_PER_S, "alu": alu / PEAK_MAD_PER_S, "matrix cores": matrix / PEAK_INT8_OPS_PER_S}
+    measured_here = (D, N) == (1 << 25, 1 << 16)  # the shape of the committed counter summary
+    traffic = measured_traffic() if measured_here else None
     # the whole prove against both roofs: 112 multiply-adds per multiplication that is made, and the bytes that must
-    # move: by row those of the phases below, otherwise the fixed model's 292 per element of S less the prefix products
-    # of an inversion that is not made (hints; S read and A written; every round's arrays read once and written at half size)
+    # move: by row those of the phases below, otherwise the fixed model's 292 per element of S (hints; inversion; every
+    # round's arrays read once and written at half size), less the prefix products where the inversion of A is not made
     whole_mads = fr_mul_executed_model(D, N) * MADS_PER_FR_MUL
-    whole_bytes = 4 * D + 64 * N + 40 * D + moved29 if by_row else (WHOLE_PROVE_BYTES_PER_ELEMENT - 32) * D
+    whole_bytes = 4 * D + 64 * N + 40 * D + moved29 if by_row else (WHOLE_PROVE_BYTES_PER_ELEMENT - (32 if a_by_row(N) else 0)) * D
     kernels_ms = sum(phases[k]["ms_per_step"] for k in names if k != "total")
     total_ms = phases["total"]["ms_per_step"]
     whole = {
@@ -553,20 +584,22 @@ def main():
         "hbm_frac": whole_bytes / (ms * 1e-3) / PEAK_HBM_BYTES_PER_S,
         "fr_mul_per_s": fr_mul_model(D, N) / (ms * 1e-3),
         "hbm_GBps_algorithmic": whole_bytes / (ms * 1e-3) / 1e9,
-        "hbm_bytes_measured": measured_whole_prove_traffic(),
+        "hbm_bytes_measured": measured_whole_prove_traffic() if measured_here else None,
         # the share of a prove in which neither roof is touched: the device idle between dependent launches (waiting
         # for the transcript on the host) plus the kernels of the rounds that are bound by latency
         "latency_share": (max(total_ms - kernels_ms, 0.0) + phases["round_small"]["ms_per_step"]) / total_ms if total_ms else None,
     }
     if whole["hbm_bytes_measured"]:
         whole["hbm_frac_measured"] = whole["hbm_bytes_measured"] / (ms * 1e-3) / PEAK_HBM_BYTES_PER_S
-    # every phase of the prove against the HBM roof, by the bytes it cannot avoid (per element of S: the hints read
+    # every phase of the prove against the HBM roof, by the bytes it cannot avoid.  Per element of S the hints read
     # once while counting, once by the hash and once with S by the pass that serves the first two rounds and compares them,
-    # or, of longer tables, once with S while A is made, hashed and written, and A and S by that pass; the inversion is
-    # the table's)
-    phase_bytes = {"count": 4 * D, "inverse": 64 * N, "digest": (4 if by_row else 68) * D,
+    # the inversion being the table's; of shorter tensors once more with S where A is made and written, and A and S by that
+    # pass; of longer tables the hints with S while counting, A inverted (S and prefix products read, A written), hashed
+    # and read by that pass
+    phase_bytes = {"count": (4 if a_by_row(N) else 36) * D, "inverse": 64 * N + (0 if a_by_row(N) else 96 * D),
+                   "digest": (4 if by_row else 72 if a_by_row(N) else 32) * D,
                    "round_data": (36 if by_row else 64) * D, "round_data29": moved29}
-    phase_bound = {"count": "LDS atomics", "inverse": "latency", "digest": "alu (SHA-256 instruction issue)",
+    phase_bound = {"count": "LDS atomics" if a_by_row(N) else "memory latency", "inverse": "latency" if a_by_row(N) else "alu and hbm", "digest": "alu (SHA-256 instruction issue)",
                    "round_data": "alu (two wavefronts per SIMD)" + (" and row loads" if by_row else ""), "round_data29": "issue and hbm" if by_row else "hbm and alu, balanced"}
     whole["phases"] = {
         k: {"ms": round(phases[k]["ms_per_step"], 4), "algorithmic_bytes": b, "bound": phase_bound[k],
@@ -582,20 +615,24 @@ def main():
         "config": {"workload": "config 3: tlookup SwiGLU/activation pair table at 7B-FFN shape, "
                                "%d x %d activations padded to D=2^%d, N=2^%d" % (rows, cols, args.logD, args.logN),
                    "path": "tlookup_prove with row hints (idx given: counts from the hints, A read off the inverted table by row, "
-                           "every S compared with its row in the same pass); the variants beside it prove the same bytes",
+                           "every S compared with its row by the pass that serves the first two rounds or, of longer tables, "
+                           "while counting); the variants beside it prove the same bytes",
                    "D": D, "N": N, "proof_bytes": len(proof), "fr_mul_model": fr_mul_model(D, N),
                    "fr_mul_executed_model": fr_mul_executed_model(D, N)},
         "phases_ms": {k: round(v["ms_per_step"], 4) for k, v in phases.items()},
         "commitment_standin_ms": round(phases["digest"]["ms_per_step"], 4),
-        # k_round_pair's folds and sums are on the matrix cores: its multiplications are no load of the vector ALU
-        "roofline": {"bound": "hbm" if by_row or hbm / PEAK_HBM_BYTES_PER_S >= alu / PEAK_MAD_PER_S else "alu",
+        # (the vector ALU's share counts multiplications only: digits, carries and reductions come on top)
+        "roofline": {"bound": max(shares, key=shares.get),
                      "kernel": "%s (the large folding rounds, %d launches per prove)" % ("k_round_pair" if by_row else "k_round_data29", launches),
                      "achieved": hbm / 1e9, "peak": PEAK_HBM_BYTES_PER_S / 1e9, "unit": "GB/s",
                      "frac": hbm / PEAK_HBM_BYTES_PER_S, "traffic": traffic,
                      "launches_per_step": launches, "avg_launch_ms": avg_launch_s * 1e3,
                      "algorithmic_bytes_per_launch": bytes_per_launch,
-                     "alu": {"achieved": alu / 1e12, "peak": PEAK_MAD_PER_S / 1e12, "unit": "T int32-mad/s",
-                             "frac": alu / PEAK_MAD_PER_S, "fr_mul_per_pair_model": 9, "fr_mul_per_pair_executed": 8},
+                     "alu": {"achieved": alu / 1e12, "peak": PEAK_MAD_PER_S / 1e12, "unit": "T int32-mad/s", "frac": shares["alu"],
+                             **({"fr_mul_per_position": PAIR_FR_MUL_PER_POSITION} if by_row else
+                                {"fr_mul_per_pair_model": 9, "fr_mul_per_pair_executed": 8})},
+                     "matrix_cores": {"achieved": matrix / 1e12, "peak": PEAK_INT8_OPS_PER_S / 1e12, "unit": "T int8-op/s",
+                                      "frac": shares["matrix cores"]},
                      "whole_prove": whole},
     }
     out.update(beside)
